@@ -124,7 +124,8 @@ int check_options(const lbfgsb_options* o) {
     return LBFGSB_OK;
 }
 
-Geometry make_geometry(const Dims& dm, const void* A) {
+// fused_unaligned: the single-read pass may also take rows that do not start on 16-byte boundaries
+Geometry make_geometry(const Dims& dm, const void* A, bool fused_unaligned = true) {
     Geometry ge{};
     const int per16 = dm.dtype == LBFGSB_F32 ? 4 : 2;
     const bool aligned = ((uintptr_t)A % 16 == 0) && (dm.cols % per16 == 0) && (dm.ld % per16 == 0);
@@ -140,7 +141,8 @@ Geometry make_geometry(const Dims& dm, const void* A) {
     if (rb < 1) rb = 1;
     ge.gemvt_rows_per_block = (dm.rows + rb - 1) / rb;
     ge.gemvt_row_blocks = (int)((dm.rows + ge.gemvt_rows_per_block - 1) / ge.gemvt_rows_per_block);
-    ge.fused_ok = !is_transport(dm.kind) && fused_shape_ok(dm, A, &ge.fused_variant, &ge.fused_blocks) ? 1 : 0;
+    ge.fused_ok = !is_transport(dm.kind) && (aligned || fused_unaligned) &&
+                  fused_shape_ok(dm, &ge.fused_variant, &ge.fused_blocks) ? 1 : 0;
     ge.gram_blocks = gram_blocks_for(dm.n, dm.m);
     int64_t db = (dm.n + kBlock - 1) / kBlock;
     ge.dir_blocks = (int)(db > kDirBlocksMax ? kDirBlocksMax : db);
@@ -398,7 +400,15 @@ void enqueue_step(lbfgsb_solver* s) {
         // (transposed) pass over X run, otherwise that launch returns at once.  The transposed pass is not
         // among the timed launches: it reads A only in the iterations that backtrack.
         a.mode = kRowLogiSpec;
-        const bool full = s->logi_full_left > 0 || !s->short_ok;
+        // (Steps recorded into a graph are not seen by the bookkeeping that redoes parked ones.  Rows on 16-byte
+        // boundaries have always been recorded with the short sequence, see lbfgsb_get_x; other rows are recorded with
+        // the sequence that finishes every iteration on the device.)
+        bool recording = false;
+        if (s->ge.vec == 1) {
+            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+            recording = hipStreamIsCapturing(s->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusActive;
+        }
+        const bool full = s->logi_full_left > 0 || !s->short_ok || recording;
         a.ls_first = full ? 0 : 1;
         { TimedSlot ts(s); launch_fused(s->dm, s->ge, s->bf, a, s->stream, ts.e0, ts.e1); }
         if (full) {
@@ -497,12 +507,12 @@ int check_create_args(int64_t n, int m, const double* l, const double* u, const 
 // Fills the host object for a checked problem: launch geometry, kernel preparation, and the device arrays carved
 // out of `workspace`.  Allocates nothing and touches no device memory; *total receives the bytes of workspace in use.
 int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj, const lbfgsb_options& o,
-                 void* workspace, size_t workspace_bytes, hipStream_t stream, size_t* total) {
+                 void* workspace, size_t workspace_bytes, hipStream_t stream, size_t* total, bool fused_unaligned = true) {
     s->dm = make_dims(n, m, obj);
     s->options = o;
     s->op = Opts{o.eps, o.armijo_c1, o.backtrack, o.tol, o.max_backtracks, o.tol_relative, o.max_iter, 0, 0.0, 0.0};
     s->obj = *obj;
-    s->ge = make_geometry(s->dm, obj->A);
+    s->ge = make_geometry(s->dm, obj->A, fused_unaligned);
     s->stream = stream;
     s->h_scal = nullptr;
     s->owns_h_scal = false;
@@ -518,7 +528,8 @@ int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj
     *total = L.total;
     if (workspace_bytes < L.total)
         return fail(LBFGSB_E_INVALID_ARG, "workspace too small: %zu < %zu bytes", workspace_bytes, L.total);
-    if (o.a_pass == LBFGSB_APASS_FUSED && !s->ge.fused_ok)
+    // (asked for by name the fused pass takes rows on 16-byte boundaries only, as documented; AUTO uses it for any)
+    if (o.a_pass == LBFGSB_APASS_FUSED && (!s->ge.fused_ok || s->ge.vec == 1))
         return fail(LBFGSB_E_UNSUPPORTED, "the fused A pass does not support this shape");
     {
         const hipError_t ge_ = gram_prepare(n, m);
@@ -808,7 +819,15 @@ int lbfgsb_solve_static(int64_t n, int m, const double* l, const double* u, cons
     lbfgsb_options o;
     rc = check_create_args(n, m, l, u, obj, opt, sl->ptr, &o);
     if (rc) return rc;
-    const size_t need = lbfgsb_workspace_bytes(n, m, obj, &o);
+    size_t need = lbfgsb_workspace_bytes(n, m, obj, &o);
+    bool fused_unaligned = true;
+    if (need > (size_t)LBFGSB_STATIC_SCRATCH_BYTES) {
+        // the partial columns of the single-read pass take the most room: unaligned rows that fit the array only with
+        // the two-pass kernels run on those
+        const Dims dm = make_dims(n, m, obj);
+        const size_t without = make_layout(dm, make_geometry(dm, obj->A, false)).total;
+        if (without < need) { need = without; fused_unaligned = false; }
+    }
     if (need == 0 || need > (size_t)LBFGSB_STATIC_SCRATCH_BYTES)
         return fail(LBFGSB_E_INVALID_ARG,
                     "this problem needs %zu bytes of workspace, lbfgsb_solve_static holds %zu: use lbfgsb_create with a "
@@ -816,7 +835,7 @@ int lbfgsb_solve_static(int64_t n, int m, const double* l, const double* u, cons
     lbfgsb_solver* s = &sl->solver;
     if (s->timing || !s->ev0.empty()) return fail(LBFGSB_E_INVALID_ARG, "the static solver object is in an unexpected state");
     size_t total = 0;
-    rc = setup_solver(s, n, m, obj, o, sl->ptr, (size_t)LBFGSB_STATIC_SCRATCH_BYTES, (hipStream_t)hip_stream, &total);
+    rc = setup_solver(s, n, m, obj, o, sl->ptr, (size_t)LBFGSB_STATIC_SCRATCH_BYTES, (hipStream_t)hip_stream, &total, fused_unaligned);
     if (rc) return rc;
     s->h_scal = &sl->h_scal;
     rc = check_box_chunked(s, l, u, x);

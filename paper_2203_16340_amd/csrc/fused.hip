@@ -15,39 +15,43 @@ namespace lb {
 
 namespace {
 
+typedef void (*LaunchFn)(const Dims&, int64_t, int, size_t, const Buffers&, const APassArgs&, hipStream_t, hipEvent_t, hipEvent_t);
+
 struct Variant {
     int dtype;          // LBFGSB_F64 / LBFGSB_F32
     int logistic;       // 1: the kernel instantiated for the logistic row operations, 0: for the quadratic ones
     int trans;          // 1: with the transposed accumulation, 0: row products only (quadratic form, symmetric matrix)
     int nt, kc, r;      // threads, 16-byte chunks per thread and row, rows per stage
     int wgs_per_cu;     // workgroups per compute unit the launch is sized for
-    const void* kernel; // for hipFuncSetAttribute
-    void (*launch)(const Dims&, int64_t, int, size_t, const Buffers&, const APassArgs&, hipStream_t, hipEvent_t, hipEvent_t);
+    // [0] rows on 16-byte boundaries and whole chunks, [1] rows that start on any element, any number of columns
+    const void* kernel[2]; // for hipFuncSetAttribute
+    LaunchFn launch[2];
     size_t (*lds)(int64_t cols);
     // logistic only: the instantiation for the direction pass (same geometry, deeper ring: its row operation is
     // one exponential and one division, which leaves the registers for it)
-    const void* kernel_dir;
-    void (*launch_dir)(const Dims&, int64_t, int, size_t, const Buffers&, const APassArgs&, hipStream_t, hipEvent_t, hipEvent_t);
+    const void* kernel_dir[2];
+    LaunchFn launch_dir[2];
 };
 
-template <typename T, int NT, int KCU, int U, int R, int NB, int WPE, int LOGI, int KR, bool TRANS>
+template <typename T, int NT, int KCU, int U, int R, int NB, int WPE, int LOGI, int KR, bool TRANS, bool ANY>
 void launch_variant(const Dims& dm, int64_t rows_per_wg, int blocks, size_t lds, const Buffers& bf, const APassArgs& a,
                     hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-    hipExtLaunchKernelGGL((ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS>), dim3(blocks), dim3(NT), lds, st, ev0, ev1,
+    hipExtLaunchKernelGGL((ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, ANY>), dim3(blocks), dim3(NT), lds, st, ev0, ev1,
                           0, (const T*)a.A, dm.ld, dm.rows, dm.cols, rows_per_wg, a, bf.scal, bf.row, bf.t, bf.wpart,
                           bf.losspart);
 }
 
+#define LB_KERNELS(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS)                                                               \
+    {(const void*)ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0, false>,                              \
+     (const void*)ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0, true>},                              \
+    {launch_variant<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0, false>,                                               \
+     launch_variant<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0, true>}
 #define LB_VARIANT_FULL(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS, KR, TRANS)                                                \
-    {dt, LOGI, TRANS, NT, (KCU) * (U), R, WGS,                                                                              \
-     (const void*)ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0>,                                      \
-     launch_variant<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0>, ring::lds_bytes<T, NT, (KCU) * (U), KR, R>, nullptr,   \
-     nullptr}
+    {dt, LOGI, TRANS, NT, (KCU) * (U), R, WGS, LB_KERNELS(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS),                       \
+     ring::lds_bytes<T, NT, (KCU) * (U), KR, R>, {nullptr, nullptr}, {nullptr, nullptr}}
 #define LB_VARIANT_LOGI(dt, T, NT, KCU, U, R, NB, NBDIR, WPE, WGS)                                                           \
-    {dt, 1, 1, NT, (KCU) * (U), R, WGS, (const void*)ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, 1, 0, true>,                \
-     launch_variant<T, NT, KCU, U, R, NB, WPE, 1, 0, true>, ring::lds_bytes<T, NT, (KCU) * (U), 0, R>,                         \
-     (const void*)ring::k_fused_ring<T, NT, KCU, U, R, NBDIR, WPE, 2, 0, true>,                                              \
-     launch_variant<T, NT, KCU, U, R, NBDIR, WPE, 2, 0, true>}
+    {dt, 1, 1, NT, (KCU) * (U), R, WGS, LB_KERNELS(T, NT, KCU, U, R, NB, WPE, 1, 0, 1),                                      \
+     ring::lds_bytes<T, NT, (KCU) * (U), 0, R>, LB_KERNELS(T, NT, KCU, U, R, NBDIR, WPE, 2, 0, 1)}
 #define LB_VARIANT_KR(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS, KR) LB_VARIANT_FULL(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS, KR, 1)
 #define LB_VARIANT(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS) LB_VARIANT_FULL(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS, 0, 1)
 #define LB_VARIANT_ROWS(dt, T, NT, KCU, U, R, NB, WPE, WGS) LB_VARIANT_FULL(dt, 0, T, NT, KCU, U, R, NB, WPE, WGS, 0, 0)
@@ -119,11 +123,11 @@ int64_t rows_per_wg_for(const Dims& dm, const Variant& v) {
 
 }  // namespace
 
-bool fused_shape_ok(const Dims& dm, const void* A, int* variant, int* blocks) {
+bool fused_shape_ok(const Dims& dm, int* variant, int* blocks) {
     *variant = -1;
     *blocks = 0;
     const int vec = dm.dtype == LBFGSB_F32 ? 4 : 2;
-    if ((uintptr_t)A % 16 != 0 || dm.cols % vec != 0 || dm.ld % vec != 0) return false;   // needs 16-byte loads
+    if (dm.cols < vec) return false;   // narrower than one 16-byte load (rows may start on any element)
     for (int i = 0; i < kNumVariants; ++i) {
         const Variant& v = kVariants[i];
         if (v.dtype != dm.dtype || v.logistic != (dm.kind == LBFGSB_OBJ_LOGISTIC_L2) ||
@@ -149,9 +153,10 @@ hipError_t fused_prepare(const Dims& dm, const Geometry& ge) {
     const size_t cap = kLdsPerWorkgroup - 256;   // the kernels also hold a few bytes of static LDS
     if (most > cap) most = cap;
     if (v.lds(dm.cols) > most) most = v.lds(dm.cols);
-    hipError_t e = hipFuncSetAttribute(v.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
-    if (e == hipSuccess && v.kernel_dir)   // (may also hold two numbers per row of a workgroup: whatever fits)
-        e = hipFuncSetAttribute(v.kernel_dir, hipFuncAttributeMaxDynamicSharedMemorySize, (int)cap);
+    const int any = ge.vec == 1;
+    hipError_t e = hipFuncSetAttribute(v.kernel[any], hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+    if (e == hipSuccess && v.kernel_dir[any])   // (may also hold two numbers per row of a workgroup: whatever fits)
+        e = hipFuncSetAttribute(v.kernel_dir[any], hipFuncAttributeMaxDynamicSharedMemorySize, (int)cap);
     return e;
 }
 
@@ -161,13 +166,14 @@ static size_t ls_first_lds(const Dims& dm, const Variant& v) { return (size_t)ro
 
 bool fused_ls_first_ok(const Dims& dm, const Geometry& ge) {
     const Variant& v = kVariants[ge.fused_variant];
-    return v.launch_dir && v.lds(dm.cols) + ls_first_lds(dm, v) <= kLdsPerWorkgroup - 256;
+    return v.launch_dir[0] && v.lds(dm.cols) + ls_first_lds(dm, v) <= kLdsPerWorkgroup - 256;
 }
 
 void launch_fused(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, hipStream_t st,
                   hipEvent_t ev0, hipEvent_t ev1) {
     const Variant& v = kVariants[ge.fused_variant];
-    auto launch = (a.mode == kRowLogiSpec && v.launch_dir) ? v.launch_dir : v.launch;
+    const int any = ge.vec == 1;
+    auto launch = (a.mode == kRowLogiSpec && v.launch_dir[any]) ? v.launch_dir[any] : v.launch[any];
     const size_t extra = a.mode == kRowLogiSpec && a.ls_first ? ls_first_lds(dm, v) : 0;
     launch(dm, rows_per_wg_for(dm, v), ge.fused_blocks, v.lds(dm.cols) + extra, bf, a, st, ev0, ev1);
 }

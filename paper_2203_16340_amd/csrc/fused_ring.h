@@ -37,6 +37,13 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 template <typename T> struct Raw;
 template <> struct Raw<float> { using type = f32x4; };
 template <> struct Raw<double> { using type = f64x2; };
+// The same in memory: a row may start on any element (odd leading dimension, odd number of columns), and the memory
+// pipeline takes 16-byte loads at any 4-byte address.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef f64x2 f64x2_any __attribute__((aligned(8)));
+template <typename T, bool ANY> struct RawMem { using type = typename Raw<T>::type; };
+template <> struct RawMem<float, true> { using type = f32x4_any; };
+template <> struct RawMem<double, true> { using type = f64x2_any; };
 
 __device__ __forceinline__ void widen(const f32x4& r, double (&o)[4]) { o[0] = r.x; o[1] = r.y; o[2] = r.z; o[3] = r.w; }
 __device__ __forceinline__ void widen(const f64x2& r, double (&o)[2]) { o[0] = r.x; o[1] = r.y; }
@@ -243,10 +250,17 @@ __device__ __forceinline__ void stage_v(const double* __restrict__ va, const dou
 // dynamic LDS a launch needs: v for the columns held there (all of them unless the variant keeps the v of
 // its last KR chunks per thread in registers), one all-zero chunk, then the reduction scratch
 constexpr int kPad = 4;
+// positions of v: the columns rounded up to whole 16-byte chunks (see the last, ragged chunk in the kernel)
+template <typename T>
+__host__ __device__ constexpr int64_t chunked_cols(int64_t cols) {
+    constexpr int VEC = 16 / (int)sizeof(T);
+    return (cols + VEC - 1) / VEC * VEC;
+}
 template <typename T, int NT, int KC, int KR>
 inline int64_t lds_cols(int64_t cols) {
     const int64_t cap = (int64_t)(KC - KR) * NT * (16 / (int)sizeof(T));
-    return KR > 0 && cols > cap ? cap : cols;
+    const int64_t pos = chunked_cols<T>(cols);
+    return KR > 0 && pos > cap ? cap : pos;
 }
 template <typename T, int NT, int KC, int KR, int R>
 inline size_t lds_bytes(int64_t cols) {
@@ -255,7 +269,10 @@ inline size_t lds_bytes(int64_t cols) {
 
 // TRANS = false: the transposed accumulation is left out (quadratic form with a symmetric matrix: the row
 // products are all an iteration needs), and the registers it would take go to a deeper ring.
-template <typename T, int NT, int KCU, int U, int R, int NB, int WPE, int LOGI, int KR = 0, bool TRANS = true>
+// ANY = true: rows may start on any element and the number of columns may be anything from one chunk up (see `full`
+// below).  A parameter and not a test: with the ragged chunk's arithmetic in every instantiation the logistic pass at
+// 200 000 x 2000 fp32 took 1.3 % longer (other waits in its row loop), and rows on 16-byte boundaries need none of it.
+template <typename T, int NT, int KCU, int U, int R, int NB, int WPE, int LOGI, int KR, bool TRANS, bool ANY>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void k_fused_ring(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, int64_t rows_per_wg, APassArgs a,
                   Scal* __restrict__ scal, double* __restrict__ row, double* __restrict__ t,
@@ -272,13 +289,19 @@ void k_fused_ring(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t col
     // Rows too wide for v to fit in LDS: the v of each thread's last KR chunks stays in registers instead
     static_assert(KR == 0 || U == 1, "register-resident v is only combined with whole-row slots");
     constexpr int KL = KC - KR;                              // chunks whose v is read from LDS
-    const int lcols = KR > 0 && cols > (int64_t)KL * NT * VEC ? KL * NT * VEC : (int)cols;
+    // ANY, number of columns not a multiple of the chunk: the row's last chunk is loaded from its last VEC columns, so it
+    // overlaps the chunk before it.  Its positions `full` .. full + VEC - 1 of v hold zero for the columns it repeats,
+    // so those add nothing to the dot product, and only its own columns of w are stored.
+    const int full = ANY ? (int)(cols - cols % VEC) : (int)cols;       // columns in whole chunks
+    const int pcols = ANY ? (int)chunked_cols<T>(cols) : (int)cols;    // positions: those columns, plus the ragged chunk
+    const int lcols = KR > 0 && pcols > KL * NT * VEC ? KL * NT * VEC : pcols;
+    const int lfull = ANY && full < lcols ? full : lcols;              // positions in LDS that are plain columns
     double* vs = lds;                                        // v, `lcols` entries, then kPad zeros
     double* red = lds + lcols + kPad;                        // [2][R][NW]
     // logistic direction pass that also sums the first trial step's loss differences: (q, dq) per row of this workgroup
     double* lsq = (LOGI == 2 && a.ls_first) ? red + 2 * R * NW : nullptr;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // chunk k of this thread starts at column (k*NT + tid)*VEC.  A chunk at or past `cols` does not
+    // chunk k of this thread starts at position (k*NT + tid)*VEC.  A chunk at or past `pcols` does not
     // exist: its loads are redirected to the last chunk of the row (valid memory) and its v to the
     // zero pad, so it adds nothing to a dot product, and its w is never stored.  No load is predicated.
     const int c0 = tid * VEC;
@@ -308,7 +331,7 @@ void k_fused_ring(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t col
         for (int k = 0; k < KCU; ++k) {
             unsigned c = cb + (unsigned)((j * KCU + k) * kStride);
             c = c < (unsigned)(icols - VEC) ? c : (unsigned)(icols - VEC);
-            dst[k] = __builtin_nontemporal_load(reinterpret_cast<const RawT*>(rp + c * (unsigned)sizeof(T)));
+            dst[k] = __builtin_nontemporal_load(reinterpret_cast<const typename RawMem<T, ANY>::type*>(rp + c * (unsigned)sizeof(T)));
         }
     };
     // The ring is primed as early as it can be without getting in the way: loads return in the order they were issued,
@@ -388,15 +411,27 @@ void k_fused_ring(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t col
     for (int k = 0; k < KR; ++k) {
 #pragma unroll
         for (int j = 0; j < VEC; ++j) {
-            const int64_t c = (int64_t)((KL + k) * NT + tid) * VEC + j;
-            vreg[k][j] = c < cols ? (vb ? va[c] - vb[c] : va[c]) * (a.vs ? a.vs[c] : 1.0) : 0.0;
+            int64_t c = (int64_t)((KL + k) * NT + tid) * VEC + j;
+            bool own = c < cols;
+            if (ANY && c >= full) {                          // position in the ragged chunk (or past it) -> its column
+                own = c < pcols && icols - VEC + (c - full) >= full;
+                c = icols - VEC + (c - full);
+            }
+            vreg[k][j] = own ? (vb ? va[c] - vb[c] : va[c]) * (a.vs ? a.vs[c] : 1.0) : 0.0;
         }
     }
-    if (vb) {
-        if (a.vs) stage_v<NT, VE, true, true>(va, vb, a.vs, vs, lcols, tid, prime); else stage_v<NT, VE, true, false>(va, vb, a.vs, vs, lcols, tid, prime);
-    } else {
-        if (a.vs) stage_v<NT, VE, false, true>(va, vb, a.vs, vs, lcols, tid, prime); else stage_v<NT, VE, false, false>(va, vb, a.vs, vs, lcols, tid, prime);
+    // the ragged chunk's entries of v, requested ahead of the others
+    double vtail = 0.0;
+    if (ANY && tid < VEC && full < lcols) {
+        const int c = icols - VEC + tid;
+        if (c >= full) vtail = (vb ? va[c] - vb[c] : va[c]) * (a.vs ? a.vs[c] : 1.0);
     }
+    if (vb) {
+        if (a.vs) stage_v<NT, VE, true, true>(va, vb, a.vs, vs, lfull, tid, prime); else stage_v<NT, VE, true, false>(va, vb, a.vs, vs, lfull, tid, prime);
+    } else {
+        if (a.vs) stage_v<NT, VE, false, true>(va, vb, a.vs, vs, lfull, tid, prime); else stage_v<NT, VE, false, false>(va, vb, a.vs, vs, lfull, tid, prime);
+    }
+    if (ANY && tid < VEC && full < lcols) vs[full + tid] = vtail;
     if (tid < kPad) vs[lcols + tid] = 0.0;
 
     // The row's entries of b (targets or labels) and of the row weights (quadratic kinds) or, for the
@@ -532,9 +567,13 @@ void k_fused_ring(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t col
         double* out = wpart + (int64_t)blockIdx.x * cols + c0;
 #pragma unroll
         for (int k = 0; k < KC; ++k) {
-            if (c0 + k * kStride < icols) {
+            if (c0 + k * kStride < full) {
 #pragma unroll
                 for (int j = 0; j < VEC; ++j) out[k * kStride + j] = w[k][j];
+            } else if (ANY && c0 + k * kStride < icols) {    // the ragged chunk: its own columns only
+#pragma unroll
+                for (int j = 0; j < VEC; ++j)
+                    if (icols - VEC + j >= full) wpart[(int64_t)blockIdx.x * cols + icols - VEC + j] = w[k][j];
             }
         }
     }

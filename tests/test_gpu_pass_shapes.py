@@ -1,0 +1,137 @@
+"""The products with A over the shapes at which their kernels can go wrong: rows that start on any element, a last
+16-byte chunk that is only partly there, the edges of each variant's width, row counts around a workgroup's share.
+
+Evaluations are compared with the same sums in numpy in 64 bits, iterations with the two-pass organisation, which
+shares no kernel with the single read.  Bound: a sum of k products in 64 bits is off by at most k 2^-53 times the sum of
+their magnitudes; with k <= 3e4 terms of like size that is below 1e-12 of the vectors' norms, and three iterations
+amplify it by no more than the factors seen for well-conditioned Gaussian matrices (1e-10 is asked)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2203_16340_amd as L
+from gpu_helpers import DEV, rel_err, to_dev
+
+pytestmark = pytest.mark.gpu
+
+LSQ, L1, LOGI = L.OBJ_LSQ, L.OBJ_LSQ_L1SPLIT, L.OBJ_LOGISTIC_L2
+
+
+def _problem(kind, rows, cols, dtype, seed, pad=0, shift=0):
+    """Device matrix whose rows start `shift` elements into an allocation of leading dimension cols + pad."""
+    rng = np.random.default_rng(seed)
+    A = rng.standard_normal((rows, cols)).astype(dtype)
+    flat = torch.full((shift + rows * (cols + pad),), float("nan"), dtype=torch.from_numpy(A).dtype, device=DEV)
+    A_d = flat[shift:].view(rows, cols + pad)[:, :cols]
+    A_d.copy_(torch.from_numpy(A))
+    n = 2 * cols if kind == L1 else cols
+    if kind == LOGI:
+        b = np.where(A @ rng.standard_normal(cols).astype(dtype) + rng.standard_normal(rows) >= 0, 1.0, -1.0)
+        l, u = np.full(n, -0.5), np.full(n, 0.5)
+    else:
+        b = A.astype(np.float64) @ (rng.random(cols) * (rng.random(cols) < 0.3)) + 0.1 * rng.standard_normal(rows)
+        l, u = np.zeros(n), np.full(n, np.inf)
+    x = np.clip(rng.random(n) * 0.4, l, u)
+    return A, A_d, b, l, u, x
+
+
+def _solver(kind, A_d, b, l, u, **opts):
+    return L.Solver(kind, A_d, to_dev(b), to_dev(l), to_dev(u), 5, lam=0.3 if kind == L1 else 0.0,
+                    mu=1e-3 if kind == LOGI else 0.0, options=L.default_options(tol=0.0, refresh_every=0, **opts))
+
+
+def _reference_fg(kind, A, b, x):
+    A = A.astype(np.float64)
+    c = A.shape[1]
+    if kind == LOGI:
+        z = A @ x
+        f = np.logaddexp(0.0, -b * z).mean() + 0.5e-3 * x @ x
+        return f, A.T @ (-b / (1.0 + np.exp(b * z))) / len(b) + 1e-3 * x, z
+    r = A @ (x[:c] - x[c:] if kind == L1 else x) - b
+    w = A.T @ r
+    if kind == L1:
+        return 0.5 * r @ r + 0.3 * x.sum(), np.concatenate([w + 0.3, -w + 0.3]), r
+    return 0.5 * r @ r, w, r
+
+
+def _check(kind, rows, cols, dtype, pad, shift):
+    A, A_d, b, l, u, x = _problem(kind, rows, cols, dtype, seed=rows * 31 + cols, pad=pad, shift=shift)
+    print(f"kind {kind} rows {rows} cols {cols} {np.dtype(dtype).name} pad {pad} shift {shift}", flush=True)
+    s = _solver(kind, A_d, b, l, u)
+    assert s.apass_name == "fused"
+    f, g, row = s.dbg_fg(to_dev(x), want_rowvec=True)
+    f_ref, g_ref, row_ref = _reference_fg(kind, A, b, x)
+    assert abs(f - f_ref) <= 1e-12 * abs(f_ref)
+    assert rel_err(g.cpu().numpy(), g_ref) <= 1e-12
+    assert rel_err(row.cpu().numpy(), row_ref) <= 1e-12
+    two = _solver(kind, A_d, b, l, u, a_pass=L.APASS_TWO_PASS)
+    for sol in (s, two):
+        sol.set_x(to_dev(x))
+    for _ in range(3):
+        s.step(False)
+        two.step(False)
+    assert s.info().iters == two.info().iters == 3
+    assert rel_err(s.x().cpu().numpy(), two.x().cpu().numpy()) <= 1e-10
+    assert rel_err(s.g().cpu().numpy(), two.g().cpu().numpy()) <= 1e-10
+
+
+# one shape around every variant's upper width, with every remainder of a chunk among them
+RAGGED = [(LSQ, np.float64, c) for c in (301, 1023, 1025, 2047, 5121, 10239, 20427, 20429, 22529)]
+RAGGED += [(LSQ, np.float32, c) for c in (301, 510, 513, 1023, 1025, 2050, 5119, 10242, 20425)]
+RAGGED += [(LOGI, np.float64, c) for c in (301, 1025, 2049, 5119, 10241)]
+RAGGED += [(LOGI, np.float32, c) for c in (301, 511, 1025, 2049, 5121, 10243)]
+RAGGED += [(L1, np.float64, 1025), (L1, np.float32, 2051)]
+
+
+@pytest.mark.parametrize("kind,dtype,cols", RAGGED)
+def test_rows_on_any_element(kind, dtype, cols):
+    _check(kind, 517, cols, dtype, pad=0, shift=1)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("pad,shift", [(0, 0), (1, 0), (3, 3), (4, 2)])
+def test_leading_dimension_and_start(dtype, pad, shift):
+    """Whole chunks on unaligned rows, and the elements between the rows (NaN here) are not touched."""
+    _check(LSQ, 300, 1200, dtype, pad, shift)
+    _check(LOGI, 300, 1200, dtype, pad, shift)
+
+
+def test_unaligned_rows_asked_for_by_name_are_refused():
+    _, A_d, b, l, u, _ = _problem(LSQ, 300, 1201, np.float64, seed=1)
+    with pytest.raises(L.LbfgsbError) as e:
+        _solver(LSQ, A_d, b, l, u, a_pass=L.APASS_FUSED)
+    assert e.value.code == L.E_UNSUPPORTED
+
+
+def test_unaligned_logistic_steps_replayed_from_a_graph():
+    """Steps recorded on unaligned rows finish every iteration on the device: x is right without a look in between."""
+    A, A_d, b, l, u, x = _problem(LOGI, 900, 403, np.float32, seed=5)
+    eager, rec = _solver(LOGI, A_d, b, l, u), None
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        rec = _solver(LOGI, A_d, b, l, u)
+        rec.set_x(to_dev(x))
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            rec.step(False)
+    eager.set_x(to_dev(x))
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        eager.step(False)
+        assert rel_err(rec.x().cpu().numpy(), eager.x().cpu().numpy()) <= 1e-12
+
+
+def test_static_solve_of_unaligned_rows_that_fit_only_without_the_single_read():
+    """The single-read pass would need 40 MB of partial columns: the call still runs, on the two-pass kernels."""
+    A, A_d, b, l, u, x = _problem(LSQ, 900, 20001, np.float32, seed=6)
+    opts = L.default_options(tol=0.0, max_iter=3)
+    ref = L.Solver(LSQ, A_d, to_dev(b), to_dev(l), to_dev(u), 5, options=opts)
+    assert ref.workspace.numel() > L.STATIC_SCRATCH_BYTES
+    ref.set_x(to_dev(x))
+    ref.solve()
+    x_d = to_dev(x)
+    info = L.solve_static(LSQ, A_d, to_dev(b), to_dev(l), to_dev(u), 5, x_d, options=opts)
+    assert info.iters == 3
+    assert rel_err(x_d.cpu().numpy(), ref.x().cpu().numpy()) <= 1e-10

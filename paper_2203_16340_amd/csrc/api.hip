@@ -143,13 +143,21 @@ Geometry make_geometry(const Dims& dm, const void* A, bool fused_unaligned = tru
     ge.gemvt_row_blocks = (int)((dm.rows + ge.gemvt_rows_per_block - 1) / ge.gemvt_rows_per_block);
     ge.fused_ok = !is_transport(dm.kind) && (aligned || fused_unaligned) &&
                   fused_shape_ok(dm, &ge.fused_variant, &ge.fused_blocks) ? 1 : 0;
+    ge.narrow_variant = -1;
+    if (ge.fused_ok) {
+        int nv, nb;
+        if (narrow_shape_ok(dm, &nv, &nb)) { ge.narrow_variant = nv; ge.fused_blocks = nb; }
+    }
     ge.gram_blocks = gram_blocks_for(dm.n, dm.m);
     int64_t db = (dm.n + kBlock - 1) / kBlock;
     ge.dir_blocks = (int)(db > kDirBlocksMax ? kDirBlocksMax : db);
     int64_t ub = (dm.cols + 15) / 16;   // 16 columns per workgroup in the column-sum kernels
     ge.upd_blocks = ge.fin_blocks = (int)(ub > 2048 ? 2048 : ub);
     int64_t lb_ = (dm.rows + kBlock - 1) / kBlock;
-    ge.ls_blocks = (int)(lb_ > 128 ? 128 : lb_);   // (the line search ends in a single-address arrival: few workgroups)
+    // (The line search ends in a single-address arrival: few workgroups, until the transcendental functions of the rows
+    // outweigh it.  10^6 rows, first trial step in a sweep of its own: 35 us with 128 workgroups, 22 with 512.)
+    const int64_t ls_cap = dm.rows > (1 << 18) ? 512 : 128;
+    ge.ls_blocks = (int)(lb_ > ls_cap ? ls_cap : lb_);
     ge.lrows_blocks = (int)(lb_ > 512 ? 512 : lb_);   // the margins' update has no such ending: 512 measured faster than 128
     {
         // workgroups for the columns plus workgroups for the margins (four rows per thread), at most 512 in all
@@ -221,6 +229,20 @@ Dims make_dims(int64_t n, int m, const lbfgsb_objective* o) {
 
 void enqueue_step(lbfgsb_solver* s);
 
+// Logistic objective on the single-read pass: the columns X^T psi of an accepted step that was not the first trial step
+// (returns at once when it was).
+void enqueue_redo_columns(lbfgsb_solver* s) {
+    if (s->ge.narrow_variant >= 0) {
+        APassArgs a{};
+        a.A = s->obj.A;
+        a.mode = kRowPsiGiven;
+        a.check_status = 2;
+        launch_narrow(s->dm, s->ge, s->bf, a, s->bf.psi, s->stream);
+    } else {
+        launch_gemvt_from(s->dm, s->ge, s->bf, s->obj.A, s->bf.psi, 2, s->stream, nullptr, nullptr);
+    }
+}
+
 // Reads the scalar block after applying any update the last step left pending.  If the short logistic launch sequence
 // has parked the solver (first trial step rejected: kStatusBail), the iteration is finished here with the launches
 // that sequence leaves out, the steps that found the solver parked are enqueued again, and the block is read anew.
@@ -241,7 +263,7 @@ hipError_t read_scal(lbfgsb_solver* s) {
         // pass for the accepted step, the update
         launch_ls_logistic(s->dm, s->op, s->ge, s->bf, s->obj.b, 1, 2, s->stream);
         launch_rows_logistic(s->dm, s->ge, s->bf, s->obj.b, s->stream);
-        launch_gemvt_from(s->dm, s->ge, s->bf, s->obj.A, s->bf.psi, 2, s->stream, nullptr, nullptr);
+        enqueue_redo_columns(s);
         launch_update_logistic(s->dm, s->op, s->ge, s->bf, s->ge.lrows_blocks, 0, s->stream);
         s->logi_full_left = 8 + redo;   // a problem that backtracks once tends to do so again: full sequence for a while
         for (int k = 0; k < redo; ++k) enqueue_step(s);
@@ -358,7 +380,7 @@ void enqueue_step(lbfgsb_solver* s) {
     // The single-read pass can make Algorithm 2's choice itself from the direction kernel's partial sums, which then
     // needs no closing step (not with extra rows that have a kernel of their own, which reads the choice from the
     // scalar block; rows folded into the direction kernel get their coefficients in the update kernel)
-    const bool defer = s->use_fused && (s->dm.n_extra == 0 || fold);
+    const bool defer = s->use_fused && s->ge.narrow_variant < 0 && (s->dm.n_extra == 0 || fold);
     // ... and then the Gram kernel needs no closing step either, where its grid is small enough for the direction
     // kernel's workgroups to add its partial sums themselves: they finish its work on private copies of the scalar
     // block, and the pass moves workgroup 0's copy into place (Buffers::scal_next)
@@ -415,7 +437,7 @@ void enqueue_step(lbfgsb_solver* s) {
             if (s->logi_full_left > 0) s->logi_full_left--;
             launch_ls_logistic(s->dm, s->op, s->ge, s->bf, s->obj.b, 1, 3, s->stream);
             launch_rows_logistic(s->dm, s->ge, s->bf, s->obj.b, s->stream);
-            launch_gemvt_from(s->dm, s->ge, s->bf, s->obj.A, s->bf.psi, 2, s->stream, nullptr, nullptr);
+            enqueue_redo_columns(s);
             launch_update_logistic(s->dm, s->op, s->ge, s->bf, s->ge.lrows_blocks, 0, s->stream);
         } else {
             // Short sequence: the pass itself sums the loss differences of the first trial step over each workgroup's
@@ -550,6 +572,7 @@ int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj
     }
     s->short_ok = s->use_fused && s->dm.kind == LBFGSB_OBJ_LOGISTIC_L2 && fused_ls_first_ok(s->dm, s->ge);
     s->ge.w_parts = s->use_fused ? s->ge.fused_blocks : s->ge.gemvt_row_blocks;
+    s->ge.redo_parts = s->use_fused && s->ge.narrow_variant >= 0 ? s->ge.fused_blocks : s->ge.gemvt_row_blocks;
     s->ge.loss_parts = s->use_fused ? s->ge.fused_blocks : s->ge.gemv_blocks;
 
     char* w = (char*)workspace;

@@ -460,7 +460,9 @@ struct Geometry {
     // fused A kernel
     int fused_ok;           // shape fits the fused kernel
     int fused_variant;      // index into the instantiation table
+    int narrow_variant;     // >= 0: the single-read pass is the kernel for narrow rows (narrow.h), this entry of its table
     int fused_blocks;       // workgroups = partial vectors per column and loss partials
+    int redo_parts;         // logistic: partial vectors per column left by the transposed pass after a rejected first step
     // vector kernels
     int gram_blocks, dir_blocks, upd_blocks, fin_blocks, ls_blocks, lrows_blocks;
     int updl_blocks;        // logistic update of the short sequence (it also moves the margins: rows / 1024 workgroups, at most 512)
@@ -505,7 +507,8 @@ enum RowMode {
     kRowLogiDir = 3,   // u = a_r.v -> t only (no transposed product follows)
     kRowLogiSpec = 4,  // fused kernel only: u = a_r.v -> t; psi of the first trial step min(1, alpha_ub)
     kRowQpEval = 5,    // two-pass row kernel only: u = a_r.v -> row; loss += 0.5 v_r u   (A symmetric, v = s.x)
-    kRowQpDir = 6      // two-pass row kernel only: u = a_r.v -> t;   loss += v_r u       (v = s.p)
+    kRowQpDir = 6,     // two-pass row kernel only: u = a_r.v -> t;   loss += v_r u       (v = s.p)
+    kRowPsiGiven = 7   // narrow kernel only: w = A^T psi for given psi
 };
 
 struct APassArgs {
@@ -548,6 +551,12 @@ bool fused_ls_first_ok(const Dims& dm, const Geometry& ge);   // APassArgs::ls_f
 hipError_t fused_prepare(const Dims& dm, const Geometry& ge);   // once per solver, before the first launch_fused
 void launch_fused(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, hipStream_t st,
                   hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// The same for narrow rows; it reads Algorithm 2's choice from the scalar block.  psi: the given weights of mode
+// kRowPsiGiven (else null).
+constexpr int kNarrowBlocksMax = 512;   // two workgroups per compute unit: what the kernel's registers allow
+bool narrow_shape_ok(const Dims& dm, int* variant, int* blocks);
+void launch_narrow(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, const double* psi,
+                   hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
 void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 void launch_set_status(const Buffers& bf, int status, hipStream_t st);

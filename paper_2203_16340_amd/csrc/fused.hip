@@ -57,19 +57,19 @@ void launch_variant(const Dims& dm, int64_t rows_per_wg, int blocks, size_t lds,
 #define LB_VARIANT_ROWS(dt, T, NT, KCU, U, R, NB, WPE, WGS) LB_VARIANT_FULL(dt, 0, T, NT, KCU, U, R, NB, WPE, WGS, 0, 0)
 
 // Ordered by capacity within a (matrix type, objective family) group: the first variant of the group
-// whose NT*KC*VEC columns cover a row and whose LDS need (v for every column) fits is used.  The
+// whose NT*KC*VEC columns cover a row and whose LDS need (v for every column) fits is used.  (Narrower rows --
+// narrow_shape_ok: up to 1536 fp32, 1024 or 768 fp64 columns -- have a kernel of their own, narrow.h; they come here
+// only with fewer than 8 rows or a leading dimension past 2^24.)  The
+// (Rows of up to 1536 fp32 or 768-1024 fp64 columns belong to the kernel of narrow.h.)  The
 // logistic evaluation kernels spend ~100 registers on exp/log1p, so their rings are shallower; the direction
 // pass of the logistic objective has its own instantiation with the deepest ring that does not spill.
 const Variant kVariants[] = {
-    LB_VARIANT(LBFGSB_F64, 0, double, 256, 2, 1, 2, 4, 4, 4),    // cols <=  1024
     LB_VARIANT(LBFGSB_F64, 0, double, 512, 2, 1, 4, 8, 2, 1),    // cols <=  2048
     LB_VARIANT(LBFGSB_F64, 0, double, 512, 5, 1, 2, 4, 2, 1),    // cols <=  5120
     LB_VARIANT(LBFGSB_F64, 0, double, 512, 10, 1, 1, 2, 2, 1),   // cols <= 10240
     LB_VARIANT(LBFGSB_F64, 0, double, 512, 20, 1, 1, 1, 2, 1),   // cols <= 20480 (LDS: <= 20428)
     LB_VARIANT_KR(LBFGSB_F64, 0, double, 512, 22, 1, 1, 1, 2, 1, 3),   // cols <= 22528, v of the last 3 chunks in registers
     LB_VARIANT_KR(LBFGSB_F64, 0, double, 512, 24, 1, 1, 1, 2, 1, 5),   // cols <= 24576, v of the last 5 chunks in registers
-    LB_VARIANT(LBFGSB_F32, 0, float, 128, 1, 1, 2, 4, 4, 8),     // cols <=   512
-    LB_VARIANT(LBFGSB_F32, 0, float, 256, 1, 1, 2, 4, 4, 4),     // cols <=  1024
     LB_VARIANT(LBFGSB_F32, 0, float, 256, 2, 1, 4, 12, 2, 2),    // cols <=  2048 (the geometry of the logistic direction pass)
     LB_VARIANT(LBFGSB_F32, 0, float, 256, 5, 1, 1, 2, 2, 2),     // cols <=  5120
     LB_VARIANT(LBFGSB_F32, 0, float, 512, 5, 1, 2, 4, 2, 1),     // cols <= 10240
@@ -80,8 +80,6 @@ const Variant kVariants[] = {
     LB_VARIANT_LOGI(LBFGSB_F64, double, 512, 5, 1, 1, 2, 4, 2, 1),     // cols <=  5120
     LB_VARIANT_LOGI(LBFGSB_F64, double, 512, 10, 1, 1, 1, 2, 2, 1),    // cols <= 10240
     LB_VARIANT_LOGI(LBFGSB_F64, double, 512, 20, 1, 1, 1, 1, 2, 1),    // cols <= 20480 (LDS: <= 20428)
-    LB_VARIANT_LOGI(LBFGSB_F32, float, 128, 1, 1, 2, 4, 8, 4, 8),      // cols <=   512
-    LB_VARIANT_LOGI(LBFGSB_F32, float, 256, 1, 1, 2, 4, 8, 4, 4),      // cols <=  1024
     LB_VARIANT_LOGI(LBFGSB_F32, float, 256, 2, 1, 4, 8, 12, 2, 2),     // cols <=  2048
     LB_VARIANT_LOGI(LBFGSB_F32, float, 256, 5, 1, 1, 2, 4, 2, 2),      // cols <=  5120
     LB_VARIANT_LOGI(LBFGSB_F32, float, 512, 5, 1, 1, 2, 4, 2, 1),      // cols <= 10240
@@ -147,6 +145,7 @@ bool fused_shape_ok(const Dims& dm, int* variant, int* blocks) {
 // kernel, not of a solver, and several solvers of different widths may share a variant: it is raised to the
 // most the variant can ever ask for (its widest row, capped by what a workgroup can have).
 hipError_t fused_prepare(const Dims& dm, const Geometry& ge) {
+    if (ge.narrow_variant >= 0) return hipSuccess;   // (static LDS only)
     const Variant& v = kVariants[ge.fused_variant];
     const int vec = v.dtype == LBFGSB_F32 ? 4 : 2;
     size_t most = v.lds((int64_t)v.nt * v.kc * vec);
@@ -165,12 +164,17 @@ hipError_t fused_prepare(const Dims& dm, const Geometry& ge) {
 static size_t ls_first_lds(const Dims& dm, const Variant& v) { return (size_t)rows_per_wg_for(dm, v) * 16; }
 
 bool fused_ls_first_ok(const Dims& dm, const Geometry& ge) {
+    if (ge.narrow_variant >= 0) return true;
     const Variant& v = kVariants[ge.fused_variant];
     return v.launch_dir[0] && v.lds(dm.cols) + ls_first_lds(dm, v) <= kLdsPerWorkgroup - 256;
 }
 
 void launch_fused(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, hipStream_t st,
                   hipEvent_t ev0, hipEvent_t ev1) {
+    if (ge.narrow_variant >= 0) {
+        launch_narrow(dm, ge, bf, a, nullptr, st, ev0, ev1);
+        return;
+    }
     const Variant& v = kVariants[ge.fused_variant];
     const int any = ge.vec == 1;
     auto launch = (a.mode == kRowLogiSpec && v.launch_dir[any]) ? v.launch_dir[any] : v.launch[any];

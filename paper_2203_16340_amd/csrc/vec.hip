@@ -930,7 +930,7 @@ __global__ __launch_bounds__(kBlock) void k_update_logistic(Dims dm, double c1, 
 
 void launch_update_logistic(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int loss_parts,
                             int short_seq, hipStream_t st) {
-    hipLaunchKernelGGL(k_update_logistic, dim3(short_seq ? ge.updl_blocks : ge.upd_blocks), dim3(kBlock), 0, st, dm, op.c1, ge.gemvt_row_blocks,
+    hipLaunchKernelGGL(k_update_logistic, dim3(short_seq ? ge.updl_blocks : ge.upd_blocks), dim3(kBlock), 0, st, dm, op.c1, ge.redo_parts,
                        ge.fused_blocks, loss_parts, short_seq, (const double*)bf.t, bf.row, bf.wpart,
                        bf.losspart, bf.p1, bf.p2, bf.l, bf.u, bf.x, bf.g, bf.S, bf.Y, bf.scal, bf.redpart);
 }

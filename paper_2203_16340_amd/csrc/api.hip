@@ -380,14 +380,19 @@ void enqueue_step(lbfgsb_solver* s) {
     // The single-read pass can make Algorithm 2's choice itself from the direction kernel's partial sums, which then
     // needs no closing step (not with extra rows that have a kernel of their own, which reads the choice from the
     // scalar block; rows folded into the direction kernel get their coefficients in the update kernel)
-    const bool defer = s->use_fused && s->ge.narrow_variant < 0 && (s->dm.n_extra == 0 || fold);
+    const bool small = small_step_ok(s->dm);
+    const bool defer = s->use_fused && s->ge.narrow_variant < 0 && !small && (s->dm.n_extra == 0 || fold);
     // ... and then the Gram kernel needs no closing step either, where its grid is small enough for the direction
     // kernel's workgroups to add its partial sums themselves: they finish its work on private copies of the scalar
     // block, and the pass moves workgroup 0's copy into place (Buffers::scal_next)
     const bool open_gram = defer && gram_can_skip_close(s->dm, s->ge);
-    launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, nullptr, nullptr, open_gram ? 1 : 0);
-    launch_dir(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream, fold_rows, s->obj.extra_weight, defer ? 1 : 0,
-               open_gram ? s->ge.gram_blocks : 0);
+    if (small) {
+        launch_small_step(s->dm, s->op, s->bf, fold_rows, s->obj.extra_weight, s->stream);
+    } else {
+        launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, nullptr, nullptr, open_gram ? 1 : 0);
+        launch_dir(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream, fold_rows, s->obj.extra_weight, defer ? 1 : 0,
+                   open_gram ? s->ge.gram_blocks : 0);
+    }
     APassArgs a = base_args(s);
     a.select_p = 1;
     a.check_status = 1;
@@ -564,6 +569,10 @@ int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj
     if (s->use_resident) {
         const hipError_t re = resident_prepare(s->dm);
         if (re != hipSuccess) return fail(LBFGSB_E_HIP, "preparing the resident solver: %s", hipGetErrorString(re));
+    }
+    if (small_step_ok(s->dm)) {
+        const hipError_t se = small_step_prepare(s->dm);
+        if (se != hipSuccess) return fail(LBFGSB_E_HIP, "preparing the short-vector kernel: %s", hipGetErrorString(se));
     }
     s->use_fused = s->ge.fused_ok && o.a_pass != LBFGSB_APASS_TWO_PASS;
     if (s->use_fused) {

@@ -619,6 +619,12 @@ void launch_ot_update_gauss(const Dims& dm, const Opts& op, const Geometry& ge, 
 void launch_ot_step_entropy(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
                             hipStream_t st);
 
+// Gram matrix, recursion, direction and Algorithm 2's choice in one workgroup, for short vectors (small.hip)
+bool small_step_ok(const Dims& dm);
+hipError_t small_step_prepare(const Dims& dm);   // once per solver, before the first launch_small_step
+void launch_small_step(const Dims& dm, const Opts& op, const Buffers& bf, const double* fold_rows, const double* fold_weight,
+                       hipStream_t st);
+
 // single-workgroup resident solver for small least-squares problems (resident.hip)
 bool resident_shape_ok(const Dims& dm, bool has_row_weight);
 hipError_t resident_prepare(const Dims& dm);   // once per solver, before the first launch_resident

@@ -58,6 +58,7 @@ struct lbfgsb_solver {
     hipStream_t stream;
     Scal* h_scal;            // host copy (pinned, allocated by lbfgsb_create)
     bool owns_h_scal;
+    int* h_flag;             // pinned, behind the host copy: kernels report a start point that is no good (null: not pinned)
     int use_fused;
     int use_resident;        // small least squares: whole iterations in one resident workgroup
     // logistic objective on the fused pass: steps still to be enqueued with the full launch sequence (after a
@@ -249,10 +250,15 @@ void enqueue_redo_columns(lbfgsb_solver* s) {
 hipError_t read_scal(lbfgsb_solver* s) {
     for (;;) {
         // (the resident solver applies its updates itself; only its evaluations by the multi-kernel path leave one pending)
-        if (!s->use_resident || s->commit_needed) launch_commit(s->dm, s->bf, s->stream);
+        hipError_t e = hipSuccess;
+        if (s->owns_h_scal) {
+            launch_commit(s->dm, s->bf, s->stream, s->h_scal);   // (writes the pinned host copy itself)
+        } else {
+            if (!s->use_resident || s->commit_needed) launch_commit(s->dm, s->bf, s->stream);
+            e = hipMemcpyAsync(s->h_scal, s->bf.scal, sizeof(Scal), hipMemcpyDeviceToHost, s->stream);
+            if (e != hipSuccess) return e;
+        }
         s->commit_needed = false;
-        hipError_t e = hipMemcpyAsync(s->h_scal, s->bf.scal, sizeof(Scal), hipMemcpyDeviceToHost, s->stream);
-        if (e != hipSuccess) return e;
         e = hipStreamSynchronize(s->stream);
         if (e != hipSuccess) return e;
         s->short_steps_unseen = 0;
@@ -310,9 +316,9 @@ OtArgs ot_args(const lbfgsb_solver* s) {
     return OtArgs{s->obj.A, s->obj.b, s->obj.row_weight};
 }
 
-// f, g (and the residual / margins) from scratch at the current x.
-void enqueue_eval(lbfgsb_solver* s, int check_status) {
-    launch_commit(s->dm, s->bf, s->stream);   // a pending f must not overwrite the one computed here
+// f, g (and the residual / margins) from scratch at the current x.  fresh: the scalar block holds no pending update.
+void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false) {
+    if (!fresh) launch_commit(s->dm, s->bf, s->stream);   // a pending f must not overwrite the one computed here
     if (is_transport(s->dm.kind)) {
         const OtArgs oa = ot_args(s);
         launch_ot_sums(s->dm, s->ge, s->bf, oa, 1, check_status, s->stream);
@@ -471,40 +477,47 @@ void fresh_scal(lbfgsb_solver* s) {
     s->h_scal->hist = s->bf.hist;
 }
 
-// trusted: x0 is the solver's own iterate (feasible by construction): only f is checked for finiteness and
-// nothing iterate-sized crosses to the host
-int set_x_impl(lbfgsb_solver* s, const double* x0, bool trusted) {
+// The first x0_i outside its bounds, for the message (the device has found that there is one).
+int report_infeasible(lbfgsb_solver* s, const double* x0) {
     const int64_t n = s->dm.n;
-    std::vector<double> hx;
-    if (!trusted) {
-        std::vector<double> hl((size_t)n), hu((size_t)n);
-        hx.resize((size_t)n);
-        HIP_TRY(hipMemcpyAsync(hx.data(), x0, (size_t)n * 8, hipMemcpyDeviceToHost, s->stream));
-        HIP_TRY(hipMemcpyAsync(hl.data(), s->bf.l, (size_t)n * 8, hipMemcpyDeviceToHost, s->stream));
-        HIP_TRY(hipMemcpyAsync(hu.data(), s->bf.u, (size_t)n * 8, hipMemcpyDeviceToHost, s->stream));
-        HIP_TRY(hipStreamSynchronize(s->stream));
-        for (int64_t i = 0; i < n; ++i) {
-            const double v = hx[(size_t)i];
-            if (!(v >= hl[(size_t)i]) || !(v <= hu[(size_t)i]))
-                return fail(LBFGSB_E_INFEASIBLE_X0, "x0[%lld] = %g is outside [%g, %g]", (long long)i, v, hl[(size_t)i],
-                            hu[(size_t)i]);
-        }
+    std::vector<double> hx((size_t)n), hl((size_t)n), hu((size_t)n);
+    HIP_TRY(hipMemcpyAsync(hx.data(), x0, (size_t)n * 8, hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipMemcpyAsync(hl.data(), s->bf.l, (size_t)n * 8, hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipMemcpyAsync(hu.data(), s->bf.u, (size_t)n * 8, hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    for (int64_t i = 0; i < n; ++i) {
+        const double v = hx[(size_t)i];
+        if (!(v >= hl[(size_t)i]) || !(v <= hu[(size_t)i]))
+            return fail(LBFGSB_E_INFEASIBLE_X0, "x0[%lld] = %g is outside [%g, %g]", (long long)i, v, hl[(size_t)i],
+                        hu[(size_t)i]);
     }
-    if (x0 != s->bf.x) HIP_TRY(hipMemcpyAsync(s->bf.x, x0, (size_t)n * 8, hipMemcpyDeviceToDevice, s->stream));
-    fresh_scal(s);
-    // (no wait: the pinned block is next touched by the read below, which the stream orders after this upload)
-    HIP_TRY(hipMemcpyAsync(s->bf.scal, s->h_scal, sizeof(Scal), hipMemcpyHostToDevice, s->stream));
-    enqueue_eval(s, 0);
+    return fail(LBFGSB_E_INFEASIBLE_X0, "x0 was outside its bounds when it was checked");
+}
+
+// trusted: x0 is the solver's own iterate, or has been checked by the caller: only f is checked for finiteness
+int set_x_impl(lbfgsb_solver* s, const double* x0, bool trusted) {
+    volatile int* flag = s->h_flag;
+    if (!trusted) {
+        // nothing of the solver's state changes before this has been found to be all right
+        *flag = 0;
+        launch_check_box(s->dm, s->op, s->bf, x0, s->h_flag, s->stream);
+        HIP_TRY(hipStreamSynchronize(s->stream));
+        HIP_TRY(hipGetLastError());
+        if (*flag) return report_infeasible(s, x0);
+    }
+    launch_start(s->dm, s->bf, x0, s->stream);
+    enqueue_eval(s, 0, true);
     s->steps_since_refresh = 0;
     s->steps_since_set_x = 0;
     s->logi_full_left = 0;
     s->short_steps_unseen = 0;
-    if (!trusted) HIP_TRY(hipMemcpyAsync(hx.data(), s->bf.g, (size_t)n * 8, hipMemcpyDeviceToHost, s->stream));
+    if (!trusted) launch_check_finite(s->dm, s->bf.g, s->h_flag, s->stream);
     HIP_TRY(read_scal(s));
     HIP_TRY(hipGetLastError());
-    bool finite = std::isfinite(s->h_scal->f);
-    for (int64_t i = 0; finite && !trusted && i < n; ++i) finite = std::isfinite(hx[(size_t)i]);
-    if (!finite) { s->x_set = false; return fail(LBFGSB_E_NONFINITE, "f or grad f is not finite at x0"); }
+    if (!std::isfinite(s->h_scal->f) || (!trusted && *flag)) {
+        s->x_set = false;
+        return fail(LBFGSB_E_NONFINITE, "f or grad f is not finite at x0");
+    }
     s->x_set = true;
     return LBFGSB_OK;
 }
@@ -543,6 +556,7 @@ int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj
     s->stream = stream;
     s->h_scal = nullptr;
     s->owns_h_scal = false;
+    s->h_flag = nullptr;
     s->steps_since_refresh = 0;
     s->steps_since_set_x = 0;
     s->logi_full_left = 0;
@@ -778,9 +792,11 @@ int lbfgsb_create(lbfgsb_solver** out, int64_t n, int m, const double* l, const 
 
     auto bail = [&](int code) { lbfgsb_destroy(s); return code; };
     {
-        hipError_t e = hipHostMalloc((void**)&s->h_scal, sizeof(Scal), hipHostMallocDefault);
+        const size_t flag_at = (sizeof(Scal) + 63) / 64 * 64;
+        hipError_t e = hipHostMalloc((void**)&s->h_scal, flag_at + 64, hipHostMallocDefault);
         if (e != hipSuccess) { s->h_scal = nullptr; return bail(fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e))); }
         s->owns_h_scal = true;
+        s->h_flag = (int*)((char*)s->h_scal + flag_at);
     }
     // validate the bounds on the host
     std::vector<double> hl((size_t)n), hu((size_t)n);

@@ -567,7 +567,14 @@ void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, c
 void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int dbg_inputs,
                  int evaluate_stop, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, int no_close = 0);
 bool gram_can_skip_close(const Dims& dm, const Geometry& ge);
-void launch_commit(const Dims& dm, const Buffers& bf, hipStream_t st);
+// host_scal: pinned host memory that receives the scalar block as well (null: device copy only)
+void launch_commit(const Dims& dm, const Buffers& bf, hipStream_t st, Scal* host_scal = nullptr);
+// lbfgsb_set_x.  launch_check_box: *host_flag (pinned) becomes 1 if some x0_i is outside its bounds or NaN;
+// launch_start: x = x0 (unless they are the same array) and a fresh scalar block; launch_check_finite: *host_flag becomes
+// 1 if some g_i is not finite.
+void launch_check_box(const Dims& dm, const Opts& op, const Buffers& bf, const double* x0, int* host_flag, hipStream_t st);
+void launch_start(const Dims& dm, const Buffers& bf, const double* x0, hipStream_t st);
+void launch_check_finite(const Dims& dm, const double* g, int* host_flag, hipStream_t st);
 // store_d: also keep d itself (the primitive-level hooks read it; an iteration only needs the two candidates)
 bool dir_folds_extra_rows(const Dims& dm);
 // fold_rows / fold_weight: the objective's extra rows and their weights when they are to ride along (else NULL)

@@ -838,12 +838,20 @@ void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffe
 }
 
 // Applies a pending update when nothing else is about to (before an evaluation from scratch, and
-// before the host reads the scalars).
-__global__ void k_commit(Scal* scal, int m) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) apply_pending(scal, m);
+// before the host reads the scalars).  host_scal: where the host reads them, in pinned memory: written by this kernel,
+// one wave, instead of by a copy command behind it.
+__global__ __launch_bounds__(64) void k_commit(Scal* scal, int m, Scal* __restrict__ host_scal) {
+    if (threadIdx.x == 0) apply_pending(scal, m);
+    if (!host_scal) return;
+    __threadfence_block();           // thread 0's stores, before the wave reads the block
+    __builtin_amdgcn_wave_barrier();
+    constexpr int kWords = (int)(sizeof(Scal) / 8);
+    static_assert(sizeof(Scal) % 8 == 0, "copied in 8-byte words");
+    for (int k = threadIdx.x; k < kWords; k += 64)
+        reinterpret_cast<uint64_t*>(host_scal)[k] = reinterpret_cast<const uint64_t*>(scal)[k];
 }
-void launch_commit(const Dims& dm, const Buffers& bf, hipStream_t st) {
-    hipLaunchKernelGGL(k_commit, dim3(1), dim3(64), 0, st, bf.scal, dm.m);
+void launch_commit(const Dims& dm, const Buffers& bf, hipStream_t st, Scal* host_scal) {
+    hipLaunchKernelGGL(k_commit, dim3(1), dim3(64), 0, st, bf.scal, dm.m, host_scal);
 }
 
 }  // namespace lb

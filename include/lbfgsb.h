@@ -52,6 +52,7 @@ enum {
     LBFGSB_OBJ_LSQ_L1SPLIT = 1,  /* f = 0.5*||A(p-q) - b||^2 + lambda*sum(p+q), x=[p;q], n = 2*cols */
     LBFGSB_OBJ_LOGISTIC_L2 = 2,  /* f = (1/rows)*sum_i softplus(-b_i*(A x)_i) + mu/2*||x||^2, b_i in {-1,+1}, n = cols */
     LBFGSB_OBJ_QP = 3,           /* f = 0.5*(s.x)^T A (s.x) + b^T x, A symmetric, rows = cols = n, s = sign (or ones).
+                                    (Large matrices are read on and above the diagonal only.)
                                     With A a kernel matrix, s the labels and b = -1 this is the dual SVM objective of
                                     the paper's section "Dual SVM".  One product with A per iteration (no transposed pass) */
     /* The regularised optimal-transport objective of the paper's section "Joint Probability Distribution" over a
@@ -335,7 +336,7 @@ void lbfgsb_auglag_destroy(lbfgsb_auglag* al);
  * synchronises and returns how many launches were timed (launches that returned at once because the
  * solver had already stopped -- duration below half of the 90th-percentile duration -- are left out), their total duration in milliseconds
  * and the bytes of A one launch requests from memory (rows*cols*sizeof(element): each such
- * kernel reads A exactly once).  The transport kinds have no such kernel: there the Gram kernel of the batched
+ * kernel reads A exactly once; the upper triangle only for a large symmetric matrix of kind QP).  The transport kinds have no such kernel: there the Gram kernel of the batched
  * two-loop recursion (the longest kernel of an iteration) is timed instead, from the m-th iteration after
  * lbfgsb_set_x on, when all m pairs are stored; the bytes are 41*n (x, g, l, u, the newest y, the mask; 25*n when
  * all variables share the same bounds, which are then not streamed) plus 16*m per free variable (the pair vectors

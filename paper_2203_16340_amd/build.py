@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbfgsb.so")
-SOURCES = ["fused.hip", "narrow.hip", "small.hip", "gram.hip", "api.hip", "apass.hip", "resident.hip", "transport.hip", "vec.hip"]
+SOURCES = ["fused.hip", "narrow.hip", "small.hip", "symmetric.hip", "gram.hip", "api.hip", "apass.hip", "resident.hip", "transport.hip", "vec.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
     # packed-fp32 instructions are kept out of the generated code on purpose

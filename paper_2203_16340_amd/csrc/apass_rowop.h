@@ -2,6 +2,8 @@
 // of the vector A multiplies, and the objective's per-row operation.
 #pragma once
 
+#include <cstddef>
+
 #include "common.h"
 
 namespace lb {
@@ -37,6 +39,61 @@ __device__ __forceinline__ void resolve_v(const APassArgs& a, const Scal* scal, 
         va = (branch ? branch : scal->branch) == 1 ? a.p1 : a.p2;
         vb = a.split ? va + cols : nullptr;
     }
+}
+
+// What a pass over A does before anything else: the status word (from the copy of the scalar block the direction kernel
+// left in a.scal_next, when there is one), Algorithm 2's choice between the candidate directions from that kernel's partial
+// sums (every wave of every workgroup gets the same bits; workgroup 0 records it), and, by the first wave of workgroup 0,
+// the move of that copy into the scalar block.  Returns whether the solver is running; branch: the choice, 0 if it is to
+// be read from the scalar block.  (The ring kernel, whose registers are counted, has this in line.)
+__device__ __forceinline__ bool pass_start(const APassArgs& a, Scal* __restrict__ scal, int& branch) {
+    const int tid = threadIdx.x;
+    const int status = a.check_status ? (a.scal_next ? a.scal_next : scal)->status : LBFGSB_RUNNING;
+    constexpr int kScalWords = (int)(sizeof(Scal) / 4), kPerLane = (kScalWords + 63) / 64;
+    const bool mover = a.scal_next && blockIdx.x == 0 && tid < 64;
+    int moved[kPerLane];
+    int fresh = 0;
+    if (mover) {
+        fresh = a.scal_next->fresh;
+#pragma unroll
+        for (int j = 0; j < kPerLane; ++j) {
+            const int idx = tid + 64 * j;
+            moved[j] = idx < kScalWords ? reinterpret_cast<const int*>(a.scal_next)[idx] : 0;
+        }
+    }
+    branch = 0;
+    DirChoice ch{};
+    const bool own_choice = a.select_p && a.dir_blocks > 0;
+    if (own_choice) ch = dir_choice_from_partials(a.dir_part, a.dir_blocks, a.eps);
+    if (mover && fresh) {
+#pragma unroll
+        for (int j = 0; j < kPerLane; ++j) {
+            const int idx = tid + 64 * j;
+            int v = moved[j];
+            auto put_double = [&](size_t off, double val) {
+                if (idx == (int)(off / 4)) v = __double2loint(val);
+                if (idx == (int)(off / 4) + 1) v = __double2hiint(val);
+            };
+            if (own_choice && status == LBFGSB_RUNNING) {
+                if (idx == (int)(offsetof(Scal, branch) / 4)) v = ch.branch;
+                put_double(offsetof(Scal, gp), ch.gp);
+                put_double(offsetof(Scal, alpha_ub), ch.alpha_ub);
+                put_double(offsetof(Scal, pp), ch.pp);
+                put_double(offsetof(Scal, xp), ch.xp);
+            }
+            if (idx == (int)(offsetof(Scal, fresh) / 4)) v = 0;
+            if (idx < kScalWords) reinterpret_cast<int*>(scal)[idx] = v;
+        }
+        if (tid == 0) a.scal_next->fresh = 0;
+    }
+    if (status != LBFGSB_RUNNING) return false;
+    if (own_choice) {
+        branch = ch.branch;
+        if (blockIdx.x == 0 && tid == 0 && !(a.scal_next && fresh)) {
+            scal->branch = ch.branch; scal->gp = ch.gp; scal->alpha_ub = ch.alpha_ub; scal->pp = ch.pp; scal->xp = ch.xp;
+        }
+    }
+    return true;
 }
 
 // The objective's per-row operation on u = a_r . v.  Returns the row's loss contribution.

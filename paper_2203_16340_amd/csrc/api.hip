@@ -148,6 +148,8 @@ Geometry make_geometry(const Dims& dm, const void* A, bool fused_unaligned = tru
     if (ge.fused_ok) {
         int nv, nb;
         if (narrow_shape_ok(dm, &nv, &nb)) { ge.narrow_variant = nv; ge.fused_blocks = nb; }
+        int strips, grid;
+        if (sym_shape_ok(dm, &strips, &grid)) { ge.sym_strips = strips; ge.fused_blocks = grid; }
     }
     ge.gram_blocks = gram_blocks_for(dm.n, dm.m);
     int64_t db = (dm.n + kBlock - 1) / kBlock;
@@ -197,11 +199,14 @@ Layout make_layout(const Dims& dm, const Geometry& ge) {
     L.S = take(nb * dm.m); L.Y = take(nb * dm.m);
     L.row = take(rb); L.t = take(rb); L.psi = take(rb);
     int wparts = ge.gemvt_row_blocks;
-    if (ge.fused_ok && ge.fused_blocks > wparts) wparts = ge.fused_blocks;
+    if (ge.fused_ok && ge.sym_strips == 0 && ge.fused_blocks > wparts) wparts = ge.fused_blocks;
     if (is_transport(dm.kind)) wparts = ge.ot_row_blocks;
-    L.wpart = take((size_t)wparts * dm.cols * 8);
+    size_t wdoubles = (size_t)wparts * dm.cols;
+    if (ge.sym_strips > 0 && sym_workspace(dm, ge) > wdoubles) wdoubles = sym_workspace(dm, ge);
+    L.wpart = take(wdoubles * 8);
     int lparts = ge.gemv_blocks;
     if (ge.fused_ok && ge.fused_blocks > lparts) lparts = ge.fused_blocks;
+    if (ge.sym_strips > 0 && sym_loss_parts(dm) > lparts) lparts = sym_loss_parts(dm);
     if (ge.ls_blocks > lparts) lparts = ge.ls_blocks;
     if (ge.lrows_blocks > lparts) lparts = ge.lrows_blocks;
     if (is_transport(dm.kind) && ge.ot_row_blocks + ge.ot_col_blocks > lparts) lparts = ge.ot_row_blocks + ge.ot_col_blocks;
@@ -589,6 +594,7 @@ int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj
         if (se != hipSuccess) return fail(LBFGSB_E_HIP, "preparing the short-vector kernel: %s", hipGetErrorString(se));
     }
     s->use_fused = s->ge.fused_ok && o.a_pass != LBFGSB_APASS_TWO_PASS;
+    if (!s->use_fused) s->ge.sym_strips = 0;
     if (s->use_fused) {
         const hipError_t fe = fused_prepare(s->dm, s->ge);
         if (fe != hipSuccess) return fail(LBFGSB_E_HIP, "preparing the fused A pass: %s", hipGetErrorString(fe));
@@ -596,7 +602,7 @@ int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj
     s->short_ok = s->use_fused && s->dm.kind == LBFGSB_OBJ_LOGISTIC_L2 && fused_ls_first_ok(s->dm, s->ge);
     s->ge.w_parts = s->use_fused ? s->ge.fused_blocks : s->ge.gemvt_row_blocks;
     s->ge.redo_parts = s->use_fused && s->ge.narrow_variant >= 0 ? s->ge.fused_blocks : s->ge.gemvt_row_blocks;
-    s->ge.loss_parts = s->use_fused ? s->ge.fused_blocks : s->ge.gemv_blocks;
+    s->ge.loss_parts = s->ge.sym_strips > 0 ? sym_loss_parts(s->dm) : (s->use_fused ? s->ge.fused_blocks : s->ge.gemv_blocks);
 
     char* w = (char*)workspace;
     Buffers& b = s->bf;
@@ -977,6 +983,14 @@ int lbfgsb_apass_timing(lbfgsb_solver* s, int64_t* count, double* total_ms, doub
     *count = n;
     *total_ms = tot;
     *bytes_per_pass = (double)s->dm.rows * (double)s->dm.cols * (s->dm.dtype == LBFGSB_F32 ? 4.0 : 8.0);
+    if (s->ge.sym_strips > 0) {
+        // the upper triangle in strips of columns, with the blocks on the diagonal whole
+        *bytes_per_pass = 0.0;
+        for (int J = 0; J < s->ge.sym_strips; ++J) {
+            const double rows = std::min<double>((double)(J + 1) * kSymStrip, (double)s->dm.cols);
+            *bytes_per_pass += rows * (rows - (double)J * kSymStrip) * (s->dm.dtype == LBFGSB_F32 ? 4.0 : 8.0);
+        }
+    }
     // transport kinds: the timed kernel is the Gram kernel, timed in iterations m, m+1, ... after lbfgsb_set_x, when
     // all m pairs are stored.  It reads x, g, the newest y (and l, u unless every variable has the same bounds) in
     // full and writes the one-byte free mask; the 2m pair vectors are read at the free variables only (count taken

@@ -462,6 +462,7 @@ struct Geometry {
     int fused_variant;      // index into the instantiation table
     int narrow_variant;     // >= 0: the single-read pass is the kernel for narrow rows (narrow.h), this entry of its table
     int fused_blocks;       // workgroups = partial vectors per column and loss partials
+    int sym_strips;         // > 0: the quadratic form's products come from the upper triangle (symmetric.hip), in this many strips
     int redo_parts;         // logistic: partial vectors per column left by the transposed pass after a rejected first step
     // vector kernels
     int gram_blocks, dir_blocks, upd_blocks, fin_blocks, ls_blocks, lrows_blocks;
@@ -557,6 +558,17 @@ constexpr int kNarrowBlocksMax = 512;   // two workgroups per compute unit: what
 bool narrow_shape_ok(const Dims& dm, int* variant, int* blocks);
 void launch_narrow(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, const double* psi,
                    hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+
+// Row products of the quadratic form from the upper triangle (symmetric.hip).  Workspace: column sums of every workgroup,
+// then row sums of every strip (sym_workspace doubles, at Buffers::wpart).
+constexpr int kSymStrip = 512;
+bool sym_shape_ok(const Dims& dm, int* strips, int* grid);
+int sym_loss_parts(const Dims& dm);
+inline size_t sym_workspace(const Dims& dm, const Geometry& ge) {
+    return (size_t)ge.fused_blocks * kSymStrip + (size_t)ge.sym_strips * dm.cols;
+}
+void launch_sym(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, hipStream_t st,
+                hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
 void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 void launch_set_status(const Buffers& bf, int status, hipStream_t st);

@@ -84,14 +84,12 @@ const Variant kVariants[] = {
     LB_VARIANT_LOGI(LBFGSB_F32, float, 256, 5, 1, 1, 2, 4, 2, 2),      // cols <=  5120
     LB_VARIANT_LOGI(LBFGSB_F32, float, 512, 5, 1, 1, 2, 4, 2, 1),      // cols <= 10240
     LB_VARIANT_LOGI(LBFGSB_F32, float, 512, 10, 1, 1, 1, 2, 2, 1),     // cols <= 20480 (LDS: <= 20428)
-    // row products only: no accumulators of w, so the ring is deeper
+    // row products only: no accumulators of w, so the ring is deeper (4096 to 15872 columns: symmetric.hip)
     LB_VARIANT_ROWS(LBFGSB_F64, double, 256, 2, 1, 4, 8, 4, 4),  // cols <=  1024
     LB_VARIANT_ROWS(LBFGSB_F64, double, 512, 5, 1, 2, 8, 2, 1),  // cols <=  5120
-    LB_VARIANT_ROWS(LBFGSB_F64, double, 512, 10, 1, 1, 4, 2, 1), // cols <= 10240
     LB_VARIANT_ROWS(LBFGSB_F64, double, 512, 20, 1, 1, 2, 2, 1), // cols <= 20480 (LDS: <= 20428)
     LB_VARIANT_ROWS(LBFGSB_F32, float, 256, 1, 1, 4, 8, 4, 4),   // cols <=  1024
     LB_VARIANT_ROWS(LBFGSB_F32, float, 256, 5, 1, 2, 8, 2, 2),   // cols <=  5120
-    LB_VARIANT_ROWS(LBFGSB_F32, float, 512, 5, 1, 2, 8, 2, 1),   // cols <= 10240
     LB_VARIANT_ROWS(LBFGSB_F32, float, 512, 10, 1, 1, 4, 2, 1),  // cols <= 20480 (LDS: <= 20428)
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
@@ -145,7 +143,7 @@ bool fused_shape_ok(const Dims& dm, int* variant, int* blocks) {
 // kernel, not of a solver, and several solvers of different widths may share a variant: it is raised to the
 // most the variant can ever ask for (its widest row, capped by what a workgroup can have).
 hipError_t fused_prepare(const Dims& dm, const Geometry& ge) {
-    if (ge.narrow_variant >= 0) return hipSuccess;   // (static LDS only)
+    if (ge.narrow_variant >= 0 || ge.sym_strips > 0) return hipSuccess;   // (static LDS only)
     const Variant& v = kVariants[ge.fused_variant];
     const int vec = v.dtype == LBFGSB_F32 ? 4 : 2;
     size_t most = v.lds((int64_t)v.nt * v.kc * vec);
@@ -171,6 +169,10 @@ bool fused_ls_first_ok(const Dims& dm, const Geometry& ge) {
 
 void launch_fused(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, hipStream_t st,
                   hipEvent_t ev0, hipEvent_t ev1) {
+    if (ge.sym_strips > 0) {
+        launch_sym(dm, ge, bf, a, st, ev0, ev1);
+        return;
+    }
     if (ge.narrow_variant >= 0) {
         launch_narrow(dm, ge, bf, a, nullptr, st, ev0, ev1);
         return;

@@ -173,3 +173,42 @@ def test_narrow_row_weights():
     r = A @ x - b
     assert abs(f - 0.5 * (w * r) @ r) <= 1e-12 * f
     assert rel_err(g.cpu().numpy(), A.T @ (w * r)) <= 1e-12 and rel_err(row.cpu().numpy(), r) <= 1e-12
+
+
+# the quadratic form's products from the upper triangle (from 4096 variables on): one strip of 512 columns more or less,
+# ragged last strips and chunks, unaligned rows; a size on either side that belongs to the row kernels
+@pytest.mark.parametrize("n", [4095, 4096, 4097, 4607, 4608, 4609, 5121, 15872, 15873])
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("signed", [False, True])
+def test_symmetric_products(n, dtype, signed):
+    if n > 15000 and signed:
+        pytest.skip("the widest matrices once only")
+    rng = np.random.default_rng(n)
+    B = rng.standard_normal((n, n), dtype=dtype)
+    K = (B + B.T) / 2
+    K[np.diag_indices(n)] += dtype(2.0 * np.sqrt(n))
+    K64 = K.astype(np.float64)
+    q, x = rng.standard_normal(n), rng.random(n)
+    sign = np.where(rng.random(n) < 0.5, -1.0, 1.0) if signed else np.ones(n)
+    l, u = np.zeros(n), np.full(n, 1.0)
+
+    def solver(**opts):
+        return L.Solver(L.OBJ_QP, torch.from_numpy(K).to(DEV), to_dev(q), to_dev(l), to_dev(u), 5,
+                        sign=to_dev(sign) if signed else None, options=L.default_options(tol=0.0, refresh_every=0, **opts))
+
+    print(f"n {n} {np.dtype(dtype).name} signed {signed}", flush=True)
+    s, two = solver(), solver(a_pass=L.APASS_TWO_PASS)
+    f, g, row = s.dbg_fg(to_dev(x), want_rowvec=True)
+    v = sign * x
+    t = K64 @ v
+    assert rel_err(row.cpu().numpy(), t) <= 1e-12
+    assert rel_err(g.cpu().numpy(), sign * t + q) <= 1e-12
+    assert abs(f - (0.5 * v @ t + q @ x)) <= 1e-12 * np.linalg.norm(v) * np.linalg.norm(t)
+    for sol in (s, two):
+        sol.set_x(to_dev(x))
+    for _ in range(3):
+        a, b = s.step(), two.step()
+        assert (a.status, a.branch, a.backtracks, a.n_fixed) == (b.status, b.branch, b.backtracks, b.n_fixed)
+        assert a.f == pytest.approx(b.f, rel=1e-10)
+    assert rel_err(s.x().cpu().numpy(), two.x().cpu().numpy()) <= 1e-10
+    assert rel_err(s.g().cpu().numpy(), two.g().cpu().numpy()) <= 1e-10

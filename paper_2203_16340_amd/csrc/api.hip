@@ -59,6 +59,7 @@ struct lbfgsb_solver {
     Scal* h_scal;            // host copy (pinned, allocated by lbfgsb_create)
     bool owns_h_scal;
     int* h_flag;             // pinned, behind the host copy: kernels report a start point that is no good (null: not pinned)
+    unsigned long long* h_progress;   // pinned, behind it: the last step whose outcome is known, and the status then
     int use_fused;
     int use_resident;        // small least squares: whole iterations in one resident workgroup
     // logistic objective on the fused pass: steps still to be enqueued with the full launch sequence (after a
@@ -73,10 +74,8 @@ struct lbfgsb_solver {
     void (*after_retest)(void*) = nullptr;
     void* after_retest_ctx = nullptr;
     bool last_read_was_retest = false;   // the scalar block was last read behind such a call
-    // lbfgsb_solve looks at the status after this many steps the first time (0: after poll_every, as always later).
-    // A warm-started solve that may be over at once (the augmented Lagrangian's later inner solves) sets 1: every step
-    // enqueued behind the one that converged is four launches that return at once.
-    int first_batch = 0;
+    // lbfgsb_solve: steps enqueued since it began, redone ones included (Opts::seq), and the next one to report
+    unsigned steps_enqueued = 0, note_at = 0;
     int steps_since_refresh;
     long long steps_since_set_x;
     bool x_set;
@@ -356,6 +355,8 @@ void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false) {
 
 // One iteration of Algorithm 1 as a fixed sequence of launches; nothing here waits for the device.
 void enqueue_step(lbfgsb_solver* s) {
+    s->op.seq = ++s->steps_enqueued;
+    s->op.note = s->op.seq == s->note_at;
     if (s->use_resident) {
         // (the periodic recomputation and the pending-update bookkeeping happen inside the kernel)
         launch_resident(s->dm, s->op, s->bf, s->obj.A, s->obj.b, 1, s->options.refresh_every, s->stream);
@@ -482,6 +483,23 @@ void fresh_scal(lbfgsb_solver* s) {
     s->h_scal->hist = s->bf.hist;
 }
 
+// The first bound that is no good, for the message (the device has found that there is one).
+int report_bounds(lbfgsb_solver* s, const double* l, const double* u) {
+    const int64_t n = s->dm.n;
+    std::vector<double> hl((size_t)n), hu((size_t)n);
+    HIP_TRY(hipMemcpyAsync(hl.data(), l, (size_t)n * 8, hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipMemcpyAsync(hu.data(), u, (size_t)n * 8, hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    for (int64_t i = 0; i < n; ++i)
+        if (!(hl[(size_t)i] <= hu[(size_t)i]))
+            return fail(LBFGSB_E_BOUNDS, "bounds cross or are NaN at index %lld (l = %g, u = %g)", (long long)i, hl[(size_t)i],
+                        hu[(size_t)i]);
+    for (int64_t i = 0; i < n; ++i)
+        if (!(hl[(size_t)i] > 0.0))
+            return fail(LBFGSB_E_BOUNDS, "the entropy regulariser needs l > 0 (l[%lld] = %g)", (long long)i, hl[(size_t)i]);
+    return fail(LBFGSB_E_BOUNDS, "a bound was no good when it was checked");
+}
+
 // The first x0_i outside its bounds, for the message (the device has found that there is one).
 int report_infeasible(lbfgsb_solver* s, const double* x0) {
     const int64_t n = s->dm.n;
@@ -555,13 +573,14 @@ int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj
                  void* workspace, size_t workspace_bytes, hipStream_t stream, size_t* total, bool fused_unaligned = true) {
     s->dm = make_dims(n, m, obj);
     s->options = o;
-    s->op = Opts{o.eps, o.armijo_c1, o.backtrack, o.tol, o.max_backtracks, o.tol_relative, o.max_iter, 0, 0.0, 0.0};
+    s->op = Opts{o.eps, o.armijo_c1, o.backtrack, o.tol, o.max_backtracks, o.tol_relative, o.max_iter, 0, 0.0, 0.0, nullptr, 0u, 0};
     s->obj = *obj;
     s->ge = make_geometry(s->dm, obj->A, fused_unaligned);
     s->stream = stream;
     s->h_scal = nullptr;
     s->owns_h_scal = false;
     s->h_flag = nullptr;
+    s->h_progress = nullptr;
     s->steps_since_refresh = 0;
     s->steps_since_set_x = 0;
     s->logi_full_left = 0;
@@ -632,6 +651,21 @@ int init_workspace(lbfgsb_solver* s, const double* l, const double* u, void* wor
     return LBFGSB_OK;
 }
 
+// The stopping quantity was computed from a gradient carried by recurrence: residual and gradient are recomputed from x
+// and the test is made again before convergence is declared (the status is then in the host copy).
+hipError_t confirm_convergence(lbfgsb_solver* s) {
+    launch_set_status(s->bf, LBFGSB_RUNNING, s->stream);
+    enqueue_eval(s, 0, true);          // (the scalar block has just been read: nothing is pending)
+    s->steps_since_refresh = 0;
+    Opts quiet = s->op;                // (not one of the steps the host is following)
+    quiet.progress = nullptr;
+    launch_gram(s->dm, quiet, s->ge, s->bf, 0, 1, s->stream);
+    if (s->after_retest) s->after_retest(s->after_retest_ctx);
+    const hipError_t e = read_scal(s);
+    s->last_read_was_retest = s->after_retest != nullptr;
+    return e;
+}
+
 constexpr int kPollMax = 64;   // steps between two looks at the device status, at most
 
 // The stopping logic of lbfgsb_solve, for a solver whose arguments have been checked.
@@ -657,29 +691,83 @@ int solve_impl(lbfgsb_solver* s, lbfgsb_info* info) {
     }
     long long steps = 0;
     s->last_read_was_retest = false;
+    // Where the host copy is pinned, the kernel that takes an iteration's stopping decision reports it there, and the
+    // host follows without stopping the device: when the outcome of a reporting step is known -- before that step's pass
+    // over A has begun -- it enqueues the steps up to the next one that reports and one or two behind it.  The first four
+    // steps report, then every fourth, in long runs every eighth (a report costs 4-6 us; a run that ends reports at once).
+    // A run that is over in k steps has enqueued 1 (k < 4) to 5 in vain, ~8 us each (none when the iteration limit ends it:
+    // no step is enqueued behind the first that can find the limit reached before that one has reported).  Waiting for the
+    // device every eight steps instead left it idle for ~25 us each time, and 0 to 7 steps in vain.
+    if (s->h_progress) {
+        struct Following {
+            lbfgsb_solver* s;
+            ~Following() { s->op.progress = nullptr; s->note_at = 0; }
+        } following{s};
+        volatile unsigned long long* seen = s->h_progress;
+        *seen = 0;
+        s->steps_enqueued = 0;
+        s->op.progress = s->h_progress;
+        s->note_at = 1;
+        unsigned reporting = 1;                              // the step whose outcome is waited for next
+        const long long left = s->options.max_iter - s->h_scal->iters + 1;   // (from what the host has last seen)
+        const unsigned limit = left < 1 ? 1u : (left > 0x7fffffff ? 0x7fffffffu : (unsigned)left);
+        auto next_report = [limit](unsigned k) {
+            const unsigned n = k + (k < 4 ? 1 : (k < 32 ? 4 : 8));
+            return k < limit && n > limit ? limit : n;
+        };
+        for (;;) {
+            unsigned upto = reporting + (reporting < 4 ? 1 : 2);
+            if (reporting <= limit && upto > limit) upto = limit;
+            while (s->steps_enqueued < upto && steps < cap) {
+                enqueue_step(s);
+                ++steps;
+                if (s->steps_enqueued == s->note_at) s->note_at = next_report(s->note_at);
+            }
+            HIP_TRY(hipGetLastError());
+            int st = LBFGSB_RUNNING;
+            for (unsigned spins = 1;; ++spins) {
+                const unsigned long long p = *seen;
+                st = (int)(unsigned)p;
+                if ((unsigned)(p >> 32) >= reporting || st != LBFGSB_RUNNING) break;
+                // (now and then: has the stream run dry, or failed?  then the read below says what there is to know)
+                if (spins % 4096 == 0) {
+                    if (hipStreamQuery(s->stream) != hipErrorNotReady) { st = -1; break; }
+                    (void)hipGetLastError();   // (a stream that is busy is no error)
+                }
+            }
+            if (st == LBFGSB_RUNNING && steps < cap) {
+                reporting = next_report(reporting);
+                continue;
+            }
+            HIP_TRY(read_scal(s));
+            s->last_read_was_retest = false;
+            st = s->h_scal->status;
+            if (st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0 && s->h_scal->iters > 0) {
+                HIP_TRY(confirm_convergence(s));
+                st = s->h_scal->status;
+            }
+            if (st != LBFGSB_RUNNING || steps >= cap) break;
+            // on with it (a parked step has been finished, or convergence was not confirmed): the device is idle
+            *seen = 0;
+            s->note_at = reporting = s->steps_enqueued + 1;
+        }
+        HIP_TRY(hipGetLastError());
+        if (info) fill_info(*s->h_scal, info);
+        return LBFGSB_OK;
+    }
     // A poll leaves the device idle for about 30 us (commit, copy of the scalar block, the host's wake-up and the next
     // launches), a step enqueued after the solver has stopped costs about 6.  Long runs are therefore polled less
     // often: the interval doubles whenever eight intervals' worth of steps have gone by, up to 64.
-    int batch = s->first_batch > 0 ? s->first_batch : s->options.poll_every;
-    bool first = s->first_batch > 0;
+    int batch = s->options.poll_every;
     for (;;) {
         for (int k = 0; k < batch; ++k) enqueue_step(s);
         steps += batch;
-        if (first) { batch = s->options.poll_every; first = false; }
-        else if (batch < kPollMax && steps >= 8ll * batch) batch = 2 * batch > kPollMax ? kPollMax : 2 * batch;
+        if (batch < kPollMax && steps >= 8ll * batch) batch = 2 * batch > kPollMax ? kPollMax : 2 * batch;
         HIP_TRY(read_scal(s));
         s->last_read_was_retest = false;
         int st = s->h_scal->status;
         if (st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0 && s->h_scal->iters > 0) {
-            // the stopping quantity was computed from a gradient carried by recurrence: recompute
-            // residual and gradient from x and test again before declaring convergence
-            launch_set_status(s->bf, LBFGSB_RUNNING, s->stream);
-            enqueue_eval(s, 0);
-            s->steps_since_refresh = 0;
-            launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream);
-            if (s->after_retest) s->after_retest(s->after_retest_ctx);
-            HIP_TRY(read_scal(s));
-            s->last_read_was_retest = s->after_retest != nullptr;
+            HIP_TRY(confirm_convergence(s));
             st = s->h_scal->status;
         }
         if (st != LBFGSB_RUNNING) break;
@@ -803,29 +891,22 @@ int lbfgsb_create(lbfgsb_solver** out, int64_t n, int m, const double* l, const 
         if (e != hipSuccess) { s->h_scal = nullptr; return bail(fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e))); }
         s->owns_h_scal = true;
         s->h_flag = (int*)((char*)s->h_scal + flag_at);
+        s->h_progress = (unsigned long long*)((char*)s->h_scal + flag_at + 32);
     }
-    // validate the bounds on the host
-    std::vector<double> hl((size_t)n), hu((size_t)n);
-    hipError_t e = hipMemcpyAsync(hl.data(), l, (size_t)n * 8, hipMemcpyDeviceToHost, s->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(hu.data(), u, (size_t)n * 8, hipMemcpyDeviceToHost, s->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
-    if (e != hipSuccess) return bail(fail(LBFGSB_E_HIP, "reading the bounds: %s", hipGetErrorString(e)));
-    for (int64_t i = 0; i < n; ++i)
-        if (!(hl[(size_t)i] <= hu[(size_t)i]))
-            return bail(fail(LBFGSB_E_BOUNDS, "bounds cross or are NaN at index %lld (l = %g, u = %g)", (long long)i,
-                             hl[(size_t)i], hu[(size_t)i]));
     {
-        bool same = true;
-        for (int64_t i = 1; same && i < n; ++i) same = hl[(size_t)i] == hl[0] && hu[(size_t)i] == hu[0];
-        s->op.uniform_bounds = same ? 1 : 0;
-        s->op.lo = hl[0];
-        s->op.hi = hu[0];
+        // the device looks at the bounds; only to name an offending one does the host fetch them
+        static_assert(sizeof(BoundsReport) <= sizeof(Scal), "reported where the scalar block's copy will be");
+        BoundsReport* br = (BoundsReport*)s->h_scal;
+        std::memset(br, 0, sizeof *br);
+        launch_check_bounds(s->dm, l, u, br, s->stream);
+        hipError_t e = hipStreamSynchronize(s->stream);
+        if (e == hipSuccess) e = hipGetLastError();
+        if (e != hipSuccess) return bail(fail(LBFGSB_E_HIP, "reading the bounds: %s", hipGetErrorString(e)));
+        if (br->flag[0] || (obj->kind == LBFGSB_OBJ_OT_ENTROPY && br->flag[2])) return bail(report_bounds(s, l, u));
+        s->op.uniform_bounds = br->flag[1] ? 0 : 1;
+        s->op.lo = br->lo;
+        s->op.hi = br->hi;
     }
-    if (obj->kind == LBFGSB_OBJ_OT_ENTROPY)
-        for (int64_t i = 0; i < n; ++i)
-            if (!(hl[(size_t)i] > 0.0))
-                return bail(fail(LBFGSB_E_BOUNDS, "the entropy regulariser needs l > 0 (l[%lld] = %g)", (long long)i,
-                                 hl[(size_t)i]));
     rc = init_workspace(s, l, u, workspace, total);
     if (rc) return bail(rc);
     *out = s;
@@ -1110,8 +1191,8 @@ struct lbfgsb_auglag {
     const double* d_c;
     double *beta_c, *omega_c;
     const double* res_c;     // where the inner solver leaves a_r . x - beta_r of the constraint rows after an evaluation
-    double *lambda, *red;    // multipliers; red[0] = violation, red[1] = penalty term
-    double* h_red;           // pinned host copy of red
+    double* lambda;          // multipliers
+    double* h_red;           // pinned, written by k_al_update: [0] violation, [1] penalty term
     double rho;
     hipStream_t stream;
     // stacked variant only: the constraint rows inside the caller's matrix, and n_eq doubles of scratch (the
@@ -1177,7 +1258,7 @@ __global__ void k_al_shift_g(int64_t n_eq, int64_t cols, int64_t ld, const T* __
 
 // One workgroup.  res holds a_r . x - beta_r of the constraint rows, freshly evaluated at x:
 // h_r = res_r - lambda_r/rho; with update != 0 the multipliers become lambda + rho h.  red[0] = ||h||_inf,
-// red[1] = rho/2 sum (h + lambda/rho)^2 (the penalty term at the OLD multipliers).
+// red[1] = rho/2 sum (h + lambda/rho)^2 (the penalty term at the OLD multipliers); red is pinned host memory.
 // gate (or NULL): do nothing unless that scalar block says CONVERGED.
 __global__ __launch_bounds__(kBlock) void k_al_update(int64_t n_eq, double rho, int update,
                                                       const double* __restrict__ res, double* __restrict__ lambda,
@@ -1207,7 +1288,7 @@ __global__ __launch_bounds__(kBlock) void k_al_update(int64_t n_eq, double rho, 
 }
 
 size_t al_extra_bytes(int64_t rows, int64_t n_eq) {
-    return align_up((size_t)rows * 8) * 2 + 2 * align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8) + align_up(64);
+    return align_up((size_t)rows * 8) * 2 + 2 * align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8);
 }
 
 int check_al(int64_t n, const lbfgsb_objective* o, int64_t n_eq) {
@@ -1230,7 +1311,7 @@ int check_al_rows(const lbfgsb_objective* o, int64_t n_eq, const double* C, cons
 }
 
 size_t al_rows_extra_bytes(int64_t n_eq) {
-    return 3 * align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8) + align_up(64);
+    return 3 * align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8);
 }
 
 // residual (all rows) and gradient recomputed from x unless they already are
@@ -1291,7 +1372,6 @@ int lbfgsb_auglag_create(lbfgsb_auglag** out, int64_t n, int m, const double* l,
     al->beta_c = beta + rows_data; al->omega_c = omega + rows_data;
     al->lambda = (double*)w; w += align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8);
     al->coef = (double*)w; w += align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8);
-    al->red = (double*)w;
     al->c_rows = (const char*)obj->A + (size_t)rows_data * (size_t)obj->ld * (obj->dtype == LBFGSB_F64 ? 8 : 4);
     lbfgsb_objective inner_obj = *obj;
     inner_obj.b = beta;
@@ -1352,8 +1432,7 @@ int lbfgsb_auglag_create_rows(lbfgsb_auglag** out, int64_t n, int m, const doubl
     char* w = (char*)workspace + align_up(inner_bytes);
     al->beta_c = (double*)w; w += slot;
     al->omega_c = (double*)w; w += slot;
-    al->lambda = (double*)w; w += slot;
-    al->red = (double*)w;
+    al->lambda = (double*)w;
     inner_obj.extra_target = al->beta_c;
     inner_obj.extra_weight = al->omega_c;
     rc = lbfgsb_create(&al->inner, n, m, l, u, &inner_obj, opt, workspace, inner_bytes, hip_stream);
@@ -1408,8 +1487,7 @@ int lbfgsb_auglag_create_marginals(lbfgsb_auglag** out, int m, const double* l, 
     char* w = (char*)workspace + align_up(inner_bytes);
     al->beta_c = (double*)w; w += slot;
     al->omega_c = (double*)w; w += slot;
-    al->lambda = (double*)w; w += slot;
-    al->red = (double*)w;
+    al->lambda = (double*)w;
     inner_obj.b = al->beta_c;
     inner_obj.row_weight = al->omega_c;
     int rc = lbfgsb_create(&al->inner, n, m, l, u, &inner_obj, opt, workspace, inner_bytes, hip_stream);
@@ -1449,33 +1527,27 @@ int lbfgsb_auglag_solve(lbfgsb_auglag* al, const double* x0, lbfgsb_auglag_info*
     // here or let a following read of the scalar block do it
     auto measure = [&](int update, bool wait) -> hipError_t {
         hipLaunchKernelGGL(k_al_update, dim3(1), dim3(kBlock), 0, al->stream, al->n_eq, al->rho, update, al->res_c,
-                           al->lambda, al->red, (const Scal*)nullptr);
-        hipError_t e = hipMemcpyAsync(al->h_red, al->red, 16, hipMemcpyDeviceToHost, al->stream);
-        if (e != hipSuccess || !wait) return e;
-        return hipStreamSynchronize(al->stream);
+                           al->lambda, al->h_red, (const Scal*)nullptr);
+        return wait ? hipStreamSynchronize(al->stream) : hipSuccess;
     };
     // The multiplier update of an inner solve whose convergence is being confirmed rides on that confirmation's wait:
     // residuals are fresh behind the re-evaluation, and the kernel does nothing unless the status says CONVERGED.
     s->after_retest = [](void* ctx) {
         lbfgsb_auglag* a = (lbfgsb_auglag*)ctx;
         hipLaunchKernelGGL(k_al_update, dim3(1), dim3(kBlock), 0, a->stream, a->n_eq, a->rho, 1, a->res_c, a->lambda,
-                           a->red, (const Scal*)a->inner->bf.scal);
-        (void)hipMemcpyAsync(a->h_red, a->red, 16, hipMemcpyDeviceToHost, a->stream);
+                           a->h_red, (const Scal*)a->inner->bf.scal);
     };
     s->after_retest_ctx = al;
     struct HookReset { lbfgsb_solver* s; ~HookReset() { s->after_retest = nullptr; s->after_retest_ctx = nullptr; } } hook_reset{s};
     HIP_TRY(measure(0, true));
     double viol_prev = al->h_red[0];
     out.violation = viol_prev;
-    long long prev_inner = 0;
     for (int it = 0; it < al->ao.max_outer; ++it) {
         if (it > 0 && al->c_rows) {
             // new targets/weights of the stacked constraint rows: the pair memory is cleared, and f and g at the
             // unchanged x are shifted by the constraint rows' share (residuals and gradient are fresh at this point)
-            const double f_old = s->h_scal->f;
-            fresh_scal(s);
-            s->h_scal->f = f_old;
-            HIP_TRY(hipMemcpyAsync(s->bf.scal, s->h_scal, sizeof(Scal), hipMemcpyHostToDevice, s->stream));
+            launch_restart(s->bf, s->stream);
+            s->h_scal->iters = 0;
             hipLaunchKernelGGL(k_al_shift_rows, dim3(1), dim3(kBlock), 0, al->stream, al->n_eq, al->rho, al->d_c,
                                (const double*)al->lambda, al->beta_c, al->omega_c, (double*)al->res_c, al->coef, s->bf.scal);
             int gb = (int)((s->dm.cols + 255) / 256);
@@ -1496,12 +1568,8 @@ int lbfgsb_auglag_solve(lbfgsb_auglag* al, const double* x0, lbfgsb_auglag_info*
             if (rc) return rc;
         }
         lbfgsb_info ii;
-        // (an inner solve that follows one which needed at most two iterations is likely to be over at once)
-        s->first_batch = (it > 0 && prev_inner <= 2) ? 1 : 0;
         rc = lbfgsb_solve(s, &ii);
-        s->first_batch = 0;
         if (rc) return rc;
-        prev_inner = ii.iters;
         out.outer = it + 1;
         out.inner_iters += ii.iters;
         out.pg2 = ii.pg2;

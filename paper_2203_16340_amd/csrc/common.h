@@ -99,7 +99,17 @@ struct Opts {
     // them from here instead of streaming l and u
     int uniform_bounds;
     double lo, hi;
+    // lbfgsb_solve: the kernel that decides whether an iteration goes on writes `seq` and the status here, in pinned host
+    // memory, so that the host follows the run without stopping the device (null: a step on its own, nothing is written):
+    // always when the run is over, else where `note` is set (the store holds the kernel's end up by 4-6 us)
+    unsigned long long* progress;
+    unsigned seq;
+    int note;
 };
+__device__ __forceinline__ void note_progress(const Opts& op, int status) {
+    if (op.progress && (op.note || status != LBFGSB_RUNNING))
+        *(volatile unsigned long long*)op.progress = ((unsigned long long)op.seq << 32) | (unsigned)status;
+}
 
 // ---- reductions ---------------------------------------------------------------------------------
 
@@ -581,11 +591,16 @@ void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffe
 bool gram_can_skip_close(const Dims& dm, const Geometry& ge);
 // host_scal: pinned host memory that receives the scalar block as well (null: device copy only)
 void launch_commit(const Dims& dm, const Buffers& bf, hipStream_t st, Scal* host_scal = nullptr);
+// lbfgsb_create.  What the bounds are like, in pinned host memory: [0] some l_i > u_i or NaN, [1] not all pairs are the same,
+// [2] some l_i is not positive; the first pair.
+struct BoundsReport { int flag[3]; double lo, hi; };
+void launch_check_bounds(const Dims& dm, const double* l, const double* u, BoundsReport* host, hipStream_t st);
 // lbfgsb_set_x.  launch_check_box: *host_flag (pinned) becomes 1 if some x0_i is outside its bounds or NaN;
 // launch_start: x = x0 (unless they are the same array) and a fresh scalar block; launch_check_finite: *host_flag becomes
 // 1 if some g_i is not finite.
 void launch_check_box(const Dims& dm, const Opts& op, const Buffers& bf, const double* x0, int* host_flag, hipStream_t st);
 void launch_start(const Dims& dm, const Buffers& bf, const double* x0, hipStream_t st);
+void launch_restart(const Buffers& bf, hipStream_t st);   // a fresh scalar block that keeps f (x stays)
 void launch_check_finite(const Dims& dm, const double* g, int* host_flag, hipStream_t st);
 // store_d: also keep d itself (the primitive-level hooks read it; an iteration only needs the two candidates)
 bool dir_folds_extra_rows(const Dims& dm);

@@ -72,8 +72,11 @@ __global__ __launch_bounds__(kBlock) void k_gram(int64_t n, int m, int E, Opts o
     const int hdr = lane < 16 ? reinterpret_cast<const int*>(scal)[lane] : 0;
     if (__shfl(hdr, offsetof(Scal, status) / 4) != LBFGSB_RUNNING) {
         // a step that finds the solver parked by the short logistic sequence is counted, so that the host can redo it
-        if (__shfl(hdr, offsetof(Scal, status) / 4) == kStatusBail && evaluate_stop && !dbg_inputs && blockIdx.x == 0 && tid == 0)
-            scal->bail_skipped += 1;
+        const int status = __shfl(hdr, offsetof(Scal, status) / 4);
+        if (evaluate_stop && !dbg_inputs && blockIdx.x == 0 && tid == 0) {
+            if (status == kStatusBail) scal->bail_skipped += 1;
+            note_progress(op, status);
+        }
         return;
     }
     int head = __shfl(hdr, offsetof(Scal, head) / 4), c = __shfl(hdr, offsetof(Scal, count) / 4);
@@ -266,6 +269,7 @@ __global__ __launch_bounds__(kBlock) void k_gram(int64_t n, int m, int E, Opts o
     }
     __syncthreads();
     recursion_on_coefficients(G, Vp, c, head, m, op, scal, red[0], red[1], red[2], red[3], yn_old, alpha_s, dbg_inputs, evaluate_stop);
+    if (tid == 0 && evaluate_stop) note_progress(op, scal->status);
 }
 
 
@@ -377,8 +381,11 @@ __global__ __launch_bounds__(kBlock) void k_gram_mfma(int64_t n, int m, Opts op,
     const int hdr = lane < 16 ? reinterpret_cast<const int*>(scal)[lane] : 0;
     if (__shfl(hdr, offsetof(Scal, status) / 4) != LBFGSB_RUNNING) {
         // a step that finds the solver parked by the short logistic sequence is counted, so that the host can redo it
-        if (__shfl(hdr, offsetof(Scal, status) / 4) == kStatusBail && evaluate_stop && !dbg_inputs && blockIdx.x == 0 && tid == 0)
-            scal->bail_skipped += 1;
+        const int status = __shfl(hdr, offsetof(Scal, status) / 4);
+        if (evaluate_stop && !dbg_inputs && blockIdx.x == 0 && tid == 0) {
+            if (status == kStatusBail) scal->bail_skipped += 1;
+            note_progress(op, status);
+        }
         return;
     }
     int head = __shfl(hdr, offsetof(Scal, head) / 4), c = __shfl(hdr, offsetof(Scal, count) / 4);
@@ -526,6 +533,7 @@ __global__ __launch_bounds__(kBlock) void k_gram_mfma(int64_t n, int m, Opts op,
     }
     __syncthreads();
     recursion_on_coefficients(G, Vp, c, head, m, op, scal, red[0], red[1], red[2], red[3], yn_old, alpha_s, dbg_inputs, evaluate_stop);
+    if (tid == 0 && evaluate_stop) note_progress(op, scal->status);
 }
 
 
@@ -729,8 +737,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int hdr = lane < 16 ? reinterpret_cast<const int*>(scal)[lane] : 0;
     if (__shfl(hdr, offsetof(Scal, status) / 4) != LBFGSB_RUNNING) {
         // a step that finds the solver parked by the short logistic sequence is counted, so that the host can redo it
-        if (__shfl(hdr, offsetof(Scal, status) / 4) == kStatusBail && evaluate_stop && !dbg_inputs && blockIdx.x == 0 && tid == 0)
-            scal->bail_skipped += 1;
+        const int status = __shfl(hdr, offsetof(Scal, status) / 4);
+        if (evaluate_stop && !dbg_inputs && blockIdx.x == 0 && tid == 0) {
+            if (status == kStatusBail) scal->bail_skipped += 1;
+            note_progress(op, status);
+        }
         return;
     }
     int head = __shfl(hdr, offsetof(Scal, head) / 4), c = __shfl(hdr, offsetof(Scal, count) / 4);
@@ -757,6 +768,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     if (no_close) return;   // the direction kernel adds the partial sums and does the rest
     if (!reduce_partials(grampart, kWideNE, scal, &flag, tot)) return;
     wide_finish(tot, Gs, alpha_s, scal, m, c, head, w.base_slot, op, yn_old, dbg_inputs, evaluate_stop, true);
+    if (tid == 0 && evaluate_stop) note_progress(op, scal->status);
 }
 
 // (any even n: below 2^17 entries the grid stays small enough for the one-level sum of the partials)

@@ -82,7 +82,10 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
     __syncthreads();
     if (sc.status != LBFGSB_RUNNING) {
         // a step that finds the solver parked by the short logistic sequence is counted, so that the host can redo it
-        if (sc.status == kStatusBail && tid == 0) scal->bail_skipped = sc.bail_skipped + 1;
+        if (tid == 0) {
+            if (sc.status == kStatusBail) scal->bail_skipped = sc.bail_skipped + 1;
+            note_progress(op, sc.status);
+        }
         return;
     }
     int head, c;
@@ -188,6 +191,7 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
     if (tid == 0 && c > 0) sc.ynorm2[newest] = ynew;
     recursion_on_coefficients(G, Vp, c, head, m, op, &sc, G[(2 * c) * Vp + 2 * c], pginf, st3[0], ynew, yn_old, alpha_s, 0, 1);
     __syncthreads();
+    if (tid == 0) note_progress(op, sc.status);
     if (sc.status == LBFGSB_RUNNING) {
         if (tid < V0) {
             const int k = logical(tid);

@@ -51,6 +51,30 @@ __global__ __launch_bounds__(kBlock) void k_check_box(int64_t n, Opts op, const 
     }
     if (bad) *host_flag = 1;
 }
+__global__ __launch_bounds__(kBlock) void k_check_bounds(int64_t n, const double* __restrict__ l, const double* __restrict__ u,
+                                                         BoundsReport* __restrict__ host) {
+    const double l0 = l[0], u0 = u[0];
+    bool crossed = false, differ = false, not_positive = false;
+    for (int64_t i0 = (int64_t)blockIdx.x * kBlock + threadIdx.x; i0 < n; i0 += 4 * (int64_t)gridDim.x * kBlock) {
+        double lo[4], hi[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t i = i0 + k * (int64_t)gridDim.x * kBlock, ic = i < n ? i : n - 1;
+            lo[k] = l[ic]; hi[k] = u[ic];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            crossed = crossed || !(lo[k] <= hi[k]);
+            differ = differ || lo[k] != l0 || hi[k] != u0;
+            not_positive = not_positive || !(lo[k] > 0.0);
+        }
+    }
+    // (one store per wave at most: bounds that differ do so everywhere)
+    if (__any(crossed) && (threadIdx.x & 63) == 0) host->flag[0] = 1;
+    if (__any(differ) && (threadIdx.x & 63) == 0) host->flag[1] = 1;
+    if (__any(not_positive) && (threadIdx.x & 63) == 0) host->flag[2] = 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) { host->lo = l0; host->hi = u0; }
+}
 __global__ __launch_bounds__(kBlock) void k_check_finite(int64_t n, const double* __restrict__ g, int* __restrict__ host_flag) {
     bool bad = false;
     for (int64_t i0 = (int64_t)blockIdx.x * kBlock + threadIdx.x; i0 < n; i0 += 4 * (int64_t)gridDim.x * kBlock) {
@@ -78,9 +102,28 @@ __global__ __launch_bounds__(kBlock) void k_start(int64_t n, const double* x0, d
     if (x0 == x) return;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) x[i] = x0[i];
 }
+__global__ __launch_bounds__(kBlock) void k_restart(Scal* scal, lbfgsb_iter_record* hist) {
+    __shared__ double f;
+    if (threadIdx.x == 0) f = scal->f;
+    __syncthreads();
+    for (int k = threadIdx.x; k < (int)(sizeof(Scal) / 4); k += kBlock) reinterpret_cast<int*>(scal)[k] = 0;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        scal->status = LBFGSB_RUNNING;
+        scal->alpha_ub = 1.0;
+        scal->hist = hist;
+        scal->f = f;
+    }
+}
+void launch_restart(const Buffers& bf, hipStream_t st) {
+    hipLaunchKernelGGL(k_restart, dim3(1), dim3(kBlock), 0, st, bf.scal, bf.hist);
+}
 static int start_blocks(int64_t n) {
     const int64_t b = (n + 4 * kBlock - 1) / (4 * kBlock);
     return (int)(b > 1024 ? 1024 : b);
+}
+void launch_check_bounds(const Dims& dm, const double* l, const double* u, BoundsReport* host, hipStream_t st) {
+    hipLaunchKernelGGL(k_check_bounds, dim3(start_blocks(dm.n)), dim3(kBlock), 0, st, dm.n, l, u, host);
 }
 void launch_check_box(const Dims& dm, const Opts& op, const Buffers& bf, const double* x0, int* host_flag, hipStream_t st) {
     hipLaunchKernelGGL(k_check_box, dim3(start_blocks(dm.n)), dim3(kBlock), 0, st, dm.n, op, x0, (const double*)bf.l,
@@ -241,7 +284,7 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
         __syncthreads();
         if (sc.status != LBFGSB_RUNNING) {
             // (the pass reads its status word from scal_next: it must not find an older one there)
-            if (blockIdx.x == 0 && tid == 0) { scal_next->status = sc.status; scal_next->fresh = 0; }
+            if (blockIdx.x == 0 && tid == 0) { scal_next->status = sc.status; scal_next->fresh = 0; note_progress(op, sc.status); }
             return;
         }
         head = sc.head; c = sc.count;
@@ -263,6 +306,7 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
         wide_finish(tot, Gs, alpha_s, &sc, m, c, head, base_slot, op, yn_old, 0, 1, blockIdx.x == 0);
         __syncthreads();                                           // the first wave's results are in the copy
         if (blockIdx.x == 0) {
+            if (tid == 0) note_progress(op, sc.status);
             for (int k = tid; k < kScalWords; k += kBlock) {
                 int v = reinterpret_cast<const int*>(&sc)[k];
                 if (k == (int)(offsetof(Scal, fresh) / 4)) v = 1;

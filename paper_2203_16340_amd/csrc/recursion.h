@@ -32,6 +32,10 @@ __device__ __forceinline__ void recursion_on_coefficients(const double* G, int V
     const int tid = threadIdx.x, lane = tid & 63;
     if (tid < 64) {
         const int i = lane;   // lane i owns pair i (oldest = 0)
+        // (the same in every lane: from here on in a scalar register, so that the loops below are branches and not masks)
+        c = __builtin_amdgcn_readfirstlane(c);
+        Vp = __builtin_amdgcn_readfirstlane(Vp);
+        const double pgn = sqrt(gg);
         // what the stopping test at the end reads from the scalar block, requested now: behind the recursion these
         // were three dependent trips (each read sits under a test of the one before)
         int tol_resolved = 1, status0 = LBFGSB_RUNNING;
@@ -52,8 +56,10 @@ __device__ __forceinline__ void recursion_on_coefficients(const double* G, int V
         const unsigned long long pm = __ballot(pass);
         double alpha_i = 0.0, coef_s = 0.0, gamma = 1.0;
         if (c <= kRecFast) {
-            // every entry of G this lane needs, fetched at once; the three loops then run on registers and
-            // scalar-register broadcasts only.  Same operations in the same order as the general form below.
+            // Every entry of G this lane needs, fetched at once; the three loops then run on registers and
+            // scalar-register broadcasts only.  Row i is scaled by 1/rho_i beforehand, and is zero where it has no say
+            // (pairs that fail the gate; in the first loop pairs older than k, in the second newer ones), so a step of
+            // the chain is one broadcast and one multiply-add, and a lane's value stays what it was at its own step.
             double gsy[kRecFast], gyy[kRecFast], gys[kRecFast];
 #pragma unroll
             for (int k = 0; k < kRecFast; ++k) {
@@ -62,31 +68,30 @@ __device__ __forceinline__ void recursion_on_coefficients(const double* G, int V
                 gyy[k] = in ? G[(c + i) * Vp + (c + k)] : 0.0;    // <y_i, y_k>
                 gys[k] = in ? G[(c + i) * Vp + k] : 0.0;          // <y_i, s_k>
             }
-            double part_s = i < c ? G[i * Vp + 2 * c] : 0.0;      // <s_i, g>
-            double tsum = i < c ? G[(c + i) * Vp + 2 * c] : 0.0;  // <y_i, g>
-#pragma unroll
-            for (int k = kRecFast - 1; k >= 0; --k) {
-                if (k < c) {
-                    double ak = lane_value(part_s * inv, k);
-                    if (!((pm >> k) & 1ull)) ak = 0.0;
-                    if (i == k) alpha_i = ak;
-                    part_s = fma(-ak, gsy[k], part_s);
-                }
-            }
-            if (c > 0 && ((pm >> (c - 1)) & 1ull)) gamma = lane_value(rho / yn, c - 1);
-#pragma unroll
-            for (int k = 0; k < kRecFast; ++k)
-                if (k < c) tsum = fma(-lane_value(alpha_i, k), gyy[k], tsum);
-            double by = gamma * tsum;
+            const double sg = i < c ? G[i * Vp + 2 * c] : 0.0;         // <s_i, g>
+            double tsum = i < c ? G[(c + i) * Vp + 2 * c] : 0.0;       // <y_i, g>
 #pragma unroll
             for (int k = 0; k < kRecFast; ++k) {
+                gsy[k] = pass && k > i ? gsy[k] * inv : 0.0;
+                gys[k] = pass && k < i ? gys[k] * inv : 0.0;
+            }
+            alpha_i = pass ? sg * inv : 0.0;
+#pragma unroll
+            for (int k = kRecFast - 1; k >= 0; --k)
+                if (k < c) alpha_i = fma(-lane_value(alpha_i, k), gsy[k], alpha_i);
+            if (c > 0 && ((pm >> (c - 1)) & 1ull)) gamma = lane_value(rho / yn, c - 1);
+            double tsum2 = 0.0;
+#pragma unroll
+            for (int k = 0; k < kRecFast; k += 2) {
                 if (k < c) {
-                    double ck = lane_value(alpha_i - by * inv, k);
-                    if (!((pm >> k) & 1ull)) ck = 0.0;
-                    if (i == k) coef_s = ck;
-                    if (i > k) by = fma(ck, gys[k], by);
+                    tsum = fma(-lane_value(alpha_i, k), gyy[k], tsum);
+                    tsum2 = fma(-lane_value(alpha_i, k + 1), gyy[k + 1], tsum2);   // (zero past the last pair)
                 }
             }
+            coef_s = pass ? alpha_i - gamma * (tsum + tsum2) * inv : 0.0;
+#pragma unroll
+            for (int k = 0; k < kRecFast; ++k)
+                if (k < c) coef_s = fma(-lane_value(coef_s, k), gys[k], coef_s);
         } else {
             // first loop: alpha_k, newest to oldest.  Steps of pairs that fail the gate run with alpha_k = 0;
             // a lane's row is dead once its own alpha has been taken, so updating it further is harmless.
@@ -130,7 +135,6 @@ __device__ __forceinline__ void recursion_on_coefficients(const double* G, int V
             scal->delta[2 * c] = gamma;
             scal->pairs_used = __popcll(pm);
             if (evaluate_stop) {
-                const double pgn = sqrt(gg);
                 scal->pg2 = pgn;
                 scal->pginf = pginf;
                 scal->n_fixed = (long long)nfixed;

@@ -139,10 +139,15 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
     // g = A^T r: the periodic recomputation, and the one before convergence is declared), or the pass of an iteration.
     int steps = 0;
     bool want_eval = false;
+    int first_V = -1, first_ra = 0, first_rb = 0;   // this thread's first entry of the Gram matrix, for first_V vectors
     for (;;) {
         if (!want_eval && steps >= a.max_steps) break;
         if (!want_eval && a.refresh_every > 0 && since >= a.refresh_every) want_eval = true;
 
+        // (the same in every thread: in scalar registers from here on)
+        c = __builtin_amdgcn_readfirstlane(c);
+        head = __builtin_amdgcn_readfirstlane(head);
+        since = __builtin_amdgcn_readfirstlane(since);
         const int V = 2 * c + 1, Vp = V + 1;
         const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;
         auto vec = [&](int j) __attribute__((always_inline)) -> const double* {
@@ -179,9 +184,14 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                     int ra = 0, rb = 0;
                     double s = 0.0;
                     if (e < E) {
-                        int q = e;
-                        while (q >= V - ra) { q -= V - ra; ++ra; }
-                        rb = ra + q;
+                        if (e0 > 0 || V != first_V) {        // (which entry this is changes with the number of pairs only)
+                            int q = e;
+                            while (q >= V - ra) { q -= V - ra; ++ra; }
+                            rb = ra + q;
+                            if (e0 == 0) { first_ra = ra; first_rb = rb; }
+                        } else {
+                            ra = first_ra; rb = first_rb;
+                        }
                         const double *va = vec(ra) + sub, *vb = vec(rb) + sub, *vm = msk + sub;
                         for (int i0 = 0; i0 < np; i0 += 16) {
                             double mv[4], av[4], bv[4];
@@ -196,6 +206,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                     if (e < E && sub == 0) { G[ra * Vp + rb] = s; G[rb * Vp + ra] = s; }
                 }
             }
+            first_V = V;
             __syncthreads();
             // ---- Algorithm 3 on coefficients (wave 0), the stopping test with it
             if (tid < 64) {
@@ -266,7 +277,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                     for (int k = 0; k < 6; ++k) s6[k] += redD[w * 7 + k];
                     ubt = fmin(ubt, redD[w * 7 + 6]);
                 }
-                branch = (s6[0] <= -op.eps * s6[1] && s6[1] >= op.eps) ? 1 : 2;
+                branch = __builtin_amdgcn_readfirstlane((s6[0] <= -op.eps * s6[1] && s6[1] >= op.eps) ? 1 : 2);
                 gp = branch == 1 ? s6[0] : s6[3];
                 alpha_ub = branch == 1 ? 1.0 : ubt;
                 ps = branch == 1 ? p1s : p2s;

@@ -654,8 +654,8 @@ int init_workspace(lbfgsb_solver* s, const double* l, const double* u, void* wor
 // The stopping quantity was computed from a gradient carried by recurrence: residual and gradient are recomputed from x
 // and the test is made again before convergence is declared (the status is then in the host copy).
 hipError_t confirm_convergence(lbfgsb_solver* s) {
-    launch_set_status(s->bf, LBFGSB_RUNNING, s->stream);
-    enqueue_eval(s, 0, true);          // (the scalar block has just been read: nothing is pending)
+    launch_reopen(s->dm, s->bf, s->stream);
+    enqueue_eval(s, 0, true);          // (nothing is pending)
     s->steps_since_refresh = 0;
     Opts quiet = s->op;                // (not one of the steps the host is following)
     quiet.progress = nullptr;
@@ -725,8 +725,9 @@ int solve_impl(lbfgsb_solver* s, lbfgsb_info* info) {
             }
             HIP_TRY(hipGetLastError());
             int st = LBFGSB_RUNNING;
+            unsigned long long p = 0;
             for (unsigned spins = 1;; ++spins) {
-                const unsigned long long p = *seen;
+                p = *seen;
                 st = (int)(unsigned)p;
                 if ((unsigned)(p >> 32) >= reporting || st != LBFGSB_RUNNING) break;
                 // (now and then: has the stream run dry, or failed?  then the read below says what there is to know)
@@ -739,12 +740,18 @@ int solve_impl(lbfgsb_solver* s, lbfgsb_info* info) {
                 reporting = next_report(reporting);
                 continue;
             }
-            HIP_TRY(read_scal(s));
-            s->last_read_was_retest = false;
-            st = s->h_scal->status;
-            if (st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0 && s->h_scal->iters > 0) {
+            if (st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0 && (unsigned)(p >> 32) >= 2) {
+                // (found in the second step or later, so at least one iteration is behind it: see the condition below)
                 HIP_TRY(confirm_convergence(s));
                 st = s->h_scal->status;
+            } else {
+                HIP_TRY(read_scal(s));
+                s->last_read_was_retest = false;
+                st = s->h_scal->status;
+                if (st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0 && s->h_scal->iters > 0) {
+                    HIP_TRY(confirm_convergence(s));
+                    st = s->h_scal->status;
+                }
             }
             if (st != LBFGSB_RUNNING || steps >= cap) break;
             // on with it (a parked step has been finished, or convergence was not confirmed): the device is idle
@@ -1256,6 +1263,55 @@ __global__ void k_al_shift_g(int64_t n_eq, int64_t cols, int64_t ld, const T* __
     }
 }
 
+// Both kernels and the fresh scalar block in one workgroup and one launch, for few and short constraint rows (the sum
+// constraint of a simplex is one).  Three launches into an idle stream took about as long as the host needs to make them.
+// Where every inner solve is short that counts: 28 of them over 8000 x 2000 and one constraint row, with k_reopen
+// (gram.hip), 8.65 -> 8.28 ms in all.  Beyond 16 entries per thread one workgroup has too few loads in flight, beyond 64
+// rows the targets take more than one wave: then the kernels above.
+constexpr int kShiftThreads = 1024;
+constexpr int kShiftRowsMax = 64;                        // (one wave's lanes)
+constexpr int64_t kShiftMax = 16 * kShiftThreads;        // matrix entries: at most 16 per thread
+template <typename T>
+__global__ __launch_bounds__(kShiftThreads) void k_al_shift(int64_t n_eq, double rho, const double* __restrict__ d,
+                                                            const double* __restrict__ lambda, double* __restrict__ beta,
+                                                            double* __restrict__ omega, double* __restrict__ res,
+                                                            Scal* __restrict__ scal, lbfgsb_iter_record* hist, int64_t cols,
+                                                            int64_t ld, const T* __restrict__ Crows, double* __restrict__ g) {
+    __shared__ double coef[kShiftRowsMax];
+    __shared__ double f;
+    const int tid = threadIdx.x;
+    if (tid < 64) {
+        double df = 0.0;
+        if (tid < n_eq) {
+            const double res_old = res[tid], w_old = omega[tid];
+            const double cx = res_old + beta[tid];
+            const double b_new = d[tid] - lambda[tid] / rho;
+            const double res_new = cx - b_new;
+            coef[tid] = rho * res_new - w_old * res_old;
+            df = 0.5 * (rho * res_new * res_new - w_old * res_old * res_old);
+            beta[tid] = b_new;
+            omega[tid] = rho;
+            res[tid] = res_new;
+        }
+        df = wave_sum(df);
+        if (tid == 0) f = scal->f + df;
+    }
+    __syncthreads();
+    for (int64_t j = tid; j < cols; j += kShiftThreads) {
+        double acc = 0.0;
+        for (int r = 0; r < (int)n_eq; ++r) acc = fma(coef[r], (double)Crows[r * ld + j], acc);
+        g[j] += acc;
+    }
+    for (int k = tid; k < (int)(sizeof(Scal) / 4); k += kShiftThreads) reinterpret_cast<int*>(scal)[k] = 0;
+    __syncthreads();
+    if (tid == 0) {
+        scal->status = LBFGSB_RUNNING;
+        scal->alpha_ub = 1.0;
+        scal->hist = hist;
+        scal->f = f;
+    }
+}
+
 // One workgroup.  res holds a_r . x - beta_r of the constraint rows, freshly evaluated at x:
 // h_r = res_r - lambda_r/rho; with update != 0 the multipliers become lambda + rho h.  red[0] = ||h||_inf,
 // red[1] = rho/2 sum (h + lambda/rho)^2 (the penalty term at the OLD multipliers); red is pinned host memory.
@@ -1546,18 +1602,30 @@ int lbfgsb_auglag_solve(lbfgsb_auglag* al, const double* x0, lbfgsb_auglag_info*
         if (it > 0 && al->c_rows) {
             // new targets/weights of the stacked constraint rows: the pair memory is cleared, and f and g at the
             // unchanged x are shifted by the constraint rows' share (residuals and gradient are fresh at this point)
-            launch_restart(s->bf, s->stream);
             s->h_scal->iters = 0;
-            hipLaunchKernelGGL(k_al_shift_rows, dim3(1), dim3(kBlock), 0, al->stream, al->n_eq, al->rho, al->d_c,
-                               (const double*)al->lambda, al->beta_c, al->omega_c, (double*)al->res_c, al->coef, s->bf.scal);
-            int gb = (int)((s->dm.cols + 255) / 256);
-            if (gb > 1024) gb = 1024;
-            if (s->dm.dtype == LBFGSB_F64)
-                hipLaunchKernelGGL(k_al_shift_g<double>, dim3(gb), dim3(256), 0, al->stream, al->n_eq, s->dm.cols, s->dm.ld,
-                                   (const double*)al->c_rows, (const double*)al->coef, s->bf.g);
-            else
-                hipLaunchKernelGGL(k_al_shift_g<float>, dim3(gb), dim3(256), 0, al->stream, al->n_eq, s->dm.cols, s->dm.ld,
-                                   (const float*)al->c_rows, (const double*)al->coef, s->bf.g);
+            const bool f64 = s->dm.dtype == LBFGSB_F64;
+            if (al->n_eq <= kShiftRowsMax && al->n_eq * s->dm.cols <= kShiftMax) {
+                if (f64)
+                    hipLaunchKernelGGL(k_al_shift<double>, dim3(1), dim3(kShiftThreads), 0, al->stream, al->n_eq, al->rho, al->d_c,
+                                       (const double*)al->lambda, al->beta_c, al->omega_c, (double*)al->res_c, s->bf.scal,
+                                       s->bf.hist, s->dm.cols, s->dm.ld, (const double*)al->c_rows, s->bf.g);
+                else
+                    hipLaunchKernelGGL(k_al_shift<float>, dim3(1), dim3(kShiftThreads), 0, al->stream, al->n_eq, al->rho, al->d_c,
+                                       (const double*)al->lambda, al->beta_c, al->omega_c, (double*)al->res_c, s->bf.scal,
+                                       s->bf.hist, s->dm.cols, s->dm.ld, (const float*)al->c_rows, s->bf.g);
+            } else {
+                launch_restart(s->bf, s->stream);
+                hipLaunchKernelGGL(k_al_shift_rows, dim3(1), dim3(kBlock), 0, al->stream, al->n_eq, al->rho, al->d_c,
+                                   (const double*)al->lambda, al->beta_c, al->omega_c, (double*)al->res_c, al->coef, s->bf.scal);
+                int gb = (int)((s->dm.cols + 255) / 256);
+                if (gb > 1024) gb = 1024;
+                if (f64)
+                    hipLaunchKernelGGL(k_al_shift_g<double>, dim3(gb), dim3(256), 0, al->stream, al->n_eq, s->dm.cols, s->dm.ld,
+                                       (const double*)al->c_rows, (const double*)al->coef, s->bf.g);
+                else
+                    hipLaunchKernelGGL(k_al_shift_g<float>, dim3(gb), dim3(256), 0, al->stream, al->n_eq, s->dm.cols, s->dm.ld,
+                                       (const float*)al->c_rows, (const double*)al->coef, s->bf.g);
+            }
             s->steps_since_refresh = 0;
             s->steps_since_set_x = 0;
         } else if (it > 0) {

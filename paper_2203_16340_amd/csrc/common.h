@@ -591,6 +591,7 @@ void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffe
 bool gram_can_skip_close(const Dims& dm, const Geometry& ge);
 // host_scal: pinned host memory that receives the scalar block as well (null: device copy only)
 void launch_commit(const Dims& dm, const Buffers& bf, hipStream_t st, Scal* host_scal = nullptr);
+void launch_reopen(const Dims& dm, const Buffers& bf, hipStream_t st);   // applies a pending update; CONVERGED -> RUNNING
 // lbfgsb_create.  What the bounds are like, in pinned host memory: [0] some l_i > u_i or NaN, [1] not all pairs are the same,
 // [2] some l_i is not positive; the first pair.
 struct BoundsReport { int flag[3]; double lo, hi; };

@@ -866,4 +866,16 @@ void launch_commit(const Dims& dm, const Buffers& bf, hipStream_t st, Scal* host
     hipLaunchKernelGGL(k_commit, dim3(1), dim3(64), 0, st, bf.scal, dm.m, host_scal);
 }
 
+// The same, and a run that ended in convergence is open again: the gradient it was judged by is about to be recomputed
+// from x and judged once more.  One launch behind the last step, where the host used to fetch the scalar block, wait, and
+// then set the status with a launch of its own.  NNLS 3001 x 301, whole solve: 405 -> 387 us.
+__global__ void k_reopen(Scal* scal, int m) {
+    if (threadIdx.x != 0) return;
+    apply_pending(scal, m);
+    if (scal->status == LBFGSB_CONVERGED) scal->status = LBFGSB_RUNNING;
+}
+void launch_reopen(const Dims& dm, const Buffers& bf, hipStream_t st) {
+    hipLaunchKernelGGL(k_reopen, dim3(1), dim3(64), 0, st, bf.scal, dm.m);
+}
+
 }  // namespace lb

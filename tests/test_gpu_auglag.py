@@ -156,3 +156,17 @@ def test_argument_errors():
     info = al.solve(to_dev(np.zeros(4)))
     assert info.status == L.CONVERGED and info.outer == 1 and info.violation == 0.0
     al.close()
+
+
+@pytest.mark.parametrize("rows,cols,n_eq", [(900, 256, 64), (900, 257, 64), (900, 200, 65), (900, 130, 3)])
+def test_change_of_targets_between_inner_solves(rows, cols, n_eq):
+    """f and g are shifted to the next targets and weights by one workgroup up to 64 rows and 16384 entries, by two
+    kernels beyond.  Three inner solves to a tight tolerance: a wrong shift would end the third elsewhere.  Each ends with
+    ||grad||_inf-like residuals of 1e-9 against curvatures of order 100, so x agrees far below 1e-6."""
+    cp = workloads.constrained_lsq(rows, cols, n_eq, 0, seed=31, m=8)
+    x_ref, lam_ref, _, iref = _run_oracle(cp, 1e-9, 1e-30, max_outer=3)
+    x, lam, info = _run_gpu(cp, 1e-9, 1e-30, max_outer=3)
+    assert info.outer == iref.outer == 3 and info.rho == iref.rho
+    assert rel_err(x, x_ref) <= 1e-6
+    assert rel_err(lam, lam_ref) <= 1e-5
+    assert info.f == pytest.approx(iref.f, rel=1e-7)

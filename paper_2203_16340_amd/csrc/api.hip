@@ -124,8 +124,12 @@ int check_options(const lbfgsb_options* o) {
     return LBFGSB_OK;
 }
 
-// fused_unaligned: the single-read pass may also take rows that do not start on 16-byte boundaries
-Geometry make_geometry(const Dims& dm, const void* A, bool fused_unaligned = true) {
+// Which of the single-read kernels may be chosen.  lbfgsb_solve_static, whose workspace is fixed, does with less where
+// their partial columns would not fit.
+enum SingleRead { kReadAligned = 0,   // the ring kernel, rows on 16-byte boundaries only
+                  kReadRing = 1,      // the ring kernel, any rows
+                  kReadAny = 2 };     // also the kernels for short rows and for symmetric matrices
+Geometry make_geometry(const Dims& dm, const void* A, SingleRead reads = kReadAny) {
     Geometry ge{};
     const int per16 = dm.dtype == LBFGSB_F32 ? 4 : 2;
     const bool aligned = ((uintptr_t)A % 16 == 0) && (dm.cols % per16 == 0) && (dm.ld % per16 == 0);
@@ -141,14 +145,14 @@ Geometry make_geometry(const Dims& dm, const void* A, bool fused_unaligned = tru
     if (rb < 1) rb = 1;
     ge.gemvt_rows_per_block = (dm.rows + rb - 1) / rb;
     ge.gemvt_row_blocks = (int)((dm.rows + ge.gemvt_rows_per_block - 1) / ge.gemvt_rows_per_block);
-    ge.fused_ok = !is_transport(dm.kind) && (aligned || fused_unaligned) &&
+    ge.fused_ok = !is_transport(dm.kind) && (aligned || reads >= kReadRing) &&
                   fused_shape_ok(dm, &ge.fused_variant, &ge.fused_blocks) ? 1 : 0;
     ge.narrow_variant = -1;
     if (ge.fused_ok) {
         int nv, nb;
-        if (narrow_shape_ok(dm, &nv, &nb)) { ge.narrow_variant = nv; ge.fused_blocks = nb; }
+        if (reads == kReadAny && narrow_shape_ok(dm, &nv, &nb)) { ge.narrow_variant = nv; ge.fused_blocks = nb; }
         int strips, grid;
-        if (sym_shape_ok(dm, &strips, &grid)) { ge.sym_strips = strips; ge.fused_blocks = grid; }
+        if (reads == kReadAny && sym_shape_ok(dm, &strips, &grid)) { ge.sym_strips = strips; ge.fused_blocks = grid; }
     }
     ge.gram_blocks = gram_blocks_for(dm.n, dm.m);
     int64_t db = (dm.n + kBlock - 1) / kBlock;
@@ -570,12 +574,12 @@ int check_create_args(int64_t n, int m, const double* l, const double* u, const 
 // Fills the host object for a checked problem: launch geometry, kernel preparation, and the device arrays carved
 // out of `workspace`.  Allocates nothing and touches no device memory; *total receives the bytes of workspace in use.
 int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj, const lbfgsb_options& o,
-                 void* workspace, size_t workspace_bytes, hipStream_t stream, size_t* total, bool fused_unaligned = true) {
+                 void* workspace, size_t workspace_bytes, hipStream_t stream, size_t* total, SingleRead reads = kReadAny) {
     s->dm = make_dims(n, m, obj);
     s->options = o;
     s->op = Opts{o.eps, o.armijo_c1, o.backtrack, o.tol, o.max_backtracks, o.tol_relative, o.max_iter, 0, 0.0, 0.0, nullptr, 0u, 0};
     s->obj = *obj;
-    s->ge = make_geometry(s->dm, obj->A, fused_unaligned);
+    s->ge = make_geometry(s->dm, obj->A, reads);
     s->stream = stream;
     s->h_scal = nullptr;
     s->owns_h_scal = false;
@@ -962,13 +966,14 @@ int lbfgsb_solve_static(int64_t n, int m, const double* l, const double* u, cons
     rc = check_create_args(n, m, l, u, obj, opt, sl->ptr, &o);
     if (rc) return rc;
     size_t need = lbfgsb_workspace_bytes(n, m, obj, &o);
-    bool fused_unaligned = true;
-    if (need > (size_t)LBFGSB_STATIC_SCRATCH_BYTES) {
-        // the partial columns of the single-read pass take the most room: unaligned rows that fit the array only with
-        // the two-pass kernels run on those
+    // the partial columns of the single-read kernels take the most room: a problem that does not fit the array with the
+    // kernel of its shape may fit it with a plainer one
+    SingleRead reads = kReadAny;
+    for (const SingleRead less : {kReadRing, kReadAligned}) {
+        if (need <= (size_t)LBFGSB_STATIC_SCRATCH_BYTES) break;
         const Dims dm = make_dims(n, m, obj);
-        const size_t without = make_layout(dm, make_geometry(dm, obj->A, false)).total;
-        if (without < need) { need = without; fused_unaligned = false; }
+        const size_t without = make_layout(dm, make_geometry(dm, obj->A, less)).total;
+        if (without < need) { need = without; reads = less; }
     }
     if (need == 0 || need > (size_t)LBFGSB_STATIC_SCRATCH_BYTES)
         return fail(LBFGSB_E_INVALID_ARG,
@@ -977,7 +982,7 @@ int lbfgsb_solve_static(int64_t n, int m, const double* l, const double* u, cons
     lbfgsb_solver* s = &sl->solver;
     if (s->timing || !s->ev0.empty()) return fail(LBFGSB_E_INVALID_ARG, "the static solver object is in an unexpected state");
     size_t total = 0;
-    rc = setup_solver(s, n, m, obj, o, sl->ptr, (size_t)LBFGSB_STATIC_SCRATCH_BYTES, (hipStream_t)hip_stream, &total, fused_unaligned);
+    rc = setup_solver(s, n, m, obj, o, sl->ptr, (size_t)LBFGSB_STATIC_SCRATCH_BYTES, (hipStream_t)hip_stream, &total, reads);
     if (rc) return rc;
     s->h_scal = &sl->h_scal;
     rc = check_box_chunked(s, l, u, x);

@@ -178,8 +178,11 @@ Geometry make_geometry(const Dims& dm, const void* A, SingleRead reads = kReadAn
         ge.ot_row_blocks = (int)((dm.rows + rpw - 1) / rpw);
         int64_t cb = (dm.cols + kCX - 1) / kCX;
         ge.ot_col_blocks = (int)(cb > 2048 ? 2048 : cb);
-        ge.ot_el_blocks = (int)(dm.rows > 512 ? 512 : dm.rows);
-        int64_t eb = (dm.n + kBlock - 1) / kBlock;
+        const int subs = ot_threads(dm) / kOtTile;
+        // (256 threads: whole rows; more: tiles of rows, one per sub-group and trip)
+        const int64_t tb = subs > 1 ? (dm.rows * ((dm.cols + kOtTile - 1) / kOtTile) + subs - 1) / subs : dm.rows;
+        ge.ot_el_blocks = (int)(tb > 512 ? 512 : tb);
+        int64_t eb = (dm.n + ot_threads(dm) - 1) / ot_threads(dm);
         ge.ls_blocks = (int)(eb > 512 ? 512 : eb);
     }
     return ge;

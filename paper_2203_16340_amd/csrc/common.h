@@ -445,18 +445,29 @@ __device__ __forceinline__ double column_sum(const double* __restrict__ wpart, i
 }
 
 // Sum of `count` doubles, identical in every workgroup that calls it (same order everywhere).
+template <int NT = kBlock>
 __device__ __forceinline__ double sum_all(const double* __restrict__ v, int count, double* lds) {
     double s[1] = {0.0};
-    for (int k0 = threadIdx.x; k0 < count; k0 += kBlock * 8) {
+    for (int k0 = threadIdx.x; k0 < count; k0 += NT * 8) {
         double t[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) t[k] = k0 + kBlock * k < count ? v[k0 + kBlock * k] : 0.0;
+        for (int k = 0; k < 8; ++k) t[k] = k0 + NT * k < count ? v[k0 + NT * k] : 0.0;
 #pragma unroll
         for (int k = 0; k < 8; ++k) s[0] += t[k];
     }
-    block_sum<1, kWaves>(s, lds);
+    block_sum<1, NT / 64>(s, lds);
     return s[0];
 }
+
+// Transport kinds: entries of a row of P that 256 threads take at a time, and the threads of a workgroup in the kernels
+// with a logarithm per entry (transport.hip): these end in an arrival at one address, so they have at most 512 workgroups,
+// and with 256 threads each those leave two wavefronts per SIMD to hide a memory trip and a logarithm behind each other,
+// sixteen entries in a row per thread at 2 10^6.  Shorter problems need fewer threads in all, and there the wider workgroups
+// only make every launch dearer, those that return at once included.  Entropy regulariser, whole runs, 256 / 1024 threads:
+// 4.4 10^5 entries 2355 / 2420 us, 10^6 3450 / 3387, 1.44 10^6 3920 / 3865, 2 10^6 4838 / 4700.
+constexpr int kOtTile = 256;
+constexpr int64_t kOtWideMin = 3 << 18;
+inline int ot_threads(const Dims& dm) { return dm.n >= kOtWideMin ? 1024 : 256; }
 
 // ---- launch geometry decided once at creation -------------------------------------------------------
 

@@ -129,25 +129,52 @@ __global__ __launch_bounds__(kBlock) void k_ot_cols(Dims dm, OtArgs a, int eval,
     if (tid == 0) losspart[blockIdx.x] = loss[0];
 }
 
-// g = M + lambda phi'(x) + K^T (omega . residual); the last workgroup adds up f.
-__global__ __launch_bounds__(kBlock) void k_ot_eval_finish(Dims dm, OtArgs a, int loss_parts,
+// The kernels with a logarithm per entry (ot_threads: why two workgroup sizes): calls f(i, j, row(i)) for this thread's
+// entries of P.  A workgroup of 256 threads takes whole rows; a larger one is made of sub-groups of kOtTile threads, each
+// of which walks over tiles (row i, columns kOtTile k ..).  (Tiles for 256 threads as well: 2-5 % slower whole runs at 4.4 10^5
+// entries, the divisions and the row's factor per tile.)
+template <int NT, typename R, typename F>
+__device__ __forceinline__ void for_entries(int64_t rows, int64_t cols, R row, F f) {
+    if constexpr (NT == kOtTile) {
+        for (int64_t i = blockIdx.x; i < rows; i += gridDim.x) {
+            const double ri = row(i);
+            for (int64_t j = threadIdx.x; j < cols; j += NT) f(i, j, ri);
+        }
+    } else {
+        constexpr int kSub = NT / kOtTile;
+        const int64_t tpr = (cols + kOtTile - 1) / kOtTile, step = (int64_t)gridDim.x * kSub;
+        const int64_t q = (int64_t)blockIdx.x * kSub + threadIdx.x / kOtTile;
+        const int64_t di = step / tpr, dk = step - di * tpr;
+        int64_t i = q / tpr, k = q - i * tpr;
+        while (i < rows) {
+            const int64_t j = k * kOtTile + threadIdx.x % kOtTile;
+            if (j < cols) f(i, j, row(i));
+            i += di;
+            k += dk;
+            if (k >= tpr) { k -= tpr; ++i; }
+        }
+    }
+}
+
+// g = M + lambda phi'(x) + K^T (omega . residual); the last workgroup adds up f.  (2 10^6 entries, entropy, against
+// workgroups of 256 threads: 31.1 -> 28.6 us; the logarithm is the larger part of it.)
+template <int NT>
+__global__ __launch_bounds__(NT, NT == 1024 ? 8 : 4) void k_ot_eval_finish(Dims dm, OtArgs a, int loss_parts,
                                                            const double* __restrict__ x, const double* __restrict__ res,
                                                            const double* __restrict__ losspart, double* __restrict__ g,
                                                            Scal* __restrict__ scal) {
-    __shared__ double red[kWaves];
+    __shared__ double red[NT / 64];
     __shared__ int flag;
     if (scal->status != LBFGSB_RUNNING) return;
     const int tid = threadIdx.x;
-    for (int64_t i = blockIdx.x; i < dm.rows; i += gridDim.x) {
-        const double ri = a.omega ? a.omega[i] * res[i] : 0.0;
-        for (int64_t j = tid; j < dm.cols; j += kBlock) {
-            const int64_t e = i * dm.cols + j;
-            const double cj = a.omega ? a.omega[dm.rows + j] * res[dm.rows + j] : 0.0;
-            g[e] = m_at(a.M, dm.dtype, i * dm.ld + j) + reg_slope(dm.kind, dm.lambda, x[e]) + (ri + cj);
-        }
-    }
+    auto row = [&](int64_t i) { return a.omega ? a.omega[i] * res[i] : 0.0; };
+    for_entries<NT>(dm.rows, dm.cols, row, [&](int64_t i, int64_t j, double ri) {
+        const int64_t e = i * dm.cols + j;
+        const double cj = a.omega ? a.omega[dm.rows + j] * res[dm.rows + j] : 0.0;
+        g[e] = m_at(a.M, dm.dtype, i * dm.ld + j) + reg_slope(dm.kind, dm.lambda, x[e]) + (ri + cj);
+    });
     if (!arrive_is_last(&scal->counters[kCntEvalFinish], &flag)) return;
-    const double f = sum_all(losspart, loss_parts, red);
+    const double f = sum_all<NT>(losspart, loss_parts, red);
     if (tid == 0) {
         scal->f = f;
         scal->fevals += 1;
@@ -252,6 +279,11 @@ __device__ __forceinline__ double entropy_h(double r) {
 // limit of 60 backtracks; only beyond those does the last workgroup of the last launch go on alone, one length at
 // a time.
 constexpr int kLsTail = 51;   // 2 + kLsBatch + kLsTail = 61 step lengths
+// In wide workgroups the tail's step lengths are taken in groups, a sweep over (x, p) each (they come from the cache after
+// the first): 51 sums and as many logarithms in flight take all registers of a SIMD for one wavefront.  First iteration of a
+// run at 2 10^6 entries: 545 -> 481 us for the 51 lengths (the update kernel 47 -> 43 us, the first two lengths 25 -> 23).
+// With 256 threads there are two wavefronts per SIMD either way, and groups gained nothing (4.4 10^5 entries).
+constexpr int ls_group(int threads) { return threads > 256 ? 17 : kLsTail; }
 
 // Armijo test of NTRY step lengths a_first, a_first * backtrack, ... (indices first, first + 1, ...) given their sums
 // tot[k] = sum_e x_e h(a_k p_e / x_e): the first acceptable one, or found = -1.
@@ -270,17 +302,43 @@ __device__ __forceinline__ void entropy_decide(const double (&tot)[NTRY], int fi
     a_last = av;
 }
 
+// block_sum for workgroups of many waves: thread k adds up the waves' sums of value k (every thread adding all of them
+// keeps K NW values in registers).  lds: (NW + 1) K doubles.
+template <int K, int NW>
+__device__ __forceinline__ void block_sum_by_thread(double (&v)[K], double* lds) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
+    __syncthreads();   // protect lds against readers of a previous use
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) lds[wave * K + k] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < K) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t += lds[w * K + threadIdx.x];
+        lds[NW * K + threadIdx.x] = t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = lds[NW * K + k];
+}
+
 // NPREV > 0: the launch before this one (NPREV step lengths from index first - NPREV on) ended without deciding;
 // every workgroup of this launch adds that launch's partial sums (prev) and takes its decision, and only if none of
 // those step lengths was acceptable goes on with its own.  NPREV == 0 with defer != 0: this launch leaves its decision
 // to the next one (no closing arrival).
-template <int NTRY, int NPREV>
-__global__ __launch_bounds__(kBlock) void k_ot_ls_entropy(Dims dm, Opts op, int loss_parts, int first, int last_resort,
+template <int NT, int NTRY, int GROUP, int NPREV>
+__global__ __launch_bounds__(NT, NT == 1024 ? (GROUP <= 2 ? 8 : 4) : 1) void k_ot_ls_entropy(Dims dm, Opts op, int loss_parts, int first, int last_resort,
                                                           int defer, const double* __restrict__ losspart,
                                                           const double* __restrict__ x, const double* __restrict__ p1,
                                                           const double* __restrict__ p2, Scal* __restrict__ scal,
                                                           const double* __restrict__ prev, double* __restrict__ lspart) {
-    __shared__ double red[kWaves * (NTRY > NPREV ? NTRY : NPREV)];
+    static_assert(NTRY % GROUP == 0, "whole groups");
+    constexpr int NW = NT / 64;
+    __shared__ double red[(NW + 1) * (GROUP > NPREV ? GROUP : NPREV)];
     __shared__ int flag;
     if (scal->status != LBFGSB_RUNNING) return;
     if (NPREV == 0 && first > 0 && scal->ls_ok) return;   // an earlier launch of this iteration found the step
@@ -292,12 +350,12 @@ __global__ __launch_bounds__(kBlock) void k_ot_ls_entropy(Dims dm, Opts op, int 
         double tp[NPREV];
 #pragma unroll
         for (int k = 0; k < NPREV; ++k) tp[k] = 0.0;
-        for (int b = tid; b < (int)gridDim.x; b += kBlock) {
+        for (int b = tid; b < (int)gridDim.x; b += NT) {
 #pragma unroll
             for (int k = 0; k < NPREV; ++k) tp[k] += prev[(int64_t)b * NPREV + k];
         }
-        const double tt = sum_all(losspart, loss_parts, red);
-        block_sum<NPREV, kWaves>(tp, red);
+        const double tt = sum_all<NT>(losspart, loss_parts, red);
+        block_sum<NPREV, NW>(tp, red);
         double a_prev = a0;
         for (int k = 0; k < first - NPREV; ++k) a_prev *= op.backtrack;
         int found;
@@ -314,49 +372,68 @@ __global__ __launch_bounds__(kBlock) void k_ot_ls_entropy(Dims dm, Opts op, int 
         }
         __syncthreads();   // (red is used again below)
     }
-    double s[NTRY];
-    double a_first = a0;
-    for (int k = 0; k < first; ++k) a_first *= op.backtrack;
+    auto group_sum = [&](double (&v)[GROUP]) {
+        if constexpr (NW > kWaves) block_sum_by_thread<GROUP, NW>(v, red);
+        else block_sum<GROUP, NW>(v, red);
+    };
+    double a_group = a0;
+    for (int k = 0; k < first; ++k) a_group *= op.backtrack;
+    const double a_first = a_group;
+#pragma unroll 1
+    for (int k0 = 0; k0 < NTRY; k0 += GROUP) {
+        double s[GROUP], a = a_group;
 #pragma unroll
-    for (int k = 0; k < NTRY; ++k) s[k] = 0.0;
-    for (int64_t e = (int64_t)blockIdx.x * kBlock + tid; e < dm.n; e += (int64_t)gridDim.x * kBlock) {
-        const double xe = x[e], ratio = p[e] / xe;
-        double a = a_first;
+        for (int k = 0; k < GROUP; ++k) s[k] = 0.0;
+        for (int64_t e = (int64_t)blockIdx.x * NT + tid; e < dm.n; e += (int64_t)gridDim.x * NT) {
+            const double xe = x[e], ratio = p[e] / xe;
+            a = a_group;
 #pragma unroll
-        for (int k = 0; k < NTRY; ++k) {
-            s[k] = fma(xe, entropy_h(a * ratio), s[k]);
-            a *= op.backtrack;
+            for (int k = 0; k < GROUP; ++k) {
+                s[k] = fma(xe, entropy_h(a * ratio), s[k]);
+                a *= op.backtrack;
+                // wide workgroups: one logarithm at a time, and the lengths not kept either: the registers hold the sums
+                if constexpr (NW > kWaves) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (GROUP > kLsBatch) asm volatile("" : "+v"(a));
+                }
+            }
         }
-    }
-    block_sum<NTRY, kWaves>(s, red);
-    if (tid == 0) {
+        for (int k = 0; k < GROUP; ++k) a_group *= op.backtrack;
+        group_sum(s);
+        if (tid == 0) {
 #pragma unroll
-        for (int k = 0; k < NTRY; ++k) lspart[(int64_t)blockIdx.x * NTRY + k] = s[k];
+            for (int k = 0; k < GROUP; ++k) lspart[(int64_t)blockIdx.x * NTRY + k0 + k] = s[k];
+        }
     }
     if (NPREV == 0 && defer) return;
     if (!arrive_is_last(&scal->counters[kCntLs], &flag)) return;
     const double gp = scal->gp;
-    const double tt = sum_all(losspart, loss_parts, red);
-    double tot[NTRY];
+    const double tt = sum_all<NT>(losspart, loss_parts, red);
+    int found = -1;
+    double a_acc = 0.0, av = a_first;
+#pragma unroll 1
+    for (int k0 = 0; k0 < NTRY && found < 0; k0 += GROUP) {
+        double tot[GROUP];
 #pragma unroll
-    for (int k = 0; k < NTRY; ++k) tot[k] = 0.0;
-    for (int b = tid; b < (int)gridDim.x; b += kBlock) {
+        for (int k = 0; k < GROUP; ++k) tot[k] = 0.0;
+        for (int b = tid; b < (int)gridDim.x; b += NT) {
 #pragma unroll
-        for (int k = 0; k < NTRY; ++k) tot[k] += lspart[(int64_t)b * NTRY + k];
+            for (int k = 0; k < GROUP; ++k) tot[k] += lspart[(int64_t)b * NTRY + k0 + k];
+        }
+        group_sum(tot);
+        if (k0 > 0) av *= op.backtrack;
+        const double a_from = av;
+        entropy_decide<GROUP>(tot, first + k0, a_from, gp, tt, dm.lambda, op, found, a_acc, av);
     }
-    block_sum<NTRY, kWaves>(tot, red);
-    int found;
-    double a_acc, av;
-    entropy_decide<NTRY>(tot, first, a_first, gp, tt, dm.lambda, op, found, a_acc, av);
     // rare: continue one step length at a time (every thread holds the same totals: uniform control flow)
     for (int k = first + NTRY; last_resort && found < 0 && k <= op.max_backtracks; ++k) {
         av *= op.backtrack;
         double sv[1] = {0.0};
-        for (int64_t e = tid; e < dm.n; e += kBlock) {
+        for (int64_t e = tid; e < dm.n; e += NT) {
             const double xe = x[e];
             sv[0] = fma(xe, entropy_h(av * p[e] / xe), sv[0]);
         }
-        block_sum<1, kWaves>(sv, red);
+        block_sum<1, NW>(sv, red);
         const double df = av * (gp + 0.5 * av * tt) + dm.lambda * sv[0];
         if (isfinite(df) && df <= op.c1 * av * gp) { found = k; a_acc = av; }
     }
@@ -371,14 +448,15 @@ __global__ __launch_bounds__(kBlock) void k_ot_ls_entropy(Dims dm, Opts op, int 
 }
 
 // x+ = P(x + a p); g+ = M + lambda (log x+ + 1) + K^T (omega . (res + a K p)); pair; f+ from scratch at x+.
-__global__ __launch_bounds__(kBlock) void k_ot_update_entropy(Dims dm, Opts op, OtArgs a, double* res,
+template <int NT>
+__global__ __launch_bounds__(NT, NT == 1024 ? 8 : 4) void k_ot_update_entropy(Dims dm, Opts op, OtArgs a, double* res,
                                                               const double* __restrict__ t, const double* __restrict__ p1,
                                                               const double* __restrict__ p2, const double* __restrict__ l,
                                                               const double* __restrict__ u, double* __restrict__ x,
                                                               double* __restrict__ g, double* __restrict__ S,
                                                               double* __restrict__ Y, Scal* __restrict__ scal,
                                                               double* __restrict__ redpart) {
-    __shared__ double red[kWaves];
+    __shared__ double red[NT / 64];
     __shared__ int flag;
     if (scal->status != LBFGSB_RUNNING) return;
     const int tid = threadIdx.x;
@@ -390,41 +468,39 @@ __global__ __launch_bounds__(kBlock) void k_ot_update_entropy(Dims dm, Opts op, 
     if (ok) {
         double* Sn = S + (int64_t)slot * dm.n;
         double* Yn = Y + (int64_t)slot * dm.n;
-        for (int64_t i = blockIdx.x; i < dm.rows; i += gridDim.x) {
-            const double ri = a.omega ? a.omega[i] * fma(alpha, t[i], res[i]) : 0.0;
-            for (int64_t j = tid; j < dm.cols; j += kBlock) {
-                const int64_t e = i * dm.cols + j;
-                const double cj = a.omega ? a.omega[dm.rows + j] * fma(alpha, t[dm.rows + j], res[dm.rows + j]) : 0.0;
-                const double mij = m_at(a.M, dm.dtype, i * dm.ld + j);
-                const double xi = x[e];
-                const double xn = op.uniform_bounds ? clampd(fma(alpha, p[e], xi), op.lo, op.hi)
-                                                    : clampd(fma(alpha, p[e], xi), l[e], u[e]);
-                const double lg = log(xn);
-                const double gn = mij + dm.lambda * (lg + 1.0) + (ri + cj);
-                Sn[e] = xn - xi;
-                Yn[e] = gn - g[e];
-                x[e] = xn;
-                g[e] = gn;
-                fs[0] = fma(mij, xn, fs[0]);
-                if (xn > 0.0) fs[0] = fma(dm.lambda * xn, lg, fs[0]);
-            }
-        }
+        auto row = [&](int64_t i) { return a.omega ? a.omega[i] * fma(alpha, t[i], res[i]) : 0.0; };
+        for_entries<NT>(dm.rows, dm.cols, row, [&](int64_t i, int64_t j, double ri) {
+            const int64_t e = i * dm.cols + j;
+            const double cj = a.omega ? a.omega[dm.rows + j] * fma(alpha, t[dm.rows + j], res[dm.rows + j]) : 0.0;
+            const double mij = m_at(a.M, dm.dtype, i * dm.ld + j);
+            const double xi = x[e];
+            const double xn = op.uniform_bounds ? clampd(fma(alpha, p[e], xi), op.lo, op.hi)
+                                                : clampd(fma(alpha, p[e], xi), l[e], u[e]);
+            const double lg = log(xn);
+            const double gn = mij + dm.lambda * (lg + 1.0) + (ri + cj);
+            Sn[e] = xn - xi;
+            Yn[e] = gn - g[e];
+            x[e] = xn;
+            g[e] = gn;
+            fs[0] = fma(mij, xn, fs[0]);
+            if (xn > 0.0) fs[0] = fma(dm.lambda * xn, lg, fs[0]);
+        });
     }
-    block_sum<1, kWaves>(fs, red);
+    block_sum<1, NT / 64>(fs, red);
     if (tid == 0) redpart[blockIdx.x] = fs[0];
     if (!arrive_is_last(&scal->counters[kCntUpdate], &flag)) return;
     double tot[1] = {0.0};
-    for (int b = tid; b < (int)gridDim.x; b += kBlock) tot[0] += redpart[b];
+    for (int b = tid; b < (int)gridDim.x; b += NT) tot[0] += redpart[b];
     if (ok) {
         // the residuals of the marginal terms move to the new point here, res += a K p: every other workgroup has
         // finished reading them (it has arrived)
-        for (int64_t k = tid; k < dm.rows + dm.cols; k += kBlock) {
+        for (int64_t k = tid; k < dm.rows + dm.cols; k += NT) {
             const double rn = fma(alpha, t[k], res[k]);
             res[k] = rn;
             if (a.omega) tot[0] = fma(0.5 * a.omega[k] * rn, rn, tot[0]);
         }
     }
-    block_sum<1, kWaves>(tot, red);
+    block_sum<1, NT / 64>(tot, red);
     if (tid == 0) {
         if (ok) {
             scal->f = tot[0];
@@ -464,10 +540,15 @@ void launch_ot_sums(const Dims& dm, const Geometry& ge, const Buffers& bf, const
                        (const double*)bf.wpart, (const Scal*)bf.scal, eval ? bf.row : bf.t, bf.losspart + ge.ot_row_blocks);
 }
 
-void launch_ot_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(k_ot_eval_finish, dim3(ge.ot_el_blocks), dim3(kBlock), 0, st, dm, a,
+template <int NT>
+static void launch_eval_finish_t(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL(k_ot_eval_finish<NT>, dim3(ge.ot_el_blocks), dim3(NT), 0, st, dm, a,
                        ge.ot_row_blocks + ge.ot_col_blocks, (const double*)bf.x, (const double*)bf.row,
                        (const double*)bf.losspart, bf.g, bf.scal);
+}
+void launch_ot_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, hipStream_t st) {
+    if (ot_threads(dm) == 1024) launch_eval_finish_t<1024>(dm, ge, bf, a, st);
+    else launch_eval_finish_t<256>(dm, ge, bf, a, st);
 }
 
 void launch_ot_update_gauss(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
@@ -479,27 +560,33 @@ void launch_ot_update_gauss(const Dims& dm, const Opts& op, const Geometry& ge, 
                        bf.S, bf.Y, bf.scal);
 }
 
-void launch_ot_step_entropy(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
-                            hipStream_t st) {
+template <int NT>
+static void launch_step_entropy_t(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
+                                  hipStream_t st) {
     // three launches, each with a region of lspart of its own: the first (two step lengths) only leaves its partial
     // sums, the second takes the first's decision before anything else
     double* part0 = bf.lspart;
     double* part1 = part0 + (size_t)ge.ls_blocks * 2;
     double* part2 = part1 + (size_t)ge.ls_blocks * kLsBatch;
     static_assert(2 + kLsBatch + kLsTail <= 64, "lspart holds 64 step lengths per workgroup");
-    hipLaunchKernelGGL((k_ot_ls_entropy<2, 0>), dim3(ge.ls_blocks), dim3(kBlock), 0, st, dm, op,
+    hipLaunchKernelGGL((k_ot_ls_entropy<NT, 2, 2, 0>), dim3(ge.ls_blocks), dim3(NT), 0, st, dm, op,
                        ge.ot_row_blocks + ge.ot_col_blocks, 0, 0, 1, (const double*)bf.losspart, (const double*)bf.x,
                        (const double*)bf.p1, (const double*)bf.p2, bf.scal, (const double*)nullptr, part0);
-    hipLaunchKernelGGL((k_ot_ls_entropy<kLsBatch, 2>), dim3(ge.ls_blocks), dim3(kBlock), 0, st, dm, op,
+    hipLaunchKernelGGL((k_ot_ls_entropy<NT, kLsBatch, kLsBatch, 2>), dim3(ge.ls_blocks), dim3(NT), 0, st, dm, op,
                        ge.ot_row_blocks + ge.ot_col_blocks, 2, 0, 0, (const double*)bf.losspart, (const double*)bf.x,
                        (const double*)bf.p1, (const double*)bf.p2, bf.scal, (const double*)part0, part1);
-    hipLaunchKernelGGL((k_ot_ls_entropy<kLsTail, 0>), dim3(ge.ls_blocks), dim3(kBlock), 0, st, dm, op,
+    hipLaunchKernelGGL((k_ot_ls_entropy<NT, kLsTail, ls_group(NT), 0>), dim3(ge.ls_blocks), dim3(NT), 0, st, dm, op,
                        ge.ot_row_blocks + ge.ot_col_blocks, 2 + kLsBatch, 1, 0, (const double*)bf.losspart,
                        (const double*)bf.x, (const double*)bf.p1, (const double*)bf.p2, bf.scal, (const double*)nullptr,
                        part2);
-    hipLaunchKernelGGL(k_ot_update_entropy, dim3(ge.ot_el_blocks), dim3(kBlock), 0, st, dm, op, a, bf.row,
+    hipLaunchKernelGGL(k_ot_update_entropy<NT>, dim3(ge.ot_el_blocks), dim3(NT), 0, st, dm, op, a, bf.row,
                        (const double*)bf.t, (const double*)bf.p1, (const double*)bf.p2, (const double*)bf.l,
                        (const double*)bf.u, bf.x, bf.g, bf.S, bf.Y, bf.scal, bf.redpart);
+}
+void launch_ot_step_entropy(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
+                            hipStream_t st) {
+    if (ot_threads(dm) == 1024) launch_step_entropy_t<1024>(dm, op, ge, bf, a, st);
+    else launch_step_entropy_t<256>(dm, op, ge, bf, a, st);
 }
 
 }  // namespace lb

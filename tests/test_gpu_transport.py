@@ -310,3 +310,33 @@ def test_timing_records_of_the_gram_kernel():
     assert 0 < info.n_fixed < n
     assert total_ms / count > 1e-3 * nbytes / 8e9
     s.close()
+
+
+@pytest.mark.parametrize("rows,cols", [(769, 1025), (3150, 250), (3, 270000), (767, 1025)])
+def test_long_entropy_iterations_follow_the_oracle(rows, cols):
+    """From 3 2^18 entries on the kernels with a logarithm per entry run in workgroups of four sub-groups: ragged last tile,
+    rows shorter than a tile, more tiles per row than the grid takes at once, and a size just below.  The start on the lower
+    bound makes the first search reach the last stage of step lengths.  Tolerances as for the short problems (sums of n 64-bit terms in tree
+    order: sqrt(n) 2^-53 ~ 1e-13 relative, and the curvature of the penalty term amplifies it by less than 1e4)."""
+    rng = np.random.default_rng(rows)
+    M, u, v = _problem(rng, rows, cols)
+    n, lam, rho, lower = rows * cols, 0.5, 4.0, 1e-30
+    l, ub = np.full(n, lower), np.full(n, np.inf)
+    x0 = np.where(rng.random(n) < 0.5, lower, rng.random(n) / n)
+    ref = oracle.Solver(oracle.Objective(oracle.OT_ENTROPY, M, lam=lam).set_marginals(u, v, lam=np.zeros(rows + cols), rho=rho),
+                        l, ub, x0, 5, oracle.default_options(tol=0.0))
+    s = _solver(L.OBJ_OT_ENTROPY, M, l, ub, 5, lam, np.concatenate([u, v]), np.full(rows + cols, rho), tol=0.0)
+    s.set_x(to_dev(x0))
+    most = 0
+    for it in range(3):
+        ref.step()
+        info = s.step()
+        ri = ref.info
+        most = max(most, ri.backtracks)
+        assert info.branch == ri.branch and info.backtracks == ri.backtracks, (it, info.as_dict())
+        assert info.f == pytest.approx(ri.f, rel=1e-10), it
+        assert rel_err(s.x().cpu().numpy(), ref.x) <= 1e-8, it
+        assert rel_err(s.g().cpu().numpy(), ref.g) <= 1e-8, it
+    assert most >= 10
+    ref.close()
+    s.close()

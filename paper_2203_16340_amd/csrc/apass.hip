@@ -6,10 +6,10 @@
 //              16-byte loads, fp64 accumulation) applies the per-row operation of the objective
 //              and leaves per-row weights psi; k_gemvt (w = A^T psi, threads own columns, row
 //              blocks produce partial columns) reads A a second time.
-//   fused    : see fused.hip -- a workgroup owns whole rows, keeps them in registers between the
-//              row dot product and the transposed accumulation, so A is read once.
-// The two-pass kernels serve the shapes the fused kernel does not take (rows wider than its
-// registers and LDS hold, unaligned rows), the transposed product after a rejected first trial
+//   fused    : see fused.hip and narrow.hip -- a workgroup or a wave owns whole rows, keeps them in
+//              registers between the row dot product and the transposed accumulation, so A is read once.
+// The two-pass kernels serve the shapes the fused kernels do not take (rows wider than their
+// registers and LDS hold), the transposed product after a rejected first trial
 // step of the logistic objective (skipped when the fused pass's speculative step was accepted:
 // check_status == 2), and the row products of the symmetric quadratic form when forced.
 //

@@ -1,4 +1,4 @@
-// Fused single-read A pass for the quadratic objectives: variant table and launchers.
+// Fused single-read A pass: variant table and launchers (short rows: narrow.hip; large symmetric matrices: symmetric.hip).
 // The kernel itself (and the reasoning behind its layout) is in fused_ring.h.
 //
 // A variant fixes the workgroup size NT, the 16-byte chunks per thread and row KC = KCU*U, the rows

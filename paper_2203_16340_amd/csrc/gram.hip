@@ -14,10 +14,9 @@
 // wave owns row i, so a step is one broadcast and one multiply-add, with no cross-lane reduction.
 // G must be rebuilt every iteration because S changes; it costs one pass over the 2c+1 vectors.
 //
-// Three kernels build G, chosen by the length of the vectors: k_gram (tiles of G per thread, operands staged
-// through LDS; a few dozen workgroups, which is what short vectors want), and for n >= 2^17 (even) k_gram_wide
-// (m <= 10: element pairs per lane, entries of G divided among the waves) or k_gram_mfma (m > 10: matrix cores).
-// All three end in the same recursion on coefficients (recursion_on_coefficients).
+// Three kernels build G: k_gram_wide (m <= 10 and even n: element pairs per lane, entries of G divided among the waves),
+// k_gram_mfma (m > 10 from 2^17 entries on: matrix cores), else k_gram (tiles of G per thread, operands staged through
+// LDS).  Steps on short vectors build it in small.hip.  All end in the same recursion on coefficients (recursion_on_coefficients).
 #include <cstddef>
 
 #include "common.h"

@@ -747,8 +747,10 @@ int solve_impl(lbfgsb_solver* s, lbfgsb_info* info) {
                 reporting = next_report(reporting);
                 continue;
             }
-            if (st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0 && (unsigned)(p >> 32) >= 2) {
-                // (found in the second step or later, so at least one iteration is behind it: see the condition below)
+            // (The first step is known to have gone on, so at least one iteration is behind: see the condition below.  The
+            // number in the report does not say so: a step behind the one that ended the run reports the end as well, and
+            // which of the two is seen depends on the host's pace.)
+            if (st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0 && reporting >= 2) {
                 HIP_TRY(confirm_convergence(s));
                 st = s->h_scal->status;
             } else {

@@ -255,10 +255,18 @@ void enqueue_redo_columns(lbfgsb_solver* s) {
     }
 }
 
+// A problem that backtracks once tends to do so again: this many steps behind a rejected first trial step take the full
+// launch sequence.  Counted from the step that was rejected, so that which steps take which sequence -- they carry f with
+// different roundings -- does not depend on how many had been enqueued when the host found out.
+constexpr int kLogiFullSteps = 8;
+// Steps enqueued again between two looks at the device: those behind a further rejection have to be enqueued a third time.
+constexpr int kRedoBatch = 16;
+
 // Reads the scalar block after applying any update the last step left pending.  If the short logistic launch sequence
 // has parked the solver (first trial step rejected: kStatusBail), the iteration is finished here with the launches
 // that sequence leaves out, the steps that found the solver parked are enqueued again, and the block is read anew.
 hipError_t read_scal(lbfgsb_solver* s) {
+    int owed = 0;   // steps that found the solver parked and have not been enqueued again
     for (;;) {
         // (the resident solver applies its updates itself; only its evaluations by the multi-kernel path leave one pending)
         hipError_t e = hipSuccess;
@@ -273,17 +281,22 @@ hipError_t read_scal(lbfgsb_solver* s) {
         e = hipStreamSynchronize(s->stream);
         if (e != hipSuccess) return e;
         s->short_steps_unseen = 0;
-        if (s->h_scal->status != kStatusBail) return hipSuccess;
-        const int redo = s->h_scal->bail_skipped;
-        launch_clear_bail(s->bf, s->stream);
-        // the rest of the interrupted iteration: more step lengths, new margins and row weights, the transposed
-        // pass for the accepted step, the update
-        launch_ls_logistic(s->dm, s->op, s->ge, s->bf, s->obj.b, 1, 2, s->stream);
-        launch_rows_logistic(s->dm, s->ge, s->bf, s->obj.b, s->stream);
-        enqueue_redo_columns(s);
-        launch_update_logistic(s->dm, s->op, s->ge, s->bf, s->ge.lrows_blocks, 0, s->stream);
-        s->logi_full_left = 8 + redo;   // a problem that backtracks once tends to do so again: full sequence for a while
-        for (int k = 0; k < redo; ++k) enqueue_step(s);
+        if (s->h_scal->status == kStatusBail) {
+            owed += s->h_scal->bail_skipped;
+            launch_clear_bail(s->bf, s->stream);
+            // the rest of the interrupted iteration: more step lengths, new margins and row weights, the transposed
+            // pass for the accepted step, the update
+            launch_ls_logistic(s->dm, s->op, s->ge, s->bf, s->obj.b, 1, 2, s->stream);
+            launch_rows_logistic(s->dm, s->ge, s->bf, s->obj.b, s->stream);
+            enqueue_redo_columns(s);
+            launch_update_logistic(s->dm, s->op, s->ge, s->bf, s->ge.lrows_blocks, 0, s->stream);
+            s->logi_full_left = kLogiFullSteps;
+        } else if (owed == 0 || s->h_scal->status != LBFGSB_RUNNING) {
+            return hipSuccess;
+        }
+        const int now = owed < kRedoBatch ? owed : kRedoBatch;
+        owed -= now;
+        for (int k = 0; k < now; ++k) enqueue_step(s);
     }
 }
 

@@ -3,9 +3,12 @@ returns must not depend on how far ahead the host happened to be: the same bits,
 same as steps that are waited for one by one."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2203_16340_amd as L
-from gpu_helpers import make_solver, to_dev
+import workloads
+from gpu_helpers import DEV, make_solver, to_dev
+from test_gpu_linesearch import LOGISTIC_CASES
 
 pytestmark = pytest.mark.gpu
 
@@ -31,3 +34,30 @@ def test_a_solve_that_starts_at_the_solution_evaluates_nothing(rows, cols, a_pas
         info = s.solve()
         assert (info.status, info.iters, info.fevals) == (L.CONVERGED, 0, 1)
     s.close()
+
+
+def _records(s):
+    return [tuple(r.as_dict().values()) for r in s.history()]
+
+
+@pytest.mark.parametrize("case", range(len(LOGISTIC_CASES)))
+def test_rejected_first_steps_leave_the_same_bits_however_far_ahead_the_host_was(case):
+    """Logistic searches that backtrack: a rejected first trial step parks the solver, the steps behind it are enqueued
+    again, and for a while steps take the longer launch sequence, which carries f with other roundings.  lbfgsb_solve, steps
+    waited for one by one and steps that are all enqueued before the first look must agree in every record, bit for bit."""
+    prob = workloads.logistic(dtype=np.float64, **LOGISTIC_CASES[case])
+    iters = 40
+    solved, waited, ahead = (L.solver_for_problem(prob, DEV, tol=0.0, max_iter=iters) for _ in range(3))
+    end = solved.solve()
+    while waited.step().status == L.RUNNING:
+        pass
+    for _ in range(2 * iters):
+        ahead.step(want_info=False)
+    want = _records(waited)
+    assert sum(1 for r in waited.history() if r.backtracks > 0) >= 3
+    assert waited.info().as_dict() == end.as_dict() == ahead.info().as_dict()
+    for s in (solved, ahead):
+        assert _records(s) == want
+        assert torch.equal(s.x(), waited.x()) and torch.equal(s.g(), waited.g())
+    for s in (solved, waited, ahead):
+        s.close()

@@ -44,37 +44,58 @@ __device__ __forceinline__ void resolve_v(const APassArgs& a, const Scal* scal, 
 // What a pass over A does before anything else: the status word (from the copy of the scalar block the direction kernel
 // left in a.scal_next, when there is one), Algorithm 2's choice between the candidate directions from that kernel's partial
 // sums (every wave of every workgroup gets the same bits; workgroup 0 records it), and, by the first wave of workgroup 0,
-// the move of that copy into the scalar block.  Returns whether the solver is running; branch: the choice, 0 if it is to
-// be read from the scalar block.  (The ring kernel, whose registers are counted, has this in line.)
-__device__ __forceinline__ bool pass_start(const APassArgs& a, Scal* __restrict__ scal, int& branch) {
-    const int tid = threadIdx.x;
-    const int status = a.check_status ? (a.scal_next ? a.scal_next : scal)->status : LBFGSB_RUNNING;
-    constexpr int kScalWords = (int)(sizeof(Scal) / 4), kPerLane = (kScalWords + 63) / 64;
-    const bool mover = a.scal_next && blockIdx.x == 0 && tid < 64;
+// the move of that copy into the scalar block.  In two parts, so that a pass may request its rows in between: loads return
+// in the order they were issued, and these few come first.  At most kPassDirBlocksMax records of
+// partial sums, one per lane.  (The ring
+// kernel, whose registers are counted and whose rows are wider, has this in line.)
+struct PassStart {
+    static constexpr int kWords = (int)(sizeof(Scal) / 4), kPerLane = (kWords + 63) / 64;
+    int status, fresh, branch;
     int moved[kPerLane];
-    int fresh = 0;
-    if (mover) {
-        fresh = a.scal_next->fresh;
+    double alpha_ub;
+    double rec[7];
+    bool mover, own_choice;
+};
+// own_choice: the choice is made here (a.dir_part), not read from the scalar block
+__device__ __forceinline__ void pass_request(const APassArgs& a, const Scal* scal, bool own_choice, PassStart& ps) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const Scal* src = a.scal_next ? a.scal_next : scal;
+    ps.status = a.check_status ? src->status : LBFGSB_RUNNING;
+    ps.mover = a.scal_next && blockIdx.x == 0 && tid < 64;
+    ps.own_choice = own_choice;
+    ps.fresh = 0;
+    ps.branch = 0;
+    ps.alpha_ub = 1.0;
+    if (own_choice) {
+        const double* r = a.dir_part + (int64_t)(lane < a.dir_blocks ? lane : 0) * kDirRed;
 #pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
+        for (int k = 0; k < 7; ++k) ps.rec[k] = r[k];
+    }
+    if (ps.mover) {
+        ps.fresh = a.scal_next->fresh;
+#pragma unroll
+        for (int j = 0; j < PassStart::kPerLane; ++j) {
             const int idx = tid + 64 * j;
-            moved[j] = idx < kScalWords ? reinterpret_cast<const int*>(a.scal_next)[idx] : 0;
+            ps.moved[j] = idx < PassStart::kWords ? reinterpret_cast<const int*>(a.scal_next)[idx] : 0;
         }
     }
-    branch = 0;
+}
+// Returns whether the solver is running; ps.branch (0: it is to be read from the scalar block) and ps.alpha_ub are then
+// the choice and its step bound.
+__device__ __forceinline__ bool pass_decide(const APassArgs& a, Scal* scal, PassStart& ps) {
+    const int tid = threadIdx.x;
     DirChoice ch{};
-    const bool own_choice = a.select_p && a.dir_blocks > 0;
-    if (own_choice) ch = dir_choice_from_partials(a.dir_part, a.dir_blocks, a.eps);
-    if (mover && fresh) {
+    if (ps.own_choice) ch = dir_choice_from_records((tid & 63) < a.dir_blocks, ps.rec, a.eps);
+    if (ps.mover && ps.fresh) {
 #pragma unroll
-        for (int j = 0; j < kPerLane; ++j) {
+        for (int j = 0; j < PassStart::kPerLane; ++j) {
             const int idx = tid + 64 * j;
-            int v = moved[j];
+            int v = ps.moved[j];
             auto put_double = [&](size_t off, double val) {
                 if (idx == (int)(off / 4)) v = __double2loint(val);
                 if (idx == (int)(off / 4) + 1) v = __double2hiint(val);
             };
-            if (own_choice && status == LBFGSB_RUNNING) {
+            if (ps.own_choice && ps.status == LBFGSB_RUNNING) {
                 if (idx == (int)(offsetof(Scal, branch) / 4)) v = ch.branch;
                 put_double(offsetof(Scal, gp), ch.gp);
                 put_double(offsetof(Scal, alpha_ub), ch.alpha_ub);
@@ -82,14 +103,15 @@ __device__ __forceinline__ bool pass_start(const APassArgs& a, Scal* __restrict_
                 put_double(offsetof(Scal, xp), ch.xp);
             }
             if (idx == (int)(offsetof(Scal, fresh) / 4)) v = 0;
-            if (idx < kScalWords) reinterpret_cast<int*>(scal)[idx] = v;
+            if (idx < PassStart::kWords) reinterpret_cast<int*>(scal)[idx] = v;
         }
         if (tid == 0) a.scal_next->fresh = 0;
     }
-    if (status != LBFGSB_RUNNING) return false;
-    if (own_choice) {
-        branch = ch.branch;
-        if (blockIdx.x == 0 && tid == 0 && !(a.scal_next && fresh)) {
+    if (ps.status != LBFGSB_RUNNING) return false;
+    if (ps.own_choice) {
+        ps.branch = ch.branch;
+        ps.alpha_ub = ch.alpha_ub;
+        if (blockIdx.x == 0 && tid == 0 && !(a.scal_next && ps.fresh)) {
             scal->branch = ch.branch; scal->gp = ch.gp; scal->alpha_ub = ch.alpha_ub; scal->pp = ch.pp; scal->xp = ch.xp;
         }
     }

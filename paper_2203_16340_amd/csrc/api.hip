@@ -413,7 +413,9 @@ void enqueue_step(lbfgsb_solver* s) {
     // needs no closing step (not with extra rows that have a kernel of their own, which reads the choice from the
     // scalar block; rows folded into the direction kernel get their coefficients in the update kernel)
     const bool small = small_step_ok(s->dm);
-    const bool defer = s->use_fused && s->ge.narrow_variant < 0 && !small && (s->dm.n_extra == 0 || fold);
+    const bool pass_chooses = s->ge.narrow_variant >= 0 ? narrow_makes_choice(s->ge)
+                                                        : (s->ge.sym_strips == 0 || s->ge.dir_blocks <= kPassDirBlocksMax);
+    const bool defer = s->use_fused && pass_chooses && !small && (s->dm.n_extra == 0 || fold);
     // ... and then the Gram kernel needs no closing step either, where its grid is small enough for the direction
     // kernel's workgroups to add its partial sums themselves: they finish its work on private copies of the scalar
     // block, and the pass moves workgroup 0's copy into place (Buffers::scal_next)

@@ -336,6 +336,19 @@ __device__ __forceinline__ DirChoice dir_choice_from_partials(const double* __re
     return c;
 }
 
+// The same from at most 64 records, lane l's already in its registers (has: there is one): the same bits.
+__device__ __forceinline__ DirChoice dir_choice_from_records(bool has, const double (&rec)[7], double eps) {
+    double t6[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) t6[k] = wave_sum(has ? rec[k] : 0.0);
+    const double tmin = wave_min(has ? rec[6] : INFINITY);
+    DirChoice c;
+    c.branch = (t6[0] <= -eps * t6[1] && t6[1] >= eps) ? 1 : 2;
+    if (c.branch == 1) { c.gp = t6[0]; c.alpha_ub = 1.0; c.pp = t6[1]; c.xp = t6[2]; }
+    else { c.gp = t6[3]; c.alpha_ub = tmin; c.pp = t6[4]; c.xp = t6[5]; }
+    return c;
+}
+
 // Sums, over the same records, of the folded extra rows' products with both candidates (one full wave; lane l adds
 // records l, l + 64, ...): tx[2r] with the first candidate, tx[2r+1] with the second.
 __device__ __forceinline__ void dir_fold_from_partials(const double* __restrict__ redpart, int nblocks,
@@ -573,10 +586,11 @@ bool fused_ls_first_ok(const Dims& dm, const Geometry& ge);   // APassArgs::ls_f
 hipError_t fused_prepare(const Dims& dm, const Geometry& ge);   // once per solver, before the first launch_fused
 void launch_fused(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, hipStream_t st,
                   hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-// The same for narrow rows; it reads Algorithm 2's choice from the scalar block.  psi: the given weights of mode
-// kRowPsiGiven (else null).
+// The same for narrow rows.  psi: the given weights of mode kRowPsiGiven (else null).
+constexpr int kPassDirBlocksMax = 64;   // records (APassArgs::dir_blocks) the kernels for narrow rows and symmetric matrices take
 constexpr int kNarrowBlocksMax = 512;   // two workgroups per compute unit: what the kernel's registers allow
 bool narrow_shape_ok(const Dims& dm, int* variant, int* blocks);
+bool narrow_makes_choice(const Geometry& ge);   // its direction pass may be given APassArgs::dir_blocks > 0
 void launch_narrow(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, const double* psi,
                    hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 

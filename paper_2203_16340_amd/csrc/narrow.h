@@ -55,9 +55,11 @@ __device__ __forceinline__ double row_sums(double (&a)[S], int lane) {
 
 // LOGI: the family of row operations, as for the ring kernel (0 quadratic, 1 logistic, 2 logistic direction pass).
 // mode kRowPsiGiven (LOGI 0): w = A^T psi for the weights the launch is given; nothing else is computed or stored.
-template <typename T, int L, int KC, int S, int LOGI>
+// OWN: Algorithm 2's choice is made here, from the direction kernel's partial sums (direction passes only); else it is read
+// from the scalar block.  (A parameter and not a test: with both in one kernel a pass behind k_small_step took 0.3 us longer.)
+template <typename T, int L, int KC, int S, int LOGI, bool OWN>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
-void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, APassArgs a, const Scal* __restrict__ scal,
+void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, APassArgs a, Scal* __restrict__ scal,
               double* __restrict__ row, double* __restrict__ t, const double* __restrict__ psi_given,
               double* __restrict__ wpart, double* __restrict__ losspart) {
     using RawT = typename ring::Raw<T>::type;
@@ -111,10 +113,16 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
     };
 
     // (the small reads first: loads return in the order they were issued)
-    const int status = a.check_status ? scal->status : LBFGSB_RUNNING;
-    const int spec_ok = a.check_status == 2 ? scal->spec_ok : 0;
-    const int branch = scal->branch;
-    const double alpha_ub = scal->alpha_ub;
+    PassStart ps;
+    int spec_ok = 0;
+    if constexpr (OWN) {
+        pass_request(a, scal, true, ps);
+    } else {
+        ps.status = a.check_status ? scal->status : LBFGSB_RUNNING;
+        spec_ok = a.check_status == 2 ? scal->spec_ok : 0;
+        ps.branch = scal->branch;
+        ps.alpha_ub = scal->alpha_ub;
+    }
     double bc = 0.0, zc = 1.0;
     {
         const int64_t t0 = tile < ntiles ? tile : 0;
@@ -122,9 +130,13 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
 #pragma unroll
         for (int s = 0; s < S; ++s) fetch(raw[s], t0, s);
     }
-    if (status != LBFGSB_RUNNING || spec_ok) return;
+    if constexpr (OWN) {
+        if (!pass_decide(a, scal, ps)) return;
+    } else {
+        if (ps.status != LBFGSB_RUNNING || spec_ok) return;
+    }
     const double *va, *vb;
-    resolve_v(a, scal, cols, va, vb, branch);
+    resolve_v(a, scal, cols, va, vb, ps.branch);
     double w[W];
 #pragma unroll
     for (int q = 0; q < W; ++q) w[q] = 0.0;
@@ -140,7 +152,7 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
         reinterpret_cast<double*>(v_s)[q] = x;
     }
     __syncthreads();
-    const double alpha0 = LOGI == 2 ? fmin(1.0, alpha_ub) : 0.0;   // first trial step of the line search
+    const double alpha0 = LOGI == 2 ? fmin(1.0, ps.alpha_ub) : 0.0;   // first trial step of the line search
     const double invn = 1.0 / (double)rows;
     double loss = 0.0;
     double lq = 0.0, ldq = 0.0;                              // first trial step: rows whose loss difference is still to be taken

@@ -6,27 +6,41 @@ namespace lb {
 
 namespace {
 
+typedef void (*NarrowLaunch)(const Dims&, int, const Buffers&, const APassArgs&, const double*, hipStream_t, hipEvent_t, hipEvent_t);
+
 struct NarrowVariant {
     int dtype, lanes, kc, sets;
-    void (*launch[3])(const Dims&, int, const Buffers&, const APassArgs&, const double*, hipStream_t, hipEvent_t, hipEvent_t);
+    NarrowLaunch launch[3];
+    NarrowLaunch own[2];   // the direction passes that make Algorithm 2's choice themselves, quadratic and logistic (null: none)
 };
 
-template <typename T, int L, int KC, int S, int LOGI>
+template <typename T, int L, int KC, int S, int LOGI, bool OWN>
 void launch_t(const Dims& dm, int blocks, const Buffers& bf, const APassArgs& a, const double* psi, hipStream_t st,
               hipEvent_t ev0, hipEvent_t ev1) {
-    hipExtLaunchKernelGGL((narrow::k_narrow<T, L, KC, S, LOGI>), dim3(blocks), dim3(kBlock), 0, st, ev0, ev1, 0,
-                          (const T*)a.A, dm.ld, dm.rows, dm.cols, a, (const Scal*)bf.scal, bf.row, bf.t, psi, bf.wpart,
-                          bf.losspart);
+    hipExtLaunchKernelGGL((narrow::k_narrow<T, L, KC, S, LOGI, OWN>), dim3(blocks), dim3(kBlock), 0, st, ev0, ev1, 0,
+                          (const T*)a.A, dm.ld, dm.rows, dm.cols, a, bf.scal, bf.row, bf.t, psi, bf.wpart, bf.losspart);
+}
+// With few lanes to a row (up to 192 fp32 or 96 fp64 columns) vectors are short for most m (small_step_ok) and nothing is
+// gained by the choice being made here; beyond, it saves the direction kernel's arrival and up to 10 pairs the Gram
+// kernel's too.  Whole iterations, us, choice read / made here: lasso fp64 122 x 1024 33.2 / 30.6, 2441 x 1024 35.0 / 32.2,
+// 48828 x 1024 89.9 / 86.8; least squares fp32 4882 x 1024 35.7 / 32.4, m = 30 657 x 380 41.2 / 39.3.
+template <typename T, int L, int KC, int S, int LOGI>
+constexpr NarrowLaunch own_t() {
+    if constexpr (L >= 32) return launch_t<T, L, KC, S, LOGI, true>;
+    else return nullptr;
 }
 
-#define LB_NARROW(dt, T, L, KC, S) {dt, L, KC, S, {launch_t<T, L, KC, S, 0>, launch_t<T, L, KC, S, 1>, launch_t<T, L, KC, S, 2>}}
+#define LB_NARROW(dt, T, L, KC, S) {dt, L, KC, S, {launch_t<T, L, KC, S, 0, false>, launch_t<T, L, KC, S, 1, false>, launch_t<T, L, KC, S, 2, false>},  \
+                                    {own_t<T, L, KC, S, 0>(), own_t<T, L, KC, S, 2>()}}
 // the quadratic kinds only (the logistic row operations do not fit the registers beside the rows)
-#define LB_NARROW_QUAD(dt, T, L, KC, S) {dt, L, KC, S, {launch_t<T, L, KC, S, 0>, nullptr, nullptr}}
+#define LB_NARROW_QUAD(dt, T, L, KC, S) {dt, L, KC, S, {launch_t<T, L, KC, S, 0, false>, nullptr, nullptr}, {own_t<T, L, KC, S, 0>(), nullptr}}
 // By capacity L * KC in 16-byte chunks; the first whose capacity covers a row is used.  The line to the ring kernel is
 // where it measured faster (0.4 GB matrices, us per pass, this kernel / ring): fp32 least squares 100 columns 69 / 271,
 // 512 69 / 70, 1024 66 / 70, 1536 66 / 72, 1800 76 / 75; fp32 logistic 100 81 / 390, 512 72 / 89, 1000 66 / 94,
 // 1536 77 / 83, 2000 78 / 77; fp64 least squares 100 64 / 270, 512 62 / 70, 1024 64 / 67; fp64 logistic 100 68 / 426,
 // 512 67 / 97, 768 63 / 75, 900 80 / 76 (spills).
+// Whole iterations at 1, 2, 5, 20, 80 and 400 MB, 100 to 1536 columns, m = 10, 20 and 30, all kinds: between 0.27 and 1.00 of
+// the ring kernel's time (nearest to it the lasso of 1-2 MB at 1600 to 2048 variables).
 #define LB_NARROW_TABLE(dt, T)                                                                                       \
     LB_NARROW(dt, T, 8, 1, 8), LB_NARROW(dt, T, 8, 2, 8), LB_NARROW(dt, T, 8, 3, 8), LB_NARROW(dt, T, 16, 2, 8),     \
     LB_NARROW(dt, T, 16, 3, 8), LB_NARROW(dt, T, 32, 2, 8), LB_NARROW(dt, T, 32, 3, 8), LB_NARROW(dt, T, 64, 2, 8),  \
@@ -61,11 +75,15 @@ bool narrow_shape_ok(const Dims& dm, int* variant, int* blocks) {
     return false;
 }
 
+bool narrow_makes_choice(const Geometry& ge) {
+    return kNarrow[ge.narrow_variant].own[0] && ge.dir_blocks <= kPassDirBlocksMax;
+}
+
 void launch_narrow(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, const double* psi,
                    hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     const NarrowVariant& v = kNarrow[ge.narrow_variant];
     const int logi = a.mode == kRowLogiSpec ? 2 : (a.mode == kRowLogiEval ? 1 : 0);
-    v.launch[logi](dm, ge.fused_blocks, bf, a, psi, st, ev0, ev1);
+    (a.select_p && a.dir_blocks > 0 ? v.own[logi / 2] : v.launch[logi])(dm, ge.fused_blocks, bf, a, psi, st, ev0, ev1);
 }
 
 }  // namespace lb

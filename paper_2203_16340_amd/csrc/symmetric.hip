@@ -85,15 +85,16 @@ void k_sym(const T* __restrict__ A, int64_t ld, int n, APassArgs a, int strips, 
 #pragma unroll
         for (int k = 0; k < KC; ++k) dst[k] = __builtin_nontemporal_load(reinterpret_cast<const MemT*>(rp + off[k]));
     };
-    int branch;
-    if (!pass_start(a, scal, branch)) return;
+    PassStart ps;
+    pass_request(a, scal, a.select_p && a.dir_blocks > 0, ps);
+    if (!pass_decide(a, scal, ps)) return;
     {
         const int t0 = tile < ntiles ? tile : 0;
 #pragma unroll
         for (int s = 0; s < S; ++s) fetch(raw[s], t0, s);
     }
     const double *va, *vb;
-    resolve_v(a, scal, n, va, vb, branch);
+    resolve_v(a, scal, n, va, vb, ps.branch);
     double v[W], w[W];
 #pragma unroll
     for (int k = 0; k < KC; ++k) {

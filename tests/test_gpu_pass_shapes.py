@@ -35,9 +35,9 @@ def _problem(kind, rows, cols, dtype, seed, pad=0, shift=0):
     return A, A_d, b, l, u, x
 
 
-def _solver(kind, A_d, b, l, u, **opts):
-    return L.Solver(kind, A_d, to_dev(b), to_dev(l), to_dev(u), 5, lam=0.3 if kind == L1 else 0.0,
-                    mu=1e-3 if kind == LOGI else 0.0, options=L.default_options(tol=0.0, refresh_every=0, **opts))
+def _solver(kind, A_d, b, l, u, m=5, extra=None, **opts):
+    return L.Solver(kind, A_d, to_dev(b), to_dev(l), to_dev(u), m, lam=0.3 if kind == L1 else 0.0,
+                    mu=1e-3 if kind == LOGI else 0.0, extra=extra, options=L.default_options(tol=0.0, refresh_every=0, **opts))
 
 
 def _reference_fg(kind, A, b, x):
@@ -173,6 +173,45 @@ def test_narrow_row_weights():
     r = A @ x - b
     assert abs(f - 0.5 * (w * r) @ r) <= 1e-12 * f
     assert rel_err(g.cpu().numpy(), A.T @ (w * r)) <= 1e-12 and rel_err(row.cpu().numpy(), r) <= 1e-12
+
+
+# vectors too long for the kernel that does the direction's work in one workgroup (more than 20 pairs: any), narrow rows of
+# 32 or 64 lanes: the pass makes Algorithm 2's choice itself from the direction kernel's partial sums, with even n and up to
+# 10 pairs on a copy of the scalar block that its first wave moves into place
+CHOICE = [(kind, np.float32, c, 21) for c in (255, 383, 511, 767, 1023, 1279, 1535) for kind in (LSQ, LOGI)]
+CHOICE += [(kind, np.float64, c, 21) for c in (127, 191, 255, 383, 511, 639, 767) for kind in (LSQ, LOGI)] + [(LSQ, np.float64, 1023, 21)]
+CHOICE += [(L1, np.float64, 600, 10), (L1, np.float32, 767, 9), (LSQ, np.float32, 1100, 10), (LOGI, np.float32, 1536, 10), (LOGI, np.float32, 1535, 10)]
+
+
+def _compare_steps(s, two, x, steps):
+    for sol in (s, two):
+        sol.set_x(to_dev(x))
+    for _ in range(steps):
+        a, b = s.step(), two.step()
+        assert (a.status, a.iters, a.branch, a.backtracks, a.n_fixed, a.pairs_used) == \
+            (b.status, b.iters, b.branch, b.backtracks, b.n_fixed, b.pairs_used)
+        assert a.gp == pytest.approx(b.gp, rel=1e-9) and a.alpha_ub == pytest.approx(b.alpha_ub, rel=1e-9)
+    assert rel_err(s.x().cpu().numpy(), two.x().cpu().numpy()) <= 1e-10
+    assert rel_err(s.g().cpu().numpy(), two.g().cpu().numpy()) <= 1e-10
+
+
+@pytest.mark.parametrize("kind,dtype,cols,m", CHOICE)
+def test_narrow_pass_that_makes_the_choice(kind, dtype, cols, m):
+    A, A_d, b, l, u, x = _problem(kind, 2000, cols, dtype, seed=cols + m)
+    print(f"kind {kind} cols {cols} {np.dtype(dtype).name} m {m}", flush=True)
+    s, two = (_solver(kind, A_d, b, l, u, m=m, a_pass=p) for p in (L.APASS_AUTO, L.APASS_TWO_PASS))
+    _compare_steps(s, two, x, 5)
+
+
+@pytest.mark.parametrize("n_extra", [1, 2, 3])
+@pytest.mark.parametrize("cols,m", [(600, 21), (1500, 10)])
+def test_narrow_pass_that_makes_the_choice_with_extra_rows(n_extra, cols, m):
+    """One or two extra rows ride along with the direction kernel, three have a kernel that reads the choice."""
+    A, A_d, b, l, u, x = _problem(LSQ, 2500, cols, np.float32, seed=cols + n_extra)
+    rng = np.random.default_rng(cols)
+    extra = (to_dev(rng.standard_normal((n_extra, cols))), to_dev(rng.standard_normal(n_extra)), to_dev(rng.random(n_extra) + 5.0))
+    s, two = (_solver(LSQ, A_d, b, l, u, m=m, extra=extra, a_pass=p) for p in (L.APASS_AUTO, L.APASS_TWO_PASS))
+    _compare_steps(s, two, x, 5)
 
 
 # the quadratic form's products from the upper triangle (from 4096 variables on): one strip of 512 columns more or less,

@@ -1,6 +1,8 @@
 // C-ABI layer of liblbfgsb: argument checks, workspace layout, the fixed kernel sequence of one
 // iteration of Algorithm 1, the polling loop of lbfgsb_solve and the primitive-level hooks.
 // No solver arithmetic happens on the host.
+#include <sched.h>
+
 #include <algorithm>
 #include <cmath>
 #include <cstdarg>
@@ -753,7 +755,9 @@ int solve_impl(lbfgsb_solver* s, lbfgsb_info* info) {
                 st = (int)(unsigned)p;
                 if ((unsigned)(p >> 32) >= reporting || st != LBFGSB_RUNNING) break;
                 // (now and then: has the stream run dry, or failed?  then the read below says what there is to know)
-                if (spins % 4096 == 0) {
+                __builtin_ia32_pause();
+                if (spins % 64 == 0) sched_yield();   // (to other threads that want this core)
+                if (spins % 1024 == 0) {
                     if (hipStreamQuery(s->stream) != hipErrorNotReady) { st = -1; break; }
                     (void)hipGetLastError();   // (a stream that is busy is no error)
                 }

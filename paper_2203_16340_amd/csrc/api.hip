@@ -38,6 +38,10 @@ int fail(int code, const char* fmt, ...) {
 
 constexpr int kMaxTimed = 4096;
 
+// Host memory that kernels write while the host looks at it: coherent by request, not by the runtime's default (which the
+// environment can change).
+constexpr unsigned kPinned = hipHostMallocCoherent;
+
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -922,7 +926,7 @@ int lbfgsb_create(lbfgsb_solver** out, int64_t n, int m, const double* l, const 
     auto bail = [&](int code) { lbfgsb_destroy(s); return code; };
     {
         const size_t flag_at = (sizeof(Scal) + 63) / 64 * 64;
-        hipError_t e = hipHostMalloc((void**)&s->h_scal, flag_at + 64, hipHostMallocDefault);
+        hipError_t e = hipHostMalloc((void**)&s->h_scal, flag_at + 64, kPinned);
         if (e != hipSuccess) { s->h_scal = nullptr; return bail(fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e))); }
         s->owns_h_scal = true;
         s->h_flag = (int*)((char*)s->h_scal + flag_at);
@@ -1464,7 +1468,7 @@ int lbfgsb_auglag_create(lbfgsb_auglag** out, int64_t n, int m, const double* l,
     rc = lbfgsb_create(&al->inner, n, m, l, u, &inner_obj, opt, workspace, inner_bytes, hip_stream);
     if (rc) { delete al; return rc; }
     al->res_c = al->inner->bf.row + rows_data;
-    hipError_t e = hipHostMalloc((void**)&al->h_red, 64, hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void**)&al->h_red, 64, kPinned);
     if (e != hipSuccess) { al->h_red = nullptr; lbfgsb_auglag_destroy(al); return fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e)); }
     int blocks = (int)((obj->rows + 255) / 256);
     if (blocks > 1024) blocks = 1024;
@@ -1523,7 +1527,7 @@ int lbfgsb_auglag_create_rows(lbfgsb_auglag** out, int64_t n, int m, const doubl
     rc = lbfgsb_create(&al->inner, n, m, l, u, &inner_obj, opt, workspace, inner_bytes, hip_stream);
     if (rc) { delete al; return rc; }
     al->res_c = al->inner->bf.xres;
-    hipError_t e = hipHostMalloc((void**)&al->h_red, 64, hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void**)&al->h_red, 64, kPinned);
     if (e != hipSuccess) { al->h_red = nullptr; lbfgsb_auglag_destroy(al); return fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e)); }
     launch_fill_zero(al->beta_c, 3 * slot, al->stream);
     e = hipStreamSynchronize(al->stream);
@@ -1578,7 +1582,7 @@ int lbfgsb_auglag_create_marginals(lbfgsb_auglag** out, int m, const double* l, 
     int rc = lbfgsb_create(&al->inner, n, m, l, u, &inner_obj, opt, workspace, inner_bytes, hip_stream);
     if (rc) { delete al; return rc; }
     al->res_c = al->inner->bf.row;
-    hipError_t e = hipHostMalloc((void**)&al->h_red, 64, hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void**)&al->h_red, 64, kPinned);
     if (e != hipSuccess) { al->h_red = nullptr; lbfgsb_auglag_destroy(al); return fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e)); }
     launch_fill_zero(al->beta_c, 3 * slot, al->stream);
     e = hipStreamSynchronize(al->stream);

@@ -213,12 +213,12 @@ void launch_sym(const Dims& dm, const Geometry& ge, const Buffers& bf, const APa
                 hipEvent_t ev1) {
     double* tpart = bf.wpart + (size_t)ge.fused_blocks * kSymStrip;
     if (dm.dtype == LBFGSB_F32)
-        hipExtLaunchKernelGGL(k_sym<float>, dim3(ge.fused_blocks), dim3(kBlock), 0, st, ev0, ev1, 0, (const float*)a.A, dm.ld,
+        hipExtLaunchKernelGGL(k_sym<float>, dim3(ge.fused_blocks), dim3(kBlock), 0, st, ev0, nullptr, 0, (const float*)a.A, dm.ld,
                               (int)dm.cols, a, ge.sym_strips, ge.fused_blocks, bf.scal, bf.wpart, tpart);
     else
-        hipExtLaunchKernelGGL(k_sym<double>, dim3(ge.fused_blocks), dim3(kBlock), 0, st, ev0, ev1, 0, (const double*)a.A, dm.ld,
+        hipExtLaunchKernelGGL(k_sym<double>, dim3(ge.fused_blocks), dim3(kBlock), 0, st, ev0, nullptr, 0, (const double*)a.A, dm.ld,
                               (int)dm.cols, a, ge.sym_strips, ge.fused_blocks, bf.scal, bf.wpart, tpart);
-    hipLaunchKernelGGL(k_sym_finish, dim3(sym_loss_parts(dm)), dim3(kBlock), 0, st, dm.cols, a, ge.sym_strips, ge.fused_blocks,
+    hipExtLaunchKernelGGL(k_sym_finish, dim3(sym_loss_parts(dm)), dim3(kBlock), 0, st, nullptr, ev1, 0, dm.cols, a, ge.sym_strips, ge.fused_blocks,
                        (const Scal*)bf.scal, (const double*)bf.wpart, (const double*)tpart,
                        a.mode == kRowQpEval ? bf.row : bf.t, bf.losspart);
 }

@@ -145,11 +145,11 @@ def test_steps_enqueued_without_waiting_survive_rejected_first_steps(case):
     a.close(); b.close()
 
 
-def test_a_very_tall_matrix_takes_the_full_logistic_sequence():
-    """The short launch sequence keeps two numbers per row of a workgroup in LDS; with more than about ten thousand
-    rows per workgroup (here 5.3 million rows of 8 columns: 512 workgroups) they do not fit, and the library has to
-    fall back to the full sequence instead of asking for more LDS than a workgroup can have.  Steps enqueued without
-    waiting, steps with an info struct and the oracle must agree."""
+def test_a_very_tall_narrow_matrix():
+    """5.3 million rows of 8 columns: more than ten thousand rows per workgroup, which the ring kernel could not keep two
+    numbers each of in LDS.  Rows this short go to the kernel that sums the first trial step's loss differences as it goes
+    and keeps none.  (The launch sequence for the rows that do not fit: test_gpu_pass_shapes.py, replayed from a graph.)
+    Steps enqueued without waiting, steps with an info struct and the oracle must agree."""
     prob = workloads.logistic(rows=5_300_000, cols=8, seed=11, dtype=np.float32, label_noise=0.5, mu=1e-3, bound=0.5, m=5)
     a = L.solver_for_problem(prob, DEV, tol=0.0, a_pass=L.APASS_FUSED)
     b = L.solver_for_problem(prob, DEV, tol=0.0, a_pass=L.APASS_FUSED)

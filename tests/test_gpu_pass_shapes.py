@@ -9,7 +9,9 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_2203_16340_amd as L
+import workloads
 from gpu_helpers import DEV, rel_err, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -104,24 +106,76 @@ def test_unaligned_rows_asked_for_by_name_are_refused():
     assert e.value.code == L.E_UNSUPPORTED
 
 
-def test_unaligned_logistic_steps_replayed_from_a_graph():
-    """Steps recorded on unaligned rows finish every iteration on the device: x is right without a look in between."""
-    A, A_d, b, l, u, x = _problem(LOGI, 900, 403, np.float32, seed=5)
-    eager, rec = _solver(LOGI, A_d, b, l, u), None
+def _backtracking(rows, cols, dtype, seed, first=True):
+    """Badly scaled features: the first step is halved a dozen times and more; first = False: steps in between, once or
+    twice.  Returns the problem and the oracle's rejected trial steps of the first six iterations."""
+    how = dict(feature_scale=20, column_spread=2, bound=5.0, label_noise=0.5, mu=1e-3) if first else \
+        dict(feature_scale=1, column_spread=1.5, bound=50.0, random_start=True, label_noise=0.0, mu=1e-6)
+    prob = workloads.logistic(rows=rows, cols=cols, seed=seed, dtype=np.float64, m=5, **how)
+    prob.A = np.ascontiguousarray(prob.A.astype(dtype))
+    orc = oracle.Solver(oracle.Objective(prob.kind, prob.A, prob.b, prob.lam, prob.mu), prob.l, prob.u, prob.x0, prob.m,
+                        oracle.default_options(tol=0.0))
+    counts = []
+    for _ in range(6):
+        orc.step()
+        counts.append(orc.info.backtracks)
+    orc.close()
+    return prob, counts
+
+
+@pytest.mark.parametrize("dtype,rows,cols,first", [(np.float32, 900, 403, False), (np.float32, 900, 403, True),
+                                                   (np.float64, 517, 1025, True), (np.float64, 600, 20426, True)])
+def test_logistic_steps_that_finish_on_the_device_replayed_from_a_graph(dtype, rows, cols, first):
+    """Steps recorded on unaligned rows, and on rows so wide that the numbers per row of the short launch sequence do not
+    fit LDS beside v (20426 columns: 16 bytes are left of it, a workgroup has 3 rows), finish every iteration on the device,
+    also one whose first trial step is rejected: x is right although the host does not look in between.  (The look at x
+    before the first replay is the last that the library takes: it knows of no steps after it.)"""
+    prob, counts = _backtracking(rows, cols, dtype, seed=0, first=first)
+    assert max(counts[:5]) >= 1
+    eager = L.solver_for_problem(prob, DEV, tol=0.0, a_pass=L.APASS_AUTO)
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
-        rec = _solver(LOGI, A_d, b, l, u)
-        rec.set_x(to_dev(x))
+        rec = L.solver_for_problem(prob, DEV, tol=0.0, a_pass=L.APASS_AUTO)
+        assert rec.apass_name == "fused"
         stream.synchronize()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, stream=stream):
             rec.step(False)
-    eager.set_x(to_dev(x))
-    for _ in range(3):
+        rec.x()
+    torch.cuda.synchronize()
+    for _ in range(5):
         graph.replay()
         torch.cuda.synchronize()
         eager.step(False)
         assert rel_err(rec.x().cpu().numpy(), eager.x().cpu().numpy()) <= 1e-12
+    assert max(r.backtracks for r in eager.history()) >= 1
+
+
+# a ragged width of every logistic variant of the kernel for narrow rows, and of the ring kernel's; rows past the first
+# tile of every wave (512 workgroups of four) for the variants that hold four sets of rows
+REJECTED = [(np.float32, 517, c) for c in (31, 63, 95, 127, 191, 255, 383, 511, 767, 1537, 2049, 5121, 10243)]
+REJECTED += [(np.float64, 517, c) for c in (15, 31, 47, 63, 95, 127, 191, 255, 383, 769, 1025, 2049, 5119, 10241)]
+REJECTED += [(np.float32, 8201, c) for c in (1023, 1279, 1535)] + [(np.float64, 8201, c) for c in (511, 639, 767)]
+
+
+@pytest.mark.parametrize("dtype,rows,cols", REJECTED)
+def test_columns_after_a_rejected_first_trial_step(dtype, rows, cols):
+    """The step that is accepted in the end is not the one whose columns the single read has formed: they are formed anew,
+    by the kernel of the shape or the transposed pass.  Against the two-pass kernels over the first iterations, with and
+    without a look after every step."""
+    prob, counts = _backtracking(rows, cols, dtype, seed=cols)
+    assert counts[0] >= 1
+    print(f"rows {rows} cols {cols} {np.dtype(dtype).name} rejected {counts}", flush=True)
+    s, ahead, two = (L.solver_for_problem(prob, DEV, tol=0.0, a_pass=p) for p in (L.APASS_AUTO, L.APASS_AUTO, L.APASS_TWO_PASS))
+    assert s.apass_name == "fused"
+    for k in range(3):
+        a, b = s.step(), two.step()
+        ahead.step(False)
+        assert (a.status, a.iters, a.branch, a.backtracks, a.n_fixed) == (b.status, b.iters, b.branch, b.backtracks, b.n_fixed)
+        assert a.backtracks == counts[k]
+        assert rel_err(s.g().cpu().numpy(), two.g().cpu().numpy()) <= 1e-9
+    assert rel_err(s.x().cpu().numpy(), two.x().cpu().numpy()) <= 1e-10
+    assert torch.equal(ahead.x(), s.x()) and torch.equal(ahead.g(), s.g())
 
 
 def test_static_solve_of_unaligned_rows_that_fit_only_without_the_single_read():
@@ -161,6 +215,23 @@ def test_narrow_row_counts(kind, rows):
     _check(kind, rows, 6, np.float32, pad=1, shift=0)
     if rows < 20000:
         _check(kind, rows, 300, np.float64, pad=0, shift=0)
+
+
+# the variants that hold four sets of rows: both sides of the widest one's capacity, and rows past the first tile of every
+# wave (four rows each in 512 workgroups of four), in part and in whole
+@pytest.mark.parametrize("kind", [LSQ, LOGI])
+@pytest.mark.parametrize("dtype,cols", [(np.float32, c) for c in (1281, 1535, 1536, 1537)] + [(np.float64, c) for c in (641, 767, 768, 769)])
+def test_narrow_rows_at_the_widest(kind, dtype, cols):
+    _check(kind, 1203, cols, dtype, pad=0, shift=0)
+
+
+@pytest.mark.parametrize("rows", [8193, 16387])
+@pytest.mark.parametrize("kind,dtype,cols", [(LOGI, np.float32, 1023), (LOGI, np.float32, 1279), (LSQ, np.float32, 1279),
+                                             (LOGI, np.float32, 1535), (LSQ, np.float32, 1535), (LOGI, np.float64, 511),
+                                             (LOGI, np.float64, 639), (LSQ, np.float64, 639), (LOGI, np.float64, 767),
+                                             (LSQ, np.float64, 767), (LSQ, np.float64, 1023)])
+def test_narrow_rows_past_the_first_tile(kind, dtype, cols, rows):
+    _check(kind, rows, cols, dtype, pad=0, shift=0)
 
 
 def test_narrow_row_weights():

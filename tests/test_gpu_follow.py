@@ -67,6 +67,73 @@ def test_rejected_first_steps_leave_the_same_bits_however_far_ahead_the_host_was
         s.close()
 
 
+LIMITS = [0, 1, 2, 3, 4, 5, 7, 8, 9, 11, 12, 13, 31, 32, 33, 39, 40, 41, 47, 48, 49]   # reports: 1 2 3 4 8 12 .. 32 40 48
+
+
+@pytest.mark.parametrize("kind", [L.OBJ_LSQ, L.OBJ_LOGISTIC_L2])
+@pytest.mark.parametrize("cols", [300, 1100])
+def test_iteration_limits_around_the_reporting_steps(kind, cols):
+    """The run ends at its limit whether or not that step reports, with the bits of steps waited for one by one."""
+    if kind == L.OBJ_LSQ:
+        A, b, l, u = _lsq(2000, cols)
+        A *= np.geomspace(1.0, 30.0, cols)        # (more iterations than the largest limit)
+    else:
+        prob = workloads.logistic(rows=2000, cols=cols, seed=3, dtype=np.float64, mu=1e-4, bound=50.0)
+        A, b, l, u = prob.A, prob.b, prob.l, prob.u
+        A *= np.geomspace(0.1, 3.0, cols)
+    x0 = to_dev(np.clip(np.zeros(cols), l, u))
+    A, b, l, u = to_dev(A), to_dev(b), to_dev(l), to_dev(u)
+
+    def solver(limit):
+        s = L.Solver(kind, A, b, l, u, 10, mu=1e-4 if kind != L.OBJ_LSQ else 0.0, options=L.default_options(tol=0.0, max_iter=limit))
+        s.set_x(x0)
+        return s
+
+    for limit in LIMITS:
+        walk, s = solver(limit), solver(limit)
+        while walk.step().status == L.RUNNING:
+            pass
+        for _ in range(2):                        # (the second finds a solver that has stopped)
+            info = s.solve()
+            assert (info.status, info.iters) == (L.MAX_ITER, limit)
+            assert info.as_dict() == walk.info().as_dict() and _records(s) == _records(walk)
+            assert torch.equal(s.x(), walk.x()) and torch.equal(s.g(), walk.g())
+        s.close()
+        walk.close()
+
+
+def test_solving_again_after_convergence_changes_nothing():
+    A, b, l, u = _lsq(2000, 700)
+    s = make_solver(L.OBJ_LSQ, A, b, l, u, 10, tol=1e-9, tol_relative=1)
+    s.set_x(to_dev(l))
+    first = s.solve()
+    x = s.x().clone()
+    again = s.solve()
+    assert first.status == again.status == L.CONVERGED and first.iters == again.iters and first.f == again.f
+    assert torch.equal(s.x(), x)
+    s.close()
+
+
+def test_a_confirmation_that_does_not_confirm():
+    """The gradient carried by recurrence passes the test, the one recomputed from x does not: the run goes on from the
+    recomputed one until both pass.  (A start far away, so that the first steps leave rounding in the residual that is large
+    against the tolerance; no periodic recomputation.)"""
+    A, b, l, u = _lsq(1500, 400)
+    l = np.full(400, -np.inf)
+    x0 = np.full(400, 1e9)
+    tol = 1e-3
+    s = make_solver(L.OBJ_LSQ, A, b, l, u, 10, tol=tol, refresh_every=0)
+    s.set_x(to_dev(x0))
+    info = s.solve()
+    x = s.x().cpu().numpy()
+    trials = sum(r.backtracks + 1 for r in s.history())
+    confirmations = info.fevals - 1 - trials
+    print("confirmations", confirmations, info.as_dict())
+    assert info.status == L.CONVERGED and confirmations >= 2
+    assert np.linalg.norm(A.T @ (A @ x - b)) <= tol * 1.01
+    s.close()
+
+
 def test_threads_that_share_a_core_do_not_wait_for_each_other():
     """Four solvers on streams and threads of their own: the same bits on one core as on all, and nearly the same time.  A
     thread that follows its run gives its core to those that have steps to enqueue (3000 x 1200, ms per solve and thread:

@@ -7,12 +7,15 @@
 // beforehand, so both products are taken as a row arrives and its registers are refilled at once.  Strip J has rows
 // 0 .. 512 (J + 1) - 1; its workgroups take a share of the grid in proportion.  Left behind are the strips' row sums
 // (tpart[J][r], r in strip J or above) and each workgroup's 512 column sums (wpart); a second kernel adds a column's few
-// dozen numbers in fixed order and forms v^T t from the finished t.  (Adding v^T t up in the first kernel, from the two
-// halves, saves the launch but sums large numbers that cancel: a badly conditioned kernel matrix of 3000 points then
-// stalled in the line search.)
+// dozen numbers in fixed order and forms v^T t from the finished t, whose rounding does not depend on the split.
+//
+// Sums are kept short on purpose -- a tile's eight rows for the columns, then the tiles, then in pairs -- where one chain per
+// column over all of a wave's rows and one over the partial numbers would do.  Error of t against 80 bits in units of 2^-53
+// (kernel matrices of 4608 / 10 000 points, vectors of one sign): one chain 1.08 / 1.09, now 0.68 / 0.69, the ring kernel on
+// the whole matrix 0.88 / 0.84, the two-pass kernel 0.76 / 0.80.  The time is the same.
 //
 // Bytes: the blocks on the diagonal are read whole, n^2/2 + 256 n entries.  Per pass at n = 10 000 fp64: 131 us with the
-// ring kernel reading all of K, 70 + 5 us with these two (0.42 GB: 6.0 TB/s).
+// ring kernel reading all of K, 70 + 5 us with these two (0.42 GB: 6.0 TB/s, with k_sym_finish 5.5).
 #include "common.h"
 #include "narrow.h"
 
@@ -118,17 +121,21 @@ void k_sym(const T* __restrict__ A, int64_t ld, int n, APassArgs a, int strips, 
     for (; tile < ntiles; tile += stride) {
         const int tn = tile + stride < ntiles ? tile + stride : 0;
         const double vn = row_v(tn);
-        double acc[S];
+        double acc[S], wt[W];
         const bool diag = tile * S + S > J * kSymStrip;      // (uniform)
+#pragma unroll
+        for (int q = 0; q < W; ++q) wt[q] = 0.0;
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const double vr = lane_bcast(vrl, s);
-            if (diag) sym_row<T, true, S, KC, VEC>(raw[s], v, vr, col, tile * S + s, acc[s], w);
-            else sym_row<T, false, S, KC, VEC>(raw[s], v, vr, col, tile * S + s, acc[s], w);
+            if (diag) sym_row<T, true, S, KC, VEC>(raw[s], v, vr, col, tile * S + s, acc[s], wt);
+            else sym_row<T, false, S, KC, VEC>(raw[s], v, vr, col, tile * S + s, acc[s], wt);
             __builtin_amdgcn_sched_barrier(0);
             fetch(raw[s], tn, s);
             __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int q = 0; q < W; ++q) w[q] += wt[q];
         const double u = narrow::row_sums<64, S>(acc, lane);
         if (lane < S && tile * S + lane < rows) tpart[(int64_t)J * n + tile * S + lane] = u;
         vrl = vn;
@@ -173,16 +180,21 @@ __global__ __launch_bounds__(kBlock) void k_sym_finish(int64_t n, APassArgs a, i
             v[k] = kk < nw ? wpart[(int64_t)(b0 + kk) * kSymStrip + cc % kSymStrip]
                            : (kk < count ? tpart[(int64_t)(J + kk - nw) * n + cc] : 0.0);
         }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) s += v[k];
+        s += (v[0] + v[1]) + (v[2] + v[3]);
     }
     lds[gy * kCX + cx] = s;
     __syncthreads();
     if (tid < 64) {
         double tot = 0.0;
         if (gy == 0) {
+            double p[kGY];
 #pragma unroll
-            for (int k = 0; k < kGY; ++k) tot += lds[k * kCX + cx];
+            for (int k = 0; k < kGY; ++k) p[k] = lds[k * kCX + cx];
+#pragma unroll
+            for (int h = kGY / 2; h > 0; h /= 2)
+#pragma unroll
+                for (int k = 0; k < h; ++k) p[k] += p[k + h];
+            tot = p[0];
             if (c < n) out[c] = tot;
         }
         const double loss = wave_sum(gy == 0 && c < n ? (a.mode == kRowQpEval ? 0.5 : 1.0) * vc * tot : 0.0);

@@ -322,3 +322,30 @@ def test_symmetric_products(n, dtype, signed):
         assert a.f == pytest.approx(b.f, rel=1e-10)
     assert rel_err(s.x().cpu().numpy(), two.x().cpu().numpy()) <= 1e-10
     assert rel_err(s.g().cpu().numpy(), two.g().cpu().numpy()) <= 1e-10
+
+
+def test_symmetric_products_lose_no_precision():
+    """The products from the upper triangle are sums of row halves and column halves: no further from the exact ones than
+    the two-pass kernel's, which adds whole rows.  (Measured: 0.68 and 0.76 times 2^-53; with one chain of additions per
+    column of a wave it was 1.08.  Four vectors of one sign and 400 rows each: the figures vary by 3 %.)"""
+    n = 4608
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((n, 20)) / np.sqrt(20.0)
+    sq = (X * X).sum(1)
+    K = np.exp(-np.maximum(sq[:, None] + sq[None, :] - 2.0 * (X @ X.T), 0.0))
+    K = 0.5 * (K + K.T)
+    l, u = to_dev(np.zeros(n)), to_dev(np.ones(n))
+    error = {}
+    for a_pass in (L.APASS_AUTO, L.APASS_TWO_PASS):
+        s = L.Solver(L.OBJ_QP, to_dev(K), to_dev(-np.ones(n)), l, u, 5, options=L.default_options(a_pass=a_pass))
+        rng = np.random.default_rng(1)
+        total = 0.0
+        for _ in range(4):
+            v, rows = rng.random(n), rng.choice(n, 400, replace=False)
+            _, _, t = s.dbg_fg(to_dev(v), want_rowvec=True)
+            exact = (K[rows].astype(np.longdouble) * v).sum(1)
+            total += float(np.linalg.norm(t.cpu().numpy()[rows] - exact) / np.linalg.norm(exact)) ** 2
+        error[a_pass] = np.sqrt(total / 4) * 2.0 ** 53
+        s.close()
+    print(error, flush=True)
+    assert error[L.APASS_AUTO] <= error[L.APASS_TWO_PASS]

@@ -169,8 +169,8 @@ size_t lbfgsb_workspace_bytes(int64_t n, int m, const lbfgsb_objective* obj_host
 
 /* Creates a solver.  l, u: device, n entries each, copied.  obj_host/opt_host: host structs,
  * copied (opt_host may be NULL = defaults).  workspace: device, borrowed until destroy.
- * hip_stream: a hipStream_t (or NULL).  Synchronises the stream (bounds are validated on the
- * host).  The iterate is undefined until lbfgsb_set_x. */
+ * hip_stream: a hipStream_t (or NULL).  Synchronises the stream (the bounds are validated on the
+ * device).  The iterate is undefined until lbfgsb_set_x. */
 int lbfgsb_create(lbfgsb_solver** out, int64_t n, int m, const double* l, const double* u,
                   const lbfgsb_objective* obj_host, const lbfgsb_options* opt_host,
                   void* workspace, size_t workspace_bytes, void* hip_stream);
@@ -194,8 +194,10 @@ int lbfgsb_step(lbfgsb_solver* s, lbfgsb_info* info_host);
  * lbfgsb_solve once at the end if the difference matters.) */
 
 /* Iterates until the tolerance, max_iter or a line-search failure.  The device decides all
- * data-dependent branches; the kernel that takes an iteration's stopping decision reports it in pinned host memory, which
- * the host follows one iteration behind without stopping the device.
+ * data-dependent branches; the kernel that takes an iteration's stopping decision reports it in pinned host memory (the
+ * first iterations each, later every fourth or eighth), which the calling thread watches while it enqueues ahead, without
+ * stopping the device.  It polls until the run is over, yielding its core to other threads.  The result does not depend
+ * on how far ahead it was.
  * A least-squares solve is declared converged only with residual and gradient freshly
  * recomputed from x.  info_host may be NULL. */
 int lbfgsb_solve(lbfgsb_solver* s, lbfgsb_info* info_host);
@@ -209,9 +211,11 @@ int lbfgsb_solve(lbfgsb_solver* s, lbfgsb_info* info_host);
  * runs on holds its own copy until the process ends); the host object is static too.
  *   x: device, n entries; in: the feasible start point x0, out: the final iterate.
  *   l, u, obj_host, opt_host, hip_stream, info_host: as for lbfgsb_create / lbfgsb_solve (info_host may be NULL).
- * Same kernels, same arithmetic and same results as the four calls it stands for.  Fails with LBFGSB_E_INVALID_ARG
- * (message naming both sizes) when lbfgsb_workspace_bytes() of the problem exceeds LBFGSB_STATIC_SCRATCH_BYTES, and
- * with the error codes of lbfgsb_create / lbfgsb_set_x otherwise.  Synchronises the stream.  All calls on one GPU
+ * Same kernels, same arithmetic and same results as the four calls it stands for when lbfgsb_workspace_bytes() of the
+ * problem fits LBFGSB_STATIC_SCRATCH_BYTES.  A problem that fits only with a plainer kernel for the products with A (the
+ * partial columns of the single-read ones take the most room) runs on that one, with results that agree to rounding.
+ * Fails with LBFGSB_E_INVALID_ARG (message naming both sizes) when it fits with none, and with the error codes of
+ * lbfgsb_create / lbfgsb_set_x otherwise.  Synchronises the stream.  All calls on one GPU
  * share that GPU's array and host object: calls that overlap on one GPU (two threads, two streams) race; calls on
  * different GPUs do not.  The part of the array a call uses is cleared first, so nothing carries over between calls. */
 #define LBFGSB_STATIC_SCRATCH_BYTES (32u << 20)

@@ -349,3 +349,23 @@ def test_symmetric_products_lose_no_precision():
         s.close()
     print(error, flush=True)
     assert error[L.APASS_AUTO] <= error[L.APASS_TWO_PASS]
+
+
+@pytest.mark.parametrize("cols,bound", [(1500, 1.75), (1100, 1.65)])
+def test_narrow_row_sums_lose_no_precision(cols, bound):
+    """Residuals of Gaussian fp32 rows against 80-bit sums.  (Measured over eight draws in units of 2^-53: 1.61 and 1.55, the
+    ring kernel 1.63 and 1.59; with one chain of additions per lane 1.90 and 1.75.  400 rows of four draws each: the figures
+    vary by 2 %.)"""
+    total = 0.0
+    for seed in range(4):
+        rng = np.random.default_rng(seed)
+        A = rng.standard_normal((2500, cols)).astype(np.float32)
+        b, x, rows = -rng.random(2500), rng.random(cols), rng.choice(2500, 400, replace=False)
+        s = _solver(LSQ, to_dev(A), b, np.zeros(cols), np.full(cols, np.inf))
+        _, _, r = s.dbg_fg(to_dev(x), want_rowvec=True)
+        exact = (A[rows].astype(np.longdouble) * x).sum(1) - b[rows]
+        total += float(np.linalg.norm(r.cpu().numpy()[rows] - exact) / np.linalg.norm(exact)) ** 2
+        s.close()
+    error = np.sqrt(total / 4) * 2.0 ** 53
+    print(error, flush=True)
+    assert error <= bound

@@ -159,7 +159,7 @@ def bench_svm(args, L, workloads, np, torch, dev) -> int:
                 "max_margin_error_free_sv": float(np.abs(sp.y[free] * dec[free] - 1.0).max()) if free.any() else 0.0,
                 "training_accuracy": float(np.mean(np.sign(dec) == sp.y)),
                 "feasible_box": bool(np.all(a >= 0) and np.all(a <= sp.c))},
-        "roofline": {"bound": "hbm", "kernel": "k_sym: t = K (y.p) from the upper triangle of the symmetric matrix, read once per iteration",
+        "roofline": {"bound": "hbm", "kernel": "k_sym and k_sym_finish: t = K (y.p) from the upper triangle of the symmetric matrix, read once per iteration",
                      "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "bytes_per_launch": bytes_per_launch, "avg_launch_ms": apass_avg_ms, "launches_timed": n_launch,
                      "traffic": (MEASURED_TRAFFIC.get((args.config, "fused")) or (None, None))[0],

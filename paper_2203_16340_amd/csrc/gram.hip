@@ -867,7 +867,8 @@ void launch_commit(const Dims& dm, const Buffers& bf, hipStream_t st, Scal* host
 
 // The same, and a run that ended in convergence is open again: the gradient it was judged by is about to be recomputed
 // from x and judged once more.  One launch behind the last step, where the host used to fetch the scalar block, wait, and
-// then set the status with a launch of its own.  NNLS 3001 x 301, whole solve: 405 -> 387 us.
+// then set the status with a launch of its own.  Against fetching the block first, whole calls: NNLS 3001 x 301 400 -> 390 us,
+// 28 inner solves over 8000 x 2000 with one constraint row 8.68 -> 8.30 ms.
 __global__ void k_reopen(Scal* scal, int m) {
     if (threadIdx.x != 0) return;
     apply_pending(scal, m);

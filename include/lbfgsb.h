@@ -212,10 +212,10 @@ int lbfgsb_solve(lbfgsb_solver* s, lbfgsb_info* info_host);
  *   x: device, n entries; in: the feasible start point x0, out: the final iterate.
  *   l, u, obj_host, opt_host, hip_stream, info_host: as for lbfgsb_create / lbfgsb_solve (info_host may be NULL).
  * Same kernels, same arithmetic and same results as the four calls it stands for when lbfgsb_workspace_bytes() of the
- * problem fits LBFGSB_STATIC_SCRATCH_BYTES.  A problem that fits only with a plainer kernel for the products with A (the
- * partial columns of the single-read ones take the most room) runs on that one, with results that agree to rounding.
- * Fails with LBFGSB_E_INVALID_ARG (message naming both sizes) when it fits with none, and with the error codes of
- * lbfgsb_create / lbfgsb_set_x otherwise.  Synchronises the stream.  All calls on one GPU
+ * problem fits LBFGSB_STATIC_SCRATCH_BYTES.  A problem whose rows do not all start on 16-byte boundaries and which fits only
+ * without the partial columns of the single read runs on the two-pass kernels, with results that agree to rounding.
+ * Fails with LBFGSB_E_INVALID_ARG (message naming both sizes) when it does not fit like that either, and with the error
+ * codes of lbfgsb_create / lbfgsb_set_x otherwise.  Synchronises the stream.  All calls on one GPU
  * share that GPU's array and host object: calls that overlap on one GPU (two threads, two streams) race; calls on
  * different GPUs do not.  The part of the array a call uses is cleared first, so nothing carries over between calls. */
 #define LBFGSB_STATIC_SCRATCH_BYTES (32u << 20)

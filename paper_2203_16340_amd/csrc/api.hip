@@ -130,11 +130,12 @@ int check_options(const lbfgsb_options* o) {
     return LBFGSB_OK;
 }
 
-// Which of the single-read kernels may be chosen.  lbfgsb_solve_static, whose workspace is fixed, does with less where
-// their partial columns would not fit.
-enum SingleRead { kReadAligned = 0,   // the ring kernel, rows on 16-byte boundaries only
-                  kReadRing = 1,      // the ring kernel, any rows
-                  kReadAny = 2 };     // also the kernels for short rows and for symmetric matrices
+// Which rows may be read once only.  lbfgsb_solve_static, whose workspace is fixed, does with less where the partial columns
+// of the kernels for rows on any element would not fit: the two-pass kernels, which it ran for such rows before there were
+// any, leave fewer.  (Rows on 16-byte boundaries are left the ring kernel, which needs no less: at the widths of the other
+// two the partial columns of the transposed pass, for which the workspace has room as well, are at least as many.)
+enum SingleRead { kReadAligned = 0,   // rows on 16-byte boundaries, by the ring kernel
+                  kReadAny = 1 };     // any rows; also the kernels for short rows and for symmetric matrices
 Geometry make_geometry(const Dims& dm, const void* A, SingleRead reads = kReadAny) {
     Geometry ge{};
     const int per16 = dm.dtype == LBFGSB_F32 ? 4 : 2;
@@ -151,7 +152,7 @@ Geometry make_geometry(const Dims& dm, const void* A, SingleRead reads = kReadAn
     if (rb < 1) rb = 1;
     ge.gemvt_rows_per_block = (dm.rows + rb - 1) / rb;
     ge.gemvt_row_blocks = (int)((dm.rows + ge.gemvt_rows_per_block - 1) / ge.gemvt_rows_per_block);
-    ge.fused_ok = !is_transport(dm.kind) && (aligned || reads >= kReadRing) &&
+    ge.fused_ok = !is_transport(dm.kind) && (aligned || reads == kReadAny) &&
                   fused_shape_ok(dm, &ge.fused_variant, &ge.fused_blocks) ? 1 : 0;
     ge.narrow_variant = -1;
     if (ge.fused_ok) {
@@ -994,14 +995,11 @@ int lbfgsb_solve_static(int64_t n, int m, const double* l, const double* u, cons
     rc = check_create_args(n, m, l, u, obj, opt, sl->ptr, &o);
     if (rc) return rc;
     size_t need = lbfgsb_workspace_bytes(n, m, obj, &o);
-    // the partial columns of the single-read kernels take the most room: a problem that does not fit the array with the
-    // kernel of its shape may fit it with a plainer one
     SingleRead reads = kReadAny;
-    for (const SingleRead less : {kReadRing, kReadAligned}) {
-        if (need <= (size_t)LBFGSB_STATIC_SCRATCH_BYTES) break;
+    if (need > (size_t)LBFGSB_STATIC_SCRATCH_BYTES) {
         const Dims dm = make_dims(n, m, obj);
-        const size_t without = make_layout(dm, make_geometry(dm, obj->A, less)).total;
-        if (without < need) { need = without; reads = less; }
+        const size_t without = make_layout(dm, make_geometry(dm, obj->A, kReadAligned)).total;
+        if (without < need) { need = without; reads = kReadAligned; }
     }
     if (need == 0 || need > (size_t)LBFGSB_STATIC_SCRATCH_BYTES)
         return fail(LBFGSB_E_INVALID_ARG,

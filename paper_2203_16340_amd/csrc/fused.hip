@@ -59,7 +59,7 @@ void launch_variant(const Dims& dm, int64_t rows_per_wg, int blocks, size_t lds,
 // Ordered by capacity within a (matrix type, objective family) group: the first variant of the group
 // whose NT*KC*VEC columns cover a row and whose LDS need (v for every column) fits is used.  (Narrower rows --
 // narrow_shape_ok: up to 1536 fp32, 1024 or 768 fp64 columns -- have a kernel of their own, narrow.h; they come here
-// only with a leading dimension past 2^24, or from lbfgsb_solve_static when that kernel's partial columns do not fit.)
+// only with a leading dimension past 2^24.)
 // The logistic evaluation kernels spend ~100 registers on exp/log1p, so their rings are shallower; the direction
 // pass of the logistic objective has its own instantiation with the deepest ring that does not spill.
 const Variant kVariants[] = {

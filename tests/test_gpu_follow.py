@@ -63,6 +63,11 @@ def test_rejected_first_steps_leave_the_same_bits_however_far_ahead_the_host_was
     for s in (solved, ahead):
         assert _records(s) == want
         assert torch.equal(s.x(), waited.x()) and torch.equal(s.g(), waited.g())
+    # (the static entry point looks at the status every few steps)
+    x = to_dev(prob.x0)
+    static = L.solve_static(prob.kind, to_dev(prob.A), to_dev(prob.b), to_dev(prob.l), to_dev(prob.u), prob.m, x, lam=prob.lam,
+                            mu=prob.mu, options=L.default_options(tol=0.0, max_iter=iters))
+    assert static.as_dict() == end.as_dict() and torch.equal(x, waited.x())
     for s in (solved, waited, ahead):
         s.close()
 

@@ -192,6 +192,26 @@ def test_static_solve_of_unaligned_rows_that_fit_only_without_the_single_read():
     assert rel_err(x_d.cpu().numpy(), ref.x().cpu().numpy()) <= 1e-10
 
 
+def test_static_solve_of_unaligned_narrow_rows_that_fit_only_without_the_single_read():
+    """The pass for narrow rows would need 6 MB of partial columns beside 27 MB of row vectors."""
+    rows, cols = 1_140_000, 1535
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(6)
+    A_d = torch.randn(rows, cols, dtype=torch.float32, device=DEV, generator=gen)
+    b_d = 10.0 * torch.randn(rows, dtype=torch.float64, device=DEV, generator=gen) + A_d[:, 0].double()
+    l, u = np.zeros(cols), np.full(cols, np.inf)
+    x = np.random.default_rng(6).random(cols) * 0.4
+    opts = L.default_options(tol=0.0, max_iter=3)
+    ref = L.Solver(LSQ, A_d, b_d, to_dev(l), to_dev(u), 5, options=opts)
+    assert ref.workspace.numel() > L.STATIC_SCRATCH_BYTES
+    ref.set_x(to_dev(x))
+    ref.solve()
+    x_d = to_dev(x)
+    info = L.solve_static(LSQ, A_d, b_d, to_dev(l), to_dev(u), 5, x_d, options=opts)
+    assert info.iters == 3
+    assert rel_err(x_d.cpu().numpy(), ref.x().cpu().numpy()) <= 1e-10
+
+
 # the kernel for narrow rows: both sides of every variant's capacity (16-byte chunks 8, 16, 24, 32, 48, 64, 96, 128, 192,
 # 256), ragged widths among them, and row counts around a set (8 rows) and a tile (64 rows)
 NARROW = [4 * c + d for c in (8, 16, 24, 32, 48, 64, 96, 128, 192) for d in (-1, 0, 1)] + [4, 5, 1023, 1024]

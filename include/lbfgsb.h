@@ -92,7 +92,9 @@ typedef struct {
 /* how the products with A are organised (results agree to rounding) */
 enum {
     LBFGSB_APASS_AUTO = 0,     /* fused single read of A when the shape allows it (rows of 2 (fp64) or 4 (fp32) to 20428
-                                  columns, starting on any element), else two passes */
+                                  columns, starting on any element; for kind QP, which has one product either way, rows
+                                  that do not all start on 16-byte boundaries only where that is the faster kernel), else
+                                  two passes */
     LBFGSB_APASS_TWO_PASS = 1, /* t = A v, then w = A^T psi: A is read twice per evaluation and per iteration */
     LBFGSB_APASS_FUSED = 2,    /* force the fused kernel; lbfgsb_create fails if the shape does not fit or the rows do not
                                   all start on 16-byte boundaries.  For the

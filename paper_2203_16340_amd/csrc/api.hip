@@ -152,15 +152,14 @@ Geometry make_geometry(const Dims& dm, const void* A, SingleRead reads = kReadAn
     if (rb < 1) rb = 1;
     ge.gemvt_rows_per_block = (dm.rows + rb - 1) / rb;
     ge.gemvt_row_blocks = (int)((dm.rows + ge.gemvt_rows_per_block - 1) / ge.gemvt_rows_per_block);
-    ge.fused_ok = !is_transport(dm.kind) && (aligned || reads == kReadAny) &&
-                  fused_shape_ok(dm, &ge.fused_variant, &ge.fused_blocks) ? 1 : 0;
+    const bool any = reads == kReadAny;
+    int strips = 0, grid = 0, nv, nb;
+    const bool sym = any && sym_shape_ok(dm, &strips, &grid);
+    ge.fused_ok = !is_transport(dm.kind) && (aligned || any) &&
+                  (fused_shape_ok(dm, aligned, &ge.fused_variant, &ge.fused_blocks) || sym) ? 1 : 0;
     ge.narrow_variant = -1;
-    if (ge.fused_ok) {
-        int nv, nb;
-        if (reads == kReadAny && narrow_shape_ok(dm, &nv, &nb)) { ge.narrow_variant = nv; ge.fused_blocks = nb; }
-        int strips, grid;
-        if (reads == kReadAny && sym_shape_ok(dm, &strips, &grid)) { ge.sym_strips = strips; ge.fused_blocks = grid; }
-    }
+    if (ge.fused_ok && any && narrow_shape_ok(dm, &nv, &nb)) { ge.narrow_variant = nv; ge.fused_blocks = nb; }
+    if (sym) { ge.sym_strips = strips; ge.fused_blocks = grid; }
     ge.gram_blocks = gram_blocks_for(dm.n, dm.m);
     int64_t db = (dm.n + kBlock - 1) / kBlock;
     ge.dir_blocks = (int)(db > kDirBlocksMax ? kDirBlocksMax : db);

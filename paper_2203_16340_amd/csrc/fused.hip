@@ -23,7 +23,7 @@ struct Variant {
     int trans;          // 1: with the transposed accumulation, 0: row products only (quadratic form, symmetric matrix)
     int nt, kc, r;      // threads, 16-byte chunks per thread and row, rows per stage
     int wgs_per_cu;     // workgroups per compute unit the launch is sized for
-    // [0] rows on 16-byte boundaries and whole chunks, [1] rows that start on any element, any number of columns
+    // [0] rows on 16-byte boundaries and whole chunks, [1] rows that start on any element, any number of columns (null: none)
     const void* kernel[2]; // for hipFuncSetAttribute
     LaunchFn launch[2];
     size_t (*lds)(int64_t cols);
@@ -55,6 +55,10 @@ void launch_variant(const Dims& dm, int64_t rows_per_wg, int blocks, size_t lds,
 #define LB_VARIANT_KR(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS, KR) LB_VARIANT_FULL(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS, KR, 1)
 #define LB_VARIANT(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS) LB_VARIANT_FULL(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS, 0, 1)
 #define LB_VARIANT_ROWS(dt, T, NT, KCU, U, R, NB, WPE, WGS) LB_VARIANT_FULL(dt, 0, T, NT, KCU, U, R, NB, WPE, WGS, 0, 0)
+#define LB_VARIANT_ROWS_ALIGNED(dt, T, NT, KCU, U, R, NB, WPE, WGS)                                                          \
+    {dt, 0, 0, NT, (KCU) * (U), R, WGS, {(const void*)ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, 0, 0, false, false>, nullptr}, \
+     {launch_variant<T, NT, KCU, U, R, NB, WPE, 0, 0, false, false>, nullptr}, ring::lds_bytes<T, NT, (KCU) * (U), 0, R>,     \
+     {nullptr, nullptr}, {nullptr, nullptr}}
 
 // Ordered by capacity within a (matrix type, objective family) group: the first variant of the group
 // whose NT*KC*VEC columns cover a row and whose LDS need (v for every column) fits is used.  (Narrower rows --
@@ -83,15 +87,20 @@ const Variant kVariants[] = {
     LB_VARIANT_LOGI(LBFGSB_F32, float, 256, 5, 1, 1, 2, 4, 2, 2),      // cols <=  5120
     LB_VARIANT_LOGI(LBFGSB_F32, float, 512, 5, 1, 1, 2, 4, 2, 1),      // cols <= 10240
     LB_VARIANT_LOGI(LBFGSB_F32, float, 512, 10, 1, 1, 1, 2, 2, 1),     // cols <= 20480 (LDS: <= 20428)
-    // row products only: no accumulators of w, so the ring is deeper (4096 to 15872 columns: symmetric.hip)
-    LB_VARIANT_ROWS(LBFGSB_F64, double, 256, 2, 1, 4, 8, 4, 4),  // cols <=  1024
-    LB_VARIANT_ROWS(LBFGSB_F64, double, 512, 5, 1, 2, 8, 2, 1),  // cols <=  5120
+    // row products only: no accumulators of w, so the ring is deeper (4096 to 15872 columns: symmetric.hip).  The two-pass
+    // organisation reads A once for these too (no transposed pass), and on rows that start on any element its kernel of four
+    // rows per wave is the faster one while the caches serve much of the matrix.  Whole iterations, us, ring / k_gemv: fp64
+    // n = 301 25.0 / 22.4, 1025 41.5 / 38.0, 2201 50.0 / 45.0, 3001 53.0 / 48.8, 4095 59.1 / 54.7, 15873 347 / 377, 20001
+    // 535 / 630; fp32 301 25.0 / 22.1, 1025 40.8 / 37.0, 2001 42.6 / 40.6, 2501 43.8 / 42.8, 2801 44.7 / 45.6, 4095 48.8 / 50.3.
+    LB_VARIANT_ROWS_ALIGNED(LBFGSB_F64, double, 256, 2, 1, 4, 8, 4, 4),  // cols <=  1024
+    LB_VARIANT_ROWS_ALIGNED(LBFGSB_F64, double, 512, 5, 1, 2, 8, 2, 1),  // cols <=  5120
     LB_VARIANT_ROWS(LBFGSB_F64, double, 512, 20, 1, 1, 2, 2, 1), // cols <= 20480 (LDS: <= 20428)
-    LB_VARIANT_ROWS(LBFGSB_F32, float, 256, 1, 1, 4, 8, 4, 4),   // cols <=  1024
-    LB_VARIANT_ROWS(LBFGSB_F32, float, 256, 5, 1, 2, 8, 2, 2),   // cols <=  5120
+    LB_VARIANT_ROWS_ALIGNED(LBFGSB_F32, float, 256, 1, 1, 4, 8, 4, 4),   // cols <=  1024
+    LB_VARIANT_ROWS(LBFGSB_F32, float, 256, 5, 1, 2, 8, 2, 2),   // cols <=  5120, on any element from kRowsAnyMin on
     LB_VARIANT_ROWS(LBFGSB_F32, float, 512, 10, 1, 1, 4, 2, 1),  // cols <= 20480 (LDS: <= 20428)
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
+constexpr int64_t kRowsAnyMin = 2600;
 constexpr size_t kLdsPerWorkgroup = 160 * 1024;   // gfx950
 
 int compute_units() {
@@ -118,7 +127,7 @@ int64_t rows_per_wg_for(const Dims& dm, const Variant& v) {
 
 }  // namespace
 
-bool fused_shape_ok(const Dims& dm, int* variant, int* blocks) {
+bool fused_shape_ok(const Dims& dm, bool aligned, int* variant, int* blocks) {
     *variant = -1;
     *blocks = 0;
     const int vec = dm.dtype == LBFGSB_F32 ? 4 : 2;
@@ -130,6 +139,7 @@ bool fused_shape_ok(const Dims& dm, int* variant, int* blocks) {
             continue;
         if ((int64_t)v.nt * v.kc * vec < dm.cols) continue;
         if (v.lds(dm.cols) > kLdsPerWorkgroup - 256) continue;   // (a few bytes of static LDS come on top)
+        if (!aligned && (!v.launch[1] || (!v.trans && dm.cols < kRowsAnyMin))) return false;
         const int64_t rpw = rows_per_wg_for(dm, v);
         *variant = i;
         *blocks = (int)((dm.rows + rpw - 1) / rpw);

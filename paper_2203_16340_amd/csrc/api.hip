@@ -1295,8 +1295,9 @@ __global__ void k_al_shift_g(int64_t n_eq, int64_t cols, int64_t ld, const T* __
 
 // Both kernels and the fresh scalar block in one workgroup and one launch, for few and short constraint rows (the sum
 // constraint of a simplex is one).  Three launches into an idle stream took about as long as the host needs to make them.
-// Where every inner solve is short that counts: 28 of them over 8000 x 2000 and one constraint row 8.72 -> 8.52 ms.  Beyond 16 entries per thread one workgroup has too few loads in flight, beyond 64
-// rows the targets take more than one wave: then the kernels above.
+// Where every inner solve is short that counts: 28 of them over 8000 x 2000 and one constraint row 8.72 -> 8.52 ms.  Beyond
+// 16 entries per thread one workgroup has too few loads in flight, beyond 64 rows the targets take more than one wave: then
+// the kernels above.
 constexpr int kShiftThreads = 1024;
 constexpr int kShiftRowsMax = 64;                        // (one wave's lanes)
 constexpr int64_t kShiftMax = 16 * kShiftThreads;        // matrix entries: at most 16 per thread

@@ -132,7 +132,8 @@ int check_options(const lbfgsb_options* o) {
 
 // Which rows may be read once only.  lbfgsb_solve_static, whose workspace is fixed, does with less where the partial columns
 // of the kernels for rows on any element would not fit: the two-pass kernels, which it ran for such rows before there were
-// any, leave fewer.  (Rows on 16-byte boundaries are left the ring kernel, which needs no less: at the widths of the other
+// any, leave fewer; and the Gram kernel on long vectors gets half the workgroups, whose records take no more than those of the
+// kernel that odd lengths had before.  (Rows on 16-byte boundaries are left the ring kernel, which needs no less: at the widths of the other
 // two the partial columns of the transposed pass, for which the workspace has room as well, are at least as many.)
 enum SingleRead { kReadAligned = 0,   // rows on 16-byte boundaries, by the ring kernel
                   kReadAny = 1 };     // any rows; also the kernels for short rows and for symmetric matrices
@@ -160,7 +161,7 @@ Geometry make_geometry(const Dims& dm, const void* A, SingleRead reads = kReadAn
     ge.narrow_variant = -1;
     if (ge.fused_ok && any && narrow_shape_ok(dm, &nv, &nb)) { ge.narrow_variant = nv; ge.fused_blocks = nb; }
     if (sym) { ge.sym_strips = strips; ge.fused_blocks = grid; }
-    ge.gram_blocks = gram_blocks_for(dm.n, dm.m);
+    ge.gram_blocks = gram_blocks_for(dm.n, dm.m, !any);
     int64_t db = (dm.n + kBlock - 1) / kBlock;
     ge.dir_blocks = (int)(db > kDirBlocksMax ? kDirBlocksMax : db);
     int64_t ub = (dm.cols + 15) / 16;   // 16 columns per workgroup in the column-sum kernels
@@ -223,7 +224,7 @@ Layout make_layout(const Dims& dm, const Geometry& ge) {
     if (ge.lrows_blocks > lparts) lparts = ge.lrows_blocks;
     if (is_transport(dm.kind) && ge.ot_row_blocks + ge.ot_col_blocks > lparts) lparts = ge.ot_row_blocks + ge.ot_col_blocks;
     L.losspart = take((size_t)lparts * 8);
-    L.grampart = take(gram_partial_bytes(dm.n, dm.m));
+    L.grampart = take(gram_partial_bytes(ge.gram_blocks, dm.m));
     size_t red = (size_t)ge.dir_blocks * (8 + 2 * kFoldMax);
     if ((size_t)ge.upd_blocks * 2 > red) red = (size_t)ge.upd_blocks * 2;
     if ((size_t)ge.updl_blocks * 2 > red) red = (size_t)ge.updl_blocks * 2;
@@ -397,15 +398,16 @@ void enqueue_step(lbfgsb_solver* s) {
         // no matrix product: the iteration streams the pair memory twice (Gram matrix, direction) and the
         // iterate-sized vectors a few times.  The Gram kernel is the longest and the one that is timed.
         // (timed only once the pair memory is full, so that every timed launch moves the same bytes)
+        // (the Gram kernel ends without its closing step, which the direction kernel does, and that kernel without its own: the
+        // row-sum kernel, the first to need Algorithm 2's choice, makes it from the per-workgroup sums)
+        const int open_gram = gram_can_skip_close(s->dm) ? 1 : 0;
         {
             TimedSlot ts(s, s->steps_since_set_x >= s->dm.m);
-            launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, ts.e0, ts.e1);
+            launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, ts.e0, ts.e1, open_gram);
         }
-        // (the direction kernel ends without its closing step: the row-sum kernel, the first to need Algorithm 2's
-        // choice, makes it from the per-workgroup sums)
-        launch_dir(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream, nullptr, nullptr, 1);
+        launch_dir(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream, nullptr, nullptr, 1, open_gram);
         const OtArgs oa = ot_args(s);
-        launch_ot_sums(s->dm, s->ge, s->bf, oa, 0, 1, s->stream, s->ge.dir_blocks, s->op.eps);
+        launch_ot_sums(s->dm, s->ge, s->bf, oa, 0, 1, s->stream, s->ge.dir_blocks, s->op.eps, open_gram ? s->bf.scal_next : nullptr);
         if (quad) launch_ot_update_gauss(s->dm, s->op, s->ge, s->bf, oa, s->stream);
         else launch_ot_step_entropy(s->dm, s->op, s->ge, s->bf, oa, s->stream);
         s->steps_since_refresh++;
@@ -425,13 +427,13 @@ void enqueue_step(lbfgsb_solver* s) {
     // ... and then the Gram kernel needs no closing step either, where its grid is small enough for the direction
     // kernel's workgroups to add its partial sums themselves: they finish its work on private copies of the scalar
     // block, and the pass moves workgroup 0's copy into place (Buffers::scal_next)
-    const bool open_gram = defer && gram_can_skip_close(s->dm, s->ge);
+    const bool open_gram = defer && gram_can_skip_close(s->dm);
     if (small) {
         launch_small_step(s->dm, s->op, s->bf, fold_rows, s->obj.extra_weight, s->stream);
     } else {
         launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, nullptr, nullptr, open_gram ? 1 : 0);
         launch_dir(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream, fold_rows, s->obj.extra_weight, defer ? 1 : 0,
-                   open_gram ? s->ge.gram_blocks : 0);
+                   open_gram ? 1 : 0);
     }
     APassArgs a = base_args(s);
     a.select_p = 1;
@@ -625,7 +627,7 @@ int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj
     if (o.a_pass == LBFGSB_APASS_FUSED && (!s->ge.fused_ok || s->ge.vec == 1))
         return fail(LBFGSB_E_UNSUPPORTED, "the fused A pass does not support this shape");
     {
-        const hipError_t ge_ = gram_prepare(n, m);
+        const hipError_t ge_ = gram_prepare(s->dm);
         if (ge_ != hipSuccess) return fail(LBFGSB_E_HIP, "preparing the Gram kernel: %s", hipGetErrorString(ge_));
     }
     const bool resident_ok = resident_shape_ok(s->dm, obj->row_weight != nullptr);

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "../../include/lbfgsb.h"
@@ -294,6 +295,20 @@ struct DirChoice {
     int branch;              // 1: p = P(x + d) - x, step bound 1;  2: p = d with outward components zeroed
     double gp, alpha_ub, pp, xp;
 };
+
+// Word k of a scalar block that is v, with the choice written into it.
+__device__ __forceinline__ int scal_word_with_choice(int k, int v, const DirChoice& ch) {
+    auto put_double = [&](size_t off, double val) {
+        if (k == (int)(off / 4)) v = __double2loint(val);
+        if (k == (int)(off / 4) + 1) v = __double2hiint(val);
+    };
+    if (k == (int)(offsetof(Scal, branch) / 4)) v = ch.branch;
+    put_double(offsetof(Scal, gp), ch.gp);
+    put_double(offsetof(Scal, alpha_ub), ch.alpha_ub);
+    put_double(offsetof(Scal, pp), ch.pp);
+    put_double(offsetof(Scal, xp), ch.xp);
+    return v;
+}
 
 // The choice, computed by ONE FULL WAVE from the records of `nblocks` workgroups: lane l adds records l, l + 64, ...
 // in that order, then the fixed-order wave reductions.  Every wave that calls this on the same records gets the same
@@ -609,11 +624,14 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 void launch_set_status(const Buffers& bf, int status, hipStream_t st);
 void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* lin, const double* sign,
                         hipStream_t st);   // lin, sign: QP only (linear term b, sign vector)
-// no_close (wide kernel with a one-level grid only, see gram_can_skip_close): the kernel ends when its workgroups'
-// partial sums are written; the direction kernel does the rest (launch_dir with gram_blocks > 0)
+// no_close (see gram_can_skip_close): the kernel ends when its records of partial sums are written; the direction kernel does
+// the rest (launch_dir with open_gram)
 void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int dbg_inputs,
                  int evaluate_stop, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, int no_close = 0);
-bool gram_can_skip_close(const Dims& dm, const Geometry& ge);
+bool gram_can_skip_close(const Dims& dm);
+// ... what it then finds: `count` records (workgroups' sums, or those of groups of workgroups)
+struct GramRecords { const double* part; int count; };
+GramRecords gram_records(const Dims& dm, const Geometry& ge, const Buffers& bf);
 // host_scal: pinned host memory that receives the scalar block as well (null: device copy only)
 void launch_commit(const Dims& dm, const Buffers& bf, hipStream_t st, Scal* host_scal = nullptr);
 void launch_reopen(const Dims& dm, const Buffers& bf, hipStream_t st);   // applies a pending update; CONVERGED -> RUNNING
@@ -633,12 +651,12 @@ bool dir_folds_extra_rows(const Dims& dm);
 // fold_rows / fold_weight: the objective's extra rows and their weights when they are to ride along (else NULL)
 // defer_choice: the kernel stops after its partial sums (no last workgroup, nothing written to the scalar block): the
 // consumer of the direction makes Algorithm 2's choice from them (APassArgs::dir_part); not with folded rows
-// gram_blocks > 0 (short vectors only): the Gram kernel left its workgroups' partial sums without a closing step; every
-// workgroup of the direction kernel adds them, applies the pending update and runs the recursion on a private copy of
-// the scalar block, and workgroup 0 leaves its copy in Buffers::scal_next
+// open_gram: the Gram kernel left its records of partial sums without a closing step; every workgroup of the direction kernel
+// adds them, applies the pending update and runs the recursion on a private copy of the scalar block, and workgroup 0
+// leaves its copy in Buffers::scal_next
 void launch_dir(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int d_given, int store_d,
                 hipStream_t st, const double* fold_rows = nullptr, const double* fold_weight = nullptr,
-                int defer_choice = 0, int gram_blocks = 0);
+                int defer_choice = 0, int open_gram = 0);
 // fold_weight, dir_blocks > 0: the direction kernel ended without its closing step; the update kernel forms the folded
 // rows' coefficients itself from that kernel's per-workgroup sums (Buffers::redpart)
 void launch_update_quadratic(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const double* sign,
@@ -671,8 +689,9 @@ struct OtArgs {
 };
 // dir_blocks > 0 (direction sums only): the direction kernel has left its partial sums in Buffers::redpart without
 // choosing between Algorithm 2's candidates; the row-sum kernel makes the choice and records it in the scalar block
+// scal_next (or null): as for a pass over A, see Buffers::scal_next
 void launch_ot_sums(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, int eval, int check_status,
-                    hipStream_t st, int dir_blocks = 0, double eps = 0.0);
+                    hipStream_t st, int dir_blocks = 0, double eps = 0.0, Scal* scal_next = nullptr);
 void launch_ot_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, hipStream_t st);
 void launch_ot_update_gauss(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
                             hipStream_t st);
@@ -692,8 +711,8 @@ hipError_t resident_prepare(const Dims& dm);   // once per solver, before the fi
 void launch_resident(const Dims& dm, const Opts& op, const Buffers& bf, const void* A, const double* b, int max_steps,
                      int refresh_every, hipStream_t st, Scal* host_scal = nullptr);
 
-int gram_blocks_for(int64_t n, int m);
-size_t gram_partial_bytes(int64_t n, int m);   // Buffers::grampart
-hipError_t gram_prepare(int64_t n, int m);     // once per solver, before the first launch_gram
+int gram_blocks_for(int64_t n, int m, bool few);   // few: at most kGramOneLevelMax
+size_t gram_partial_bytes(int blocks, int m);      // Buffers::grampart
+hipError_t gram_prepare(const Dims& dm);       // once per solver, before the first launch_gram
 
 }  // namespace lb

@@ -14,285 +14,61 @@
 // wave owns row i, so a step is one broadcast and one multiply-add, with no cross-lane reduction.
 // G must be rebuilt every iteration because S changes; it costs one pass over the 2c+1 vectors.
 //
-// Three kernels build G: k_gram_wide (m <= 10 and even n: element pairs per lane, entries of G divided among the waves),
-// k_gram_mfma (m > 10 from 2^17 entries on: matrix cores), else k_gram (tiles of G per thread, operands staged through
-// LDS).  Steps on short vectors build it in small.hip.  All end in the same recursion on coefficients (recursion_on_coefficients).
+// (Steps on short vectors build it in small.hip.)
 #include <cstddef>
 
 #include "common.h"
+#include "gram_close.h"
 #include "recursion.h"
-#include "wide_close.h"
 
 namespace lb {
 
 namespace {
-constexpr int kStageMax = 32;   // vectors one thread stages per chunk
-constexpr int kHdr = kGramHdr;   // per-workgroup partial: [0] sum g[S]^2, [1] max KKT residual, [2] #fixed, [3] ||y_new||^2
-constexpr int kTPT = 3;         // tiles per thread when there are more 2x2 tiles than threads (<= 528)
 
-__host__ __device__ inline int gram_tiles(int V) {
-    const int T = (V + 1) / 2;
-    return T * (T + 1) / 2;
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+constexpr int64_t kGramLongN = 1 << 17;   // from here on one workgroup per compute unit and the two-level sum
+
+// A kernel is made for M slots of the pair memory (m <= M).
+constexpr int gram_slots(int M) { return 2 * M + 1; }                     // y ring 0 .. M-1 | g M | s ring M+1 .. 2M
+constexpr int gram_nb(int M) { return (gram_slots(M) + 15) / 16; }        // blocks of 16 slots
+constexpr int gram_waves_most(int M) { return M <= 10 ? 8 : 4; }          // (LDS: 16 NB vectors of 64 elements per wave)
+// pairs of blocks (a <= b) that hold products the recursion reads: not those of two blocks of s vectors only (16 a > M)
+constexpr int gram_na(int M) { return 1 + M / 16; }
+constexpr int gram_np(int M) { return gram_na(M) == 1 ? gram_nb(M) : 2 * gram_nb(M) - 1; }
+// A wave's 64 elements of every vector in LDS: doubles from one vector to the next, even and an odd multiple of two, so that
+// 16 lanes that read 16 bytes each of 16 vectors touch every bank once
+constexpr int kGramStride = 66;
+// the waves' elements; then their blocks; then G (at most (2 M + 2)^2) and the totals
+constexpr int gram_lds_doubles(int M, int waves) {
+    const int elems = waves * 16 * gram_nb(M) * kGramStride, blocks = waves * gram_np(M) * 256;
+    return elems > blocks ? elems : blocks;
 }
-}  // namespace
+constexpr int gram_tot_at(int M) { return (2 * M + 2) * (2 * M + 2); }
+static_assert(gram_tot_at(5) + gram_entries(5) <= gram_lds_doubles(5, 4) && gram_tot_at(10) + gram_entries(10) <= gram_lds_doubles(10, 4) &&
+              gram_tot_at(20) + gram_entries(20) <= gram_lds_doubles(20, 4) && gram_tot_at(31) + gram_entries(31) <= gram_lds_doubles(31, 4),
+              "G and the totals fit");
 
-int gram_entries(int m) { return kHdr + 4 * gram_tiles(2 * m + 1); }
-
-// elements staged per chunk: as many as a 60 KiB tile [chunk][2m+2] allows
-int gram_chunk(int m) {
-    const int vp = 2 * m + 2;
-    return vp <= 30 ? 256 : (vp <= 60 ? 128 : 64);
-}
-size_t gram_lds_bytes(int m) {
-    size_t d = (size_t)gram_chunk(m) * (2 * m + 2);
-    if (d < 1024) d = 1024;
-    return d * 8;
-}
-__device__ __forceinline__ void tile_of(int q, int T, int& ti, int& tj) {
-    int a = 0;
-    while (q >= T - a) { q -= T - a; ++a; }
-    ti = a; tj = a + q;
-}
-
-__global__ __launch_bounds__(kBlock) void k_gram(int64_t n, int m, int E, Opts op, const double* __restrict__ x,
-                                                 const double* __restrict__ g, const double* __restrict__ l,
-                                                 const double* __restrict__ u, const double* __restrict__ S,
-                                                 const double* __restrict__ Y, uint8_t* __restrict__ mask,
-                                                 Scal* __restrict__ scal, double* __restrict__ grampart, int NE,
-                                                 int dbg_inputs, int evaluate_stop) {
-    extern __shared__ __align__(16) double dyn[];   // staged chunk [element][vector]; later scratch and G
-    __shared__ double red[kWaves * 4];
-    __shared__ double alpha_s[kMaxM + 1];
-    __shared__ int flag;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // one load per wave fetches the integer header of the scalar block (status, ring position, pending
-    // update); readlanes hand the fields to every lane
-    static_assert(offsetof(Scal, pend_ok) < 64, "header fields must sit in the first 16 ints");
-    const int hdr = lane < 16 ? reinterpret_cast<const int*>(scal)[lane] : 0;
-    if (__shfl(hdr, offsetof(Scal, status) / 4) != LBFGSB_RUNNING) {
-        // a step that finds the solver parked by the short logistic sequence is counted, so that the host can redo it
-        const int status = __shfl(hdr, offsetof(Scal, status) / 4);
-        if (evaluate_stop && !dbg_inputs && blockIdx.x == 0 && tid == 0) {
-            if (status == kStatusBail) scal->bail_skipped += 1;
-            note_progress(op, status);
-        }
-        return;
-    }
-    int head = __shfl(hdr, offsetof(Scal, head) / 4), c = __shfl(hdr, offsetof(Scal, count) / 4);
-    if (__shfl(hdr, offsetof(Scal, pend_valid) / 4)) {          // same rule as effective_ring()
-        if (__shfl(hdr, offsetof(Scal, pend_ok) / 4)) { head = (head + 1) % m; c = c < m ? c + 1 : m; }
-        else c = 0;
-    }
-    const double yn_old = prefetch_ynorm2(scal, c, head, m);   // (used by the last workgroup's recursion, fetched now)
-    const int V = 2 * c + 1;
-    const int Vp = V + 1;
-    const int T = Vp / 2;
-    const int TT = T * (T + 1) / 2;
-    const int jnew = 2 * c - 1;   // newest y (none when c == 0)
-    const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;   // ring slot of the oldest pair
-    auto vec_ptr = [&](int j) -> const double* {
-        if (j >= 2 * c) return g;
-        const bool is_y = j >= c;
-        int sl = base_slot + (is_y ? j - c : j);
-        if (sl >= m) sl -= m;
-        return (is_y ? Y : S) + (int64_t)sl * n;
-    };
-
-    // which 2x2 tiles of G this thread accumulates, and over which elements of a chunk
-    const bool split = TT <= kBlock;                  // several threads share a tile, each takes a slice of the elements
-    const int groups = split ? kBlock / TT : 1;
-    const int h = split ? tid / TT : 0;
-    int ti[kTPT], tj[kTPT];
-    double acc[kTPT][4];
-#pragma unroll
-    for (int k = 0; k < kTPT; ++k) {
-        const int q = split ? (k == 0 && h < groups ? tid % TT : -1) : (tid + k * kBlock < TT ? tid + k * kBlock : -1);
-        if (q >= 0) tile_of(q, T, ti[k], tj[k]); else { ti[k] = -1; tj[k] = 0; }
-        acc[k][0] = acc[k][1] = acc[k][2] = acc[k][3] = 0.0;
-    }
-    double pg2 = 0.0, pginf = 0.0, nfixed = 0.0, ynew = 0.0;
-    const int ngrp = kBlock / E;
-    const int el = tid % E, grp = tid / E;
-    __syncthreads();
-
-    for (int64_t e0 = (int64_t)blockIdx.x * E; e0 < n; e0 += (int64_t)gridDim.x * E) {
-        // thread (el, grp) stages vectors grp, grp + ngrp, ... of element e0 + el: every load is issued
-        // before any is used
-        const int64_t e = e0 + el;
-        double st[kStageMax];
-        double mf = 0.0;
-        if (e < n) {
-            // unconditional loads (an index past the last vector re-reads g[e]) so that nothing
-            // separates them and all are in flight together; the surplus ones are zeroed afterwards
-#pragma unroll
-            for (int k = 0; k < kStageMax; ++k) {
-                const int j = grp + ngrp * k;
-                st[k] = vec_ptr(j < V ? j : V - 1)[e];
-            }
-            const double xe = x[e], ge = g[e], le = l[e], ue = u[e];
-            int fr;
-            if (dbg_inputs) {
-                fr = mask[e] != 0;
-            } else {
-                const bool at_lower = (xe <= le + op.eps) && (ge >= 0.0);
-                const bool at_upper = (xe >= ue - op.eps) && (ge <= 0.0);
-                fr = !(at_lower || at_upper);
-            }
-            mf = fr ? 1.0 : 0.0;
-#pragma unroll
-            for (int k = 0; k < kStageMax; ++k)
-                if (grp + ngrp * k >= V) st[k] = 0.0;
-            if (grp == 0) {
-                if (!dbg_inputs) mask[e] = (uint8_t)fr;
-                if (fr) pg2 = fma(ge, ge, pg2); else nfixed += 1.0;
-                pginf = fmax(pginf, fabs(xe - clampd(xe - ge, le, ue)));
-            }
-#pragma unroll
-            for (int k = 0; k < kStageMax; ++k)
-                if (grp + ngrp * k == jnew) ynew = fma(st[k], st[k], ynew);
-        } else {
-#pragma unroll
-            for (int k = 0; k < kStageMax; ++k) st[k] = 0.0;
-        }
-        __syncthreads();   // the previous chunk has been consumed
-#pragma unroll
-        for (int k = 0; k < kStageMax; ++k) {
-            const int j = grp + ngrp * k;
-            if (j < Vp) dyn[el * Vp + j] = st[k] * mf;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kTPT; ++k) {
-            if (ti[k] >= 0) {
-                const double* pa = dyn + 2 * ti[k];
-                const double* pb = dyn + 2 * tj[k];
-#pragma unroll 4
-                for (int i = h; i < E; i += groups) {
-                    const double2 a = *reinterpret_cast<const double2*>(pa + i * Vp);
-                    const double2 b = *reinterpret_cast<const double2*>(pb + i * Vp);
-                    acc[k][0] = fma(a.x, b.x, acc[k][0]);
-                    acc[k][1] = fma(a.x, b.y, acc[k][1]);
-                    acc[k][2] = fma(a.y, b.x, acc[k][2]);
-                    acc[k][3] = fma(a.y, b.y, acc[k][3]);
-                }
-            }
-        }
-    }
-    double* part = grampart + (int64_t)blockIdx.x * NE;
-    if (split && groups > 1) {
-        // add the element slices of each tile in slice order
-        __syncthreads();
-        if (ti[0] >= 0) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) dyn[(h * TT + tid % TT) * 4 + s] = acc[0][s];
-        }
-        __syncthreads();
-        if (h == 0) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                double t = 0.0;
-                for (int hh = 0; hh < groups; ++hh) t += dyn[(hh * TT + tid) * 4 + s];
-                part[kHdr + 4 * tid + s] = t;
-            }
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < kTPT; ++k) {
-            if (ti[k] >= 0) {
-                const int q = split ? tid : tid + k * kBlock;
-#pragma unroll
-                for (int s = 0; s < 4; ++s) part[kHdr + 4 * q + s] = acc[k][s];
-            }
-        }
-    }
-    {
-        double sv[3] = {pg2, nfixed, ynew};
-        block_sum<3, kWaves>(sv, red);
-        double mx = wave_max(pginf);
-        __syncthreads();
-        if (lane == 0) red[wave] = mx;
-        __syncthreads();
-        if (tid == 0) {
-            mx = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-            part[0] = sv[0]; part[1] = mx; part[2] = sv[1]; part[3] = sv[2];
-        }
-    }
-    if (!arrive_is_last(&scal->counters[kCntGram], &flag)) return;
-
-    // ---- last workgroup: total G, then the recursion on coefficients ----
-    const int nb = gridDim.x;
-    double* G = dyn;   // Vp x Vp, row-major
-    __shared__ double wsum[kWaves];
-    // statistics header of every workgroup (strided over the threads): issued first, used after the G sums
-    double sv[3] = {0.0, 0.0, 0.0};
-    double mx = 0.0;
-    for (int b = tid; b < nb; b += kBlock) {
-        const double* hp = grampart + (int64_t)b * NE;
-        sv[0] += hp[0]; sv[1] += hp[2]; sv[2] += hp[3];
-        mx = fmax(mx, hp[1]);
-    }
-    // one thread per entry adds the partials in workgroup order, 24 loads in flight (larger batches
-    // measured no faster: one compute unit's load bandwidth is the limit once there are ~100 partials)
-    for (int q4 = tid; q4 < 4 * TT; q4 += kBlock) {
-        const double* src = grampart + kHdr + q4;
-        double s = 0.0;
-        for (int b0 = 0; b0 < nb; b0 += 24) {
-            double v[24];
-#pragma unroll
-            for (int k = 0; k < 24; ++k) v[k] = b0 + k < nb ? src[(int64_t)(b0 + k) * NE] : 0.0;
-#pragma unroll
-            for (int k = 0; k < 24; ++k) s += v[k];
-        }
-        int a, bq;
-        tile_of(q4 >> 2, T, a, bq);
-        const int row = 2 * a + ((q4 >> 1) & 1), col = 2 * bq + (q4 & 1);
-        G[row * Vp + col] = s;
-        G[col * Vp + row] = s;
-    }
-    {
-        // per-workgroup statistics: fixed-order reductions
-        block_sum<3, kWaves>(sv, red);
-        mx = wave_max(mx);
-        __syncthreads();
-        if (lane == 0) wsum[wave] = mx;
-        __syncthreads();
-        if (tid == 0) {
-            red[0] = sv[0];
-            red[1] = fmax(fmax(wsum[0], wsum[1]), fmax(wsum[2], wsum[3]));
-            red[2] = sv[1];
-            red[3] = sv[2];
-            // apply the update the previous kernel left pending, then record the newest pair's norm
-            apply_pending(scal, m);
-            if (c > 0 && !dbg_inputs) scal->ynorm2[(head - 1 + m) % m] = sv[2];
-        }
-    }
-    __syncthreads();
-    recursion_on_coefficients(G, Vp, c, head, m, op, scal, red[0], red[1], red[2], red[3], yn_old, alpha_s, dbg_inputs, evaluate_stop);
-    if (tid == 0 && evaluate_stop) note_progress(op, scal->status);
-}
-
-
-// ---- large n: partial results of many workgroups, added in two levels ---------------------------------------
-//
-// Every workgroup has written NE doubles at grampart + blockIdx.x * NE (entry 1 is a maximum, all others are
+// Every workgroup has written NE doubles at grampart + blockIdx.x * NE (entry 0 is a maximum, all others are
 // sums).  The workgroups form at most kGramGroups groups of consecutive indices; the last workgroup of a group
 // to finish adds the group's partials in index order into grampart + (gridDim.x + group) * NE, and the last
 // group to finish adds the group results, again in index order, into tot[0 .. NE) (LDS).  Returns true in that
 // one workgroup (after a barrier), false everywhere else.  No workgroup reads more than kGramGroupMax partials,
 // and the order of the additions does not depend on which workgroup finishes last.  Grids of at most
 // kGramOneLevelMax workgroups skip the first level (each level costs two fences, an atomic and a dependent round of
-// loads: 6-7 us).
-constexpr int kGramGroupMax = 32;   // workgroups per group at most: grids of up to kGramGroups * kGramGroupMax
+// loads: 6-7 us).  groups_only: the second level, and what follows it, is left to the direction kernel.
+constexpr int kGramGroupMax = 16;   // workgroups per group at most: grids of up to kGramGroups * kGramGroupMax
 
+template <int NT>
 __device__ __forceinline__ bool reduce_partials(double* __restrict__ grampart, int NE, Scal* __restrict__ scal, int* flag,
-                                                double* tot) {
+                                                double* tot, bool groups_only) {
     const int tid = threadIdx.x, nwg = gridDim.x;
     if (nwg <= kGramOneLevelMax) {
+        if (groups_only) return false;
         // few workgroups: one level, the last one to finish adds all partials in index order
         if (!arrive_is_last(&scal->gram_cnt[kGramGroups], flag, (unsigned)nwg)) return false;
-        // 64 partials of an entry at a time, every load of a batch issued before the first is used (one trip to
-        // memory per batch; the accumulators' registers are free by now)
-        gram_sum_partials_flat(grampart, NE, nwg, tot);
+        gram_sum_partials_flat<NT>(grampart, NE, nwg, tot);
         __syncthreads();
         return true;
     }
@@ -300,552 +76,347 @@ __device__ __forceinline__ bool reduce_partials(double* __restrict__ grampart, i
     const int ngroups = (nwg + gs - 1) / gs;
     const int grp = blockIdx.x / gs, gfirst = grp * gs;
     const int gsize = nwg - gfirst < gs ? nwg - gfirst : gs;
-    if (!arrive_is_last(&scal->gram_cnt[grp], flag, (unsigned)gsize)) return false;
-    double* part2 = grampart + (int64_t)(nwg + grp) * NE;
-    for (int idx = tid; idx < NE; idx += kBlock) {
+    auto add = [&](int first, int count, int idx) -> double {
         double v[kGramGroupMax];
 #pragma unroll
-        for (int k = 0; k < kGramGroupMax; ++k) v[k] = k < gsize ? grampart[(int64_t)(gfirst + k) * NE + idx] : 0.0;
+        for (int k = 0; k < kGramGroupMax; ++k) v[k] = k < count ? grampart[(int64_t)(first + k) * NE + idx] : 0.0;
         double t = v[0];
-        if (idx == 1) {
+        if (idx == 0) {
 #pragma unroll
             for (int k = 1; k < kGramGroupMax; ++k) t = fmax(t, v[k]);
         } else {
 #pragma unroll
             for (int k = 1; k < kGramGroupMax; ++k) t += v[k];
         }
-        part2[idx] = t;
-    }
+        return t;
+    };
+    static_assert(kGramGroups <= kGramGroupMax, "one batch of loads at either level");
+    if (!arrive_is_last(&scal->gram_cnt[grp], flag, (unsigned)gsize)) return false;
+    for (int idx = tid; idx < NE; idx += NT) grampart[(int64_t)(nwg + grp) * NE + idx] = add(gfirst, gsize, idx);
+    if (groups_only) return false;
     if (!arrive_is_last(&scal->gram_cnt[kGramGroups], flag, (unsigned)ngroups)) return false;
-    for (int idx = tid; idx < NE; idx += kBlock) {
-        double v[kGramGroups];
-#pragma unroll
-        for (int k = 0; k < kGramGroups; ++k) v[k] = k < ngroups ? grampart[(int64_t)(nwg + k) * NE + idx] : 0.0;
-        double t = v[0];
-        if (idx == 1) {
-#pragma unroll
-            for (int k = 1; k < kGramGroups; ++k) t = fmax(t, v[k]);
-        } else {
-#pragma unroll
-            for (int k = 1; k < kGramGroups; ++k) t += v[k];
-        }
-        tot[idx] = t;
-    }
+    for (int idx = tid; idx < NE; idx += NT) tot[idx] = add(nwg, ngroups, idx);
     __syncthreads();
     return true;
 }
 
-// ---- large n: the Gram matrix on the matrix cores ---------------------------------------------------------
+}  // namespace
+
+// G = B^T B on the matrix cores.  B = [vectors | n x (2m+1)], masked by the free set, is a tall-skinny contraction whose
+// operands stream from memory once.  A wave takes 64 consecutive elements per chunk: lane j loads element e0 + j of every
+// vector (512 contiguous bytes per load), evaluates Eq. (ws) for it, and writes the vectors' entries, masked, to the wave's
+// own part of LDS.  From there v_mfma_f64_16x16x4_f64 takes them, which multiplies a 16 x 4 by a 4 x 16 block: lane
+// (i = lane % 16, q = lane / 16) supplies A[i][q] and B[q][i'], for a Gram matrix both the same number, vector 16 b + i at one
+// element, so that one register feeds both operands.  Which element a (lane, step) holds does not matter for the sum: 16-byte
+// reads, elements 8 s + 2 q and the next.  Result of lane l, register r of a 16 x 16 block: row l/16 + 4 r, column l % 16.
+// No wave waits for another before its last chunk.
 //
-// G = B^T B with B = [vectors | n x (2c+1)] masked by the free set is a tall-skinny symmetric rank-n update: a
-// dense contraction whose operands stream from memory once.  v_mfma_f64_16x16x4_f64 multiplies a 16 x 4 by a
-// 4 x 16 block; lane (i = lane % 16, q = lane / 16) supplies A[i][q] and B[q][i'] -- for a Gram matrix both are
-// the same number, vector (16 b + i) at one element, so ONE register per lane feeds both operands and the loads
-// go straight from memory into the operand layout (no LDS staging).  A wave takes 64 consecutive elements per
-// chunk: lane (i, q) loads, for each of its NB vectors, eight element pairs e0 + 8 s + 2 q + {0,1} (16-byte loads,
-// 64 contiguous bytes per vector and instruction) and issues 16 multiply steps; which element a (lane, step)
-// holds does not matter for the sum as long as the free-set bit applied to it is that element's.  Lane j of the
-// wave evaluates Eq. (ws) for element e0 + j, a ballot turns the 64 results into a bit mask, and step t reads
-// bit 8 (t/2) + 2 q + (t%2).  One extra vector slot carries an UNMASKED copy of the newest y, whose diagonal
-// entry is the full-vector ||y||^2 the curvature gate needs.
-// Result of lane l, register r of a 16 x 16 block: row l/16 + 4 r, column l % 16.
-
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
-constexpr int64_t kMfmaMinN = 1 << 17;
-__host__ __device__ inline int mfma_blocks16(int m) { return (2 * m + 2 + 15) / 16; }   // 2m+1 vectors + unmasked y
-__host__ __device__ inline int mfma_nb(int m) { const int b = mfma_blocks16(m); return b <= 1 ? 1 : (b <= 2 ? 2 : 4); }
-__host__ __device__ inline int mfma_entries(int nb) { return kHdr + nb * (nb + 1) / 2 * 256; }
-// (m <= 10: k_gram_wide.  With 20 pairs and 10^6 variables this kernel takes 181 us per launch where the LDS-tiled
-// k_gram takes 457 us on the same data: a 41 x 41 x 10^6 contraction is matrix-core work.)
-bool gram_uses_mfma(int64_t n, int m) { return n >= kMfmaMinN && n % 2 == 0 && m > 10; }
-
-template <int NB>
-__global__ __launch_bounds__(kBlock) void k_gram_mfma(int64_t n, int m, Opts op, const double* __restrict__ x,
-                                                      const double* __restrict__ g, const double* __restrict__ l,
-                                                      const double* __restrict__ u, const double* __restrict__ S,
-                                                      const double* __restrict__ Y, uint8_t* __restrict__ mask,
-                                                      Scal* __restrict__ scal, double* __restrict__ grampart,
-                                                      int dbg_inputs, int evaluate_stop) {
-    constexpr int NBP = NB * (NB + 1) / 2;
-    constexpr int NEM = kHdr + NBP * 256;
-    extern __shared__ __align__(16) double dyn[];   // kWaves x NBP x 256 accumulators; later G
-    __shared__ double red[kWaves * 4];
+// LONG: what bounds it is memory: at n = 10^6 and 10 pairs the multiplications take 13 us of matrix-core time, the 21 vectors
+// 28 us at 6 TB/s.  Two chunks of vectors are in flight per wave in registers, eight waves per compute unit.  The chain of a
+// chunk: x, g (and l, u) three chunks ahead, the free set two chunks ahead -- fixed variables contribute nothing: their
+// lanes read what the first free lane reads, and a chunk without any reads the first chunk's -- the vectors next, then the
+// products.  10 pairs, us per launch, the vector unit's kernel (77 sums per lane, three waves reading 14 vectors each, 512
+// workgroups, closing step included) / this one / this one without its closing step: n = 10^6 47.6 / 42.7 / 35.7, 2 10^6
+// 100 / 88 / 77; odd n 185 (operands staged for 2 x 2 tiles) / 45 / 38.5; 20 pairs 182 / 96.  A bare sum over the same vectors
+// takes 29 us at 10^6.  Loads straight into the operand layout, 16 vectors and 64 bytes of each per load: 41 / 90 with the
+// closing step at 10^6 / 2 10^6; three chunks in flight: slower than two.
+// else: a few chunks in all, and what bounds it is latency: everything is requested at once, the ring slots whatever they
+// hold, and looked at when it is there.  Without the closing step, 10 pairs: n = 2000 6.9 -> 6.1 us, 5000 6.4 -> 5.6, 40 000
+// 9.2 -> 7.7; n = 3001, where the closing step was not left out, 21.0 + 5.5 (direction) -> 6.4 + 12.0.
+// The sums are kept short: 32 elements by the matrix core from zero, added to the wave's running sum, the waves', then the
+// workgroups' sums.
+template <int M, int NW, bool LONG, bool DBG>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4)))
+void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const double* __restrict__ g, const double* __restrict__ l,
+            const double* __restrict__ u, const double* __restrict__ S, const double* __restrict__ Y, uint8_t* __restrict__ mask,
+            Scal* __restrict__ scal, double* __restrict__ grampart, int evaluate_stop, int no_close) {
+    constexpr int NT = 64 * NW, NB = gram_nb(M), NA = gram_na(M), NP = gram_np(M), NV = gram_slots(M);
+    extern __shared__ __align__(16) double dyn[];   // the waves' elements; their blocks; later G and the totals
+    __shared__ double red[NW * 3];
     __shared__ double alpha_s[kMaxM + 1];
     __shared__ int flag;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // one load per wave fetches the integer header of the scalar block (status, ring position, pending
+    // update); readlanes hand the fields to every lane
     static_assert(offsetof(Scal, pend_ok) < 64, "header fields must sit in the first 16 ints");
     const int hdr = lane < 16 ? reinterpret_cast<const int*>(scal)[lane] : 0;
-    if (__shfl(hdr, offsetof(Scal, status) / 4) != LBFGSB_RUNNING) {
-        // a step that finds the solver parked by the short logistic sequence is counted, so that the host can redo it
-        const int status = __shfl(hdr, offsetof(Scal, status) / 4);
-        if (evaluate_stop && !dbg_inputs && blockIdx.x == 0 && tid == 0) {
-            if (status == kStatusBail) scal->bail_skipped += 1;
-            note_progress(op, status);
-        }
-        return;
-    }
-    int head = __shfl(hdr, offsetof(Scal, head) / 4), c = __shfl(hdr, offsetof(Scal, count) / 4);
-    if (__shfl(hdr, offsetof(Scal, pend_valid) / 4)) {          // same rule as effective_ring()
-        if (__shfl(hdr, offsetof(Scal, pend_ok) / 4)) { head = (head + 1) % m; c = c < m ? c + 1 : m; }
-        else c = 0;
-    }
-    const double yn_old = prefetch_ynorm2(scal, c, head, m);   // (used by the last workgroup's recursion, fetched now)
-    const int V = 2 * c + 1;
-    const int Vp = V + 1;
-    const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;   // ring slot of the oldest pair
-    auto vec_ptr = [&](int j) -> const double* {
-        if (j >= 2 * c) return g;
-        const bool is_y = j >= c;
-        int sl = base_slot + (is_y ? j - c : j);
-        if (sl >= m) sl -= m;
-        return (is_y ? Y : S) + (int64_t)sl * n;
-    };
-    const int nslots = c > 0 ? V + 1 : V;            // slot V: the unmasked copy of the newest y
-    const int nbk = (nslots + 15) / 16;              // 16-vector blocks in use (<= NB)
-    const int i16 = lane & 15, q = lane >> 4;
-    const double* vp[NB];
-    int kind[NB];                                    // 0 = unused slot (operand forced to zero), 1 = masked vector, 2 = unmasked
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const int j = 16 * b + i16;
-        kind[b] = j < V ? 1 : (j == V && c > 0 ? 2 : 0);
-        vp[b] = kind[b] == 1 ? vec_ptr(j) : (kind[b] == 2 ? vec_ptr(2 * c - 1) : g);
-    }
-    f64x4 acc[NBP];
-#pragma unroll
-    for (int k = 0; k < NBP; ++k) acc[k] = f64x4{0.0, 0.0, 0.0, 0.0};
-    double pginf = 0.0;
-    long long nfixed = 0;
 
-    const int64_t nchunks = (n + 63) / 64;
-    for (int64_t ch = (int64_t)blockIdx.x * kWaves + wave; ch < nchunks; ch += (int64_t)gridDim.x * kWaves) {
-        const int64_t e0 = ch * 64;
-        f64x2 v[NB][8];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            if (b < nbk) {
-#pragma unroll
-                for (int s8 = 0; s8 < 8; ++s8) {
-                    int64_t e = e0 + 8 * s8 + 2 * q;
-                    if (e > n - 2) e = n - 2;          // past the end (n is even): any in-range pair, zeroed below
-                    v[b][s8] = *reinterpret_cast<const f64x2*>(vp[b] + e);
-                }
-            } else {
-#pragma unroll
-                for (int s8 = 0; s8 < 8; ++s8) v[b][s8] = f64x2{0.0, 0.0};
-            }
-        }
-        // Eq. (ws) and the KKT residual for element e0 + lane
-        const int64_t e = e0 + lane;
+    const int64_t nchunks = (n + 63) / 64, stride = (int64_t)gridDim.x * NW;
+    const int64_t ch0 = (int64_t)blockIdx.x * NW + wave;
+    const int64_t bstride = op.uniform_bounds ? 0 : 1;   // same bounds everywhere: l and u are not streamed
+    struct Elem { double x, g, l, u, y; uint8_t mk; };
+    auto request = [&](int64_t ch, Elem& s, const double* y_new) {
+        const int64_t e = ch * 64 + lane, ec = e < n ? e : n - 1;
+        s.x = x[ec]; s.g = g[ec]; s.l = l[ec * bstride]; s.u = u[ec * bstride];
+        s.y = LONG ? y_new[ec] : 0.0;
+        if constexpr (DBG) s.mk = mask[ec];
+    };
+    double pginf = 0.0, ynew = 0.0;
+    int nfixed = 0;
+    // Eq. (ws) and the statistics of a chunk; the bits of its free elements
+    auto decide = [&](int64_t ch, const Elem& s) -> unsigned long long {
+        const int64_t e = ch * 64 + lane;
         const bool in = e < n;
-        const int64_t ec = in ? e : n - 1;
-        const double xe = x[ec], ge = g[ec], le = l[ec], ue = u[ec];
         bool fr;
-        if (dbg_inputs) {
-            fr = mask[ec] != 0;
+        if constexpr (DBG) {
+            fr = s.mk != 0;
         } else {
-            const bool at_lower = (xe <= le + op.eps) && (ge >= 0.0);
-            const bool at_upper = (xe >= ue - op.eps) && (ge <= 0.0);
+            const bool at_lower = (s.x <= s.l + op.eps) && (s.g >= 0.0);
+            const bool at_upper = (s.x >= s.u - op.eps) && (s.g <= 0.0);
             fr = !(at_lower || at_upper);
-            if (in) mask[e] = (uint8_t)fr;
+            mask[in ? e : n - 1] = (uint8_t)fr;       // (past the end: the last element's own value once more)
         }
-        if (in) pginf = fmax(pginf, fabs(xe - clampd(xe - ge, le, ue)));
-        const unsigned long long bits_in = __ballot(in);
-        const unsigned long long bits_free = __ballot(fr && in);
-        nfixed += __popcll(bits_in & ~bits_free);
-#pragma unroll
-        for (int t = 0; t < 16; ++t) {
-            const int sh = 8 * (t >> 1) + 2 * q + (t & 1);
-            const bool b_free = (bits_free >> sh) & 1ull, b_in = (bits_in >> sh) & 1ull;
-            double opnd[NB];
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const double val = (t & 1) ? v[b][t >> 1].y : v[b][t >> 1].x;
-                const bool keep = kind[b] == 1 ? b_free : (kind[b] == 2 ? b_in : false);
-                opnd[b] = keep ? val : 0.0;
-            }
-            int k = 0;
-#pragma unroll
-            for (int a = 0; a < NB; ++a) {
-#pragma unroll
-                for (int b = a; b < NB; ++b, ++k) {
-                    if (b < nbk) acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(opnd[a], opnd[b], acc[k], 0, 0, 0);
-                }
-            }
-        }
-    }
-
-    // this workgroup's partial: the waves' accumulators added in wave order
-#pragma unroll
-    for (int k = 0; k < NBP; ++k) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) dyn[(wave * NBP + k) * 256 + r * 64 + lane] = acc[k][r];
-    }
-    double* part = grampart + (int64_t)blockIdx.x * NEM;
-    {
-        double nf[1] = {lane == 0 ? (double)nfixed : 0.0};
-        block_sum<1, kWaves>(nf, red);               // (also the barrier that publishes dyn)
-        double mx = wave_max(pginf);
-        __syncthreads();
-        if (lane == 0) red[wave] = mx;
-        __syncthreads();
-        if (tid == 0) {
-            part[0] = 0.0;
-            part[1] = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-            part[2] = nf[0];
-            part[3] = 0.0;
-        }
-    }
-    for (int idx = tid; idx < NBP * 256; idx += kBlock) {
-        double t = 0.0;
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) t += dyn[w * NBP * 256 + idx];
-        part[kHdr + idx] = t;
-    }
-
-    double* tot = dyn + 4096;    // totals of the partial entries; G occupies dyn[0 .. 4096)
-    if (!reduce_partials(grampart, NEM, scal, &flag, tot)) return;
-    double* G = dyn;   // Vp x Vp, row-major
-    for (int idx = tid; idx < NBP * 256; idx += kBlock) {
-        const double t = tot[kHdr + idx];
-        const int pair = idx >> 8, r = (idx >> 6) & 3, ln = idx & 63;
-        int a = 0, pb = pair;
-        while (pb >= NB - a) { pb -= NB - a; ++a; }      // pair -> blocks (a, a + pb)
-        const int b = a + pb;
-        const int row = 16 * a + (ln >> 4) + 4 * r, col = 16 * b + (ln & 15);
-        if (row < V && col < V) {
-            G[row * Vp + col] = t;
-            if (a != b) G[col * Vp + row] = t;          // a diagonal block holds both (row, col) and (col, row)
-        }
-        if (row == V && col == V) red[3] = t;            // ||y_new||^2 over the full vector
-        if (row == 2 * c && col == 2 * c) red[0] = t;    // sum over the free set of g^2
-    }
-    if (tid == 0) { red[1] = tot[1]; red[2] = tot[2]; }
-    __syncthreads();
-    if (tid == 0) {
-        // apply the update the previous kernel left pending, then record the newest pair's norm
-        apply_pending(scal, m);
-        if (c > 0 && !dbg_inputs) scal->ynorm2[(head - 1 + m) % m] = red[3];
-    }
-    __syncthreads();
-    recursion_on_coefficients(G, Vp, c, head, m, op, scal, red[0], red[1], red[2], red[3], yn_old, alpha_s, dbg_inputs, evaluate_stop);
-    if (tid == 0 && evaluate_stop) note_progress(op, scal->status);
-}
-
-
-// ---- at most 10 pairs: one element pair per lane, the entries of G divided among the waves -------------------
-//
-// The fp64 matrix cores of this chip run at the vector rate, and the 16-wide blocks above compute three times
-// the entries a 21-vector Gram matrix has.  For m <= 10 the plain vector unit does better: lane l of every wave
-// holds elements e0 + 2l, e0 + 2l + 1 of a 128-element chunk (16-byte loads, each instruction a contiguous
-// kilobyte of one vector), and the 231 entries of the 21 x 21 matrix over the STATIC slots
-//     S ring slots 0..9 | Y ring slots 10..19 | g 20
-// are divided among three waves of a workgroup.  With the slots in three groups of seven, a = 0..6, b = 7..13,
-// c = 14..20, wave r takes group r among itself and group r times group r + 1 (cyclically):
-//     wave 0: a x a (28) + a x b (49)     wave 1: b x b + b x c     wave 2: c x c + c x a
-// -- 77 per-lane accumulators and 14 vector loads per chunk each, so the three finish together (an earlier split
-// into 66/55/55/55 entries had two waves load 16 vectors and two 10-11, and the workgroup waited 6-9 us for the
-// slow pair).  The fourth wave writes the free-set mask and sums the statistics (KKT residual, number of fixed
-// variables, full ||y_new||^2).  The waves read the same chunk, so the vectors come from memory once and from the
-// cache after that.  Only one operand of a product is masked (the mask is 0 or 1).  Ring slots not in use
-// contribute zeros; the last workgroup maps ring slots to the oldest-first order of the recursion.
-
-// Sums 64 per-lane values over the 64 lanes of a wave all at once: on return lane j holds the total of a[j].
-// Each step halves the number of values a lane carries (the half it gives away goes to the lane 32, 16, ... 1
-// away), so 63 exchanges do what 64 separate butterfly sums would need 384 for.  Fixed order of additions.
-template <int D, int N>
-__device__ __forceinline__ void transpose_sum_step(double (&a)[N], int lane) {
-    const bool upper = (lane & D) != 0;
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-        const double send = upper ? a[k] : a[k + D];
-        const double keep = upper ? a[k + D] : a[k];
-        a[k] = keep + __shfl_xor(send, D);
-    }
-}
-__device__ __forceinline__ double transpose_sum64(double (&a)[64]) {
-    const int lane = threadIdx.x & 63;
-    transpose_sum_step<32>(a, lane);
-    transpose_sum_step<16>(a, lane);
-    transpose_sum_step<8>(a, lane);
-    transpose_sum_step<4>(a, lane);
-    transpose_sum_step<2>(a, lane);
-    transpose_sum_step<1>(a, lane);
-    return a[0];
-}
-
-// The same for 16 values: on return every lane l holds the total of a[l % 16].
-__device__ __forceinline__ double transpose_sum16(double (&a)[16]) {
-    const int lane = threadIdx.x & 63;
-    transpose_sum_step<8>(a, lane);
-    transpose_sum_step<4>(a, lane);
-    transpose_sum_step<2>(a, lane);
-    transpose_sum_step<1>(a, lane);
-    double t = a[0];                      // total over this row of 16 lanes
-    t += __shfl_xor(t, 16);
-    t += __shfl_xor(t, 32);
-    return t;
-}
-
-struct WideCtx {
-    int64_t n;
-    int m, c, base_slot;
-    const double *S, *Y, *g;
-    unsigned active;     // bit s: static slot s holds a vector
-};
-
-__device__ __forceinline__ const double* wide_ptr(const WideCtx& w, int slot) {
-    if (slot < kWideM) return w.S + (int64_t)slot * w.n;
-    if (slot < 2 * kWideM) return w.Y + (int64_t)(slot - kWideM) * w.n;
-    return w.g;
-}
-
-// One wave's share.  ROLE 0..2: the seven slots from P0 among themselves and times the seven from Q0; ROLE 3: the
-// free-set mask and the statistics.  Chunks ch0, ch0 + chs, ... of 128 elements.
-template <int P0, int Q0, int ROLE, bool UB>
-__device__ __forceinline__ void wide_role(const WideCtx& w, const Opts& op, const double* __restrict__ x,
-                                          const double* __restrict__ l, const double* __restrict__ u,
-                                          uint8_t* __restrict__ mask, int dbg_inputs, double* __restrict__ part,
-                                          int offset) {
-    constexpr bool STATS = ROLE == 3;
-    constexpr int NACC = STATS ? 1 : kWideRole;
-    const int lane = threadIdx.x & 63;
-    double acc[NACC];
-#pragma unroll
-    for (int k = 0; k < NACC; ++k) acc[k] = 0.0;
-    double pginf = 0.0, ynew = 0.0, nfixed = 0.0;
-    const double* yn_ptr = w.c > 0 ? w.Y + (int64_t)((w.base_slot + w.c - 1) % w.m) * w.n : w.g;
-    const int64_t nchunks = (w.n + 127) / 128;
-    // x, g, l, u (and the given mask) of a chunk decide which lanes load the vectors at all, so they are fetched one
-    // chunk ahead: the two dependent round trips of a chunk overlap with the previous chunk's
-    auto pair_index = [&](int64_t ch, bool& in) -> int64_t {
-        const int64_t e = ch * 128 + 2 * lane;
-        in = ch < nchunks && e < w.n;                  // n is even: both elements of the pair, or neither
-        return in ? e : w.n - 2;
+        pginf = fmax(pginf, in ? fabs(s.x - clampd(s.x - s.g, s.l, s.u)) : 0.0);
+        ynew = fma(in ? s.y : 0.0, s.y, ynew);
+        const unsigned long long bits = __ballot(fr && in);
+        nfixed += __popcll(__ballot(in)) - __popcll(bits);
+        return bits;
     };
-    bool in_next;
-    int64_t ec_next = pair_index(blockIdx.x, in_next);
-    // UB: same bounds everywhere, l and u are not streamed (and take no registers)
-    f64x2 xn = *reinterpret_cast<const f64x2*>(x + ec_next), gn = *reinterpret_cast<const f64x2*>(w.g + ec_next);
-    f64x2 ln = f64x2{op.lo, op.lo}, un = f64x2{op.hi, op.hi};
-    if constexpr (!UB) { ln = *reinterpret_cast<const f64x2*>(l + ec_next); un = *reinterpret_cast<const f64x2*>(u + ec_next); }
-    unsigned short mkn = dbg_inputs ? *reinterpret_cast<const unsigned short*>(mask + ec_next) : (unsigned short)0;
-    for (int64_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
-        const bool in = in_next;
-        const int64_t ec = ec_next, e = ec_next;
-        const f64x2 xe = xn, ge = gn;
-        const f64x2 le = UB ? f64x2{op.lo, op.lo} : ln, ue = UB ? f64x2{op.hi, op.hi} : un;
-        const unsigned short mk = mkn;
-        ec_next = pair_index(ch + gridDim.x, in_next);
-        xn = *reinterpret_cast<const f64x2*>(x + ec_next); gn = *reinterpret_cast<const f64x2*>(w.g + ec_next);
-        if constexpr (!UB) { ln = *reinterpret_cast<const f64x2*>(l + ec_next); un = *reinterpret_cast<const f64x2*>(u + ec_next); }
-        if (dbg_inputs) mkn = *reinterpret_cast<const unsigned short*>(mask + ec_next);
-        bool f0, f1;
-        if (dbg_inputs) {
-            f0 = (mk & 0xffu) != 0;
-            f1 = (mk >> 8) != 0;
-        } else {
-            f0 = !(((xe.x <= le.x + op.eps) && (ge.x >= 0.0)) || ((xe.x >= ue.x - op.eps) && (ge.x <= 0.0)));
-            f1 = !(((xe.y <= le.y + op.eps) && (ge.y >= 0.0)) || ((xe.y >= ue.y - op.eps) && (ge.y <= 0.0)));
-        }
-        if constexpr (STATS) {
-            if (in) {
-                if (!dbg_inputs)
-                    *reinterpret_cast<unsigned short*>(mask + e) = (unsigned short)((f0 ? 1u : 0u) | (f1 ? 0x100u : 0u));
-                pginf = fmax(pginf, fmax(fabs(xe.x - clampd(xe.x - ge.x, le.x, ue.x)), fabs(xe.y - clampd(xe.y - ge.y, le.y, ue.y))));
-                nfixed += (f0 ? 0.0 : 1.0) + (f1 ? 0.0 : 1.0);
-                if (w.c > 0) {
-                    const f64x2 yv = *reinterpret_cast<const f64x2*>(yn_ptr + ec);
-                    ynew = fma(yv.x, yv.x, ynew);
-                    ynew = fma(yv.y, yv.y, ynew);
-                }
-            }
-        } else {
-            const double m0 = (in && f0) ? 1.0 : 0.0, m1 = (in && f1) ? 1.0 : 0.0;
-            // fixed variables contribute nothing: lanes whose two elements are both fixed (or past the end) load no vector
-            if (m0 != 0.0 || m1 != 0.0) {
-                f64x2 vp[kWideG], vq[kWideG];
+    f64x4 sum[NP];
 #pragma unroll
-                for (int i = 0; i < kWideG; ++i) {
-                    vp[i] = f64x2{0.0, 0.0};
-                    if ((w.active >> (P0 + i)) & 1u) vp[i] = *reinterpret_cast<const f64x2*>(wide_ptr(w, P0 + i) + ec);
-                }
+    for (int k = 0; k < NP; ++k) sum[k] = f64x4{0.0, 0.0, 0.0, 0.0};
+    double* mine = dyn + wave * (16 * NB * kGramStride);
+    const int i16 = lane & 15, q = lane >> 4;
+    const double* opnd_at = mine + i16 * kGramStride + 2 * q;
+    // (slots past the last vector: products that nobody reads, but no stale bits of another launch either)
+    for (int k = NV; k < 16 * NB; ++k) mine[k * kGramStride + lane] = 0.0;
+    auto multiply = [&](const double (&v)[NV], unsigned long long bits) {
+        const int keep = (bits >> lane) & 1ull ? -1 : 0;
 #pragma unroll
-                for (int j = 0; j < kWideG; ++j) {
-                    vq[j] = f64x2{0.0, 0.0};
-                    if ((w.active >> (Q0 + j)) & 1u) vq[j] = *reinterpret_cast<const f64x2*>(wide_ptr(w, Q0 + j) + ec);
-                }
+        for (int k = 0; k < NV; ++k)
+            mine[k * kGramStride + lane] = __hiloint2double(__double2hiint(v[k]) & keep, __double2loint(v[k]) & keep);
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                for (int i = 0; i < kWideG; ++i) { vp[i].x *= m0; vp[i].y *= m1; }
-                int k = 0;
+        for (int half = 0; half < 2; ++half) {
+            f64x4 acc[NP];
 #pragma unroll
-                for (int a = 0; a < kWideG; ++a) {
+            for (int k = 0; k < NP; ++k) acc[k] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                    for (int b = a; b < kWideG; ++b, ++k) {
-                        acc[k] = fma(vp[a].x, vp[b].x, acc[k]);
-                        acc[k] = fma(vp[a].y, vp[b].y, acc[k]);
-                    }
-                }
+            for (int s8 = 4 * half; s8 < 4 * half + 4; ++s8) {
+                f64x2 o[NB];
 #pragma unroll
-                for (int a = 0; a < kWideG; ++a) {
+                for (int b = 0; b < NB; ++b) o[b] = *reinterpret_cast<const f64x2*>(opnd_at + 16 * b * kGramStride + 8 * s8);
 #pragma unroll
-                    for (int b = 0; b < kWideG; ++b, ++k) {
-                        acc[k] = fma(vp[a].x, vq[b].x, acc[k]);
-                        acc[k] = fma(vp[a].y, vq[b].y, acc[k]);
+                for (int t = 0; t < 2; ++t) {
+                    int k = 0;
+#pragma unroll
+                    for (int a = 0; a < NA; ++a) {
+#pragma unroll
+                        for (int b = a; b < NB; ++b, ++k)
+                            acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(t ? o[a].y : o[a].x, t ? o[b].y : o[b].x, acc[k], 0, 0, 0);
                     }
                 }
             }
+#pragma unroll
+            for (int k = 0; k < NP; ++k) sum[k] += acc[k];
         }
-    }
-    if constexpr (STATS) {
-        pginf = wave_max(pginf);
-        nfixed = wave_sum(nfixed);
-        ynew = wave_sum(ynew);
-        if (lane == 0) { part[0] = 0.0; part[1] = pginf; part[2] = nfixed; part[3] = ynew; }
-    } else {
-        // sums over the lanes: 64 accumulators at once (lane j ends up with the total of accumulator j), then the other 13
-        double first[64];
+        __builtin_amdgcn_wave_barrier();
+    };
+    // where the waves' blocks hold the product that is entry idx of a record
+    auto block_place = [&](int idx) -> int {
+        int a, b;
+        gram_product_slots(idx, m, a, b);
+        // (record: y, g, s of m slots each; here of M)
+        a += a == m ? M - m : 0;
+        b += b >= m ? M - m : 0;
+        const int ab = a >> 4, bb = b >> 4, pair = ab * NB - ab * (ab - 1) / 2 + bb - ab;
+        return pair * 256 + ((a & 15) >> 2) * 64 + (a & 3) * 16 + (b & 15);
+    };
+    auto slot_ptr = [&](int k) -> const double* {
+        if (k == M) return g;
+        const int ring = k < M ? k : k - M - 1;
+        return (k < M ? Y : S) + (int64_t)(ring < m ? ring : m - 1) * n;
+    };
+    Elem sa;
+    double va[NV];
+    if constexpr (!LONG) {
+        request(ch0, sa, nullptr);
+        const int64_t e = ch0 * 64 + lane, ec = e < n ? e : n - 1;
 #pragma unroll
-        for (int k = 0; k < 64; ++k) first[k] = acc[k];
-        const double mine = transpose_sum64(first);
-        part[kHdr + offset + lane] = mine;
-        double rest[16];
-#pragma unroll
-        for (int k = 0; k < 16; ++k) rest[k] = 64 + k < NACC ? acc[64 + k] : 0.0;
-        const double mine2 = transpose_sum16(rest);
-        if (lane < NACC - 64) part[kHdr + offset + 64 + lane] = mine2;
+        for (int k = 0; k < NV; ++k) va[k] = slot_ptr(k)[ec];
     }
-}
 
-template <bool UB>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gram_wide(int64_t n, int m, Opts op, const double* __restrict__ x,
-                                                      const double* __restrict__ g, const double* __restrict__ l,
-                                                      const double* __restrict__ u, const double* __restrict__ S,
-                                                      const double* __restrict__ Y, uint8_t* __restrict__ mask,
-                                                      Scal* __restrict__ scal, double* __restrict__ grampart,
-                                                      int dbg_inputs, int evaluate_stop, int no_close) {
-    __shared__ double Gs[(2 * kWideM + 2) * (2 * kWideM + 2)];
-    __shared__ double tot[kWideNE];
-    __shared__ double alpha_s[kMaxM + 1];
-    __shared__ int flag;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    static_assert(offsetof(Scal, pend_ok) < 64, "header fields must sit in the first 16 ints");
-    const int hdr = lane < 16 ? reinterpret_cast<const int*>(scal)[lane] : 0;
-    if (__shfl(hdr, offsetof(Scal, status) / 4) != LBFGSB_RUNNING) {
+    int place = block_place(tid < gram_products(m) ? tid : 0);   // (here, while the loads are on their way)
+    asm volatile("" : "+v"(place));
+    auto field = [&](size_t off) { return __builtin_amdgcn_readlane(hdr, (int)(off / 4)); };
+    const int status = field(offsetof(Scal, status));
+    if (status != LBFGSB_RUNNING) {
         // a step that finds the solver parked by the short logistic sequence is counted, so that the host can redo it
-        const int status = __shfl(hdr, offsetof(Scal, status) / 4);
-        if (evaluate_stop && !dbg_inputs && blockIdx.x == 0 && tid == 0) {
+        if (evaluate_stop && !DBG && blockIdx.x == 0 && tid == 0) {
             if (status == kStatusBail) scal->bail_skipped += 1;
             note_progress(op, status);
         }
         return;
     }
-    int head = __shfl(hdr, offsetof(Scal, head) / 4), c = __shfl(hdr, offsetof(Scal, count) / 4);
-    if (__shfl(hdr, offsetof(Scal, pend_valid) / 4)) {          // same rule as effective_ring()
-        if (__shfl(hdr, offsetof(Scal, pend_ok) / 4)) { head = (head + 1) % m; c = c < m ? c + 1 : m; }
+    int head = field(offsetof(Scal, head)), c = field(offsetof(Scal, count));
+    if (field(offsetof(Scal, pend_valid))) {          // same rule as effective_ring()
+        if (field(offsetof(Scal, pend_ok))) { head = (head + 1) % m; c = c < m ? c + 1 : m; }
         else c = 0;
     }
-    const double yn_old = prefetch_ynorm2(scal, c, head, m);   // (used by the last workgroup's recursion, fetched now)
-    WideCtx w;
-    w.n = n; w.m = m; w.c = c; w.S = S; w.Y = Y; w.g = g;
-    w.base_slot = c > 0 ? (head - c + 2 * m) % m : 0;           // ring slot of the oldest pair
-    w.active = 1u << (2 * kWideM);
-    for (int j = 0; j < c; ++j) {
-        const int sl = (w.base_slot + j) % m;
-        w.active |= (1u << sl) | (1u << (kWideM + sl));
+    const double yn_old = no_close ? 1.0 : prefetch_ynorm2(scal, c, head, m);   // (used by the last workgroup's recursion, fetched now)
+    const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;   // ring slot of the oldest pair
+    const int newest = c > 0 ? (head - 1 + m) % m : -1;
+    if constexpr (LONG) {
+        const double* y_new = newest >= 0 ? Y + (int64_t)newest * n : g;
+        unsigned long long active = 1ull << M;        // bit k: slot k holds a vector
+        for (int j = 0; j < c; ++j) {
+            const int sl = base_slot + j < m ? base_slot + j : base_slot + j - m;
+            active |= (1ull << sl) | (1ull << (M + 1 + sl));
+        }
+        auto fetch = [&](int64_t ch, unsigned long long bits, double (&v)[NV]) {
+            const int first = bits ? __builtin_ctzll(bits) : 0;
+            const int64_t e0 = bits ? ch * 64 : 0;    // (uniform)
+            const unsigned off = (unsigned)((bits >> lane) & 1ull ? lane : first);
+#pragma unroll
+            for (int k = 0; k < NV; ++k) v[k] = (((active >> k) & 1ull ? slot_ptr(k) : g) + e0)[off];
+        };
+        if (ch0 < nchunks) {
+            double vb[NV];
+            Elem sb;
+            request(ch0, sa, y_new);
+            request(ch0 + stride, sb, y_new);
+            unsigned long long ba = decide(ch0, sa), bb;
+            fetch(ch0, ba, va);
+            request(ch0 + 2 * stride, sa, y_new);
+            // (two chunks a trip and one way out: a chunk past the end has no free element and adds nothing)
+            for (int64_t ch = ch0; ch < nchunks; ch += 2 * stride) {
+                bb = decide(ch + stride, sb);
+                fetch(ch + stride, bb, vb);
+                request(ch + 3 * stride, sb, y_new);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(va, ba);
+                __builtin_amdgcn_sched_barrier(0);
+                ba = decide(ch + 2 * stride, sa);
+                fetch(ch + 2 * stride, ba, va);
+                request(ch + 4 * stride, sa, y_new);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(vb, bb);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    } else {
+        for (int64_t ch = ch0; ch < nchunks; ch += stride) {
+            if (ch != ch0) {
+                request(ch, sa, nullptr);
+                const int64_t e = ch * 64 + lane, ec = e < n ? e : n - 1;
+#pragma unroll
+                for (int k = 0; k < NV; ++k) va[k] = slot_ptr(k)[ec];
+            }
+#pragma unroll
+            for (int k = 0; k < M; ++k)
+                if (k == newest) sa.y = va[k];
+            const unsigned long long bits = decide(ch, sa);
+            multiply(va, bits);
+        }
     }
-    double* part = grampart + (int64_t)blockIdx.x * kWideNE;
-    switch (wave) {
-        case 0: wide_role<0, kWideG, 0, UB>(w, op, x, l, u, mask, dbg_inputs, part, 0); break;
-        case 1: wide_role<kWideG, 2 * kWideG, 1, UB>(w, op, x, l, u, mask, dbg_inputs, part, kWideRole); break;
-        case 2: wide_role<2 * kWideG, 0, 2, UB>(w, op, x, l, u, mask, dbg_inputs, part, 2 * kWideRole); break;
-        default: wide_role<0, 0, 3, UB>(w, op, x, l, u, mask, dbg_inputs, part, 0); break;
+
+    // this workgroup's record: the waves' blocks added in wave order
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dyn[(wave * NP + k) * 256 + r * 64 + lane] = sum[k][r];
     }
-    if (no_close) return;   // the direction kernel adds the partial sums and does the rest
-    if (!reduce_partials(grampart, kWideNE, scal, &flag, tot)) return;
-    wide_finish(tot, Gs, alpha_s, scal, m, c, head, w.base_slot, op, yn_old, dbg_inputs, evaluate_stop, true);
+    pginf = wave_max(pginf);
+    ynew = wave_sum(ynew);
+    if (lane == 0) { red[wave] = pginf; red[NW + wave] = (double)nfixed; red[2 * NW + wave] = ynew; }
+    __syncthreads();
+    const int NE = gram_entries(m);
+    double* part = grampart + (int64_t)blockIdx.x * NE;
+    for (int idx = tid; idx < gram_products(m); idx += NT) {
+        const int src = idx == tid ? place : block_place(idx);
+        double t = dyn[src];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t += dyn[w * NP * 256 + src];
+        part[kGramHdr + idx] = t;
+    }
+    if (tid < 3) {
+        double t = red[tid * NW];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t = tid == 0 ? fmax(t, red[w]) : t + red[tid * NW + w];
+        part[tid] = t;
+    }
+    if (!LONG && no_close) return;   // the direction kernel adds the records and does the rest
+    double* tot = dyn + gram_tot_at(M);
+    if (!reduce_partials<NT>(grampart, NE, scal, &flag, tot, LONG && no_close)) return;
+    gram_finish<NT>(tot, dyn, alpha_s, scal, m, c, head, base_slot, op, yn_old, DBG, evaluate_stop, true);
     if (tid == 0 && evaluate_stop) note_progress(op, scal->status);
 }
 
-// (any even n: below 2^17 entries the grid stays small enough for the one-level sum of the partials)
-bool gram_uses_wide(int64_t n, int m) { return n % 2 == 0 && m <= kWideM; }
-int gram_wide_blocks(int64_t n) {
-    const int64_t b = (n + 127) / 128;
-    const int64_t cap = n >= kMfmaMinN ? 512 : kGramOneLevelMax;
+namespace {
+constexpr int gram_m_for(int m) { return m <= 5 ? 5 : (m <= 10 ? 10 : (m <= 20 ? 20 : 31)); }
+}  // namespace
+
+// Waves per workgroup.  Two waves of a SIMD take turns at its matrix core (0.85 us a chunk), so a problem of few chunks has
+// four; beyond 64 workgroups their records would take the direction kernel more than one round of loads to add.
+static int gram_waves_for(int64_t n, int m) { return n <= 64 * 4 * 64 ? 4 : gram_waves_most(gram_m_for(m)); }
+
+int gram_blocks_for(int64_t n, int m, bool few) {
+    const int nw = gram_waves_for(n, m);
+    const int64_t b = ((n + 63) / 64 + nw - 1) / nw;
+    const int64_t cap = n >= kGramLongN && !few ? kGramGroups * kGramGroupMax : kGramOneLevelMax;
     return (int)(b > cap ? cap : b);
 }
 
-template <int NB>
-size_t mfma_lds_bytes() {
-    size_t d = (size_t)kWaves * (NB * (NB + 1) / 2) * 256;         // the waves' accumulators
-    const size_t fin = 4096 + (size_t)mfma_entries(NB);            // later: G (at most 64 x 64) and the totals
-    return (d > fin ? d : fin) * 8;
+// (the records of the groups of workgroups, where there are any, lie behind the workgroups')
+size_t gram_partial_bytes(int blocks, int m) {
+    return (size_t)(blocks + (blocks > kGramOneLevelMax ? kGramGroups : 0)) * gram_entries(m) * 8;
 }
 
-int gram_mfma_blocks(int64_t n) {
-    const int64_t b = ((n + 63) / 64 + kWaves - 1) / kWaves;
-    return (int)(b > 256 ? 256 : b);
+bool gram_can_skip_close(const Dims& dm) { return dm.m <= kGramOpenM; }
+
+GramRecords gram_records(const Dims& dm, const Geometry& ge, const Buffers& bf) {
+    if (ge.gram_blocks <= kGramOneLevelMax) return GramRecords{bf.grampart, ge.gram_blocks};
+    const int gs = (ge.gram_blocks + kGramGroups - 1) / kGramGroups;
+    return GramRecords{bf.grampart + (size_t)ge.gram_blocks * gram_entries(dm.m), (ge.gram_blocks + gs - 1) / gs};
 }
 
-int gram_blocks_for(int64_t n, int m) {
-    if (gram_uses_wide(n, m)) return gram_wide_blocks(n);
-    if (gram_uses_mfma(n, m)) return gram_mfma_blocks(n);
-    const int e = gram_chunk(m);
-    int64_t b = (n + e - 1) / e;
-    return (int)(b < 1 ? 1 : (b > 128 ? 128 : b));
+namespace {
+
+typedef void (*GramKernel)(int64_t, int, Opts, const double*, const double*, const double*, const double*, const double*,
+                           const double*, uint8_t*, Scal*, double*, int, int);
+template <int M, int NW>
+GramKernel gram_kernel(bool is_long, bool dbg) {
+    if constexpr (NW == gram_waves_most(M)) {
+        if (is_long) return dbg ? k_gram<M, NW, true, true> : k_gram<M, NW, true, false>;
+    }
+    return dbg ? k_gram<M, NW, false, true> : k_gram<M, NW, false, false>;
+}
+GramKernel gram_kernel_for(const Dims& dm, bool dbg, size_t* lds, int* threads) {
+    const bool is_long = dm.n >= kGramLongN;
+    const int M = gram_m_for(dm.m), nw = gram_waves_for(dm.n, dm.m);
+    *lds = (size_t)gram_lds_doubles(M, nw) * 8;
+    *threads = 64 * nw;
+    switch (M) {
+        case 5: return nw == 4 ? gram_kernel<5, 4>(is_long, dbg) : gram_kernel<5, 8>(is_long, dbg);
+        case 10: return nw == 4 ? gram_kernel<10, 4>(is_long, dbg) : gram_kernel<10, 8>(is_long, dbg);
+        case 20: return gram_kernel<20, 4>(is_long, dbg);
+        default: return gram_kernel<31, 4>(is_long, dbg);
+    }
 }
 
-size_t gram_partial_bytes(int64_t n, int m) {
-    if (gram_uses_wide(n, m)) return (size_t)(gram_wide_blocks(n) + kGramGroups) * kWideNE * 8;
-    if (gram_uses_mfma(n, m))
-        return (size_t)(gram_mfma_blocks(n) + kGramGroups) * mfma_entries(mfma_nb(m)) * 8;
-    return (size_t)gram_blocks_for(n, m) * gram_entries(m) * 8;
-}
+}  // namespace
 
-hipError_t gram_prepare(int64_t n, int m) {
-    if (!gram_uses_mfma(n, m) || mfma_nb(m) != 4) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gram_mfma<4>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)mfma_lds_bytes<4>());
-}
-
-template <int NB>
-void launch_gram_mfma(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int dbg_inputs,
-                      int evaluate_stop, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-    hipExtLaunchKernelGGL((k_gram_mfma<NB>), dim3(ge.gram_blocks), dim3(kBlock), mfma_lds_bytes<NB>(), st, ev0, ev1, 0, dm.n,
-                          dm.m, op, bf.x, bf.g, bf.l, bf.u, bf.S, bf.Y, bf.mask, bf.scal, bf.grampart, dbg_inputs,
-                          evaluate_stop);
-}
-
-bool gram_can_skip_close(const Dims& dm, const Geometry& ge) {
-    return gram_uses_wide(dm.n, dm.m) && ge.gram_blocks <= kGramOneLevelMax;
+// (the limit is a property of the kernel)
+hipError_t gram_prepare(const Dims& dm) {
+    hipError_t e = hipSuccess;
+    for (int dbg = 0; dbg < 2 && e == hipSuccess; ++dbg) {
+        size_t lds;
+        int threads;
+        const GramKernel k = gram_kernel_for(dm, dbg != 0, &lds, &threads);
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    }
+    return e;
 }
 
 void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int dbg_inputs,
                  int evaluate_stop, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, int no_close) {
-    if (gram_uses_wide(dm.n, dm.m)) {
-        if (no_close && !gram_can_skip_close(dm, ge)) no_close = 0;
-        if (op.uniform_bounds)
-            hipExtLaunchKernelGGL(k_gram_wide<true>, dim3(ge.gram_blocks), dim3(kBlock), 0, st, ev0, ev1, 0, dm.n, dm.m, op, bf.x,
-                                  bf.g, bf.l, bf.u, bf.S, bf.Y, bf.mask, bf.scal, bf.grampart, dbg_inputs, evaluate_stop, no_close);
-        else
-            hipExtLaunchKernelGGL(k_gram_wide<false>, dim3(ge.gram_blocks), dim3(kBlock), 0, st, ev0, ev1, 0, dm.n, dm.m, op, bf.x,
-                                  bf.g, bf.l, bf.u, bf.S, bf.Y, bf.mask, bf.scal, bf.grampart, dbg_inputs, evaluate_stop, no_close);
-        return;
-    }
-    if (gram_uses_mfma(dm.n, dm.m)) {
-        switch (mfma_nb(dm.m)) {
-            case 1: launch_gram_mfma<1>(dm, op, ge, bf, dbg_inputs, evaluate_stop, st, ev0, ev1); break;
-            case 2: launch_gram_mfma<2>(dm, op, ge, bf, dbg_inputs, evaluate_stop, st, ev0, ev1); break;
-            default: launch_gram_mfma<4>(dm, op, ge, bf, dbg_inputs, evaluate_stop, st, ev0, ev1); break;
-        }
-        return;
-    }
-    hipExtLaunchKernelGGL(k_gram, dim3(ge.gram_blocks), dim3(kBlock), gram_lds_bytes(dm.m), st, ev0, ev1, 0, dm.n, dm.m,
-                          gram_chunk(dm.m), op, bf.x, bf.g, bf.l, bf.u, bf.S, bf.Y, bf.mask, bf.scal, bf.grampart,
-                          gram_entries(dm.m), dbg_inputs, evaluate_stop);
+    size_t lds;
+    int threads;
+    const GramKernel k = gram_kernel_for(dm, dbg_inputs != 0, &lds, &threads);
+    hipExtLaunchKernelGGL(k, dim3(ge.gram_blocks), dim3(threads), lds, st, ev0, ev1, 0, dm.n, dm.m, op, (const double*)bf.x,
+                          (const double*)bf.g, (const double*)bf.l, (const double*)bf.u, (const double*)bf.S, (const double*)bf.Y,
+                          bf.mask, bf.scal, bf.grampart, evaluate_stop, no_close);
 }
 
 // Applies a pending update when nothing else is about to (before an evaluation from scratch, and

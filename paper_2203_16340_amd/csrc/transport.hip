@@ -11,6 +11,8 @@
 //   k_ot_update_gauss       closed-form Armijo search (the objective is quadratic along p) and the update
 //   k_ot_ls_entropy / k_ot_update_entropy   the same for the entropy, whose line search
 //                           needs one pass over (x, p) per batch of trial steps
+#include <cstddef>
+
 #include "common.h"
 
 namespace lb {
@@ -38,17 +40,29 @@ __global__ __launch_bounds__(kBlock) void k_ot_sums(Dims dm, OtArgs a, int eval,
                                                     const double* __restrict__ p2, Scal* __restrict__ scal,
                                                     double* __restrict__ out, double* __restrict__ wpart,
                                                     double* __restrict__ losspart, const double* __restrict__ dir_part,
-                                                    int dir_blocks, double eps) {
+                                                    int dir_blocks, double eps, Scal* __restrict__ scal_next) {
     __shared__ double red[kWaves * (RPW + 1 > 7 ? RPW + 1 : 7)];
     const int tid = threadIdx.x;
-    const int status = check_status ? scal->status : LBFGSB_RUNNING;
+    const int status = check_status ? (scal_next ? scal_next : scal)->status : LBFGSB_RUNNING;
     const double* z = x;
     if (!eval && dir_blocks > 0) {
         // Algorithm 2's choice from the direction kernel's per-workgroup sums (requested together with the status
-        // word); workgroup 0 records it for the kernels that follow
+        // word); workgroup 0 records it for the kernels that follow, and moves the copy of the scalar block that the
+        // direction kernel has left in scal_next into place, the choice written into it on the way
+        const bool move = scal_next && blockIdx.x == 0 && scal_next->fresh;
         const DirChoice ch = dir_choice_block(dir_part, dir_blocks, eps, red);
+        if (move) {
+            for (int k = tid; k < (int)(sizeof(Scal) / 4); k += kBlock) {
+                int v = reinterpret_cast<const int*>(scal_next)[k];
+                if (status == LBFGSB_RUNNING) v = scal_word_with_choice(k, v, ch);
+                if (k == (int)(offsetof(Scal, fresh) / 4)) v = 0;
+                reinterpret_cast<int*>(scal)[k] = v;
+            }
+            __syncthreads();                                   // (every thread has read `fresh`)
+            if (tid == 0) scal_next->fresh = 0;
+        }
         if (status != LBFGSB_RUNNING) return;
-        if (blockIdx.x == 0 && tid == 0) {
+        if (blockIdx.x == 0 && tid == 0 && !move) {
             scal->branch = ch.branch; scal->gp = ch.gp; scal->alpha_ub = ch.alpha_ub; scal->pp = ch.pp; scal->xp = ch.xp;
         }
         z = ch.branch == 1 ? p1 : p2;
@@ -519,22 +533,22 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 8 : 4) void k_ot_update_entropy(Di
 
 template <int RPW>
 void launch_sums_t(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, int eval, int check_status,
-                   hipStream_t st, int dir_blocks, double eps) {
+                   hipStream_t st, int dir_blocks, double eps, Scal* scal_next) {
     hipLaunchKernelGGL(k_ot_sums<RPW>, dim3(ge.ot_row_blocks), dim3(kBlock), 0, st, dm, a, eval, check_status,
                        (const double*)bf.x, (const double*)bf.p1, (const double*)bf.p2, bf.scal, eval ? bf.row : bf.t,
-                       bf.wpart, bf.losspart, (const double*)bf.redpart, eval ? 0 : dir_blocks, eps);
+                       bf.wpart, bf.losspart, (const double*)bf.redpart, eval ? 0 : dir_blocks, eps, scal_next);
 }
 
 }  // namespace
 
 void launch_ot_sums(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, int eval, int check_status,
-                    hipStream_t st, int dir_blocks, double eps) {
+                    hipStream_t st, int dir_blocks, double eps, Scal* scal_next) {
     switch (ge.ot_rpw) {
-        case 1: launch_sums_t<1>(dm, ge, bf, a, eval, check_status, st, dir_blocks, eps); break;
-        case 2: launch_sums_t<2>(dm, ge, bf, a, eval, check_status, st, dir_blocks, eps); break;
-        case 4: launch_sums_t<4>(dm, ge, bf, a, eval, check_status, st, dir_blocks, eps); break;
-        case 8: launch_sums_t<8>(dm, ge, bf, a, eval, check_status, st, dir_blocks, eps); break;
-        default: launch_sums_t<kOtRpwMax>(dm, ge, bf, a, eval, check_status, st, dir_blocks, eps); break;
+        case 1: launch_sums_t<1>(dm, ge, bf, a, eval, check_status, st, dir_blocks, eps, scal_next); break;
+        case 2: launch_sums_t<2>(dm, ge, bf, a, eval, check_status, st, dir_blocks, eps, scal_next); break;
+        case 4: launch_sums_t<4>(dm, ge, bf, a, eval, check_status, st, dir_blocks, eps, scal_next); break;
+        case 8: launch_sums_t<8>(dm, ge, bf, a, eval, check_status, st, dir_blocks, eps, scal_next); break;
+        default: launch_sums_t<kOtRpwMax>(dm, ge, bf, a, eval, check_status, st, dir_blocks, eps, scal_next); break;
     }
     hipLaunchKernelGGL(k_ot_cols, dim3(ge.ot_col_blocks), dim3(kBlock), 0, st, dm, a, eval, check_status, ge.ot_row_blocks,
                        (const double*)bf.wpart, (const Scal*)bf.scal, eval ? bf.row : bf.t, bf.losspart + ge.ot_row_blocks);

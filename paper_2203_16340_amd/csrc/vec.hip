@@ -4,7 +4,7 @@
 // device by the last workgroup of the kernel that produces the numbers it depends on.
 // (The free set, the Gram matrix and the recursion of Algorithm 3 are in gram.hip.)
 #include "common.h"
-#include "wide_close.h"
+#include "gram_close.h"
 
 namespace lb {
 
@@ -239,9 +239,8 @@ __device__ __forceinline__ void dir_finish(double (&s)[6], double ub, double eps
     }
 }
 
-// CLOSE: the wide Gram kernel before this one ended without its closing step (gram_blocks workgroups' partial sums in
-// grampart).  Every workgroup here then does that step on a private copy of the scalar block: adds the partial sums in
-// workgroup order, applies the pending update, runs Algorithm 3 on coefficients and the stopping test -- the same
+// CLOSE: the Gram kernel before this one ended without its closing step.  Every workgroup here then does that step on a
+// private copy of the scalar block: adds the records of partial sums in workgroup order, applies the pending update, runs Algorithm 3 on coefficients and the stopping test -- the same
 // functions in the same order as the Gram kernel's last workgroup, so the same bits -- and takes the coefficients from
 // its copy.  Workgroup 0 leaves its copy in scal_next for the pass (nothing in this kernel reads that); the scalar
 // block itself is only read here.  What this saves is the Gram kernel's arrival (a fence, an atomic, a dependent round
@@ -254,8 +253,7 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
                                                 Scal* __restrict__ scal, double* __restrict__ d,
                                                 double* __restrict__ p1, double* __restrict__ p2,
                                                 double* __restrict__ redpart, int d_given, int store_d, FoldArgs fold,
-                                                int defer_choice, const double* __restrict__ grampart, int gram_blocks,
-                                                Scal* __restrict__ scal_next) {
+                                                int defer_choice, GramRecords records, Scal* __restrict__ scal_next) {
     __shared__ double delta_s[kMaxV + 8];
     __shared__ const double* vecp[kMaxV + 8];
     __shared__ double red[kWaves * 7];
@@ -268,19 +266,22 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
     double xn = x[e_safe], gn = g[e_safe], ln = l[e_safe], un = u[e_safe];
     uint8_t mkn = mask[e_safe];
     int c, head;
-    constexpr int kDirPre = CLOSE ? 2 * kWideM + 1 : 1;      // (the wide Gram kernel takes at most kWideM pairs)
+    constexpr int kDirPre = CLOSE ? 2 * kGramOpenM + 1 : 1;
     double vpre[kDirPre];
 #pragma unroll
     for (int j = 0; j < kDirPre; ++j) vpre[j] = 0.0;
     if constexpr (CLOSE) {
         __shared__ Scal sc;
-        __shared__ double Gs[(2 * kWideM + 2) * (2 * kWideM + 2)];
-        __shared__ double tot[kWideNE];
+        __shared__ double Gs[(2 * kGramOpenM + 2) * (2 * kGramOpenM + 2)];
+        __shared__ double tot[gram_entries(kGramOpenM)];
         __shared__ double alpha_s[kMaxM + 1];
         constexpr int kScalWords = (int)(sizeof(Scal) / 4);
         for (int k = tid; k < kScalWords; k += kBlock)
             reinterpret_cast<int*>(&sc)[k] = reinterpret_cast<const int*>(scal)[k];
-        gram_sum_partials_flat(grampart, kWideNE, gram_blocks, tot);
+        int pa, pb;                                                // (worked out while the records are on their way)
+        gram_product_slots(tid < gram_products(m) ? tid : 0, m, pa, pb);
+        asm volatile("" : "+v"(pa), "+v"(pb));
+        gram_sum_partials_flat<kBlock>(records.part, gram_entries(m), records.count, tot);
         __syncthreads();
         if (sc.status != LBFGSB_RUNNING) {
             // (the pass reads its status word from scal_next: it must not find an older one there)
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
             for (int j = 0; j < kDirPre; ++j) vpre[j] = j < 2 * c + 1 ? vecp[j][e_first] : 0.0;
         }
         __syncthreads();                                           // every thread has read the ring before it changes
-        wide_finish(tot, Gs, alpha_s, &sc, m, c, head, base_slot, op, yn_old, 0, 1, blockIdx.x == 0);
+        gram_finish<kBlock>(tot, Gs, alpha_s, &sc, m, c, head, base_slot, op, yn_old, 0, 1, blockIdx.x == 0, pa, pb);
         __syncthreads();                                           // the first wave's results are in the copy
         if (blockIdx.x == 0) {
             if (tid == 0) note_progress(op, sc.status);
@@ -390,9 +391,12 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
     dir_finish(s, ub, op.eps, scal, redpart, red, &flag, sx, fold, defer_choice);
 }
 
-// The same for long vectors (n even, from 2^17 entries on): two elements per lane through 16-byte accesses; lanes
-// whose elements are fixed skip the pair memory.
+// The same for long vectors (from 2^17 entries on): two elements per lane through 16-byte accesses; lanes whose elements are
+// fixed skip the pair memory.  With odd n a vector of the pair memory may start on any element (the memory pipeline takes
+// 16-byte accesses at any multiple of four), and the last pair's second element belongs to whatever follows in the workspace:
+// it is read with the first, counts as fixed, and is not written.
 typedef double dir_f64x2 __attribute__((ext_vector_type(2)));
+typedef dir_f64x2 dir_f64x2_any __attribute__((aligned(8)));
 
 __device__ __forceinline__ void dir_element(double xe, double ge, double le, double ue, double de, double eps, double& a,
                                             double& b, double (&s)[6], double& ub) {
@@ -406,6 +410,7 @@ __device__ __forceinline__ void dir_element(double xe, double ge, double le, dou
     else if (b < 0.0) ub = fmin(ub, (le - xe) / b);
 }
 
+template <bool CLOSE>
 __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op, const double* __restrict__ x,
                                                       const double* __restrict__ g, const double* __restrict__ l,
                                                       const double* __restrict__ u, const uint8_t* __restrict__ mask,
@@ -413,24 +418,17 @@ __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op,
                                                       Scal* __restrict__ scal, double* __restrict__ d,
                                                       double* __restrict__ p1, double* __restrict__ p2,
                                                       double* __restrict__ redpart, int d_given, int store_d,
-                                                      int defer_choice) {
+                                                      int defer_choice, GramRecords records, Scal* __restrict__ scal_next) {
     __shared__ double delta_s[kMaxV + 24];
     __shared__ double red[kWaves * 7];
     __shared__ int flag;
-    if (scal->status != LBFGSB_RUNNING) return;
     const int tid = threadIdx.x;
-    const int c = scal->count, head = scal->head;
-    const int V = 2 * c + 1;
-    if (tid < kMaxV + 24) delta_s[tid] = tid < V ? scal->delta[tid] : 0.0;
-    __syncthreads();
-    double s[6] = {0, 0, 0, 0, 0, 0};
-    double ub = INFINITY;
     const int64_t nchunks = (n + 2 * kBlock - 1) / (2 * kBlock);
     // the mask decides which lanes read the pair memory at all, so it (with x, g, l, u) is fetched one chunk ahead
     auto pair_index = [&](int64_t ch, bool& in) -> int64_t {
         const int64_t e = ch * (2 * kBlock) + 2 * tid;
-        in = ch < nchunks && e < n;                              // n is even: both elements or neither
-        return in ? e : n - 2;
+        in = ch < nchunks && e < n;
+        return in ? e : 0;
     };
     bool in_next;
     int64_t ec_next = pair_index(blockIdx.x, in_next);
@@ -439,77 +437,161 @@ __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op,
     dir_f64x2 ln = dir_f64x2{op.lo, op.lo}, un = dir_f64x2{op.hi, op.hi};
     if (!ub_same) { ln = *reinterpret_cast<const dir_f64x2*>(l + ec_next); un = *reinterpret_cast<const dir_f64x2*>(u + ec_next); }
     unsigned short mkn = *reinterpret_cast<const unsigned short*>(mask + ec_next);
-    for (int64_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
+    // the free bytes of a pair (an odd vector's last pair has one element)
+    auto pair_mask = [&](bool in, int64_t e, unsigned short mk) -> unsigned short {
+        return in ? (e + 1 < n ? mk : (unsigned short)(mk & 0xffu)) : (unsigned short)0;
+    };
+    int c, V;
+    // 24 vectors per round: with m <= 11 every load of an element is in flight at once
+    constexpr int kRound = 24;
+    auto vec = [&](int j, int base_slot) -> const double* {      // (uniform: scalar registers)
+        if (j >= 2 * c) return g;
+        const int k = base_slot + (j < c ? j : j - c), slot = k < m ? k : k - m;
+        return (j < c ? S : Y) + (int64_t)slot * n;
+    };
+    auto load = [&](int j0, int base_slot, int64_t e, dir_f64x2 (&v)[kRound]) {
+#pragma unroll
+        for (int k = 0; k < kRound; ++k) {
+            v[k] = dir_f64x2{0.0, 0.0};
+            if (j0 + k < V) v[k] = *reinterpret_cast<const dir_f64x2_any*>(vec(j0 + k, base_slot) + e);
+        }
+    };
+    auto add = [&](int j0, const dir_f64x2 (&v)[kRound], double& q0, double& q1) {
+#pragma unroll
+        for (int k = 0; k < kRound; ++k) {
+            q0 = fma(delta_s[j0 + k], v[k].x, q0);
+            q1 = fma(delta_s[j0 + k], v[k].y, q1);
+        }
+    };
+    int base_slot;
+    dir_f64x2 first[CLOSE ? kRound : 1];
+    if constexpr (CLOSE) {
+        // the Gram kernel's closing step on a private copy of the scalar block, as in k_dir<true>; the first chunk's vectors
+        // are requested before it and arrive under it
+        __shared__ Scal sc;
+        __shared__ double Gs[(2 * kGramOpenM + 2) * (2 * kGramOpenM + 2)];
+        __shared__ double tot[gram_entries(kGramOpenM)];
+        __shared__ double alpha_s[kMaxM + 1];
+        static_assert(2 * kGramOpenM + 1 <= kRound, "one round holds every vector");
+        constexpr int kScalWords = (int)(sizeof(Scal) / 4);
+        for (int k = tid; k < kScalWords; k += kBlock)
+            reinterpret_cast<int*>(&sc)[k] = reinterpret_cast<const int*>(scal)[k];
+        int pa, pb;
+        gram_product_slots(tid < gram_products(m) ? tid : 0, m, pa, pb);
+        asm volatile("" : "+v"(pa), "+v"(pb));
+        gram_sum_partials_flat<kBlock>(records.part, gram_entries(m), records.count, tot);
+        __syncthreads();
+        if (sc.status != LBFGSB_RUNNING) {
+            // (the kernel behind reads its status word from scal_next: it must not find an older one there)
+            if (blockIdx.x == 0 && tid == 0) { scal_next->status = sc.status; scal_next->fresh = 0; note_progress(op, sc.status); }
+            return;
+        }
+        int head = __builtin_amdgcn_readfirstlane(sc.head);
+        c = __builtin_amdgcn_readfirstlane(sc.count);
+        if (sc.pend_valid) {                                     // same rule as effective_ring()
+            if (sc.pend_ok) { head = (head + 1) % m; c = c < m ? c + 1 : m; }
+            else c = 0;
+        }
+        c = __builtin_amdgcn_readfirstlane(c);
+        head = __builtin_amdgcn_readfirstlane(head);
+        V = 2 * c + 1;
+        base_slot = c > 0 ? (head - c + 2 * m) % m : 0;
+        const double yn_old = prefetch_ynorm2(&sc, c, head, m);
+        if (pair_mask(in_next, ec_next, mkn) != 0) load(0, base_slot, ec_next, first);
+        __syncthreads();                                         // every thread has read the ring before it changes
+        gram_finish<kBlock>(tot, Gs, alpha_s, &sc, m, c, head, base_slot, op, yn_old, 0, 1, blockIdx.x == 0, pa, pb);
+        __syncthreads();                                         // the first wave's results are in the copy
+        if (blockIdx.x == 0) {
+            if (tid == 0) note_progress(op, sc.status);
+            for (int k = tid; k < kScalWords; k += kBlock) {
+                int v = reinterpret_cast<const int*>(&sc)[k];
+                if (k == (int)(offsetof(Scal, fresh) / 4)) v = 1;
+                reinterpret_cast<int*>(scal_next)[k] = v;
+            }
+        }
+        if (sc.status != LBFGSB_RUNNING) return;
+        if (tid < kMaxV + 24) delta_s[tid] = tid < V ? sc.delta[tid] : 0.0;
+    } else {
+        if (scal->status != LBFGSB_RUNNING) return;
+        c = scal->count;
+        V = 2 * c + 1;
+        base_slot = c > 0 ? (scal->head - c + 2 * m) % m : 0;
+        if (tid < kMaxV + 24) delta_s[tid] = tid < V ? scal->delta[tid] : 0.0;
+    }
+    __syncthreads();
+    double s[6] = {0, 0, 0, 0, 0, 0};
+    double ub = INFINITY;
+    auto chunk = [&](int64_t ch, bool have_first) {
         const bool in = in_next;
         const int64_t ec = ec_next, e = ec_next;
         const dir_f64x2 xe = xn, ge = gn, le = ln, ue = un;
-        const unsigned short mk = in ? mkn : (unsigned short)0;
+        const bool in2 = e + 1 < n;
+        const unsigned short mk = pair_mask(in, e, mkn);
         ec_next = pair_index(ch + gridDim.x, in_next);
         xn = *reinterpret_cast<const dir_f64x2*>(x + ec_next); gn = *reinterpret_cast<const dir_f64x2*>(g + ec_next);
         if (!ub_same) { ln = *reinterpret_cast<const dir_f64x2*>(l + ec_next); un = *reinterpret_cast<const dir_f64x2*>(u + ec_next); }
         mkn = *reinterpret_cast<const unsigned short*>(mask + ec_next);
         dir_f64x2 de;
         if (d_given) {
-            de = *reinterpret_cast<const dir_f64x2*>(d + ec);
+            de = dir_f64x2{d[e], in2 ? d[e + 1] : 0.0};
         } else {
             double q0 = 0.0, q1 = 0.0;
             if (mk != 0) {                                       // lanes whose two elements are both fixed read nothing
-                // 24 vectors per round: with m <= 11 every load of an element is in flight at once
-                for (int j0 = 0; j0 < V; j0 += 24) {
-                    dir_f64x2 v[24];
-#pragma unroll
-                    for (int k = 0; k < 24; ++k) {
-                        v[k] = dir_f64x2{0.0, 0.0};
-                        if (j0 + k < V) v[k] = *reinterpret_cast<const dir_f64x2*>(ring_vec(j0 + k, c, head, m, n, S, Y, g) + ec);
-                    }
-#pragma unroll
-                    for (int k = 0; k < 24; ++k) {
-                        q0 = fma(delta_s[j0 + k], v[k].x, q0);
-                        q1 = fma(delta_s[j0 + k], v[k].y, q1);
+                if (CLOSE && have_first) {
+                    if constexpr (CLOSE) add(0, first, q0, q1);
+                } else {
+                    for (int j0 = 0; j0 < V; j0 += kRound) {
+                        dir_f64x2 v[kRound];
+                        load(j0, base_slot, ec, v);
+                        add(j0, v, q0, q1);
                     }
                 }
             }
             de.x = (mk & 0xffu) ? -q0 : 0.0;
             de.y = (mk >> 8) ? -q1 : 0.0;
-            if (in && store_d) *reinterpret_cast<dir_f64x2*>(d + e) = de;
+            if (in && store_d) { d[e] = de.x; if (in2) d[e + 1] = de.y; }
         }
         if (in) {
             double a0, b0, a1, b1;
             dir_element(xe.x, ge.x, le.x, ue.x, de.x, op.eps, a0, b0, s, ub);
-            dir_element(xe.y, ge.y, le.y, ue.y, de.y, op.eps, a1, b1, s, ub);
-            *reinterpret_cast<dir_f64x2*>(p1 + e) = dir_f64x2{a0, a1};
-            *reinterpret_cast<dir_f64x2*>(p2 + e) = dir_f64x2{b0, b1};
+            if (in2) {
+                dir_element(xe.y, ge.y, le.y, ue.y, de.y, op.eps, a1, b1, s, ub);
+                *reinterpret_cast<dir_f64x2*>(p1 + e) = dir_f64x2{a0, a1};
+                *reinterpret_cast<dir_f64x2*>(p2 + e) = dir_f64x2{b0, b1};
+            } else {
+                p1[e] = a0;
+                p2[e] = b0;
+            }
         }
-    }
+    };
+    int64_t ch = blockIdx.x;
+    if (CLOSE && ch < nchunks) { chunk(ch, true); ch += gridDim.x; }
+    for (; ch < nchunks; ch += gridDim.x) chunk(ch, false);
     double sx[2 * kFoldMax];
 #pragma unroll
     for (int k = 0; k < 2 * kFoldMax; ++k) sx[k] = 0.0;
     dir_finish(s, ub, op.eps, scal, redpart, red, &flag, sx, FoldArgs{0, nullptr, nullptr, nullptr, nullptr}, defer_choice);
 }
 
-// extra rows can ride along with the direction kernel for short vectors only
+// one or two extra rows ride along with k_dir; k_dir_pairs has no room for them
 bool dir_folds_extra_rows(const Dims& dm) {
     return dm.n_extra > 0 && dm.n_extra <= kFoldMax && !(dm.n >= (1 << 17) && dm.n % 2 == 0);
 }
 
 void launch_dir(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int d_given, int store_d,
-                hipStream_t st, const double* fold_rows, const double* fold_weight, int defer_choice, int gram_blocks) {
+                hipStream_t st, const double* fold_rows, const double* fold_weight, int defer_choice, int open_gram) {
     FoldArgs fold{0, nullptr, nullptr, nullptr, nullptr};
     if (fold_rows && dir_folds_extra_rows(dm)) fold = FoldArgs{dm.n_extra, fold_rows, fold_weight, bf.wextra, bf.xres + dm.n_extra};
-    if (dm.n >= (1 << 17) && dm.n % 2 == 0) {
-        hipLaunchKernelGGL(k_dir_pairs, dim3(ge.dir_blocks), dim3(kBlock), 0, st, dm.n, dm.m, op, bf.x, bf.g, bf.l, bf.u,
-                           bf.mask, bf.S, bf.Y, bf.scal, bf.d, bf.p1, bf.p2, bf.redpart, d_given, store_d, defer_choice);
-        return;
-    }
-    if (gram_blocks > 0) {
-        hipLaunchKernelGGL(k_dir<true>, dim3(ge.dir_blocks), dim3(kBlock), 0, st, dm.n, dm.m, op, bf.x, bf.g, bf.l, bf.u,
-                           bf.mask, bf.S, bf.Y, bf.scal, bf.d, bf.p1, bf.p2, bf.redpart, d_given, store_d, fold, defer_choice,
-                           (const double*)bf.grampart, gram_blocks, bf.scal_next);
-        return;
-    }
-    hipLaunchKernelGGL(k_dir<false>, dim3(ge.dir_blocks), dim3(kBlock), 0, st, dm.n, dm.m, op, bf.x, bf.g, bf.l, bf.u,
-                       bf.mask, bf.S, bf.Y, bf.scal, bf.d, bf.p1, bf.p2, bf.redpart, d_given, store_d, fold, defer_choice,
-                       (const double*)nullptr, 0, (Scal*)nullptr);
+    const GramRecords records = open_gram ? gram_records(dm, ge, bf) : GramRecords{nullptr, 0};
+    Scal* next = open_gram ? bf.scal_next : nullptr;
+    if (dm.n >= (1 << 17) && !dir_folds_extra_rows(dm))
+        hipLaunchKernelGGL(open_gram ? k_dir_pairs<true> : k_dir_pairs<false>, dim3(ge.dir_blocks), dim3(kBlock), 0, st, dm.n, dm.m,
+                           op, bf.x, bf.g, bf.l, bf.u, bf.mask, bf.S, bf.Y, bf.scal, bf.d, bf.p1, bf.p2, bf.redpart, d_given,
+                           store_d, defer_choice, records, next);
+    else
+        hipLaunchKernelGGL(open_gram ? k_dir<true> : k_dir<false>, dim3(ge.dir_blocks), dim3(kBlock), 0, st, dm.n, dm.m, op, bf.x,
+                           bf.g, bf.l, bf.u, bf.mask, bf.S, bf.Y, bf.scal, bf.d, bf.p1, bf.p2, bf.redpart, d_given, store_d, fold,
+                           defer_choice, records, next);
 }
 
 // ---- after an evaluation pass: g and f ------------------------------------------------------------------

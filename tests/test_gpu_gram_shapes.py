@@ -1,0 +1,82 @@
+"""The Gram kernel where its layout changes: pairs per instantiation (5, 10, 20, 31 slots, part of them used), four and eight
+waves per workgroup (16384 elements), one and several chunks per wave, long vectors (2^17), a last chunk of any length, vectors
+that start on any element; its closing step in the kernel itself (the hook) and in the direction kernel (whole iterations).
+
+Tolerances: sums of n products of numbers of order one in a fixed tree order, against the literal recursion's: 1e-12 normwise
+(the bound of the other two-loop tests).  Iterations accumulate that through the recursion: 1e-8, as in the transport tests."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2203_16340_amd as L
+from gpu_helpers import DEV, make_solver, rel_err, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,pairs", [(1, 1), (5, 5), (6, 6), (10, 10), (10, 4), (11, 11), (16, 16), (20, 20), (21, 21), (31, 31)])
+@pytest.mark.parametrize("n", [2, 63, 65, 4095, 16384, 16385, 33000, 65537, 131071, 131073, 131136])
+def test_two_loop(n, m, pairs):
+    rng = np.random.default_rng(n + 101 * m + pairs)
+    S = rng.normal(size=(pairs, n))
+    Y = S * np.exp(rng.normal(size=n) * 0.5) + 0.3 * S.sum(axis=1, keepdims=True) / n
+    Y[pairs // 2] *= -1.0 if pairs > 2 else 1.0                     # one that fails the gate
+    g, mask, yn = rng.normal(size=n), (rng.random(n) < 0.7).astype(np.uint8), np.einsum("ij,ij->i", Y, Y)
+    mask[64:160] = 0                                                # chunks without a free variable
+    s = make_solver(L.OBJ_LSQ, np.zeros((1, n)), np.zeros(1), np.full(n, -np.inf), np.full(n, np.inf), m)
+    d, used = s.dbg_two_loop(to_dev(S), to_dev(Y), to_dev(yn), to_dev(g), to_dev(mask))
+    s.close()
+    ref, used_ref = oracle.two_loop(S, Y, g, mask, 1e-10, ynorm2=yn)
+    d = d.cpu().numpy()
+    assert used == used_ref and np.all(d[mask == 0] == 0.0)
+    assert rel_err(d, ref) <= 1e-12
+
+
+# 63 504 (short vectors), 131 043 and 131 769 (odd, either side of 2^17), 131 404 entries
+@pytest.mark.parametrize("rows,cols", [(252, 252), (361, 363), (363, 363), (362, 362 + 1)])
+@pytest.mark.parametrize("m", [3, 10, 12])
+@pytest.mark.parametrize("uniform", [True, False])
+def test_iterations(rows, cols, m, uniform):
+    rng = np.random.default_rng(rows + cols + m)
+    M, n, rho = rng.random((rows, cols)) - 0.3, rows * cols, 4.0
+    u, v = rng.random(rows) + 0.1, rng.random(cols) + 0.1
+    u, v = u / u.sum(), v / v.sum()
+    l, ub = np.zeros(n), np.full(n, np.inf)
+    if not uniform:
+        ub[rng.random(n) < 0.1] = 0.5 / n
+    x0 = np.where(rng.random(n) < 0.5, 0.0, 0.4 * rng.random(n) / n)
+    ref = oracle.Solver(oracle.Objective(oracle.OT_GAUSS, M, lam=0.5).set_marginals(u, v, lam=np.zeros(rows + cols), rho=rho), l, ub,
+                        x0, m, oracle.default_options(tol=0.0))
+    s = L.Solver(L.OBJ_OT_GAUSS, to_dev(M), to_dev(np.concatenate([u, v])), to_dev(l), to_dev(ub), m, lam=0.5,
+                 options=L.default_options(tol=0.0), row_weight=to_dev(np.full(rows + cols, rho)))
+    s.set_x(to_dev(x0))
+    for _ in range(m + 3):
+        ref.step()
+        s.step(False)
+    info = s.info()
+    assert info.iters == ref.info.iters and info.branch == ref.info.branch and info.n_fixed == ref.info.n_fixed
+    assert info.pg2 == pytest.approx(ref.info.pg2, rel=1e-8) and info.pginf == pytest.approx(ref.info.pginf, rel=1e-8)
+    assert rel_err(s.x().cpu().numpy(), ref.x) <= 1e-8 and rel_err(s.g().cpu().numpy(), ref.g) <= 1e-8
+    ref.close()
+    s.close()
+
+
+def test_a_step_after_the_end_changes_nothing():
+    """Long vectors: the direction kernel finds the end of the run and leaves it to the row-sum kernel to record; further steps
+    find it there."""
+    rows, cols = 363, 365
+    rng = np.random.default_rng(5)
+    M = rng.standard_normal((rows, cols))
+    n = rows * cols
+    s = L.Solver(L.OBJ_OT_GAUSS, to_dev(M), None, to_dev(np.zeros(n)), to_dev(np.full(n, np.inf)), 5, lam=0.5,
+                 options=L.default_options(tol=1e-9, max_iter=50))
+    s.set_x(torch.zeros(n, dtype=torch.float64, device=DEV))
+    for _ in range(20):
+        s.step(False)
+    a, xa = s.info(), s.x().clone()
+    for _ in range(3):
+        s.step(False)
+    b = s.info()
+    assert a.status == L.CONVERGED and a.as_dict() == b.as_dict() and torch.equal(xa, s.x())
+    s.close()

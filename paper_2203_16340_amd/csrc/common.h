@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include "../../include/lbfgsb.h"
+#include "elementary.h"
 
 namespace lb {
 
@@ -267,7 +268,7 @@ __device__ __forceinline__ double clampd(double v, double lo, double hi) {
     return v < lo ? lo : (v > hi ? hi : v);
 }
 
-__device__ __forceinline__ double softplus_d(double t) { return fmax(t, 0.0) + log1p(exp(-fabs(t))); }
+__device__ __forceinline__ double softplus_d(double t) { return fmax(t, 0.0) + log1p_d(exp(-fabs(t))); }
 __device__ __forceinline__ double sigmoid_d(double t) {
     if (t >= 0.0) return 1.0 / (1.0 + exp(-t));
     const double e = exp(t);
@@ -281,8 +282,8 @@ __device__ __forceinline__ double softplus_diff(double q, double sq, double dq) 
     // log1p of it would itself take the logarithm of a difference of nearly equal numbers; there the same number is
     // log(sigmoid(-q) + sigmoid(q) e^dq), a sum of two positive terms.
     const double u = sq * expm1(dq);
-    if (u > -0.5) return log1p(u);
-    return log(sigmoid_d(-q) + sq * exp(dq));
+    if (u > -0.5) return log1p_d(u);
+    return log_d(sigmoid_d(-q) + sq * exp(dq));
 }
 
 // ---- Algorithm 2's choice between the two candidate directions, from the direction kernel's partial sums ----------

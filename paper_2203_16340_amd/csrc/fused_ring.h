@@ -87,7 +87,7 @@ __device__ __forceinline__ void row_eval(int mode, double u, double b, double z,
             const double q = -b * u;
             const double e = exp(-fabs(q));
             psi = -b * ((q >= 0.0 ? 1.0 : e) / (1.0 + e)) * invn;
-            loss = (fmax(q, 0.0) + log1p(e)) * invn;
+            loss = (fmax(q, 0.0) + log1p_d(e)) * invn;
             keep = u;
         } else {                            // kRowLogiSpec: t = X p, and the weights of the FIRST trial step alpha0
             // psi = -y sigma(-y (z + alpha0 t))/N: what the transposed product needs if alpha0 is accepted.

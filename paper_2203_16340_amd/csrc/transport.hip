@@ -26,11 +26,11 @@ __device__ __forceinline__ double m_at(const void* M, int dtype, int64_t idx) {
 // lambda * phi(p) and lambda * phi'(p)
 __device__ __forceinline__ double reg_value(int kind, double lambda, double p) {
     if (kind == LBFGSB_OBJ_OT_GAUSS) return 0.5 * lambda * p * p;
-    return p > 0.0 ? lambda * p * log(p) : 0.0;
+    return p > 0.0 ? lambda * p * log_d(p) : 0.0;
 }
 __device__ __forceinline__ double reg_slope(int kind, double lambda, double p) {
     if (kind == LBFGSB_OBJ_OT_GAUSS) return lambda * p;
-    return lambda * (log(p) + 1.0);
+    return lambda * (log_d(p) + 1.0);
 }
 
 // K z, first half: the sums of the RPW rows this workgroup owns, and its partial column sums.
@@ -283,7 +283,7 @@ __device__ __forceinline__ double entropy_h(double r) {
         const double r2 = r * r;
         return r2 * (0.5 + r * (-1.0 / 6.0 + r * (1.0 / 12.0 + r * (-1.0 / 20.0 + r * (1.0 / 30.0 + r * (-1.0 / 42.0))))));
     }
-    return (1.0 + r) * log1p(r) - r;
+    return (1.0 + r) * log1p_d(r) - r;
 }
 
 // NTRY step lengths a0 backtrack^first, ... per sweep over (x, p).  The first launch tries two; two further
@@ -295,7 +295,8 @@ __device__ __forceinline__ double entropy_h(double r) {
 constexpr int kLsTail = 51;   // 2 + kLsBatch + kLsTail = 61 step lengths
 // In wide workgroups the tail's step lengths are taken in groups, a sweep over (x, p) each (they come from the cache after
 // the first): 51 sums and as many logarithms in flight take all registers of a SIMD for one wavefront.  First iteration of a
-// run at 2 10^6 entries: 545 -> 481 us for the 51 lengths (the update kernel 47 -> 43 us, the first two lengths 25 -> 23).
+// run at 2 10^6 entries, with the runtime's logarithm: 545 -> 481 us for the 51 lengths (the update kernel 47 -> 43 us, the first two lengths
+// 25 -> 23); with the one of elementary.h 294, the next eight 91 -> 63, the first two 25 -> 17.
 // With 256 threads there are two wavefronts per SIMD either way, and groups gained nothing (4.4 10^5 entries).
 constexpr int ls_group(int threads) { return threads > 256 ? 17 : kLsTail; }
 
@@ -490,7 +491,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 8 : 4) void k_ot_update_entropy(Di
             const double xi = x[e];
             const double xn = op.uniform_bounds ? clampd(fma(alpha, p[e], xi), op.lo, op.hi)
                                                 : clampd(fma(alpha, p[e], xi), l[e], u[e]);
-            const double lg = log(xn);
+            const double lg = log_d(xn);
             const double gn = mij + dm.lambda * (lg + 1.0) + (ri + cj);
             Sn[e] = xn - xi;
             Yn[e] = gn - g[e];

@@ -185,10 +185,7 @@ Geometry make_geometry(const Dims& dm, const void* A, SingleRead reads = kReadAn
         ge.ot_row_blocks = (int)((dm.rows + rpw - 1) / rpw);
         int64_t cb = (dm.cols + kCX - 1) / kCX;
         ge.ot_col_blocks = (int)(cb > 2048 ? 2048 : cb);
-        const int subs = ot_threads(dm) / kOtTile;
-        // (256 threads: whole rows; more: tiles of rows, one per sub-group and trip)
-        const int64_t tb = subs > 1 ? (dm.rows * ((dm.cols + kOtTile - 1) / kOtTile) + subs - 1) / subs : dm.rows;
-        ge.ot_el_blocks = (int)(tb > 512 ? 512 : tb);
+        ge.ot_el_blocks = ot_entry_blocks(dm);
         int64_t eb = (dm.n + ot_threads(dm) - 1) / ot_threads(dm);
         ge.ls_blocks = (int)(eb > 512 ? 512 : eb);
     }
@@ -627,7 +624,7 @@ int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj
     if (o.a_pass == LBFGSB_APASS_FUSED && (!s->ge.fused_ok || s->ge.vec == 1))
         return fail(LBFGSB_E_UNSUPPORTED, "the fused A pass does not support this shape");
     {
-        const hipError_t ge_ = gram_prepare(s->dm);
+        const hipError_t ge_ = gram_prepare(s->dm, 0);
         if (ge_ != hipSuccess) return fail(LBFGSB_E_HIP, "preparing the Gram kernel: %s", hipGetErrorString(ge_));
     }
     const bool resident_ok = resident_shape_ok(s->dm, obj->row_weight != nullptr);
@@ -1180,6 +1177,7 @@ int lbfgsb_dbg_two_loop(lbfgsb_solver* s, const double* S, const double* Y, cons
     HIP_TRY(write_scal(s));
     HIP_TRY(hipMemcpyAsync(s->bf.g, g, nb, hipMemcpyDeviceToDevice, s->stream));
     HIP_TRY(hipMemcpyAsync(s->bf.mask, mask, (size_t)s->dm.n, hipMemcpyDeviceToDevice, s->stream));
+    HIP_TRY(gram_prepare(s->dm, 1));
     launch_gram(s->dm, s->op, s->ge, s->bf, 1, 0, s->stream);
     launch_dir(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream);
     HIP_TRY(hipMemcpyAsync(d, s->bf.d, nb, hipMemcpyDeviceToDevice, s->stream));

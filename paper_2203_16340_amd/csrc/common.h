@@ -20,7 +20,7 @@ constexpr int kFoldMax = 2;       // extra dense rows the direction kernel handl
 constexpr int kLsBatch = 8;        // step lengths the logistic line search evaluates per sweep over the rows
 
 // Which per-kernel arrival counter (Scal::counters) a kernel uses to find its last workgroup.
-enum { kCntGram = 0, kCntDir, kCntUpdate, kCntEvalFinish, kCntLs, kCntCount };
+enum { kCntDir = 0, kCntUpdate, kCntLs, kCntCount };
 // Grids of the kernels whose last workgroup finishes the job (arrive_is_last) stay at two workgroups per compute
 // unit: every workgroup ends with an atomic on one address, and those serialise (4096 workgroups measured 90 us
 // slower per launch than 512 on the same data).
@@ -173,25 +173,25 @@ __device__ __forceinline__ void block_sum(double (&v)[K], double* lds /* NW*K do
     }
 }
 
-// Signals that this workgroup's partial results are in memory and tells whether it is the last
-// one of the grid to do so.  Every wave first waits for its own stores to be acknowledged; after the
-// barrier thread 0 alone issues the device-scope release fence (which writes the L2 back) and the
-// relaxed device-scope atomic, and in the last workgroup the acquire fence; the barrier that follows
-// extends that to the other waves.  Fencing in every wave instead costs ~60 ns per workgroup of
-// serialised time on MI355X.  The last workgroup resets the counter for the next launch.  Must be
-// called by all threads of the workgroup.
+// What workgroups of one launch hand to its last one: stored and loaded at device scope, past the caches that belong to one
+// accelerator die.
+__device__ __forceinline__ void publish(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ double observe(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Signals that this workgroup's published results are in memory and tells whether it is the last one of the grid to do so.
+// Every wave first waits for its own stores to be acknowledged -- a published one is when it has reached memory that all dies
+// share -- and its loads to have returned; after the barrier thread 0 counts the workgroup in.  The last workgroup may then
+// observe() what the others have published, and overwrite what they have read.  Nothing else they have stored is in order for
+// it: there is no fence here, because a release at device scope writes the die's whole cache back, whatever is dirty in it, and
+// each workgroup would do so (entropy update, 2 10^6 entries, 64 MB written by 500 workgroups: 52 us with the fences, 35.5
+// without; long Gram kernel 35.7 / 33.1).  The last workgroup resets the counter for the next launch.  Must be called by all threads of the workgroup.
 __device__ __forceinline__ bool arrive_is_last(unsigned* counter, int* lds_flag, unsigned expected = 0u) {
-    __builtin_amdgcn_s_waitcnt(0);   // vmcnt(0) expcnt(0) lgkmcnt(0): this wave's stores have reached L2
+    __builtin_amdgcn_s_waitcnt(0);   // vmcnt(0) expcnt(0) lgkmcnt(0)
     __syncthreads();
     if (threadIdx.x == 0) {
-        __threadfence();
         const unsigned total = expected ? expected : gridDim.x * gridDim.y;   // expected: arrivals at this counter
-        const unsigned old = atomicAdd(counter, 1u);
-        const int last = old == total - 1u;
-        if (last) {
-            __threadfence();
-            *counter = 0u;
-        }
+        const int last = atomicAdd(counter, 1u) == total - 1u;
+        if (last) *counter = 0u;
         *lds_flag = last;
     }
     __syncthreads();
@@ -488,13 +488,11 @@ __device__ __forceinline__ double sum_all(const double* __restrict__ v, int coun
     return s[0];
 }
 
-// Transport kinds: entries of a row of P that 256 threads take at a time, and the threads of a workgroup in the kernels
-// with a logarithm per entry (transport.hip): these end in an arrival at one address, so they have at most 512 workgroups,
+// Transport kinds, entropy: the threads of a workgroup in the line search (transport.hip).  Its kernels end in an arrival at one address, so they have at most 512 workgroups,
 // and with 256 threads each those leave two wavefronts per SIMD to hide a memory trip and a logarithm behind each other,
 // sixteen entries in a row per thread at 2 10^6.  Shorter problems need fewer threads in all, and there the wider workgroups
 // only make every launch dearer, those that return at once included.  Entropy regulariser, whole runs, 256 / 1024 threads:
 // 4.4 10^5 entries 2355 / 2420 us, 10^6 3450 / 3387, 1.44 10^6 3920 / 3865, 2 10^6 4838 / 4700.
-constexpr int kOtTile = 256;
 constexpr int64_t kOtWideMin = 3 << 18;
 inline int ot_threads(const Dims& dm) { return dm.n >= kOtWideMin ? 1024 : 256; }
 
@@ -693,6 +691,7 @@ struct OtArgs {
 // scal_next (or null): as for a pass over A, see Buffers::scal_next
 void launch_ot_sums(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, int eval, int check_status,
                     hipStream_t st, int dir_blocks = 0, double eps = 0.0, Scal* scal_next = nullptr);
+int ot_entry_blocks(const Dims& dm);   // grid of the gradient's and the entropy update's kernel
 void launch_ot_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, hipStream_t st);
 void launch_ot_update_gauss(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
                             hipStream_t st);
@@ -714,6 +713,6 @@ void launch_resident(const Dims& dm, const Opts& op, const Buffers& bf, const vo
 
 int gram_blocks_for(int64_t n, int m, bool few);   // few: at most kGramOneLevelMax
 size_t gram_partial_bytes(int blocks, int m);      // Buffers::grampart
-hipError_t gram_prepare(const Dims& dm);       // once per solver, before the first launch_gram
+hipError_t gram_prepare(const Dims& dm, int dbg_inputs);   // once per solver, before the first launch_gram
 
 }  // namespace lb

@@ -40,9 +40,9 @@ constexpr int gram_np(int M) { return gram_na(M) == 1 ? gram_nb(M) : 2 * gram_nb
 // A wave's 64 elements of every vector in LDS: doubles from one vector to the next, even and an odd multiple of two, so that
 // 16 lanes that read 16 bytes each of 16 vectors touch every bank once
 constexpr int kGramStride = 66;
-// the waves' elements; then their blocks; then G (at most (2 M + 2)^2) and the totals
+// the waves' elements and a row of zeros each; then their blocks; then G (at most (2 M + 2)^2) and the totals
 constexpr int gram_lds_doubles(int M, int waves) {
-    const int elems = waves * 16 * gram_nb(M) * kGramStride, blocks = waves * gram_np(M) * 256;
+    const int elems = waves * (gram_slots(M) + 1) * kGramStride, blocks = waves * gram_np(M) * 256;
     return elems > blocks ? elems : blocks;
 }
 constexpr int gram_tot_at(int M) { return (2 * M + 2) * (2 * M + 2); }
@@ -68,7 +68,7 @@ __device__ __forceinline__ bool reduce_partials(double* __restrict__ grampart, i
         if (groups_only) return false;
         // few workgroups: one level, the last one to finish adds all partials in index order
         if (!arrive_is_last(&scal->gram_cnt[kGramGroups], flag, (unsigned)nwg)) return false;
-        gram_sum_partials_flat<NT>(grampart, NE, nwg, tot);
+        gram_sum_partials_flat<NT, true>(grampart, NE, nwg, tot);
         __syncthreads();
         return true;
     }
@@ -79,7 +79,7 @@ __device__ __forceinline__ bool reduce_partials(double* __restrict__ grampart, i
     auto add = [&](int first, int count, int idx) -> double {
         double v[kGramGroupMax];
 #pragma unroll
-        for (int k = 0; k < kGramGroupMax; ++k) v[k] = k < count ? grampart[(int64_t)(first + k) * NE + idx] : 0.0;
+        for (int k = 0; k < kGramGroupMax; ++k) v[k] = k < count ? observe(grampart + (int64_t)(first + k) * NE + idx) : 0.0;
         double t = v[0];
         if (idx == 0) {
 #pragma unroll
@@ -92,7 +92,7 @@ __device__ __forceinline__ bool reduce_partials(double* __restrict__ grampart, i
     };
     static_assert(kGramGroups <= kGramGroupMax, "one batch of loads at either level");
     if (!arrive_is_last(&scal->gram_cnt[grp], flag, (unsigned)gsize)) return false;
-    for (int idx = tid; idx < NE; idx += NT) grampart[(int64_t)(nwg + grp) * NE + idx] = add(gfirst, gsize, idx);
+    for (int idx = tid; idx < NE; idx += NT) publish(grampart + (int64_t)(nwg + grp) * NE + idx, add(gfirst, gsize, idx));
     if (groups_only) return false;
     if (!arrive_is_last(&scal->gram_cnt[kGramGroups], flag, (unsigned)ngroups)) return false;
     for (int idx = tid; idx < NE; idx += NT) tot[idx] = add(nwg, ngroups, idx);
@@ -175,11 +175,13 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
     f64x4 sum[NP];
 #pragma unroll
     for (int k = 0; k < NP; ++k) sum[k] = f64x4{0.0, 0.0, 0.0, 0.0};
-    double* mine = dyn + wave * (16 * NB * kGramStride);
+    double* mine = dyn + wave * ((NV + 1) * kGramStride);
     const int i16 = lane & 15, q = lane >> 4;
-    const double* opnd_at = mine + i16 * kGramStride + 2 * q;
-    // (slots past the last vector: products that nobody reads, but no stale bits of another launch either)
-    for (int k = NV; k < 16 * NB; ++k) mine[k * kGramStride + lane] = 0.0;
+    // (slots past the last vector: a row of zeros)
+    const double* opnd_at[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) opnd_at[b] = mine + (16 * b + i16 < NV ? 16 * b + i16 : NV) * kGramStride + 2 * q;
+    mine[NV * kGramStride + lane] = 0.0;
     auto multiply = [&](const double (&v)[NV], unsigned long long bits) {
         const int keep = (bits >> lane) & 1ull ? -1 : 0;
 #pragma unroll
@@ -195,7 +197,7 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
             for (int s8 = 4 * half; s8 < 4 * half + 4; ++s8) {
                 f64x2 o[NB];
 #pragma unroll
-                for (int b = 0; b < NB; ++b) o[b] = *reinterpret_cast<const f64x2*>(opnd_at + 16 * b * kGramStride + 8 * s8);
+                for (int b = 0; b < NB; ++b) o[b] = *reinterpret_cast<const f64x2*>(opnd_at[b] + 8 * s8);
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     int k = 0;
@@ -328,13 +330,13 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
         double t = dyn[src];
 #pragma unroll
         for (int w = 1; w < NW; ++w) t += dyn[w * NP * 256 + src];
-        part[kGramHdr + idx] = t;
+        publish(part + kGramHdr + idx, t);
     }
     if (tid < 3) {
         double t = red[tid * NW];
 #pragma unroll
         for (int w = 1; w < NW; ++w) t = tid == 0 ? fmax(t, red[w]) : t + red[tid * NW + w];
-        part[tid] = t;
+        publish(part + tid, t);
     }
     if (!LONG && no_close) return;   // the direction kernel adds the records and does the rest
     double* tot = dyn + gram_tot_at(M);
@@ -397,16 +399,13 @@ GramKernel gram_kernel_for(const Dims& dm, bool dbg, size_t* lds, int* threads) 
 
 }  // namespace
 
-// (the limit is a property of the kernel)
-hipError_t gram_prepare(const Dims& dm) {
-    hipError_t e = hipSuccess;
-    for (int dbg = 0; dbg < 2 && e == hipSuccess; ++dbg) {
-        size_t lds;
-        int threads;
-        const GramKernel k = gram_kernel_for(dm, dbg != 0, &lds, &threads);
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    }
-    return e;
+// (the limit is a property of the kernel; the hooks' instantiation is prepared by them)
+hipError_t gram_prepare(const Dims& dm, int dbg_inputs) {
+    size_t lds;
+    int threads;
+    const GramKernel k = gram_kernel_for(dm, dbg_inputs != 0, &lds, &threads);
+    if (lds <= 64 * 1024 - 1024) return hipSuccess;   // (the default, less what the kernel holds besides)
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
 }
 
 void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int dbg_inputs,

@@ -27,8 +27,8 @@ __device__ __forceinline__ void gram_product_slots(int idx, int m, int& a, int& 
 
 // Adds the records of `nwg` workgroups (NE doubles each; entry 0 is a maximum, the others are sums) in workgroup order into
 // tot[0 .. NE): thread idx takes entry idx, 64 records at a time with every load of a batch issued before the first is used.
-// Called by all NT threads; no barrier inside.
-template <int NT>
+// Called by all NT threads; no barrier inside.  SAME: the records are of this launch (published), else of an earlier one.
+template <int NT, bool SAME>
 __device__ __forceinline__ void gram_sum_partials_flat(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
     constexpr int kBatch = 64;
     for (int idx = threadIdx.x; idx < NE; idx += NT) {
@@ -36,7 +36,10 @@ __device__ __forceinline__ void gram_sum_partials_flat(const double* __restrict_
         for (int k0 = 0; k0 < nwg; k0 += kBatch) {
             double v[kBatch];
 #pragma unroll
-            for (int k = 0; k < kBatch; ++k) v[k] = k0 + k < nwg ? grampart[(int64_t)(k0 + k) * NE + idx] : (idx == 0 ? -INFINITY : 0.0);
+            for (int k = 0; k < kBatch; ++k) {
+                const double* r = grampart + (int64_t)(k0 + k) * NE + idx;
+                v[k] = k0 + k < nwg ? (SAME ? observe(r) : *r) : (idx == 0 ? -INFINITY : 0.0);
+            }
             if (idx == 0) {
 #pragma unroll
                 for (int k = 0; k < kBatch; ++k) t = fmax(t, v[k]);

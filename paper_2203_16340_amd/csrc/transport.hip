@@ -12,6 +12,7 @@
 //   k_ot_ls_entropy / k_ot_update_entropy   the same for the entropy, whose line search
 //                           needs one pass over (x, p) per batch of trial steps
 #include <cstddef>
+#include <type_traits>
 
 #include "common.h"
 
@@ -143,55 +144,49 @@ __global__ __launch_bounds__(kBlock) void k_ot_cols(Dims dm, OtArgs a, int eval,
     if (tid == 0) losspart[blockIdx.x] = loss[0];
 }
 
-// The kernels with a logarithm per entry (ot_threads: why two workgroup sizes): calls f(i, j, row(i)) for this thread's
-// entries of P.  A workgroup of 256 threads takes whole rows; a larger one is made of sub-groups of kOtTile threads, each
-// of which walks over tiles (row i, columns kOtTile k ..).  (Tiles for 256 threads as well: 2-5 % slower whole runs at 4.4 10^5
-// entries, the divisions and the row's factor per tile.)
-template <int NT, typename R, typename F>
-__device__ __forceinline__ void for_entries(int64_t rows, int64_t cols, R row, F f) {
-    if constexpr (NT == kOtTile) {
-        for (int64_t i = blockIdx.x; i < rows; i += gridDim.x) {
-            const double ri = row(i);
-            for (int64_t j = threadIdx.x; j < cols; j += NT) f(i, j, ri);
-        }
-    } else {
-        constexpr int kSub = NT / kOtTile;
-        const int64_t tpr = (cols + kOtTile - 1) / kOtTile, step = (int64_t)gridDim.x * kSub;
-        const int64_t q = (int64_t)blockIdx.x * kSub + threadIdx.x / kOtTile;
-        const int64_t di = step / tpr, dk = step - di * tpr;
-        int64_t i = q / tpr, k = q - i * tpr;
-        while (i < rows) {
-            const int64_t j = k * kOtTile + threadIdx.x % kOtTile;
-            if (j < cols) f(i, j, row(i));
-            i += di;
-            k += dk;
-            if (k >= tpr) { k -= tpr; ++i; }
-        }
-    }
-}
+// The gradient's and the entropy update's kernel: a workgroup takes R consecutive rows, a thread a column of them at a time, so
+// that the column's coefficient -- three loads -- is formed once for R entries and the loads of all R are issued before the first
+// is used.  R is the least that leaves 512 workgroups (the update ends in an arrival), four at most: registers.  What bounds
+// them is memory and, for the entropy, the logarithm.  Entropy, 2 10^6 entries: update 35.5 us (128 MB), gradient 10.7 (52 and 27
+// with one entry at a time and the fences arrive_is_last had); whole runs of 17 to 46 steps, with the runtime's logarithm and
+// the former Gram kernels / now, us: 1000 x 1000 3350 / 2800, 700 x 630 2290 / 1820, 300 x 300 (m = 5) 1660 / 1530, 1901 x 333 fp32
+// 3900 / 2320, 251 x 997 2190 / 1630.
+constexpr int kOtRowsMax = 4;
+inline int ot_rows(const Dims& dm) { return dm.rows > 1024 ? 4 : (dm.rows > 512 ? 2 : 1); }
+inline int ot_cols_threads(const Dims& dm) { return dm.cols > 384 ? 512 : 256; }
 
-// g = M + lambda phi'(x) + K^T (omega . residual); the last workgroup adds up f.  (2 10^6 entries, entropy, against
-// workgroups of 256 threads: 31.1 -> 28.6 us; the logarithm is the larger part of it.)
-template <int NT>
-__global__ __launch_bounds__(NT, NT == 1024 ? 8 : 4) void k_ot_eval_finish(Dims dm, OtArgs a, int loss_parts,
-                                                           const double* __restrict__ x, const double* __restrict__ res,
-                                                           const double* __restrict__ losspart, double* __restrict__ g,
-                                                           Scal* __restrict__ scal) {
+// g = M + lambda phi'(x) + K^T (omega . residual); the first workgroup adds up f.
+template <int NT, int R>
+__global__ __launch_bounds__(NT) void k_ot_eval_finish(Dims dm, OtArgs a, int loss_parts, const double* __restrict__ x,
+                                                       const double* __restrict__ res, const double* __restrict__ losspart,
+                                                       double* __restrict__ g, Scal* __restrict__ scal) {
     __shared__ double red[NT / 64];
-    __shared__ int flag;
     if (scal->status != LBFGSB_RUNNING) return;
     const int tid = threadIdx.x;
-    auto row = [&](int64_t i) { return a.omega ? a.omega[i] * res[i] : 0.0; };
-    for_entries<NT>(dm.rows, dm.cols, row, [&](int64_t i, int64_t j, double ri) {
-        const int64_t e = i * dm.cols + j;
-        const double cj = a.omega ? a.omega[dm.rows + j] * res[dm.rows + j] : 0.0;
-        g[e] = m_at(a.M, dm.dtype, i * dm.ld + j) + reg_slope(dm.kind, dm.lambda, x[e]) + (ri + cj);
-    });
-    if (!arrive_is_last(&scal->counters[kCntEvalFinish], &flag)) return;
-    const double f = sum_all<NT>(losspart, loss_parts, red);
-    if (tid == 0) {
-        scal->f = f;
-        scal->fevals += 1;
+    if (blockIdx.x == 0) {
+        const double f = sum_all<NT>(losspart, loss_parts, red);   // (all of earlier launches)
+        if (tid == 0) {
+            scal->f = f;
+            scal->fevals += 1;
+        }
+    }
+    for (int64_t r0 = (int64_t)blockIdx.x * R; r0 < dm.rows; r0 += (int64_t)gridDim.x * R) {
+        double ri[R];
+        int64_t row[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            row[r] = r0 + r < dm.rows ? r0 + r : dm.rows - 1;
+            ri[r] = a.omega ? a.omega[row[r]] * res[row[r]] : 0.0;
+        }
+        for (int64_t j = tid; j < dm.cols; j += NT) {
+            double xv[R], mv[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) { xv[r] = x[row[r] * dm.cols + j]; mv[r] = m_at(a.M, dm.dtype, row[r] * dm.ld + j); }
+            const double cj = a.omega ? a.omega[dm.rows + j] * res[dm.rows + j] : 0.0;
+#pragma unroll
+            for (int r = 0; r < R; ++r)   // (a row past the end: the last row's entry once more)
+                g[row[r] * dm.cols + j] = mv[r] + reg_slope(dm.kind, dm.lambda, xv[r]) + (ri[r] + cj);
+        }
     }
 }
 
@@ -417,7 +412,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? (GROUP <= 2 ? 8 : 4) : 1) void k_o
         group_sum(s);
         if (tid == 0) {
 #pragma unroll
-            for (int k = 0; k < GROUP; ++k) lspart[(int64_t)blockIdx.x * NTRY + k0 + k] = s[k];
+            for (int k = 0; k < GROUP; ++k) publish(lspart + (int64_t)blockIdx.x * NTRY + k0 + k, s[k]);
         }
     }
     if (NPREV == 0 && defer) return;
@@ -433,7 +428,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? (GROUP <= 2 ? 8 : 4) : 1) void k_o
         for (int k = 0; k < GROUP; ++k) tot[k] = 0.0;
         for (int b = tid; b < (int)gridDim.x; b += NT) {
 #pragma unroll
-            for (int k = 0; k < GROUP; ++k) tot[k] += lspart[(int64_t)b * NTRY + k0 + k];
+            for (int k = 0; k < GROUP; ++k) tot[k] += observe(lspart + (int64_t)b * NTRY + k0 + k);
         }
         group_sum(tot);
         if (k0 > 0) av *= op.backtrack;
@@ -463,14 +458,13 @@ __global__ __launch_bounds__(NT, NT == 1024 ? (GROUP <= 2 ? 8 : 4) : 1) void k_o
 }
 
 // x+ = P(x + a p); g+ = M + lambda (log x+ + 1) + K^T (omega . (res + a K p)); pair; f+ from scratch at x+.
-template <int NT>
-__global__ __launch_bounds__(NT, NT == 1024 ? 8 : 4) void k_ot_update_entropy(Dims dm, Opts op, OtArgs a, double* res,
-                                                              const double* __restrict__ t, const double* __restrict__ p1,
-                                                              const double* __restrict__ p2, const double* __restrict__ l,
-                                                              const double* __restrict__ u, double* __restrict__ x,
-                                                              double* __restrict__ g, double* __restrict__ S,
-                                                              double* __restrict__ Y, Scal* __restrict__ scal,
-                                                              double* __restrict__ redpart) {
+template <int NT, int R>
+__global__ __launch_bounds__(NT) void k_ot_update_entropy(Dims dm, Opts op, OtArgs a, double* res, const double* __restrict__ t,
+                                                          const double* __restrict__ p1, const double* __restrict__ p2,
+                                                          const double* __restrict__ l, const double* __restrict__ u,
+                                                          double* __restrict__ x, double* __restrict__ g, double* __restrict__ S,
+                                                          double* __restrict__ Y, Scal* __restrict__ scal,
+                                                          double* __restrict__ redpart) {
     __shared__ double red[NT / 64];
     __shared__ int flag;
     if (scal->status != LBFGSB_RUNNING) return;
@@ -483,29 +477,49 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 8 : 4) void k_ot_update_entropy(Di
     if (ok) {
         double* Sn = S + (int64_t)slot * dm.n;
         double* Yn = Y + (int64_t)slot * dm.n;
-        auto row = [&](int64_t i) { return a.omega ? a.omega[i] * fma(alpha, t[i], res[i]) : 0.0; };
-        for_entries<NT>(dm.rows, dm.cols, row, [&](int64_t i, int64_t j, double ri) {
-            const int64_t e = i * dm.cols + j;
-            const double cj = a.omega ? a.omega[dm.rows + j] * fma(alpha, t[dm.rows + j], res[dm.rows + j]) : 0.0;
-            const double mij = m_at(a.M, dm.dtype, i * dm.ld + j);
-            const double xi = x[e];
-            const double xn = op.uniform_bounds ? clampd(fma(alpha, p[e], xi), op.lo, op.hi)
-                                                : clampd(fma(alpha, p[e], xi), l[e], u[e]);
-            const double lg = log_d(xn);
-            const double gn = mij + dm.lambda * (lg + 1.0) + (ri + cj);
-            Sn[e] = xn - xi;
-            Yn[e] = gn - g[e];
-            x[e] = xn;
-            g[e] = gn;
-            fs[0] = fma(mij, xn, fs[0]);
-            if (xn > 0.0) fs[0] = fma(dm.lambda * xn, lg, fs[0]);
-        });
+        const int64_t bstride = op.uniform_bounds ? 0 : 1;
+        for (int64_t r0 = (int64_t)blockIdx.x * R; r0 < dm.rows; r0 += (int64_t)gridDim.x * R) {
+            double ri[R];
+            int64_t row[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                row[r] = r0 + r < dm.rows ? r0 + r : dm.rows - 1;
+                ri[r] = a.omega ? a.omega[row[r]] * fma(alpha, t[row[r]], res[row[r]]) : 0.0;
+            }
+            for (int64_t j = tid; j < dm.cols; j += NT) {
+                double xv[R], pv[R], gv[R], mv[R], lv[R], uv[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int64_t e = row[r] * dm.cols + j;
+                    xv[r] = x[e]; pv[r] = p[e]; gv[r] = g[e];
+                    mv[r] = m_at(a.M, dm.dtype, row[r] * dm.ld + j);
+                    lv[r] = op.lo; uv[r] = op.hi;
+                    if (bstride) { lv[r] = l[e]; uv[r] = u[e]; }
+                }
+                const double cj = a.omega ? a.omega[dm.rows + j] * fma(alpha, t[dm.rows + j], res[dm.rows + j]) : 0.0;
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const double xn = clampd(fma(alpha, pv[r], xv[r]), lv[r], uv[r]);
+                    const double lg = log_d(xn);
+                    const double gn = mv[r] + dm.lambda * (lg + 1.0) + (ri[r] + cj);
+                    if (r0 + r < dm.rows) {
+                        const int64_t e = row[r] * dm.cols + j;
+                        Sn[e] = xn - xv[r];
+                        Yn[e] = gn - gv[r];
+                        x[e] = xn;
+                        g[e] = gn;
+                        fs[0] = fma(mv[r], xn, fs[0]);
+                        if (xn > 0.0) fs[0] = fma(dm.lambda * xn, lg, fs[0]);
+                    }
+                }
+            }
+        }
     }
     block_sum<1, NT / 64>(fs, red);
-    if (tid == 0) redpart[blockIdx.x] = fs[0];
+    if (tid == 0) publish(redpart + blockIdx.x, fs[0]);
     if (!arrive_is_last(&scal->counters[kCntUpdate], &flag)) return;
     double tot[1] = {0.0};
-    for (int b = tid; b < (int)gridDim.x; b += NT) tot[0] += redpart[b];
+    for (int b = tid; b < (int)gridDim.x; b += NT) tot[0] += observe(redpart + b);
     if (ok) {
         // the residuals of the marginal terms move to the new point here, res += a K p: every other workgroup has
         // finished reading them (it has arrived)
@@ -555,15 +569,31 @@ void launch_ot_sums(const Dims& dm, const Geometry& ge, const Buffers& bf, const
                        (const double*)bf.wpart, (const Scal*)bf.scal, eval ? bf.row : bf.t, bf.losspart + ge.ot_row_blocks);
 }
 
-template <int NT>
-static void launch_eval_finish_t(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(k_ot_eval_finish<NT>, dim3(ge.ot_el_blocks), dim3(NT), 0, st, dm, a,
-                       ge.ot_row_blocks + ge.ot_col_blocks, (const double*)bf.x, (const double*)bf.row,
-                       (const double*)bf.losspart, bf.g, bf.scal);
+// f(workgroup size, rows per workgroup) for this shape's instantiation
+template <class F>
+static void with_ot_shape(const Dims& dm, F f) {
+    auto rows = [&](auto nt) {
+        switch (ot_rows(dm)) {
+            case 1: f(nt, std::integral_constant<int, 1>()); break;
+            case 2: f(nt, std::integral_constant<int, 2>()); break;
+            default: f(nt, std::integral_constant<int, kOtRowsMax>()); break;
+        }
+    };
+    if (ot_cols_threads(dm) == 512) rows(std::integral_constant<int, 512>());
+    else rows(std::integral_constant<int, 256>());
 }
+
 void launch_ot_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, hipStream_t st) {
-    if (ot_threads(dm) == 1024) launch_eval_finish_t<1024>(dm, ge, bf, a, st);
-    else launch_eval_finish_t<256>(dm, ge, bf, a, st);
+    with_ot_shape(dm, [&](auto nt, auto rows) {
+        hipLaunchKernelGGL((k_ot_eval_finish<nt(), rows()>), dim3(ge.ot_el_blocks), dim3(nt()), 0, st, dm, a,
+                           ge.ot_row_blocks + ge.ot_col_blocks, (const double*)bf.x, (const double*)bf.row,
+                           (const double*)bf.losspart, bf.g, bf.scal);
+    });
+}
+
+int ot_entry_blocks(const Dims& dm) {
+    const int64_t b = (dm.rows + ot_rows(dm) - 1) / ot_rows(dm);
+    return (int)(b > 512 ? 512 : b);
 }
 
 void launch_ot_update_gauss(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
@@ -576,8 +606,7 @@ void launch_ot_update_gauss(const Dims& dm, const Opts& op, const Geometry& ge, 
 }
 
 template <int NT>
-static void launch_step_entropy_t(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
-                                  hipStream_t st) {
+static void launch_search_t(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, hipStream_t st) {
     // three launches, each with a region of lspart of its own: the first (two step lengths) only leaves its partial
     // sums, the second takes the first's decision before anything else
     double* part0 = bf.lspart;
@@ -594,14 +623,16 @@ static void launch_step_entropy_t(const Dims& dm, const Opts& op, const Geometry
                        ge.ot_row_blocks + ge.ot_col_blocks, 2 + kLsBatch, 1, 0, (const double*)bf.losspart,
                        (const double*)bf.x, (const double*)bf.p1, (const double*)bf.p2, bf.scal, (const double*)nullptr,
                        part2);
-    hipLaunchKernelGGL(k_ot_update_entropy<NT>, dim3(ge.ot_el_blocks), dim3(NT), 0, st, dm, op, a, bf.row,
-                       (const double*)bf.t, (const double*)bf.p1, (const double*)bf.p2, (const double*)bf.l,
-                       (const double*)bf.u, bf.x, bf.g, bf.S, bf.Y, bf.scal, bf.redpart);
 }
 void launch_ot_step_entropy(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
                             hipStream_t st) {
-    if (ot_threads(dm) == 1024) launch_step_entropy_t<1024>(dm, op, ge, bf, a, st);
-    else launch_step_entropy_t<256>(dm, op, ge, bf, a, st);
+    if (ot_threads(dm) == 1024) launch_search_t<1024>(dm, op, ge, bf, st);
+    else launch_search_t<256>(dm, op, ge, bf, st);
+    with_ot_shape(dm, [&](auto nt, auto rows) {
+        hipLaunchKernelGGL((k_ot_update_entropy<nt(), rows()>), dim3(ge.ot_el_blocks), dim3(nt()), 0, st, dm, op, a, bf.row,
+                           (const double*)bf.t, (const double*)bf.p1, (const double*)bf.p2, (const double*)bf.l,
+                           (const double*)bf.u, bf.x, bf.g, bf.S, bf.Y, bf.scal, bf.redpart);
+    });
 }
 
 }  // namespace lb

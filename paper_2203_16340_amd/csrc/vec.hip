@@ -176,9 +176,9 @@ __device__ __forceinline__ void dir_finish(double (&s)[6], double ub, double eps
         mn = red[0];
         for (int w = 1; w < kWaves; ++w) mn = fmin(mn, red[w]);
         double* part = redpart + (int64_t)blockIdx.x * kDirRed;
-        for (int k = 0; k < 6; ++k) part[k] = s[k];
-        part[6] = mn;
-        for (int k = 0; k < 2 * kFoldMax; ++k) part[8 + k] = sx[k];
+        for (int k = 0; k < 6; ++k) publish(part + k, s[k]);
+        publish(part + 6, mn);
+        for (int k = 0; k < 2 * kFoldMax; ++k) publish(part + 8 + k, sx[k]);
     }
     if (defer_choice) return;   // the consumer of the direction chooses between the candidates from the records
     if (!arrive_is_last(&scal->counters[kCntDir], flag_p)) return;
@@ -191,11 +191,11 @@ __device__ __forceinline__ void dir_finish(double (&s)[6], double ub, double eps
         for (int k = 0; k < 2 * kFoldMax; ++k) tx[k] = 0.0;
         for (int b = tid; b < (int)gridDim.x; b += kBlock) {
 #pragma unroll
-            for (int k = 0; k < 6; ++k) t6[k] += redpart[(int64_t)b * kDirRed + k];
-            tmin = fmin(tmin, redpart[(int64_t)b * kDirRed + 6]);
+            for (int k = 0; k < 6; ++k) t6[k] += observe(redpart + (int64_t)b * kDirRed + k);
+            tmin = fmin(tmin, observe(redpart + (int64_t)b * kDirRed + 6));
             if (fold.n_fold > 0) {
 #pragma unroll
-                for (int k = 0; k < 2 * kFoldMax; ++k) tx[k] += redpart[(int64_t)b * kDirRed + 8 + k];
+                for (int k = 0; k < 2 * kFoldMax; ++k) tx[k] += observe(redpart + (int64_t)b * kDirRed + 8 + k);
             }
         }
         block_sum<6, kWaves>(t6, red);
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
         int pa, pb;                                                // (worked out while the records are on their way)
         gram_product_slots(tid < gram_products(m) ? tid : 0, m, pa, pb);
         asm volatile("" : "+v"(pa), "+v"(pb));
-        gram_sum_partials_flat<kBlock>(records.part, gram_entries(m), records.count, tot);
+        gram_sum_partials_flat<kBlock, false>(records.part, gram_entries(m), records.count, tot);
         __syncthreads();
         if (sc.status != LBFGSB_RUNNING) {
             // (the pass reads its status word from scal_next: it must not find an older one there)
@@ -479,7 +479,7 @@ __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op,
         int pa, pb;
         gram_product_slots(tid < gram_products(m) ? tid : 0, m, pa, pb);
         asm volatile("" : "+v"(pa), "+v"(pb));
-        gram_sum_partials_flat<kBlock>(records.part, gram_entries(m), records.count, tot);
+        gram_sum_partials_flat<kBlock, false>(records.part, gram_entries(m), records.count, tot);
         __syncthreads();
         if (sc.status != LBFGSB_RUNNING) {
             // (the kernel behind reads its status word from scal_next: it must not find an older one there)
@@ -596,21 +596,51 @@ void launch_dir(const Dims& dm, const Opts& op, const Geometry& ge, const Buffer
 
 // ---- after an evaluation pass: g and f ------------------------------------------------------------------
 
+// The last workgroup of the grid adds up f, beside the others: what f takes beyond the pass's loss partials (the regulariser,
+// the linear term, the extra rows) needs x and not the gradient.  (It was formed from the workgroups' shares by the last one to
+// finish; the arrival alone made the kernel 15.7 us at 10 000 columns of a quadratic form, 32 at 20 000 of the L1-split kind.)
 __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, int loss_parts,
                                                         const double* __restrict__ wpart,
                                                         const double* __restrict__ losspart,
                                                         const double* __restrict__ x, double* __restrict__ g,
-                                                        Scal* __restrict__ scal, double* __restrict__ redpart,
+                                                        Scal* __restrict__ scal,
                                                         const double* __restrict__ lin, const double* __restrict__ sign,
                                                         const double* __restrict__ wextra,
                                                         const double* __restrict__ xres) {
     __shared__ double lds[kBlock];
     __shared__ double red[kWaves];
-    __shared__ int flag;
     if (scal->status != LBFGSB_RUNNING) return;
     const int tid = threadIdx.x;
-    double reg = 0.0;
-    for (int64_t c0 = (int64_t)blockIdx.x * kCX; c0 < dm.cols; c0 += (int64_t)gridDim.x * kCX) {
+    if (blockIdx.x == gridDim.x - 1) {
+        double reg[1] = {0.0};
+        if (dm.kind != LBFGSB_OBJ_LSQ) {
+            // (eight variables per trip; L1-split: both halves are variables)
+            for (int64_t i0 = tid; i0 < dm.n; i0 += 8 * kBlock) {
+                double xv[8], cv[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const int64_t i = i0 + k * kBlock;
+                    xv[k] = i < dm.n ? x[i] : 0.0;
+                    cv[k] = dm.kind == LBFGSB_OBJ_QP ? (i < dm.n ? lin[i] : 0.0) : (dm.kind == LBFGSB_OBJ_LOGISTIC_L2 ? xv[k] : 1.0);
+                }
+#pragma unroll
+                for (int k = 0; k < 8; ++k) reg[0] = fma(cv[k], xv[k], reg[0]);
+            }
+            block_sum<1, kWaves>(reg, red);
+        }
+        const double loss = sum_all(losspart, loss_parts, red);
+        if (tid == 0) {
+            double f = loss;
+            if (dm.kind == LBFGSB_OBJ_LSQ_L1SPLIT) f += dm.lambda * reg[0];
+            else if (dm.kind == LBFGSB_OBJ_LOGISTIC_L2) f += 0.5 * dm.mu * reg[0];
+            else if (dm.kind == LBFGSB_OBJ_QP) f += reg[0];
+            if (xres) f += xres[dm.n_extra];   // 0.5 sum weight * residual^2 of the extra rows
+            scal->f = f;
+            scal->fevals += 1;
+        }
+        return;
+    }
+    for (int64_t c0 = (int64_t)blockIdx.x * kCX; c0 < dm.cols; c0 += (int64_t)(gridDim.x - 1) * kCX) {
         const int64_t c = c0 + tid % kCX;
         const double w = column_sum(wpart, w_parts, dm.cols, c, lds);
         if (tid < kCX && c < dm.cols) {
@@ -620,40 +650,21 @@ __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, in
             } else if (dm.kind == LBFGSB_OBJ_LSQ_L1SPLIT) {
                 g[c] = w + dm.lambda + (wextra ? wextra[c] : 0.0);
                 g[c + dm.cols] = -w + dm.lambda + (wextra ? wextra[c + dm.cols] : 0.0);
-                reg += x[c] + x[c + dm.cols];
             } else if (dm.kind == LBFGSB_OBJ_QP) {
-                // w = (A (s.x))_c (a single "partial": the row kernel's output); g = s w + b, f = loss + b.x
+                // w = (A (s.x))_c (a single "partial": the row kernel's output); g = s w + b
                 g[c] = (sign ? sign[c] : 1.0) * w + lin[c] + (wextra ? wextra[c] : 0.0);
-                reg = fma(lin[c], x[c], reg);
             } else {
-                const double xc = x[c];
-                g[c] = fma(dm.mu, xc, w);
-                reg = fma(xc, xc, reg);
+                g[c] = fma(dm.mu, x[c], w);
             }
         }
-    }
-    double rv[1] = {reg};
-    block_sum<1, kWaves>(rv, red);
-    if (tid == 0) redpart[blockIdx.x] = rv[0];
-    if (!arrive_is_last(&scal->counters[kCntEvalFinish], &flag)) return;
-    const double loss = sum_all(losspart, loss_parts, red);
-    const double regt = sum_all(redpart, gridDim.x, red);
-    if (tid == 0) {
-        double f = loss;
-        if (dm.kind == LBFGSB_OBJ_LSQ_L1SPLIT) f += dm.lambda * regt;
-        else if (dm.kind == LBFGSB_OBJ_LOGISTIC_L2) f += 0.5 * dm.mu * regt;
-        else if (dm.kind == LBFGSB_OBJ_QP) f += regt;
-        if (xres) f += xres[dm.n_extra];   // 0.5 sum weight * residual^2 of the extra rows
-        scal->f = f;
-        scal->fevals += 1;
     }
 }
 
 void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* lin, const double* sign,
                         hipStream_t st) {
     const bool qp = dm.kind == LBFGSB_OBJ_QP;
-    hipLaunchKernelGGL(k_eval_finish, dim3(ge.fin_blocks), dim3(kBlock), 0, st, dm, qp ? 1 : ge.w_parts, ge.loss_parts,
-                       qp ? (const double*)bf.row : (const double*)bf.wpart, bf.losspart, bf.x, bf.g, bf.scal, bf.redpart,
+    hipLaunchKernelGGL(k_eval_finish, dim3(ge.fin_blocks + 1), dim3(kBlock), 0, st, dm, qp ? 1 : ge.w_parts, ge.loss_parts,
+                       qp ? (const double*)bf.row : (const double*)bf.wpart, bf.losspart, bf.x, bf.g, bf.scal,
                        lin, sign, dm.n_extra > 0 ? (const double*)bf.wextra : nullptr,
                        dm.n_extra > 0 ? (const double*)bf.xres : nullptr);
 }
@@ -901,7 +912,7 @@ __global__ __launch_bounds__(kBlock) void k_ls_logistic(Dims dm, Opts op, int fi
     block_sum<NTRY, kWaves>(s, red);
     if (tid == 0) {
 #pragma unroll
-        for (int j = 0; j < NTRY; ++j) lspart[(int64_t)blockIdx.x * NTRY + j] = s[j];
+        for (int j = 0; j < NTRY; ++j) publish(lspart + (int64_t)blockIdx.x * NTRY + j, s[j]);
     }
     if (!arrive_is_last(&scal->counters[kCntLs], &flag)) return;
     const double gp = scal->gp, xp = scal->xp, pp = scal->pp;
@@ -912,7 +923,7 @@ __global__ __launch_bounds__(kBlock) void k_ls_logistic(Dims dm, Opts op, int fi
     for (int j = 0; j < NTRY; ++j) tot[j] = 0.0;
     for (int b = tid; b < (int)gridDim.x; b += kBlock) {
 #pragma unroll
-        for (int j = 0; j < NTRY; ++j) tot[j] += lspart[(int64_t)b * NTRY + j];
+        for (int j = 0; j < NTRY; ++j) tot[j] += observe(lspart + (int64_t)b * NTRY + j);
     }
     block_sum<NTRY, kWaves>(tot, red);
     int found = -1;
@@ -1096,10 +1107,10 @@ __global__ __launch_bounds__(kBlock) void k_update_logistic(Dims dm, double c1, 
         return;
     }
     block_sum<2, kWaves>(sums, red);
-    if (tid == 0) { redpart[2 * blockIdx.x] = sums[0]; redpart[2 * blockIdx.x + 1] = sums[1]; }
+    if (tid == 0) { publish(redpart + 2 * blockIdx.x, sums[0]); publish(redpart + 2 * blockIdx.x + 1, sums[1]); }
     if (!arrive_is_last(&scal->counters[kCntUpdate], &flag)) return;
     double tot[2] = {0.0, 0.0};
-    for (int b = tid; b < (int)gridDim.x; b += kBlock) { tot[0] += redpart[2 * b]; tot[1] += redpart[2 * b + 1]; }
+    for (int b = tid; b < (int)gridDim.x; b += kBlock) { tot[0] += observe(redpart + 2 * b); tot[1] += observe(redpart + 2 * b + 1); }
     block_sum<2, kWaves>(tot, red);
     const double loss = ok ? sum_all(losspart, loss_parts, red) : 0.0;
     if (tid == 0) {

@@ -290,10 +290,10 @@ hipError_t read_scal(lbfgsb_solver* s) {
             launch_clear_bail(s->bf, s->stream);
             // the rest of the interrupted iteration: more step lengths, new margins and row weights, the transposed
             // pass for the accepted step, the update
-            launch_ls_logistic(s->dm, s->op, s->ge, s->bf, s->obj.b, 1, 2, s->stream);
-            launch_rows_logistic(s->dm, s->ge, s->bf, s->obj.b, s->stream);
+            launch_ls_logistic(s->dm, s->op, s->ge, s->bf, s->obj.b, 1, 2, 0, s->stream);
+            launch_rows_logistic(s->dm, s->ge, s->bf, s->obj.b, 0, s->stream);
             enqueue_redo_columns(s);
-            launch_update_logistic(s->dm, s->op, s->ge, s->bf, s->ge.lrows_blocks, 0, s->stream);
+            launch_update_logistic(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream);
             s->logi_full_left = kLogiFullSteps;
         } else if (owed == 0 || s->h_scal->status != LBFGSB_RUNNING) {
             return hipSuccess;
@@ -475,30 +475,31 @@ void enqueue_step(lbfgsb_solver* s) {
             recording = hipStreamIsCapturing(s->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusActive;
         }
         const bool full = s->logi_full_left > 0 || !s->short_ok || recording;
-        a.ls_first = full ? 0 : 1;
+        a.ls_first = s->short_ok ? 1 : 0;
+        const int first_parts = s->short_ok ? s->ge.fused_blocks : 0;
         { TimedSlot ts(s); launch_fused(s->dm, s->ge, s->bf, a, s->stream, ts.e0, ts.e1); }
         if (full) {
             if (s->logi_full_left > 0) s->logi_full_left--;
-            launch_ls_logistic(s->dm, s->op, s->ge, s->bf, s->obj.b, 1, 3, s->stream);
-            launch_rows_logistic(s->dm, s->ge, s->bf, s->obj.b, s->stream);
+            launch_ls_logistic(s->dm, s->op, s->ge, s->bf, s->obj.b, 1, s->short_ok ? 2 : 3, first_parts, s->stream);
+            launch_rows_logistic(s->dm, s->ge, s->bf, s->obj.b, s->short_ok ? 1 : 0, s->stream);
             enqueue_redo_columns(s);
-            launch_update_logistic(s->dm, s->op, s->ge, s->bf, s->ge.lrows_blocks, 0, s->stream);
+            launch_update_logistic(s->dm, s->op, s->ge, s->bf, first_parts, 0, s->stream);
         } else {
             // Short sequence: the pass itself sums the loss differences of the first trial step over each workgroup's
             // rows, and the update kernel takes the Armijo decision from those partials; the update of an accepted
             // first step also moves the margins.  The search kernels, the recomputation of the row weights and the
             // second transposed pass -- launches that almost never do work -- are left out; should the first step be
             // rejected, the solver parks itself and read_scal() supplies them.
-            launch_update_logistic(s->dm, s->op, s->ge, s->bf, s->ge.fused_blocks, 1, s->stream);
+            launch_update_logistic(s->dm, s->op, s->ge, s->bf, first_parts, 1, s->stream);
             s->short_steps_unseen++;
         }
     } else {
         a.mode = kRowLogiDir;
         { TimedSlot ts(s); launch_gemv(s->dm, s->ge, s->bf, a, s->stream, ts.e0, ts.e1); }
-        launch_ls_logistic(s->dm, s->op, s->ge, s->bf, s->obj.b, 0, 3, s->stream);
-        launch_rows_logistic(s->dm, s->ge, s->bf, s->obj.b, s->stream);
+        launch_ls_logistic(s->dm, s->op, s->ge, s->bf, s->obj.b, 0, 3, 0, s->stream);
+        launch_rows_logistic(s->dm, s->ge, s->bf, s->obj.b, 0, s->stream);
         { TimedSlot ts(s); launch_gemvt_from(s->dm, s->ge, s->bf, s->obj.A, s->bf.psi, 1, s->stream, ts.e0, ts.e1); }
-        launch_update_logistic(s->dm, s->op, s->ge, s->bf, s->ge.lrows_blocks, 0, s->stream);
+        launch_update_logistic(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream);
     }
     s->steps_since_refresh++;
 }

@@ -270,9 +270,8 @@ __device__ __forceinline__ double clampd(double v, double lo, double hi) {
 
 __device__ __forceinline__ double softplus_d(double t) { return fmax(t, 0.0) + log1p_d(exp(-fabs(t))); }
 __device__ __forceinline__ double sigmoid_d(double t) {
-    if (t >= 0.0) return 1.0 / (1.0 + exp(-t));
-    const double e = exp(t);
-    return e / (1.0 + e);
+    const double e = exp(-fabs(t));
+    return quotient_d(t >= 0.0 ? 1.0 : e, 1.0 + e);
 }
 
 // softplus(q + dq) - softplus(q) without differencing two rounded values; sq = sigmoid(q).
@@ -668,13 +667,17 @@ void launch_extra_rows(const Dims& dm, const Buffers& bf, const double* rows, co
 // stages: 2 = the continuation only (eight more step lengths per sweep, then one at a time: what the host supplies
 // after the short sequence has rejected the first trial step), 3 = the first trial step in a sweep of its own, then
 // the continuation
+// first_parts > 0 (stages 2): the pass over X has summed the loss differences of the first trial step into that many loss
+// partials; the continuation decides on it first.  launch_rows_logistic is then given not_first, launch_update_logistic the
+// same first_parts: the update does all there is to do for an accepted first step.
 void launch_ls_logistic(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const double* labels,
-                        int spec, int stages, hipStream_t st);
-void launch_rows_logistic(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* labels, hipStream_t st);
+                        int spec, int stages, int first_parts, hipStream_t st);
+void launch_rows_logistic(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* labels, int not_first,
+                          hipStream_t st);
 // short != 0: the short sequence's update.  The pass over X has left the loss differences of the first trial step in
 // its loss partials; every workgroup adds them up and takes the Armijo decision itself.  Accepted: margins z += alpha t
 // here, f from that difference.  Rejected: the solver is parked in kStatusBail and nothing is updated.
-void launch_update_logistic(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int loss_parts,
+void launch_update_logistic(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int first_parts,
                             int short_seq, hipStream_t st);
 void launch_clear_bail(const Buffers& bf, hipStream_t st);   // status kStatusBail -> RUNNING, bail_skipped -> 0
 

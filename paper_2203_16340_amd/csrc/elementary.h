@@ -63,6 +63,15 @@ LB_BOTH double log_and_rest(double u, double small) {
     return b + (b_rest + (a_rest + (tail - ff_rest)));
 }
 
+// a/z for z in [1, 2] and |a| <= 1: one Newton step on the reciprocal, then the quotient corrected by its own residue (off by at
+// most 0.51 units in the last place; without the scaling that a quotient of any two numbers needs, 6 instructions for 11)
+LB_BOTH double quotient_d(double a, double z) {
+    double y = reciprocal_seed(z);
+    y = __builtin_fma(__builtin_fma(-z, y, 1.0), y, y);
+    const double q = a * y;
+    return __builtin_fma(__builtin_fma(-z, q, a), y, q);
+}
+
 LB_BOTH double log_d(double x) {
     const double r = log_and_rest(x, 0.0);
     // (zero, infinite, negative or no number: -infinity, infinity, no number)

@@ -61,14 +61,15 @@ constexpr int gcd_i(int a, int b) { return b == 0 ? a : gcd_i(b, a % b); }
 // the target/label vector and of the stored margins, read ahead of time):
 //   psi  : the row's weight in the transposed product,
 //   loss : the row's contribution to the loss partial,
-//   keep : the value stored for the row (into t for the direction modes, into row for the evaluations).
+//   keep : the value stored for the row (into t for the direction modes, into row for the evaluations),
+//   q_new, sig_new (kRowLogiSpec): -y (z + alpha0 t) and its sigmoid.
 // LOGI selects the family at compile time: 0 = quadratic objectives, 1 = logistic (evaluation and
 // direction pass), 2 = logistic direction pass only, whose chain is short enough to leave registers for
 // a deeper ring (the transcendental code of the logistic modes would
 // otherwise cost the quadratic kernels registers they need for the ring).
 template <int LOGI>
 __device__ __forceinline__ void row_eval(int mode, double u, double b, double z, double alpha0, double invn,
-                                         double& psi, double& loss, double& keep) {
+                                         double& psi, double& loss, double& keep, double& q_new, double& sig_new) {
     if constexpr (LOGI == 0) {
         // z carries the row's weight here (1 when the objective has none); in the quadratic-form modes the
         // row's own entry of v (the row index is also a column index of the symmetric matrix)
@@ -86,7 +87,7 @@ __device__ __forceinline__ void row_eval(int mode, double u, double b, double z,
         if (LOGI == 1 && mode == kRowLogiEval) {   // margins z = X w; psi = -y sigma(-y z)/N
             const double q = -b * u;
             const double e = exp(-fabs(q));
-            psi = -b * ((q >= 0.0 ? 1.0 : e) / (1.0 + e)) * invn;
+            psi = -b * quotient_d(q >= 0.0 ? 1.0 : e, 1.0 + e) * invn;
             loss = (fmax(q, 0.0) + log1p_d(e)) * invn;
             keep = u;
         } else {                            // kRowLogiSpec: t = X p, and the weights of the FIRST trial step alpha0
@@ -95,7 +96,9 @@ __device__ __forceinline__ void row_eval(int mode, double u, double b, double z,
             // chain every stage waits for is one exponential and one division.
             const double q = -b * fma(alpha0, u, z);
             const double e = exp(-fabs(q));
-            psi = -b * ((q >= 0.0 ? 1.0 : e) / (1.0 + e)) * invn;
+            q_new = q;
+            sig_new = quotient_d(q >= 0.0 ? 1.0 : e, 1.0 + e);
+            psi = -b * sig_new * invn;
             loss = 0.0;
             keep = u;
         }
@@ -128,8 +131,8 @@ __device__ __forceinline__ void stage_row_op(const double* red, int lane, int wa
     }
     const int64_t grow = row0 + rl;
     const bool valid = lane < R && grow < r_end;
-    double psil, lossl, keep;
-    row_eval<LOGI>(mode, u, bl, zl, alpha0, invn, psil, lossl, keep);
+    double psil, lossl, keep, qn, sn;
+    row_eval<LOGI>(mode, u, bl, zl, alpha0, invn, psil, lossl, keep, qn, sn);
     if (!valid) { psil = 0.0; lossl = 0.0; }
     loss += lossl;
     if (valid && wave == 0) {

@@ -84,9 +84,12 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
         const int c = (k * L + j) * VEC;
         off[k] = (unsigned)g * ldb + (unsigned)(c < icols - VEC ? c : icols - VEC) * (unsigned)sizeof(T);
     }
-    const int64_t ntiles = (rows + RT - 1) / RT;
-    const int64_t stride = (int64_t)gridDim.x * kWaves;
-    int64_t tile = (int64_t)blockIdx.x * kWaves + wave;
+    // (row numbers are 32-bit, tiles past the last one included: the addresses of a tile's sets take half the scalar
+    // instructions that 64-bit rows did)
+    const int irows = (int)rows, last = irows - GR;          // (rows >= GR)
+    const int ntiles = (int)((rows + RT - 1) / RT);
+    const int stride = (int)gridDim.x * kWaves;
+    int tile = (int)blockIdx.x * kWaves + wave;
     RawT raw[S][KC];
     // No load is predicated (a refill under a test costs a second copy of the registers): a set that runs past the last
     // row reads the last GR rows instead, and its rows that belong to the set before it get weight zero.
@@ -94,11 +97,16 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
     // step would otherwise all read from the same few memory channels (0.4 GB of 1024 columns: fp64 70.4 -> 63.8 us a
     // pass, fp32 72.2 -> 65.5; 1000 columns 67.1 -> 64.4).
     const int rot = (int)(blockIdx.x * kWaves + wave) % S;
-    auto set_base = [&](int64_t r) -> int64_t { return r + GR <= rows ? r : rows - GR; };
-    auto fetch = [&](RawT (&dst)[KC], int64_t tl, int s) {
-        const char* rp = reinterpret_cast<const char*>(A + set_base(tl * RT + ((s + rot) % S) * GR) * ld);   // uniform
+    auto set_base = [&](int r) -> int { return r < last ? r : last; };
+    auto fetch = [&](RawT (&dst)[KC], int tl, int s) {
+        const unsigned r = (unsigned)set_base(tl * RT + ((s + rot) % S) * GR);
+        const char* rp = reinterpret_cast<const char*>(A) + (uint64_t)r * ldb;   // uniform
 #pragma unroll
-        for (int k = 0; k < KC; ++k) dst[k] = __builtin_nontemporal_load(reinterpret_cast<const MemT*>(rp + off[k]));
+        for (int k = 0; k < KC; ++k) {
+            unsigned o = off[k];
+            asm volatile("" : "+v"(o));                      // (opaque here: scalar base + 32-bit vector offset)
+            dst[k] = __builtin_nontemporal_load(reinterpret_cast<const MemT*>(rp + o));
+        }
     };
     // what the row operation reads, for the row whose sum this lane will hold
     const int mode = a.mode;
@@ -106,8 +114,8 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
     const bool need_z = LOGI == 2 || mode == kRowPsiGiven;
     const double* zsrc = LOGI == 2 ? row : psi_given;
     const int sl = (((lane % S) + rot) % S) * GR;                          // this lane's set: its first row within the tile
-    auto row_inputs = [&](int64_t tl, double& b, double& z) {
-        const int64_t r = set_base(tl * RT + sl) + g;
+    auto row_inputs = [&](int tl, double& b, double& z) {
+        const unsigned r = (unsigned)(set_base(tl * RT + sl) + g);
         b = need_b ? a.b[r] : 0.0;
         z = need_z ? zsrc[r] : (a.w ? a.w[r] : 1.0);
     };
@@ -125,7 +133,7 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
     }
     double bc = 0.0, zc = 1.0;
     {
-        const int64_t t0 = tile < ntiles ? tile : 0;
+        const int t0 = tile < ntiles ? tile : 0;
         row_inputs(t0, bc, zc);
 #pragma unroll
         for (int s = 0; s < S; ++s) fetch(raw[s], t0, s);
@@ -155,7 +163,9 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
     const double alpha0 = LOGI == 2 ? fmin(1.0, ps.alpha_ub) : 0.0;   // first trial step of the line search
     const double invn = 1.0 / (double)rows;
     double loss = 0.0;
-    double lq = 0.0, ldq = 0.0;                              // first trial step: rows whose loss difference is still to be taken
+    // first trial step: rows whose loss difference is still to be taken, by the new margin, whose sigmoid is at hand:
+    // softplus(q') - softplus(q' - dq)
+    double lq = 0.0, ls = 0.5, ldq = 0.0;
     int pending = 0;
 
     for (; tile < ntiles; tile += stride) {
@@ -185,18 +195,18 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
             }
         }
         const double u = row_sums<L, S>(acc, lane);
-        const int64_t r = set_base(tile * RT + sl) + g;
+        const int r = set_base(tile * RT + sl) + g;
         const bool valid = r >= tile * RT + sl;
         const bool mine = valid && (L == S || j < S);        // (rows longer than S lanes: copies of the sums in the others)
         // the wave's next tile; behind its last one the first tile of all, which every wave then reads: from cache
-        const int64_t tn = tile + stride < ntiles ? tile + stride : 0;
+        const int tn = tile + stride < ntiles ? tile + stride : 0;
         double bn, zn;
         row_inputs(tn, bn, zn);
-        double psi, lo, keep;
+        double psi, lo, keep, qn = 0.0, sn = 0.5;
         if (LOGI == 0 && mode == kRowPsiGiven) {
             psi = zc; lo = 0.0;
         } else {
-            ring::row_eval<LOGI>(mode, u, bc, zc, alpha0, invn, psi, lo, keep);
+            ring::row_eval<LOGI>(mode, u, bc, zc, alpha0, invn, psi, lo, keep, qn, sn);
             if (mine) {
                 if (mode == kRowDir || mode == kRowLogiSpec) t[r] = keep; else row[r] = keep;
                 loss += lo;
@@ -206,12 +216,13 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
         if (LOGI == 2 && a.ls_first) {
             // softplus(-y (z + alpha0 t)) - softplus(-y z) of the rows, for as many rows at a time as the wave has lanes
             if (L == S || j / S == pending) {
-                lq = valid ? -bc * zc : 0.0;              // (both zero: no contribution)
+                lq = valid ? qn : 0.0;                    // (no step: no contribution)
+                ls = valid ? sn : 0.5;
                 ldq = valid ? -bc * alpha0 * u : 0.0;
             }
             if (++pending == L / S) {
-                loss += softplus_diff(lq, sigmoid_d(lq), ldq);
-                pending = 0; lq = 0.0; ldq = 0.0;
+                loss -= softplus_diff(lq, ls, -ldq);
+                pending = 0; ldq = 0.0;
             }
         }
         bc = bn; zc = zn;
@@ -239,7 +250,7 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    if (LOGI == 2 && a.ls_first && pending > 0) loss += softplus_diff(lq, sigmoid_d(lq), ldq);
+    if (LOGI == 2 && a.ls_first && pending > 0) loss -= softplus_diff(lq, ls, -ldq);
 
     // w over the wave's groups of lanes, then over the waves in wave order
 #pragma unroll

@@ -59,8 +59,8 @@ bool narrow_shape_ok(const Dims& dm, int* variant, int* blocks) {
     *blocks = 0;
     const int vec = dm.dtype == LBFGSB_F32 ? 4 : 2;
     if (dm.kind == LBFGSB_OBJ_QP || is_transport(dm.kind) || dm.cols < vec) return false;
-    // byte offsets inside a set of rows are 32-bit
-    if (dm.ld > (int64_t)1 << 24) return false;
+    // byte offsets inside a set of rows are 32-bit, and so are the numbers of rows, those of a tile behind the last included
+    if (dm.ld > (int64_t)1 << 24 || dm.rows > 0x7fffff00) return false;
     const int64_t chunks = (dm.cols + vec - 1) / vec;
     for (int i = 0; i < kNumNarrow; ++i) {
         const NarrowVariant& v = kNarrow[i];

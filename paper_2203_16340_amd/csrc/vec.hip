@@ -868,19 +868,44 @@ void launch_extra_rows(const Dims& dm, const Buffers& bf, const double* rows, co
 // - softplus(-y_r z_r)] + mu (a <x,p> + a^2/2 <p,p>).  The bracket is evaluated in the cancellation-free
 // form log(1 + sigmoid(q) expm1(dq)), q = -y z, dq = -y a t (softplus_diff).  Step lengths are evaluated NTRY at a time per sweep
 // over the rows: the first launch tries the first one alone (it is accepted in almost every quasi-Newton
-// iteration; the short launch sequence has the pass over X form that sum itself and the update kernel decide,
-// see k_update_logistic), a second launch, which returns at once when the first found the step, tries the next kLsBatch, and
+// iteration; where the pass over X has formed that sum itself -- first_parts > 0 loss partials -- there is no such launch: the
+// short launch sequence has the update kernel decide, see k_update_logistic, the full one this kernel, every workgroup for
+// itself), a second launch, which returns at once when the first found the step, tries the next kLsBatch, and
 // if none of them is acceptable its last workgroup goes on alone, one length at a time.
+
+// Change of f at the first trial step a, from the loss differences the pass over X has summed (every workgroup the same bits).
+__device__ __forceinline__ double first_step_difference(const Dims& dm, const Scal* scal, const double* __restrict__ losspart,
+                                                        int parts, double a, double* lds) {
+    const double xp = scal->xp, pp = scal->pp;
+    return sum_all(losspart, parts, lds) / (double)dm.rows + dm.mu * a * (xp + 0.5 * a * pp);
+}
+
 template <int NTRY>
-__global__ __launch_bounds__(kBlock) void k_ls_logistic(Dims dm, Opts op, int first, int last_resort, int spec,
+__global__ __launch_bounds__(kBlock) void k_ls_logistic(Dims dm, Opts op, int first, int last_resort, int spec, int first_parts,
+                                                        const double* __restrict__ losspart,
                                                         const double* __restrict__ yl, const double* __restrict__ z,
                                                         const double* __restrict__ t, Scal* __restrict__ scal,
                                                         double* __restrict__ lspart) {
     __shared__ double red[kWaves * NTRY];
     __shared__ int flag;
     if (scal->status != LBFGSB_RUNNING) return;
-    if (first > 0 && scal->ls_ok) return;            // an earlier launch of this iteration found the step
     const int tid = threadIdx.x;
+    if (first_parts > 0) {
+        const double a = fmin(1.0, scal->alpha_ub);
+        const double df = first_step_difference(dm, scal, losspart, first_parts, a, red);
+        if (isfinite(df) && df <= op.c1 * a * scal->gp) {
+            if (blockIdx.x == 0 && tid == 0) {
+                scal->ls_ok = 1;
+                scal->spec_ok = 1;
+                scal->backtracks = 0;
+                scal->fevals += 1;
+                scal->alpha = a;
+            }
+            return;
+        }
+    } else if (first > 0 && scal->ls_ok) {
+        return;                                      // an earlier launch of this iteration found the step
+    }
     double al[NTRY], s[NTRY];
     {
         double a = fmin(1.0, scal->alpha_ub);
@@ -948,7 +973,7 @@ __global__ __launch_bounds__(kBlock) void k_ls_logistic(Dims dm, Opts op, int fi
     }
     if (tid == 0) {
         scal->ls_ok = found >= 0;
-        if (first == 0) scal->spec_ok = spec && found == 0;
+        if (first == 0 || first_parts > 0) scal->spec_ok = spec && found == 0;
         if (found >= 0 || last_resort) {
             scal->backtracks = found >= 0 ? found : op.max_backtracks + 1;
             scal->fevals += found >= 0 ? found + 1 : op.max_backtracks + 1;
@@ -958,21 +983,23 @@ __global__ __launch_bounds__(kBlock) void k_ls_logistic(Dims dm, Opts op, int fi
 }
 
 void launch_ls_logistic(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const double* labels,
-                        int spec, int stages, hipStream_t st) {
+                        int spec, int stages, int first_parts, hipStream_t st) {
     if (stages & 1)
-        hipLaunchKernelGGL(k_ls_logistic<1>, dim3(ge.ls_blocks), dim3(kBlock), 0, st, dm, op, 0, 0, spec, labels, (const double*)bf.row, (const double*)bf.t, bf.scal, bf.lspart);
+        hipLaunchKernelGGL(k_ls_logistic<1>, dim3(ge.ls_blocks), dim3(kBlock), 0, st, dm, op, 0, 0, spec, 0, (const double*)bf.losspart,
+                           labels, (const double*)bf.row, (const double*)bf.t, bf.scal, bf.lspart);
     if (stages & 2)
-        hipLaunchKernelGGL(k_ls_logistic<kLsBatch>, dim3(ge.ls_blocks), dim3(kBlock), 0, st, dm, op, 1, 1, spec, labels,
-                           (const double*)bf.row, (const double*)bf.t, bf.scal, bf.lspart);
+        hipLaunchKernelGGL(k_ls_logistic<kLsBatch>, dim3(ge.ls_blocks), dim3(kBlock), 0, st, dm, op, 1, 1, spec, first_parts,
+                           (const double*)bf.losspart, labels, (const double*)bf.row, (const double*)bf.t, bf.scal, bf.lspart);
 }
 
 // z += alpha t; psi = -y sigma(-y z)/N; loss partials of the new point (from the new margins).
-__global__ __launch_bounds__(kBlock) void k_rows_logistic(Dims dm, const double* __restrict__ yl,
+// not_first: the update kernel does what is left of this when the first trial step was accepted.
+__global__ __launch_bounds__(kBlock) void k_rows_logistic(Dims dm, int not_first, const double* __restrict__ yl,
                                                           const double* __restrict__ t, double* __restrict__ z,
                                                           double* __restrict__ psi, const Scal* __restrict__ scal,
                                                           double* __restrict__ losspart) {
     __shared__ double red[kWaves];
-    if (scal->status != LBFGSB_RUNNING || !scal->ls_ok) return;
+    if (scal->status != LBFGSB_RUNNING || !scal->ls_ok || (not_first && scal->spec_ok)) return;
     const double alpha = scal->alpha;
     const double invn = 1.0 / (double)dm.rows;
     double s[1] = {0.0};
@@ -988,8 +1015,9 @@ __global__ __launch_bounds__(kBlock) void k_rows_logistic(Dims dm, const double*
     if (threadIdx.x == 0) losspart[blockIdx.x] = s[0];
 }
 
-void launch_rows_logistic(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* labels, hipStream_t st) {
-    hipLaunchKernelGGL(k_rows_logistic, dim3(ge.lrows_blocks), dim3(kBlock), 0, st, dm, labels, bf.t, bf.row, bf.psi, bf.scal,
+void launch_rows_logistic(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* labels, int not_first,
+                          hipStream_t st) {
+    hipLaunchKernelGGL(k_rows_logistic, dim3(ge.lrows_blocks), dim3(kBlock), 0, st, dm, not_first, labels, bf.t, bf.row, bf.psi, bf.scal,
                        bf.losspart);
 }
 
@@ -998,9 +1026,11 @@ void launch_rows_logistic(const Dims& dm, const Geometry& ge, const Buffers& bf,
 // softplus(-y (z + a0 t)) - softplus(-y z) for the first trial step a0 = min(1, alpha_ub).  Every workgroup adds
 // them in the same order and takes the same Armijo decision; an accepted step is applied here (the margins move
 // too), a rejected one parks the solver (kStatusBail) with nothing changed and no arrival counted.
+// first_parts > 0 without short_seq: the search kernel has decided from those partials; what it accepted of them is applied
+// the same way, with the loss from the same sum, any other step from the recomputed margins.
 __global__ __launch_bounds__(kBlock) void k_update_logistic(Dims dm, double c1, int w_parts_two_pass, int w_parts_spec,
-                                                            int loss_parts, int short_seq, const double* __restrict__ t,
-                                                            double* __restrict__ z, const double* __restrict__ wpart,
+                                                            int loss_parts, int first_parts, int short_seq,
+                                                            const double* __restrict__ t, double* __restrict__ z, const double* __restrict__ wpart,
                                                             const double* __restrict__ losspart,
                                                             const double* __restrict__ p1, const double* __restrict__ p2,
                                                             const double* __restrict__ l, const double* __restrict__ u,
@@ -1018,12 +1048,12 @@ __global__ __launch_bounds__(kBlock) void k_update_logistic(Dims dm, double c1, 
     const double* p = scal->branch == 1 ? p1 : p2;
     int w_parts = scal->spec_ok ? w_parts_spec : w_parts_two_pass;   // which kernel wrote the partial columns
     double df = 0.0, f_old = 0.0;
-    if (short_seq) {
-        const double gp = scal->gp, xp = scal->xp, pp = scal->pp;
+    const bool first_step = short_seq || (first_parts > 0 && ok && scal->spec_ok);
+    if (first_step) {
         f_old = scal->f;
         alpha = fmin(1.0, scal->alpha_ub);
-        df = sum_all(losspart, loss_parts, red) / (double)dm.rows + dm.mu * alpha * (xp + 0.5 * alpha * pp);
-        ok = isfinite(df) && df <= c1 * alpha * gp;
+        df = first_step_difference(dm, scal, losspart, first_parts, alpha, red);
+        ok = !short_seq || (isfinite(df) && df <= c1 * alpha * scal->gp);
         w_parts = w_parts_spec;
         if (!ok) {
             // (a workgroup that starts after this store finds the solver parked and returns at once: same outcome)
@@ -1036,13 +1066,13 @@ __global__ __launch_bounds__(kBlock) void k_update_logistic(Dims dm, double c1, 
         }
     }
     double sums[2] = {0.0, 0.0};   // ||y||^2, ||x+||^2
-    // short sequence: the first `col_blocks` workgroups take the columns, the others the margins (side by side, not
+    // first trial step: the first `col_blocks` workgroups take the columns, the others the margins (side by side, not
     // one after the other: a workgroup's trips to memory are dependent and nothing else runs on its compute unit);
     // a grid of one workgroup does both
     int col_first = 0, col_stride = (int)gridDim.x;
-    if (ok && short_seq) {
-        // the margins of the new point (the full sequence has a kernel for this, which also recomputes the row weights:
-        // here the single-read pass already holds X^T psi of this step)
+    if (ok && first_step) {
+        // the margins of the new point (for any other step a kernel before this one, which also recomputes the row weights:
+        // the single-read pass already holds X^T psi of this step)
         const int want = (int)((dm.cols + kCX - 1) / kCX);
         const int col_blocks = want < (int)gridDim.x / 2 ? want : (int)gridDim.x / 2;
         int rb = (int)blockIdx.x, nrb = (int)gridDim.x;
@@ -1091,7 +1121,7 @@ __global__ __launch_bounds__(kBlock) void k_update_logistic(Dims dm, double c1, 
             }
         }
     }
-    if (short_seq) {
+    if (first_step) {
         // Nothing is left to add up: f moves by the line search's difference, and the new pair's ||y||^2 comes from
         // the next free-set pass (as for the quadratic kinds).  No workgroup of this kernel reads the pend_* fields,
         // so one thread may write them while others are still running; the next Gram kernel (or k_commit) turns
@@ -1131,10 +1161,10 @@ __global__ __launch_bounds__(kBlock) void k_update_logistic(Dims dm, double c1, 
     }
 }
 
-void launch_update_logistic(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int loss_parts,
+void launch_update_logistic(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int first_parts,
                             int short_seq, hipStream_t st) {
-    hipLaunchKernelGGL(k_update_logistic, dim3(short_seq ? ge.updl_blocks : ge.upd_blocks), dim3(kBlock), 0, st, dm, op.c1, ge.redo_parts,
-                       ge.fused_blocks, loss_parts, short_seq, (const double*)bf.t, bf.row, bf.wpart,
+    hipLaunchKernelGGL(k_update_logistic, dim3(first_parts > 0 ? ge.updl_blocks : ge.upd_blocks), dim3(kBlock), 0, st, dm, op.c1,
+                       ge.redo_parts, ge.fused_blocks, ge.lrows_blocks, first_parts, short_seq, (const double*)bf.t, bf.row, bf.wpart,
                        bf.losspart, bf.p1, bf.p2, bf.l, bf.u, bf.x, bf.g, bf.S, bf.Y, bf.scal, bf.redpart);
 }
 

@@ -1,5 +1,6 @@
-// log_d and log1p_d of the kernels, compiled for the host (the seed of the reciprocal has 24 bits here, no more than the
+// log_d, log1p_d and quotient_d of the kernels, compiled for the host (the seed of the reciprocal has 24 bits here, no more than the
 // device's), against long double.  Prints the largest error in units of the last place per range, then the special values.
+#include <algorithm>
 #include <cstdio>
 #include <random>
 
@@ -27,6 +28,12 @@ int main() {
         }
         std::printf("range %s %g %g %.6f\n", r.plus_one ? "log1p" : "log", r.lo, r.hi, worst);
     }
+    double worst = 0.0;
+    for (int i = 0; i < 400000; ++i) {
+        const double e = std::exp(-700.0 * unit(gen) * unit(gen)), z = 1.0 + e, a = i & 1 ? 1.0 : e;
+        worst = std::max(worst, ulps(lb::quotient_d(a, z), (long double)a / (long double)z));
+    }
+    std::printf("quotient %.6f\n", worst);
     const double special[] = {0.0, INFINITY, -INFINITY, NAN, -1.0, -2.0, 1.0, 5e-324, 1.7976931348623157e308};
     for (double x : special) std::printf("at %.17g %.17g %.17g %.17g %.17g\n", x, lb::log_d(x), std::log(x), lb::log1p_d(x), std::log1p(x));
     return 0;

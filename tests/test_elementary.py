@@ -25,6 +25,11 @@ def test_errors(output):
         assert float(worst) <= 0.7, (name, lo, hi, worst)
 
 
+def test_quotient(output):
+    """Half a unit from the final rounding; the residue's correction leaves 2^-48 of the seed's error to the square."""
+    assert float([line.split()[1] for line in output if line.startswith("quotient")][0]) <= 0.51
+
+
 def test_special_values(output):
     lines = [[float(t) for t in line.split()[1:]] for line in output if line.startswith("at")]
     assert len(lines) == 9

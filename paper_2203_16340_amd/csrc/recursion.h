@@ -22,8 +22,51 @@ __device__ __forceinline__ double prefetch_ynorm2(const Scal* __restrict__ scal,
 
 constexpr int kRecFast = 10;   // up to this many pairs the recursion keeps its rows of G in registers
 
-// The recursion of Algorithm 3 on coefficients, by one wave (threads 0..63) of the calling workgroup.  G: Vp x Vp (LDS),
-// row-major, vectors ordered s^0..s^{c-1}, y^0..y^{c-1}, g.  gg = sum g[S]^2, pginf = max KKT residual, nfixed = #fixed,
+// The recursion for at most K pairs.  Every entry of G a lane needs is fetched at once; the three loops then run on registers
+// and scalar-register broadcasts only.  Row i is scaled by 1/rho_i beforehand, and is zero where it has no say (pairs that fail
+// the gate; in the first loop pairs older than k, in the second newer ones), so a step of the chain is one broadcast and one
+// multiply-add, and a lane's value stays what it was at its own step.  All K steps are taken whatever c is, and the lanes past
+// the last pair read the last pair's rows: alpha is zero there, which makes the surplus steps add nothing, while a test per
+// step or load cost a branch each (a step took 130 cycles and not 25).
+template <int K>
+__device__ __forceinline__ void recursion_in_registers(const double* G, int Vp, int c, int i, int ic, bool pass,
+                                                       unsigned long long pm, double inv, double rho_yn, double& alpha_i,
+                                                       double& coef_s, double& gamma) {
+    double gsy[K], gyy[K], gys[K];
+    const double *srow = G + ic * Vp, *yrow = G + (c + ic) * Vp;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int kc = k < c ? k : (c > 0 ? c - 1 : 0);       // (uniform)
+        gsy[k] = srow[c + kc];                                // <s_i, y_k>
+        gyy[k] = yrow[c + kc];                                // <y_i, y_k>
+        gys[k] = yrow[kc];                                    // <y_i, s_k>
+    }
+    const double sg = srow[2 * c];                            // <s_i, g>
+    double tsum = yrow[2 * c], tsum2 = 0.0;                   // <y_i, g>
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        gsy[k] = pass && k > i ? gsy[k] * inv : 0.0;
+        gys[k] = pass && k < i ? gys[k] * inv : 0.0;
+    }
+    double alpha = pass ? sg * inv : 0.0;
+#pragma unroll
+    for (int k = K - 1; k >= 0; --k) alpha = fma(-lane_value(alpha, k), gsy[k], alpha);
+    if (c > 0 && ((pm >> (c - 1)) & 1ull)) gamma = lane_value(rho_yn, c - 1);
+#pragma unroll
+    for (int k = 0; k < K; k += 2) {
+        tsum = fma(-lane_value(alpha, k), gyy[k], tsum);
+        if (k + 1 < K) tsum2 = fma(-lane_value(alpha, k + 1), gyy[k + 1], tsum2);
+    }
+    double coef = pass ? alpha - gamma * (tsum + tsum2) * inv : 0.0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) coef = fma(-lane_value(coef, k), gys[k], coef);
+    alpha_i = alpha;
+    coef_s = coef;
+}
+
+// The recursion of Algorithm 3 on coefficients, by one wave (threads 0..63) of the calling workgroup, and the stopping test by
+// another (which reads and writes other fields of the scalar block): called by all threads, at least 128, with a barrier before
+// anybody reads either's results.  G: Vp x Vp (LDS), row-major, vectors ordered s^0..s^{c-1}, y^0..y^{c-1}, g.  gg = sum g[S]^2, pginf = max KKT residual, nfixed = #fixed,
 // ynew = ||y_new||^2 (full vector), yn_old = prefetch_ynorm2().
 __device__ __forceinline__ void recursion_on_coefficients(const double* G, int Vp, int c, int head, int m, const Opts& op,
                                                           Scal* __restrict__ scal, double gg, double pginf, double nfixed,
@@ -35,63 +78,22 @@ __device__ __forceinline__ void recursion_on_coefficients(const double* G, int V
         // (the same in every lane: from here on in a scalar register, so that the loops below are branches and not masks)
         c = __builtin_amdgcn_readfirstlane(c);
         Vp = __builtin_amdgcn_readfirstlane(Vp);
-        const double pgn = sqrt(gg);
-        // what the stopping test at the end reads from the scalar block, requested now: behind the recursion these
-        // were three dependent trips (each read sits under a test of the one before)
-        int tol_resolved = 1, status0 = LBFGSB_RUNNING;
-        double tol_abs0 = 0.0;
-        long long iters0 = 0;
-        if (lane == 0 && evaluate_stop) {
-            tol_resolved = scal->tol_resolved; status0 = scal->status; tol_abs0 = scal->tol_abs; iters0 = scal->iters;
-        }
-        double rho = 1.0, yn = 1.0, inv = 0.0;
-        bool pass = false;
-        if (i < c) {
-            rho = G[i * Vp + (c + i)];
+        // lanes past the last pair work on the last pair's rows and are left out by `pass`: no access is predicated
+        const int ic = i < c ? i : (c > 0 ? c - 1 : 0);
+        double rho = 1.0, yn = 1.0;
+        if (c > 0) {
+            rho = G[ic * Vp + (c + ic)];
             // the newest pair's norm was just summed (and stored for later iterations)
             yn = (i == c - 1 && !dbg_inputs) ? ynew : yn_old;
-            pass = rho > op.eps * yn;
-            inv = 1.0 / rho;
         }
+        const bool pass = i < c && rho > op.eps * yn;
+        const double inv = 1.0 / rho, rho_yn = rho / yn;
         const unsigned long long pm = __ballot(pass);
         double alpha_i = 0.0, coef_s = 0.0, gamma = 1.0;
-        if (c <= kRecFast) {
-            // Every entry of G this lane needs, fetched at once; the three loops then run on registers and
-            // scalar-register broadcasts only.  Row i is scaled by 1/rho_i beforehand, and is zero where it has no say
-            // (pairs that fail the gate; in the first loop pairs older than k, in the second newer ones), so a step of
-            // the chain is one broadcast and one multiply-add, and a lane's value stays what it was at its own step.
-            double gsy[kRecFast], gyy[kRecFast], gys[kRecFast];
-#pragma unroll
-            for (int k = 0; k < kRecFast; ++k) {
-                const bool in = i < c && k < c;
-                gsy[k] = in ? G[i * Vp + (c + k)] : 0.0;          // <s_i, y_k>
-                gyy[k] = in ? G[(c + i) * Vp + (c + k)] : 0.0;    // <y_i, y_k>
-                gys[k] = in ? G[(c + i) * Vp + k] : 0.0;          // <y_i, s_k>
-            }
-            const double sg = i < c ? G[i * Vp + 2 * c] : 0.0;         // <s_i, g>
-            double tsum = i < c ? G[(c + i) * Vp + 2 * c] : 0.0;       // <y_i, g>
-#pragma unroll
-            for (int k = 0; k < kRecFast; ++k) {
-                gsy[k] = pass && k > i ? gsy[k] * inv : 0.0;
-                gys[k] = pass && k < i ? gys[k] * inv : 0.0;
-            }
-            alpha_i = pass ? sg * inv : 0.0;
-#pragma unroll
-            for (int k = kRecFast - 1; k >= 0; --k)
-                if (k < c) alpha_i = fma(-lane_value(alpha_i, k), gsy[k], alpha_i);
-            if (c > 0 && ((pm >> (c - 1)) & 1ull)) gamma = lane_value(rho / yn, c - 1);
-            double tsum2 = 0.0;
-#pragma unroll
-            for (int k = 0; k < kRecFast; k += 2) {
-                if (k < c) {
-                    tsum = fma(-lane_value(alpha_i, k), gyy[k], tsum);
-                    tsum2 = fma(-lane_value(alpha_i, k + 1), gyy[k + 1], tsum2);   // (zero past the last pair)
-                }
-            }
-            coef_s = pass ? alpha_i - gamma * (tsum + tsum2) * inv : 0.0;
-#pragma unroll
-            for (int k = 0; k < kRecFast; ++k)
-                if (k < c) coef_s = fma(-lane_value(coef_s, k), gys[k], coef_s);
+        if (c <= kRecFast / 2) {
+            recursion_in_registers<kRecFast / 2>(G, Vp, c, i, ic, pass, pm, inv, rho_yn, alpha_i, coef_s, gamma);
+        } else if (c <= kRecFast) {
+            recursion_in_registers<kRecFast>(G, Vp, c, i, ic, pass, pm, inv, rho_yn, alpha_i, coef_s, gamma);
         } else {
             // first loop: alpha_k, newest to oldest.  Steps of pairs that fail the gate run with alpha_k = 0;
             // a lane's row is dead once its own alpha has been taken, so updating it further is harmless.
@@ -105,7 +107,7 @@ __device__ __forceinline__ void recursion_on_coefficients(const double* G, int V
                 part_s = fma(-ak, gsy, part_s);
             }
             if (i < c) alpha_s[i] = alpha_i;
-            if (c > 0 && ((pm >> (c - 1)) & 1ull)) gamma = lane_value(rho / yn, c - 1);
+            if (c > 0 && ((pm >> (c - 1)) & 1ull)) gamma = lane_value(rho_yn, c - 1);
             // <y_i, gamma (g - sum_k alpha_k y_k)>
             double by = 0.0;
             {
@@ -134,20 +136,24 @@ __device__ __forceinline__ void recursion_on_coefficients(const double* G, int V
         if (lane == 0) {
             scal->delta[2 * c] = gamma;
             scal->pairs_used = __popcll(pm);
-            if (evaluate_stop) {
-                scal->pg2 = pgn;
-                scal->pginf = pginf;
-                scal->n_fixed = (long long)nfixed;
-                if (!tol_resolved) {
-                    tol_abs0 = op.tol_relative ? op.tol * fmax(1.0, pgn) : op.tol;
-                    scal->tol_abs = tol_abs0;
-                    scal->tol_resolved = 1;
-                }
-                if (status0 == LBFGSB_RUNNING) {
-                    if (pgn <= tol_abs0) scal->status = LBFGSB_CONVERGED;
-                    else if (iters0 >= op.max_iter) scal->status = LBFGSB_MAX_ITER;
-                }
-            }
+        }
+    } else if (tid == 64 && evaluate_stop) {
+        // the stopping test, by the second wave meanwhile
+        const int status = scal->status;
+        const long long iters = scal->iters;
+        const double pgn = sqrt(gg);
+        double tol_abs = scal->tol_abs;
+        scal->pg2 = pgn;
+        scal->pginf = pginf;
+        scal->n_fixed = (long long)nfixed;
+        if (!scal->tol_resolved) {
+            tol_abs = op.tol_relative ? op.tol * fmax(1.0, pgn) : op.tol;
+            scal->tol_abs = tol_abs;
+            scal->tol_resolved = 1;
+        }
+        if (status == LBFGSB_RUNNING) {
+            if (pgn <= tol_abs) scal->status = LBFGSB_CONVERGED;
+            else if (iters >= op.max_iter) scal->status = LBFGSB_MAX_ITER;
         }
     }
 }

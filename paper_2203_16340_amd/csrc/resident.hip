@@ -29,6 +29,7 @@ constexpr int kResThreads = 512;                // 8 waves, two per SIMD: 256 re
 constexpr int kResWaves = kResThreads / 64;
 constexpr int kResGroups = kResThreads / 16;    // 16-lane groups, each owning whole rows of the matrix
 constexpr size_t kResLdsLimit = 150 * 1024;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 struct ResArgs {
     Dims dm;
@@ -47,20 +48,22 @@ struct ResArgs {
 
 // LDS layout in doubles
 struct ResLayout {
-    int x, g, l, u, p1, p2, msk, w, S, Y, G, wred, red, alpha, total;
+    int x, g, l, u, p1, p2, msk, zero, S, Y, G, wred, red, alpha, total;
 };
-// every n-vector has npad = n rounded up to 16 entries, the padding kept at zero, so that loops over elements in
-// steps of 16 need no bounds checks
+// every n-vector has n rounded up to 16 entries, the padding kept at zero, so that loops over elements in steps of 16 need no
+// bounds checks, and two more, so that 16 lanes that read 16 bytes each of 16 vectors touch every bank once
 __host__ __device__ inline int res_npad(int n) { return (n + 15) & ~15; }
+constexpr int kResSkew = 2;
+__host__ __device__ inline int res_vectors(int m) { return 8 + 2 * m; }
 __host__ __device__ inline ResLayout res_layout(int n, int m, int cpad) {
     ResLayout L;
-    const int np = res_npad(n);
+    const int np = res_npad(n) + kResSkew;
     int off = 0;
     auto take = [&](int k) { int o = off; off += (k + 1) & ~1; return o; };
-    L.x = take(np); L.g = take(np); L.l = take(np); L.u = take(np); L.p1 = take(np); L.p2 = take(np); L.msk = take(np); L.w = take(np);
+    L.x = take(np); L.g = take(np); L.l = take(np); L.u = take(np); L.p1 = take(np); L.p2 = take(np); L.msk = take(np); L.zero = take(np);
     L.S = take(m * np); L.Y = take(m * np);
     L.G = take((2 * m + 2) * (2 * m + 2));
-    L.wred = take(kResGroups * cpad);
+    L.wred = take(kResGroups * cpad);   // (the Gram matrix's blocks as well: at least 64 columns, so at least a block per wave)
     L.red = take(96);               // per-phase exchange areas of the waves' partial results
     L.alpha = take(kMaxM + 1);
     L.total = off;
@@ -73,7 +76,12 @@ __host__ __device__ inline ResLayout res_layout(int n, int m, int cpad) {
 // What bounds an iteration here is the latency of dependent steps (an LDS access or a shuffle is ~130 cycles when
 // the next instruction waits for it), so: thread i owns element i of every n-vector (n <= 512 = threads) and keeps
 // x_i, g_i, l_i, u_i in registers; sums over a wave use the lane permutations of wave_sum; LDS loads that feed a
-// chain are issued in groups before they are used; reductions over the workgroup that can share a barrier do.
+// chain are issued in groups before they are used; reductions over the workgroup that can share a barrier do.  And of
+// branches: one that is taken empties the wave's instruction buffer, and one in an unrolled loop keeps its chains from
+// interleaving, so loops run to a fixed count on clamped indexes, what must not count has a coefficient of zero, and the
+// bookkeeping of an iteration is done by a wave that owns no elements.  200 x 100, m = 5, thousands of cycles per iteration,
+// with tests in the loops / without: free set 1.3 / 2.4 (the bookkeeping overlaps it), Gram matrix 4.4 / 2.5 (matrix cores),
+// recursion 4.6 / 2.3, direction 4.8 / 3.9, pass 4.3 / 4.0, update 2.6 / 1.2: 9.6 -> 7.2 us, whole solve 533 -> 407 us.
 template <int CPL, int RG>
 __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
     extern __shared__ __align__(16) double lds[];
@@ -81,7 +89,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int grp = tid >> 4, gj = tid & 15;    // this lane's group and its place in it
     const int n = (int)a.dm.cols, rows = (int)a.dm.rows, m = a.dm.m;
-    const int np = res_npad(n);
+    const int np = res_npad(n) + kResSkew;      // from one vector to the next
     const int64_t ld = a.dm.ld;
     const ResLayout L = res_layout(n, m, CPL * 16);
     double *gs = lds + L.g, *p1s = lds + L.p1, *p2s = lds + L.p2, *xs = lds + L.x;
@@ -139,7 +147,6 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
     // g = A^T r: the periodic recomputation, and the one before convergence is declared), or the pass of an iteration.
     int steps = 0;
     bool want_eval = false;
-    int first_V = -1, first_ra = 0, first_rb = 0;   // this thread's first entry of the Gram matrix, for first_V vectors
     for (;;) {
         if (!want_eval && steps >= a.max_steps) break;
         if (!want_eval && a.refresh_every > 0 && since >= a.refresh_every) want_eval = true;
@@ -148,14 +155,16 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
         c = __builtin_amdgcn_readfirstlane(c);
         head = __builtin_amdgcn_readfirstlane(head);
         since = __builtin_amdgcn_readfirstlane(since);
-        const int V = 2 * c + 1, Vp = V + 1;
+        const int Vp = 2 * c + 2;
         const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;
-        auto vec = [&](int j) __attribute__((always_inline)) -> const double* {
-            if (j >= 2 * c) return gs;
-            const bool is_y = j >= c;
-            int sl = base_slot + (is_y ? j - c : j);
-            if (sl >= m) sl -= m;
-            return (is_y ? Ys : Ss) + sl * np;
+        auto slot_vec = [&](int j) __attribute__((always_inline)) -> const double* {
+            return lds + (j < m ? L.Y + j * np : (j == m ? L.g : (j <= 2 * m ? L.S + (j - m - 1) * np : L.zero)));
+        };
+        // static slot -> place in the recursion's order s^0..s^{c-1}, y^0..y^{c-1}, g (oldest first), -1: holds no pair
+        auto logical = [&](int j) __attribute__((always_inline)) -> int {
+            const int ring = j < m ? j : j - m - 1;
+            const int k = ring >= base_slot ? ring - base_slot : ring - base_slot + m;
+            return j == m ? 2 * c : (j > 2 * m || k >= c ? -1 : (j < m ? c + k : k));
         };
         double s6[6] = {0, 0, 0, 0, 0, 0};
         double gp = 0.0, alpha_ub = 1.0, pa = 0.0, pb = 0.0;
@@ -168,50 +177,57 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                 const bool fr = !(((xi <= li + op.eps) && (gi >= 0.0)) || ((xi >= ui - op.eps) && (gi <= 0.0)));
                 mi = (act && fr) ? 1.0 : 0.0;
                 if (act) msk[tid] = mi;
-                const double nf = wave_sum((act && !fr) ? 1.0 : 0.0);
+                const double nf = (double)__popcll(__ballot(act && !fr));
                 const double pg = wave_max(act ? fabs(xi - clampd(xi - gi, li, ui)) : 0.0);
                 if (lane == 0) { redA[wave] = nf; redA[kResWaves + wave] = pg; }
             }
             __syncthreads();                        // msk and the waves' partial statistics are in LDS
 
-            // ---- masked Gram matrix of [s^0 .. s^{c-1}, y^0 .. y^{c-1}, g]: four lanes per entry, each taking every
-            // fourth element; the loads of four elements are issued before their products
-            {
-                const int E = V * (V + 1) / 2;
-                const int eg = tid >> 2, sub = tid & 3;
-                for (int e0 = 0; e0 < E; e0 += kResThreads / 4) {
-                    const int e = e0 + eg;
-                    int ra = 0, rb = 0;
-                    double s = 0.0;
-                    if (e < E) {
-                        if (e0 > 0 || V != first_V) {        // (which entry this is changes with the number of pairs only)
-                            int q = e;
-                            while (q >= V - ra) { q -= V - ra; ++ra; }
-                            rb = ra + q;
-                            if (e0 == 0) { first_ra = ra; first_rb = rb; }
-                        } else {
-                            ra = first_ra; rb = first_rb;
+            // ---- masked Gram matrix on the matrix cores, as in k_gram: static slots y ring | g | s ring in blocks of 16, a
+            // wave per 16 elements (four steps of 4), the waves' blocks added in wave order.  Products of two blocks of s
+            // vectors are not read.  (Four lanes per entry, every operand from LDS for itself: 1.9 us; this: 0.8.)
+            for (int ba = 0; 16 * ba <= m; ++ba) {
+                for (int bb = ba; 16 * bb <= 2 * m; ++bb) {
+                    const double *oa = slot_vec(16 * ba + gj) + 2 * (lane >> 4), *ob = slot_vec(16 * bb + gj) + 2 * (lane >> 4);
+                    const double* om = msk + 2 * (lane >> 4);
+                    f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
+                    for (int e0 = 16 * wave; e0 < n; e0 += 16 * kResWaves) {
+                        double2 va[2], vb[2], vm[2];
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            va[h] = *reinterpret_cast<const double2*>(oa + e0 + 8 * h);
+                            vb[h] = *reinterpret_cast<const double2*>(ob + e0 + 8 * h);
+                            vm[h] = *reinterpret_cast<const double2*>(om + e0 + 8 * h);
                         }
-                        const double *va = vec(ra) + sub, *vb = vec(rb) + sub, *vm = msk + sub;
-                        for (int i0 = 0; i0 < np; i0 += 16) {
-                            double mv[4], av[4], bv[4];
 #pragma unroll
-                            for (int k = 0; k < 4; ++k) { mv[k] = vm[i0 + 4 * k]; av[k] = va[i0 + 4 * k]; bv[k] = vb[i0 + 4 * k]; }
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) s = fma(mv[k] * av[k], bv[k], s);
+                        for (int h = 0; h < 2; ++h) {
+                            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(vm[h].x * va[h].x, vb[h].x, acc, 0, 0, 0);
+                            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(vm[h].y * va[h].y, vb[h].y, acc, 0, 0, 0);
                         }
                     }
-                    s += dpp_move<kDppXor1>(s);
-                    s += dpp_move<kDppXor2>(s);
-                    if (e < E && sub == 0) { G[ra * Vp + rb] = s; G[rb * Vp + ra] = s; }
+                    if (ba + bb > 0) __syncthreads();           // the blocks before these have been added
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) wred[wave * 256 + r * 64 + lane] = acc[r];
+                    __syncthreads();
+                    if (tid < 256) {
+                        const int row = logical(16 * ba + ((tid & 63) >> 4) + 4 * (tid >> 6)), col = logical(16 * bb + (tid & 15));
+                        double t = wred[tid];
+#pragma unroll
+                        for (int w = 1; w < kResWaves; ++w) t += wred[w * 256 + tid];
+                        if (row >= 0 && col >= 0) {
+                            G[row * Vp + col] = t;
+                            if (ba != bb) G[col * Vp + row] = t;   // (a block with itself holds both)
+                        }
+                    }
                 }
             }
-            first_V = V;
             __syncthreads();
-            // ---- Algorithm 3 on coefficients (wave 0), the stopping test with it
-            if (tid < 64) {
+            // ---- Algorithm 3 on coefficients (first wave) and the stopping test (second)
+            if (tid < 128) {
                 double nfix = 0.0, pginf = 0.0;
-                for (int w = 0; w < nw; ++w) { nfix += redA[w]; pginf = fmax(pginf, redA[kResWaves + w]); }
+                if (tid == 64) {
+                    for (int w = 0; w < nw; ++w) { nfix += redA[w]; pginf = fmax(pginf, redA[kResWaves + w]); }
+                }
                 const double ynew = c > 0 ? sc.ynorm2[(head - 1 + m) % m] : 0.0;
                 const double yn_old = prefetch_ynorm2(&sc, c, head, m);
                 recursion_on_coefficients(G, Vp, c, head, m, op, &sc, G[(2 * c) * Vp + 2 * c], pginf, nfix, ynew, yn_old,
@@ -232,22 +248,28 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
 
             // ---- d = -B delta on the free set; both candidate directions of Algorithm 2 and their sums
             if (wact) {
-                double de = 0.0;
-                if (mi != 0.0) {
-                    double q = 0.0;
-                    for (int j0 = 0; j0 < V; j0 += 8) {
-                        double dv[8], vv[8];
+                // this lane's slot's coefficient, handed round by broadcast; six slots' vectors per round, no test on a lane
+                const int lg = logical(lane);
+                const double coef = lg >= 0 ? sc.delta[lg] : 0.0;
+                const int t = act ? tid : 0;
+                double q0 = lane_value(coef, m) * gi, q1 = 0.0;
+                for (int k0 = 0; k0 < m; k0 += 6) {
+                    double yv[6], sv[6];
 #pragma unroll
-                        for (int k = 0; k < 8; ++k) {
-                            const bool in = j0 + k < V;
-                            dv[k] = in ? sc.delta[j0 + k] : 0.0;
-                            vv[k] = in ? vec(j0 + k)[tid] : 0.0;
-                        }
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) q = fma(dv[k], vv[k], q);
+                    for (int k = 0; k < 6; ++k) {
+                        const int kk = k0 + k < m ? k0 + k : m - 1;
+                        yv[k] = Ys[kk * np + t];
+                        sv[k] = Ss[kk * np + t];
                     }
-                    de = -q;
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) {
+                        const int kk = k0 + k < m ? k0 + k : m - 1;
+                        const double cy = lane_value(coef, kk), cs = lane_value(coef, m + 1 + kk);
+                        q0 = fma(k0 + k < m ? cy : 0.0, yv[k], q0);
+                        q1 = fma(k0 + k < m ? cs : 0.0, sv[k], q1);
+                    }
                 }
+                const double de = mi != 0.0 ? -(q0 + q1) : 0.0;
                 double ub = INFINITY;
                 if (act) {
                     pa = clampd(xi + de, li, ui) - xi;
@@ -256,8 +278,8 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                     if (de > 0.0 && xi >= ui - op.eps) pb = 0.0;
                     p1s[tid] = pa;
                     p2s[tid] = pb;
-                    if (pb > 0.0) ub = (ui - xi) / pb;
-                    else if (pb < 0.0) ub = (li - xi) / pb;
+                    const double room = ((pb > 0.0 ? ui : li) - xi) / pb;
+                    if (pb != 0.0) ub = room;
                 }
                 double w6[6] = {pa * gi, pa * pa, xi * pa, pb * gi, pb * pb, xi * pb};
 #pragma unroll
@@ -295,6 +317,14 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                 wl[k] = 0.0;
             }
             double ttg = 0.0;
+            // (the targets are read in the rare evaluations only; no test inside the rows' loop, whose chains interleave)
+            double bq[RG];
+#pragma unroll
+            for (int q = 0; q < RG; ++q) bq[q] = 0.0;
+            if (want_eval) {
+#pragma unroll
+                for (int q = 0; q < RG; ++q) bq[q] = grp + kResGroups * q < rows ? a.b[grp + kResGroups * q] : 0.0;
+            }
 #pragma unroll
             for (int q = 0; q < RG; ++q) {
                 double s = 0.0;
@@ -305,9 +335,8 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                 s += dpp_move<kDppXor2>(s);
                 s += dpp_move<kDppHalfMirror>(s);
                 s += dpp_move<kDppMirror>(s);
-                const int r = grp + kResGroups * q;
-                double psi = r < rows ? s : 0.0;
-                if (want_eval && r < rows) psi -= a.b[r];      // (the targets are read in the rare evaluations only)
+                // (a row past the end is zero in the registers, and so is its product)
+                const double psi = s - bq[q];
                 ttg = fma(psi, psi, ttg);
 #pragma unroll
                 for (int k = 0; k < CPL; ++k) wl[k] = fma(at[q][k], psi, wl[k]);
@@ -371,7 +400,8 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
             if (lane == 0) redU[wave] = ysq;
         }
         __syncthreads();
-        if (tid == 0) {
+        // (the last thread: its wave owns no elements -- n <= 256 -- and is not waited for before the next free set is known)
+        if (tid == kResThreads - 1) {
             double yn = 0.0;
             for (int w = 0; w < nw; ++w) yn += redU[w];
             sc.branch = branch; sc.gp = gp; sc.alpha_ub = alpha_ub;
@@ -396,7 +426,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                 sc.status = LBFGSB_LINESEARCH_FAILED;
             }
         }
-        // the same bookkeeping in every thread's registers; the next trip's first barrier orders thread 0's writes to
+        // the same bookkeeping in every thread's registers; the next trip's first barrier orders that thread's writes to
         // the scalar block before the recursion reads them
         if (ok) { head = (slot + 1) % m; c = c < m ? c + 1 : m; since += 1; }
         else if (c > 0) c = 0;
@@ -445,7 +475,8 @@ const ResVariant* resident_variant(const Dims& dm) {
 bool resident_shape_ok(const Dims& dm, bool has_row_weight) {
     if (dm.kind != LBFGSB_OBJ_LSQ || has_row_weight || dm.n_extra > 0 || dm.n != dm.cols) return false;
     const ResVariant* v = resident_variant(dm);
-    return v && (size_t)res_layout((int)dm.n, dm.m, v->cpl * 16).total * 8 <= kResLdsLimit;
+    // (the skew between the vectors is not counted: what fitted without it is still taken)
+    return v && (size_t)(res_layout((int)dm.n, dm.m, v->cpl * 16).total - kResSkew * res_vectors(dm.m)) * 8 <= kResLdsLimit;
 }
 
 hipError_t resident_prepare(const Dims& dm) {

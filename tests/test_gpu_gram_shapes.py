@@ -80,3 +80,32 @@ def test_a_step_after_the_end_changes_nothing():
     b = s.info()
     assert a.status == L.CONVERGED and a.as_dict() == b.as_dict() and torch.equal(xa, s.x())
     s.close()
+
+
+# the resident solver's Gram matrix: one, two, three and four blocks of 16 slots (m = 7 is the last with one), vectors of fewer
+# elements than one wave takes, of more than the eight waves take at once, and of a length that is no multiple of 16
+@pytest.mark.parametrize("m", [1, 7, 8, 10, 16, 24, 31])
+@pytest.mark.parametrize("rows,cols", [(60, 9), (200, 100), (120, 129), (90, 60)])
+def test_resident_iterations(rows, cols, m):
+    rng = np.random.default_rng(rows + cols + m)
+    A = rng.normal(size=(rows, cols)) * np.exp(0.7 * rng.normal(size=cols))
+    b = A @ np.where(rng.random(cols) < 0.5, 0.0, np.abs(rng.normal(size=cols))) + 0.1 * rng.normal(size=rows)
+    l, u = np.zeros(cols), np.full(cols, np.inf)
+    ref = oracle.Solver(oracle.Objective(oracle.LSQ, A, b), l, u, np.zeros(cols), m, oracle.default_options(tol=0.0))
+    s = make_solver(L.OBJ_LSQ, A, b, l, u, m, tol=0.0)
+    if (cols, m) == (129, 31):                           # (does not fit the compute unit's memory)
+        assert s.apass_name != "resident"
+        s.close()
+        return
+    assert s.apass_name == "resident"
+    s.set_x(torch.zeros(cols, dtype=torch.float64, device=DEV))
+    g0 = float(np.linalg.norm(ref.g))
+    for it in range(min(m + 4, 12)):
+        ref.step()
+        info = s.step()
+        if float(np.linalg.norm(ref.g[oracle.free_mask(ref.x, ref.g, l, u, 1e-10) != 0])) <= 1e-6 * g0:
+            break                                        # (close to the minimiser the gradient is rounding)
+        assert info.branch == ref.info.branch and info.backtracks == ref.info.backtracks and info.pairs_used == ref.info.pairs_used, it
+        assert rel_err(s.x().cpu().numpy(), ref.x) <= 1e-8 and rel_err(s.g().cpu().numpy(), ref.g) <= 1e-7, it
+    ref.close()
+    s.close()

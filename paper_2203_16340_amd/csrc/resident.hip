@@ -129,14 +129,17 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
         return;
     }
     if (tid == 0 && sc.pend_valid) apply_pending(&sc, m);   // (left by a step of the multi-kernel path; normally none)
+    __syncthreads();                                         // (the ring below is the one with that update applied)
 
     // ---- the vectors into LDS and registers
     double xi = 0.0, gi = 0.0, li = 0.0, ui = 0.0, mi = 0.0;
     if (act) { xi = a.x[tid]; gi = a.g[tid]; li = a.l[tid]; ui = a.u[tid]; mi = a.mask[tid] ? 1.0 : 0.0; xs[tid] = xi; gs[tid] = gi; }
     for (int i = tid; i < m * n; i += kResThreads) {
         const int sl = i / n, e = i - sl * n;
-        Ss[sl * np + e] = a.S[i];
-        Ys[sl * np + e] = a.Y[i];
+        // (a slot that holds no pair is read by the loops below, with coefficients of zero: not what an earlier run left there)
+        const int age = sc.head - 1 - sl + (sl < sc.head ? 0 : m);
+        Ss[sl * np + e] = age < sc.count ? a.S[i] : 0.0;
+        Ys[sl * np + e] = age < sc.count ? a.Y[i] : 0.0;
     }
     __syncthreads();
     // loop state every thread carries in registers (the same values in all of them)
@@ -250,7 +253,8 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
             if (wact) {
                 // this lane's slot's coefficient, handed round by broadcast; six slots' vectors per round, no test on a lane
                 const int lg = logical(lane);
-                const double coef = lg >= 0 ? sc.delta[lg] : 0.0;
+                double coef = lg >= 0 ? sc.delta[lg] : 0.0;
+                asm volatile("" : "+v"(coef));               // (here, by all lanes)
                 const int t = act ? tid : 0;
                 double q0 = lane_value(coef, m) * gi, q1 = 0.0;
                 for (int k0 = 0; k0 < m; k0 += 6) {

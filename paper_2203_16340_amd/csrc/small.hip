@@ -12,7 +12,10 @@
 //
 // Measured (least squares, iterations of a problem with 1.5 n + 260 rows, us per iteration, Gram + direction kernels /
 // this kernel): m = 5: n = 100 26.9 / 18.5, 301 32.4 / 20.4, 1024 32.4 / 26.5; m = 10: 100 28.5 / 20.9, 512 32.4 / 25.3, 832 32.8 / 30.2
-// (1000: 33.4 / 33.3, left to the two kernels); m = 20: 100 38.8 / 27.6, 384 41.4 / 32.1.
+// (1000: 33.4 / 33.3, left to the two kernels); m = 20: 100 38.8 / 27.6, 384 41.4 / 32.1.  That was with a branch per slot in the
+// statistics and the direction (130 cycles each), 64 elements per wave and turn at the matrix cores and three exchanges between
+// the waves where two do; without them 50 steps take 1221 -> 1098 us at n = 301 and 1853 -> 1670 at 801 (m = 10), 1024 -> 902 at 101
+// (m = 5), 1723 -> 1533 at 350 (m = 20).
 #include <cstddef>
 
 #include "common.h"
@@ -33,7 +36,7 @@ constexpr int small_pairs(int M) {
 }
 // doubles between two vectors in LDS: even, and an odd multiple of two, so that 16 lanes that read 16 bytes each of 16
 // vectors touch every bank once
-constexpr int small_stride(int64_t n) { return (int)((n + 63) / 64 * 64 + 2); }
+constexpr int small_stride(int64_t n) { return (int)((n + 15) / 16 * 16 + 2); }
 constexpr size_t small_lds_bytes(int M, int64_t n) {
     const size_t vec = (size_t)(2 * M + 1) * small_stride(n), part = (size_t)kSmallNW * small_pairs(M) * 256;
     return (vec > part ? vec : part) * 8;
@@ -58,8 +61,8 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
     extern __shared__ __align__(16) double dyn[];   // masked vectors, later the waves' blocks
     __shared__ double G[GD * GD];
     __shared__ Scal sc;
-    __shared__ double dslot[V0];                    // the direction's coefficients by static slot
     __shared__ double red[kSmallNW * 8];
+    __shared__ double redx[kSmallNW * 2 * kFoldMax];
     __shared__ double alpha_s[kMaxM + 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = (int)dm.n, m = dm.m;
@@ -99,13 +102,22 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
     auto logical = [&](int slot) -> int {
         if (slot == M) return 2 * c;
         const int ring = slot < M ? slot : slot - M - 1;
-        if (ring >= m) return -1;
-        const int k = (ring - base_slot + m) % m;
-        return k >= c ? -1 : (slot < M ? c + k : k);
+        const int k = ring >= base_slot ? ring - base_slot : ring - base_slot + m;
+        return ring >= m || slot >= V0 || k >= c ? -1 : (slot < M ? c + k : k);
     };
-    double st3[3] = {0.0, 0.0, 0.0};                 // #fixed, ||y_new||^2 over the full vector, unused
-    double pginf = 0.0;
+    double ysum = 0.0, pginf = 0.0;                  // ||y_new||^2 over the full vector, KKT residual
+    int nfix = 0;                                    // #fixed, of this wave
     unsigned freebits = 0;                           // bit r: this thread's element of round r is free
+    // (what a slot that holds no pair contains is not looked at)
+#pragma unroll
+    for (int k = 0; k < M; ++k) {
+        const bool holds = logical(k) >= 0;          // (uniform)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            vy[r][k] = holds ? vy[r][k] : 0.0;
+            vs[r][k] = holds ? vs[r][k] : 0.0;
+        }
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int e = tid + r * kSmallNT;
@@ -113,15 +125,15 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
         const bool at_lower = (xe[r] <= le[r] + op.eps) && (ge[r] >= 0.0);
         const bool at_upper = (xe[r] >= ue[r] - op.eps) && (ge[r] <= 0.0);
         const bool fr = in && !(at_lower || at_upper);
-        if (in) {
-            mask[e] = (uint8_t)fr;
-            pginf = fmax(pginf, fabs(xe[r] - clampd(xe[r] - ge[r], le[r], ue[r])));
-            if (fr) freebits |= 1u << r; else st3[0] += 1.0;
+        double yn = 0.0;
 #pragma unroll
-            for (int k = 0; k < M; ++k)
-                if (k == newest) st3[1] = fma(vy[r][k], vy[r][k], st3[1]);
-        }
-        if (e < ls - 2) {                            // (zeros from n to the end of the last chunk of 64)
+        for (int k = 0; k < M; ++k) yn = k == newest ? vy[r][k] : yn;
+        ysum = in ? fma(yn, yn, ysum) : ysum;
+        pginf = in ? fmax(pginf, fabs(xe[r] - clampd(xe[r] - ge[r], le[r], ue[r]))) : pginf;
+        freebits |= fr ? 1u << r : 0u;
+        nfix += __popcll(__ballot(in && !fr));
+        if (in) mask[e] = (uint8_t)fr;
+        if (e < ls - 2) {                            // (zeros from n to the end of the last chunk of 16)
             dyn[M * ls + e] = fr ? ge[r] : 0.0;
 #pragma unroll
             for (int k = 0; k < M; ++k) {
@@ -130,79 +142,79 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
             }
         }
     }
-    block_sum<3, kSmallNW>(st3, red);                // (also the barriers that publish dyn)
+    ysum = wave_sum(ysum);
     pginf = wave_max(pginf);
+    if (lane == 0) { red[wave] = pginf; red[kSmallNW + wave] = ysum; red[2 * kSmallNW + wave] = (double)nfix; }
+    __syncthreads();                                 // (publishes dyn and the waves' statistics)
     if (tid == kSmallNT - 1) apply_pending(&sc, m);  // (every thread has read the ring position out of the copy)
 
     f64x4 acc[NP];
 #pragma unroll
     for (int k = 0; k < NP; ++k) acc[k] = f64x4{0.0, 0.0, 0.0, 0.0};
     const int i16 = lane & 15, q = lane >> 4;
-    const int chunks = (n + 63) / 64;
-    for (int ch = wave; ch < chunks; ch += kSmallNW) {
+    // 16 elements -- four steps of 4 -- per wave and turn, so that the matrix cores of all four SIMDs are busy (a step of one
+    // block takes 64 cycles, and at a few hundred elements these are what the phase lasts)
+    for (int e0 = 16 * wave; e0 < n; e0 += 16 * kSmallNW) {
+        double2 v[NB][2];
 #pragma unroll
-        for (int s8 = 0; s8 < 8; ++s8) {
-            double2 v[NB];
+        for (int b = 0; b < NB; ++b) {
+            const int j = 16 * b + i16;
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int j = 16 * b + i16;
-                v[b] = *reinterpret_cast<const double2*>(&dyn[(j < V0 ? j : 0) * ls + ch * 64 + 8 * s8 + 2 * q]);
-                if (j >= V0) v[b] = double2{0.0, 0.0};
+            for (int h = 0; h < 2; ++h) {
+                v[b][h] = *reinterpret_cast<const double2*>(&dyn[(j < V0 ? j : 0) * ls + e0 + 8 * h + 2 * q]);
+                if (j >= V0) v[b][h] = double2{0.0, 0.0};
             }
+        }
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                int k = 0;
+        for (int t = 0; t < 4; ++t) {
+            int k = 0;
 #pragma unroll
-                for (int a = 0; a < NB; ++a) {
+            for (int a = 0; a < NB; ++a) {
 #pragma unroll
-                    for (int b = a; b < NB; ++b, ++k)
-                        if (k < NP) acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(t ? v[a].y : v[a].x, t ? v[b].y : v[b].x, acc[k], 0, 0, 0);
-                }
+                for (int b = a; b < NB; ++b, ++k)
+                    if (k < NP) acc[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(t & 1 ? v[a][t / 2].y : v[a][t / 2].x, t & 1 ? v[b][t / 2].y : v[b][t / 2].x, acc[k], 0, 0, 0);
             }
         }
     }
-    __syncthreads();                                 // (the vectors have been read; red is free)
-    if (lane == 0) red[wave] = pginf;
+    double ynew = red[kSmallNW];
+    double nfixed = red[2 * kSmallNW];
+    pginf = red[0];
+#pragma unroll
+    for (int w = 1; w < kSmallNW; ++w) {
+        pginf = fmax(pginf, red[w]);
+        ynew += red[kSmallNW + w];
+        nfixed += red[2 * kSmallNW + w];
+    }
+    __syncthreads();                                 // (the vectors and the statistics have been read)
 #pragma unroll
     for (int k = 0; k < NP; ++k)
 #pragma unroll
         for (int r = 0; r < 4; ++r) dyn[(wave * NP + k) * 256 + r * 64 + lane] = acc[k][r];
     __syncthreads();
-    pginf = red[0];
-#pragma unroll
-    for (int w = 1; w < kSmallNW; ++w) pginf = fmax(pginf, red[w]);
     // the waves' blocks added in wave order, static slots -> the recursion's order
-    const int used = chunks < kSmallNW ? chunks : kSmallNW;
     for (int idx = tid; idx < NP * 256; idx += kSmallNT) {
         const int pair = idx >> 8, r = (idx >> 6) & 3, ln = idx & 63;
         int a = 0, pb = pair;
         while (pb >= NB - a) { pb -= NB - a; ++a; }      // pair -> blocks (a, a + pb)
         const int ra = 16 * a + (ln >> 4) + 4 * r, cb = 16 * (a + pb) + (ln & 15);
-        if (ra >= V0 || cb >= V0) continue;
         const int row = logical(ra), col = logical(cb);
+        double t = dyn[idx];
+#pragma unroll
+        for (int w = 1; w < kSmallNW; ++w) t += dyn[w * NP * 256 + idx];
         if (row < 0 || col < 0) continue;
-        double t = 0.0;
-        for (int w = 0; w < used; ++w) t += dyn[w * NP * 256 + idx];
         G[row * Vp + col] = t;
         if (pb != 0) G[col * Vp + row] = t;              // (a block with itself holds both (row, col) and (col, row))
     }
     __syncthreads();
-    const double ynew = st3[1];
     if (tid == 0 && c > 0) sc.ynorm2[newest] = ynew;
-    recursion_on_coefficients(G, Vp, c, head, m, op, &sc, G[(2 * c) * Vp + 2 * c], pginf, st3[0], ynew, yn_old, alpha_s, 0, 1);
+    recursion_on_coefficients(G, Vp, c, head, m, op, &sc, G[(2 * c) * Vp + 2 * c], pginf, nfixed, ynew, yn_old, alpha_s, 0, 1);
     __syncthreads();
     if (tid == 0) note_progress(op, sc.status);
     if (sc.status == LBFGSB_RUNNING) {
-        if (tid < V0) {
-            const int k = logical(tid);
-            dslot[tid] = k >= 0 ? sc.delta[k] : 0.0;
-        }
-        unsigned long long active = 0;               // bit s: static slot s holds a vector
-        for (int k = 0; k < c; ++k) {
-            const int sl = (base_slot + k) % m;
-            active |= (1ull << sl) | (1ull << (M + 1 + sl));
-        }
-        __syncthreads();
+        // this lane's slot's coefficient, handed round by broadcast (zero where the slot holds no pair)
+        const int lg = logical(lane);
+        double coef = lg >= 0 ? sc.delta[lg] : 0.0;
+        asm volatile("" : "+v"(coef));                   // (here, by all lanes)
         // d = -B delta on the free set, Algorithm 2's two candidates and what the choice between them needs
         double s[6] = {0, 0, 0, 0, 0, 0};
         double sx[2 * kFoldMax];
@@ -212,19 +224,15 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int e = tid + r * kSmallNT;
-            if (e < n) {
-                double de = 0.0;
-                if ((freebits >> r) & 1u) {
-                    double qv = dslot[M] * ge[r];
+            // (outside the test: a broadcast from a lane that is switched off would be undefined)
+            double q0 = lane_value(coef, M) * ge[r], q1 = 0.0;
 #pragma unroll
-                    for (int k = 0; k < M; ++k) {
-                        if ((active >> k) & 1ull) {      // (uniform; what an unused slot holds is not looked at)
-                            qv = fma(dslot[k], vy[r][k], qv);
-                            qv = fma(dslot[M + 1 + k], vs[r][k], qv);
-                        }
-                    }
-                    de = -qv;
-                }
+            for (int k = 0; k < M; ++k) {
+                q0 = fma(lane_value(coef, k), vy[r][k], q0);
+                q1 = fma(lane_value(coef, M + 1 + k), vs[r][k], q1);
+            }
+            const double de = (freebits >> r) & 1u ? -(q0 + q1) : 0.0;
+            if (e < n) {
                 const double a = clampd(xe[r] + de, le[r], ue[r]) - xe[r];
                 double b = de;
                 if (de < 0.0 && xe[r] <= le[r] + op.eps) b = 0.0;
@@ -233,8 +241,8 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
                 p2[e] = b;
                 s[0] = fma(a, ge[r], s[0]); s[1] = fma(a, a, s[1]); s[2] = fma(xe[r], a, s[2]);
                 s[3] = fma(b, ge[r], s[3]); s[4] = fma(b, b, s[4]); s[5] = fma(xe[r], b, s[5]);
-                if (b > 0.0) ub = fmin(ub, (ue[r] - xe[r]) / b);
-                else if (b < 0.0) ub = fmin(ub, (le[r] - xe[r]) / b);
+                const double room = ((b > 0.0 ? ue[r] : le[r]) - xe[r]) / b;
+                if (b != 0.0) ub = fmin(ub, room);
 #pragma unroll
                 for (int f = 0; f < kFoldMax; ++f) {
                     if (f < n_fold) {
@@ -245,15 +253,45 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
                 }
             }
         }
-        block_sum<6, kSmallNW>(s, red);
-        if (n_fold > 0) block_sum<2 * kFoldMax, kSmallNW>(sx, red);
+        // one exchange: the waves' seven results side by side, added by the first wave with the lanes as they lie
         ub = wave_min(ub);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) s[k] = wave_sum(s[k]);
+        if (lane == 0) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) red[wave * 8 + k] = s[k];
+            red[wave * 8 + 6] = ub;
+            red[wave * 8 + 7] = 0.0;
+        }
+        if (n_fold > 0) {
+#pragma unroll
+            for (int k = 0; k < 2 * kFoldMax; ++k) sx[k] = wave_sum(sx[k]);
+            if (lane == 0) {
+#pragma unroll
+                for (int k = 0; k < 2 * kFoldMax; ++k) redx[wave * 2 * kFoldMax + k] = sx[k];
+            }
+        }
         __syncthreads();
-        if (lane == 0) red[wave] = ub;
-        __syncthreads();
+        if (tid < 64) {
+            double tsum = red[lane], tmin = tsum;    // lane = 8 wave + k
+#pragma unroll
+            for (int dlt = 8; dlt < 64; dlt *= 2) {
+                tsum += __shfl_xor(tsum, dlt);
+                tmin = fmin(tmin, __shfl_xor(tmin, dlt));
+            }
+#pragma unroll
+            for (int k = 0; k < 6; ++k) s[k] = lane_bcast(tsum, k);
+            ub = lane_bcast(tmin, 6);
+        }
         if (tid == 0) {
-            ub = red[0];
-            for (int w = 1; w < kSmallNW; ++w) ub = fmin(ub, red[w]);
+            if (n_fold > 0) {
+#pragma unroll
+                for (int k = 0; k < 2 * kFoldMax; ++k) {
+                    sx[k] = redx[k];
+#pragma unroll
+                    for (int w = 1; w < kSmallNW; ++w) sx[k] += redx[w * 2 * kFoldMax + k];
+                }
+            }
             const int branch = (s[0] <= -op.eps * s[1] && s[1] >= op.eps) ? 1 : 2;
             sc.branch = branch;
             if (branch == 1) { sc.gp = s[0]; sc.alpha_ub = 1.0; sc.pp = s[1]; sc.xp = s[2]; }

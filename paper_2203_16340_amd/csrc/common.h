@@ -20,7 +20,7 @@ constexpr int kFoldMax = 2;       // extra dense rows the direction kernel handl
 constexpr int kLsBatch = 8;        // step lengths the logistic line search evaluates per sweep over the rows
 
 // Which per-kernel arrival counter (Scal::counters) a kernel uses to find its last workgroup.
-enum { kCntDir = 0, kCntUpdate, kCntLs, kCntCount };
+enum { kCntDir = 0, kCntUpdate, kCntEvalFinish, kCntLs, kCntCount };
 // Grids of the kernels whose last workgroup finishes the job (arrive_is_last) stay at two workgroups per compute
 // unit: every workgroup ends with an atomic on one address, and those serialise (4096 workgroups measured 90 us
 // slower per launch than 512 on the same data).
@@ -455,10 +455,10 @@ __device__ __forceinline__ double column_sum(const double* __restrict__ wpart, i
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const int kk = k0 + kGY * k;
-                v[k] = kk < parts ? wpart[(int64_t)kk * cols + c] : 0.0;
+                v[k] = wpart[(int64_t)(kk < parts ? kk : k0) * cols + c];   // (no load is predicated: a test each is a branch each)
             }
 #pragma unroll
-            for (int k = 0; k < 8; ++k) s += v[k];
+            for (int k = 0; k < 8; ++k) s += k0 + kGY * k < parts ? v[k] : 0.0;
         }
     }
     __syncthreads();
@@ -479,9 +479,9 @@ __device__ __forceinline__ double sum_all(const double* __restrict__ v, int coun
     for (int k0 = threadIdx.x; k0 < count; k0 += NT * 8) {
         double t[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) t[k] = k0 + NT * k < count ? v[k0 + NT * k] : 0.0;
+        for (int k = 0; k < 8; ++k) t[k] = v[k0 + NT * k < count ? k0 + NT * k : k0];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) s[0] += t[k];
+        for (int k = 0; k < 8; ++k) s[0] += k0 + NT * k < count ? t[k] : 0.0;
     }
     block_sum<1, NT / 64>(s, lds);
     return s[0];

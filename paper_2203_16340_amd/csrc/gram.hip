@@ -79,15 +79,14 @@ __device__ __forceinline__ bool reduce_partials(double* __restrict__ grampart, i
     auto add = [&](int first, int count, int idx) -> double {
         double v[kGramGroupMax];
 #pragma unroll
-        for (int k = 0; k < kGramGroupMax; ++k) v[k] = k < count ? observe(grampart + (int64_t)(first + k) * NE + idx) : 0.0;
-        double t = v[0];
-        if (idx == 0) {
+        for (int k = 0; k < kGramGroupMax; ++k) v[k] = observe(grampart + (int64_t)(first + (k < count ? k : 0)) * NE + idx);
+        double t = v[0], most = v[0];
 #pragma unroll
-            for (int k = 1; k < kGramGroupMax; ++k) t = fmax(t, v[k]);
-        } else {
-#pragma unroll
-            for (int k = 1; k < kGramGroupMax; ++k) t += v[k];
+        for (int k = 1; k < kGramGroupMax; ++k) {
+            t += k < count ? v[k] : 0.0;
+            most = fmax(most, v[k]);
         }
+        t = idx == 0 ? most : t;
         return t;
     };
     static_assert(kGramGroups <= kGramGroupMax, "one batch of loads at either level");

@@ -26,30 +26,35 @@ __device__ __forceinline__ void gram_product_slots(int idx, int m, int& a, int& 
 }
 
 // Adds the records of `nwg` workgroups (NE doubles each; entry 0 is a maximum, the others are sums) in workgroup order into
-// tot[0 .. NE): thread idx takes entry idx, 64 records at a time with every load of a batch issued before the first is used.
+// tot[0 .. NE): thread idx takes entry idx, BATCH records at a time with every load of a batch issued before the first is used and
+// none of them under a test (past the last record: the last one again, not added).
 // Called by all NT threads; no barrier inside.  SAME: the records are of this launch (published), else of an earlier one.
-template <int NT, bool SAME>
-__device__ __forceinline__ void gram_sum_partials_flat(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
-    constexpr int kBatch = 64;
+template <int NT, bool SAME, int BATCH>
+__device__ __forceinline__ void gram_sum_batches(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
     for (int idx = threadIdx.x; idx < NE; idx += NT) {
-        double t = idx == 0 ? -INFINITY : 0.0;
-        for (int k0 = 0; k0 < nwg; k0 += kBatch) {
-            double v[kBatch];
+        double sum = 0.0, most = -INFINITY;
+        for (int k0 = 0; k0 < nwg; k0 += BATCH) {
+            double v[BATCH];
 #pragma unroll
-            for (int k = 0; k < kBatch; ++k) {
-                const double* r = grampart + (int64_t)(k0 + k) * NE + idx;
-                v[k] = k0 + k < nwg ? (SAME ? observe(r) : *r) : (idx == 0 ? -INFINITY : 0.0);
+            for (int k = 0; k < BATCH; ++k) {
+                const double* r = grampart + (int64_t)(k0 + k < nwg ? k0 + k : nwg - 1) * NE + idx;
+                v[k] = SAME ? observe(r) : *r;
             }
-            if (idx == 0) {
 #pragma unroll
-                for (int k = 0; k < kBatch; ++k) t = fmax(t, v[k]);
-            } else {
-#pragma unroll
-                for (int k = 0; k < kBatch; ++k) t += v[k];
+            for (int k = 0; k < BATCH; ++k) {
+                sum += k0 + k < nwg ? v[k] : 0.0;
+                most = fmax(most, v[k]);
             }
         }
-        tot[idx] = t;
+        tot[idx] = idx == 0 ? most : sum;
     }
+}
+template <int NT, bool SAME>
+__device__ __forceinline__ void gram_sum_partials_flat(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
+    // (the trips of different batches to memory follow one another: a batch for all where that is not too many loads)
+    if (nwg <= 16) gram_sum_batches<NT, SAME, 16>(grampart, NE, nwg, tot);
+    else if (nwg <= 32) gram_sum_batches<NT, SAME, 32>(grampart, NE, nwg, tot);
+    else gram_sum_batches<NT, SAME, 64>(grampart, NE, nwg, tot);
 }
 
 // The closing step from the totals tot[0 .. gram_entries(m)) (LDS, complete: a barrier lies between their last write and this

@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
         __syncthreads();
         if (!d_given && mkn && e_first < n) {
 #pragma unroll
-            for (int j = 0; j < kDirPre; ++j) vpre[j] = j < 2 * c + 1 ? vecp[j][e_first] : 0.0;
+            for (int j = 0; j < kDirPre; ++j) vpre[j] = vecp[j][e_first];   // (past the last vector: g, with a coefficient of zero)
         }
         __syncthreads();                                           // every thread has read the ring before it changes
         gram_finish<kBlock>(tot, Gs, alpha_s, &sc, m, c, head, base_slot, op, yn_old, 0, 1, blockIdx.x == 0, pa, pb);
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
                     for (int j0 = 0; j0 < V; j0 += 8) {
                         double v[8];
 #pragma unroll
-                        for (int k = 0; k < 8; ++k) v[k] = j0 + k < V ? vecp[j0 + k][e] : 0.0;
+                        for (int k = 0; k < 8; ++k) v[k] = vecp[j0 + k][e];
 #pragma unroll
                         for (int k = 0; k < 8; ++k) q = fma(delta_s[j0 + k], v[k], q);
                     }
@@ -452,8 +452,7 @@ __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op,
     auto load = [&](int j0, int base_slot, int64_t e, dir_f64x2 (&v)[kRound]) {
 #pragma unroll
         for (int k = 0; k < kRound; ++k) {
-            v[k] = dir_f64x2{0.0, 0.0};
-            if (j0 + k < V) v[k] = *reinterpret_cast<const dir_f64x2_any*>(vec(j0 + k, base_slot) + e);
+            v[k] = *reinterpret_cast<const dir_f64x2_any*>(vec(j0 + k, base_slot) + e);   // (past the last: g, its coefficient is zero)
         }
     };
     auto add = [&](int j0, const dir_f64x2 (&v)[kRound], double& q0, double& q1) {
@@ -596,51 +595,45 @@ void launch_dir(const Dims& dm, const Opts& op, const Geometry& ge, const Buffer
 
 // ---- after an evaluation pass: g and f ------------------------------------------------------------------
 
-// The last workgroup of the grid adds up f, beside the others: what f takes beyond the pass's loss partials (the regulariser,
-// the linear term, the extra rows) needs x and not the gradient.  (It was formed from the workgroups' shares by the last one to
-// finish; the arrival alone made the kernel 15.7 us at 10 000 columns of a quadratic form, 32 at 20 000 of the L1-split kind.)
+// f needs x and the pass's loss partials, not the gradient.  Least squares: the first workgroup adds up the partials.  What the
+// other kinds take beyond them (the regulariser, the linear term) is shared by the first kRegBlocks workgroups, the last of which
+// to finish adds up.  (When every workgroup took a share and arrived, the arrivals at one address made the kernel 15.7 us at 10 000
+// columns of a quadratic form and 32 at 20 000 of the L1-split kind; one workgroup for all of it: 53 there.  Now 6.0 and 10.4.)
+constexpr int kRegBlocks = 64;
 __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, int loss_parts,
                                                         const double* __restrict__ wpart,
                                                         const double* __restrict__ losspart,
                                                         const double* __restrict__ x, double* __restrict__ g,
-                                                        Scal* __restrict__ scal,
+                                                        Scal* __restrict__ scal, double* __restrict__ redpart,
                                                         const double* __restrict__ lin, const double* __restrict__ sign,
                                                         const double* __restrict__ wextra,
                                                         const double* __restrict__ xres) {
     __shared__ double lds[kBlock];
     __shared__ double red[kWaves];
+    __shared__ int flag;
     if (scal->status != LBFGSB_RUNNING) return;
     const int tid = threadIdx.x;
-    if (blockIdx.x == gridDim.x - 1) {
-        double reg[1] = {0.0};
-        if (dm.kind != LBFGSB_OBJ_LSQ) {
-            // (eight variables per trip; L1-split: both halves are variables)
-            for (int64_t i0 = tid; i0 < dm.n; i0 += 8 * kBlock) {
-                double xv[8], cv[8];
+    const bool shares = dm.kind != LBFGSB_OBJ_LSQ;
+    const int nreg = shares ? ((int)gridDim.x < kRegBlocks ? (int)gridDim.x : kRegBlocks) : 1;
+    const bool reg_wg = (int)blockIdx.x < nreg;
+    double reg[1] = {0.0};
+    if (reg_wg && shares) {
+        for (int64_t i0 = (int64_t)blockIdx.x * kBlock + tid; i0 < dm.n; i0 += 4 * (int64_t)nreg * kBlock) {
+            double xv[4], cv[4];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const int64_t i = i0 + k * kBlock;
-                    xv[k] = i < dm.n ? x[i] : 0.0;
-                    cv[k] = dm.kind == LBFGSB_OBJ_QP ? (i < dm.n ? lin[i] : 0.0) : (dm.kind == LBFGSB_OBJ_LOGISTIC_L2 ? xv[k] : 1.0);
-                }
-#pragma unroll
-                for (int k = 0; k < 8; ++k) reg[0] = fma(cv[k], xv[k], reg[0]);
+            for (int k = 0; k < 4; ++k) {
+                const int64_t i = i0 + k * (int64_t)nreg * kBlock, ic = i < dm.n ? i : i0;
+                xv[k] = x[ic];
+                cv[k] = dm.kind == LBFGSB_OBJ_QP ? lin[ic] : (dm.kind == LBFGSB_OBJ_LOGISTIC_L2 ? xv[k] : 1.0);
+                if (i >= dm.n) cv[k] = 0.0;
             }
-            block_sum<1, kWaves>(reg, red);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) reg[0] = fma(cv[k], xv[k], reg[0]);
         }
-        const double loss = sum_all(losspart, loss_parts, red);
-        if (tid == 0) {
-            double f = loss;
-            if (dm.kind == LBFGSB_OBJ_LSQ_L1SPLIT) f += dm.lambda * reg[0];
-            else if (dm.kind == LBFGSB_OBJ_LOGISTIC_L2) f += 0.5 * dm.mu * reg[0];
-            else if (dm.kind == LBFGSB_OBJ_QP) f += reg[0];
-            if (xres) f += xres[dm.n_extra];   // 0.5 sum weight * residual^2 of the extra rows
-            scal->f = f;
-            scal->fevals += 1;
-        }
-        return;
+        block_sum<1, kWaves>(reg, red);
+        if (tid == 0) publish(redpart + blockIdx.x, reg[0]);
     }
-    for (int64_t c0 = (int64_t)blockIdx.x * kCX; c0 < dm.cols; c0 += (int64_t)(gridDim.x - 1) * kCX) {
+    for (int64_t c0 = (int64_t)blockIdx.x * kCX; c0 < dm.cols; c0 += (int64_t)gridDim.x * kCX) {
         const int64_t c = c0 + tid % kCX;
         const double w = column_sum(wpart, w_parts, dm.cols, c, lds);
         if (tid < kCX && c < dm.cols) {
@@ -658,13 +651,28 @@ __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, in
             }
         }
     }
+    if (!reg_wg || (shares && !arrive_is_last(&scal->counters[kCntEvalFinish], &flag, (unsigned)nreg))) return;
+    const double loss = sum_all(losspart, loss_parts, red);
+    if (shares) {
+        reg[0] = tid < nreg ? observe(redpart + tid) : 0.0;
+        block_sum<1, kWaves>(reg, red);
+    }
+    if (tid == 0) {
+        double f = loss;
+        if (dm.kind == LBFGSB_OBJ_LSQ_L1SPLIT) f += dm.lambda * reg[0];
+        else if (dm.kind == LBFGSB_OBJ_LOGISTIC_L2) f += 0.5 * dm.mu * reg[0];
+        else if (dm.kind == LBFGSB_OBJ_QP) f += reg[0];
+        if (xres) f += xres[dm.n_extra];   // 0.5 sum weight * residual^2 of the extra rows
+        scal->f = f;
+        scal->fevals += 1;
+    }
 }
 
 void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* lin, const double* sign,
                         hipStream_t st) {
     const bool qp = dm.kind == LBFGSB_OBJ_QP;
-    hipLaunchKernelGGL(k_eval_finish, dim3(ge.fin_blocks + 1), dim3(kBlock), 0, st, dm, qp ? 1 : ge.w_parts, ge.loss_parts,
-                       qp ? (const double*)bf.row : (const double*)bf.wpart, bf.losspart, bf.x, bf.g, bf.scal,
+    hipLaunchKernelGGL(k_eval_finish, dim3(ge.fin_blocks), dim3(kBlock), 0, st, dm, qp ? 1 : ge.w_parts, ge.loss_parts,
+                       qp ? (const double*)bf.row : (const double*)bf.wpart, bf.losspart, bf.x, bf.g, bf.scal, bf.redpart,
                        lin, sign, dm.n_extra > 0 ? (const double*)bf.wextra : nullptr,
                        dm.n_extra > 0 ? (const double*)bf.xres : nullptr);
 }

@@ -340,7 +340,7 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
     if (!LONG && no_close) return;   // the direction kernel adds the records and does the rest
     double* tot = dyn + gram_tot_at(M);
     if (!reduce_partials<NT>(grampart, NE, scal, &flag, tot, LONG && no_close)) return;
-    gram_finish<NT>(tot, dyn, alpha_s, scal, m, c, head, base_slot, op, yn_old, DBG, evaluate_stop, true);
+    gram_finish<NT, M < 10 ? 10 : M>(tot, dyn, alpha_s, scal, m, c, head, base_slot, op, yn_old, DBG, evaluate_stop, true);
     __syncthreads();
     if (tid == 0 && evaluate_stop) note_progress(op, scal->status);
 }

@@ -61,7 +61,8 @@ __device__ __forceinline__ void gram_sum_partials_flat(const double* __restrict_
 // call).  c, head: the ring as it will be once the pending update is applied; base_slot: ring slot of the oldest pair.
 // Gs: (2 m + 2)^2 doubles, alpha_s: kMaxM + 1 (both LDS).  sc: the scalar block this works on.  mine_a, mine_b (or -1): the
 // slots of entry threadIdx.x, when the caller has worked them out while it waited for something.
-template <int NT>
+// MAXK: see recursion_on_coefficients.
+template <int NT, int MAXK>
 __device__ __forceinline__ void gram_finish(const double* tot, double* Gs, double* alpha_s, Scal* sc, int m,
                                             int c, int head, int base_slot, const Opts& op, double yn_old, int dbg_inputs,
                                             int evaluate_stop, bool record, int mine_a = -1, int mine_b = 0) {
@@ -93,7 +94,7 @@ __device__ __forceinline__ void gram_finish(const double* tot, double* Gs, doubl
     const double gg = Gs[(2 * c) * Vp + 2 * c];   // sum over the free set of g^2
     const double ynew = tot[2];                    // ||y_new||^2 over the full vector: kept for later iterations
     if (tid == 0 && c > 0 && !dbg_inputs) sc->ynorm2[(head - 1 + m) % m] = ynew;
-    recursion_on_coefficients(Gs, Vp, c, head, m, op, sc, gg, tot[0], tot[1], ynew, yn_old, alpha_s, dbg_inputs, evaluate_stop);
+    recursion_on_coefficients<MAXK>(Gs, Vp, c, head, m, op, sc, gg, tot[0], tot[1], ynew, yn_old, alpha_s, dbg_inputs, evaluate_stop);
 }
 
 }  // namespace lb

@@ -20,8 +20,6 @@ __device__ __forceinline__ double prefetch_ynorm2(const Scal* __restrict__ scal,
     return (tid < 64 && tid < c) ? scal->ynorm2[(head - c + tid + 2 * m) % m] : 1.0;
 }
 
-constexpr int kRecFast = 10;   // up to this many pairs the recursion keeps its rows of G in registers
-
 // The recursion for at most K pairs.  Every entry of G a lane needs is fetched at once; the three loops then run on registers
 // and scalar-register broadcasts only.  Row i is scaled by 1/rho_i beforehand, and is zero where it has no say (pairs that fail
 // the gate; in the first loop pairs older than k, in the second newer ones), so a step of the chain is one broadcast and one
@@ -68,6 +66,9 @@ __device__ __forceinline__ void recursion_in_registers(const double* G, int Vp, 
 // another (which reads and writes other fields of the scalar block): called by all threads, at least 128, with a barrier before
 // anybody reads either's results.  G: Vp x Vp (LDS), row-major, vectors ordered s^0..s^{c-1}, y^0..y^{c-1}, g.  gg = sum g[S]^2, pginf = max KKT residual, nfixed = #fixed,
 // ynew = ||y_new||^2 (full vector), yn_old = prefetch_ynorm2().
+// MAXK: up to this many pairs the recursion keeps its rows of G in registers (three numbers each), beyond it reads LDS in its
+// steps (20 pairs, n = 350, 50 steps of the one-workgroup kernel: 1533 -> 1418 us with the registers).
+template <int MAXK>
 __device__ __forceinline__ void recursion_on_coefficients(const double* G, int Vp, int c, int head, int m, const Opts& op,
                                                           Scal* __restrict__ scal, double gg, double pginf, double nfixed,
                                                           double ynew, double yn_old, double* alpha_s, int dbg_inputs,
@@ -90,10 +91,12 @@ __device__ __forceinline__ void recursion_on_coefficients(const double* G, int V
         const double inv = 1.0 / rho, rho_yn = rho / yn;
         const unsigned long long pm = __ballot(pass);
         double alpha_i = 0.0, coef_s = 0.0, gamma = 1.0;
-        if (c <= kRecFast / 2) {
-            recursion_in_registers<kRecFast / 2>(G, Vp, c, i, ic, pass, pm, inv, rho_yn, alpha_i, coef_s, gamma);
-        } else if (c <= kRecFast) {
-            recursion_in_registers<kRecFast>(G, Vp, c, i, ic, pass, pm, inv, rho_yn, alpha_i, coef_s, gamma);
+        if (c <= 5) {
+            recursion_in_registers<5>(G, Vp, c, i, ic, pass, pm, inv, rho_yn, alpha_i, coef_s, gamma);
+        } else if (c <= 10) {
+            recursion_in_registers<10>(G, Vp, c, i, ic, pass, pm, inv, rho_yn, alpha_i, coef_s, gamma);
+        } else if (MAXK > 10 && c <= MAXK) {
+            recursion_in_registers<MAXK>(G, Vp, c, i, ic, pass, pm, inv, rho_yn, alpha_i, coef_s, gamma);
         } else {
             // first loop: alpha_k, newest to oldest.  Steps of pairs that fail the gate run with alpha_k = 0;
             // a lane's row is dead once its own alpha has been taken, so updating it further is harmless.

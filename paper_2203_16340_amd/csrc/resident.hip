@@ -233,7 +233,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                 }
                 const double ynew = c > 0 ? sc.ynorm2[(head - 1 + m) % m] : 0.0;
                 const double yn_old = prefetch_ynorm2(&sc, c, head, m);
-                recursion_on_coefficients(G, Vp, c, head, m, op, &sc, G[(2 * c) * Vp + 2 * c], pginf, nfix, ynew, yn_old,
+                recursion_on_coefficients<10>(G, Vp, c, head, m, op, &sc, G[(2 * c) * Vp + 2 * c], pginf, nfix, ynew, yn_old,
                                           alpha_s, 0, 1);
             }
             __syncthreads();

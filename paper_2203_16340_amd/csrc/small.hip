@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
     }
     __syncthreads();
     if (tid == 0 && c > 0) sc.ynorm2[newest] = ynew;
-    recursion_on_coefficients(G, Vp, c, head, m, op, &sc, G[(2 * c) * Vp + 2 * c], pginf, nfixed, ynew, yn_old, alpha_s, 0, 1);
+    recursion_on_coefficients<M < 10 ? 10 : M>(G, Vp, c, head, m, op, &sc, G[(2 * c) * Vp + 2 * c], pginf, nfixed, ynew, yn_old, alpha_s, 0, 1);
     __syncthreads();
     if (tid == 0) note_progress(op, sc.status);
     if (sc.status == LBFGSB_RUNNING) {

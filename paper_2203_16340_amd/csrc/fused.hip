@@ -64,38 +64,72 @@ void launch_variant(const Dims& dm, int64_t rows_per_wg, int blocks, size_t lds,
 // whose NT*KC*VEC columns cover a row and whose LDS need (v for every column) fits is used.  (Narrower rows --
 // narrow_shape_ok: up to 1536 fp32, 1024 or 768 fp64 columns -- have a kernel of their own, narrow.h; they come here
 // only with a leading dimension past 2^24.)
+// What a pass over a tile that is not full pays: the chunks past the row's end are loads of its last chunk (the cache serves
+// them) and multiplications by zero, and they hold ring slots that could be rows in flight.  A width between two that lie
+// apart by 1.6 or more is therefore worth a variant of its own where it leaves the ring as deep or deeper; four chunks under
+// five, six or seven under ten in 64 bits and sixteen under twenty measured the same or slower and are not there (the fp32
+// logistic ones under five chunks, 2 to 8 % faster, are).  Whole iterations, us, before / now: fp32 50001 x 3001 149 / 137, 50000 x 2500 145 / 121, 30000 x 2100 104 / 83, 50000 x 5500 249 /
+// 220, 25000 x 11001 264 / 225, 20000 x 13000 239 / 219; fp64 20000 x 2500 108 / 100 (2900: the same), 20000 x 11000 377 /
+// 344, 20000 x 13000 415 / 398, 20000 x 14200 442 / 428; logistic fp32 100000 x 2500 297 / 230, 100001 x 3001 307 / 275,
+// 80000 x 3400 241 / 231, 40000 x 6000 252 / 200, 40000 x 7000 256 / 236, 20000 x 12000 229 / 205, fp64 100000 x 1500 262 /
+// 234, 60000 x 2500 283 / 239, 20000 x 11000 384 / 345.
 // The logistic evaluation kernels spend ~100 registers on exp/log1p, so their rings are shallower; the direction
 // pass of the logistic objective has its own instantiation with the deepest ring that does not spill.
 const Variant kVariants[] = {
     LB_VARIANT(LBFGSB_F64, 0, double, 512, 2, 1, 4, 8, 2, 1),    // cols <=  2048
+    LB_VARIANT(LBFGSB_F64, 0, double, 512, 3, 1, 2, 4, 2, 1),    // cols <=  3072
     LB_VARIANT(LBFGSB_F64, 0, double, 512, 5, 1, 2, 4, 2, 1),    // cols <=  5120
     LB_VARIANT(LBFGSB_F64, 0, double, 512, 10, 1, 1, 2, 2, 1),   // cols <= 10240
+    LB_VARIANT(LBFGSB_F64, 0, double, 512, 12, 1, 1, 1, 2, 1),   // cols <= 12288
+    LB_VARIANT(LBFGSB_F64, 0, double, 512, 14, 1, 1, 1, 2, 1),   // cols <= 14336
     LB_VARIANT(LBFGSB_F64, 0, double, 512, 20, 1, 1, 1, 2, 1),   // cols <= 20480 (LDS: <= 20428)
     LB_VARIANT_KR(LBFGSB_F64, 0, double, 512, 22, 1, 1, 1, 2, 1, 3),   // cols <= 22528, v of the last 3 chunks in registers
     LB_VARIANT_KR(LBFGSB_F64, 0, double, 512, 24, 1, 1, 1, 2, 1, 5),   // cols <= 24576, v of the last 5 chunks in registers
     LB_VARIANT(LBFGSB_F32, 0, float, 256, 2, 1, 4, 12, 2, 2),    // cols <=  2048 (the geometry of the logistic direction pass)
+    LB_VARIANT(LBFGSB_F32, 0, float, 256, 3, 1, 4, 4, 2, 2),     // cols <=  3072
     LB_VARIANT(LBFGSB_F32, 0, float, 256, 5, 1, 1, 2, 2, 2),     // cols <=  5120
+    LB_VARIANT(LBFGSB_F32, 0, float, 512, 3, 1, 2, 4, 2, 1),     // cols <=  6144
     LB_VARIANT(LBFGSB_F32, 0, float, 512, 5, 1, 2, 4, 2, 1),     // cols <= 10240
+    LB_VARIANT(LBFGSB_F32, 0, float, 512, 6, 1, 1, 2, 2, 1),     // cols <= 12288
+    LB_VARIANT(LBFGSB_F32, 0, float, 512, 7, 1, 1, 2, 2, 1),     // cols <= 14336
     LB_VARIANT(LBFGSB_F32, 0, float, 512, 10, 1, 1, 2, 2, 1),    // cols <= 20480 (LDS: <= 20428)
     //              (…, R, ring depth of the evaluation kernel, of the direction kernel, …)
     LB_VARIANT_LOGI(LBFGSB_F64, double, 256, 2, 1, 4, 8, 12, 2, 2),    // cols <=  1024
+    LB_VARIANT_LOGI(LBFGSB_F64, double, 256, 3, 1, 2, 4, 6, 2, 2),     // cols <=  1536
     LB_VARIANT_LOGI(LBFGSB_F64, double, 512, 2, 1, 4, 4, 8, 2, 1),     // cols <=  2048
+    LB_VARIANT_LOGI(LBFGSB_F64, double, 512, 3, 1, 2, 4, 6, 2, 1),     // cols <=  3072
     LB_VARIANT_LOGI(LBFGSB_F64, double, 512, 5, 1, 1, 2, 4, 2, 1),     // cols <=  5120
     LB_VARIANT_LOGI(LBFGSB_F64, double, 512, 10, 1, 1, 1, 2, 2, 1),    // cols <= 10240
+    LB_VARIANT_LOGI(LBFGSB_F64, double, 512, 12, 1, 1, 1, 2, 2, 1),    // cols <= 12288
     LB_VARIANT_LOGI(LBFGSB_F64, double, 512, 20, 1, 1, 1, 1, 2, 1),    // cols <= 20480 (LDS: <= 20428)
     LB_VARIANT_LOGI(LBFGSB_F32, float, 256, 2, 1, 4, 8, 12, 2, 2),     // cols <=  2048
+    LB_VARIANT_LOGI(LBFGSB_F32, float, 256, 3, 1, 2, 2, 4, 2, 2),      // cols <=  3072
+    LB_VARIANT_LOGI(LBFGSB_F32, float, 256, 4, 1, 2, 2, 4, 2, 2),      // cols <=  4096
     LB_VARIANT_LOGI(LBFGSB_F32, float, 256, 5, 1, 1, 2, 4, 2, 2),      // cols <=  5120
+    LB_VARIANT_LOGI(LBFGSB_F32, float, 512, 3, 1, 2, 4, 6, 2, 1),      // cols <=  6144
+    LB_VARIANT_LOGI(LBFGSB_F32, float, 512, 4, 1, 2, 2, 4, 2, 1),      // cols <=  8192
     LB_VARIANT_LOGI(LBFGSB_F32, float, 512, 5, 1, 1, 2, 4, 2, 1),      // cols <= 10240
+    LB_VARIANT_LOGI(LBFGSB_F32, float, 512, 6, 1, 1, 2, 2, 2, 1),      // cols <= 12288
     LB_VARIANT_LOGI(LBFGSB_F32, float, 512, 10, 1, 1, 1, 2, 2, 1),     // cols <= 20480 (LDS: <= 20428)
-    // row products only: no accumulators of w, so the ring is deeper (4096 to 15872 columns: symmetric.hip).  The two-pass
+    // row products only: no accumulators of w, so the ring is deeper (4096 to 15872 columns: symmetric.hip).  A form of
+    // a few thousand variables is in the caches: rows in flight count, not bytes.  Pass, us, in the tile for 5120 columns / in
+    // its own (mean over a solve, launches that find it finished among them): fp64 n = 1200 12.4 / 7.8, 2000 13.7 / 9.9, 2400
+    // 19.9 / 13.8, 3000 21.7 / 16.3, 4000 25.5 / 22.2; fp32 1200 12.2 / 9.9, 2000 12.5 / 10.2, 3000 14.9 / 12.3, 4000 17.6 /
+    // 14.9.  The two-pass
     // organisation reads A once for these too (no transposed pass), and on rows that start on any element its kernel of four
     // rows per wave is the faster one while the caches serve much of the matrix.  Whole iterations, us, ring / k_gemv: fp64
     // n = 301 25.0 / 22.4, 1025 41.5 / 38.0, 2201 50.0 / 45.0, 3001 53.0 / 48.8, 4095 59.1 / 54.7, 15873 347 / 377, 20001
     // 535 / 630; fp32 301 25.0 / 22.1, 1025 40.8 / 37.0, 2001 42.6 / 40.6, 2501 43.8 / 42.8, 2801 44.7 / 45.6, 4095 48.8 / 50.3.
     LB_VARIANT_ROWS_ALIGNED(LBFGSB_F64, double, 256, 2, 1, 4, 8, 4, 4),  // cols <=  1024
+    LB_VARIANT_ROWS_ALIGNED(LBFGSB_F64, double, 256, 4, 1, 2, 4, 4, 2),  // cols <=  2048
+    LB_VARIANT_ROWS_ALIGNED(LBFGSB_F64, double, 512, 3, 1, 2, 6, 2, 1),  // cols <=  3072
+    LB_VARIANT_ROWS_ALIGNED(LBFGSB_F64, double, 512, 4, 1, 1, 4, 2, 1),  // cols <=  4096
     LB_VARIANT_ROWS_ALIGNED(LBFGSB_F64, double, 512, 5, 1, 2, 8, 2, 1),  // cols <=  5120
     LB_VARIANT_ROWS(LBFGSB_F64, double, 512, 20, 1, 1, 2, 2, 1), // cols <= 20480 (LDS: <= 20428)
     LB_VARIANT_ROWS_ALIGNED(LBFGSB_F32, float, 256, 1, 1, 4, 8, 4, 4),   // cols <=  1024
+    LB_VARIANT_ROWS_ALIGNED(LBFGSB_F32, float, 256, 2, 1, 4, 8, 4, 4),   // cols <=  2048
+    LB_VARIANT_ROWS(LBFGSB_F32, float, 256, 3, 1, 2, 6, 2, 2),   // cols <=  3072, on any element from kRowsAnyMin on
+    LB_VARIANT_ROWS(LBFGSB_F32, float, 256, 4, 1, 1, 4, 2, 2),   // cols <=  4096
     LB_VARIANT_ROWS(LBFGSB_F32, float, 256, 5, 1, 2, 8, 2, 2),   // cols <=  5120, on any element from kRowsAnyMin on
     LB_VARIANT_ROWS(LBFGSB_F32, float, 512, 10, 1, 1, 4, 2, 1),  // cols <= 20480 (LDS: <= 20428)
 };

@@ -1,0 +1,46 @@
+"""The single-read pass at the edges of the row widths its tiles are cut for: whole tiles, one column less, one more.
+Bounds as in test_gpu_pass_shapes.py, of a sum of at most 1.5e4 products; a quadratic form's value is a difference of sums of
+the size of its gradient."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2203_16340_amd as L
+import test_gpu_pass_shapes as shapes
+from gpu_helpers import rel_err, to_dev
+
+pytestmark = pytest.mark.gpu
+
+LSQ, L1, LOGI = L.OBJ_LSQ, L.OBJ_LSQ_L1SPLIT, L.OBJ_LOGISTIC_L2
+TILES = [(LSQ, np.float64, c) for c in (3072, 12288, 14336)] + [(LSQ, np.float32, c) for c in (3072, 6144, 12288, 14336)]
+TILES += [(LOGI, np.float64, c) for c in (1536, 3072, 12288)] + [(LOGI, np.float32, c) for c in (3072, 4096, 6144, 8192, 12288)]
+TILES += [(L1, np.float64, 3072), (L1, np.float32, 6144)]
+
+
+@pytest.mark.parametrize("kind,dtype,cols", TILES)
+@pytest.mark.parametrize("rows,more", [(517, 0), (517, -1), (517, 1), (2051, -4), (67, 4)])
+def test_around_a_tile(kind, dtype, cols, rows, more):
+    shapes._check(kind, rows, cols + more, dtype, pad=0, shift=abs(more) % 2)
+
+
+@pytest.mark.parametrize("dtype,cols", [t[1:] for t in TILES if t[0] == LOGI])
+@pytest.mark.parametrize("more", [0, -1])
+def test_rejected_first_steps(dtype, cols, more):
+    shapes.test_columns_after_a_rejected_first_trial_step(dtype, 517, cols + more)
+
+
+@pytest.mark.parametrize("dtype,n", [(np.float64, n) for n in (1026, 2048, 2050, 3072, 3074, 4094)] +
+                         [(np.float32, n) for n in (1028, 2048, 2052, 2601, 3071, 3072, 3073, 3076, 4092, 4095)])
+def test_quadratic_form(dtype, n):
+    rng = np.random.default_rng(n)
+    K = rng.standard_normal((n, n)).astype(dtype)
+    K = np.ascontiguousarray((K + K.T) / dtype(2))
+    b, x = rng.standard_normal(n), rng.standard_normal(n)
+    f_ref, g_ref, row_ref = oracle.fg(oracle.Objective(oracle.QP, K, b), x, want_rowvec=True)
+    s = L.Solver(L.OBJ_QP, to_dev(K), to_dev(b), to_dev(np.full(n, -np.inf)), to_dev(np.full(n, np.inf)), 3)
+    assert s.apass_name == "fused"
+    f, g, row = s.dbg_fg(to_dev(x), want_rowvec=True)
+    assert abs(f - f_ref) <= 1e-12 * max(abs(f_ref), np.linalg.norm(x) * np.linalg.norm(g_ref))
+    assert rel_err(g.cpu().numpy(), g_ref) <= 1e-12
+    assert rel_err(row.cpu().numpy(), row_ref) <= 1e-12
+    s.close()

@@ -71,8 +71,8 @@ MEASURED_TRAFFIC = {
     ("C5", "fused"): (8.099e9, "profiles/c5_nnls_100000x20000_f32_fused_a_pass.md @ e4ff258"),      # algorithmic 8.0e9
     ("AL2", "fused"): (8.368e8, "profiles/al2_auglag_20001x5000_f64_fused_a_pass.md @ e4ff258"),    # algorithmic 8.0004e8
     ("SVM", "fused"): (4.34e8, "profiles/svm_dual_10000x10000_f64_row_products_pass.md @ adadd23"),   # algorithmic 4.2e8
-    ("JP1G", "gram"): (1.025e8, "profiles/jp1g_joint_probability_1000x1000_f64_gram_kernel.md @ e4ff258"),   # algorithmic 0.83e8 at the final free set
-    ("JP2G", "gram"): (6.175e7, "profiles/jp2g_joint_probability_2000x1000_f64_gram_kernel.md @ e4ff258"),   # algorithmic 0.51e8
+    ("JP1G", "gram"): (9.84e7, "profiles/joint_probability_gram_traffic.md @ 742e206"),   # algorithmic 0.83e8 at the final free set
+    ("JP2G", "gram"): (5.87e7, "profiles/joint_probability_gram_traffic.md @ 742e206"),   # algorithmic 0.51e8
 }
 
 

@@ -115,10 +115,11 @@ __device__ __forceinline__ bool reduce_partials(double* __restrict__ grampart, i
 // chunk: x, g (and l, u) three chunks ahead, the free set two chunks ahead -- fixed variables contribute nothing: their
 // lanes read what the first free lane reads, and a chunk without any reads the first chunk's -- the vectors next, then the
 // products.  10 pairs, us per launch, the vector unit's kernel (77 sums per lane, three waves reading 14 vectors each, 512
-// workgroups, closing step included) / this one / this one without its closing step: n = 10^6 47.6 / 42.7 / 35.7, 2 10^6
-// 100 / 88 / 77; odd n 185 (operands staged for 2 x 2 tiles) / 45 / 38.5; 20 pairs 182 / 96.  A bare sum over the same vectors
-// takes 29 us at 10^6.  Loads straight into the operand layout, 16 vectors and 64 bytes of each per load: 41 / 90 with the
-// closing step at 10^6 / 2 10^6; three chunks in flight: slower than two.
+// workgroups, closing step included) / this one / this one without its closing step: n = 10^6 47.6 / 42.7 / 35.7 (33.1 since
+// the groups' arrivals need no cache written back), 2 10^6 100 / 88 / 77; odd n 185 (operands staged for 2 x 2 tiles) / 45 /
+// 38.5; 20 pairs 182 / 96.  A bare sum over the same vectors takes 29 us at 10^6.  Loads straight into the operand layout, 16
+// vectors and 64 bytes of each per load: 41 / 90 with the closing step at 10^6 / 2 10^6; three chunks in flight: slower than
+// two.
 // else: a few chunks in all, and what bounds it is latency: everything is requested at once, the ring slots whatever they
 // hold, and looked at when it is there.  Without the closing step, 10 pairs: n = 2000 6.9 -> 6.1 us, 5000 6.4 -> 5.6, 40 000
 // 9.2 -> 7.7; n = 3001, where the closing step was not left out, 21.0 + 5.5 (direction) -> 6.4 + 12.0.

@@ -6,7 +6,7 @@
 // in ONE trip: the scalar block, x, g, the bounds and every slot of the pair memory are requested together (which slots
 // hold pairs is looked at afterwards).  Thread e owns elements e and e + 512 from the free-set test to the direction and
 // keeps all their vectors' entries in registers; masked copies go to LDS, from where the matrix cores take the products
-// (v_mfma_f64_16x16x4, lane (i, q) supplies vector i of a block of 16 at one element, as in k_gram_mfma).  The vectors are
+// (v_mfma_f64_16x16x4, lane (i, q) supplies vector i of a block of 16 at one element, as in the Gram kernel).  The vectors are
 // ordered y | g | s, so that the blocks of products the recursion does not read -- s with s -- are left out.  The
 // recursion runs on an LDS copy of the scalar block, which goes back to memory once, with Algorithm 2's choice in it.
 //

@@ -594,6 +594,17 @@ void launch_gemv(const Dims& dm, const Geometry& ge, const Buffers& bf, const AP
 // w partials = A^T psi_src (psi_src: Buffers::psi after an evaluation, Buffers::t after a direction pass)
 void launch_gemvt_from(const Dims& dm, const Geometry& ge, const Buffers& bf, const void* A, const double* psi_src,
                        int check_status, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// Do the single-read passes leave the matrix in the chip's memory-side cache (256 MB), from one iteration to the next?  Ordinary
+// loads do, non-temporal ones pass it by; a matrix that does not fit only evicts itself.  Whole iterations, us, non-temporal /
+// ordinary: fp64 25000 x 1000 (200 MB) 67 / 63, 4000 x 6000 71 / 64, 2000 x 10000 72 / 63.5, 1500 x 16000 83 / 74, 8000 x 2000
+// 54 / 53; fp32 4000 x 3001 50 / 45, 18000 x 3001 78 / 71, 3000 x 16000 80 / 71; logistic 400000 x 100 59 / 54, 20000 x 3000
+// 85 / 78; 3 to 20 MB the same.  Beyond: 280 MB 99 / 91, 288 MB 80.1 / 79.3, 333 MB 90.6 / 92.2, 340 MB 105 / 110, 320 MB
+// logistic 101 / 106; from 400 MB on up to 14 % slower.  Quadratic forms (row products only, a deeper ring): pass at 3000 fp64
+// variables 16.4 / 16.6, 3500 fp32 14.6 / 15.1, so not there.
+constexpr int64_t kMemorySideCache = (int64_t)256 << 20;
+inline int matrix_cached(const Dims& dm) {
+    return dm.kind != LBFGSB_OBJ_QP && dm.rows * dm.cols * (dm.dtype == LBFGSB_F32 ? 4 : 8) <= kMemorySideCache;
+}
 bool fused_shape_ok(const Dims& dm, bool aligned, int* variant, int* blocks);
 bool fused_ls_first_ok(const Dims& dm, const Geometry& ge);   // APassArgs::ls_first may be set (its LDS fits)
 hipError_t fused_prepare(const Dims& dm, const Geometry& ge);   // once per solver, before the first launch_fused

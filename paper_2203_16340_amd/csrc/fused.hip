@@ -23,42 +23,53 @@ struct Variant {
     int trans;          // 1: with the transposed accumulation, 0: row products only (quadratic form, symmetric matrix)
     int nt, kc, r;      // threads, 16-byte chunks per thread and row, rows per stage
     int wgs_per_cu;     // workgroups per compute unit the launch is sized for
-    // [0] rows on 16-byte boundaries and whole chunks, [1] rows that start on any element, any number of columns (null: none)
-    const void* kernel[2]; // for hipFuncSetAttribute
-    LaunchFn launch[2];
+    // [.][0] rows on 16-byte boundaries and whole chunks, [.][1] rows that start on any element, any number of columns (null:
+    // none); [0][.] with non-temporal loads of the matrix, [1][.] with ordinary ones (matrix_cached)
+    const void* kernel[2][2]; // for hipFuncSetAttribute
+    LaunchFn launch[2][2];
     size_t (*lds)(int64_t cols);
     // logistic only: the instantiation for the direction pass (same geometry, deeper ring: its row operation is
     // one exponential and one division, which leaves the registers for it)
-    const void* kernel_dir[2];
-    LaunchFn launch_dir[2];
+    const void* kernel_dir[2][2];
+    LaunchFn launch_dir[2][2];
 };
 
-template <typename T, int NT, int KCU, int U, int R, int NB, int WPE, int LOGI, int KR, bool TRANS, bool ANY>
+template <typename T, int NT, int KCU, int U, int R, int NB, int WPE, int LOGI, int KR, bool TRANS, bool ANY, bool CACHED>
 void launch_variant(const Dims& dm, int64_t rows_per_wg, int blocks, size_t lds, const Buffers& bf, const APassArgs& a,
                     hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-    hipExtLaunchKernelGGL((ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, ANY>), dim3(blocks), dim3(NT), lds, st, ev0, ev1,
+    hipExtLaunchKernelGGL((ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, ANY, CACHED>), dim3(blocks), dim3(NT), lds, st, ev0, ev1,
                           0, (const T*)a.A, dm.ld, dm.rows, dm.cols, rows_per_wg, a, bf.scal, bf.row, bf.t, bf.wpart,
                           bf.losspart);
 }
 
+#define LB_KERNEL(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, ANY, CACHED)                                                   \
+    (const void*)ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0, ANY, CACHED>
+#define LB_LAUNCH(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, ANY, CACHED)                                                   \
+    launch_variant<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0, ANY, CACHED>
 #define LB_KERNELS(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS)                                                               \
-    {(const void*)ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0, false>,                              \
-     (const void*)ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0, true>},                              \
-    {launch_variant<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0, false>,                                               \
-     launch_variant<T, NT, KCU, U, R, NB, WPE, LOGI, KR, (TRANS) != 0, true>}
+    {{LB_KERNEL(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, false, false), LB_KERNEL(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, true, false)},  \
+     {LB_KERNEL(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, false, true), LB_KERNEL(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, true, true)}},   \
+    {{LB_LAUNCH(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, false, false), LB_LAUNCH(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, true, false)},  \
+     {LB_LAUNCH(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, false, true), LB_LAUNCH(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS, true, true)}}
 #define LB_VARIANT_FULL(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS, KR, TRANS)                                                \
     {dt, LOGI, TRANS, NT, (KCU) * (U), R, WGS, LB_KERNELS(T, NT, KCU, U, R, NB, WPE, LOGI, KR, TRANS),                       \
-     ring::lds_bytes<T, NT, (KCU) * (U), KR, R>, {nullptr, nullptr}, {nullptr, nullptr}}
+     ring::lds_bytes<T, NT, (KCU) * (U), KR, R>, {}, {}}
 #define LB_VARIANT_LOGI(dt, T, NT, KCU, U, R, NB, NBDIR, WPE, WGS)                                                           \
     {dt, 1, 1, NT, (KCU) * (U), R, WGS, LB_KERNELS(T, NT, KCU, U, R, NB, WPE, 1, 0, 1),                                      \
      ring::lds_bytes<T, NT, (KCU) * (U), 0, R>, LB_KERNELS(T, NT, KCU, U, R, NBDIR, WPE, 2, 0, 1)}
 #define LB_VARIANT_KR(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS, KR) LB_VARIANT_FULL(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS, KR, 1)
 #define LB_VARIANT(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS) LB_VARIANT_FULL(dt, LOGI, T, NT, KCU, U, R, NB, WPE, WGS, 0, 1)
-#define LB_VARIANT_ROWS(dt, T, NT, KCU, U, R, NB, WPE, WGS) LB_VARIANT_FULL(dt, 0, T, NT, KCU, U, R, NB, WPE, WGS, 0, 0)
+// (a quadratic form is not read with ordinary loads: matrix_cached)
+#define LB_VARIANT_ROWS(dt, T, NT, KCU, U, R, NB, WPE, WGS)                                                                  \
+    {dt, 0, 0, NT, (KCU) * (U), R, WGS,                                                                                      \
+     {{LB_KERNEL(T, NT, KCU, U, R, NB, WPE, 0, 0, 0, false, false), LB_KERNEL(T, NT, KCU, U, R, NB, WPE, 0, 0, 0, true, false)}, {}},  \
+     {{LB_LAUNCH(T, NT, KCU, U, R, NB, WPE, 0, 0, 0, false, false), LB_LAUNCH(T, NT, KCU, U, R, NB, WPE, 0, 0, 0, true, false)}, {}},  \
+     ring::lds_bytes<T, NT, (KCU) * (U), 0, R>, {}, {}}
 #define LB_VARIANT_ROWS_ALIGNED(dt, T, NT, KCU, U, R, NB, WPE, WGS)                                                          \
-    {dt, 0, 0, NT, (KCU) * (U), R, WGS, {(const void*)ring::k_fused_ring<T, NT, KCU, U, R, NB, WPE, 0, 0, false, false>, nullptr}, \
-     {launch_variant<T, NT, KCU, U, R, NB, WPE, 0, 0, false, false>, nullptr}, ring::lds_bytes<T, NT, (KCU) * (U), 0, R>,     \
-     {nullptr, nullptr}, {nullptr, nullptr}}
+    {dt, 0, 0, NT, (KCU) * (U), R, WGS,                                                                                      \
+     {{LB_KERNEL(T, NT, KCU, U, R, NB, WPE, 0, 0, 0, false, false), nullptr}, {}},                                           \
+     {{LB_LAUNCH(T, NT, KCU, U, R, NB, WPE, 0, 0, 0, false, false), nullptr}, {}},                                           \
+     ring::lds_bytes<T, NT, (KCU) * (U), 0, R>, {}, {}}
 
 // Ordered by capacity within a (matrix type, objective family) group: the first variant of the group
 // whose NT*KC*VEC columns cover a row and whose LDS need (v for every column) fits is used.  (Narrower rows --
@@ -173,7 +184,7 @@ bool fused_shape_ok(const Dims& dm, bool aligned, int* variant, int* blocks) {
             continue;
         if ((int64_t)v.nt * v.kc * vec < dm.cols) continue;
         if (v.lds(dm.cols) > kLdsPerWorkgroup - 256) continue;   // (a few bytes of static LDS come on top)
-        if (!aligned && (!v.launch[1] || (!v.trans && dm.cols < kRowsAnyMin))) return false;
+        if (!aligned && (!v.launch[0][1] || (!v.trans && dm.cols < kRowsAnyMin))) return false;
         const int64_t rpw = rows_per_wg_for(dm, v);
         *variant = i;
         *blocks = (int)((dm.rows + rpw - 1) / rpw);
@@ -193,10 +204,10 @@ hipError_t fused_prepare(const Dims& dm, const Geometry& ge) {
     const size_t cap = kLdsPerWorkgroup - 256;   // the kernels also hold a few bytes of static LDS
     if (most > cap) most = cap;
     if (v.lds(dm.cols) > most) most = v.lds(dm.cols);
-    const int any = ge.vec == 1;
-    hipError_t e = hipFuncSetAttribute(v.kernel[any], hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
-    if (e == hipSuccess && v.kernel_dir[any])   // (may also hold two numbers per row of a workgroup: whatever fits)
-        e = hipFuncSetAttribute(v.kernel_dir[any], hipFuncAttributeMaxDynamicSharedMemorySize, (int)cap);
+    const int any = ge.vec == 1, cached = matrix_cached(dm);
+    hipError_t e = hipFuncSetAttribute(v.kernel[cached][any], hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+    if (e == hipSuccess && v.kernel_dir[cached][any])   // (may also hold two numbers per row of a workgroup: whatever fits)
+        e = hipFuncSetAttribute(v.kernel_dir[cached][any], hipFuncAttributeMaxDynamicSharedMemorySize, (int)cap);
     return e;
 }
 
@@ -207,7 +218,7 @@ static size_t ls_first_lds(const Dims& dm, const Variant& v) { return (size_t)ro
 bool fused_ls_first_ok(const Dims& dm, const Geometry& ge) {
     if (ge.narrow_variant >= 0) return true;
     const Variant& v = kVariants[ge.fused_variant];
-    return v.launch_dir[0] && v.lds(dm.cols) + ls_first_lds(dm, v) <= kLdsPerWorkgroup - 256;
+    return v.launch_dir[0][0] && v.lds(dm.cols) + ls_first_lds(dm, v) <= kLdsPerWorkgroup - 256;
 }
 
 void launch_fused(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, hipStream_t st,
@@ -221,8 +232,8 @@ void launch_fused(const Dims& dm, const Geometry& ge, const Buffers& bf, const A
         return;
     }
     const Variant& v = kVariants[ge.fused_variant];
-    const int any = ge.vec == 1;
-    auto launch = (a.mode == kRowLogiSpec && v.launch_dir[any]) ? v.launch_dir[any] : v.launch[any];
+    const int any = ge.vec == 1, cached = matrix_cached(dm);
+    auto launch = (a.mode == kRowLogiSpec && v.launch_dir[cached][any]) ? v.launch_dir[cached][any] : v.launch[cached][any];
     const size_t extra = a.mode == kRowLogiSpec && a.ls_first ? ls_first_lds(dm, v) : 0;
     launch(dm, rows_per_wg_for(dm, v), ge.fused_blocks, v.lds(dm.cols) + extra, bf, a, st, ev0, ev1);
 }

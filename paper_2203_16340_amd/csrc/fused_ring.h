@@ -275,7 +275,8 @@ inline size_t lds_bytes(int64_t cols) {
 // ANY = true: rows may start on any element and the number of columns may be anything from one chunk up (see `full`
 // below).  A parameter and not a test: with the ragged chunk's arithmetic in every instantiation the logistic pass at
 // 200 000 x 2000 fp32 took 1.3 % longer (other waits in its row loop), and rows on 16-byte boundaries need none of it.
-template <typename T, int NT, int KCU, int U, int R, int NB, int WPE, int LOGI, int KR, bool TRANS, bool ANY>
+// CACHED: ordinary loads of A instead of non-temporal ones (matrix_cached in common.h).
+template <typename T, int NT, int KCU, int U, int R, int NB, int WPE, int LOGI, int KR, bool TRANS, bool ANY, bool CACHED>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void k_fused_ring(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, int64_t rows_per_wg, APassArgs a,
                   Scal* __restrict__ scal, double* __restrict__ row, double* __restrict__ t,
@@ -334,7 +335,9 @@ void k_fused_ring(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t col
         for (int k = 0; k < KCU; ++k) {
             unsigned c = cb + (unsigned)((j * KCU + k) * kStride);
             c = c < (unsigned)(icols - VEC) ? c : (unsigned)(icols - VEC);
-            dst[k] = __builtin_nontemporal_load(reinterpret_cast<const typename RawMem<T, ANY>::type*>(rp + c * (unsigned)sizeof(T)));
+            const auto* from = reinterpret_cast<const typename RawMem<T, ANY>::type*>(rp + c * (unsigned)sizeof(T));
+            if constexpr (CACHED) dst[k] = *from;
+            else dst[k] = __builtin_nontemporal_load(from);
         }
     };
     // The ring is primed as early as it can be without getting in the way: loads return in the order they were issued,

@@ -57,7 +57,7 @@ __device__ __forceinline__ double row_sums(double (&a)[S], int lane) {
 // mode kRowPsiGiven (LOGI 0): w = A^T psi for the weights the launch is given; nothing else is computed or stored.
 // OWN: Algorithm 2's choice is made here, from the direction kernel's partial sums (direction passes only); else it is read
 // from the scalar block.  (A parameter and not a test: with both in one kernel a pass behind k_small_step took 0.3 us longer.)
-template <typename T, int L, int KC, int S, int LOGI, bool OWN>
+template <typename T, int L, int KC, int S, int LOGI, bool OWN, bool CACHED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
 void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, APassArgs a, Scal* __restrict__ scal,
               double* __restrict__ row, double* __restrict__ t, const double* __restrict__ psi_given,
@@ -105,7 +105,8 @@ void k_narrow(const T* __restrict__ A, int64_t ld, int64_t rows, int64_t cols, A
         for (int k = 0; k < KC; ++k) {
             unsigned o = off[k];
             asm volatile("" : "+v"(o));                      // (opaque here: scalar base + 32-bit vector offset)
-            dst[k] = __builtin_nontemporal_load(reinterpret_cast<const MemT*>(rp + o));
+            if constexpr (CACHED) dst[k] = *reinterpret_cast<const MemT*>(rp + o);
+            else dst[k] = __builtin_nontemporal_load(reinterpret_cast<const MemT*>(rp + o));
         }
     };
     // what the row operation reads, for the row whose sum this lane will hold

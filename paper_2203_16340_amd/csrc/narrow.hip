@@ -10,30 +10,35 @@ typedef void (*NarrowLaunch)(const Dims&, int, const Buffers&, const APassArgs&,
 
 struct NarrowVariant {
     int dtype, lanes, kc, sets;
-    NarrowLaunch launch[3];
-    NarrowLaunch own[2];   // the direction passes that make Algorithm 2's choice themselves, quadratic and logistic (null: none)
+    // [0] with non-temporal loads of the matrix, [1] with ordinary ones (matrix_cached)
+    NarrowLaunch launch[2][3];
+    NarrowLaunch own[2][2];   // the direction passes that make Algorithm 2's choice themselves, quadratic and logistic (null: none)
 };
 
-template <typename T, int L, int KC, int S, int LOGI, bool OWN>
+template <typename T, int L, int KC, int S, int LOGI, bool OWN, bool CACHED>
 void launch_t(const Dims& dm, int blocks, const Buffers& bf, const APassArgs& a, const double* psi, hipStream_t st,
               hipEvent_t ev0, hipEvent_t ev1) {
-    hipExtLaunchKernelGGL((narrow::k_narrow<T, L, KC, S, LOGI, OWN>), dim3(blocks), dim3(kBlock), 0, st, ev0, ev1, 0,
+    hipExtLaunchKernelGGL((narrow::k_narrow<T, L, KC, S, LOGI, OWN, CACHED>), dim3(blocks), dim3(kBlock), 0, st, ev0, ev1, 0,
                           (const T*)a.A, dm.ld, dm.rows, dm.cols, a, bf.scal, bf.row, bf.t, psi, bf.wpart, bf.losspart);
 }
 // With few lanes to a row (up to 192 fp32 or 96 fp64 columns) vectors are short for most m (small_step_ok) and nothing is
 // gained by the choice being made here; beyond, it saves the direction kernel's arrival and up to 10 pairs the Gram
 // kernel's too.  Whole iterations, us, choice read / made here: lasso fp64 122 x 1024 33.2 / 30.6, 2441 x 1024 35.0 / 32.2,
 // 48828 x 1024 89.9 / 86.8; least squares fp32 4882 x 1024 35.7 / 32.4, m = 30 657 x 380 41.2 / 39.3.
-template <typename T, int L, int KC, int S, int LOGI>
+template <typename T, int L, int KC, int S, int LOGI, bool CACHED>
 constexpr NarrowLaunch own_t() {
-    if constexpr (L >= 32) return launch_t<T, L, KC, S, LOGI, true>;
+    if constexpr (L >= 32) return launch_t<T, L, KC, S, LOGI, true, CACHED>;
     else return nullptr;
 }
 
-#define LB_NARROW(dt, T, L, KC, S) {dt, L, KC, S, {launch_t<T, L, KC, S, 0, false>, launch_t<T, L, KC, S, 1, false>, launch_t<T, L, KC, S, 2, false>},  \
-                                    {own_t<T, L, KC, S, 0>(), own_t<T, L, KC, S, 2>()}}
+#define LB_NARROW_ALL(T, L, KC, S, C) {launch_t<T, L, KC, S, 0, false, C>, launch_t<T, L, KC, S, 1, false, C>, launch_t<T, L, KC, S, 2, false, C>}
+#define LB_NARROW(dt, T, L, KC, S) {dt, L, KC, S, {LB_NARROW_ALL(T, L, KC, S, false), LB_NARROW_ALL(T, L, KC, S, true)},               \
+                                    {{own_t<T, L, KC, S, 0, false>(), own_t<T, L, KC, S, 2, false>()},                                  \
+                                     {own_t<T, L, KC, S, 0, true>(), own_t<T, L, KC, S, 2, true>()}}}
 // the quadratic kinds only (the logistic row operations do not fit the registers beside the rows)
-#define LB_NARROW_QUAD(dt, T, L, KC, S) {dt, L, KC, S, {launch_t<T, L, KC, S, 0, false>, nullptr, nullptr}, {own_t<T, L, KC, S, 0>(), nullptr}}
+#define LB_NARROW_QUAD(dt, T, L, KC, S) {dt, L, KC, S, {{launch_t<T, L, KC, S, 0, false, false>, nullptr, nullptr},                      \
+                                                        {launch_t<T, L, KC, S, 0, false, true>, nullptr, nullptr}},                     \
+                                         {{own_t<T, L, KC, S, 0, false>(), nullptr}, {own_t<T, L, KC, S, 0, true>(), nullptr}}}
 // By capacity L * KC in 16-byte chunks; the first whose capacity covers a row is used.  The line to the ring kernel is
 // where it measured faster (0.4 GB matrices, us per pass, this kernel / ring): fp32 least squares 100 columns 69 / 271,
 // 512 69 / 70, 1024 66 / 70, 1536 66 / 72, 1800 76 / 75; fp32 logistic 100 81 / 390, 512 72 / 89, 1000 66 / 94,
@@ -65,7 +70,7 @@ bool narrow_shape_ok(const Dims& dm, int* variant, int* blocks) {
     for (int i = 0; i < kNumNarrow; ++i) {
         const NarrowVariant& v = kNarrow[i];
         if (v.dtype != dm.dtype || v.lanes * v.kc < chunks || dm.rows < 64 / v.lanes) continue;
-        if (dm.kind == LBFGSB_OBJ_LOGISTIC_L2 && !v.launch[2]) continue;
+        if (dm.kind == LBFGSB_OBJ_LOGISTIC_L2 && !v.launch[0][2]) continue;
         const int64_t rt = v.sets * (64 / v.lanes), tiles = (dm.rows + rt - 1) / rt;
         const int64_t b = (tiles + kWaves - 1) / kWaves;
         *variant = i;
@@ -76,14 +81,15 @@ bool narrow_shape_ok(const Dims& dm, int* variant, int* blocks) {
 }
 
 bool narrow_makes_choice(const Geometry& ge) {
-    return kNarrow[ge.narrow_variant].own[0] && ge.dir_blocks <= kPassDirBlocksMax;
+    return kNarrow[ge.narrow_variant].own[0][0] && ge.dir_blocks <= kPassDirBlocksMax;
 }
 
 void launch_narrow(const Dims& dm, const Geometry& ge, const Buffers& bf, const APassArgs& a, const double* psi,
                    hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     const NarrowVariant& v = kNarrow[ge.narrow_variant];
     const int logi = a.mode == kRowLogiSpec ? 2 : (a.mode == kRowLogiEval ? 1 : 0);
-    (a.select_p && a.dir_blocks > 0 ? v.own[logi / 2] : v.launch[logi])(dm, ge.fused_blocks, bf, a, psi, st, ev0, ev1);
+    const int cached = matrix_cached(dm);
+    (a.select_p && a.dir_blocks > 0 ? v.own[cached][logi / 2] : v.launch[cached][logi])(dm, ge.fused_blocks, bf, a, psi, st, ev0, ev1);
 }
 
 }  // namespace lb

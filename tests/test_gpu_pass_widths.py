@@ -3,11 +3,12 @@ Bounds as in test_gpu_pass_shapes.py, of a sum of at most 1.5e4 products; a quad
 the size of its gradient."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_2203_16340_amd as L
 import test_gpu_pass_shapes as shapes
-from gpu_helpers import rel_err, to_dev
+from gpu_helpers import DEV, rel_err, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +45,40 @@ def test_quadratic_form(dtype, n):
     assert rel_err(g.cpu().numpy(), g_ref) <= 1e-12
     assert rel_err(row.cpu().numpy(), row_ref) <= 1e-12
     s.close()
+
+
+# both sides of the size up to which the matrix is left in the memory-side cache, for every family of kernels that reads it once
+@pytest.mark.parametrize("kind,dtype,cols", [(LSQ, np.float64, 301), (LSQ, np.float32, 1000), (LSQ, np.float64, 3001), (LSQ, np.float32, 3000),
+                                             (LSQ, np.float64, 22529), (L1, np.float32, 6001), (LOGI, np.float32, 100), (LOGI, np.float64, 701),
+                                             (LOGI, np.float32, 3001), (LOGI, np.float64, 2000), (L.OBJ_QP, np.float64, None), (L.OBJ_QP, np.float32, None)])
+@pytest.mark.parametrize("above", [False, True])
+def test_around_the_cache_size(kind, dtype, cols, above):
+    size = np.dtype(dtype).itemsize
+    if cols is None:                                         # rows = cols; above: past the kernels that read half of it
+        cols = rows = (16000 if above else 2048) if size == 8 else (16100 if above else 4092)
+    else:
+        rows = (1 << 28) // (size * cols) + (1 if above else 0)
+    gen = torch.Generator(device=DEV).manual_seed(cols)
+    A = torch.randn(rows, cols, generator=gen, device=DEV, dtype=torch.float64 if size == 8 else torch.float32)
+    n = 2 * cols if kind == L1 else cols
+    x = torch.rand(n, generator=gen, device=DEV, dtype=torch.float64) * 0.4
+    b = torch.randn(rows, generator=gen, device=DEV, dtype=torch.float64)
+    if kind == LOGI:
+        b = torch.where(b >= 0, 1.0, -1.0).double()
+    if kind == L.OBJ_QP:
+        A = ((A + A.T) / 2).contiguous()
+    l, u = torch.zeros(n, dtype=torch.float64, device=DEV), torch.full((n,), np.inf, dtype=torch.float64, device=DEV)
+    kw = dict(lam=0.3 if kind == L1 else 0.0, mu=1e-3 if kind == LOGI else 0.0)
+    one, two = (L.Solver(kind, A, b, l, u, 5, options=L.default_options(tol=0.0, refresh_every=0, a_pass=p), **kw)
+                for p in (L.APASS_AUTO, L.APASS_TWO_PASS))
+    assert (one.apass_name, two.apass_name) == ("fused", "two_pass")
+    (f1, g1, r1), (f2, g2, r2) = (s.dbg_fg(x, want_rowvec=True) for s in (one, two))
+    assert abs(f1 - f2) <= 1e-12 * max(abs(f2), float(x.norm() * g2.norm()))
+    assert float((g1 - g2).norm()) <= 1e-12 * float(g2.norm()) and float((r1 - r2).norm()) <= 1e-12 * float(r2.norm())
+    if kind != L.OBJ_QP:                                     # (indefinite here)
+        for s in (one, two):
+            s.set_x(x)
+            for _ in range(3):
+                s.step(False)
+        assert float((one.x() - two.x()).norm()) <= 1e-10 * float(two.x().norm())
+    one.close(), two.close()

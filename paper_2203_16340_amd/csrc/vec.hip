@@ -902,11 +902,11 @@ __global__ __launch_bounds__(kBlock) void k_ls_logistic(Dims dm, Opts op, int fi
         const double a = fmin(1.0, scal->alpha_ub);
         const double df = first_step_difference(dm, scal, losspart, first_parts, a, red);
         if (isfinite(df) && df <= op.c1 * a * scal->gp) {
+            // (the update kernel leaves this step pending, and the trial is counted when that is applied)
             if (blockIdx.x == 0 && tid == 0) {
                 scal->ls_ok = 1;
                 scal->spec_ok = 1;
                 scal->backtracks = 0;
-                scal->fevals += 1;
                 scal->alpha = a;
             }
             return;

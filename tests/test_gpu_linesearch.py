@@ -145,6 +145,24 @@ def test_steps_enqueued_without_waiting_survive_rejected_first_steps(case):
     a.close(); b.close()
 
 
+@pytest.mark.parametrize("cols,a_pass", [(80, L.APASS_FUSED), (1201, L.APASS_AUTO), (80, L.APASS_TWO_PASS)],
+                         ids=["short_rows", "ring", "two_pass"])
+@pytest.mark.parametrize("waited", [True, False], ids=["waited", "enqueued"])
+def test_evaluations_are_the_trials_of_the_history(cols, a_pass, waited):
+    """fevals counts the evaluation at x0 and every trial step once: accepted first trial steps behind a rejected one (the full
+    launch sequence) as well as those of the short sequence."""
+    prob = workloads.logistic(dtype=np.float64, **{**LOGISTIC_CASES[0], "cols": cols})
+    s = L.solver_for_problem(prob, DEV, tol=0.0, a_pass=a_pass)
+    for _ in range(16):
+        s.step(want_info=waited)
+    info = s.info()
+    bts = [r.backtracks for r in s.history()]
+    assert info.iters == len(bts) == 16 and info.memory_resets == 0
+    assert max(bts) > 0 and bts[bts.index(max(bts)) + 1:].count(0) > 0      # accepted first steps behind a rejection
+    assert info.fevals == 1 + sum(b + 1 for b in bts), bts
+    s.close()
+
+
 def test_a_very_tall_narrow_matrix():
     """5.3 million rows of 8 columns: more than ten thousand rows per workgroup, which the ring kernel could not keep two
     numbers each of in LDS.  Rows this short go to the kernel that sums the first trial step's loss differences as it goes

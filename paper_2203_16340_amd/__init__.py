@@ -24,7 +24,7 @@ EXPORTS = [
     "lbfgsb_last_error", "lbfgsb_default_options", "lbfgsb_workspace_bytes", "lbfgsb_create", "lbfgsb_set_x",
     "lbfgsb_step", "lbfgsb_solve", "lbfgsb_solve_static", "lbfgsb_get_history", "lbfgsb_get_info", "lbfgsb_get_x", "lbfgsb_get_g", "lbfgsb_destroy",
     "lbfgsb_enable_apass_timing", "lbfgsb_apass_timing", "lbfgsb_apass_name", "lbfgsb_dbg_fg",
-    "lbfgsb_dbg_free_mask", "lbfgsb_dbg_two_loop", "lbfgsb_dbg_project_direction",
+    "lbfgsb_dbg_free_mask", "lbfgsb_dbg_two_loop", "lbfgsb_dbg_project_direction", "lbfgsb_dbg_elementary",
     "lbfgsb_auglag_default_options", "lbfgsb_auglag_workspace_bytes", "lbfgsb_auglag_create", "lbfgsb_auglag_solve",
     "lbfgsb_auglag_get_x", "lbfgsb_auglag_get_lambda", "lbfgsb_auglag_inner", "lbfgsb_auglag_destroy",
     "lbfgsb_auglag_rows_workspace_bytes", "lbfgsb_auglag_create_rows",
@@ -140,6 +140,8 @@ def lib():
         L.lbfgsb_dbg_two_loop.argtypes = [vp, vp, vp, vp, C.c_int, vp, vp, vp, C.POINTER(C.c_int)]
         L.lbfgsb_dbg_project_direction.restype = C.c_int
         L.lbfgsb_dbg_project_direction.argtypes = [vp, vp, vp, vp, vp, C.POINTER(C.c_int), C.POINTER(dbl)]
+        L.lbfgsb_dbg_elementary.restype = C.c_int
+        L.lbfgsb_dbg_elementary.argtypes = [C.c_int, i64, vp, vp]
         L.lbfgsb_auglag_default_options.restype = None
         L.lbfgsb_auglag_default_options.argtypes = [C.POINTER(AuglagOptions)]
         L.lbfgsb_auglag_workspace_bytes.restype = C.c_size_t

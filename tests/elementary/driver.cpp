@@ -1,5 +1,5 @@
-// log_d, log1p_d and quotient_d of the kernels, compiled for the host (the seed of the reciprocal has 24 bits here, no more than the
-// device's), against long double.  Prints the largest error in units of the last place per range, then the special values.
+// log_d, log1p_d and quotient_d of the kernels, compiled for the host (the seed of the reciprocal is worse here than the device's),
+// against long double.  Prints the largest error in units of the last place per range, then the special values.
 #include <algorithm>
 #include <cstdio>
 #include <random>
@@ -17,12 +17,15 @@ int main() {
     std::uniform_real_distribution<double> unit(0.0, 1.0);
     struct Range { bool plus_one, logarithmic; double lo, hi; };
     const Range ranges[] = {{false, false, 0.5, 2.0},  {false, false, 0.999, 1.001}, {false, true, 1e-300, 1e300}, {false, true, 1e-320, 1e-300},
-                            {true, false, -0.5, 1.0},  {true, false, -0.999999, -0.4}, {true, true, 1e-25, 1.0},   {true, true, 1e-2, 1e200}};
+                            {true, false, -0.5, 1.0},  {true, false, -0.999999, -0.4}, {true, true, 1e-25, 1.0},   {true, true, 1e-2, 1e200},
+                            {true, true, 1e-16, 1e-6}, {true, true, -1e-16, -1e-6}};
     for (const Range& r : ranges) {
         double worst = 0.0;
         for (int i = 0; i < 400000; ++i) {
             const double t = unit(gen);
-            const double x = r.logarithmic ? std::exp(std::log(r.lo) + t * (std::log(r.hi) - std::log(r.lo))) : r.lo + t * (r.hi - r.lo);
+            const double sign = r.logarithmic && r.lo < 0.0 ? -1.0 : 1.0;
+            const double x = r.logarithmic ? sign * std::exp(std::log(sign * r.lo) + t * (std::log(sign * r.hi) - std::log(sign * r.lo)))
+                                           : r.lo + t * (r.hi - r.lo);
             const double err = r.plus_one ? ulps(lb::log1p_d(x), log1pl((long double)x)) : ulps(lb::log_d(x), logl((long double)x));
             if (!(err <= worst)) worst = err;
         }

@@ -20,7 +20,7 @@ def output(tmp_path_factory):
 
 def test_errors(output):
     lines = [line.split() for line in output if line.startswith("range")]
-    assert len(lines) == 8
+    assert len(lines) == 10
     for _, name, lo, hi, worst in lines:
         assert float(worst) <= 0.7, (name, lo, hi, worst)
 

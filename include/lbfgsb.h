@@ -378,8 +378,8 @@ int lbfgsb_dbg_two_loop(lbfgsb_solver* s, const double* S, const double* Y, cons
 int lbfgsb_dbg_project_direction(lbfgsb_solver* s, const double* x, const double* g, const double* d,
                                  double* p, int* branch_host, double* alpha_ub_host);
 
-/* The kernels' own elementary functions at n arguments (x, y on the device; which = 0: log x, 1: log(1 + x), 2: 1 / (1 + exp(-x))
- * as the logistic objective forms it).  Needs no solver; runs on the null stream. */
+/* The kernels' own elementary functions at n arguments (x, y on the device).  which = 0: log x, 1: log(1 + x), and the quotients of
+ * the logistic function, for x in [0, 1], 2: 1 / (1 + x), 3: x / (1 + x).  Needs no solver; runs on the null stream. */
 int lbfgsb_dbg_elementary(int which, int64_t n, const double* x, double* y);
 
 #ifdef __cplusplus

@@ -245,7 +245,7 @@ Dims make_dims(int64_t n, int m, const lbfgsb_objective* o) {
 
 __global__ __launch_bounds__(kBlock) void k_dbg_elementary(int which, int64_t n, const double* __restrict__ x, double* __restrict__ y) {
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
-        y[i] = which == 0 ? log_d(x[i]) : (which == 1 ? log1p_d(x[i]) : sigmoid_d(x[i]));
+        y[i] = which == 0 ? log_d(x[i]) : (which == 1 ? log1p_d(x[i]) : quotient_d(which == 2 ? 1.0 : x[i], 1.0 + x[i]));
 }
 
 void enqueue_step(lbfgsb_solver* s);
@@ -1215,7 +1215,7 @@ int lbfgsb_dbg_project_direction(lbfgsb_solver* s, const double* x, const double
 }
 
 int lbfgsb_dbg_elementary(int which, int64_t n, const double* x, double* y) {
-    if (which < 0 || which > 2 || n <= 0 || !x || !y) return fail(LBFGSB_E_INVALID_ARG, "which must be 0, 1 or 2, n > 0, x and y not NULL");
+    if (which < 0 || which > 3 || n <= 0 || !x || !y) return fail(LBFGSB_E_INVALID_ARG, "which must be 0 to 3, n > 0, x and y not NULL");
     const int64_t blocks = (n + kBlock - 1) / kBlock;
     hipLaunchKernelGGL(k_dbg_elementary, dim3((unsigned)(blocks > 4096 ? 4096 : blocks)), dim3(kBlock), 0, nullptr, which, n, x, y);
     HIP_TRY(hipGetLastError());

@@ -62,6 +62,42 @@ __device__ __forceinline__ void recursion_in_registers(const double* G, int Vp, 
     coef_s = coef;
 }
 
+// The same for more pairs, whose triangular solves are longer: the rows stay as they are and each step divides by rho itself, so
+// that an entry is rounded once (scaled rows add a rounding to each; the sums are those of the loops in memory, bit for bit).
+template <int K>
+__device__ __forceinline__ void recursion_in_registers_unscaled(const double* G, int Vp, int c, int i, int ic, bool pass,
+                                                                unsigned long long pm, double inv, double rho_yn, double& alpha_i,
+                                                                double& coef_s, double& gamma) {
+    double gsy[K], gyy[K], gys[K];
+    const double *srow = G + ic * Vp, *yrow = G + (c + ic) * Vp;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int kc = k < c ? k : (c > 0 ? c - 1 : 0);       // (uniform)
+        gsy[k] = srow[c + kc];                                // <s_i, y_k>
+        gyy[k] = yrow[c + kc];                                // <y_i, y_k>
+        gys[k] = yrow[kc];                                    // <y_i, s_k>
+    }
+    const double inv_p = pass ? inv : 0.0;
+    double part = pass ? srow[2 * c] : 0.0;                   // <s_i, g>
+    double tsum = yrow[2 * c];                                // <y_i, g>
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        gsy[k] = pass && k > i ? gsy[k] : 0.0;
+        gys[k] = pass && k < i ? gys[k] : 0.0;
+    }
+#pragma unroll
+    for (int k = K - 1; k >= 0; --k) part = fma(-lane_value(part * inv_p, k), gsy[k], part);
+    const double alpha = part * inv_p;
+    if (c > 0 && ((pm >> (c - 1)) & 1ull)) gamma = lane_value(rho_yn, c - 1);
+#pragma unroll
+    for (int k = 0; k < K; ++k) tsum = fma(-lane_value(alpha, k), gyy[k], tsum);
+    double by = pass ? gamma * tsum : 0.0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) by = fma(lane_value(fma(-by, inv_p, alpha), k), gys[k], by);
+    alpha_i = alpha;
+    coef_s = fma(-by, inv_p, alpha);
+}
+
 // The recursion of Algorithm 3 on coefficients, by one wave (threads 0..63) of the calling workgroup, and the stopping test by
 // another (which reads and writes other fields of the scalar block): called by all threads, at least 128, with a barrier before
 // anybody reads either's results.  G: Vp x Vp (LDS), row-major, vectors ordered s^0..s^{c-1}, y^0..y^{c-1}, g.  gg = sum g[S]^2, pginf = max KKT residual, nfixed = #fixed,
@@ -96,7 +132,7 @@ __device__ __forceinline__ void recursion_on_coefficients(const double* G, int V
         } else if (c <= 10) {
             recursion_in_registers<10>(G, Vp, c, i, ic, pass, pm, inv, rho_yn, alpha_i, coef_s, gamma);
         } else if (MAXK > 10 && c <= MAXK) {
-            recursion_in_registers<MAXK>(G, Vp, c, i, ic, pass, pm, inv, rho_yn, alpha_i, coef_s, gamma);
+            recursion_in_registers_unscaled<MAXK>(G, Vp, c, i, ic, pass, pm, inv, rho_yn, alpha_i, coef_s, gamma);
         } else {
             // first loop: alpha_k, newest to oldest.  Steps of pairs that fail the gate run with alpha_k = 0;
             // a lane's row is dead once its own alpha has been taken, so updating it further is harmless.

@@ -4,6 +4,8 @@ that start on any element; its closing step in the kernel itself (the hook) and 
 
 Tolerances: sums of n products of numbers of order one in a fixed tree order, against the literal recursion's: 1e-12 normwise
 (the bound of the other two-loop tests).  Iterations accumulate that through the recursion: 1e-8, as in the transport tests."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -31,6 +33,39 @@ def test_two_loop(n, m, pairs):
     d = d.cpu().numpy()
     assert used == used_ref and np.all(d[mask == 0] == 0.0)
     assert rel_err(d, ref) <= 1e-12
+
+
+def exact_two_loop_case(c, n, seed):
+    """Integer pairs with <s_i, y_i> = 3 whose every alpha_i, beta_i and result is a whole number: dividing a sum by 3 is exact
+    also as a product with the rounded 1/3, where a row of G divided by 3 beforehand is rounded entry by entry.
+    s_i = e_i; R holds the <s_k, y_i>, k <= i; q after the first loop is w, one coordinate; gamma = 2^-20."""
+    rng = np.random.default_rng(seed)
+    alpha = rng.integers(1, 10, c) * rng.choice([-1, 1], c)
+    R = np.triu(rng.integers(-5, 6, (c, c)), 1) + 3 * np.eye(c, dtype=int)
+    beta = -np.sign(alpha) * rng.integers(0, 6, c)
+    coef = alpha - beta
+    E = np.array([3 * beta[i] - coef[:i] @ R[:i, i] for i in range(c)])
+    rest, squares = (3 << 20) - int(R[:, -1] @ R[:, -1]) - int(E[-1]) ** 2, []      # ||y_{c-1}||^2 = 3 2^20
+    while rest:
+        squares.append(math.isqrt(rest))
+        rest -= squares[-1] ** 2
+    S, Y, w = np.zeros((c, n)), np.zeros((c, n)), np.zeros(n)
+    S[np.arange(c), np.arange(c)] = 1.0
+    Y[:, :c], Y[:, c], Y[-1, c + 1:c + 1 + len(squares)], w[c] = R.T, E, squares, 1 << 20
+    return S, Y, w + alpha @ Y, -(w / (1 << 20) + coef @ S)
+
+
+@pytest.mark.parametrize("m,pairs", [(11, 11), (20, 11), (20, 20), (21, 21), (31, 12), (31, 31)])
+@pytest.mark.parametrize("seed", range(3))
+def test_the_recursion_divides_sums_not_rows(m, pairs, seed):
+    S, Y, g, ref = exact_two_loop_case(pairs, pairs + 9, seed)
+    n = g.size
+    s = make_solver(L.OBJ_LSQ, np.zeros((1, n)), np.zeros(1), np.full(n, -np.inf), np.full(n, np.inf), m)
+    d, used = s.dbg_two_loop(to_dev(S), to_dev(Y), to_dev(np.einsum("ij,ij->i", Y, Y)), to_dev(g),
+                             torch.ones(n, dtype=torch.uint8, device=DEV))
+    s.close()
+    assert used == pairs
+    np.testing.assert_array_equal(d.cpu().numpy(), ref)
 
 
 # 63 504 (short vectors), 131 043 and 131 769 (odd, either side of 2^17), 131 404 entries

@@ -18,51 +18,101 @@ constexpr int kGramOpenM = 10;          // up to this many pairs the direction k
 __host__ __device__ constexpr int gram_products(int m) { return (m + 1) * (2 * m + 1) - m * (m + 1) / 2; }
 __host__ __device__ constexpr int gram_entries(int m) { return kGramHdr + gram_products(m); }
 
+// (row a begins at entry a (4 m + 3 - a)/2: the root of that quadratic, which the hardware's square root hits to within one row)
 __device__ __forceinline__ void gram_product_slots(int idx, int m, int& a, int& b) {
-    int len = 2 * m + 1;
-    a = 0;
-    while (idx >= len) { idx -= len; --len; ++a; }
-    b = a + idx;
+    const int q = 4 * m + 3;
+    a = (int)(((float)q - __builtin_amdgcn_sqrtf((float)(q * q - 8 * idx))) * 0.5f);
+    a += (a + 1) * (q - a - 1) / 2 <= idx ? 1 : 0;
+    a -= a * (q - a) / 2 > idx ? 1 : 0;
+    b = a + idx - a * (q - a) / 2;
 }
+
+// Where a record holds what the closing step reads, for c pairs, the oldest in ring slot base_slot: entry i < kGramHdr of the
+// statistics, behind them the products of c pairs in the order a ring of c slots that starts with the oldest would have.
+struct GramPlaces {
+    int m, c, base_slot;
+    __device__ __forceinline__ int count() const { return gram_entries(c); }
+    __device__ __forceinline__ int operator()(int i) const {
+        if (i < kGramHdr) return i;
+        int a, b;
+        gram_product_slots(i - kGramHdr, c, a, b);
+        auto slot = [&](int k) -> int {
+            if (k == c) return m;
+            int ring = base_slot + (k < c ? k : k - c - 1);
+            ring -= ring >= m ? m : 0;
+            return k < c ? ring : m + 1 + ring;
+        };
+        const int sa = slot(a), sb = slot(b), lo = sa < sb ? sa : sb, hi = sa < sb ? sb : sa;
+        return kGramHdr + lo * (4 * m + 3 - lo) / 2 + hi - lo;
+    }
+};
+// ... and all of it as it lies there
+struct GramAll {
+    int m;
+    __device__ __forceinline__ int count() const { return gram_entries(m); }
+    __device__ __forceinline__ int operator()(int i) const { return i; }
+};
 
 // Adds the records of `nwg` workgroups (NE doubles each; entry 0 is a maximum, the others are sums) in workgroup order into
-// tot[0 .. NE): thread idx takes entry idx, BATCH records at a time with every load of a batch issued before the first is used and
-// none of them under a test (past the last record: the last one again, not added).
+// tot[0 .. places.count()): entry i of tot is entry places(i) of the records.  Thread i takes entry i, BATCH records at a time with
+// every load of a batch issued before the first is used and none of them under a test (past the last record: the last one again,
+// not added).
 // Called by all NT threads; no barrier inside.  SAME: the records are of this launch (published), else of an earlier one.
-template <int NT, bool SAME, int BATCH>
-__device__ __forceinline__ void gram_sum_batches(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
-    for (int idx = threadIdx.x; idx < NE; idx += NT) {
-        double sum = 0.0, most = -INFINITY;
-        for (int k0 = 0; k0 < nwg; k0 += BATCH) {
-            double v[BATCH];
+// PER: entries a thread takes at a time (their loads are in flight together).
+template <int NT, bool SAME, int BATCH, int PER, class P>
+__device__ __forceinline__ void gram_sum_batches(const double* __restrict__ grampart, int NE, int nwg, double* tot, P places) {
+    const int count = places.count();
+    for (int i0 = threadIdx.x; i0 < count; i0 += NT * PER) {
+        double sum[PER], most = -INFINITY;
+        int at[PER];
 #pragma unroll
-            for (int k = 0; k < BATCH; ++k) {
-                const double* r = grampart + (int64_t)(k0 + k < nwg ? k0 + k : nwg - 1) * NE + idx;
-                v[k] = SAME ? observe(r) : *r;
+        for (int p = 0; p < PER; ++p) {
+            sum[p] = 0.0;
+            at[p] = places(i0 + p * NT < count ? i0 + p * NT : i0);
+        }
+        for (int k0 = 0; k0 < nwg; k0 += BATCH) {
+            double v[PER][BATCH];
+#pragma unroll
+            for (int p = 0; p < PER; ++p) {
+#pragma unroll
+                for (int k = 0; k < BATCH; ++k) {
+                    const double* r = grampart + (int64_t)(k0 + k < nwg ? k0 + k : nwg - 1) * NE + at[p];
+                    v[p][k] = SAME ? observe(r) : *r;
+                }
             }
 #pragma unroll
-            for (int k = 0; k < BATCH; ++k) {
-                sum += k0 + k < nwg ? v[k] : 0.0;
-                most = fmax(most, v[k]);
+            for (int p = 0; p < PER; ++p) {
+#pragma unroll
+                for (int k = 0; k < BATCH; ++k) {
+                    sum[p] += k0 + k < nwg ? v[p][k] : 0.0;
+                    if (p == 0) most = fmax(most, v[p][k]);
+                }
             }
         }
-        tot[idx] = idx == 0 ? most : sum;
+#pragma unroll
+        for (int p = 0; p < PER; ++p)
+            if (i0 + p * NT < count) tot[i0 + p * NT] = i0 + p * NT == 0 ? most : sum[p];
     }
 }
-template <int NT, bool SAME>
-__device__ __forceinline__ void gram_sum_partials_flat(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
+// MANY: more entries than threads (beyond 10 pairs).  Short vectors leave few records, and a thread then asks for several of its
+// entries at once.  Gram kernel with room for 31 pairs, 12 held at most, us: every entry of the records added one after the other and
+// its slots found by walking the rows / this: n = 500 26.4 / 17.4, 20 000 51.5 / 21.2; 60 steps, 31 held, n = 500 27.7 / 20.3.
+template <int NT, bool SAME, bool MANY, class P>
+__device__ __forceinline__ void gram_sum_partials_flat(const double* __restrict__ grampart, int NE, int nwg, double* tot, P places) {
     // (the trips of different batches to memory follow one another: a batch for all where that is not too many loads)
-    if (nwg <= 16) gram_sum_batches<NT, SAME, 16>(grampart, NE, nwg, tot);
-    else if (nwg <= 32) gram_sum_batches<NT, SAME, 32>(grampart, NE, nwg, tot);
-    else gram_sum_batches<NT, SAME, 64>(grampart, NE, nwg, tot);
+    if (MANY && nwg <= 4) gram_sum_batches<NT, SAME, 4, MANY ? 8 : 1>(grampart, NE, nwg, tot, places);
+    else if (MANY && nwg <= 8) gram_sum_batches<NT, SAME, 8, MANY ? 4 : 1>(grampart, NE, nwg, tot, places);
+    else if (nwg <= 16) gram_sum_batches<NT, SAME, 16, MANY ? 4 : 1>(grampart, NE, nwg, tot, places);
+    else if (nwg <= 32) gram_sum_batches<NT, SAME, 32, MANY ? 2 : 1>(grampart, NE, nwg, tot, places);
+    else gram_sum_batches<NT, SAME, 64, 1>(grampart, NE, nwg, tot, places);
 }
 
-// The closing step from the totals tot[0 .. gram_entries(m)) (LDS, complete: a barrier lies between their last write and this
+// The closing step from the totals tot (HELD: of GramPlaces, else of GramAll; LDS, complete: a barrier lies between their last write and this
 // call).  c, head: the ring as it will be once the pending update is applied; base_slot: ring slot of the oldest pair.
 // Gs: (2 m + 2)^2 doubles, alpha_s: kMaxM + 1 (both LDS).  sc: the scalar block this works on.  mine_a, mine_b (or -1): the
 // slots of entry threadIdx.x, when the caller has worked them out while it waited for something.
 // MAXK: see recursion_on_coefficients.
-template <int NT, int MAXK>
+template <int NT, int MAXK, bool HELD>
 __device__ __forceinline__ void gram_finish(const double* tot, double* Gs, double* alpha_s, Scal* sc, int m,
                                             int c, int head, int base_slot, const Opts& op, double yn_old, int dbg_inputs,
                                             int evaluate_stop, bool record, int mine_a = -1, int mine_b = 0) {
@@ -73,10 +123,11 @@ __device__ __forceinline__ void gram_finish(const double* tot, double* Gs, doubl
     // head already are the ring as it will be; the recursion reads the iteration count and the status after the barrier.)
     if (tid == NT - 1) apply_pending(sc, m, record);
     // static slots -> the recursion's order (s oldest..newest, y oldest..newest, g)
-    for (int idx = tid; idx < gram_products(m); idx += NT) {
+    for (int idx = tid; idx < gram_products(HELD ? c : m); idx += NT) {
         int a = mine_a, b = mine_b;
-        if (mine_a < 0 || idx != tid) gram_product_slots(idx, m, a, b);
+        if (mine_a < 0 || idx != tid) gram_product_slots(idx, HELD ? c : m, a, b);
         auto logical = [&](int slot) -> int {
+            if (HELD) return slot == c ? 2 * c : (slot < c ? c + slot : slot - c - 1);
             if (slot == m) return 2 * c;
             const int ring = slot < m ? slot : slot - m - 1;
             const int j = ring >= base_slot ? ring - base_slot : ring - base_slot + m;

@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
         int pa, pb;                                                // (worked out while the records are on their way)
         gram_product_slots(tid < gram_products(m) ? tid : 0, m, pa, pb);
         asm volatile("" : "+v"(pa), "+v"(pb));
-        gram_sum_partials_flat<kBlock, false>(records.part, gram_entries(m), records.count, tot);
+        gram_sum_partials_flat<kBlock, false, false>(records.part, gram_entries(m), records.count, tot, GramAll{m});
         __syncthreads();
         if (sc.status != LBFGSB_RUNNING) {
             // (the pass reads its status word from scal_next: it must not find an older one there)
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
             for (int j = 0; j < kDirPre; ++j) vpre[j] = vecp[j][e_first];   // (past the last vector: g, with a coefficient of zero)
         }
         __syncthreads();                                           // every thread has read the ring before it changes
-        gram_finish<kBlock, kGramOpenM>(tot, Gs, alpha_s, &sc, m, c, head, base_slot, op, yn_old, 0, 1, blockIdx.x == 0, pa, pb);
+        gram_finish<kBlock, kGramOpenM, false>(tot, Gs, alpha_s, &sc, m, c, head, base_slot, op, yn_old, 0, 1, blockIdx.x == 0, pa, pb);
         __syncthreads();                                           // the first wave's results are in the copy
         if (blockIdx.x == 0) {
             if (tid == 0) note_progress(op, sc.status);
@@ -478,7 +478,7 @@ __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op,
         int pa, pb;
         gram_product_slots(tid < gram_products(m) ? tid : 0, m, pa, pb);
         asm volatile("" : "+v"(pa), "+v"(pb));
-        gram_sum_partials_flat<kBlock, false>(records.part, gram_entries(m), records.count, tot);
+        gram_sum_partials_flat<kBlock, false, false>(records.part, gram_entries(m), records.count, tot, GramAll{m});
         __syncthreads();
         if (sc.status != LBFGSB_RUNNING) {
             // (the kernel behind reads its status word from scal_next: it must not find an older one there)
@@ -498,7 +498,7 @@ __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op,
         const double yn_old = prefetch_ynorm2(&sc, c, head, m);
         if (pair_mask(in_next, ec_next, mkn) != 0) load(0, base_slot, ec_next, first);
         __syncthreads();                                         // every thread has read the ring before it changes
-        gram_finish<kBlock, kGramOpenM>(tot, Gs, alpha_s, &sc, m, c, head, base_slot, op, yn_old, 0, 1, blockIdx.x == 0, pa, pb);
+        gram_finish<kBlock, kGramOpenM, false>(tot, Gs, alpha_s, &sc, m, c, head, base_slot, op, yn_old, 0, 1, blockIdx.x == 0, pa, pb);
         __syncthreads();                                         // the first wave's results are in the copy
         if (blockIdx.x == 0) {
             if (tid == 0) note_progress(op, sc.status);

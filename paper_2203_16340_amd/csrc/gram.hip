@@ -218,7 +218,8 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
     // where the waves' blocks hold the product that is entry idx of a record
     auto block_place = [&](int idx) -> int {
         int a, b;
-        gram_product_slots(idx, m, a, b);
+        if (M > 10) gram_product_slots_many(idx, m, a, b);
+        else gram_product_slots(idx, m, a, b);
         // (record: y, g, s of m slots each; here of M)
         a += a == m ? M - m : 0;
         b += b >= m ? M - m : 0;

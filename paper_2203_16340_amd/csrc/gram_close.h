@@ -18,8 +18,15 @@ constexpr int kGramOpenM = 10;          // up to this many pairs the direction k
 __host__ __device__ constexpr int gram_products(int m) { return (m + 1) * (2 * m + 1) - m * (m + 1) / 2; }
 __host__ __device__ constexpr int gram_entries(int m) { return kGramHdr + gram_products(m); }
 
-// (row a begins at entry a (4 m + 3 - a)/2: the root of that quadratic, which the hardware's square root hits to within one row)
 __device__ __forceinline__ void gram_product_slots(int idx, int m, int& a, int& b) {
+    int len = 2 * m + 1;
+    a = 0;
+    while (idx >= len) { idx -= len; --len; ++a; }
+    b = a + idx;
+}
+// The same for many slots, without the walk: row a begins at entry a (4 m + 3 - a)/2, a quadratic whose root the hardware's square
+// root hits to within one row.
+__device__ __forceinline__ void gram_product_slots_many(int idx, int m, int& a, int& b) {
     const int q = 4 * m + 3;
     a = (int)(((float)q - __builtin_amdgcn_sqrtf((float)(q * q - 8 * idx))) * 0.5f);
     a += (a + 1) * (q - a - 1) / 2 <= idx ? 1 : 0;
@@ -35,7 +42,7 @@ struct GramPlaces {
     __device__ __forceinline__ int operator()(int i) const {
         if (i < kGramHdr) return i;
         int a, b;
-        gram_product_slots(i - kGramHdr, c, a, b);
+        gram_product_slots_many(i - kGramHdr, c, a, b);
         auto slot = [&](int k) -> int {
             if (k == c) return m;
             int ring = base_slot + (k < c ? k : k - c - 1);
@@ -125,7 +132,8 @@ __device__ __forceinline__ void gram_finish(const double* tot, double* Gs, doubl
     // static slots -> the recursion's order (s oldest..newest, y oldest..newest, g)
     for (int idx = tid; idx < gram_products(HELD ? c : m); idx += NT) {
         int a = mine_a, b = mine_b;
-        if (mine_a < 0 || idx != tid) gram_product_slots(idx, HELD ? c : m, a, b);
+        if (HELD) gram_product_slots_many(idx, c, a, b);
+        else if (mine_a < 0 || idx != tid) gram_product_slots(idx, m, a, b);
         auto logical = [&](int slot) -> int {
             if (HELD) return slot == c ? 2 * c : (slot < c ? c + slot : slot - c - 1);
             if (slot == m) return 2 * c;

@@ -151,26 +151,68 @@ __global__ __launch_bounds__(kBlock) void k_ot_cols(Dims dm, OtArgs a, int eval,
 // with one entry at a time and the fences arrive_is_last had); whole runs of 17 to 46 steps, with the runtime's logarithm and
 // the former Gram kernels / now, us: 1000 x 1000 3350 / 2800, 700 x 630 2290 / 1820, 300 x 300 (m = 5) 1660 / 1530, 1901 x 333 fp32
 // 3900 / 2320, 251 x 997 2190 / 1630.
+// Few rows: the workgroups of a group of rows share its columns (split), so that there are up to 512 of them.  Few columns: a row's
+// columns take a power of two of lanes and the workgroup as many groups of rows as it has such sets of lanes (SHORT).  Entropy,
+// whole runs, us, one workgroup per group of rows and all of its threads along a row / this (the last workgroup's own loop,
+// eight to a trip, included): 1 x 500 000 35 100 / 19 000, 5 x 200 000 20 000 / 11 600, 16 x 100 000 12 150 / 8 230, 40 x 20 000 3 880 /
+// 3 400, 100 000 x 16 14 650 / 10 560, 100 000 x 40 18 860 / 15 680, 30 000 x 64 6 300 / 5 550, 8000 x 128 3 090 / 3 000; 8000 x 129, where
+// a row has the workgroup for itself, the same.
 constexpr int kOtRowsMax = 4;
-inline int ot_rows(const Dims& dm) { return dm.rows > 1024 ? 4 : (dm.rows > 512 ? 2 : 1); }
-inline int ot_cols_threads(const Dims& dm) { return dm.cols > 384 ? 512 : 256; }
+constexpr int kOtShortCols = 128;   // up to this many columns a row takes a part of the workgroup
+struct OtShape { int threads, rows, lanes_log2, groups, split; };   // lanes_log2: SHORT, else 0
+inline OtShape ot_shape(const Dims& dm) {
+    OtShape s{dm.cols > 384 ? 512 : 256, 1, 0, 1, 1};
+    if (dm.cols <= kOtShortCols) {
+        s.lanes_log2 = 4;
+        while ((1 << s.lanes_log2) < dm.cols) ++s.lanes_log2;
+    }
+    const int sets = s.lanes_log2 ? s.threads >> s.lanes_log2 : 1;   // of rows, side by side in a workgroup
+    const int64_t wgs = (dm.rows + sets - 1) / sets;
+    s.rows = wgs > 1024 ? 4 : (wgs > 512 ? 2 : 1);
+    const int64_t groups = (dm.rows + (int64_t)sets * s.rows - 1) / ((int64_t)sets * s.rows);
+    s.groups = (int)(groups > 512 ? 512 : groups);
+    const int64_t tiles = (dm.cols + s.threads - 1) / s.threads;
+    // (four columns a thread at least: each workgroup of the update is an arrival more; 128 x 2000, 512 workgroups for 128: 11.3 us, not 9.8)
+    s.split = (int)(512 / s.groups < (tiles + 3) / 4 ? 512 / s.groups : (tiles + 3) / 4);
+    return s;
+}
+// This thread's first group of rows, the stride to its next one, its first column and the stride to its next one.
+template <int NT, int R, bool SHORT>
+struct OtPlace {
+    int64_t row0, row_step, col0, col_step;
+    __device__ __forceinline__ explicit OtPlace(int lanes_log2) {
+        if (SHORT) {
+            const int sets = NT >> lanes_log2;
+            row0 = ((int64_t)blockIdx.x * sets + (threadIdx.x >> lanes_log2)) * R;
+            row_step = (int64_t)gridDim.x * sets * R;
+            col0 = threadIdx.x & ((1 << lanes_log2) - 1);
+            col_step = 1 << lanes_log2;
+        } else {
+            row0 = (int64_t)blockIdx.x * R;
+            row_step = (int64_t)gridDim.x * R;
+            col0 = (int64_t)blockIdx.y * NT + threadIdx.x;
+            col_step = (int64_t)gridDim.y * NT;
+        }
+    }
+};
 
 // g = M + lambda phi'(x) + K^T (omega . residual); the first workgroup adds up f.
-template <int NT, int R>
-__global__ __launch_bounds__(NT) void k_ot_eval_finish(Dims dm, OtArgs a, int loss_parts, const double* __restrict__ x,
+template <int NT, int R, bool SHORT>
+__global__ __launch_bounds__(NT) void k_ot_eval_finish(Dims dm, OtArgs a, int loss_parts, int lanes_log2, const double* __restrict__ x,
                                                        const double* __restrict__ res, const double* __restrict__ losspart,
                                                        double* __restrict__ g, Scal* __restrict__ scal) {
     __shared__ double red[NT / 64];
     if (scal->status != LBFGSB_RUNNING) return;
     const int tid = threadIdx.x;
-    if (blockIdx.x == 0) {
+    if (blockIdx.x == 0 && blockIdx.y == 0) {
         const double f = sum_all<NT>(losspart, loss_parts, red);   // (all of earlier launches)
         if (tid == 0) {
             scal->f = f;
             scal->fevals += 1;
         }
     }
-    for (int64_t r0 = (int64_t)blockIdx.x * R; r0 < dm.rows; r0 += (int64_t)gridDim.x * R) {
+    const OtPlace<NT, R, SHORT> at(lanes_log2);
+    for (int64_t r0 = at.row0; r0 < dm.rows; r0 += at.row_step) {
         double ri[R];
         int64_t row[R];
 #pragma unroll
@@ -178,7 +220,7 @@ __global__ __launch_bounds__(NT) void k_ot_eval_finish(Dims dm, OtArgs a, int lo
             row[r] = r0 + r < dm.rows ? r0 + r : dm.rows - 1;
             ri[r] = a.omega ? a.omega[row[r]] * res[row[r]] : 0.0;
         }
-        for (int64_t j = tid; j < dm.cols; j += NT) {
+        for (int64_t j = at.col0; j < dm.cols; j += at.col_step) {
             double xv[R], mv[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) { xv[r] = x[row[r] * dm.cols + j]; mv[r] = m_at(a.M, dm.dtype, row[r] * dm.ld + j); }
@@ -458,9 +500,9 @@ __global__ __launch_bounds__(NT, NT == 1024 ? (GROUP <= 2 ? 8 : 4) : 1) void k_o
 }
 
 // x+ = P(x + a p); g+ = M + lambda (log x+ + 1) + K^T (omega . (res + a K p)); pair; f+ from scratch at x+.
-template <int NT, int R>
-__global__ __launch_bounds__(NT) void k_ot_update_entropy(Dims dm, Opts op, OtArgs a, double* res, const double* __restrict__ t,
-                                                          const double* __restrict__ p1, const double* __restrict__ p2,
+template <int NT, int R, bool SHORT>
+__global__ __launch_bounds__(NT) void k_ot_update_entropy(Dims dm, Opts op, OtArgs a, int lanes_log2, double* res,
+                                                          const double* __restrict__ t, const double* __restrict__ p1, const double* __restrict__ p2,
                                                           const double* __restrict__ l, const double* __restrict__ u,
                                                           double* __restrict__ x, double* __restrict__ g, double* __restrict__ S,
                                                           double* __restrict__ Y, Scal* __restrict__ scal,
@@ -478,7 +520,8 @@ __global__ __launch_bounds__(NT) void k_ot_update_entropy(Dims dm, Opts op, OtAr
         double* Sn = S + (int64_t)slot * dm.n;
         double* Yn = Y + (int64_t)slot * dm.n;
         const int64_t bstride = op.uniform_bounds ? 0 : 1;
-        for (int64_t r0 = (int64_t)blockIdx.x * R; r0 < dm.rows; r0 += (int64_t)gridDim.x * R) {
+        const OtPlace<NT, R, SHORT> at(lanes_log2);
+        for (int64_t r0 = at.row0; r0 < dm.rows; r0 += at.row_step) {
             double ri[R];
             int64_t row[R];
 #pragma unroll
@@ -486,7 +529,7 @@ __global__ __launch_bounds__(NT) void k_ot_update_entropy(Dims dm, Opts op, OtAr
                 row[r] = r0 + r < dm.rows ? r0 + r : dm.rows - 1;
                 ri[r] = a.omega ? a.omega[row[r]] * fma(alpha, t[row[r]], res[row[r]]) : 0.0;
             }
-            for (int64_t j = tid; j < dm.cols; j += NT) {
+            for (int64_t j = at.col0; j < dm.cols; j += at.col_step) {
                 double xv[R], pv[R], gv[R], mv[R], lv[R], uv[R];
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
@@ -516,17 +559,31 @@ __global__ __launch_bounds__(NT) void k_ot_update_entropy(Dims dm, Opts op, OtAr
         }
     }
     block_sum<1, NT / 64>(fs, red);
-    if (tid == 0) publish(redpart + blockIdx.x, fs[0]);
+    if (tid == 0) publish(redpart + blockIdx.y * gridDim.x + blockIdx.x, fs[0]);
     if (!arrive_is_last(&scal->counters[kCntUpdate], &flag)) return;
     double tot[1] = {0.0};
-    for (int b = tid; b < (int)gridDim.x; b += NT) tot[0] += observe(redpart + b);
+    for (int b = tid; b < (int)(gridDim.x * gridDim.y); b += NT) tot[0] += observe(redpart + b);
     if (ok) {
         // the residuals of the marginal terms move to the new point here, res += a K p: every other workgroup has
         // finished reading them (it has arrived)
-        for (int64_t k = tid; k < dm.rows + dm.cols; k += NT) {
-            const double rn = fma(alpha, t[k], res[k]);
-            res[k] = rn;
-            if (a.omega) tot[0] = fma(0.5 * a.omega[k] * rn, rn, tot[0]);
+        // (this workgroup alone: eight to a thread and trip, or the trips to memory of 10^5 of them last longer than the rest)
+        const int64_t count = dm.rows + dm.cols;
+        for (int64_t k0 = tid; k0 < count; k0 += 8 * NT) {
+            double tv[8], rv[8], wv[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int64_t k = k0 + q * NT < count ? k0 + q * NT : k0;
+                tv[q] = t[k]; rv[q] = res[k];
+                wv[q] = a.omega ? a.omega[k] : 0.0;
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                if (k0 + q * NT < count) {
+                    const double rn = fma(alpha, tv[q], rv[q]);
+                    res[k0 + q * NT] = rn;
+                    if (a.omega) tot[0] = fma(0.5 * wv[q] * rn, rn, tot[0]);
+                }
+            }
         }
     }
     block_sum<1, NT / 64>(tot, red);
@@ -569,31 +626,33 @@ void launch_ot_sums(const Dims& dm, const Geometry& ge, const Buffers& bf, const
                        (const double*)bf.wpart, (const Scal*)bf.scal, eval ? bf.row : bf.t, bf.losspart + ge.ot_row_blocks);
 }
 
-// f(workgroup size, rows per workgroup) for this shape's instantiation
+// f(workgroup size, rows per group, short rows) for this shape's instantiation
 template <class F>
-static void with_ot_shape(const Dims& dm, F f) {
-    auto rows = [&](auto nt) {
-        switch (ot_rows(dm)) {
-            case 1: f(nt, std::integral_constant<int, 1>()); break;
-            case 2: f(nt, std::integral_constant<int, 2>()); break;
-            default: f(nt, std::integral_constant<int, kOtRowsMax>()); break;
+static void with_ot_shape(const OtShape& s, F f) {
+    auto rows = [&](auto nt, auto is_short) {
+        switch (s.rows) {
+            case 1: f(nt, std::integral_constant<int, 1>(), is_short); break;
+            case 2: f(nt, std::integral_constant<int, 2>(), is_short); break;
+            default: f(nt, std::integral_constant<int, kOtRowsMax>(), is_short); break;
         }
     };
-    if (ot_cols_threads(dm) == 512) rows(std::integral_constant<int, 512>());
-    else rows(std::integral_constant<int, 256>());
+    if (s.lanes_log2) rows(std::integral_constant<int, 256>(), std::true_type());
+    else if (s.threads == 512) rows(std::integral_constant<int, 512>(), std::false_type());
+    else rows(std::integral_constant<int, 256>(), std::false_type());
 }
 
 void launch_ot_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const OtArgs& a, hipStream_t st) {
-    with_ot_shape(dm, [&](auto nt, auto rows) {
-        hipLaunchKernelGGL((k_ot_eval_finish<nt(), rows()>), dim3(ge.ot_el_blocks), dim3(nt()), 0, st, dm, a,
-                           ge.ot_row_blocks + ge.ot_col_blocks, (const double*)bf.x, (const double*)bf.row,
+    const OtShape s = ot_shape(dm);
+    with_ot_shape(s, [&](auto nt, auto rows, auto is_short) {
+        hipLaunchKernelGGL((k_ot_eval_finish<nt(), rows(), is_short()>), dim3(s.groups, s.split), dim3(nt()), 0, st, dm, a,
+                           ge.ot_row_blocks + ge.ot_col_blocks, s.lanes_log2, (const double*)bf.x, (const double*)bf.row,
                            (const double*)bf.losspart, bf.g, bf.scal);
     });
 }
 
 int ot_entry_blocks(const Dims& dm) {
-    const int64_t b = (dm.rows + ot_rows(dm) - 1) / ot_rows(dm);
-    return (int)(b > 512 ? 512 : b);
+    const OtShape s = ot_shape(dm);
+    return s.groups * s.split;
 }
 
 void launch_ot_update_gauss(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
@@ -628,9 +687,10 @@ void launch_ot_step_entropy(const Dims& dm, const Opts& op, const Geometry& ge, 
                             hipStream_t st) {
     if (ot_threads(dm) == 1024) launch_search_t<1024>(dm, op, ge, bf, st);
     else launch_search_t<256>(dm, op, ge, bf, st);
-    with_ot_shape(dm, [&](auto nt, auto rows) {
-        hipLaunchKernelGGL((k_ot_update_entropy<nt(), rows()>), dim3(ge.ot_el_blocks), dim3(nt()), 0, st, dm, op, a, bf.row,
-                           (const double*)bf.t, (const double*)bf.p1, (const double*)bf.p2, (const double*)bf.l,
+    const OtShape s = ot_shape(dm);
+    with_ot_shape(s, [&](auto nt, auto rows, auto is_short) {
+        hipLaunchKernelGGL((k_ot_update_entropy<nt(), rows(), is_short()>), dim3(s.groups, s.split), dim3(nt()), 0, st, dm, op, a,
+                           s.lanes_log2, bf.row, (const double*)bf.t, (const double*)bf.p1, (const double*)bf.p2, (const double*)bf.l,
                            (const double*)bf.u, bf.x, bf.g, bf.S, bf.Y, bf.scal, bf.redpart);
     });
 }

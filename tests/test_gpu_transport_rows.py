@@ -1,5 +1,7 @@
 """The transport kinds' gradient and entropy update where their workgroups change: one, two and four rows each (512 and 1024
-rows), 256 and 512 threads (384 columns), a last group of rows that is not full, one row, one column; the whole-kernel sums
+rows), 256 and 512 threads (384 columns), a last group of rows that is not full, one row, one column; few rows, whose columns
+several workgroups share (up to 256 rows, the last workgroup's share empty or ragged); few columns, of which several rows fit
+into a workgroup (up to 128: whole, ragged and 16 lanes, and the three row counts there); the whole-kernel sums
 without a closing step.  Tolerances as in test_gpu_transport.py."""
 import numpy as np
 import pytest
@@ -11,7 +13,8 @@ from test_gpu_transport import KIND_IDS, KINDS, _problem, _solver
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(512, 384), (513, 385), (1023, 40), (1025, 386), (1030, 513), (1, 600), (700, 1), (2051, 70)]
+SHAPES = [(512, 384), (513, 385), (1023, 40), (1025, 386), (1030, 513), (1, 600), (700, 1), (2051, 70),
+          (3, 5121), (16, 5000), (255, 1030), (256, 1024), (130, 128), (130, 129), (17000, 16), (9000, 17), (33000, 3), (4100, 65)]
 
 
 @pytest.mark.parametrize("kinds", KINDS, ids=KIND_IDS)
@@ -34,7 +37,8 @@ def test_value_and_gradient(kinds, rows, cols, dtype):
     s.close()
 
 
-@pytest.mark.parametrize("rows,cols", [(513, 385), (1025, 386), (1, 600), (700, 1), (2051, 70)])
+@pytest.mark.parametrize("rows,cols", [(513, 385), (1025, 386), (1, 600), (700, 1), (2051, 70), (3, 5121), (255, 1030), (17000, 16),
+                                       (4100, 65)])
 @pytest.mark.parametrize("uniform", [True, False])
 def test_entropy_iterations(rows, cols, uniform):
     rng = np.random.default_rng(rows + 3 * cols)

@@ -265,8 +265,8 @@ void enqueue_redo_columns(lbfgsb_solver* s) {
 }
 
 // A problem that backtracks once tends to do so again: this many steps behind a rejected first trial step take the full
-// launch sequence.  Counted from the step that was rejected, so that which steps take which sequence -- they carry f with
-// different roundings -- does not depend on how many had been enqueued when the host found out.
+// launch sequence.  Counted from the step that was rejected, so that which steps take which sequence does not depend on how many
+// had been enqueued when the host found out (an accepted first trial step is the same in both, f included).
 constexpr int kLogiFullSteps = 8;
 // Steps enqueued again between two looks at the device: those behind a further rejection have to be enqueued a third time.
 constexpr int kRedoBatch = 16;

@@ -186,8 +186,10 @@ __device__ __forceinline__ double observe(const double* p) { return __hip_atomic
 // each workgroup would do so (entropy update, 2 10^6 entries, 64 MB written by 500 workgroups: 52 us with the fences, 35.5
 // without; long Gram kernel 35.7 / 33.1).  The last workgroup resets the counter for the next launch.  Must be called by all threads of the workgroup.
 __device__ __forceinline__ bool arrive_is_last(unsigned* counter, int* lds_flag, unsigned expected = 0u) {
-    // (the compiler knows the builtin for this wait as touching no memory: as it stands here nothing that publishes moves behind it)
-    asm volatile("s_waitcnt vmcnt(0) expcnt(0) lgkmcnt(0)" ::: "memory");
+    // (the compiler takes the wait to touch no memory: the empty statements on either side of it keep what publishes before it)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);   // vmcnt(0) expcnt(0) lgkmcnt(0)
+    asm volatile("" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
         const unsigned total = expected ? expected : gridDim.x * gridDim.y;   // expected: arrivals at this counter

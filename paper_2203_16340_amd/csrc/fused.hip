@@ -76,8 +76,9 @@ void launch_variant(const Dims& dm, int64_t rows_per_wg, int blocks, size_t lds,
 // narrow_shape_ok: up to 1536 fp32, 1024 or 768 fp64 columns -- have a kernel of their own, narrow.h; they come here
 // only with a leading dimension past 2^24.)
 // What a pass over a tile that is not full pays: the chunks past the row's end are loads of its last chunk (the cache serves
-// them) and multiplications by zero, and they hold ring slots that could be rows in flight.  A width between two that lie
-// apart by 1.6 or more is therefore worth a variant of its own where it leaves the ring as deep or deeper; four chunks under
+// them) and multiplications by zero, and they hold ring slots that could be rows in flight.  Between two widths that lie
+// apart by 1.6 or more there is therefore a variant where one leaves the ring as deep or deeper and measured faster, two under
+// twenty chunks in 64 bits and ten in 32 for the quadratic kinds (the second gives 3 to 4 %, 8 % in 32 bits); four chunks under
 // five, six or seven under ten in 64 bits and sixteen under twenty measured the same or slower and are not there (the fp32
 // logistic ones under five chunks, 2 to 8 % faster, are).  Whole iterations, us, before / now: fp32 50001 x 3001 149 / 137, 50000 x 2500 145 / 121, 30000 x 2100 104 / 83, 50000 x 5500 249 /
 // 220, 25000 x 11001 264 / 225, 20000 x 13000 239 / 219; fp64 20000 x 2500 108 / 100 (2900: the same), 20000 x 11000 377 /

@@ -16,7 +16,6 @@
 //
 // (Steps on short vectors build it in small.hip.)
 #include <cstddef>
-#include <type_traits>
 
 #include "common.h"
 #include "gram_close.h"
@@ -54,22 +53,22 @@ static_assert(gram_tot_at(5) + gram_entries(5) <= gram_lds_doubles(5, 4) && gram
 // Every workgroup has written NE doubles at grampart + blockIdx.x * NE (entry 0 is a maximum, all others are
 // sums).  The workgroups form at most kGramGroups groups of consecutive indices; the last workgroup of a group
 // to finish adds the group's partials in index order into grampart + (gridDim.x + group) * NE, and the last
-// group to finish adds those entries of the group results that `places` names, again in index order, into tot (LDS).  Returns true in that
+// group to finish adds the group results (HELD: those entries that `places` names), again in index order, into tot (LDS).  Returns true in that
 // one workgroup (after a barrier), false everywhere else.  No workgroup reads more than kGramGroupMax partials,
 // and the order of the additions does not depend on which workgroup finishes last.  Grids of at most
-// kGramOneLevelMax workgroups skip the first level (each level costs two fences, an atomic and a dependent round of
-// loads: 6-7 us).  groups_only: the second level, and what follows it, is left to the direction kernel.
+// kGramOneLevelMax workgroups skip the first level (each level costs an atomic and a dependent round of loads).  groups_only: the second level, and what follows it, is left to the direction kernel.
 constexpr int kGramGroupMax = 16;   // workgroups per group at most: grids of up to kGramGroups * kGramGroupMax
 
-template <int NT, bool MANY, class P>
+template <int NT, bool HELD>
 __device__ __forceinline__ bool reduce_partials(double* __restrict__ grampart, int NE, Scal* __restrict__ scal, int* flag,
-                                                double* tot, bool groups_only, P places) {
+                                                double* tot, bool groups_only, const GramPlaces& places) {
     const int tid = threadIdx.x, nwg = gridDim.x;
     if (nwg <= kGramOneLevelMax) {
         if (groups_only) return false;
         // few workgroups: one level, the last one to finish adds all partials in index order
         if (!arrive_is_last(&scal->gram_cnt[kGramGroups], flag, (unsigned)nwg)) return false;
-        gram_sum_partials_flat<NT, true, MANY>(grampart, NE, nwg, tot, places);
+        if constexpr (HELD) gram_sum_held<NT>(grampart, NE, nwg, tot, places);
+        else gram_sum_partials_flat<NT, true>(grampart, NE, nwg, tot);
         __syncthreads();
         return true;
     }
@@ -95,7 +94,11 @@ __device__ __forceinline__ bool reduce_partials(double* __restrict__ grampart, i
     for (int idx = tid; idx < NE; idx += NT) publish(grampart + (int64_t)(nwg + grp) * NE + idx, add(gfirst, gsize, idx));
     if (groups_only) return false;
     if (!arrive_is_last(&scal->gram_cnt[kGramGroups], flag, (unsigned)ngroups)) return false;
-    for (int i = tid; i < places.count(); i += NT) tot[i] = add(nwg, ngroups, places(i));
+    if constexpr (HELD) {
+        for (int i = tid; i < places.count(); i += NT) tot[i] = add(nwg, ngroups, places(i));
+    } else {
+        for (int idx = tid; idx < NE; idx += NT) tot[idx] = add(nwg, ngroups, idx);
+    }
     __syncthreads();
     return true;
 }
@@ -344,10 +347,7 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
     double* tot = dyn + gram_tot_at(M);
     // (beyond 10 pairs a record has more entries than the workgroup threads, so only those are added that the pairs held need)
     constexpr bool HELD = M > 10;
-    std::conditional_t<HELD, GramPlaces, GramAll> places;
-    places.m = m;
-    if constexpr (HELD) { places.c = c; places.base_slot = base_slot; }
-    if (!reduce_partials<NT, HELD>(grampart, NE, scal, &flag, tot, LONG && no_close, places)) return;
+    if (!reduce_partials<NT, HELD>(grampart, NE, scal, &flag, tot, LONG && no_close, GramPlaces{m, c, base_slot})) return;
     gram_finish<NT, M < 10 ? 10 : M, HELD>(tot, dyn, alpha_s, scal, m, c, head, base_slot, op, yn_old, DBG, evaluate_stop, true);
     __syncthreads();
     if (tid == 0 && evaluate_stop) note_progress(op, scal->status);

@@ -53,21 +53,46 @@ struct GramPlaces {
         return kGramHdr + lo * (4 * m + 3 - lo) / 2 + hi - lo;
     }
 };
-// ... and all of it as it lies there
-struct GramAll {
-    int m;
-    __device__ __forceinline__ int count() const { return gram_entries(m); }
-    __device__ __forceinline__ int operator()(int i) const { return i; }
-};
-
 // Adds the records of `nwg` workgroups (NE doubles each; entry 0 is a maximum, the others are sums) in workgroup order into
-// tot[0 .. places.count()): entry i of tot is entry places(i) of the records.  Thread i takes entry i, BATCH records at a time with
-// every load of a batch issued before the first is used and none of them under a test (past the last record: the last one again,
-// not added).
+// tot[0 .. NE): thread idx takes entry idx, BATCH records at a time with every load of a batch issued before the first is used and
+// none of them under a test (past the last record: the last one again, not added).
 // Called by all NT threads; no barrier inside.  SAME: the records are of this launch (published), else of an earlier one.
-// PER: entries a thread takes at a time (their loads are in flight together).
-template <int NT, bool SAME, int BATCH, int PER, class P>
-__device__ __forceinline__ void gram_sum_batches(const double* __restrict__ grampart, int NE, int nwg, double* tot, P places) {
+template <int NT, bool SAME, int BATCH>
+__device__ __forceinline__ void gram_sum_batches(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
+    for (int idx = threadIdx.x; idx < NE; idx += NT) {
+        double sum = 0.0, most = -INFINITY;
+        for (int k0 = 0; k0 < nwg; k0 += BATCH) {
+            double v[BATCH];
+#pragma unroll
+            for (int k = 0; k < BATCH; ++k) {
+                const double* r = grampart + (int64_t)(k0 + k < nwg ? k0 + k : nwg - 1) * NE + idx;
+                v[k] = SAME ? observe(r) : *r;
+            }
+#pragma unroll
+            for (int k = 0; k < BATCH; ++k) {
+                sum += k0 + k < nwg ? v[k] : 0.0;
+                most = fmax(most, v[k]);
+            }
+        }
+        tot[idx] = idx == 0 ? most : sum;
+    }
+}
+template <int NT, bool SAME>
+__device__ __forceinline__ void gram_sum_partials_flat(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
+    // (the trips of different batches to memory follow one another: a batch for all where that is not too many loads)
+    if (nwg <= 16) gram_sum_batches<NT, SAME, 16>(grampart, NE, nwg, tot);
+    else if (nwg <= 32) gram_sum_batches<NT, SAME, 32>(grampart, NE, nwg, tot);
+    else gram_sum_batches<NT, SAME, 64>(grampart, NE, nwg, tot);
+}
+
+// The same beyond 10 pairs, where a record has more entries than the workgroup threads: only those that the pairs held need, entry
+// places(i) of the records into tot[i].  Short vectors leave few records, and a thread then asks for PER of its entries at once.
+// (A function of its own: one for both made the kernel for 10 pairs 0.4 us longer on short vectors.)  Gram kernel with room for 31
+// pairs, 12 held at most, us: every entry of the records added one after the other and its slots found by walking the rows / this:
+// n = 500 26.4 / 17.4, 20 000 51.5 / 21.2; 60 steps, 31 held, n = 500 27.7 / 20.3.
+template <int NT, int BATCH, int PER>
+__device__ __forceinline__ void gram_sum_held_batches(const double* __restrict__ grampart, int NE, int nwg, double* tot,
+                                                      const GramPlaces& places) {
     const int count = places.count();
     for (int i0 = threadIdx.x; i0 < count; i0 += NT * PER) {
         double sum[PER], most = -INFINITY;
@@ -82,10 +107,8 @@ __device__ __forceinline__ void gram_sum_batches(const double* __restrict__ gram
 #pragma unroll
             for (int p = 0; p < PER; ++p) {
 #pragma unroll
-                for (int k = 0; k < BATCH; ++k) {
-                    const double* r = grampart + (int64_t)(k0 + k < nwg ? k0 + k : nwg - 1) * NE + at[p];
-                    v[p][k] = SAME ? observe(r) : *r;
-                }
+                for (int k = 0; k < BATCH; ++k)   // (at most kGramOneLevelMax records: 32 bits)
+                    v[p][k] = observe(grampart + ((k0 + k < nwg ? k0 + k : nwg - 1) * NE + at[p]));
             }
 #pragma unroll
             for (int p = 0; p < PER; ++p) {
@@ -101,20 +124,16 @@ __device__ __forceinline__ void gram_sum_batches(const double* __restrict__ gram
             if (i0 + p * NT < count) tot[i0 + p * NT] = i0 + p * NT == 0 ? most : sum[p];
     }
 }
-// MANY: more entries than threads (beyond 10 pairs).  Short vectors leave few records, and a thread then asks for several of its
-// entries at once.  Gram kernel with room for 31 pairs, 12 held at most, us: every entry of the records added one after the other and
-// its slots found by walking the rows / this: n = 500 26.4 / 17.4, 20 000 51.5 / 21.2; 60 steps, 31 held, n = 500 27.7 / 20.3.
-template <int NT, bool SAME, bool MANY, class P>
-__device__ __forceinline__ void gram_sum_partials_flat(const double* __restrict__ grampart, int NE, int nwg, double* tot, P places) {
-    // (the trips of different batches to memory follow one another: a batch for all where that is not too many loads)
-    if (MANY && nwg <= 4) gram_sum_batches<NT, SAME, 4, MANY ? 8 : 1>(grampart, NE, nwg, tot, places);
-    else if (MANY && nwg <= 8) gram_sum_batches<NT, SAME, 8, MANY ? 4 : 1>(grampart, NE, nwg, tot, places);
-    else if (nwg <= 16) gram_sum_batches<NT, SAME, 16, MANY ? 4 : 1>(grampart, NE, nwg, tot, places);
-    else if (nwg <= 32) gram_sum_batches<NT, SAME, 32, MANY ? 2 : 1>(grampart, NE, nwg, tot, places);
-    else gram_sum_batches<NT, SAME, 64, 1>(grampart, NE, nwg, tot, places);
+template <int NT>
+__device__ __forceinline__ void gram_sum_held(const double* __restrict__ grampart, int NE, int nwg, double* tot, const GramPlaces& places) {
+    if (nwg <= 4) gram_sum_held_batches<NT, 4, 8>(grampart, NE, nwg, tot, places);
+    else if (nwg <= 8) gram_sum_held_batches<NT, 8, 4>(grampart, NE, nwg, tot, places);
+    else if (nwg <= 16) gram_sum_held_batches<NT, 16, 4>(grampart, NE, nwg, tot, places);
+    else if (nwg <= 32) gram_sum_held_batches<NT, 32, 2>(grampart, NE, nwg, tot, places);
+    else gram_sum_held_batches<NT, 64, 1>(grampart, NE, nwg, tot, places);
 }
 
-// The closing step from the totals tot (HELD: of GramPlaces, else of GramAll; LDS, complete: a barrier lies between their last write and this
+// The closing step from the totals tot (HELD: of GramPlaces, else of whole records; LDS, complete: a barrier lies between their last write and this
 // call).  c, head: the ring as it will be once the pending update is applied; base_slot: ring slot of the oldest pair.
 // Gs: (2 m + 2)^2 doubles, alpha_s: kMaxM + 1 (both LDS).  sc: the scalar block this works on.  mine_a, mine_b (or -1): the
 // slots of entry threadIdx.x, when the caller has worked them out while it waited for something.

@@ -240,11 +240,11 @@ __device__ __forceinline__ void dir_finish(double (&s)[6], double ub, double eps
 }
 
 // CLOSE: the Gram kernel before this one ended without its closing step.  Every workgroup here then does that step on a
-// private copy of the scalar block: adds the records of partial sums in workgroup order, applies the pending update, runs Algorithm 3 on coefficients and the stopping test -- the same
-// functions in the same order as the Gram kernel's last workgroup, so the same bits -- and takes the coefficients from
-// its copy.  Workgroup 0 leaves its copy in scal_next for the pass (nothing in this kernel reads that); the scalar
-// block itself is only read here.  What this saves is the Gram kernel's arrival (a fence, an atomic, a dependent round
-// of loads) and this kernel's own dependent reads of the status word and the coefficients.
+// private copy of the scalar block: adds the records of partial sums in workgroup order, applies the pending update, runs
+// Algorithm 3 on coefficients and the stopping test -- the same functions in the same order as the Gram kernel's last
+// workgroup, so the same bits -- and takes the coefficients from its copy.  Workgroup 0 leaves its copy in scal_next for the
+// pass (nothing in this kernel reads that); the scalar block itself is only read here.  What this saves is the Gram kernel's
+// arrival (an atomic, a dependent round of loads) and this kernel's own dependent reads of the status word and the coefficients.
 template <bool CLOSE>
 __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const double* __restrict__ x,
                                                 const double* __restrict__ g, const double* __restrict__ l,
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
         int pa, pb;                                                // (worked out while the records are on their way)
         gram_product_slots(tid < gram_products(m) ? tid : 0, m, pa, pb);
         asm volatile("" : "+v"(pa), "+v"(pb));
-        gram_sum_partials_flat<kBlock, false, false>(records.part, gram_entries(m), records.count, tot, GramAll{m});
+        gram_sum_partials_flat<kBlock, false>(records.part, gram_entries(m), records.count, tot);
         __syncthreads();
         if (sc.status != LBFGSB_RUNNING) {
             // (the pass reads its status word from scal_next: it must not find an older one there)
@@ -478,7 +478,7 @@ __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op,
         int pa, pb;
         gram_product_slots(tid < gram_products(m) ? tid : 0, m, pa, pb);
         asm volatile("" : "+v"(pa), "+v"(pb));
-        gram_sum_partials_flat<kBlock, false, false>(records.part, gram_entries(m), records.count, tot, GramAll{m});
+        gram_sum_partials_flat<kBlock, false>(records.part, gram_entries(m), records.count, tot);
         __syncthreads();
         if (sc.status != LBFGSB_RUNNING) {
             // (the kernel behind reads its status word from scal_next: it must not find an older one there)

@@ -68,7 +68,7 @@ def test_the_recursion_divides_sums_not_rows(m, pairs, seed):
     np.testing.assert_array_equal(d.cpu().numpy(), ref)
 
 
-# 63 504 (short vectors), 131 043 and 131 769 (odd, either side of 2^17), 131 404 entries
+# 63 504 (short vectors), 131 043 and 131 769 (odd, either side of 2^17), 131 406 entries
 @pytest.mark.parametrize("rows,cols", [(252, 252), (361, 363), (363, 363), (362, 362 + 1)])
 @pytest.mark.parametrize("m", [3, 10, 12])
 @pytest.mark.parametrize("uniform", [True, False])

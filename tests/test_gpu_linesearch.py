@@ -135,9 +135,9 @@ def test_steps_enqueued_without_waiting_survive_rejected_first_steps(case):
     ia, ib = a.info(), b.info()
     assert ia.iters == ib.iters == 16 and ia.status == ib.status == L.RUNNING
     assert torch.equal(xa, xb) and torch.equal(a.g(), b.g())
-    # f is a reported scalar that no decision reads (the Armijo test uses the difference): the short sequence carries it
-    # as f + [f(x + a p) - f(x)], the full one evaluates it from the new margins.  Which iterations run which sequence is
-    # counted from the rejected step, so f agrees too (bit for bit, with every record: test_gpu_follow.py)
+    # f is a reported scalar that no decision reads (the Armijo test uses the difference): an accepted first trial step carries
+    # it as f + [f(x + a p) - f(x)] in either sequence, a shorter step has it evaluated from the new margins.  Which iterations
+    # run which sequence is counted from the rejected step, so f agrees too (bit for bit, with every record: test_gpu_follow.py)
     assert ia.f == pytest.approx(ib.f, rel=1e-14) and ia.fevals == ib.fevals
     # and lbfgsb_solve from here on agrees too
     a2, b2 = a.solve(), b.solve()

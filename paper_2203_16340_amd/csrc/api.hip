@@ -243,11 +243,6 @@ Dims make_dims(int64_t n, int m, const lbfgsb_objective* o) {
     return dm;
 }
 
-__global__ __launch_bounds__(kBlock) void k_dbg_elementary(int which, int64_t n, const double* __restrict__ x, double* __restrict__ y) {
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
-        y[i] = which == 0 ? log_d(x[i]) : (which == 1 ? log1p_d(x[i]) : quotient_d(which == 2 ? 1.0 : x[i], 1.0 + x[i]));
-}
-
 void enqueue_step(lbfgsb_solver* s);
 
 // Logistic objective on the single-read pass: the columns X^T psi of an accepted step that was not the first trial step
@@ -1214,15 +1209,6 @@ int lbfgsb_dbg_project_direction(lbfgsb_solver* s, const double* x, const double
     return LBFGSB_OK;
 }
 
-int lbfgsb_dbg_elementary(int which, int64_t n, const double* x, double* y) {
-    if (which < 0 || which > 3 || n <= 0 || !x || !y) return fail(LBFGSB_E_INVALID_ARG, "which must be 0 to 3, n > 0, x and y not NULL");
-    const int64_t blocks = (n + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL(k_dbg_elementary, dim3((unsigned)(blocks > 4096 ? 4096 : blocks)), dim3(kBlock), 0, nullptr, which, n, x, y);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipStreamSynchronize(nullptr));
-    return LBFGSB_OK;
-}
-
 
 // ---- augmented Lagrangian algorithm (Algorithm 4 of the appendix, Eq. (augLag)) ------------------------------
 //
@@ -1717,5 +1703,25 @@ int lbfgsb_auglag_get_lambda(lbfgsb_auglag* al, double* lambda_out) {
 }
 
 lbfgsb_solver* lbfgsb_auglag_inner(lbfgsb_auglag* al) { return al ? al->inner : nullptr; }
+
+}  // extern "C"
+
+namespace {
+__global__ __launch_bounds__(kBlock) void k_dbg_elementary(int which, int64_t n, const double* __restrict__ x, double* __restrict__ y) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
+        y[i] = which == 0 ? log_d(x[i]) : (which == 1 ? log1p_d(x[i]) : quotient_d(which == 2 ? 1.0 : x[i], 1.0 + x[i]));
+}
+}  // namespace
+
+extern "C" {
+
+int lbfgsb_dbg_elementary(int which, int64_t n, const double* x, double* y) {
+    if (which < 0 || which > 3 || n <= 0 || !x || !y) return fail(LBFGSB_E_INVALID_ARG, "which must be 0 to 3, n > 0, x and y not NULL");
+    const int64_t blocks = (n + kBlock - 1) / kBlock;
+    hipLaunchKernelGGL(k_dbg_elementary, dim3((unsigned)(blocks > 4096 ? 4096 : blocks)), dim3(kBlock), 0, nullptr, which, n, x, y);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(nullptr));
+    return LBFGSB_OK;
+}
 
 }  // extern "C"

@@ -597,8 +597,10 @@ void launch_gemv(const Dims& dm, const Geometry& ge, const Buffers& bf, const AP
 // w partials = A^T psi_src (psi_src: Buffers::psi after an evaluation, Buffers::t after a direction pass)
 void launch_gemvt_from(const Dims& dm, const Geometry& ge, const Buffers& bf, const void* A, const double* psi_src,
                        int check_status, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-// Do the single-read passes leave the matrix in the chip's memory-side cache (256 MB), from one iteration to the next?  Ordinary
-// loads do, non-temporal ones pass it by; a matrix that does not fit only evicts itself.  Whole iterations, us, non-temporal /
+// Do the single-read passes read the matrix with ordinary loads, of which the chip's memory-side cache (256 MB) keeps more from one
+// iteration to the next than of non-temporal ones?  (Inferred from times; no counter tells its reads from the memory's.  A bare sum
+// repeated over one buffer, TB/s, ordinary / non-temporal: 192 MiB 5.83 / 5.51, 224 5.86 / 5.47, 256 5.44 / 5.40, 400 4.53 / 4.98.)  A
+// matrix that does not fit only evicts itself.  Whole iterations, us, non-temporal /
 // ordinary: fp64 25000 x 1000 (200 MB) 67 / 63, 4000 x 6000 71 / 64, 2000 x 10000 72 / 63.5, 1500 x 16000 83 / 74, 8000 x 2000
 // 54 / 53; fp32 4000 x 3001 50 / 45, 18000 x 3001 78 / 71, 3000 x 16000 80 / 71; logistic 400000 x 100 59 / 54, 20000 x 3000
 // 85 / 78; 3 to 20 MB the same.  Beyond: 280 MB 99 / 91, 288 MB 80.1 / 79.3, 333 MB 90.6 / 92.2, 340 MB 105 / 110, 320 MB

@@ -82,3 +82,19 @@ def test_around_the_cache_size(kind, dtype, cols, above):
                 s.step(False)
         assert float((one.x() - two.x()).norm()) <= 1e-10 * float(two.x().norm())
     one.close(), two.close()
+
+
+# the instantiations that stream the matrix (the tests on small matrices reach the other ones): whole tiles, and rows one element
+# short of them, which start on any element
+STREAMED = [(LSQ, np.float64, c) for c in (2048, 3072, 5120, 10240, 12288, 14336, 20428, 22528, 24576)]
+STREAMED += [(LSQ, np.float32, c) for c in (2048, 3072, 5120, 6144, 10240, 12288, 14336, 20428)]
+STREAMED += [(LOGI, np.float64, c) for c in (1024, 1536, 2048, 3072, 5120, 10240, 12288, 20428)]
+STREAMED += [(LOGI, np.float32, c) for c in (2048, 3072, 4096, 5120, 6144, 8192, 10240, 12288, 20428)]
+STREAMED += [(k, t, c * 16 // np.dtype(t).itemsize) for k in (LSQ, LOGI) for t in (np.float64, np.float32)
+             for c in (8, 16, 24, 32, 48, 64, 96, 128, 192, 256, 320, 384)]
+
+
+@pytest.mark.parametrize("kind,dtype,cols", STREAMED)
+@pytest.mark.parametrize("less", [0, 1])
+def test_streamed(kind, dtype, cols, less):
+    test_around_the_cache_size(kind, dtype, cols - less, True)

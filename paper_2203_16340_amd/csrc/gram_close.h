@@ -53,6 +53,7 @@ struct GramPlaces {
         return kGramHdr + lo * (4 * m + 3 - lo) / 2 + hi - lo;
     }
 };
+
 // Adds the records of `nwg` workgroups (NE doubles each; entry 0 is a maximum, the others are sums) in workgroup order into
 // tot[0 .. NE): thread idx takes entry idx, BATCH records at a time with every load of a batch issued before the first is used and
 // none of them under a test (past the last record: the last one again, not added).

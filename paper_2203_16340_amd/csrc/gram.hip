@@ -16,6 +16,7 @@
 //
 // (Steps on short vectors build it in small.hip.)
 #include <cstddef>
+#include <type_traits>
 
 #include "common.h"
 #include "gram_close.h"
@@ -31,12 +32,15 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int64_t kGramLongN = 1 << 17;   // from here on one workgroup per compute unit and the two-level sum
 
 // A kernel is made for M slots of the pair memory (m <= M).
+constexpr int gram_tot_at(int M) { return (2 * M + 2) * (2 * M + 2); }    // G, then the totals
+// Blocks of 16 slots (k_gram_blocks)
 constexpr int gram_slots(int M) { return 2 * M + 1; }                     // y ring 0 .. M-1 | g M | s ring M+1 .. 2M
-constexpr int gram_nb(int M) { return (gram_slots(M) + 15) / 16; }        // blocks of 16 slots
-constexpr int gram_waves_most(int M) { return M <= 10 ? 8 : 4; }          // (LDS: 16 NB vectors of 64 elements per wave)
+constexpr int gram_nb(int M) { return (gram_slots(M) + 15) / 16; }
 // pairs of blocks (a <= b) that hold products the recursion reads: not those of two blocks of s vectors only (16 a > M)
 constexpr int gram_na(int M) { return 1 + M / 16; }
-constexpr int gram_np(int M) { return gram_na(M) == 1 ? gram_nb(M) : 2 * gram_nb(M) - 1; }
+constexpr int gram_np(int M) { return 2 * gram_nb(M) - 1; }
+static_assert(gram_na(20) == 2 && gram_na(31) == 2, "the first two rows of blocks");
+constexpr int kGramBlockWaves = 4;                                        // (LDS: 16 NB vectors of 64 elements per wave)
 // A wave's 64 elements of every vector in LDS: doubles from one vector to the next, even and an odd multiple of two, so that
 // 16 lanes that read 16 bytes each of 16 vectors touch every bank once
 constexpr int kGramStride = 66;
@@ -45,10 +49,8 @@ constexpr int gram_lds_doubles(int M, int waves) {
     const int elems = waves * (gram_slots(M) + 1) * kGramStride, blocks = waves * gram_np(M) * 256;
     return elems > blocks ? elems : blocks;
 }
-constexpr int gram_tot_at(int M) { return (2 * M + 2) * (2 * M + 2); }
-static_assert(gram_tot_at(5) + gram_entries(5) <= gram_lds_doubles(5, 4) && gram_tot_at(10) + gram_entries(10) <= gram_lds_doubles(10, 4) &&
-              gram_tot_at(20) + gram_entries(20) <= gram_lds_doubles(20, 4) && gram_tot_at(31) + gram_entries(31) <= gram_lds_doubles(31, 4),
-              "G and the totals fit");
+static_assert(gram_tot_at(20) + gram_entries(20) <= gram_lds_doubles(20, kGramBlockWaves) &&
+              gram_tot_at(31) + gram_entries(31) <= gram_lds_doubles(31, kGramBlockWaves), "G and the totals fit");
 
 // Every workgroup has written NE doubles at grampart + blockIdx.x * NE (entry 0 is a maximum, all others are
 // sums).  The workgroups form at most kGramGroups groups of consecutive indices; the last workgroup of a group
@@ -106,34 +108,311 @@ __device__ __forceinline__ bool reduce_partials(double* __restrict__ grampart, i
 }  // namespace
 
 // G = B^T B on the matrix cores.  B = [vectors | n x (2m+1)], masked by the free set, is a tall-skinny contraction whose
-// operands stream from memory once.  A wave takes 64 consecutive elements per chunk: lane j loads element e0 + j of every
-// vector (512 contiguous bytes per load), evaluates Eq. (ws) for it, and writes the vectors' entries, masked, to the wave's
-// own part of LDS.  From there v_mfma_f64_16x16x4_f64 takes them, which multiplies a 16 x 4 by a 4 x 16 block: lane
-// (i = lane % 16, q = lane / 16) supplies A[i][q] and B[q][i'], for a Gram matrix both the same number, vector 16 b + i at one
-// element, so that one register feeds both operands.  Which element a (lane, step) holds does not matter for the sum: 16-byte
-// reads, elements 8 s + 2 q and the next.  Result of lane l, register r of a 16 x 16 block: row l/16 + 4 r, column l % 16.
-// No wave waits for another before its last chunk.
+// operands stream from memory once.
 //
-// LONG: what bounds it is memory: at n = 10^6 and 10 pairs the multiplications take 13 us of matrix-core time, the 21 vectors
-// 28 us at 6 TB/s.  Two chunks of vectors are in flight per wave in registers, eight waves per compute unit.  The chain of a
-// chunk: x, g (and l, u) three chunks ahead, the free set two chunks ahead -- fixed variables contribute nothing: their
-// lanes read what the first free lane reads, and a chunk without any reads the first chunk's -- the vectors next, then the
-// products.  10 pairs, us per launch, the vector unit's kernel (77 sums per lane, three waves reading 14 vectors each, 512
-// workgroups, closing step included) / this one / this one without its closing step: n = 10^6 47.6 / 42.7 / 35.7 (33.1 since
-// the groups' arrivals need no cache written back), 2 10^6 100 / 88 / 77; odd n 185 (operands staged for 2 x 2 tiles) / 45 /
-// 38.5; 20 pairs 182 / 96.  A bare sum over the same vectors takes 29 us at 10^6.  Loads straight into the operand layout, 16
-// vectors and 64 bytes of each per load: 41 / 90 with the closing step at 10^6 / 2 10^6; three chunks in flight: slower than
-// two.
+// Up to 10 pairs: v_mfma_f64_4x4x4_4b, four products of a 4 x 4 by a 4 x 4 block side by side.  Lane l supplies A[i][k] and
+// B[k][i] of block b, i = l % 4, b = l / 4 % 4, k = l / 16, and gets D[l / 16][l % 4] of block b; for a Gram matrix both
+// operands are the same kind of number, vector 4 t + i at one element, so one register feeds either side, and the four blocks
+// and k are sixteen elements whose order does not matter.  A lane can therefore load its operands straight into place: 16 bytes
+// of vector 4 t + i, which makes four runs of 256 bytes per load, and nothing passes through LDS.  The vectors are y | g in the
+// first K tiles and s in the next K; s with s is never asked for.  With 10 pairs that is 15 pairs of tiles, 960 cycles for 64
+// elements, where blocks of 16 x 16 take two, 2048 cycles, half of them for rows and columns that nobody reads -- and with
+// fewer pairs held it is less: K tiles hold 4 K - 1 pairs.
+//
+// LONG: memory bounds it.  A wave takes 64 consecutive elements per chunk, the vectors of two chunks in flight in registers,
+// eight waves per compute unit.  The chain of a chunk: x, g (and l, u) three chunks ahead, one element per lane; the free set
+// two chunks ahead -- fixed variables contribute nothing: a lane whose two elements are fixed reads what the first free pair's
+// lane reads, and a chunk without any reads the first chunk's -- the vectors next, then the products.  The loop is made for
+// K = 1, 2 and 3 tiles and the number of pairs held chooses.
+// us per launch, 16 x 16 blocks by way of LDS, whatever the number of pairs held / this: n = 2 10^6 (all free) with 0 pairs 50.9 /
+// 18.4, 3 51.3 / 27.6, 7 55.7 / 45, 10 76 / 71.5 (5.4 TB/s); 10^6 with 0 31 / 14.8, 3 31 / 17.1, 10 33.7 / 33.2.  (The vector
+// unit, 77 sums per lane, took 47.6 and 100 with 10 pairs; loads straight into the 16 x 16 layout, 64 bytes of each vector a load, 41 and 90.)
 // else: a few chunks in all, and what bounds it is latency: everything is requested at once, the ring slots whatever they
-// hold, and looked at when it is there.  Without the closing step, 10 pairs: n = 2000 6.9 -> 6.1 us, 5000 6.4 -> 5.6, 40 000
-// 9.2 -> 7.7; n = 3001, where the closing step was not left out, 21.0 + 5.5 (direction) -> 6.4 + 12.0.
-// The sums are kept short: 32 elements by the matrix core from zero, added to the wave's running sum, the waves', then the
-// workgroups' sums.
+// hold, and looked at when it is there.  10 pairs, without the closing step, as above: n = 5000 5.4 / 5.0, 40 000 7.4 / 7.0.
+// The sums are kept short: 16 elements by the matrix core from zero, added to the lane's running sum, the four blocks, the
+// waves, then the workgroups' sums.
+constexpr int kGramTileM = 10;                                            // up to this many pairs
+constexpr int gram_tiles(int M) { return M / 4 + 1; }                     // of y and g; as many of s
+constexpr int gram_tile_pairs(int K) { return K * (K + 1) / 2 + K * K; }
+
+typedef f64x2 f64x2_any __attribute__((aligned(8)));
+
+__device__ __forceinline__ double keep_if(double v, int keep) {           // keep: 0 or -1
+    return __hiloint2double(__double2hiint(v) & keep, __double2loint(v) & keep);
+}
+
+// Adds the products of 64 elements: lane l holds elements 2 (l / 4), the next, and the same behind 32 of vector 4 t + l % 4.
+template <int K>
+__device__ __forceinline__ void tile_products(const f64x2 (&v)[2 * K][2], unsigned long long bits, double (&sum)[gram_tile_pairs(K)]) {
+    const int at = ((threadIdx.x & 63) >> 2) * 2;
+    int keep[4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const unsigned w = (unsigned)(bits >> (32 * h)) >> at;
+        keep[2 * h] = __builtin_amdgcn_sbfe(w, 0, 1);
+        keep[2 * h + 1] = __builtin_amdgcn_sbfe(w, 1, 1);
+    }
+    double acc[gram_tile_pairs(K)];
+#pragma unroll
+    for (int k = 0; k < gram_tile_pairs(K); ++k) acc[k] = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        double o[2 * K];
+#pragma unroll
+        for (int t = 0; t < 2 * K; ++t) o[t] = keep_if(q & 1 ? v[t][q / 2].y : v[t][q / 2].x, keep[q]);
+        int k = 0;
+#pragma unroll
+        for (int a = 0; a < K; ++a) {
+#pragma unroll
+            for (int b = a; b < 2 * K; ++b, ++k) acc[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(o[a], o[b], acc[k], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < gram_tile_pairs(K); ++k) sum[k] += acc[k];
+}
+
+// The four blocks added, and the wave's 4 x 4 results of every pair of tiles into its part of LDS: pair k, row i, column j at
+// 16 k + 4 i + j.
+template <int K>
+__device__ __forceinline__ void tile_results(double (&sum)[gram_tile_pairs(K)], double* mine) {
+    const int lane = threadIdx.x & 63;
+    constexpr int kRowRor4 = 0x124, kRowRor8 = 0x128;                     // lane i of a row of 16 takes from i - 4, i - 8
+#pragma unroll
+    for (int k = 0; k < gram_tile_pairs(K); ++k) {
+        double t = sum[k];
+        t += dpp_move<kRowRor4>(t);
+        t += dpp_move<kRowRor8>(t);
+        if ((lane & 12) == 0) mine[16 * k + 4 * (lane >> 4) + (lane & 3)] = t;
+    }
+}
+// Where tile_results has left the product of row a (y and g) with row b (the same) or column b (s).
+__device__ __forceinline__ int tile_place(int K, int a, int b, bool b_is_s) {
+    const int lo = b_is_s || a < b ? a : b, hi = (b_is_s || a < b ? b : a) + (b_is_s ? 4 * K : 0);
+    const int ta = lo >> 2, tb = hi >> 2;
+    return 16 * (ta * 2 * K - ta * (ta - 1) / 2 + tb - ta) + 4 * (lo & 3) + (hi & 3);
+}
+
 template <int M, int NW, bool LONG, bool DBG>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4)))
 void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const double* __restrict__ g, const double* __restrict__ l,
             const double* __restrict__ u, const double* __restrict__ S, const double* __restrict__ Y, uint8_t* __restrict__ mask,
             Scal* __restrict__ scal, double* __restrict__ grampart, int evaluate_stop, int no_close) {
+    constexpr int NT = 64 * NW, KM = gram_tiles(M), kWaveLds = 16 * gram_tile_pairs(KM);
+    constexpr int kClose = gram_tot_at(M) + gram_entries(M);
+    __shared__ __align__(16) double dyn[NW * kWaveLds > kClose ? NW * kWaveLds : kClose];   // the waves' results; later G and the totals
+    __shared__ double red[NW * 3];
+    __shared__ double alpha_s[kMaxM + 1];
+    __shared__ int flag;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // one load per wave fetches the integer header of the scalar block (status, ring position, pending
+    // update); readlanes hand the fields to every lane
+    static_assert(offsetof(Scal, pend_ok) < 64, "header fields must sit in the first 16 ints");
+    const int hdr = lane < 16 ? reinterpret_cast<const int*>(scal)[lane] : 0;
+
+    const int64_t nchunks = (n + 63) / 64, stride = (int64_t)gridDim.x * NW;
+    const int64_t ch0 = (int64_t)blockIdx.x * NW + wave;
+    const int64_t bstride = op.uniform_bounds ? 0 : 1;   // same bounds everywhere: l and u are not streamed
+    struct Elem { double x, g, l, u, y; uint8_t mk; };
+    auto request = [&](int64_t ch, Elem& s, const double* y_new) {
+        const int64_t e = ch * 64 + lane, ec = e < n ? e : n - 1;
+        s.x = x[ec]; s.g = g[ec]; s.l = l[ec * bstride]; s.u = u[ec * bstride];
+        s.y = LONG ? y_new[ec] : 0.0;
+        if constexpr (DBG) s.mk = mask[ec];
+    };
+    double pginf = 0.0, ynew = 0.0;
+    int nfixed = 0;
+    // Eq. (ws) and the statistics of a chunk; the bits of its free elements
+    auto decide = [&](int64_t ch, const Elem& s) -> unsigned long long {
+        const int64_t e = ch * 64 + lane;
+        const bool in = e < n;
+        bool fr;
+        if constexpr (DBG) {
+            fr = s.mk != 0;
+        } else {
+            const bool at_lower = (s.x <= s.l + op.eps) && (s.g >= 0.0);
+            const bool at_upper = (s.x >= s.u - op.eps) && (s.g <= 0.0);
+            fr = !(at_lower || at_upper);
+            mask[in ? e : n - 1] = (uint8_t)fr;       // (past the end: the last element's own value once more)
+        }
+        pginf = fmax(pginf, in ? fabs(s.x - clampd(s.x - s.g, s.l, s.u)) : 0.0);
+        if (LONG) ynew = fma(in ? s.y : 0.0, s.y, ynew);
+        const unsigned long long bits = __ballot(fr && in);
+        nfixed += __popcll(__ballot(in)) - __popcll(bits);
+        return bits;
+    };
+    const int i4 = lane & 3, pair_at = (lane >> 2) * 2;
+    // (the second element of an odd vector's last pair is whatever follows the vector in the workspace: it counts as fixed)
+    auto short_slot = [&](int t) -> const double* {      // tile t's vector of this lane, by ring slot
+        const int k = 4 * (t < KM ? t : t - KM) + i4;
+        if (t < KM && k >= M) return g;
+        return (t < KM ? Y : S) + (int64_t)(k < m ? k : m - 1) * n;
+    };
+    Elem sa;
+    f64x2 first[LONG ? 1 : 2 * KM][2];
+    auto short_fetch = [&](int64_t ch) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int64_t e = ch * 64 + 32 * h + pair_at, ec = e < n ? e : n - 1;
+#pragma unroll
+            for (int t = 0; t < (LONG ? 1 : 2 * KM); ++t) first[t][h] = *reinterpret_cast<const f64x2_any*>(short_slot(t) + ec);
+        }
+    };
+    if constexpr (!LONG) {
+        request(ch0, sa, nullptr);
+        short_fetch(ch0);
+    }
+    int slot_a, slot_b;                                  // (entry tid of the record; here, while the loads are on their way)
+    gram_product_slots(tid < gram_products(m) ? tid : 0, m, slot_a, slot_b);
+    asm volatile("" : "+v"(slot_a), "+v"(slot_b));
+    auto field = [&](size_t off) { return __builtin_amdgcn_readlane(hdr, (int)(off / 4)); };
+    const int status = field(offsetof(Scal, status));
+    if (status != LBFGSB_RUNNING) {
+        // a step that finds the solver parked by the short logistic sequence is counted, so that the host can redo it
+        if (evaluate_stop && !DBG && blockIdx.x == 0 && tid == 0) {
+            if (status == kStatusBail) scal->bail_skipped += 1;
+            note_progress(op, status);
+        }
+        return;
+    }
+    int head = field(offsetof(Scal, head)), c = field(offsetof(Scal, count));
+    if (field(offsetof(Scal, pend_valid))) {          // same rule as effective_ring()
+        if (field(offsetof(Scal, pend_ok))) { head = (head + 1) % m; c = c < m ? c + 1 : m; }
+        else c = 0;
+    }
+    const double yn_old = no_close ? 1.0 : prefetch_ynorm2(scal, c, head, m);   // (used by the last workgroup's recursion, fetched now)
+    const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;   // ring slot of the oldest pair
+    const int newest = c > 0 ? (head - 1 + m) % m : -1;
+    double* mine = dyn + wave * kWaveLds;
+    int K = KM;                                          // tiles of y and g in the sums left in LDS
+    if constexpr (LONG) {
+        // vectors by age: y of pair j in row j, g in row c, s of pair j in column j; the rest read g, and nobody their products
+        const double* y_new = newest >= 0 ? Y + (int64_t)newest * n : g;
+        auto stream = [&](auto tiles) {
+            constexpr int KT = decltype(tiles)::value;
+            const double* from[2 * KT];
+#pragma unroll
+            for (int t = 0; t < 2 * KT; ++t) {
+                const int j = 4 * (t < KT ? t : t - KT) + i4, slot = base_slot + j < m ? base_slot + j : base_slot + j - m;
+                from[t] = j < c ? (t < KT ? Y : S) + (int64_t)slot * n : g;
+            }
+            auto fetch = [&](int64_t ch, unsigned long long bits, f64x2 (&v)[2 * KT][2]) {
+                const unsigned head_pair = bits ? (unsigned)__builtin_ctzll(bits) & ~1u : 0u;
+                const int64_t e0 = bits ? ch * 64 : 0;   // (uniform)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const unsigned w = (unsigned)(bits >> (32 * h)) >> pair_at;
+                    const int64_t e = e0 + (w & 3u ? 32u * h + pair_at : head_pair);
+#pragma unroll
+                    for (int t = 0; t < 2 * KT; ++t) v[t][h] = *reinterpret_cast<const f64x2_any*>(from[t] + e);
+                }
+            };
+            double sum[gram_tile_pairs(KT)];
+#pragma unroll
+            for (int k = 0; k < gram_tile_pairs(KT); ++k) sum[k] = 0.0;
+            if (ch0 < nchunks) {
+                f64x2 va[2 * KT][2], vb[2 * KT][2];
+                Elem sb;
+                request(ch0, sa, y_new);
+                request(ch0 + stride, sb, y_new);
+                unsigned long long ba = decide(ch0, sa), bb;
+                fetch(ch0, ba, va);
+                request(ch0 + 2 * stride, sa, y_new);
+                // (two chunks a trip and one way out: a chunk past the end has no free element and adds nothing)
+                for (int64_t ch = ch0; ch < nchunks; ch += 2 * stride) {
+                    bb = decide(ch + stride, sb);
+                    fetch(ch + stride, bb, vb);
+                    request(ch + 3 * stride, sb, y_new);
+                    __builtin_amdgcn_sched_barrier(0);
+                    tile_products<KT>(va, ba, sum);
+                    __builtin_amdgcn_sched_barrier(0);
+                    ba = decide(ch + 2 * stride, sa);
+                    fetch(ch + 2 * stride, ba, va);
+                    request(ch + 4 * stride, sa, y_new);
+                    __builtin_amdgcn_sched_barrier(0);
+                    tile_products<KT>(vb, bb, sum);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            tile_results<KT>(sum, mine);
+        };
+        K = c / 4 + 1;
+        if (K == 1) stream(std::integral_constant<int, 1>());
+        else if (KM == 2 || K == 2) stream(std::integral_constant<int, 2>());
+        else if constexpr (KM == 3) stream(std::integral_constant<int, 3>());
+    } else {
+        double sum[gram_tile_pairs(KM)];
+#pragma unroll
+        for (int k = 0; k < gram_tile_pairs(KM); ++k) sum[k] = 0.0;
+        for (int64_t ch = ch0; ch < nchunks; ch += stride) {
+            if (ch != ch0) {
+                request(ch, sa, nullptr);
+                short_fetch(ch);
+            }
+            // ||y_new||^2, over fixed variables too, by the lanes that hold it
+#pragma unroll
+            for (int t = 0; t < KM; ++t) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int64_t e = ch * 64 + 32 * h + pair_at;
+                    if (4 * t + i4 == newest) {
+                        ynew = fma(e < n ? first[t][h].x : 0.0, first[t][h].x, ynew);
+                        ynew = fma(e + 1 < n ? first[t][h].y : 0.0, first[t][h].y, ynew);
+                    }
+                }
+            }
+            const unsigned long long bits = decide(ch, sa);
+            tile_products<KM>(first, bits, sum);
+        }
+        tile_results<KM>(sum, mine);
+    }
+
+    // this workgroup's record: the waves' results added in wave order
+    pginf = wave_max(pginf);
+    ynew = wave_sum(ynew);
+    if (lane == 0) { red[wave] = pginf; red[NW + wave] = (double)nfixed; red[2 * NW + wave] = ynew; }
+    __syncthreads();
+    const int NE = gram_entries(m);
+    double* part = grampart + (int64_t)blockIdx.x * NE;
+    for (int idx = tid; idx < gram_products(m); idx += NT) {
+        int a = slot_a, b = slot_b;
+        if (idx != tid) gram_product_slots(idx, m, a, b);
+        // row or column of a slot: by ring slot, LONG by age (c, or M, is g; past the last pair: not held, any number)
+        auto place = [&](int slot) -> int {
+            if (slot == m) return LONG ? c : M;
+            const int ring = slot < m ? slot : slot - m - 1;
+            if (!LONG) return ring;
+            const int j = ring >= base_slot ? ring - base_slot : ring - base_slot + m;
+            return j < c ? j : 0;
+        };
+        const int src = tile_place(K, place(a), place(b), b > m);
+        double t = dyn[src];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t += dyn[w * kWaveLds + src];
+        publish(part + kGramHdr + idx, t);
+    }
+    if (tid < 3) {
+        double t = red[tid * NW];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t = tid == 0 ? fmax(t, red[w]) : t + red[tid * NW + w];
+        publish(part + tid, t);
+    }
+    if (!LONG && no_close) return;   // the direction kernel adds the records and does the rest
+    double* tot = dyn + gram_tot_at(M);
+    if (!reduce_partials<NT, false>(grampart, NE, scal, &flag, tot, LONG && no_close, GramPlaces{m, c, base_slot})) return;
+    gram_finish<NT, 10, false>(tot, dyn, alpha_s, scal, m, c, head, base_slot, op, yn_old, DBG, evaluate_stop, true);
+    __syncthreads();
+    if (tid == 0 && evaluate_stop) note_progress(op, scal->status);
+}
+
+// Beyond 10 pairs: v_mfma_f64_16x16x4_f64, a 16 x 4 by a 4 x 16 block (the pairs of 4 x 4 tiles would take all registers).  A lane
+// loads one element of every vector (512 contiguous bytes per load) and writes it, masked, to the wave's own part of LDS; from
+// there lane (i = lane % 16, q = lane / 16) supplies vector 16 b + i at elements 8 s + 2 q and the next, for either operand.  Result
+// of lane l, register r of a block: row l/16 + 4 r, column l % 16.  The rest is as above.  20 pairs, n = 10^6: 96 us a launch.
+template <int M, int NW, bool LONG, bool DBG>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4)))
+void k_gram_blocks(int64_t n, int m, Opts op, const double* __restrict__ x, const double* __restrict__ g, const double* __restrict__ l,
+            const double* __restrict__ u, const double* __restrict__ S, const double* __restrict__ Y, uint8_t* __restrict__ mask,
+            Scal* __restrict__ scal, double* __restrict__ grampart, int evaluate_stop, int) {
     constexpr int NT = 64 * NW, NB = gram_nb(M), NA = gram_na(M), NP = gram_np(M), NV = gram_slots(M);
     extern __shared__ __align__(16) double dyn[];   // the waves' elements; their blocks; later G and the totals
     __shared__ double red[NW * 3];
@@ -221,8 +500,7 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
     // where the waves' blocks hold the product that is entry idx of a record
     auto block_place = [&](int idx) -> int {
         int a, b;
-        if (M > 10) gram_product_slots_many(idx, m, a, b);
-        else gram_product_slots(idx, m, a, b);
+        gram_product_slots_many(idx, m, a, b);
         // (record: y, g, s of m slots each; here of M)
         a += a == m ? M - m : 0;
         b += b >= m ? M - m : 0;
@@ -260,7 +538,7 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
         if (field(offsetof(Scal, pend_ok))) { head = (head + 1) % m; c = c < m ? c + 1 : m; }
         else c = 0;
     }
-    const double yn_old = no_close ? 1.0 : prefetch_ynorm2(scal, c, head, m);   // (used by the last workgroup's recursion, fetched now)
+    const double yn_old = prefetch_ynorm2(scal, c, head, m);   // (used by the last workgroup's recursion, fetched now)
     const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;   // ring slot of the oldest pair
     const int newest = c > 0 ? (head - 1 + m) % m : -1;
     if constexpr (LONG) {
@@ -343,12 +621,10 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
         for (int w = 1; w < NW; ++w) t = tid == 0 ? fmax(t, red[w]) : t + red[tid * NW + w];
         publish(part + tid, t);
     }
-    if (!LONG && no_close) return;   // the direction kernel adds the records and does the rest
     double* tot = dyn + gram_tot_at(M);
-    // (beyond 10 pairs a record has more entries than the workgroup threads, so only those are added that the pairs held need)
-    constexpr bool HELD = M > 10;
-    if (!reduce_partials<NT, HELD>(grampart, NE, scal, &flag, tot, LONG && no_close, GramPlaces{m, c, base_slot})) return;
-    gram_finish<NT, M < 10 ? 10 : M, HELD>(tot, dyn, alpha_s, scal, m, c, head, base_slot, op, yn_old, DBG, evaluate_stop, true);
+    // (a record has more entries than the workgroup threads, so only those are added that the pairs held need)
+    if (!reduce_partials<NT, true>(grampart, NE, scal, &flag, tot, false, GramPlaces{m, c, base_slot})) return;
+    gram_finish<NT, M, true>(tot, dyn, alpha_s, scal, m, c, head, base_slot, op, yn_old, DBG, evaluate_stop, true);
     __syncthreads();
     if (tid == 0 && evaluate_stop) note_progress(op, scal->status);
 }
@@ -357,9 +633,9 @@ namespace {
 constexpr int gram_m_for(int m) { return m <= 5 ? 5 : (m <= 10 ? 10 : (m <= 20 ? 20 : 31)); }
 }  // namespace
 
-// Waves per workgroup.  Two waves of a SIMD take turns at its matrix core (0.85 us a chunk), so a problem of few chunks has
-// four; beyond 64 workgroups their records would take the direction kernel more than one round of loads to add.
-static int gram_waves_for(int64_t n, int m) { return n <= 64 * 4 * 64 ? 4 : gram_waves_most(gram_m_for(m)); }
+// Waves per workgroup.  A problem of few chunks has four, so that the matrix cores' work is spread; beyond 64 workgroups their
+// records would take the direction kernel more than one round of loads to add.
+static int gram_waves_for(int64_t n, int m) { return m > kGramTileM || n <= 64 * 4 * 64 ? 4 : 8; }
 
 int gram_blocks_for(int64_t n, int m, bool few) {
     const int nw = gram_waves_for(n, m);
@@ -385,24 +661,19 @@ namespace {
 
 typedef void (*GramKernel)(int64_t, int, Opts, const double*, const double*, const double*, const double*, const double*,
                            const double*, uint8_t*, Scal*, double*, int, int);
-template <int M, int NW>
-GramKernel gram_kernel(bool is_long, bool dbg) {
-    if constexpr (NW == gram_waves_most(M)) {
-        if (is_long) return dbg ? k_gram<M, NW, true, true> : k_gram<M, NW, true, false>;
-    }
-    return dbg ? k_gram<M, NW, false, true> : k_gram<M, NW, false, false>;
-}
 GramKernel gram_kernel_for(const Dims& dm, bool dbg, size_t* lds, int* threads) {
     const bool is_long = dm.n >= kGramLongN;
     const int M = gram_m_for(dm.m), nw = gram_waves_for(dm.n, dm.m);
-    *lds = (size_t)gram_lds_doubles(M, nw) * 8;
+    *lds = M > kGramTileM ? (size_t)gram_lds_doubles(M, nw) * 8 : 0;
     *threads = 64 * nw;
+#define LB_GRAM(K, M, NW, LONG) (dbg ? K<M, NW, LONG, true> : K<M, NW, LONG, false>)
     switch (M) {
-        case 5: return nw == 4 ? gram_kernel<5, 4>(is_long, dbg) : gram_kernel<5, 8>(is_long, dbg);
-        case 10: return nw == 4 ? gram_kernel<10, 4>(is_long, dbg) : gram_kernel<10, 8>(is_long, dbg);
-        case 20: return gram_kernel<20, 4>(is_long, dbg);
-        default: return gram_kernel<31, 4>(is_long, dbg);
+        case 5: return is_long ? LB_GRAM(k_gram, 5, 8, true) : (nw == 4 ? LB_GRAM(k_gram, 5, 4, false) : LB_GRAM(k_gram, 5, 8, false));
+        case 10: return is_long ? LB_GRAM(k_gram, 10, 8, true) : (nw == 4 ? LB_GRAM(k_gram, 10, 4, false) : LB_GRAM(k_gram, 10, 8, false));
+        case 20: return is_long ? LB_GRAM(k_gram_blocks, 20, 4, true) : LB_GRAM(k_gram_blocks, 20, 4, false);
+        default: return is_long ? LB_GRAM(k_gram_blocks, 31, 4, true) : LB_GRAM(k_gram_blocks, 31, 4, false);
     }
+#undef LB_GRAM
 }
 
 }  // namespace

@@ -35,6 +35,24 @@ def test_two_loop(n, m, pairs):
     assert rel_err(d, ref) <= 1e-12
 
 
+# tiles of four vectors: the last pair count of one, two and three tiles and the next, in a memory they fill and in one they do not
+@pytest.mark.parametrize("m,pairs", [(3, 3), (4, 4), (10, 3), (10, 7), (8, 8), (10, 8), (5, 0), (10, 0)])
+@pytest.mark.parametrize("n", [95, 8193, 131071, 131072, 163839])
+def test_two_loop_by_pairs_held(m, pairs, n):
+    rng = np.random.default_rng(n + 101 * m + pairs)
+    S = rng.normal(size=(pairs, n))
+    Y = S * np.exp(rng.normal(size=n) * 0.5) + 0.3 * rng.normal(size=(pairs, n))
+    g, mask, yn = rng.normal(size=n), (rng.random(n) < 0.4).astype(np.uint8), np.einsum("ij,ij->i", Y, Y)
+    mask[0] = 1
+    s = make_solver(L.OBJ_LSQ, np.zeros((1, n)), np.zeros(1), np.full(n, -np.inf), np.full(n, np.inf), m)
+    d, used = s.dbg_two_loop(to_dev(S), to_dev(Y), to_dev(yn), to_dev(g), to_dev(mask))
+    s.close()
+    ref, used_ref = oracle.two_loop(S, Y, g, mask, 1e-10, ynorm2=yn)
+    d = d.cpu().numpy()
+    assert used == used_ref and np.all(d[mask == 0] == 0.0)
+    assert rel_err(d, ref) <= 1e-12
+
+
 def exact_two_loop_case(c, n, seed):
     """Integer pairs with <s_i, y_i> = 3 whose every alpha_i, beta_i and result is a whole number: dividing a sum by 3 is exact
     also as a product with the rounded 1/3, where a row of G divided by 3 beforehand is rounded entry by entry.

@@ -9,7 +9,7 @@
 //   k_ot_sums + k_ot_cols   K z for z = x (evaluation) or the selected direction p, the loss partials
 //   k_ot_eval_finish        gradient M + lambda phi'(P) + K^T (omega . residual), objective value
 //   k_ot_update_gauss       closed-form Armijo search (the objective is quadratic along p) and the update
-//   k_ot_ls_entropy / k_ot_update_entropy   the same for the entropy, whose line search
+//   k_ot_ls_* / k_ot_update_entropy   the same for the entropy, whose line search
 //                           needs one pass over (x, p) per batch of trial steps
 #include <cstddef>
 #include <type_traits>
@@ -34,18 +34,40 @@ __device__ __forceinline__ double reg_slope(int kind, double lambda, double p) {
     return lambda * (log_d(p) + 1.0);
 }
 
-// K z, first half: the sums of the RPW rows this workgroup owns, and its partial column sums.
+// Entropy: f(x + a p) - f(x) = a <g,p> + a^2/2 sum omega (K p)^2 + lambda sum_ij D(x_ij + a p_ij ; x_ij) with the
+// Bregman divergence of p log p,  D(xt; x) = xt log(xt/x) - (xt - x) = x h(r),  r = (xt - x)/x,
+// h(r) = (1 + r) log(1 + r) - r  (series for small r, where the closed form cancels).
+__device__ __forceinline__ double entropy_h(double r) {
+    if (r <= -1.0) return 1.0;                       // xt = 0: 0 log 0 = 0
+    if (fabs(r) < 1e-2) {
+        const double r2 = r * r;
+        return r2 * (0.5 + r * (-1.0 / 6.0 + r * (1.0 / 12.0 + r * (-1.0 / 20.0 + r * (1.0 / 30.0 + r * (-1.0 / 42.0))))));
+    }
+    return (1.0 + r) * log1p_d(r) - r;
+}
+
+// Does the row-sum kernel form the first step length's sum?  It saves a launch and a trip of p from memory, where its workgroups
+// fill the chip or have little to do, and are not so many that adding their sums costs more.  Whole runs, us, a launch of its own /
+// in the row sums: 32 x 2000 1421 / 1401, 128 x 1000 1439 / 1404, 128 x 4000 1703 / 1687, 250 x 1000 1405 / 1350, 300 x 300 1389 / 1368,
+// 1000 x 1000 2348 / 2288; but 64 x 8000 1857 / 1929, 20 000 x 40 (1250 workgroups) 3567 / 3596.
+bool ot_sums_first_length(const Dims& dm, const Geometry& ge) {
+    return dm.kind == LBFGSB_OBJ_OT_ENTROPY && ge.ot_row_blocks <= 512 && (ge.ot_row_blocks >= 192 || ge.ot_rpw * dm.cols <= 4096);
+}
+
+// K z, first half: the sums of the RPW rows this workgroup owns, and its partial column sums.  first (or null): the entropy's
+// line search, sum_e x_e h(a_0 z_e / x_e) over these rows.
 template <int RPW>
 __global__ __launch_bounds__(kBlock) void k_ot_sums(Dims dm, OtArgs a, int eval, int check_status,
                                                     const double* __restrict__ x, const double* __restrict__ p1,
                                                     const double* __restrict__ p2, Scal* __restrict__ scal,
                                                     double* __restrict__ out, double* __restrict__ wpart,
                                                     double* __restrict__ losspart, const double* __restrict__ dir_part,
-                                                    int dir_blocks, double eps, Scal* __restrict__ scal_next) {
+                                                    int dir_blocks, double eps, Scal* __restrict__ scal_next, double* __restrict__ first) {
     __shared__ double red[kWaves * (RPW + 1 > 7 ? RPW + 1 : 7)];
     const int tid = threadIdx.x;
     const int status = check_status ? (scal_next ? scal_next : scal)->status : LBFGSB_RUNNING;
     const double* z = x;
+    double a0 = 1.0;
     if (!eval && dir_blocks > 0) {
         // Algorithm 2's choice from the direction kernel's per-workgroup sums (requested together with the status
         // word); workgroup 0 records it for the kernels that follow, and moves the copy of the scalar block that the
@@ -67,9 +89,10 @@ __global__ __launch_bounds__(kBlock) void k_ot_sums(Dims dm, OtArgs a, int eval,
             scal->branch = ch.branch; scal->gp = ch.gp; scal->alpha_ub = ch.alpha_ub; scal->pp = ch.pp; scal->xp = ch.xp;
         }
         z = ch.branch == 1 ? p1 : p2;
+        a0 = fmin(1.0, ch.alpha_ub);
     } else {
         if (status != LBFGSB_RUNNING) return;
-        if (!eval) z = scal->branch == 1 ? p1 : p2;
+        if (!eval) { z = scal->branch == 1 ? p1 : p2; a0 = fmin(1.0, scal->alpha_ub); }
     }
     const int64_t r0 = (int64_t)blockIdx.x * RPW;
     const int nr = dm.rows - r0 < RPW ? (int)(dm.rows - r0) : RPW;
@@ -119,6 +142,27 @@ __global__ __launch_bounds__(kBlock) void k_ot_sums(Dims dm, OtArgs a, int eval,
             }
         }
         losspart[blockIdx.x] = loss;
+    }
+    if (first) {
+        // (the rows' entries once more, from the cache: the sums above want all of a column's rows in flight, the logarithms a few)
+        const int64_t e_end = (r0 + nr) * dm.cols;
+        double s[1] = {0.0};
+        for (int64_t e0 = r0 * dm.cols + tid; e0 < e_end; e0 += 4 * kBlock) {
+            double xv[4], pv[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int64_t e = e0 + k * kBlock < e_end ? e0 + k * kBlock : e0;
+                xv[k] = x[e];
+                pv[k] = z[e];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double h = entropy_h(a0 * (pv[k] / xv[k]));
+                s[0] = e0 + k * kBlock < e_end ? fma(xv[k], h, s[0]) : s[0];
+            }
+        }
+        block_sum<1, kWaves>(s, red);
+        if (tid == 0) first[blockIdx.x] = s[0];
     }
 }
 
@@ -311,47 +355,28 @@ __global__ __launch_bounds__(kBlock) void k_ot_update_gauss(Dims dm, Opts op, Ot
     }
 }
 
-// Entropy: f(x + a p) - f(x) = a <g,p> + a^2/2 sum omega (K p)^2 + lambda sum_ij D(x_ij + a p_ij ; x_ij) with the
-// Bregman divergence of p log p,  D(xt; x) = xt log(xt/x) - (xt - x) = x h(r),  r = (xt - x)/x,
-// h(r) = (1 + r) log(1 + r) - r  (series for small r, where the closed form cancels).
-__device__ __forceinline__ double entropy_h(double r) {
-    if (r <= -1.0) return 1.0;                       // xt = 0: 0 log 0 = 0
-    if (fabs(r) < 1e-2) {
-        const double r2 = r * r;
-        return r2 * (0.5 + r * (-1.0 / 6.0 + r * (1.0 / 12.0 + r * (-1.0 / 20.0 + r * (1.0 / 30.0 + r * (-1.0 / 42.0))))));
-    }
-    return (1.0 + r) * log1p_d(r) - r;
+// The step lengths are a_0 = min(1, bound), a_k = a_{k-1} backtrack.  From the second iteration of a run on the first is accepted
+// nearly always, at a start on the lower bound, where p/x is huge, one after a dozen or more.  So a_0 is judged alone, from a sum
+// that the row-sum kernel has formed on the way (where the rows are enough workgroups for a logarithm per entry, else a launch of
+// its own), by the first of two further launches; if it is refused, that launch sums the 8 lengths k = kLsCoarse.  The second one
+// looks for the first of these that is acceptable and sums what lies between it and the one before: the change of the objective
+// along p is convex (the entropy is, and the marginal terms where their weights make a curvature sum omega (K p)^2 >= 0), so every
+// length behind an acceptable one is acceptable and none before a refused one.  At most kLsFine lengths at a time; with a negative
+// curvature all from the second on.  Only beyond k = 60, the default limit, does the last workgroup go on alone, one at a time.
+// 2 10^6 entries, us: row sums 9, the first two lengths 15, the next eight 59, the remaining 51 287, the two launches when not needed
+// 7 and 4.6 -> row sums with the first length 17.5, coarse lengths 51, fine 86, not needed 6.5 and 4.6.
+constexpr int kLsCoarseCount = 8, kLsFine = 13, kLsAllMax = 54;
+__device__ constexpr int kLsCoarse[kLsCoarseCount] = {1, 2, 3, 8, 14, 21, 34, 47};
+constexpr int kLsLast = 60;
+
+__device__ __forceinline__ double step_length(double a0, int k, double backtrack) {   // (the same multiplications everywhere)
+    for (int j = 0; j < k; ++j) a0 *= backtrack;
+    return a0;
 }
-
-// NTRY step lengths a0 backtrack^first, ... per sweep over (x, p).  The first launch tries two; two further
-// launches, which return at once when an earlier one found the step (such a launch still costs ~4.5 us: the scalar
-// block was just written, so its status word comes from memory), try the next kLsBatch and then kLsTail (a long run
-// of rejected steps happens at a start on the lower bound, where p/x is huge).  Together they cover the default
-// limit of 60 backtracks; only beyond those does the last workgroup of the last launch go on alone, one length at
-// a time.
-constexpr int kLsTail = 51;   // 2 + kLsBatch + kLsTail = 61 step lengths
-// In wide workgroups the tail's step lengths are taken in groups, a sweep over (x, p) each (they come from the cache after
-// the first): 51 sums and as many logarithms in flight take all registers of a SIMD for one wavefront.  First iteration of a
-// run at 2 10^6 entries, with the runtime's logarithm: 545 -> 481 us for the 51 lengths (the update kernel 47 -> 43 us, the first two lengths
-// 25 -> 23); with the one of elementary.h 294, the next eight 91 -> 63, the first two 25 -> 17.
-// With 256 threads there are two wavefronts per SIMD either way, and groups gained nothing (4.4 10^5 entries).
-constexpr int ls_group(int threads) { return threads > 256 ? 17 : kLsTail; }
-
-// Armijo test of NTRY step lengths a_first, a_first * backtrack, ... (indices first, first + 1, ...) given their sums
-// tot[k] = sum_e x_e h(a_k p_e / x_e): the first acceptable one, or found = -1.
-template <int NTRY>
-__device__ __forceinline__ void entropy_decide(const double (&tot)[NTRY], int first, double a_first, double gp, double tt,
-                                               double lambda, const Opts& op, int& found, double& a_acc, double& a_last) {
-    found = -1;
-    a_acc = 0.0;
-    double av = a_first;
-#pragma unroll
-    for (int k = 0; k < NTRY; ++k) {
-        const double df = av * (gp + 0.5 * av * tt) + lambda * tot[k];
-        if (found < 0 && first + k <= op.max_backtracks && isfinite(df) && df <= op.c1 * av * gp) { found = first + k; a_acc = av; }
-        if (k + 1 < NTRY) av *= op.backtrack;
-    }
-    a_last = av;
+// Armijo test of step length a, given sum_e x_e h(a p_e / x_e)
+__device__ __forceinline__ bool entropy_accepts(double sum, double a, double gp, double tt, double lambda, const Opts& op) {
+    const double df = a * (gp + 0.5 * a * tt) + lambda * sum;
+    return isfinite(df) && df <= op.c1 * a * gp;
 }
 
 // block_sum for workgroups of many waves: thread k adds up the waves' sums of value k (every thread adding all of them
@@ -378,124 +403,158 @@ __device__ __forceinline__ void block_sum_by_thread(double (&v)[K], double* lds)
     for (int k = 0; k < K; ++k) v[k] = lds[NW * K + k];
 }
 
-// NPREV > 0: the launch before this one (NPREV step lengths from index first - NPREV on) ended without deciding;
-// every workgroup of this launch adds that launch's partial sums (prev) and takes its decision, and only if none of
-// those step lengths was acceptable goes on with its own.  NPREV == 0 with defer != 0: this launch leaves its decision
-// to the next one (no closing arrival).
-template <int NT, int NTRY, int GROUP, int NPREV>
-__global__ __launch_bounds__(NT, NT == 1024 ? (GROUP <= 2 ? 8 : 4) : 1) void k_ot_ls_entropy(Dims dm, Opts op, int loss_parts, int first, int last_resort,
-                                                          int defer, const double* __restrict__ losspart,
-                                                          const double* __restrict__ x, const double* __restrict__ p1,
-                                                          const double* __restrict__ p2, Scal* __restrict__ scal,
-                                                          const double* __restrict__ prev, double* __restrict__ lspart) {
-    static_assert(NTRY % GROUP == 0, "whole groups");
-    constexpr int NW = NT / 64;
-    __shared__ double red[(NW + 1) * (GROUP > NPREV ? GROUP : NPREV)];
-    __shared__ int flag;
-    if (scal->status != LBFGSB_RUNNING) return;
-    if (NPREV == 0 && first > 0 && scal->ls_ok) return;   // an earlier launch of this iteration found the step
-    const int tid = threadIdx.x;
-    const double* p = scal->branch == 1 ? p1 : p2;
-    const double a0 = fmin(1.0, scal->alpha_ub);     // step lengths by repeated multiplication, the same everywhere
-    if constexpr (NPREV > 0) {
-        const double gp = scal->gp;
-        double tp[NPREV];
+// sum over this workgroup's entries of x h(a_k p / x): GROUP lengths a[0 .. GROUP), or, where BACKTRACK, a[0], a[0] backtrack, ..
+// (which are then not kept: the registers hold the sums)
+template <int NT, int GROUP, bool BACKTRACK>
+__device__ __forceinline__ void entropy_sums(int64_t n, const double* __restrict__ x, const double* __restrict__ p,
+                                             const double (&a)[BACKTRACK ? 1 : GROUP], double backtrack, double (&s)[GROUP], double* red) {
 #pragma unroll
-        for (int k = 0; k < NPREV; ++k) tp[k] = 0.0;
-        for (int b = tid; b < (int)gridDim.x; b += NT) {
+    for (int k = 0; k < GROUP; ++k) s[k] = 0.0;
+    for (int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x; e < n; e += (int64_t)gridDim.x * NT) {
+        const double xe = x[e], ratio = p[e] / xe;
+        double ak = a[0];
 #pragma unroll
-            for (int k = 0; k < NPREV; ++k) tp[k] += prev[(int64_t)b * NPREV + k];
-        }
-        const double tt = sum_all<NT>(losspart, loss_parts, red);
-        block_sum<NPREV, NW>(tp, red);
-        double a_prev = a0;
-        for (int k = 0; k < first - NPREV; ++k) a_prev *= op.backtrack;
-        int found;
-        double a_acc, a_last;
-        entropy_decide<NPREV>(tp, first - NPREV, a_prev, gp, tt, dm.lambda, op, found, a_acc, a_last);
-        if (found >= 0) {
-            if (blockIdx.x == 0 && tid == 0) {
-                scal->ls_ok = 1;
-                scal->backtracks = found;
-                scal->fevals += found + 1;
-                scal->alpha = a_acc;
+        for (int k = 0; k < GROUP; ++k) {
+            s[k] = fma(xe, entropy_h((BACKTRACK ? ak : a[BACKTRACK ? 0 : k]) * ratio), s[k]);
+            if constexpr (BACKTRACK) {
+                ak *= backtrack;
+                asm volatile("" : "+v"(ak));
             }
-            return;
+            // (wide workgroups: one logarithm at a time)
+            if constexpr (NT > kBlock) __builtin_amdgcn_sched_barrier(0);
         }
-        __syncthreads();   // (red is used again below)
     }
-    auto group_sum = [&](double (&v)[GROUP]) {
-        if constexpr (NW > kWaves) block_sum_by_thread<GROUP, NW>(v, red);
-        else block_sum<GROUP, NW>(v, red);
-    };
-    double a_group = a0;
-    for (int k = 0; k < first; ++k) a_group *= op.backtrack;
-    const double a_first = a_group;
-#pragma unroll 1
-    for (int k0 = 0; k0 < NTRY; k0 += GROUP) {
-        double s[GROUP], a = a_group;
+    if constexpr (NT > kBlock) block_sum_by_thread<GROUP, NT / 64>(s, red);
+    else block_sum<GROUP, NT / 64>(s, red);
+}
+
+// a_0 in a launch of its own
+template <int NT>
+__global__ __launch_bounds__(NT) void k_ot_ls_first(int64_t n, const double* __restrict__ x, const double* __restrict__ p1,
+                                                    const double* __restrict__ p2, const Scal* __restrict__ scal,
+                                                    double* __restrict__ first) {
+    __shared__ double red[NT / 64 * 2];
+    if (scal->status != LBFGSB_RUNNING) return;
+    const double a[1] = {fmin(1.0, scal->alpha_ub)};
+    double s[1];
+    entropy_sums<NT, 1, false>(n, x, scal->branch == 1 ? p1 : p2, a, 1.0, s, red);
+    if (threadIdx.x == 0) first[blockIdx.x] = s[0];
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT, NT > kBlock ? 4 : 1) void k_ot_ls_coarse(Dims dm, Opts op, int loss_parts, const double* __restrict__ losspart,
+                                                     int first_parts, const double* __restrict__ first, const double* __restrict__ x,
+                                                     const double* __restrict__ p1, const double* __restrict__ p2,
+                                                     Scal* __restrict__ scal, double* __restrict__ coarse) {
+    __shared__ double red[(NT / 64 + 1) * kLsCoarseCount];
+    if (scal->status != LBFGSB_RUNNING) return;
+    const double a0 = fmin(1.0, scal->alpha_ub), gp = scal->gp;
+    const double* p = scal->branch == 1 ? p1 : p2;
+    const double tt = sum_all<NT>(losspart, loss_parts, red);
+    const double s0 = sum_all<NT>(first, first_parts, red);
+    const bool ok = entropy_accepts(s0, a0, gp, tt, dm.lambda, op);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        scal->ls_ok = ok;
+        if (ok) {
+            scal->backtracks = 0;
+            scal->fevals += 1;
+            scal->alpha = a0;
+        }
+    }
+    if (ok) return;
+    double a[kLsCoarseCount], s[kLsCoarseCount];
 #pragma unroll
-        for (int k = 0; k < GROUP; ++k) s[k] = 0.0;
-        for (int64_t e = (int64_t)blockIdx.x * NT + tid; e < dm.n; e += (int64_t)gridDim.x * NT) {
-            const double xe = x[e], ratio = p[e] / xe;
-            a = a_group;
+    for (int k = 0; k < kLsCoarseCount; ++k) a[k] = step_length(a0, kLsCoarse[k], op.backtrack);
+    __syncthreads();   // (red is used again)
+    entropy_sums<NT, kLsCoarseCount, false>(dm.n, x, p, a, op.backtrack, s, red);
+    if (threadIdx.x == 0) {
 #pragma unroll
-            for (int k = 0; k < GROUP; ++k) {
-                s[k] = fma(xe, entropy_h(a * ratio), s[k]);
-                a *= op.backtrack;
-                // wide workgroups: one logarithm at a time, and the lengths not kept either: the registers hold the sums
-                if constexpr (NW > kWaves) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    if constexpr (GROUP > kLsBatch) asm volatile("" : "+v"(a));
+        for (int k = 0; k < kLsCoarseCount; ++k) coarse[(int64_t)blockIdx.x * kLsCoarseCount + k] = s[k];
+    }
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT, NT > kBlock ? 4 : 1) void k_ot_ls_fine(Dims dm, Opts op, int loss_parts, const double* __restrict__ losspart,
+                                                   const double* __restrict__ x, const double* __restrict__ p1,
+                                                   const double* __restrict__ p2, Scal* __restrict__ scal,
+                                                   const double* __restrict__ coarse, double* __restrict__ fine) {
+    __shared__ double red[(NT / 64 + 1) * kLsFine];
+    __shared__ int flag;
+    if (scal->status != LBFGSB_RUNNING || scal->ls_ok) return;
+    const int tid = threadIdx.x;
+    const double a0 = fmin(1.0, scal->alpha_ub), gp = scal->gp;
+    const double* p = scal->branch == 1 ? p1 : p2;
+    double tc[kLsCoarseCount];
+#pragma unroll
+    for (int k = 0; k < kLsCoarseCount; ++k) tc[k] = 0.0;
+    for (int b = tid; b < (int)gridDim.x; b += NT) {
+#pragma unroll
+        for (int k = 0; k < kLsCoarseCount; ++k) tc[k] += coarse[(int64_t)b * kLsCoarseCount + k];
+    }
+    const double tt = sum_all<NT>(losspart, loss_parts, red);
+    if constexpr (NT > kBlock) block_sum_by_thread<kLsCoarseCount, NT / 64>(tc, red);
+    else block_sum<kLsCoarseCount, NT / 64>(tc, red);
+    // (every workgroup the same bits from here to the sums)
+    const int most = op.max_backtracks;
+    int lo = 1, hi = most < kLsAllMax ? most : kLsAllMax, stop = -1;   // stop: a coarse length known to be acceptable
+    if (tt >= 0.0) {
+        hi = most < kLsLast ? most : kLsLast;
+#pragma unroll
+        for (int k = 0; k < kLsCoarseCount; ++k) {
+            if (stop < 0 && kLsCoarse[k] <= most) {
+                if (entropy_accepts(tc[k], step_length(a0, kLsCoarse[k], op.backtrack), gp, tt, dm.lambda, op)) {
+                    stop = kLsCoarse[k];
+                    hi = stop - 1;
+                } else {
+                    lo = kLsCoarse[k] + 1;
                 }
             }
         }
-        for (int k = 0; k < GROUP; ++k) a_group *= op.backtrack;
-        group_sum(s);
-        if (tid == 0) {
-#pragma unroll
-            for (int k = 0; k < GROUP; ++k) publish(lspart + (int64_t)blockIdx.x * NTRY + k0 + k, s[k]);
-        }
     }
-    if (NPREV == 0 && defer) return;
-    if (!arrive_is_last(&scal->counters[kCntLs], &flag)) return;
-    const double gp = scal->gp;
-    const double tt = sum_all<NT>(losspart, loss_parts, red);
-    int found = -1;
-    double a_acc = 0.0, av = a_first;
+    int found = stop;
+    if (lo <= hi) {
+        const double a_lo = step_length(a0, lo, op.backtrack);
+        double a_group = a_lo;
 #pragma unroll 1
-    for (int k0 = 0; k0 < NTRY && found < 0; k0 += GROUP) {
-        double tot[GROUP];
+        for (int k0 = lo; k0 <= hi; k0 += kLsFine) {
+            const double a[1] = {a_group};
+            double s[kLsFine];
+            __syncthreads();
+            entropy_sums<NT, kLsFine, true>(dm.n, x, p, a, op.backtrack, s, red);
+            a_group = step_length(a_group, kLsFine, op.backtrack);
+            if (tid == 0) {
 #pragma unroll
-        for (int k = 0; k < GROUP; ++k) tot[k] = 0.0;
-        for (int b = tid; b < (int)gridDim.x; b += NT) {
-#pragma unroll
-            for (int k = 0; k < GROUP; ++k) tot[k] += observe(lspart + (int64_t)b * NTRY + k0 + k);
+                for (int k = 0; k < kLsFine; ++k)
+                    if (k0 + k <= hi) publish(fine + (int64_t)blockIdx.x * kLsAllMax + (k0 - lo) + k, s[k]);
+            }
         }
-        group_sum(tot);
-        if (k0 > 0) av *= op.backtrack;
-        const double a_from = av;
-        entropy_decide<GROUP>(tot, first + k0, a_from, gp, tt, dm.lambda, op, found, a_acc, av);
+        if (!arrive_is_last(&scal->counters[kCntLs], &flag)) return;
+        double a = a_lo;
+#pragma unroll 1
+        for (int k = lo; k <= hi; ++k) {
+            double t[1] = {0.0};
+            for (int b = tid; b < (int)gridDim.x; b += NT) t[0] += observe(fine + (int64_t)b * kLsAllMax + k - lo);
+            block_sum<1, NT / 64>(t, red);
+            if (entropy_accepts(t[0], a, gp, tt, dm.lambda, op)) { found = k; break; }
+            a *= op.backtrack;
+        }
+    } else if (blockIdx.x != 0) {
+        return;
     }
-    // rare: continue one step length at a time (every thread holds the same totals: uniform control flow)
-    for (int k = first + NTRY; last_resort && found < 0 && k <= op.max_backtracks; ++k) {
-        av *= op.backtrack;
+    // rare: one step length after the other, one workgroup alone (every thread holds the same totals: uniform control flow)
+    for (int k = hi + 1; found < 0 && k <= most; ++k) {
+        const double a = step_length(a0, k, op.backtrack);
         double sv[1] = {0.0};
-        for (int64_t e = tid; e < dm.n; e += NT) {
-            const double xe = x[e];
-            sv[0] = fma(xe, entropy_h(av * p[e] / xe), sv[0]);
-        }
-        block_sum<1, NW>(sv, red);
-        const double df = av * (gp + 0.5 * av * tt) + dm.lambda * sv[0];
-        if (isfinite(df) && df <= op.c1 * av * gp) { found = k; a_acc = av; }
+        for (int64_t e = tid; e < dm.n; e += NT) sv[0] = fma(x[e], entropy_h(a * (p[e] / x[e])), sv[0]);
+        block_sum<1, NT / 64>(sv, red);
+        if (entropy_accepts(sv[0], a, gp, tt, dm.lambda, op)) found = k;
     }
     if (tid == 0) {
+        // (the other workgroups have arrived, or decide the same for themselves)
         scal->ls_ok = found >= 0;
-        if (found >= 0 || last_resort) {
-            scal->backtracks = found >= 0 ? found : op.max_backtracks + 1;
-            scal->fevals += found >= 0 ? found + 1 : op.max_backtracks + 1;
-        }
-        if (found >= 0) scal->alpha = a_acc;
+        scal->backtracks = found >= 0 ? found : most + 1;
+        scal->fevals += found >= 0 ? found + 1 : most + 1;
+        if (found >= 0) scal->alpha = step_length(a0, found, op.backtrack);
     }
 }
 
@@ -608,7 +667,8 @@ void launch_sums_t(const Dims& dm, const Geometry& ge, const Buffers& bf, const 
                    hipStream_t st, int dir_blocks, double eps, Scal* scal_next) {
     hipLaunchKernelGGL(k_ot_sums<RPW>, dim3(ge.ot_row_blocks), dim3(kBlock), 0, st, dm, a, eval, check_status,
                        (const double*)bf.x, (const double*)bf.p1, (const double*)bf.p2, bf.scal, eval ? bf.row : bf.t,
-                       bf.wpart, bf.losspart, (const double*)bf.redpart, eval ? 0 : dir_blocks, eps, scal_next);
+                       bf.wpart, bf.losspart, (const double*)bf.redpart, eval ? 0 : dir_blocks, eps, scal_next,
+                       !eval && ot_sums_first_length(dm, ge) ? bf.psi : nullptr);
 }
 
 }  // namespace
@@ -666,22 +726,21 @@ void launch_ot_update_gauss(const Dims& dm, const Opts& op, const Geometry& ge, 
 
 template <int NT>
 static void launch_search_t(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, hipStream_t st) {
-    // three launches, each with a region of lspart of its own: the first (two step lengths) only leaves its partial
-    // sums, the second takes the first's decision before anything else
-    double* part0 = bf.lspart;
-    double* part1 = part0 + (size_t)ge.ls_blocks * 2;
-    double* part2 = part1 + (size_t)ge.ls_blocks * kLsBatch;
-    static_assert(2 + kLsBatch + kLsTail <= 64, "lspart holds 64 step lengths per workgroup");
-    hipLaunchKernelGGL((k_ot_ls_entropy<NT, 2, 2, 0>), dim3(ge.ls_blocks), dim3(NT), 0, st, dm, op,
-                       ge.ot_row_blocks + ge.ot_col_blocks, 0, 0, 1, (const double*)bf.losspart, (const double*)bf.x,
-                       (const double*)bf.p1, (const double*)bf.p2, bf.scal, (const double*)nullptr, part0);
-    hipLaunchKernelGGL((k_ot_ls_entropy<NT, kLsBatch, kLsBatch, 2>), dim3(ge.ls_blocks), dim3(NT), 0, st, dm, op,
-                       ge.ot_row_blocks + ge.ot_col_blocks, 2, 0, 0, (const double*)bf.losspart, (const double*)bf.x,
-                       (const double*)bf.p1, (const double*)bf.p2, bf.scal, (const double*)part0, part1);
-    hipLaunchKernelGGL((k_ot_ls_entropy<NT, kLsTail, ls_group(NT), 0>), dim3(ge.ls_blocks), dim3(NT), 0, st, dm, op,
-                       ge.ot_row_blocks + ge.ot_col_blocks, 2 + kLsBatch, 1, 0, (const double*)bf.losspart,
-                       (const double*)bf.x, (const double*)bf.p1, (const double*)bf.p2, bf.scal, (const double*)nullptr,
-                       part2);
+    // (a region of lspart for each launch)
+    double* coarse = bf.lspart;
+    double* fine = coarse + (size_t)ge.ls_blocks * kLsCoarseCount;
+    double* first = fine + (size_t)ge.ls_blocks * kLsAllMax;
+    static_assert(kLsCoarseCount + kLsAllMax + 1 <= 64, "lspart holds 64 sums per workgroup");
+    const int loss_parts = ge.ot_row_blocks + ge.ot_col_blocks;
+    const bool own = !ot_sums_first_length(dm, ge);
+    if (own)
+        hipLaunchKernelGGL((k_ot_ls_first<NT>), dim3(ge.ls_blocks), dim3(NT), 0, st, dm.n, (const double*)bf.x, (const double*)bf.p1,
+                           (const double*)bf.p2, (const Scal*)bf.scal, first);
+    hipLaunchKernelGGL((k_ot_ls_coarse<NT>), dim3(ge.ls_blocks), dim3(NT), 0, st, dm, op, loss_parts, (const double*)bf.losspart,
+                       own ? ge.ls_blocks : ge.ot_row_blocks, own ? (const double*)first : (const double*)bf.psi, (const double*)bf.x,
+                       (const double*)bf.p1, (const double*)bf.p2, bf.scal, coarse);
+    hipLaunchKernelGGL((k_ot_ls_fine<NT>), dim3(ge.ls_blocks), dim3(NT), 0, st, dm, op, loss_parts, (const double*)bf.losspart,
+                       (const double*)bf.x, (const double*)bf.p1, (const double*)bf.p2, bf.scal, (const double*)coarse, fine);
 }
 void launch_ot_step_entropy(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const OtArgs& a,
                             hipStream_t st) {

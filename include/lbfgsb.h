@@ -328,7 +328,7 @@ int lbfgsb_auglag_create_marginals(lbfgsb_auglag** out, int m, const double* l, 
                                    const lbfgsb_options* opt_host, const lbfgsb_auglag_options* al_opt_host,
                                    void* workspace, size_t workspace_bytes, void* hip_stream);
 /* Runs Algorithm 4 from x0 (device, n entries, feasible for the box) with lambda = 0, rho = rho0.  The host
- * reads two scalars per outer iteration; everything else stays on the device.  Synchronises. */
+ * follows reports and enqueues; every decision is taken on the device.  Synchronises. */
 int lbfgsb_auglag_solve(lbfgsb_auglag* al, const double* x0, lbfgsb_auglag_info* info_host);
 int lbfgsb_auglag_get_x(lbfgsb_auglag* al, double* x_out);            /* device, n entries */
 int lbfgsb_auglag_get_lambda(lbfgsb_auglag* al, double* lambda_out);  /* device, n_eq entries */

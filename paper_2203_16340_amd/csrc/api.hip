@@ -74,12 +74,6 @@ struct lbfgsb_solver {
     int short_steps_unseen;
     bool short_ok;           // the short sequence is available (the pass has the LDS for its per-row numbers)
     bool commit_needed;      // resident solver: a kernel of the multi-kernel path may have left an update pending
-    // Called by lbfgsb_solve after it has enqueued the re-evaluation that confirms convergence and before it waits for
-    // the result: work that is only wanted if convergence is confirmed can ride on the same wait (the augmented
-    // Lagrangian's multiplier update, whose kernel looks at the status word itself).
-    void (*after_retest)(void*) = nullptr;
-    void* after_retest_ctx = nullptr;
-    bool last_read_was_retest = false;   // the scalar block was last read behind such a call
     // lbfgsb_solve: steps enqueued since it began, redone ones included (Opts::seq), and the next one to report
     unsigned steps_enqueued = 0, note_at = 0;
     int steps_since_refresh;
@@ -679,22 +673,95 @@ int init_workspace(lbfgsb_solver* s, const double* l, const double* u, void* wor
     return LBFGSB_OK;
 }
 
+// Free set and stopping test at x, whose gradient has just been evaluated from scratch.
+void enqueue_retest(lbfgsb_solver* s) {
+    Opts quiet = s->op;                // (not one of the steps the host is following)
+    quiet.progress = nullptr;
+    launch_gram(s->dm, quiet, s->ge, s->bf, 0, 1, s->stream);
+}
+
 // The stopping quantity was computed from a gradient carried by recurrence: residual and gradient are recomputed from x
 // and the test is made again before convergence is declared (the status is then in the host copy).
 hipError_t confirm_convergence(lbfgsb_solver* s) {
     launch_reopen(s->dm, s->bf, s->stream);
     enqueue_eval(s, 0, true);          // (nothing is pending)
     s->steps_since_refresh = 0;
-    Opts quiet = s->op;                // (not one of the steps the host is following)
-    quiet.progress = nullptr;
-    launch_gram(s->dm, quiet, s->ge, s->bf, 0, 1, s->stream);
-    if (s->after_retest) s->after_retest(s->after_retest_ctx);
-    const hipError_t e = read_scal(s);
-    s->last_read_was_retest = s->after_retest != nullptr;
-    return e;
+    enqueue_retest(s);
+    return read_scal(s);
 }
 
 constexpr int kPollMax = 64;   // steps between two looks at the device status, at most
+
+// Where the host copy is pinned, the kernel that takes an iteration's stopping decision reports it there, and the
+// host follows without stopping the device: when the outcome of a reporting step is known -- before that step's pass
+// over A has begun -- it enqueues the steps up to the next one that reports and one or two behind it.  The first four
+// steps report, then every fourth, in long runs every eighth (a report costs 4-6 us; a run that ends reports at once).
+// A run that is over in k steps has enqueued 1 (k < 4) to 5 in vain, ~8 us each (none when the iteration limit ends it:
+// no step is enqueued behind the first that can find the limit reached before that one has reported).  Waiting for the
+// device every eight steps instead left it idle for ~25 us each time, and 0 to 7 steps in vain.
+struct Follower {
+    lbfgsb_solver* s;
+    unsigned origin = 0;       // steps enqueued when the run began: the reporting ones are counted from there
+    unsigned known = 0;        // reports of steps up to this one are not this run's, or have been acted upon
+    unsigned reporting = 1;    // the step whose outcome is waited for next
+    unsigned limit = 1;        // steps after which the iteration limit can have been reached
+    long long steps = 0, cap;
+    explicit Follower(lbfgsb_solver* solver) : s(solver), cap(2ll * solver->options.max_iter + 64) {   // (accepted iterations + memory-reset retries)
+        *(volatile unsigned long long*)s->h_progress = 0;
+        s->steps_enqueued = 0;
+        s->op.progress = s->h_progress;
+    }
+    ~Follower() { s->op.progress = nullptr; s->note_at = 0; }
+
+    // a run begins: iters iterations of max_iter are behind
+    void begin(long long iters) {
+        const long long left = s->options.max_iter - iters + 1;
+        limit = left < 1 ? 1u : (left > 0x7fffffff ? 0x7fffffffu : (unsigned)left);
+        origin = s->steps_enqueued;
+        steps = 0;
+        resume();
+    }
+    // on with it from here
+    void resume() {
+        known = s->steps_enqueued;
+        s->note_at = reporting = known + 1;
+    }
+    unsigned next_report(unsigned step) const {
+        const unsigned k = step - origin, n = k + (k < 4 ? 1 : (k < 32 ? 4 : 8));
+        return origin + (k < limit && n > limit ? limit : n);
+    }
+    // Enqueues steps until a report says that the run is over: *st is the status then, RUNNING when `cap` steps have not
+    // sufficed, -1 when the stream has run dry or failed (the scalar block says what there is to know).
+    int until_over(int* st) {
+        volatile unsigned long long* seen = s->h_progress;
+        for (;;) {
+            const unsigned rel = reporting - origin;
+            unsigned upto = rel + (rel < 4 ? 1 : 2);
+            if (rel <= limit && upto > limit) upto = limit;
+            while (s->steps_enqueued - origin < upto && steps < cap) {
+                enqueue_step(s);
+                ++steps;
+                if (s->steps_enqueued == s->note_at) s->note_at = next_report(s->note_at);
+            }
+            HIP_TRY(hipGetLastError());
+            for (unsigned spins = 1;; ++spins) {
+                const unsigned long long p = *seen;
+                const unsigned step = (unsigned)(p >> 32);
+                *st = (int)(unsigned)p;
+                if (step > known && (step >= reporting || *st != LBFGSB_RUNNING)) break;
+                // (now and then: has the stream run dry, or failed?)
+                __builtin_ia32_pause();
+                if (spins % 64 == 0) sched_yield();   // (to other threads that want this core)
+                if (spins % 1024 == 0) {
+                    if (hipStreamQuery(s->stream) != hipErrorNotReady) { *st = -1; return LBFGSB_OK; }
+                    (void)hipGetLastError();   // (a stream that is busy is no error)
+                }
+            }
+            if (*st != LBFGSB_RUNNING || steps >= cap) return LBFGSB_OK;
+            reporting = next_report(reporting);
+        }
+    }
+};
 
 // The stopping logic of lbfgsb_solve, for a solver whose arguments have been checked.
 int solve_impl(lbfgsb_solver* s, lbfgsb_info* info) {
@@ -717,83 +784,35 @@ int solve_impl(lbfgsb_solver* s, lbfgsb_info* info) {
         if (info) fill_info(*s->h_scal, info);
         return LBFGSB_OK;
     }
-    long long steps = 0;
-    s->last_read_was_retest = false;
-    // Where the host copy is pinned, the kernel that takes an iteration's stopping decision reports it there, and the
-    // host follows without stopping the device: when the outcome of a reporting step is known -- before that step's pass
-    // over A has begun -- it enqueues the steps up to the next one that reports and one or two behind it.  The first four
-    // steps report, then every fourth, in long runs every eighth (a report costs 4-6 us; a run that ends reports at once).
-    // A run that is over in k steps has enqueued 1 (k < 4) to 5 in vain, ~8 us each (none when the iteration limit ends it:
-    // no step is enqueued behind the first that can find the limit reached before that one has reported).  Waiting for the
-    // device every eight steps instead left it idle for ~25 us each time, and 0 to 7 steps in vain.
     if (s->h_progress) {
-        struct Following {
-            lbfgsb_solver* s;
-            ~Following() { s->op.progress = nullptr; s->note_at = 0; }
-        } following{s};
-        volatile unsigned long long* seen = s->h_progress;
-        *seen = 0;
-        s->steps_enqueued = 0;
-        s->op.progress = s->h_progress;
-        s->note_at = 1;
-        unsigned reporting = 1;                              // the step whose outcome is waited for next
-        const long long left = s->options.max_iter - s->h_scal->iters + 1;   // (from what the host has last seen)
-        const unsigned limit = left < 1 ? 1u : (left > 0x7fffffff ? 0x7fffffffu : (unsigned)left);
-        auto next_report = [limit](unsigned k) {
-            const unsigned n = k + (k < 4 ? 1 : (k < 32 ? 4 : 8));
-            return k < limit && n > limit ? limit : n;
-        };
+        Follower run(s);
+        run.begin(s->h_scal->iters);   // (from what the host has last seen)
         for (;;) {
-            unsigned upto = reporting + (reporting < 4 ? 1 : 2);
-            if (reporting <= limit && upto > limit) upto = limit;
-            while (s->steps_enqueued < upto && steps < cap) {
-                enqueue_step(s);
-                ++steps;
-                if (s->steps_enqueued == s->note_at) s->note_at = next_report(s->note_at);
-            }
-            HIP_TRY(hipGetLastError());
             int st = LBFGSB_RUNNING;
-            unsigned long long p = 0;
-            for (unsigned spins = 1;; ++spins) {
-                p = *seen;
-                st = (int)(unsigned)p;
-                if ((unsigned)(p >> 32) >= reporting || st != LBFGSB_RUNNING) break;
-                // (now and then: has the stream run dry, or failed?  then the read below says what there is to know)
-                __builtin_ia32_pause();
-                if (spins % 64 == 0) sched_yield();   // (to other threads that want this core)
-                if (spins % 1024 == 0) {
-                    if (hipStreamQuery(s->stream) != hipErrorNotReady) { st = -1; break; }
-                    (void)hipGetLastError();   // (a stream that is busy is no error)
-                }
-            }
-            if (st == LBFGSB_RUNNING && steps < cap) {
-                reporting = next_report(reporting);
-                continue;
-            }
+            const int rc = run.until_over(&st);
+            if (rc) return rc;
             // (The first step is known to have gone on, so at least one iteration is behind: see the condition below.  The
             // number in the report does not say so: a step behind the one that ended the run reports the end as well, and
             // which of the two is seen depends on the host's pace.)
-            if (st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0 && reporting >= 2) {
+            if (st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0 && run.reporting - run.origin >= 2) {
                 HIP_TRY(confirm_convergence(s));
                 st = s->h_scal->status;
             } else {
                 HIP_TRY(read_scal(s));
-                s->last_read_was_retest = false;
                 st = s->h_scal->status;
                 if (st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0 && s->h_scal->iters > 0) {
                     HIP_TRY(confirm_convergence(s));
                     st = s->h_scal->status;
                 }
             }
-            if (st != LBFGSB_RUNNING || steps >= cap) break;
-            // on with it (a parked step has been finished, or convergence was not confirmed): the device is idle
-            *seen = 0;
-            s->note_at = reporting = s->steps_enqueued + 1;
+            if (st != LBFGSB_RUNNING || run.steps >= run.cap) break;
+            run.resume();   // (a parked step has been finished, or convergence was not confirmed: the device is idle)
         }
         HIP_TRY(hipGetLastError());
         if (info) fill_info(*s->h_scal, info);
         return LBFGSB_OK;
     }
+    long long steps = 0;
     // A poll leaves the device idle for about 30 us (commit, copy of the scalar block, the host's wake-up and the next
     // launches), a step enqueued after the solver has stopped costs about 6.  Long runs are therefore polled less
     // often: the interval doubles whenever eight intervals' worth of steps have gone by, up to 64.
@@ -803,7 +822,6 @@ int solve_impl(lbfgsb_solver* s, lbfgsb_info* info) {
         steps += batch;
         if (batch < kPollMax && steps >= 8ll * batch) batch = 2 * batch > kPollMax ? kPollMax : 2 * batch;
         HIP_TRY(read_scal(s));
-        s->last_read_was_retest = false;
         int st = s->h_scal->status;
         if (st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0 && s->h_scal->iters > 0) {
             HIP_TRY(confirm_convergence(s));
@@ -1220,6 +1238,17 @@ int lbfgsb_dbg_project_direction(lbfgsb_solver* s, const double* x, const double
 
 }  // extern "C"
 
+// The algorithm's own state, on the device (a copy goes to the host when a run is over).
+struct AlState {
+    double rho, violation;     // violation: at the last outer iterate, to begin with at x0
+    double L, f, pg2;
+    long long inner_iters;
+    int outer, status;
+    int inner_status;          // how the inner solve that is being wound up ended
+    int turned;                // the last k_al_turn has set up another inner solve
+    int done, nonfinite;
+};
+
 struct lbfgsb_auglag {
     lbfgsb_solver* inner;
     lbfgsb_auglag_options ao;
@@ -1230,12 +1259,15 @@ struct lbfgsb_auglag {
     double *beta_c, *omega_c;
     const double* res_c;     // where the inner solver leaves a_r . x - beta_r of the constraint rows after an evaluation
     double* lambda;          // multipliers
-    double* h_red;           // pinned, written by k_al_update: [0] violation, [1] penalty term
-    double rho;
+    AlState* state;
+    AlState* h_state;        // pinned
     hipStream_t stream;
-    // stacked variant only: the constraint rows inside the caller's matrix, and n_eq doubles of scratch (the
-    // change of weight*residual per constraint row), for re-evaluating f and g after the targets changed
+    enum { kStacked, kRows, kMarginals } variant;
+    // the constraint rows (c_ld entries from one to the next, of type c_dtype; not the marginals, which have none), and n_eq
+    // doubles of scratch (the change of weight * residual per constraint row)
     const void* c_rows = nullptr;
+    int64_t c_ld = 0;
+    int c_dtype = LBFGSB_F64;
     double* coef = nullptr;
 };
 
@@ -1258,124 +1290,199 @@ __global__ void k_al_prepare(int64_t n_eq, double rho, const double* __restrict_
     }
 }
 
-// Stacked variant, between two inner solves: only the targets beta and the weights omega of the constraint rows
-// change, so f and g at the unchanged x follow from the fresh residuals without another pass over the whole matrix:
-// with c_r . x = res_r + beta_r,  res_r' = c_r . x - beta_r',  f' = f + 0.5 sum (omega' res'^2 - omega res^2),
-// g' = g + C^T (omega' res' - omega res).  First kernel (one workgroup): new targets, weights and residuals, the
-// coefficients omega' res' - omega res, and f; second kernel: the n_eq x n product into g.
-__global__ __launch_bounds__(kBlock) void k_al_shift_rows(int64_t n_eq, double rho, const double* __restrict__ d,
-                                                          const double* __restrict__ lambda, double* __restrict__ beta,
-                                                          double* __restrict__ omega, double* __restrict__ res,
-                                                          double* __restrict__ coef, Scal* __restrict__ scal) {
-    __shared__ double lds[kWaves];
-    double df[1] = {0.0};
-    for (int64_t r = threadIdx.x; r < n_eq; r += kBlock) {
-        const double res_old = res[r], w_old = omega[r];
-        const double cx = res_old + beta[r];
-        const double b_new = d[r] - lambda[r] / rho;
-        const double res_new = cx - b_new;
-        coef[r] = rho * res_new - w_old * res_old;
-        df[0] += 0.5 * (rho * res_new * res_new - w_old * res_old * res_old);
-        beta[r] = b_new;
-        omega[r] = rho;
-        res[r] = res_new;
-    }
-    block_sum<1, kWaves>(df, lds);
-    if (threadIdx.x == 0) scal->f += df[0];
+// ||h||_inf over a workgroup of NT threads, from each thread's share; every thread gets it.  lds: NT/64 doubles.
+template <int NT>
+__device__ __forceinline__ double block_max(double v, double* lds) {
+    v = wave_max(v);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = lds[0];
+    for (int w = 1; w < NT / 64; ++w) v = fmax(v, lds[w]);
+    return v;
 }
 
+// Algorithm 4 begins: lambda^0 = 0, and residuals evaluated at x^0 with the targets d.
+constexpr int kTurnThreads = 1024;
+__global__ __launch_bounds__(kTurnThreads) void k_al_begin(int64_t n_eq, double rho0, const double* __restrict__ res, AlState* __restrict__ state) {
+    __shared__ double lds[kTurnThreads / 64];
+    double viol = 0.0;
+    for (int64_t r = threadIdx.x; r < n_eq; r += kTurnThreads) viol = fmax(viol, fabs(res[r]));
+    viol = block_max<kTurnThreads>(viol, lds);
+    if (threadIdx.x == 0) {
+        *state = AlState{};
+        state->rho = rho0;
+        state->violation = viol;
+        state->status = LBFGSB_MAX_ITER;
+    }
+}
+
+// An inner solve has ended: any pending update is applied, and the solver is open for an evaluation at its last iterate.
+// (Once the run is over nothing changes any more, should the host have seen the last steps' report before it saw that.)
+__global__ void k_al_reopen(Scal* scal, int m, AlState* state) {
+    if (threadIdx.x != 0 || state->done) return;
+    apply_pending(scal, m);
+    state->inner_status = scal->status;
+    scal->status = LBFGSB_RUNNING;
+}
+
+// Between two inner solves (one workgroup): multipliers, penalty parameter, the algorithm's own stopping test, and the next
+// subproblem.  The host enqueues it behind the evaluation at the inner solve's last iterate and goes on with the next inner solve's
+// steps without waiting for it: it used to fetch two scalars per outer iteration, ~60 us in which the device was idle.
+//
+// res: residuals a_r . x - beta_r of the constraint rows at x.  h_r = res_r - lambda_r/rho; lambda += rho h; rho doubles when
+// ||h||_inf has not been halved; over when it is at most ctol and the inner solve has converged.
+// Else only the targets beta and the weights omega change, so f and g at the unchanged x follow from the residuals without another
+// evaluation: with c_r . x = res_r + beta_r,  res_r' = c_r . x - beta_r',  f' = f + 0.5 sum (omega' res'^2 - omega res^2),
+// g' = g + C^T (omega' res' - omega res) -- the latter here where the rows are few and short (SHIFT; the sum constraint of a
+// simplex is one), else by a kernel of its own from coef.  The scalar block starts afresh.
+// retest: the inner solve's convergence has been tested anew on the evaluated gradient; it goes on if that was not confirmed.
+struct AlTurn {
+    int64_t n_eq, cols, ld;
+    double ctol;
+    int max_outer, retest, fevals;
+    const double* d;
+    double *lambda, *beta, *omega, *res, *coef, *total;   // total (or null): where 0.5 sum omega res^2 is kept
+    const void* Crows;
+    double* g;
+    Scal* scal;
+    lbfgsb_iter_record* hist;
+    AlState* state;
+    AlState* host;
+};
+// Beyond 16 entries per thread one workgroup has too few loads in flight, beyond 64 rows the coefficients do not lie in LDS.
+constexpr int kShiftRowsMax = 64;
+constexpr int64_t kShiftMax = 16 * kTurnThreads;
+template <typename T, bool SHIFT>
+__global__ __launch_bounds__(kTurnThreads) void k_al_turn(AlTurn a) {
+    __shared__ double lds[2 * kTurnThreads / 64];
+    __shared__ double coef_s[SHIFT ? kShiftRowsMax : 1];
+    __shared__ double rho_s;
+    __shared__ int go_s;
+    const int tid = threadIdx.x;
+    const int status = a.retest ? a.scal->status : a.state->inner_status;
+    const double rho = a.state->rho, viol_prev = a.state->violation;
+    if (a.state->done) return;
+    if (a.retest && status == LBFGSB_RUNNING) {
+        if (tid == 0) a.state->turned = 0;
+        return;
+    }
+    double viol = 0.0, s[1] = {0.0};
+    for (int64_t r = tid; r < a.n_eq; r += kTurnThreads) {
+        const double v = a.res[r], lam = a.lambda[r], h = v - lam / rho;
+        viol = fmax(viol, fabs(h));
+        s[0] = fma(v, v, s[0]);
+        a.lambda[r] = lam + rho * h;
+    }
+    viol = block_max<kTurnThreads>(viol, lds);
+    block_sum<1, kTurnThreads / 64>(s, lds);
+    if (tid == 0) {
+        AlState st = *a.state;
+        const double f = a.scal->f, rho_next = viol > 0.5 * viol_prev ? 2.0 * rho : rho;
+        st.outer += 1;
+        st.inner_iters += a.scal->iters;
+        st.pg2 = a.scal->pg2;
+        st.violation = viol;
+        st.L = f;
+        st.f = f - 0.5 * rho * s[0];
+        const bool over = viol <= a.ctol && status == LBFGSB_CONVERGED;
+        if (over) st.status = LBFGSB_CONVERGED;
+        else st.rho = rho_next;
+        st.done = over || st.outer >= a.max_outer;
+        st.turned = !st.done;
+        *a.state = st;
+        if (st.done) {
+            a.scal->status = status;
+            *a.host = st;
+        }
+        rho_s = st.rho;
+        go_s = !st.done;
+    }
+    __syncthreads();
+    if (!go_s) return;
+    const double rho_new = rho_s;
+    double t[2] = {0.0, 0.0};
+    for (int64_t r = tid; r < a.n_eq; r += kTurnThreads) {
+        const double res_old = a.res[r], w_old = a.omega[r];
+        const double cx = res_old + a.beta[r];
+        const double b_new = a.d[r] - a.lambda[r] / rho_new;
+        const double res_new = cx - b_new;
+        const double c = rho_new * res_new - w_old * res_old;
+        if (SHIFT) coef_s[r] = c;
+        else a.coef[r] = c;
+        t[0] += 0.5 * (rho_new * res_new * res_new - w_old * res_old * res_old);
+        t[1] += 0.5 * rho_new * res_new * res_new;
+        a.beta[r] = b_new;
+        a.omega[r] = rho_new;
+        a.res[r] = res_new;
+    }
+    block_sum<2, kTurnThreads / 64>(t, lds);
+    const double f_new = a.scal->f + t[0];
+    if (SHIFT) {
+        for (int64_t j = tid; j < a.cols; j += kTurnThreads) {
+            double acc = 0.0;
+            for (int r = 0; r < (int)a.n_eq; ++r) acc = fma(coef_s[r], (double)((const T*)a.Crows)[r * a.ld + j], acc);
+            a.g[j] += acc;
+        }
+    }
+    __syncthreads();   // (every thread has read f)
+    for (int k = tid; k < (int)(sizeof(Scal) / 4); k += kTurnThreads) reinterpret_cast<int*>(a.scal)[k] = 0;
+    __syncthreads();
+    if (tid == 0) {
+        a.scal->status = LBFGSB_RUNNING;
+        a.scal->alpha_ub = 1.0;
+        a.scal->hist = a.hist;
+        a.scal->f = f_new;
+        a.scal->fevals = a.fevals;
+        if (a.total) *a.total = t[1];
+        if (!isfinite(f_new)) {
+            // (refused, as a start point whose f is not finite is)
+            a.state->done = a.state->nonfinite = 1;
+            a.state->turned = 0;
+            a.scal->status = LBFGSB_LINESEARCH_FAILED;
+            *a.host = *a.state;
+        }
+    }
+}
+
+// g += C^T coef behind a turn
 template <typename T>
-__global__ void k_al_shift_g(int64_t n_eq, int64_t cols, int64_t ld, const T* __restrict__ Crows,
-                             const double* __restrict__ coef, double* __restrict__ g) {
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < cols; j += (int64_t)gridDim.x * blockDim.x) {
+__global__ __launch_bounds__(kBlock) void k_al_shift_g(int64_t n_eq, int64_t cols, int64_t ld, const T* __restrict__ Crows,
+                                                       const double* __restrict__ coef, double* __restrict__ g,
+                                                       const AlState* __restrict__ state) {
+    if (!state->turned) return;
+    for (int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x; j < cols; j += (int64_t)gridDim.x * kBlock) {
         double acc = 0.0;
         for (int64_t r = 0; r < n_eq; ++r) acc = fma(coef[r], (double)Crows[r * ld + j], acc);
         g[j] += acc;
     }
 }
-
-// Both kernels and the fresh scalar block in one workgroup and one launch, for few and short constraint rows (the sum
-// constraint of a simplex is one).  Three launches into an idle stream took about as long as the host needs to make them.
-// Where every inner solve is short that counts: 28 of them over 8000 x 2000 and one constraint row 8.72 -> 8.52 ms.  Beyond
-// 16 entries per thread one workgroup has too few loads in flight, beyond 64 rows the targets take more than one wave: then
-// the kernels above.
-constexpr int kShiftThreads = 1024;
-constexpr int kShiftRowsMax = 64;                        // (one wave's lanes)
-constexpr int64_t kShiftMax = 16 * kShiftThreads;        // matrix entries: at most 16 per thread
-template <typename T>
-__global__ __launch_bounds__(kShiftThreads) void k_al_shift(int64_t n_eq, double rho, const double* __restrict__ d,
-                                                            const double* __restrict__ lambda, double* __restrict__ beta,
-                                                            double* __restrict__ omega, double* __restrict__ res,
-                                                            Scal* __restrict__ scal, lbfgsb_iter_record* hist, int64_t cols,
-                                                            int64_t ld, const T* __restrict__ Crows, double* __restrict__ g) {
-    __shared__ double coef[kShiftRowsMax];
-    __shared__ double f;
-    const int tid = threadIdx.x;
-    if (tid < 64) {
-        double df = 0.0;
-        if (tid < n_eq) {
-            const double res_old = res[tid], w_old = omega[tid];
-            const double cx = res_old + beta[tid];
-            const double b_new = d[tid] - lambda[tid] / rho;
-            const double res_new = cx - b_new;
-            coef[tid] = rho * res_new - w_old * res_old;
-            df = 0.5 * (rho * res_new * res_new - w_old * res_old * res_old);
-            beta[tid] = b_new;
-            omega[tid] = rho;
-            res[tid] = res_new;
+// ... where the rows are the marginals of a rows x cols matrix: one row at a time, four columns' loads in flight
+__global__ __launch_bounds__(kBlock) void k_al_shift_marginals(int64_t rows, int64_t cols, const double* __restrict__ coef,
+                                                               double* __restrict__ g, const AlState* __restrict__ state) {
+    if (!state->turned) return;
+    const int64_t tiles = (cols + 4 * kBlock - 1) / (4 * kBlock);
+    for (int64_t b = blockIdx.x; b < rows * tiles; b += gridDim.x) {
+        const int64_t i = b / tiles, j0 = (b - i * tiles) * 4 * kBlock + threadIdx.x;
+        const double ci = coef[i];
+        double gv[4], cv[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t j = j0 + k * kBlock < cols ? j0 + k * kBlock : cols - 1;
+            gv[k] = g[i * cols + j];
+            cv[k] = coef[rows + j];
         }
-        df = wave_sum(df);
-        if (tid == 0) f = scal->f + df;
-    }
-    __syncthreads();
-    for (int64_t j = tid; j < cols; j += kShiftThreads) {
-        double acc = 0.0;
-        for (int r = 0; r < (int)n_eq; ++r) acc = fma(coef[r], (double)Crows[r * ld + j], acc);
-        g[j] += acc;
-    }
-    for (int k = tid; k < (int)(sizeof(Scal) / 4); k += kShiftThreads) reinterpret_cast<int*>(scal)[k] = 0;
-    __syncthreads();
-    if (tid == 0) {
-        scal->status = LBFGSB_RUNNING;
-        scal->alpha_ub = 1.0;
-        scal->hist = hist;
-        scal->f = f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (j0 + k * kBlock < cols) g[i * cols + j0 + k * kBlock] = gv[k] + (ci + cv[k]);
     }
 }
-
-// One workgroup.  res holds a_r . x - beta_r of the constraint rows, freshly evaluated at x:
-// h_r = res_r - lambda_r/rho; with update != 0 the multipliers become lambda + rho h.  red[0] = ||h||_inf,
-// red[1] = rho/2 sum (h + lambda/rho)^2 (the penalty term at the OLD multipliers); red is pinned host memory.
-// gate (or NULL): do nothing unless that scalar block says CONVERGED.
-__global__ __launch_bounds__(kBlock) void k_al_update(int64_t n_eq, double rho, int update,
-                                                      const double* __restrict__ res, double* __restrict__ lambda,
-                                                      double* __restrict__ red, const Scal* __restrict__ gate) {
-    __shared__ double lds[kWaves * 2];
-    if (gate && gate->status != LBFGSB_CONVERGED) return;
-    double viol = 0.0, pen = 0.0;
-    for (int64_t r = threadIdx.x; r < n_eq; r += kBlock) {
-        const double a = res[r];
-        const double h = a - lambda[r] / rho;
-        viol = fmax(viol, fabs(h));
-        pen = fma(a, a, pen);
-        if (update) lambda[r] += rho * h;
-    }
-    double pv[1] = {pen};
-    block_sum<1, kWaves>(pv, lds);
-    viol = wave_max(viol);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = viol;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double v = lds[0];
-        for (int w = 1; w < kWaves; ++w) v = fmax(v, lds[w]);
-        red[0] = v;
-        red[1] = 0.5 * rho * pv[0];
-    }
+__global__ void k_al_report(const AlState* state, AlState* host) {
+    if (threadIdx.x == 0) *host = *state;
 }
 
 size_t al_extra_bytes(int64_t rows, int64_t n_eq) {
-    return align_up((size_t)rows * 8) * 2 + 2 * align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8);
+    return align_up((size_t)rows * 8) * 2 + 2 * align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8) + align_up(sizeof(AlState));
 }
 
 int check_al(int64_t n, const lbfgsb_objective* o, int64_t n_eq) {
@@ -1398,20 +1505,48 @@ int check_al_rows(const lbfgsb_objective* o, int64_t n_eq, const double* C, cons
 }
 
 size_t al_rows_extra_bytes(int64_t n_eq) {
-    return 3 * align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8);
+    return 4 * align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8) + align_up(sizeof(AlState));
 }
 
-// residual (all rows) and gradient recomputed from x unless they already are
-// (called right behind lbfgsb_solve, whose last act was to read the scalar block: the host copy is current)
-hipError_t al_fresh_eval(lbfgsb_solver* s) {
+// The inner solver has ended, or `confirm`: has found the end by a gradient carried by recurrence.  Everything up to the next inner
+// solve's first step is enqueued here, nothing is waited for.
+void enqueue_turn(lbfgsb_auglag* al, bool confirm) {
+    lbfgsb_solver* s = al->inner;
+    hipLaunchKernelGGL(k_al_reopen, dim3(1), dim3(64), 0, al->stream, s->bf.scal, s->dm.m, al->state);
     if (s->steps_since_refresh > 0) {
-        const int status = s->h_scal->status;
-        launch_set_status(s->bf, LBFGSB_RUNNING, s->stream);   // the evaluation's last kernel only runs in this state
-        enqueue_eval(s, 0);
-        launch_set_status(s->bf, status, s->stream);
-        s->steps_since_refresh = 0;
+        enqueue_eval(s, 0, true);
+        if (confirm) enqueue_retest(s);
     }
-    return hipGetLastError();
+    s->steps_since_refresh = 0;
+    s->steps_since_set_x = 0;
+    const bool stacked = al->variant == lbfgsb_auglag::kStacked, marginals = al->variant == lbfgsb_auglag::kMarginals;
+    AlTurn a{};
+    a.n_eq = al->n_eq; a.cols = stacked ? s->dm.cols : s->dm.n; a.ld = al->c_ld;
+    a.ctol = al->ao.ctol; a.max_outer = al->ao.max_outer; a.retest = confirm ? 1 : 0;
+    a.fevals = stacked ? 0 : 1;        // (of a stacked subproblem's start this never counted)
+    a.d = al->d_c; a.lambda = al->lambda; a.beta = al->beta_c; a.omega = al->omega_c; a.res = (double*)al->res_c; a.coef = al->coef;
+    a.total = s->dm.n_extra > 0 ? s->bf.xres + s->dm.n_extra : nullptr;
+    a.Crows = al->c_rows; a.g = s->bf.g; a.scal = s->bf.scal; a.hist = s->bf.hist; a.state = al->state; a.host = al->h_state;
+    const bool f32 = al->c_dtype == LBFGSB_F32;
+    if (!marginals && al->n_eq <= kShiftRowsMax && al->n_eq * a.cols <= kShiftMax) {
+        hipLaunchKernelGGL((f32 ? k_al_turn<float, true> : k_al_turn<double, true>), dim3(1), dim3(kTurnThreads), 0, al->stream, a);
+        return;
+    }
+    hipLaunchKernelGGL((k_al_turn<double, false>), dim3(1), dim3(kTurnThreads), 0, al->stream, a);
+    if (marginals) {
+        const int64_t blocks = s->dm.rows * ((s->dm.cols + 4 * kBlock - 1) / (4 * kBlock));
+        hipLaunchKernelGGL(k_al_shift_marginals, dim3((unsigned)(blocks > 2048 ? 2048 : blocks)), dim3(kBlock), 0, al->stream, s->dm.rows,
+                           s->dm.cols, (const double*)al->coef, s->bf.g, (const AlState*)al->state);
+        return;
+    }
+    int64_t blocks = (a.cols + kBlock - 1) / kBlock;
+    if (blocks > 1024) blocks = 1024;
+    if (f32)
+        hipLaunchKernelGGL(k_al_shift_g<float>, dim3((unsigned)blocks), dim3(kBlock), 0, al->stream, al->n_eq, a.cols, a.ld,
+                           (const float*)al->c_rows, (const double*)al->coef, s->bf.g, (const AlState*)al->state);
+    else
+        hipLaunchKernelGGL(k_al_shift_g<double>, dim3((unsigned)blocks), dim3(kBlock), 0, al->stream, al->n_eq, a.cols, a.ld,
+                           (const double*)al->c_rows, (const double*)al->coef, s->bf.g, (const AlState*)al->state);
 }
 
 }  // namespace
@@ -1452,13 +1587,16 @@ int lbfgsb_auglag_create(lbfgsb_auglag** out, int64_t n, int m, const double* l,
     if (!al) return fail(LBFGSB_E_INVALID_ARG, "out of host memory");
     const int64_t rows_data = obj->rows - n_eq;
     al->ao = ao; al->n_eq = n_eq; al->n = n; al->d_c = obj->b + rows_data;
-    al->stream = (hipStream_t)hip_stream; al->rho = ao.rho0; al->inner = nullptr; al->h_red = nullptr;
+    al->stream = (hipStream_t)hip_stream; al->inner = nullptr; al->h_state = nullptr;
     char* w = (char*)workspace + align_up(inner_bytes);
     double* beta = (double*)w; w += align_up((size_t)obj->rows * 8);
     double* omega = (double*)w; w += align_up((size_t)obj->rows * 8);
     al->beta_c = beta + rows_data; al->omega_c = omega + rows_data;
     al->lambda = (double*)w; w += align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8);
     al->coef = (double*)w; w += align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8);
+    al->state = (AlState*)w;
+    al->variant = lbfgsb_auglag::kStacked;
+    al->c_ld = obj->ld; al->c_dtype = obj->dtype;
     al->c_rows = (const char*)obj->A + (size_t)rows_data * (size_t)obj->ld * (obj->dtype == LBFGSB_F64 ? 8 : 4);
     lbfgsb_objective inner_obj = *obj;
     inner_obj.b = beta;
@@ -1466,8 +1604,8 @@ int lbfgsb_auglag_create(lbfgsb_auglag** out, int64_t n, int m, const double* l,
     rc = lbfgsb_create(&al->inner, n, m, l, u, &inner_obj, opt, workspace, inner_bytes, hip_stream);
     if (rc) { delete al; return rc; }
     al->res_c = al->inner->bf.row + rows_data;
-    hipError_t e = hipHostMalloc((void**)&al->h_red, 64, kPinned);
-    if (e != hipSuccess) { al->h_red = nullptr; lbfgsb_auglag_destroy(al); return fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e)); }
+    hipError_t e = hipHostMalloc((void**)&al->h_state, sizeof(AlState), kPinned);
+    if (e != hipSuccess) { al->h_state = nullptr; lbfgsb_auglag_destroy(al); return fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e)); }
     int blocks = (int)((obj->rows + 255) / 256);
     if (blocks > 1024) blocks = 1024;
     hipLaunchKernelGGL(k_al_init, dim3(blocks), dim3(256), 0, al->stream, obj->rows, obj->b, beta, omega);
@@ -1515,19 +1653,23 @@ int lbfgsb_auglag_create_rows(lbfgsb_auglag** out, int64_t n, int m, const doubl
     if (!al) return fail(LBFGSB_E_INVALID_ARG, "out of host memory");
     const size_t slot = align_up((size_t)(n_eq > 0 ? n_eq : 1) * 8);
     al->ao = ao; al->n_eq = n_eq; al->n = n; al->d_c = d;
-    al->stream = (hipStream_t)hip_stream; al->rho = ao.rho0; al->inner = nullptr; al->h_red = nullptr;
+    al->stream = (hipStream_t)hip_stream; al->inner = nullptr; al->h_state = nullptr;
     char* w = (char*)workspace + align_up(inner_bytes);
     al->beta_c = (double*)w; w += slot;
     al->omega_c = (double*)w; w += slot;
-    al->lambda = (double*)w;
+    al->lambda = (double*)w; w += slot;
+    al->coef = (double*)w; w += slot;
+    al->state = (AlState*)w;
+    al->variant = lbfgsb_auglag::kRows;
+    al->c_rows = C; al->c_ld = n; al->c_dtype = LBFGSB_F64;
     inner_obj.extra_target = al->beta_c;
     inner_obj.extra_weight = al->omega_c;
     rc = lbfgsb_create(&al->inner, n, m, l, u, &inner_obj, opt, workspace, inner_bytes, hip_stream);
     if (rc) { delete al; return rc; }
     al->res_c = al->inner->bf.xres;
-    hipError_t e = hipHostMalloc((void**)&al->h_red, 64, kPinned);
-    if (e != hipSuccess) { al->h_red = nullptr; lbfgsb_auglag_destroy(al); return fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e)); }
-    launch_fill_zero(al->beta_c, 3 * slot, al->stream);
+    hipError_t e = hipHostMalloc((void**)&al->h_state, sizeof(AlState), kPinned);
+    if (e != hipSuccess) { al->h_state = nullptr; lbfgsb_auglag_destroy(al); return fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e)); }
+    launch_fill_zero(al->beta_c, 4 * slot, al->stream);
     e = hipStreamSynchronize(al->stream);
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) { lbfgsb_auglag_destroy(al); return fail(LBFGSB_E_HIP, "initialising: %s", hipGetErrorString(e)); }
@@ -1570,19 +1712,22 @@ int lbfgsb_auglag_create_marginals(lbfgsb_auglag** out, int m, const double* l, 
     if (!al) return fail(LBFGSB_E_INVALID_ARG, "out of host memory");
     const size_t slot = align_up((size_t)n_eq * 8);
     al->ao = ao; al->n_eq = n_eq; al->n = n; al->d_c = marginals;
-    al->stream = (hipStream_t)hip_stream; al->rho = ao.rho0; al->inner = nullptr; al->h_red = nullptr;
+    al->stream = (hipStream_t)hip_stream; al->inner = nullptr; al->h_state = nullptr;
     char* w = (char*)workspace + align_up(inner_bytes);
     al->beta_c = (double*)w; w += slot;
     al->omega_c = (double*)w; w += slot;
-    al->lambda = (double*)w;
+    al->lambda = (double*)w; w += slot;
+    al->coef = (double*)w; w += slot;
+    al->state = (AlState*)w;
+    al->variant = lbfgsb_auglag::kMarginals;
     inner_obj.b = al->beta_c;
     inner_obj.row_weight = al->omega_c;
     int rc = lbfgsb_create(&al->inner, n, m, l, u, &inner_obj, opt, workspace, inner_bytes, hip_stream);
     if (rc) { delete al; return rc; }
     al->res_c = al->inner->bf.row;
-    hipError_t e = hipHostMalloc((void**)&al->h_red, 64, kPinned);
-    if (e != hipSuccess) { al->h_red = nullptr; lbfgsb_auglag_destroy(al); return fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e)); }
-    launch_fill_zero(al->beta_c, 3 * slot, al->stream);
+    hipError_t e = hipHostMalloc((void**)&al->h_state, sizeof(AlState), kPinned);
+    if (e != hipSuccess) { al->h_state = nullptr; lbfgsb_auglag_destroy(al); return fail(LBFGSB_E_HIP, "hipHostMalloc: %s", hipGetErrorString(e)); }
+    launch_fill_zero(al->beta_c, 4 * slot, al->stream);
     e = hipStreamSynchronize(al->stream);
     if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) { lbfgsb_auglag_destroy(al); return fail(LBFGSB_E_HIP, "initialising: %s", hipGetErrorString(e)); }
@@ -1593,100 +1738,71 @@ int lbfgsb_auglag_create_marginals(lbfgsb_auglag** out, int m, const double* l, 
 void lbfgsb_auglag_destroy(lbfgsb_auglag* al) {
     if (!al) return;
     lbfgsb_destroy(al->inner);
-    if (al->h_red) (void)hipHostFree(al->h_red);
+    if (al->h_state) (void)hipHostFree(al->h_state);
     delete al;
 }
 
 int lbfgsb_auglag_solve(lbfgsb_auglag* al, const double* x0, lbfgsb_auglag_info* info) {
     if (!al || !x0) return fail(LBFGSB_E_INVALID_ARG, "NULL argument");
     lbfgsb_solver* s = al->inner;
-    lbfgsb_auglag_info out{};
-    out.status = LBFGSB_MAX_ITER;
     const int pb = (int)((al->n_eq + 255) / 256) > 0 ? (int)((al->n_eq + 255) / 256) : 1;
     // lambda^0 = 0, rho = rho0; the violation at x^0 is what the first iteration is compared with
     launch_fill_zero(al->lambda, align_up((size_t)(al->n_eq > 0 ? al->n_eq : 1) * 8), al->stream);
-    al->rho = al->ao.rho0;
-    hipLaunchKernelGGL(k_al_prepare, dim3(pb), dim3(256), 0, al->stream, al->n_eq, al->rho, al->d_c, al->lambda,
+    hipLaunchKernelGGL(k_al_prepare, dim3(pb), dim3(256), 0, al->stream, al->n_eq, al->ao.rho0, al->d_c, al->lambda,
                        al->beta_c, al->omega_c);
     int rc = lbfgsb_set_x(s, x0);
     if (rc) return rc;
-    // constraint violation and penalty term at the current x (and the multiplier update); wait: whether to wait
-    // here or let a following read of the scalar block do it
-    auto measure = [&](int update, bool wait) -> hipError_t {
-        hipLaunchKernelGGL(k_al_update, dim3(1), dim3(kBlock), 0, al->stream, al->n_eq, al->rho, update, al->res_c,
-                           al->lambda, al->h_red, (const Scal*)nullptr);
-        return wait ? hipStreamSynchronize(al->stream) : hipSuccess;
-    };
-    // The multiplier update of an inner solve whose convergence is being confirmed rides on that confirmation's wait:
-    // residuals are fresh behind the re-evaluation, and the kernel does nothing unless the status says CONVERGED.
-    s->after_retest = [](void* ctx) {
-        lbfgsb_auglag* a = (lbfgsb_auglag*)ctx;
-        hipLaunchKernelGGL(k_al_update, dim3(1), dim3(kBlock), 0, a->stream, a->n_eq, a->rho, 1, a->res_c, a->lambda,
-                           a->h_red, (const Scal*)a->inner->bf.scal);
-    };
-    s->after_retest_ctx = al;
-    struct HookReset { lbfgsb_solver* s; ~HookReset() { s->after_retest = nullptr; s->after_retest_ctx = nullptr; } } hook_reset{s};
-    HIP_TRY(measure(0, true));
-    double viol_prev = al->h_red[0];
-    out.violation = viol_prev;
-    for (int it = 0; it < al->ao.max_outer; ++it) {
-        if (it > 0 && al->c_rows) {
-            // new targets/weights of the stacked constraint rows: the pair memory is cleared, and f and g at the
-            // unchanged x are shifted by the constraint rows' share (residuals and gradient are fresh at this point)
-            s->h_scal->iters = 0;
-            const bool f64 = s->dm.dtype == LBFGSB_F64;
-            if (al->n_eq <= kShiftRowsMax && al->n_eq * s->dm.cols <= kShiftMax) {
-                if (f64)
-                    hipLaunchKernelGGL(k_al_shift<double>, dim3(1), dim3(kShiftThreads), 0, al->stream, al->n_eq, al->rho, al->d_c,
-                                       (const double*)al->lambda, al->beta_c, al->omega_c, (double*)al->res_c, s->bf.scal,
-                                       s->bf.hist, s->dm.cols, s->dm.ld, (const double*)al->c_rows, s->bf.g);
-                else
-                    hipLaunchKernelGGL(k_al_shift<float>, dim3(1), dim3(kShiftThreads), 0, al->stream, al->n_eq, al->rho, al->d_c,
-                                       (const double*)al->lambda, al->beta_c, al->omega_c, (double*)al->res_c, s->bf.scal,
-                                       s->bf.hist, s->dm.cols, s->dm.ld, (const float*)al->c_rows, s->bf.g);
-            } else {
-                launch_restart(s->bf, s->stream);
-                hipLaunchKernelGGL(k_al_shift_rows, dim3(1), dim3(kBlock), 0, al->stream, al->n_eq, al->rho, al->d_c,
-                                   (const double*)al->lambda, al->beta_c, al->omega_c, (double*)al->res_c, al->coef, s->bf.scal);
-                int gb = (int)((s->dm.cols + 255) / 256);
-                if (gb > 1024) gb = 1024;
-                if (f64)
-                    hipLaunchKernelGGL(k_al_shift_g<double>, dim3(gb), dim3(256), 0, al->stream, al->n_eq, s->dm.cols, s->dm.ld,
-                                       (const double*)al->c_rows, (const double*)al->coef, s->bf.g);
-                else
-                    hipLaunchKernelGGL(k_al_shift_g<float>, dim3(gb), dim3(256), 0, al->stream, al->n_eq, s->dm.cols, s->dm.ld,
-                                       (const float*)al->c_rows, (const double*)al->coef, s->bf.g);
-            }
-            s->steps_since_refresh = 0;
-            s->steps_since_set_x = 0;
-        } else if (it > 0) {
-            // new targets/weights: the objective changed, so f and g are re-evaluated at x and the pair memory is cleared
-            hipLaunchKernelGGL(k_al_prepare, dim3(pb), dim3(256), 0, al->stream, al->n_eq, al->rho, al->d_c, al->lambda,
-                               al->beta_c, al->omega_c);
-            rc = set_x_impl(s, s->bf.x, true);
-            if (rc) return rc;
+    hipLaunchKernelGGL(k_al_begin, dim3(1), dim3(kTurnThreads), 0, al->stream, al->n_eq, al->ao.rho0, al->res_c, al->state);
+    volatile AlState* end = al->h_state;
+    end->done = 0;
+    const bool quad = is_quadratic(s->dm.kind);
+    Follower run(s);
+    run.begin(0);
+    for (int turns = 0;;) {
+        int st = LBFGSB_RUNNING;
+        if (s->use_resident) {
+            rc = solve_impl(s, nullptr);
+            st = s->h_scal->status;
+        } else {
+            rc = run.until_over(&st);
         }
-        lbfgsb_info ii;
-        rc = lbfgsb_solve(s, &ii);
         if (rc) return rc;
-        out.outer = it + 1;
-        out.inner_iters += ii.iters;
-        out.pg2 = ii.pg2;
-        if (ii.status == LBFGSB_LINESEARCH_FAILED) { out.status = ii.status; break; }
-        if (!(ii.status == LBFGSB_CONVERGED && s->last_read_was_retest)) {
-            HIP_TRY(al_fresh_eval(s));
-            HIP_TRY(measure(1, false));           // lambda += rho h(x); violation; penalty term
-            HIP_TRY(read_scal(s));                // (one wait for both)
-        }                                         // (else: done behind the solve's last wait)
-        out.L = s->h_scal->f;
-        out.violation = al->h_red[0];
-        out.f = out.L - al->h_red[1];
-        if (out.violation <= al->ao.ctol && ii.status == LBFGSB_CONVERGED) { out.status = LBFGSB_CONVERGED; break; }
-        if (out.violation > 0.5 * viol_prev) al->rho *= 2.0;
-        viol_prev = out.violation;
+        if (end->done) break;          // (by the turn in front of the steps that report the end)
+        if (st == -1) {
+            HIP_TRY(read_scal(s));
+            st = s->h_scal->status;
+            if (st == LBFGSB_RUNNING && run.steps < run.cap) { run.resume(); continue; }
+        }
+        if (st == LBFGSB_LINESEARCH_FAILED) {
+            hipLaunchKernelGGL(k_al_report, dim3(1), dim3(64), 0, al->stream, (const AlState*)al->state, al->h_state);
+            HIP_TRY(read_scal(s));
+            al->h_state->outer += 1;
+            al->h_state->inner_iters += s->h_scal->iters;
+            al->h_state->pg2 = s->h_scal->pg2;
+            al->h_state->status = LBFGSB_LINESEARCH_FAILED;
+            break;
+        }
+        enqueue_turn(al, st == LBFGSB_CONVERGED && quad && s->steps_since_refresh > 0);
+        HIP_TRY(hipGetLastError());
+        if (++turns >= al->ao.max_outer || s->use_resident) {
+            // (the last one, unless convergence was not confirmed: no step is enqueued behind it in vain)
+            HIP_TRY(hipStreamSynchronize(s->stream));
+            if (end->done) break;
+        }
+        run.begin(0);
     }
-    out.rho = al->rho;
-    if (info) *info = out;
+    if (end->nonfinite) {
+        s->x_set = false;
+        return fail(LBFGSB_E_NONFINITE, "the augmented Lagrangian is not finite at the iterate");
+    }
+    HIP_TRY(read_scal(s));
+    HIP_TRY(hipGetLastError());
+    if (info) {
+        const AlState& e = *al->h_state;
+        *info = lbfgsb_auglag_info{};
+        info->status = e.status; info->outer = e.outer; info->inner_iters = e.inner_iters;
+        info->violation = e.violation; info->rho = e.rho; info->f = e.f; info->L = e.L; info->pg2 = e.pg2;
+    }
     return LBFGSB_OK;
 }
 

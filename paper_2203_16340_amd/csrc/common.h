@@ -635,7 +635,6 @@ void launch_sym(const Dims& dm, const Geometry& ge, const Buffers& bf, const APa
                 hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
 void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
-void launch_set_status(const Buffers& bf, int status, hipStream_t st);
 void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* lin, const double* sign,
                         hipStream_t st);   // lin, sign: QP only (linear term b, sign vector)
 // no_close (see gram_can_skip_close): the kernel ends when its records of partial sums are written; the direction kernel does
@@ -658,7 +657,6 @@ void launch_check_bounds(const Dims& dm, const double* l, const double* u, Bound
 // 1 if some g_i is not finite.
 void launch_check_box(const Dims& dm, const Opts& op, const Buffers& bf, const double* x0, int* host_flag, hipStream_t st);
 void launch_start(const Dims& dm, const Buffers& bf, const double* x0, hipStream_t st);
-void launch_restart(const Buffers& bf, hipStream_t st);   // a fresh scalar block that keeps f (x stays)
 void launch_check_finite(const Dims& dm, const double* g, int* host_flag, hipStream_t st);
 // store_d: also keep d itself (the primitive-level hooks read it; an iteration only needs the two candidates)
 bool dir_folds_extra_rows(const Dims& dm);

@@ -20,13 +20,6 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
     hipLaunchKernelGGL(k_fill_zero, dim3(blocks), dim3(256), 0, st, (uint64_t*)p, words);
 }
 
-__global__ void k_set_status(Scal* scal, int status) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) scal->status = status;
-}
-void launch_set_status(const Buffers& bf, int status, hipStream_t st) {
-    hipLaunchKernelGGL(k_set_status, dim3(1), dim3(64), 0, st, bf.scal, status);
-}
-
 // ---- a new start point ----------------------------------------------------------------------------------
 //
 // Whether l <= x0 <= u and whether grad f(x0) is finite is found out on the device: the host used to fetch x0, l, u and g
@@ -101,22 +94,6 @@ __global__ __launch_bounds__(kBlock) void k_start(int64_t n, const double* x0, d
     }
     if (x0 == x) return;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) x[i] = x0[i];
-}
-__global__ __launch_bounds__(kBlock) void k_restart(Scal* scal, lbfgsb_iter_record* hist) {
-    __shared__ double f;
-    if (threadIdx.x == 0) f = scal->f;
-    __syncthreads();
-    for (int k = threadIdx.x; k < (int)(sizeof(Scal) / 4); k += kBlock) reinterpret_cast<int*>(scal)[k] = 0;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        scal->status = LBFGSB_RUNNING;
-        scal->alpha_ub = 1.0;
-        scal->hist = hist;
-        scal->f = f;
-    }
-}
-void launch_restart(const Buffers& bf, hipStream_t st) {
-    hipLaunchKernelGGL(k_restart, dim3(1), dim3(kBlock), 0, st, bf.scal, bf.hist);
 }
 static int start_blocks(int64_t n) {
     const int64_t b = (n + 4 * kBlock - 1) / (4 * kBlock);

@@ -76,6 +76,8 @@ struct lbfgsb_solver {
     bool commit_needed;      // resident solver: a kernel of the multi-kernel path may have left an update pending
     // lbfgsb_solve: steps enqueued since it began, redone ones included (Opts::seq), and the next one to report
     unsigned steps_enqueued = 0, note_at = 0;
+    // the last launch that touched x, g or the pairs has left the next Gram kernel's records (launch_update_gram_gauss)
+    bool gram_ready = false;
     int steps_since_refresh;
     long long steps_since_set_x;
     bool x_set;
@@ -340,6 +342,7 @@ OtArgs ot_args(const lbfgsb_solver* s) {
 
 // f, g (and the residual / margins) from scratch at the current x.  fresh: the scalar block holds no pending update.
 void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false) {
+    s->gram_ready = false;
     if (!fresh) launch_commit(s->dm, s->bf, s->stream);   // a pending f must not overwrite the one computed here
     if (is_transport(s->dm.kind)) {
         const OtArgs oa = ot_args(s);
@@ -371,6 +374,11 @@ void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false) {
     launch_eval_finish(s->dm, s->ge, s->bf, s->obj.b, s->obj.sign, s->stream);
 }
 
+bool is_recording(const lbfgsb_solver* s) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusActive;
+}
+
 // One iteration of Algorithm 1 as a fixed sequence of launches; nothing here waits for the device.
 void enqueue_step(lbfgsb_solver* s) {
     s->op.seq = ++s->steps_enqueued;
@@ -392,14 +400,18 @@ void enqueue_step(lbfgsb_solver* s) {
         // (the Gram kernel ends without its closing step, which the direction kernel does, and that kernel without its own: the
         // row-sum kernel, the first to need Algorithm 2's choice, makes it from the per-workgroup sums)
         const int open_gram = gram_can_skip_close(s->dm) ? 1 : 0;
-        {
+        if (!s->gram_ready || is_recording(s)) {
             TimedSlot ts(s, s->steps_since_set_x >= s->dm.m);
             launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, ts.e0, ts.e1, open_gram);
         }
         launch_dir(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream, nullptr, nullptr, 1, open_gram);
         const OtArgs oa = ot_args(s);
         launch_ot_sums(s->dm, s->ge, s->bf, oa, 0, 1, s->stream, s->ge.dir_blocks, s->op.eps, open_gram ? s->bf.scal_next : nullptr);
-        if (quad) launch_ot_update_gauss(s->dm, s->op, s->ge, s->bf, oa, s->stream);
+        // (a launch of its own while the Gram kernel is being timed, and in a graph, whose replays may follow anything)
+        s->gram_ready = quad && update_gram_ok(s->dm) && !s->timing && !is_recording(s);
+        if (s->gram_ready)
+            launch_update_gram_gauss(s->dm, s->op, s->ge, s->bf, s->bf.psi, s->ge.ot_row_blocks + s->ge.ot_col_blocks, s->stream);
+        else if (quad) launch_ot_update_gauss(s->dm, s->op, s->ge, s->bf, oa, s->stream);
         else launch_ot_step_entropy(s->dm, s->op, s->ge, s->bf, oa, s->stream);
         s->steps_since_refresh++;
         s->steps_since_set_x++;
@@ -463,11 +475,7 @@ void enqueue_step(lbfgsb_solver* s) {
         // (Steps recorded into a graph are not seen by the bookkeeping that redoes parked ones.  Rows on 16-byte
         // boundaries have always been recorded with the short sequence, see lbfgsb_get_x; other rows are recorded with
         // the sequence that finishes every iteration on the device.)
-        bool recording = false;
-        if (s->ge.vec == 1) {
-            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-            recording = hipStreamIsCapturing(s->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusActive;
-        }
+        const bool recording = s->ge.vec == 1 && is_recording(s);
         const bool full = s->logi_full_left > 0 || !s->short_ok || recording;
         a.ls_first = s->short_ok ? 1 : 0;
         const int first_parts = s->short_ok ? s->ge.fused_blocks : 0;
@@ -608,7 +616,7 @@ int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj
     s->logi_full_left = 0;
     s->short_steps_unseen = 0;
     s->commit_needed = true;
-    s->x_set = false;
+    s->x_set = s->gram_ready = false;
     s->timing = false;
     s->timed = 0;
     const Layout L = make_layout(s->dm, s->ge);
@@ -1151,7 +1159,7 @@ const char* lbfgsb_apass_name(const lbfgsb_solver* s) {
 
 int lbfgsb_dbg_fg(lbfgsb_solver* s, const double* x, double* f_host, double* g, double* rowvec) {
     if (!s || !x || !f_host || !g) return fail(LBFGSB_E_INVALID_ARG, "NULL argument");
-    s->x_set = false;
+    s->x_set = s->gram_ready = false;
     HIP_TRY(hipMemcpyAsync(s->bf.x, x, (size_t)s->dm.n * 8, hipMemcpyDeviceToDevice, s->stream));
     fresh_scal(s);
     HIP_TRY(write_scal(s));
@@ -1168,7 +1176,7 @@ int lbfgsb_dbg_fg(lbfgsb_solver* s, const double* x, double* f_host, double* g, 
 
 int lbfgsb_dbg_free_mask(lbfgsb_solver* s, const double* x, const double* g, uint8_t* mask) {
     if (!s || !x || !g || !mask) return fail(LBFGSB_E_INVALID_ARG, "NULL argument");
-    s->x_set = false;
+    s->x_set = s->gram_ready = false;
     HIP_TRY(hipMemcpyAsync(s->bf.x, x, (size_t)s->dm.n * 8, hipMemcpyDeviceToDevice, s->stream));
     HIP_TRY(hipMemcpyAsync(s->bf.g, g, (size_t)s->dm.n * 8, hipMemcpyDeviceToDevice, s->stream));
     fresh_scal(s);
@@ -1185,7 +1193,7 @@ int lbfgsb_dbg_two_loop(lbfgsb_solver* s, const double* S, const double* Y, cons
     if (!s || !g || !mask || !d) return fail(LBFGSB_E_INVALID_ARG, "NULL argument");
     if (npairs < 0 || npairs > s->dm.m) return fail(LBFGSB_E_INVALID_ARG, "npairs must be in 0..m");
     if (npairs > 0 && (!S || !Y || !ynorm2)) return fail(LBFGSB_E_INVALID_ARG, "NULL pair arrays");
-    s->x_set = false;
+    s->x_set = s->gram_ready = false;
     const size_t nb = (size_t)s->dm.n * 8;
     fresh_scal(s);
     if (npairs > 0) {
@@ -1212,7 +1220,7 @@ int lbfgsb_dbg_two_loop(lbfgsb_solver* s, const double* S, const double* Y, cons
 int lbfgsb_dbg_project_direction(lbfgsb_solver* s, const double* x, const double* g, const double* d, double* p,
                                  int* branch, double* alpha_ub) {
     if (!s || !x || !g || !d || !p) return fail(LBFGSB_E_INVALID_ARG, "NULL argument");
-    s->x_set = false;
+    s->x_set = s->gram_ready = false;
     const size_t nb = (size_t)s->dm.n * 8;
     HIP_TRY(hipMemcpyAsync(s->bf.x, x, nb, hipMemcpyDeviceToDevice, s->stream));
     HIP_TRY(hipMemcpyAsync(s->bf.g, g, nb, hipMemcpyDeviceToDevice, s->stream));
@@ -1524,6 +1532,7 @@ void enqueue_turn(lbfgsb_auglag* al, bool confirm) {
     s->steps_since_set_x = 0;
     const bool stacked = al->variant == lbfgsb_auglag::kStacked, marginals = al->variant == lbfgsb_auglag::kMarginals;
     AlTurn a{};
+    s->gram_ready = false;             // (the gradient is shifted, the pairs are dropped)
     a.n_eq = al->n_eq; a.cols = stacked ? s->dm.cols : s->dm.n; a.ld = al->c_ld;
     a.ctol = al->ao.ctol; a.max_outer = al->ao.max_outer; a.retest = confirm ? 1 : 0;
     a.fevals = stacked ? 0 : 1;        // (of a stacked subproblem's start this never counted)

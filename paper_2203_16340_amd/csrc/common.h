@@ -498,6 +498,20 @@ __device__ __forceinline__ double sum_all(const double* __restrict__ v, int coun
 constexpr int64_t kOtWideMin = 3 << 18;
 inline int ot_threads(const Dims& dm) { return dm.n >= kOtWideMin ? 1024 : 256; }
 
+// Closed-form Armijo search along a direction of curvature tt: the first of a, a backtrack, .. (a = min(1, bound)) with
+// a gp + a^2/2 tt <= c1 a gp, tested after division by a > 0.  bt: halvings, ok = 0: none accepted.
+__device__ __forceinline__ double armijo_quadratic(double gp, double tt, double alpha_ub, const Opts& op, int& ok, int& bt) {
+    double a = fmin(1.0, alpha_ub);
+    ok = 0;
+    bt = op.max_backtracks + 1;
+    for (int k = 0; k <= op.max_backtracks; ++k) {
+        const double lhs = gp + 0.5 * a * tt;          // (f(x + a p) - f(x)) / a
+        if (isfinite(a * lhs) && lhs <= op.c1 * gp) { ok = 1; bt = k; break; }
+        a *= op.backtrack;
+    }
+    return a;
+}
+
 // ---- launch geometry decided once at creation -------------------------------------------------------
 
 struct Geometry {
@@ -538,7 +552,7 @@ struct Buffers {
     double *S, *Y;          // m x n rings
     double *row;            // residual A v - b (least squares) or margins (logistic), rows entries
     double *t;              // A p, rows entries
-    double *psi;            // per-row weights of the transposed product, rows entries
+    double *psi;            // per-row weights of the transposed product, rows entries (transport: omega . (K p), or first-length sums)
     double *wpart;          // w_parts x cols partial columns of A^T psi
     double *losspart;       // loss partials of the A pass
     double *grampart;       // gram_blocks x gram_entries
@@ -642,6 +656,11 @@ void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, c
 void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int dbg_inputs,
                  int evaluate_stop, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, int no_close = 0);
 bool gram_can_skip_close(const Dims& dm);
+// The update of the Gaussian transport kind with the next iteration's Gram kernel in it (its records are then there: no launch_gram
+// before that iteration's direction kernel).  wt: omega . (K p), rows + cols entries.
+bool update_gram_ok(const Dims& dm);
+void launch_update_gram_gauss(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const double* wt, int loss_parts,
+                              hipStream_t st);
 // ... what it then finds: `count` records (workgroups' sums, or those of groups of workgroups)
 struct GramRecords { const double* part; int count; };
 GramRecords gram_records(const Dims& dm, const Geometry& ge, const Buffers& bf);

@@ -142,7 +142,29 @@ __device__ __forceinline__ double keep_if(double v, int keep) {           // kee
 }
 
 // Adds the products of 64 elements: lane l holds elements 2 (l / 4), the next, and the same behind 32 of vector 4 t + l % 4.
-template <int K>
+// A0, A1: the rows of tiles that are meant (all of them at once want 4 registers a pair).
+template <int K, int A0, int A1>
+__device__ __forceinline__ void tile_products_rows(const f64x2 (&v)[2 * K][2], const int (&keep)[4], double (&sum)[gram_tile_pairs(K)]) {
+    constexpr int kFirst = A0 * 2 * K - A0 * (A0 - 1) / 2, kCount = A1 * 2 * K - A1 * (A1 - 1) / 2 - kFirst;
+    double acc[kCount];
+#pragma unroll
+    for (int k = 0; k < kCount; ++k) acc[k] = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        double o[2 * K];
+#pragma unroll
+        for (int t = A0; t < 2 * K; ++t) o[t] = keep_if(q & 1 ? v[t][q / 2].y : v[t][q / 2].x, keep[q]);
+        int k = 0;
+#pragma unroll
+        for (int a = A0; a < A1; ++a) {
+#pragma unroll
+            for (int b = a; b < 2 * K; ++b, ++k) acc[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(o[a], o[b], acc[k], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kCount; ++k) sum[kFirst + k] += acc[k];
+}
+template <int K, bool APART = false>
 __device__ __forceinline__ void tile_products(const f64x2 (&v)[2 * K][2], unsigned long long bits, double (&sum)[gram_tile_pairs(K)]) {
     const int at = ((threadIdx.x & 63) >> 2) * 2;
     int keep[4];
@@ -152,23 +174,13 @@ __device__ __forceinline__ void tile_products(const f64x2 (&v)[2 * K][2], unsign
         keep[2 * h] = __builtin_amdgcn_sbfe(w, 0, 1);
         keep[2 * h + 1] = __builtin_amdgcn_sbfe(w, 1, 1);
     }
-    double acc[gram_tile_pairs(K)];
-#pragma unroll
-    for (int k = 0; k < gram_tile_pairs(K); ++k) acc[k] = 0.0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        double o[2 * K];
-#pragma unroll
-        for (int t = 0; t < 2 * K; ++t) o[t] = keep_if(q & 1 ? v[t][q / 2].y : v[t][q / 2].x, keep[q]);
-        int k = 0;
-#pragma unroll
-        for (int a = 0; a < K; ++a) {
-#pragma unroll
-            for (int b = a; b < 2 * K; ++b, ++k) acc[k] = __builtin_amdgcn_mfma_f64_4x4x4f64(o[a], o[b], acc[k], 0, 0, 0);
-        }
+    if constexpr (APART && K == 3) {
+        tile_products_rows<K, 0, 1>(v, keep, sum);
+        __builtin_amdgcn_sched_barrier(0);
+        tile_products_rows<K, 1, 3>(v, keep, sum);
+    } else {
+        tile_products_rows<K, 0, K>(v, keep, sum);
     }
-#pragma unroll
-    for (int k = 0; k < gram_tile_pairs(K); ++k) sum[k] += acc[k];
 }
 
 // The four blocks added, and the wave's 4 x 4 results of every pair of tiles into its part of LDS: pair k, row i, column j at
@@ -190,6 +202,43 @@ __device__ __forceinline__ int tile_place(int K, int a, int b, bool b_is_s) {
     const int lo = b_is_s || a < b ? a : b, hi = (b_is_s || a < b ? b : a) + (b_is_s ? 4 * K : 0);
     const int ta = lo >> 2, tb = hi >> 2;
     return 16 * (ta * 2 * K - ta * (ta - 1) / 2 + tb - ta) + 4 * (lo & 3) + (hi & 3);
+}
+
+// A workgroup's record: the waves' results (tile_results, `wave_lds` doubles a wave) added in wave order.  BY_AGE: rows and columns
+// of the tiles are pairs by age and g is row c; else ring slots and g row M.
+template <int NW, int WAVE_LDS, bool BY_AGE>
+__device__ __forceinline__ void gram_record(double pginf, double ynew, int nfixed, int K, int M, int m, int c, int base_slot, int slot_a,
+                                            int slot_b, const double* dyn, double* red, double* __restrict__ grampart) {
+    constexpr int NT = 64 * NW;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    pginf = wave_max(pginf);
+    ynew = wave_sum(ynew);
+    if (lane == 0) { red[wave] = pginf; red[NW + wave] = (double)nfixed; red[2 * NW + wave] = ynew; }
+    __syncthreads();
+    double* part = grampart + (int64_t)blockIdx.x * gram_entries(m);
+    for (int idx = tid; idx < gram_products(m); idx += NT) {
+        int a = slot_a, b = slot_b;
+        if (idx != tid) gram_product_slots(idx, m, a, b);
+        // row or column of a slot (past the last pair: not held, any number)
+        auto place = [&](int slot) -> int {
+            if (slot == m) return BY_AGE ? c : M;
+            const int ring = slot < m ? slot : slot - m - 1;
+            if (!BY_AGE) return ring;
+            const int j = ring >= base_slot ? ring - base_slot : ring - base_slot + m;
+            return j < c ? j : 0;
+        };
+        const int src = tile_place(K, place(a), place(b), b > m);
+        double t = dyn[src];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t += dyn[w * WAVE_LDS + src];
+        publish(part + kGramHdr + idx, t);
+    }
+    if (tid < 3) {
+        double t = red[tid * NW];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t = tid == 0 ? fmax(t, red[w]) : t + red[tid * NW + w];
+        publish(part + tid, t);
+    }
 }
 
 template <int M, int NW, bool LONG, bool DBG>
@@ -366,42 +415,203 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
         tile_results<KM>(sum, mine);
     }
 
-    // this workgroup's record: the waves' results added in wave order
-    pginf = wave_max(pginf);
-    ynew = wave_sum(ynew);
-    if (lane == 0) { red[wave] = pginf; red[NW + wave] = (double)nfixed; red[2 * NW + wave] = ynew; }
-    __syncthreads();
     const int NE = gram_entries(m);
-    double* part = grampart + (int64_t)blockIdx.x * NE;
-    for (int idx = tid; idx < gram_products(m); idx += NT) {
-        int a = slot_a, b = slot_b;
-        if (idx != tid) gram_product_slots(idx, m, a, b);
-        // row or column of a slot: by ring slot, LONG by age (c, or M, is g; past the last pair: not held, any number)
-        auto place = [&](int slot) -> int {
-            if (slot == m) return LONG ? c : M;
-            const int ring = slot < m ? slot : slot - m - 1;
-            if (!LONG) return ring;
-            const int j = ring >= base_slot ? ring - base_slot : ring - base_slot + m;
-            return j < c ? j : 0;
-        };
-        const int src = tile_place(K, place(a), place(b), b > m);
-        double t = dyn[src];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) t += dyn[w * kWaveLds + src];
-        publish(part + kGramHdr + idx, t);
-    }
-    if (tid < 3) {
-        double t = red[tid * NW];
-#pragma unroll
-        for (int w = 1; w < NW; ++w) t = tid == 0 ? fmax(t, red[w]) : t + red[tid * NW + w];
-        publish(part + tid, t);
-    }
+    gram_record<NW, kWaveLds, LONG>(pginf, ynew, nfixed, K, M, m, c, base_slot, slot_a, slot_b, dyn, red, grampart);
     if (!LONG && no_close) return;   // the direction kernel adds the records and does the rest
     double* tot = dyn + gram_tot_at(M);
     if (!reduce_partials<NT, false>(grampart, NE, scal, &flag, tot, LONG && no_close, GramPlaces{m, c, base_slot})) return;
     gram_finish<NT, 10, false>(tot, dyn, alpha_s, scal, m, c, head, base_slot, op, yn_old, DBG, evaluate_stop, true);
     __syncthreads();
     if (tid == 0 && evaluate_stop) note_progress(op, scal->status);
+}
+
+// The Gaussian transport kind's update (k_ot_update_gauss) and the free set and Gram matrix of the next iteration in one pass: what
+// the update writes -- x, g and the new pair -- the Gram kernel would read again next, and an element's products need nothing that
+// other workgroups write.  The stream is k_gram's with one stage more: x, g, p and the entry's two coefficients arrive three
+// chunks ahead; the new values are formed, stored and kept in LDS, from where the products take them.  A step whose line search
+// fails changes nothing, and the next one starts from the gradient alone.  Rows of 64 columns at least: a chunk then crosses one row's
+// end at most.
+// n = 10^6, us, the update's kernel and k_gram / this: 1 pair 26 / 21.6, 4 32 / 27.7, 10 44.3 / 38.4.  (Two groups of tiles one after
+// the other and 32-bit offsets from scalar bases for the registers' sake: with 11 spilled the last figure was 41.)
+// SAME: every variable has the same bounds.
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+template <int M, bool SAME>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_update_gram_gauss(Dims dm, Opts op, int loss_parts, const double* __restrict__ losspart, const double* __restrict__ wt,
+                         const double* __restrict__ p1, const double* __restrict__ p2, const double* __restrict__ l,
+                         const double* __restrict__ u, double* __restrict__ x, double* __restrict__ g, double* __restrict__ S,
+                         double* __restrict__ Y, uint8_t* __restrict__ mask, Scal* __restrict__ scal, double* __restrict__ grampart) {
+    constexpr int NW = 8, NT = 64 * NW, KM = gram_tiles(M), kWaveLds = 16 * gram_tile_pairs(KM);
+    constexpr int kNew = 3 * 64;                         // a chunk's new g, y and s
+    __shared__ __align__(16) double dyn[NW * kWaveLds];
+    __shared__ __align__(16) double fresh_s[NW * 2 * kNew];
+    __shared__ double red[NW * 3];
+    __shared__ double ls_alpha;
+    __shared__ int ls_ok, ls_bt, flag;
+    if (scal->status != LBFGSB_RUNNING) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = dm.m;
+    const int64_t n = dm.n, cols = dm.cols;
+    const int head = scal->head, held = scal->count, branch = scal->branch;
+    const double gp = scal->gp, alpha_ub = scal->alpha_ub, f_old = scal->f;
+    const double tt = sum_all<NT>(losspart, loss_parts, red) + dm.lambda * scal->pp;
+    if (tid == 0) {
+        int ok, bt;
+        ls_alpha = armijo_quadratic(gp, tt, alpha_ub, op, ok, bt);
+        ls_ok = ok; ls_bt = bt;
+    }
+    int slot_a, slot_b;
+    gram_product_slots(tid < gram_products(m) ? tid : 0, m, slot_a, slot_b);
+    __syncthreads();
+    const double alpha = ls_alpha;
+    const bool ok = __builtin_amdgcn_readfirstlane(ls_ok) != 0;
+    const int c = __builtin_amdgcn_readfirstlane(ok ? (held < m ? held + 1 : m) : 0);      // pairs held from here on; the newest in slot `head`
+    const int base_slot = __builtin_amdgcn_readfirstlane(c > 0 ? (head + 1 - c + 2 * m) % m : 0);
+    const double* p = branch == 1 ? p1 : p2;
+    double *Sn = S + (int64_t)head * n, *Yn = Y + (int64_t)head * n;
+
+    const int64_t nchunks = (n + 63) / 64, stride = (int64_t)gridDim.x * NW;
+    const int64_t ch0 = (int64_t)blockIdx.x * NW + wave;
+    const double inv_cols = 1.0 / (double)cols;
+    struct Elem { double x, g, p, wr, wc, l[SAME ? 1 : 2]; };
+    auto request = [&](int64_t ch, Elem& s) {
+        // (a chunk past the end: the last one's; scalar base and 32-bit offset)
+        const int64_t first = (ch < nchunks ? ch : nchunks - 1) * 64;
+        const unsigned at = first + 64 <= n ? (unsigned)lane : ((unsigned)lane < (unsigned)(n - first) ? (unsigned)lane : (unsigned)(n - first) - 1u);
+        s.x = (x + first)[at]; s.g = (g + first)[at]; s.p = (p + first)[at];
+        if constexpr (!SAME) { s.l[0] = (l + first)[at]; s.l[1] = (u + first)[at]; }
+        // row and column of the chunk's first element (uniform), then of this lane's
+        int64_t row = (int64_t)((double)first * inv_cols), col = first - row * cols;
+        if (col < 0) { col += cols; --row; }
+        if (col >= cols) { col -= cols; ++row; }
+        row = uniform64(row);
+        col = uniform64(col);
+        const int64_t left = cols - col;                  // (of this row)
+        const bool next = (int64_t)at >= left;
+        s.wr = (wt + row)[next ? 1u : 0u];
+        s.wc = (wt + dm.rows + (left < 64 ? 0 : col))[left < 64 ? (next ? at - (unsigned)left : (unsigned)col + at) : at];
+    };
+    double pginf = 0.0, ynew = 0.0;
+    int nfixed = 0;
+    double* fresh = fresh_s + wave * (2 * kNew);
+    auto decide = [&](int64_t ch, const Elem& s, double* keep) -> unsigned long long {
+        const int64_t first = ch * 64;
+        const bool in = first + lane < n;
+        const double y = ok ? alpha * fma(dm.lambda, s.p, s.wr + s.wc) : 0.0;
+        const double lo = SAME ? op.lo : s.l[0], hi = SAME ? op.hi : s.l[SAME ? 0 : 1];
+        const double xn = ok ? clampd(fma(alpha, s.p, s.x), lo, hi) : s.x;
+        const double gn = s.g + y, sn = xn - s.x;
+        const bool at_lower = (xn <= lo + op.eps) && (gn >= 0.0);
+        const bool at_upper = (xn >= hi - op.eps) && (gn <= 0.0);
+        const bool fr = !(at_lower || at_upper);
+        if (in) {
+            (mask + first)[(unsigned)lane] = (uint8_t)fr;
+            if (ok) {
+                (Sn + first)[(unsigned)lane] = sn; (Yn + first)[(unsigned)lane] = y;
+                (x + first)[(unsigned)lane] = xn; (g + first)[(unsigned)lane] = gn;
+            }
+        }
+        keep[lane] = gn; keep[64 + lane] = y; keep[128 + lane] = sn;
+        pginf = fmax(pginf, in ? fabs(xn - clampd(xn - gn, lo, hi)) : 0.0);
+        ynew = fma(in ? y : 0.0, y, ynew);
+        const unsigned long long bits = __ballot(fr && in);
+        nfixed += __popcll(__ballot(in)) - __popcll(bits);
+        return bits;
+    };
+    const int i4 = lane & 3, pair_at = (lane >> 2) * 2;
+    double* mine = dyn + wave * kWaveLds;
+    auto stream = [&](auto tiles) {
+        constexpr int KT = decltype(tiles)::value;
+        const double* from[2 * KT];                      // (old pairs; what is new, or not there, reads g and is not looked at)
+#pragma unroll
+        for (int t = 0; t < 2 * KT; ++t) {
+            const int j = 4 * (t < KT ? t : t - KT) + i4, slot = base_slot + j < m ? base_slot + j : base_slot + j - m;
+            from[t] = j + 1 < c ? (t < KT ? Y : S) + (int64_t)slot * n : g;
+        }
+        // tiles that hold something new: row c is g, row and column c - 1 the new pair
+        const int tile_g = c >> 2, tile_pair = (c - 1) >> 2;
+        auto fetch = [&](int64_t ch, unsigned long long bits, f64x2 (&v)[2 * KT][2]) {
+            const unsigned head_pair = bits ? (unsigned)__builtin_ctzll(bits) & ~1u : 0u;
+            const int64_t e0 = bits ? ch * 64 : 0;       // (uniform)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const unsigned w = (unsigned)(bits >> (32 * h)) >> pair_at;
+                const int64_t e = e0 + (w & 3u ? 32u * h + pair_at : head_pair);
+#pragma unroll
+                for (int t = 0; t < 2 * KT; ++t) v[t][h] = *reinterpret_cast<const f64x2_any*>(from[t] + e);
+            }
+        };
+        auto insert = [&](const double* keep, f64x2 (&v)[2 * KT][2]) {
+#pragma unroll
+            for (int t = 0; t < 2 * KT; ++t) {
+                const int tt_ = t < KT ? t : t - KT;
+                if (t < KT && tt_ == tile_g) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const f64x2 q = *reinterpret_cast<const f64x2*>(keep + 32 * h + pair_at);
+                        v[t][h] = i4 == (c & 3) ? q : v[t][h];
+                    }
+                }
+                if (c > 0 && tt_ == tile_pair) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const f64x2 q = *reinterpret_cast<const f64x2*>(keep + (t < KT ? 64 : 128) + 32 * h + pair_at);
+                        v[t][h] = i4 == ((c - 1) & 3) ? q : v[t][h];
+                    }
+                }
+            }
+        };
+        double sum[gram_tile_pairs(KT)];
+#pragma unroll
+        for (int k = 0; k < gram_tile_pairs(KT); ++k) sum[k] = 0.0;
+        if (ch0 < nchunks) {
+            f64x2 va[2 * KT][2], vb[2 * KT][2];
+            Elem sa, sb;
+            request(ch0, sa);
+            request(ch0 + stride, sb);
+            unsigned long long ba = decide(ch0, sa, fresh), bb;
+            fetch(ch0, ba, va);
+            request(ch0 + 2 * stride, sa);
+            for (int64_t ch = ch0; ch < nchunks; ch += 2 * stride) {
+                bb = decide(ch + stride, sb, fresh + kNew);
+                fetch(ch + stride, bb, vb);
+                request(ch + 3 * stride, sb);
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_wave_barrier();
+                insert(fresh, va);
+                tile_products<KT, true>(va, ba, sum);
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+                ba = decide(ch + 2 * stride, sa, fresh);
+                fetch(ch + 2 * stride, ba, va);
+                request(ch + 4 * stride, sa);
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_wave_barrier();
+                insert(fresh + kNew, vb);
+                tile_products<KT, true>(vb, bb, sum);
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        tile_results<KT>(sum, mine);
+    };
+    const int K = c / 4 + 1;
+    if (K == 1) stream(std::integral_constant<int, 1>());
+    else if (KM == 2 || K == 2) stream(std::integral_constant<int, 2>());
+    else if constexpr (KM == 3) stream(std::integral_constant<int, 3>());
+
+    gram_record<NW, kWaveLds, true>(pginf, ynew, nfixed, K, M, m, c, base_slot, slot_a, slot_b, dyn, red, grampart);
+    // (no workgroup of this kernel reads the pend_* fields)
+    if (blockIdx.x == 0 && tid == 0) {
+        scal->pend_ok = ok;
+        scal->pend_bt = ls_bt;
+        scal->pend_alpha = alpha;
+        scal->pend_f = f_old + alpha * (gp + 0.5 * alpha * tt);
+        scal->pend_valid = 1;
+    }
+    reduce_partials<NT, false>(grampart, gram_entries(m), scal, &flag, nullptr, true, GramPlaces{m, c, base_slot});
 }
 
 // Beyond 10 pairs: v_mfma_f64_16x16x4_f64, a 16 x 4 by a 4 x 16 block (the pairs of 4 x 4 tiles would take all registers).  A lane
@@ -695,6 +905,19 @@ void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffe
     hipExtLaunchKernelGGL(k, dim3(ge.gram_blocks), dim3(threads), lds, st, ev0, ev1, 0, dm.n, dm.m, op, (const double*)bf.x,
                           (const double*)bf.g, (const double*)bf.l, (const double*)bf.u, (const double*)bf.S, (const double*)bf.Y,
                           bf.mask, bf.scal, bf.grampart, evaluate_stop, no_close);
+}
+
+// Rows of 64 columns at least (see the kernel), long vectors, and a direction kernel that does the closing step.
+bool update_gram_ok(const Dims& dm) {
+    return dm.kind == LBFGSB_OBJ_OT_GAUSS && dm.n >= kGramLongN && dm.cols >= 64 && gram_can_skip_close(dm);
+}
+void launch_update_gram_gauss(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const double* wt, int loss_parts,
+                              hipStream_t st) {
+    const auto k = gram_m_for(dm.m) == 5 ? (op.uniform_bounds ? k_update_gram_gauss<5, true> : k_update_gram_gauss<5, false>)
+                                         : (op.uniform_bounds ? k_update_gram_gauss<10, true> : k_update_gram_gauss<10, false>);
+    hipLaunchKernelGGL(k, dim3(ge.gram_blocks), dim3(512), 0, st,
+                       dm, op, loss_parts, (const double*)bf.losspart, wt, (const double*)bf.p1, (const double*)bf.p2,
+                       (const double*)bf.l, (const double*)bf.u, bf.x, bf.g, bf.S, bf.Y, bf.mask, bf.scal, bf.grampart);
 }
 
 // Applies a pending update when nothing else is about to (before an evaluation from scratch, and

@@ -55,14 +55,14 @@ bool ot_sums_first_length(const Dims& dm, const Geometry& ge) {
 }
 
 // K z, first half: the sums of the RPW rows this workgroup owns, and its partial column sums.  first (or null): the entropy's
-// line search, sum_e x_e h(a_0 z_e / x_e) over these rows.
+// line search, sum_e x_e h(a_0 z_e / x_e) over these rows.  wt (or null): omega . (K z) as well.
 template <int RPW>
 __global__ __launch_bounds__(kBlock) void k_ot_sums(Dims dm, OtArgs a, int eval, int check_status,
                                                     const double* __restrict__ x, const double* __restrict__ p1,
                                                     const double* __restrict__ p2, Scal* __restrict__ scal,
                                                     double* __restrict__ out, double* __restrict__ wpart,
                                                     double* __restrict__ losspart, const double* __restrict__ dir_part,
-                                                    int dir_blocks, double eps, Scal* __restrict__ scal_next, double* __restrict__ first) {
+                                                    int dir_blocks, double eps, Scal* __restrict__ scal_next, double* __restrict__ first, double* __restrict__ wt) {
     __shared__ double red[kWaves * (RPW + 1 > 7 ? RPW + 1 : 7)];
     const int tid = threadIdx.x;
     const int status = check_status ? (scal_next ? scal_next : scal)->status : LBFGSB_RUNNING;
@@ -138,6 +138,7 @@ __global__ __launch_bounds__(kBlock) void k_ot_sums(Dims dm, OtArgs a, int eval,
                 // beta is only there together with omega (no marginal terms: the plain sums are left in `out`)
                 const double res = (eval && a.omega) ? acc[r] - a.beta[r0 + r] : acc[r];
                 out[r0 + r] = res;
+                if (wt) wt[r0 + r] = a.omega ? a.omega[r0 + r] * res : 0.0;
                 if (a.omega) loss += (eval ? 0.5 : 1.0) * a.omega[r0 + r] * res * res;
             }
         }
@@ -169,7 +170,7 @@ __global__ __launch_bounds__(kBlock) void k_ot_sums(Dims dm, OtArgs a, int eval,
 // K z, second half: the column sums from the workgroups' partials.
 __global__ __launch_bounds__(kBlock) void k_ot_cols(Dims dm, OtArgs a, int eval, int check_status, int parts,
                                                     const double* __restrict__ wpart, const Scal* __restrict__ scal,
-                                                    double* __restrict__ out, double* __restrict__ losspart) {
+                                                    double* __restrict__ out, double* __restrict__ losspart, double* __restrict__ wt) {
     __shared__ double lds[kBlock];
     __shared__ double red[kWaves];
     if (check_status && scal->status != LBFGSB_RUNNING) return;
@@ -181,6 +182,7 @@ __global__ __launch_bounds__(kBlock) void k_ot_cols(Dims dm, OtArgs a, int eval,
         if (tid < kCX && c < dm.cols) {
             const double res = (eval && a.omega) ? s - a.beta[dm.rows + c] : s;
             out[dm.rows + c] = res;
+            if (wt) wt[dm.rows + c] = a.omega ? a.omega[dm.rows + c] * res : 0.0;
             if (a.omega) loss[0] += (eval ? 0.5 : 1.0) * a.omega[dm.rows + c] * res * res;
         }
     }
@@ -298,14 +300,9 @@ __global__ __launch_bounds__(kBlock) void k_ot_update_gauss(Dims dm, Opts op, Ot
     const double* p = scal->branch == 1 ? p1 : p2;
     const double tt = sum_all(losspart, loss_parts, red) + dm.lambda * scal->pp;
     if (tid == 0) {
-        double al = fmin(1.0, alpha_ub);
-        int ok = 0, bt = 0;
-        for (int k = 0; k <= op.max_backtracks; ++k) {
-            const double lhs = gp + 0.5 * al * tt;          // (f(x + a p) - f(x)) / a
-            if (isfinite(al * lhs) && lhs <= op.c1 * gp) { ok = 1; bt = k; break; }
-            al *= op.backtrack;
-        }
-        ls_alpha = al; ls_ok = ok; ls_bt = ok ? bt : op.max_backtracks + 1;
+        int ok, bt;
+        ls_alpha = armijo_quadratic(gp, tt, alpha_ub, op, ok, bt);
+        ls_ok = ok; ls_bt = bt;
     }
     __syncthreads();
     const double alpha = ls_alpha;
@@ -668,7 +665,7 @@ void launch_sums_t(const Dims& dm, const Geometry& ge, const Buffers& bf, const 
     hipLaunchKernelGGL(k_ot_sums<RPW>, dim3(ge.ot_row_blocks), dim3(kBlock), 0, st, dm, a, eval, check_status,
                        (const double*)bf.x, (const double*)bf.p1, (const double*)bf.p2, bf.scal, eval ? bf.row : bf.t,
                        bf.wpart, bf.losspart, (const double*)bf.redpart, eval ? 0 : dir_blocks, eps, scal_next,
-                       !eval && ot_sums_first_length(dm, ge) ? bf.psi : nullptr);
+                       !eval && ot_sums_first_length(dm, ge) ? bf.psi : nullptr, !eval && dm.kind == LBFGSB_OBJ_OT_GAUSS ? bf.psi : nullptr);
 }
 
 }  // namespace
@@ -683,7 +680,8 @@ void launch_ot_sums(const Dims& dm, const Geometry& ge, const Buffers& bf, const
         default: launch_sums_t<kOtRpwMax>(dm, ge, bf, a, eval, check_status, st, dir_blocks, eps, scal_next); break;
     }
     hipLaunchKernelGGL(k_ot_cols, dim3(ge.ot_col_blocks), dim3(kBlock), 0, st, dm, a, eval, check_status, ge.ot_row_blocks,
-                       (const double*)bf.wpart, (const Scal*)bf.scal, eval ? bf.row : bf.t, bf.losspart + ge.ot_row_blocks);
+                       (const double*)bf.wpart, (const Scal*)bf.scal, eval ? bf.row : bf.t, bf.losspart + ge.ot_row_blocks,
+                       !eval && dm.kind == LBFGSB_OBJ_OT_GAUSS ? bf.psi : nullptr);
 }
 
 // f(workgroup size, rows per group, short rows) for this shape's instantiation

@@ -713,14 +713,9 @@ __global__ __launch_bounds__(kBlock) void k_update_quadratic(Dims dm, Opts op, i
     // curvature along p: ||t||^2 (weighted) from the A pass, plus the extra rows' sum weight (e_r.p)^2
     const double tt = sum_all(losspart, loss_parts, red) + (own_fold ? fold_s[kFoldMax] : (xres ? xres[dm.n_extra] : 0.0));
     if (tid == 0) {
-        double a = fmin(1.0, alpha_ub);
-        int ok = 0, bt = 0;
-        for (int k = 0; k <= op.max_backtracks; ++k) {
-            const double lhs = gp + 0.5 * a * tt;          // (f(x + a p) - f(x)) / a
-            if (isfinite(a * lhs) && lhs <= op.c1 * gp) { ok = 1; bt = k; break; }
-            a *= op.backtrack;
-        }
-        ls_alpha = a; ls_ok = ok; ls_bt = ok ? bt : op.max_backtracks + 1;
+        int ok, bt;
+        ls_alpha = armijo_quadratic(gp, tt, alpha_ub, op, ok, bt);
+        ls_ok = ok; ls_bt = bt;
     }
     __syncthreads();
     const double alpha = ls_alpha;

@@ -1,0 +1,123 @@
+"""The Gaussian transport update with the next iteration's Gram matrix in it: rows of 64 columns (the least it takes) and just more,
+chunks that cross a row's end, a last chunk of any length, every number of tiles, bounds that differ, and everything that may come
+between two steps and leave its sums out of date.
+
+Tolerances as for the other transport iterations: 1e-8 normwise against the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2203_16340_amd as L
+from gpu_helpers import rel_err, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def problem(rows, cols, m, uniform=True, rho=4.0, lam=0.5, refresh_every=32, **opts):
+    rng = np.random.default_rng(rows + cols + m)
+    M, n = rng.random((rows, cols)) - 0.3, rows * cols
+    u, v = rng.random(rows) + 0.1, rng.random(cols) + 0.1
+    u, v = u / u.sum(), v / v.sum()
+    l, ub = np.zeros(n), np.full(n, np.inf)
+    if not uniform:
+        ub[rng.random(n) < 0.1] = 0.5 / n
+    x0 = np.where(rng.random(n) < 0.5, 0.0, 0.4 * rng.random(n) / n)
+    ref = oracle.Solver(oracle.Objective(oracle.OT_GAUSS, M, lam=lam).set_marginals(u, v, lam=np.zeros(rows + cols), rho=rho), l, ub,
+                        x0, m, oracle.default_options(tol=0.0, **opts))
+    s = L.Solver(L.OBJ_OT_GAUSS, to_dev(M), to_dev(np.concatenate([u, v])), to_dev(l), to_dev(ub), m, lam=lam,
+                 options=L.default_options(tol=0.0, refresh_every=refresh_every, **opts), row_weight=to_dev(np.full(rows + cols, rho)))
+    s.set_x(to_dev(x0))
+    return ref, s, to_dev(x0)
+
+
+def check(ref, s, tol=1e-8):
+    i, r = s.info(), ref.info
+    assert (i.iters, i.branch, i.backtracks, i.n_fixed, i.memory_resets) == (r.iters, r.branch, r.backtracks, r.n_fixed, r.memory_resets)
+    assert i.f == pytest.approx(r.f, rel=1e-10) and i.pg2 == pytest.approx(r.pg2, rel=tol) and i.pginf == pytest.approx(r.pginf, rel=tol)
+    assert rel_err(s.x().cpu().numpy(), ref.x) <= tol and rel_err(s.g().cpu().numpy(), ref.g) <= tol
+
+
+@pytest.mark.parametrize("rows,cols", [(2049, 64), (2060, 65), (1100, 127), (130, 1009), (2, 65537), (1, 131073)])
+@pytest.mark.parametrize("m", [2, 5, 10])
+@pytest.mark.parametrize("uniform", [True, False])
+def test_iterations(rows, cols, m, uniform):
+    ref, s, _ = problem(rows, cols, m, uniform)
+    for _ in range(m + 3):
+        ref.step()
+        s.step(False)
+    check(ref, s)
+    ref.close()
+    s.close()
+
+
+def test_rows_of_63_columns_take_two_launches():
+    ref, s, _ = problem(2081, 63, 3)
+    for _ in range(5):
+        ref.step()
+        s.step(False)
+    check(ref, s)
+    ref.close()
+    s.close()
+
+
+@pytest.mark.parametrize("lam,rho,resets", [(0.02, 3e-3, 3), (0.5, 4.0, 0)])
+def test_searches_that_fail(lam, rho, resets):
+    """Only the unit step may be taken and has to give 0.49 of the slope: pairs are dropped and the step is done again from steepest
+    descent (which the oracle does within one step), or the run ends at once."""
+    ref, s, _ = problem(700, 190, 4, rho=rho, lam=lam, max_backtracks=0, armijo_c1=0.49)
+    for _ in range(12):
+        ref.step()
+        s.step(False)
+        if s.info().status == L.RUNNING and s.info().iters < ref.info.iters:
+            s.step(False)
+        i = s.info()
+        assert (i.status, i.iters, i.memory_resets) == (ref.info.status, ref.info.iters, ref.info.memory_resets)
+        assert rel_err(s.x().cpu().numpy(), ref.x) <= 1e-8
+    assert ref.info.memory_resets == resets and (ref.info.status == oracle.LINESEARCH_FAILED) == (resets == 0)
+    ref.close()
+    s.close()
+
+
+def test_what_comes_between_two_steps():
+    """The same iterates bit for bit with nothing between the steps, with looks at the state, and with the Gram kernel on its own
+    (timed); evaluations, other start points and hooks make it compute the sums anew."""
+    ref, s, x0 = problem(400, 401, 6)
+    t = problem(400, 401, 6)[1]
+    w = problem(400, 401, 6)[1]
+    for k in range(9):
+        s.step(False)
+        t.step()
+        t.history()
+        t.x()
+    assert torch.equal(s.x(), t.x()) and torch.equal(s.g(), t.g())
+    w.enable_apass_timing(1)
+    for k in range(9):
+        if k == 5:
+            w.enable_apass_timing(0)
+        w.step(False)
+    assert rel_err(w.x().cpu().numpy(), s.x().cpu().numpy()) <= 1e-10
+    f, g = s.dbg_fg(x0)[:2]
+    for solver in (s, t, w):                             # (a hook, a run cut short, and a new start after either)
+        solver.set_x(x0)
+    t.step(False)
+    t.set_x(x0)
+    for _ in range(9):
+        ref.step()
+        for solver in (s, t):
+            solver.step(False)
+    check(ref, s)
+    assert torch.equal(s.x(), t.x())
+    for solver in (s, t, w):
+        solver.close()
+    ref.close()
+
+
+def test_refreshes():
+    ref, s, _ = problem(300, 500, 5, refresh_every=3)
+    for _ in range(11):
+        ref.step()
+        s.step(False)
+    check(ref, s)
+    ref.close()
+    s.close()

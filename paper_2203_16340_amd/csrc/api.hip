@@ -76,7 +76,7 @@ struct lbfgsb_solver {
     bool commit_needed;      // resident solver: a kernel of the multi-kernel path may have left an update pending
     // lbfgsb_solve: steps enqueued since it began, redone ones included (Opts::seq), and the next one to report
     unsigned steps_enqueued = 0, note_at = 0;
-    // the last launch that touched x, g or the pairs has left the next Gram kernel's records (launch_update_gram_gauss)
+    // the last launch that touched x, g or the pairs has left the next Gram kernel's records (launch_update_gram_gauss, _form)
     bool gram_ready = false;
     int steps_since_refresh;
     long long steps_since_set_x;
@@ -431,10 +431,15 @@ void enqueue_step(lbfgsb_solver* s) {
     // kernel's workgroups to add its partial sums themselves: they finish its work on private copies of the scalar
     // block, and the pass moves workgroup 0's copy into place (Buffers::scal_next)
     const bool open_gram = defer && gram_can_skip_close(s->dm);
+    // ... and the quadratic form's update leaves the next step's records itself, no Gram kernel at all (not in a graph, whose
+    // replays may follow anything)
+    const bool update_gram = open_gram && s->dm.kind == LBFGSB_OBJ_QP && update_gram_ok(s->dm) && !is_recording(s);
+    const bool ready = update_gram && s->gram_ready;
+    s->gram_ready = false;
     if (small) {
         launch_small_step(s->dm, s->op, s->bf, fold_rows, s->obj.extra_weight, s->stream);
     } else {
-        launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, nullptr, nullptr, open_gram ? 1 : 0);
+        if (!ready) launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, nullptr, nullptr, open_gram ? 1 : 0);
         launch_dir(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream, fold_rows, s->obj.extra_weight, defer ? 1 : 0,
                    open_gram ? 1 : 0);
     }
@@ -455,7 +460,9 @@ void enqueue_step(lbfgsb_solver* s) {
             if (s->use_fused) launch_fused(s->dm, s->ge, s->bf, a, s->stream, ts.e0, ts.e1);
             else launch_gemv(s->dm, s->ge, s->bf, a, s->stream, ts.e0, ts.e1);
         }
-        launch_update_quadratic(s->dm, s->op, s->ge, s->bf, s->obj.sign, s->stream, fold_rows, s->obj.extra_weight, fold_blocks);
+        if (update_gram) launch_update_gram_form(s->dm, s->op, s->ge, s->bf, s->obj.sign, s->stream, fold_rows, s->obj.extra_weight, fold_blocks);
+        else launch_update_quadratic(s->dm, s->op, s->ge, s->bf, s->obj.sign, s->stream, fold_rows, s->obj.extra_weight, fold_blocks);
+        s->gram_ready = update_gram;
     } else if (quad) {
         a.mode = kRowDir;
         if (s->use_fused) {

@@ -442,6 +442,24 @@ __device__ __forceinline__ DirChoice dir_choice_block(const double* __restrict__
     return c;
 }
 
+// The folded rows' coefficients weight_r (e_r . p) into coef, from their products with both candidates; returns sum weight_r (e_r . p)^2.
+__device__ __forceinline__ double fold_coefficients(const double (&tx)[2 * kFoldMax], int branch, int n_fold,
+                                                    const double* __restrict__ weight, double* coef) {
+    double total = 0.0;
+#pragma unroll
+    for (int r = 0; r < kFoldMax; ++r) {
+        double cr = 0.0;
+        if (r < n_fold) {
+            const double te = branch == 1 ? tx[2 * r] : tx[2 * r + 1];
+            const double wr = weight ? weight[r] : 1.0;
+            cr = wr * te;
+            total += wr * te * te;
+        }
+        coef[r] = cr;
+    }
+    return total;
+}
+
 // ---- helpers shared by the column-wise consumers of the A pass ---------------------------------------------
 
 constexpr int kCX = 16;             // columns per workgroup
@@ -656,9 +674,12 @@ void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, c
 void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int dbg_inputs,
                  int evaluate_stop, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, int no_close = 0);
 bool gram_can_skip_close(const Dims& dm);
-// The update of the Gaussian transport kind with the next iteration's Gram kernel in it (its records are then there: no launch_gram
-// before that iteration's direction kernel).  wt: omega . (K p), rows + cols entries.
+// The update with the next iteration's Gram kernel in it (its records are then there: no launch_gram before that iteration's
+// direction kernel).  Gaussian transport, wt: omega . (K p), rows + cols entries; the quadratic form, folded rows as for
+// launch_update_quadratic (dir_blocks: of them only).
 bool update_gram_ok(const Dims& dm);
+void launch_update_gram_form(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const double* sign, hipStream_t st,
+                             const double* fold_rows, const double* fold_weight, int dir_blocks);
 void launch_update_gram_gauss(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const double* wt, int loss_parts,
                               hipStream_t st);
 // ... what it then finds: `count` records (workgroups' sums, or those of groups of workgroups)

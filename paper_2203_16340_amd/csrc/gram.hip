@@ -614,6 +614,129 @@ void k_update_gram_gauss(Dims dm, Opts op, int loss_parts, const double* __restr
     reduce_partials<NT, false>(grampart, gram_entries(m), scal, &flag, nullptr, true, GramPlaces{m, c, base_slot});
 }
 
+// The same for the quadratic form on vectors that are not long: its update is element by element as well (the change of the gradient
+// is s.t, plus the folded rows' share).  As in k_gram everything is requested at once, here with what the update reads; the new
+// values pass through LDS.  As many records as k_gram leaves.  (The least-squares kinds add up partial columns first, 10 MB of them
+// at 20000 x 5000: few workgroups take too long over those, and the records of many keep the direction kernel, with 79 for 20
+// 11.3 us for 8.4; whole calls were no faster.)
+// n = 10 000, 10 pairs, us: update 5.1 and Gram kernel 5.3 / this 6.5; dual SVM, two outer iterations, with 10 000 points 1812 -> 1774.
+template <int M, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4)))
+void k_update_gram_form(Dims dm, Opts op, int loss_parts, const double* __restrict__ losspart, const double* __restrict__ t,
+                        const double* __restrict__ sign, const double* __restrict__ p1, const double* __restrict__ p2,
+                        const double* __restrict__ l, const double* __restrict__ u, double* __restrict__ x, double* __restrict__ g,
+                        double* __restrict__ S, double* __restrict__ Y, uint8_t* __restrict__ mask, Scal* __restrict__ scal, int n_fold,
+                        const double* __restrict__ fold_rows, const double* __restrict__ fold_weight, const double* __restrict__ dir_part,
+                        int dir_blocks, double* __restrict__ grampart) {
+    constexpr int NT = 64 * NW, KM = gram_tiles(M), kWaveLds = 16 * gram_tile_pairs(KM);
+    __shared__ __align__(16) double dyn[NW * kWaveLds];
+    __shared__ __align__(16) double fresh_s[NW * 3 * 64];
+    __shared__ double red[NW * 3];
+    __shared__ double fold_s[kFoldMax + 1];
+    __shared__ double ls_alpha;
+    __shared__ int ls_ok, ls_bt;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = dm.m;
+    const int64_t n = dm.n, nchunks = (n + 63) / 64, stride = (int64_t)gridDim.x * NW, ch0 = (int64_t)blockIdx.x * NW + wave;
+    const int i4 = lane & 3, pair_at = (lane >> 2) * 2;
+    double xe, ge, le, ue, pe1, pe2, te, se, fe[kFoldMax];
+    f64x2 v[2 * KM][2];
+    auto request = [&](int64_t ch) {
+        const int64_t e = ch * 64 + lane, ec = e < n ? e : n - 1;
+        xe = x[ec]; ge = g[ec]; le = l[ec]; ue = u[ec]; pe1 = p1[ec]; pe2 = p2[ec]; te = t[ec];
+        se = sign ? sign[ec] : 1.0;
+#pragma unroll
+        for (int r = 0; r < kFoldMax; ++r) fe[r] = r < n_fold ? fold_rows[(int64_t)r * n + ec] : 0.0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int64_t e2 = ch * 64 + 32 * h + pair_at, ec2 = e2 < n ? e2 : n - 1;
+#pragma unroll
+            for (int k = 0; k < 2 * KM; ++k) {
+                const int slot = 4 * (k < KM ? k : k - KM) + i4;
+                v[k][h] = *reinterpret_cast<const f64x2_any*>((k < KM ? Y : S) + (int64_t)(slot < m ? slot : m - 1) * n + ec2);
+            }
+        }
+    };
+    request(ch0);
+    const int status = scal->status, head = scal->head, branch = scal->branch;
+    const double gp = scal->gp, alpha_ub = scal->alpha_ub, f_old = scal->f;
+    int slot_a, slot_b;
+    gram_product_slots(tid < gram_products(m) ? tid : 0, m, slot_a, slot_b);
+    if (status != LBFGSB_RUNNING) return;
+    if (n_fold > 0 && wave == 0) {
+        // the direction kernel left only its per-workgroup sums: the folded rows' products with the chosen candidate
+        double tx[2 * kFoldMax];
+        dir_fold_from_partials(dir_part, dir_blocks, tx);
+        if (tid == 0) fold_s[kFoldMax] = fold_coefficients(tx, branch, n_fold, fold_weight, fold_s);
+    }
+    double tt = sum_all<NT>(losspart, loss_parts, red);  // (a barrier inside)
+    if (n_fold > 0) tt += fold_s[kFoldMax];
+    if (tid == 0) {
+        int ok, bt;
+        ls_alpha = armijo_quadratic(gp, tt, alpha_ub, op, ok, bt);
+        ls_ok = ok; ls_bt = bt;
+    }
+    __syncthreads();
+    const double alpha = ls_alpha;
+    const bool ok = ls_ok != 0;
+    const int newest = ok ? head : -1;
+    double *Sn = S + (int64_t)head * n, *Yn = Y + (int64_t)head * n, *keep = fresh_s + wave * (3 * 64);
+    double sum[gram_tile_pairs(KM)];
+#pragma unroll
+    for (int k = 0; k < gram_tile_pairs(KM); ++k) sum[k] = 0.0;
+    double pginf = 0.0, ynew = 0.0;
+    int nfixed = 0;
+    for (int64_t ch = ch0; ch < nchunks; ch += stride) {
+        if (ch != ch0) request(ch);
+        const int64_t e = ch * 64 + lane;
+        const bool in = e < n;
+        double w = se * te;
+#pragma unroll
+        for (int r = 0; r < kFoldMax; ++r)
+            if (r < n_fold) w = fma(fold_s[r], fe[r], w);
+        const double y = ok ? alpha * w : 0.0;
+        const double xn = ok ? clampd(fma(alpha, branch == 1 ? pe1 : pe2, xe), le, ue) : xe;
+        const double gn = ge + y, sn = xn - xe;
+        const bool at_lower = (xn <= le + op.eps) && (gn >= 0.0);
+        const bool at_upper = (xn >= ue - op.eps) && (gn <= 0.0);
+        const bool fr = !(at_lower || at_upper);
+        if (in) {
+            mask[e] = (uint8_t)fr;
+            if (ok) { Sn[e] = sn; Yn[e] = y; x[e] = xn; g[e] = gn; }
+        }
+        keep[lane] = gn; keep[64 + lane] = y; keep[128 + lane] = sn;
+        pginf = fmax(pginf, in ? fabs(xn - clampd(xn - gn, le, ue)) : 0.0);
+        ynew = fma(in ? y : 0.0, y, ynew);
+        const unsigned long long bits = __ballot(fr && in);
+        nfixed += __popcll(__ballot(in)) - __popcll(bits);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int k = 0; k < 2 * KM; ++k) {
+            const int slot = 4 * (k < KM ? k : k - KM) + i4;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (k < KM && 4 * k <= M && M < 4 * k + 4) {         // (the tile that holds g)
+                    const f64x2 q = *reinterpret_cast<const f64x2*>(keep + 32 * h + pair_at);
+                    v[k][h] = slot == M ? q : v[k][h];
+                }
+                const f64x2 q = *reinterpret_cast<const f64x2*>(keep + (k < KM ? 64 : 128) + 32 * h + pair_at);
+                v[k][h] = slot == newest ? q : v[k][h];
+            }
+        }
+        tile_products<KM>(v, bits, sum);
+        __builtin_amdgcn_wave_barrier();
+    }
+    tile_results<KM>(sum, dyn + wave * kWaveLds);
+    gram_record<NW, kWaveLds, false>(pginf, ynew, nfixed, KM, M, m, 0, 0, slot_a, slot_b, dyn, red, grampart);
+    // (no workgroup of this kernel reads the pend_* fields)
+    if (blockIdx.x == 0 && tid == 0) {
+        scal->pend_ok = ok;
+        scal->pend_bt = ls_bt;
+        scal->pend_alpha = alpha;
+        scal->pend_f = f_old + alpha * (gp + 0.5 * alpha * tt);
+        scal->pend_valid = 1;
+    }
+}
+
 // Beyond 10 pairs: v_mfma_f64_16x16x4_f64, a 16 x 4 by a 4 x 16 block (the pairs of 4 x 4 tiles would take all registers).  A lane
 // loads one element of every vector (512 contiguous bytes per load) and writes it, masked, to the wave's own part of LDS; from
 // there lane (i = lane % 16, q = lane / 16) supplies vector 16 b + i at elements 8 s + 2 q and the next, for either operand.  Result
@@ -907,9 +1030,21 @@ void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffe
                           bf.mask, bf.scal, bf.grampart, evaluate_stop, no_close);
 }
 
-// Rows of 64 columns at least (see the kernel), long vectors, and a direction kernel that does the closing step.
+// Transport: rows of 64 columns at least (see the kernel) and long vectors; the quadratic form: vectors that are not; and a direction
+// kernel that does the closing step.
 bool update_gram_ok(const Dims& dm) {
-    return dm.kind == LBFGSB_OBJ_OT_GAUSS && dm.n >= kGramLongN && dm.cols >= 64 && gram_can_skip_close(dm);
+    if (!gram_can_skip_close(dm)) return false;
+    if (dm.kind == LBFGSB_OBJ_QP) return dm.n < kGramLongN;
+    return dm.kind == LBFGSB_OBJ_OT_GAUSS && dm.n >= kGramLongN && dm.cols >= 64;
+}
+void launch_update_gram_form(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const double* sign, hipStream_t st,
+                             const double* fold_rows, const double* fold_weight, int dir_blocks) {
+    const int n_fold = fold_rows && dir_folds_extra_rows(dm) ? dm.n_extra : 0, nw = gram_waves_for(dm.n, dm.m);
+    const auto k = gram_m_for(dm.m) == 5 ? (nw == 4 ? k_update_gram_form<5, 4> : k_update_gram_form<5, 8>)
+                                         : (nw == 4 ? k_update_gram_form<10, 4> : k_update_gram_form<10, 8>);
+    hipLaunchKernelGGL(k, dim3(ge.gram_blocks), dim3(64 * nw), 0, st, dm, op, ge.loss_parts, (const double*)bf.losspart, (const double*)bf.t,
+                       sign, (const double*)bf.p1, (const double*)bf.p2, (const double*)bf.l, (const double*)bf.u, bf.x, bf.g, bf.S, bf.Y,
+                       bf.mask, bf.scal, n_fold, fold_rows, fold_weight, (const double*)bf.redpart, dir_blocks, bf.grampart);
 }
 void launch_update_gram_gauss(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const double* wt, int loss_parts,
                               hipStream_t st) {

@@ -692,21 +692,7 @@ __global__ __launch_bounds__(kBlock) void k_update_quadratic(Dims dm, Opts op, i
         if (tid < 64) {
             double tx[2 * kFoldMax];
             dir_fold_from_partials(dir_part, dir_blocks, tx);
-            if (tid == 0) {
-                double total = 0.0;
-#pragma unroll
-                for (int r = 0; r < kFoldMax; ++r) {
-                    double cr = 0.0;
-                    if (r < n_fold) {
-                        const double te = branch == 1 ? tx[2 * r] : tx[2 * r + 1];
-                        const double wr = fold_weight ? fold_weight[r] : 1.0;
-                        cr = wr * te;
-                        total += wr * te * te;
-                    }
-                    fold_s[r] = cr;
-                }
-                fold_s[kFoldMax] = total;
-            }
+            if (tid == 0) fold_s[kFoldMax] = fold_coefficients(tx, branch, n_fold, fold_weight, fold_s);
         }
         __syncthreads();
     }

@@ -78,6 +78,8 @@ struct lbfgsb_solver {
     unsigned steps_enqueued = 0, note_at = 0;
     // the last launch that touched x, g or the pairs has left the next Gram kernel's records (launch_update_gram_gauss, _form)
     bool gram_ready = false;
+    // a graph may hold steps of this solver: its replays move the state unseen, so no records are left for a next step any more
+    bool recorded = false;
     int steps_since_refresh;
     long long steps_since_set_x;
     bool x_set;
@@ -389,6 +391,8 @@ void enqueue_step(lbfgsb_solver* s) {
         return;
     }
     const bool quad = is_quadratic(s->dm.kind);
+    const bool may_leave_gram = update_gram_ok(s->dm);
+    if (may_leave_gram && !s->recorded) s->recorded = is_recording(s);
     if (quad && s->options.refresh_every > 0 && s->steps_since_refresh >= s->options.refresh_every) {
         enqueue_eval(s, 1);
         s->steps_since_refresh = 0;
@@ -400,15 +404,15 @@ void enqueue_step(lbfgsb_solver* s) {
         // (the Gram kernel ends without its closing step, which the direction kernel does, and that kernel without its own: the
         // row-sum kernel, the first to need Algorithm 2's choice, makes it from the per-workgroup sums)
         const int open_gram = gram_can_skip_close(s->dm) ? 1 : 0;
-        if (!s->gram_ready || is_recording(s)) {
+        if (!s->gram_ready || s->recorded) {
             TimedSlot ts(s, s->steps_since_set_x >= s->dm.m);
             launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, ts.e0, ts.e1, open_gram);
         }
         launch_dir(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream, nullptr, nullptr, 1, open_gram);
         const OtArgs oa = ot_args(s);
         launch_ot_sums(s->dm, s->ge, s->bf, oa, 0, 1, s->stream, s->ge.dir_blocks, s->op.eps, open_gram ? s->bf.scal_next : nullptr);
-        // (a launch of its own while the Gram kernel is being timed, and in a graph, whose replays may follow anything)
-        s->gram_ready = quad && update_gram_ok(s->dm) && !s->timing && !is_recording(s);
+        // (a launch of its own while the Gram kernel is being timed, and once steps were recorded into a graph)
+        s->gram_ready = may_leave_gram && !s->timing && !s->recorded;
         if (s->gram_ready)
             launch_update_gram_gauss(s->dm, s->op, s->ge, s->bf, s->bf.psi, s->ge.ot_row_blocks + s->ge.ot_col_blocks, s->stream);
         else if (quad) launch_ot_update_gauss(s->dm, s->op, s->ge, s->bf, oa, s->stream);
@@ -431,9 +435,9 @@ void enqueue_step(lbfgsb_solver* s) {
     // kernel's workgroups to add its partial sums themselves: they finish its work on private copies of the scalar
     // block, and the pass moves workgroup 0's copy into place (Buffers::scal_next)
     const bool open_gram = defer && gram_can_skip_close(s->dm);
-    // ... and the quadratic form's update leaves the next step's records itself, no Gram kernel at all (not in a graph, whose
-    // replays may follow anything)
-    const bool update_gram = open_gram && s->dm.kind == LBFGSB_OBJ_QP && update_gram_ok(s->dm) && !is_recording(s);
+    // ... and the quadratic form's update leaves the next step's records itself, no Gram kernel at all (not once steps were
+    // recorded into a graph)
+    const bool update_gram = open_gram && may_leave_gram && !s->recorded;
     const bool ready = update_gram && s->gram_ready;
     s->gram_ready = false;
     if (small) {

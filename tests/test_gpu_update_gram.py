@@ -123,6 +123,55 @@ def test_refreshes():
     s.close()
 
 
+@pytest.mark.parametrize("kind", ["transport", "form"])
+def test_graph_replays_between_eager_steps(kind):
+    """Replays move the state without the host's knowing: neither they nor a step after them may use sums that an earlier step
+    left.  Against a solver of eager steps only, whose sums run in another order (see the tolerance of test_quadratic_form)."""
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        if kind == "transport":
+            ref, eager, x0 = problem(500, 300, 5, refresh_every=0)
+            _, rec, _ = problem(500, 300, 5, refresh_every=0)
+            ref.close()
+        else:
+            gen = torch.Generator(device="cuda").manual_seed(5)
+            V = torch.randn(1500, 6, generator=gen, device="cuda", dtype=torch.float64)
+            K = (V @ V.T / 1500 + torch.eye(1500, device="cuda")).contiguous()
+            K, b = (0.5 * (K + K.T)).contiguous(), torch.randn(1500, generator=gen, device="cuda", dtype=torch.float64)
+            x0, one = torch.zeros_like(b), torch.ones_like(b)
+            eager, rec = (L.Solver(L.OBJ_QP, K, b, -0.5 * one, 0.7 * one, 5, sign=one, options=L.default_options(tol=0.0, refresh_every=0))
+                          for _ in range(2))
+            eager.set_x(x0)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        rec.set_x(x0)
+        rec.step(False)                                     # (leaves sums, before anything is recorded)
+        stream.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            rec.step(False)
+            rec.step(False)
+        done = 1
+        for steps in (0, 1, 2, 0, 1):
+            for _ in range(steps):
+                rec.step(False)
+            graph.replay()
+            done += steps + 2
+            while eager.info().iters < done:
+                eager.step(False)
+            assert rec.info().iters == done
+            assert rel_err(rec.x().cpu().numpy(), eager.x().cpu().numpy()) <= 1e-9
+        rec.set_x(x0)
+        graph.replay()
+        assert rec.info().iters == 2
+        rec.step(False)
+        eager.set_x(x0)
+        for _ in range(3):
+            eager.step(False)
+        assert rel_err(rec.x().cpu().numpy(), eager.x().cpu().numpy()) <= 1e-9
+        eager.close()
+        rec.close()
+
+
 # The quadratic form: ragged ends, with and without folded rows, four and eight waves (16384
 # variables), against the organisation that keeps update and Gram matrix apart.  Both sum the same numbers in other orders; ten
 # iterations carry that to 1e-9.

@@ -342,8 +342,9 @@ OtArgs ot_args(const lbfgsb_solver* s) {
     return OtArgs{s->obj.A, s->obj.b, s->obj.row_weight};
 }
 
-// f, g (and the residual / margins) from scratch at the current x.  fresh: the scalar block holds no pending update.
-void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false) {
+// f, g (and the residual / margins) from scratch at the current x.  fresh: the scalar block holds no pending update.  reopen: the
+// solver has stopped there and is to go on (not the transport kinds).
+void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false, bool reopen = false) {
     s->gram_ready = false;
     if (!fresh) launch_commit(s->dm, s->bf, s->stream);   // a pending f must not overwrite the one computed here
     if (is_transport(s->dm.kind)) {
@@ -373,7 +374,7 @@ void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false) {
     }
     if (s->dm.n_extra > 0)
         launch_extra_rows(s->dm, s->bf, s->obj.extra_rows, s->obj.extra_target, s->obj.extra_weight, 1, s->stream);
-    launch_eval_finish(s->dm, s->ge, s->bf, s->obj.b, s->obj.sign, s->stream);
+    launch_eval_finish(s->dm, s->ge, s->bf, s->obj.b, s->obj.sign, s->stream, reopen);
 }
 
 bool is_recording(const lbfgsb_solver* s) {
@@ -701,7 +702,14 @@ void enqueue_retest(lbfgsb_solver* s) {
 
 // The stopping quantity was computed from a gradient carried by recurrence: residual and gradient are recomputed from x
 // and the test is made again before convergence is declared (the status is then in the host copy).
+bool one_workgroup_judges(const lbfgsb_solver* s) { return s->dm.n <= kJudgeMax && !is_transport(s->dm.kind); }
 hipError_t confirm_convergence(lbfgsb_solver* s) {
+    if (one_workgroup_judges(s)) {
+        enqueue_eval(s, 0, true, true);
+        s->steps_since_refresh = 0;
+        launch_retest(s->dm, s->op, s->bf, s->stream, s->owns_h_scal ? s->h_scal : nullptr);
+        return s->owns_h_scal ? hipStreamSynchronize(s->stream) : read_scal(s);
+    }
     launch_reopen(s->dm, s->bf, s->stream);
     enqueue_eval(s, 0, true);          // (nothing is pending)
     s->steps_since_refresh = 0;
@@ -1363,6 +1371,10 @@ struct AlTurn {
     int64_t n_eq, cols, ld;
     double ctol;
     int max_outer, retest, fevals;
+    int judge;              // retest by this workgroup, from here on (k_retest)
+    int64_t n;
+    Opts op;
+    const double *x, *l, *u;
     const double* d;
     double *lambda, *beta, *omega, *res, *coef, *total;   // total (or null): where 0.5 sum omega res^2 is kept
     const void* Crows;
@@ -1378,13 +1390,15 @@ constexpr int64_t kShiftMax = 16 * kTurnThreads;
 template <typename T, bool SHIFT>
 __global__ __launch_bounds__(kTurnThreads) void k_al_turn(AlTurn a) {
     __shared__ double lds[2 * kTurnThreads / 64];
+    __shared__ double judge_s[3 * kTurnThreads / 64];
     __shared__ double coef_s[SHIFT ? kShiftRowsMax : 1];
     __shared__ double rho_s;
     __shared__ int go_s;
     const int tid = threadIdx.x;
-    const int status = a.retest ? a.scal->status : a.state->inner_status;
     const double rho = a.state->rho, viol_prev = a.state->violation;
     if (a.state->done) return;
+    const int status = a.judge ? judge_point<kTurnThreads>(a.n, a.op, a.x, a.g, a.l, a.u, a.scal, judge_s)
+                               : (a.retest ? a.scal->status : a.state->inner_status);
     if (a.retest && status == LBFGSB_RUNNING) {
         if (tid == 0) a.state->turned = 0;
         return;
@@ -1534,10 +1548,12 @@ size_t al_rows_extra_bytes(int64_t n_eq) {
 // solve's first step is enqueued here, nothing is waited for.
 void enqueue_turn(lbfgsb_auglag* al, bool confirm) {
     lbfgsb_solver* s = al->inner;
-    hipLaunchKernelGGL(k_al_reopen, dim3(1), dim3(64), 0, al->stream, s->bf.scal, s->dm.m, al->state);
+    // (a convergence to be confirmed: the evaluation reopens the solver and the turn makes the test itself)
+    const bool judge = confirm && s->steps_since_refresh > 0 && one_workgroup_judges(s);
+    if (!judge) hipLaunchKernelGGL(k_al_reopen, dim3(1), dim3(64), 0, al->stream, s->bf.scal, s->dm.m, al->state);
     if (s->steps_since_refresh > 0) {
-        enqueue_eval(s, 0, true);
-        if (confirm) enqueue_retest(s);
+        enqueue_eval(s, 0, true, judge);
+        if (confirm && !judge) enqueue_retest(s);
     }
     s->steps_since_refresh = 0;
     s->steps_since_set_x = 0;
@@ -1547,6 +1563,7 @@ void enqueue_turn(lbfgsb_auglag* al, bool confirm) {
     a.n_eq = al->n_eq; a.cols = stacked ? s->dm.cols : s->dm.n; a.ld = al->c_ld;
     a.ctol = al->ao.ctol; a.max_outer = al->ao.max_outer; a.retest = confirm ? 1 : 0;
     a.fevals = stacked ? 0 : 1;        // (of a stacked subproblem's start this never counted)
+    a.judge = judge ? 1 : 0; a.n = s->dm.n; a.op = s->op; a.x = s->bf.x; a.l = s->bf.l; a.u = s->bf.u;
     a.d = al->d_c; a.lambda = al->lambda; a.beta = al->beta_c; a.omega = al->omega_c; a.res = (double*)al->res_c; a.coef = al->coef;
     a.total = s->dm.n_extra > 0 ? s->bf.xres + s->dm.n_extra : nullptr;
     a.Crows = al->c_rows; a.g = s->bf.g; a.scal = s->bf.scal; a.hist = s->bf.hist; a.state = al->state; a.host = al->h_state;

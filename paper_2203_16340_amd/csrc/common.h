@@ -242,6 +242,26 @@ __device__ __forceinline__ void record_iteration(Scal* s) {
     s->hist_count += 1;
 }
 
+// What the iterate's free set says, and the stopping test (one thread).  gg = sum g[S]^2.
+__device__ __forceinline__ void stopping_test(Scal* __restrict__ scal, const Opts& op, double gg, double pginf, double nfixed) {
+    const int status = scal->status;
+    const long long iters = scal->iters;
+    const double pgn = sqrt(gg);
+    double tol_abs = scal->tol_abs;
+    scal->pg2 = pgn;
+    scal->pginf = pginf;
+    scal->n_fixed = (long long)nfixed;
+    if (!scal->tol_resolved) {
+        tol_abs = op.tol_relative ? op.tol * fmax(1.0, pgn) : op.tol;
+        scal->tol_abs = tol_abs;
+        scal->tol_resolved = 1;
+    }
+    if (status == LBFGSB_RUNNING) {
+        if (pgn <= tol_abs) scal->status = LBFGSB_CONVERGED;
+        else if (iters >= op.max_iter) scal->status = LBFGSB_MAX_ITER;
+    }
+}
+
 // Applies the pending update: accepted step (pair stored at slot `head`), or an exhausted line search
 // (clear the pair memory and retry once from the steepest-descent direction, else stop).
 // record: also write the per-iteration record (false where several workgroups apply the same update to private copies)
@@ -462,6 +482,56 @@ __device__ __forceinline__ double fold_coefficients(const double (&tx)[2 * kFold
 
 // ---- helpers shared by the column-wise consumers of the A pass ---------------------------------------------
 
+// Free set, ||g_S||, KKT residual and stopping test at (x, g) by one workgroup of NT threads, without the products a step would
+// need as well: for a gradient that has just been evaluated from scratch.  lds: 3 NT/64 doubles.  Every thread gets the status.
+// Up to here one compute unit streams the four vectors (1 MB) in less than the ~17 us of the three launches this stands for.
+constexpr int64_t kJudgeMax = 32768;
+template <int NT>
+__device__ __forceinline__ int judge_point(int64_t n, const Opts& op, const double* __restrict__ x, const double* __restrict__ g,
+                                           const double* __restrict__ l, const double* __restrict__ u, Scal* __restrict__ scal, double* lds) {
+    double s[2] = {0.0, 0.0}, most = 0.0;
+    for (int64_t i0 = threadIdx.x; i0 < n; i0 += 4 * NT) {
+        double xv[4], gv[4], lo[4], hi[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t i = i0 + k * NT, ic = i < n ? i : n - 1;
+            xv[k] = x[ic]; gv[k] = g[ic];
+            lo[k] = op.uniform_bounds ? op.lo : l[ic];
+            hi[k] = op.uniform_bounds ? op.hi : u[ic];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool in = i0 + k * NT < n;
+            const bool fixed = (xv[k] <= lo[k] + op.eps && gv[k] >= 0.0) || (xv[k] >= hi[k] - op.eps && gv[k] <= 0.0);
+            s[0] = in && !fixed ? fma(gv[k], gv[k], s[0]) : s[0];
+            s[1] += in && fixed ? 1.0 : 0.0;
+            most = in ? fmax(most, fabs(xv[k] - clampd(xv[k] - gv[k], lo[k], hi[k]))) : most;
+        }
+    }
+    most = wave_max(most);
+    s[0] = wave_sum(s[0]);
+    s[1] = wave_sum(s[1]);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        const int w = threadIdx.x >> 6;
+        lds[w] = most; lds[NT / 64 + w] = s[0]; lds[2 * (NT / 64) + w] = s[1];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double gg = lds[NT / 64], fixed = lds[2 * (NT / 64)];
+        most = lds[0];
+        for (int w = 1; w < NT / 64; ++w) {
+            most = fmax(most, lds[w]);
+            gg += lds[NT / 64 + w];
+            fixed += lds[2 * (NT / 64) + w];
+        }
+        stopping_test(scal, op, gg, most, fixed);
+        lds[0] = (double)scal->status;
+    }
+    __syncthreads();
+    return (int)lds[0];
+}
+
 constexpr int kCX = 16;             // columns per workgroup
 constexpr int kGY = kBlock / kCX;   // partial-row groups per workgroup
 
@@ -667,8 +737,9 @@ void launch_sym(const Dims& dm, const Geometry& ge, const Buffers& bf, const APa
                 hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
 void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
+// reopen: behind a convergence that is to be confirmed; launch_reopen's work is done here
 void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* lin, const double* sign,
-                        hipStream_t st);   // lin, sign: QP only (linear term b, sign vector)
+                        hipStream_t st, bool reopen = false);   // lin, sign: QP only (linear term b, sign vector)
 // no_close (see gram_can_skip_close): the kernel ends when its records of partial sums are written; the direction kernel does
 // the rest (launch_dir with open_gram)
 void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int dbg_inputs,
@@ -688,6 +759,8 @@ GramRecords gram_records(const Dims& dm, const Geometry& ge, const Buffers& bf);
 // host_scal: pinned host memory that receives the scalar block as well (null: device copy only)
 void launch_commit(const Dims& dm, const Buffers& bf, hipStream_t st, Scal* host_scal = nullptr);
 void launch_reopen(const Dims& dm, const Buffers& bf, hipStream_t st);   // applies a pending update; CONVERGED -> RUNNING
+// n <= kJudgeMax: the stopping test at an iterate whose gradient has just been evaluated; host_scal as for launch_commit
+void launch_retest(const Dims& dm, const Opts& op, const Buffers& bf, hipStream_t st, Scal* host_scal);
 // lbfgsb_create.  What the bounds are like, in pinned host memory: [0] some l_i > u_i or NaN, [1] not all pairs are the same,
 // [2] some l_i is not positive; the first pair.
 struct BoundsReport { int flag[3]; double lo, hi; };

@@ -178,22 +178,7 @@ __device__ __forceinline__ void recursion_on_coefficients(const double* G, int V
         }
     } else if (tid == 64 && evaluate_stop) {
         // the stopping test, by the second wave meanwhile
-        const int status = scal->status;
-        const long long iters = scal->iters;
-        const double pgn = sqrt(gg);
-        double tol_abs = scal->tol_abs;
-        scal->pg2 = pgn;
-        scal->pginf = pginf;
-        scal->n_fixed = (long long)nfixed;
-        if (!scal->tol_resolved) {
-            tol_abs = op.tol_relative ? op.tol * fmax(1.0, pgn) : op.tol;
-            scal->tol_abs = tol_abs;
-            scal->tol_resolved = 1;
-        }
-        if (status == LBFGSB_RUNNING) {
-            if (pgn <= tol_abs) scal->status = LBFGSB_CONVERGED;
-            else if (iters >= op.max_iter) scal->status = LBFGSB_MAX_ITER;
-        }
+        stopping_test(scal, op, gg, pginf, nfixed);
     }
 }
 

@@ -584,11 +584,11 @@ __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, in
                                                         Scal* __restrict__ scal, double* __restrict__ redpart,
                                                         const double* __restrict__ lin, const double* __restrict__ sign,
                                                         const double* __restrict__ wextra,
-                                                        const double* __restrict__ xres) {
+                                                        const double* __restrict__ xres, int reopen) {
     __shared__ double lds[kBlock];
     __shared__ double red[kWaves];
     __shared__ int flag;
-    if (scal->status != LBFGSB_RUNNING) return;
+    if (!reopen && scal->status != LBFGSB_RUNNING) return;
     const int tid = threadIdx.x;
     const bool shares = dm.kind != LBFGSB_OBJ_LSQ;
     const int nreg = shares ? ((int)gridDim.x < kRegBlocks ? (int)gridDim.x : kRegBlocks) : 1;
@@ -640,18 +640,22 @@ __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, in
         else if (dm.kind == LBFGSB_OBJ_LOGISTIC_L2) f += 0.5 * dm.mu * reg[0];
         else if (dm.kind == LBFGSB_OBJ_QP) f += reg[0];
         if (xres) f += xres[dm.n_extra];   // 0.5 sum weight * residual^2 of the extra rows
+        if (reopen) {
+            apply_pending(scal, dm.m);
+            if (scal->status == LBFGSB_CONVERGED) scal->status = LBFGSB_RUNNING;
+        }
         scal->f = f;
         scal->fevals += 1;
     }
 }
 
 void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* lin, const double* sign,
-                        hipStream_t st) {
+                        hipStream_t st, bool reopen) {
     const bool qp = dm.kind == LBFGSB_OBJ_QP;
     hipLaunchKernelGGL(k_eval_finish, dim3(ge.fin_blocks), dim3(kBlock), 0, st, dm, qp ? 1 : ge.w_parts, ge.loss_parts,
                        qp ? (const double*)bf.row : (const double*)bf.wpart, bf.losspart, bf.x, bf.g, bf.scal, bf.redpart,
                        lin, sign, dm.n_extra > 0 ? (const double*)bf.wextra : nullptr,
-                       dm.n_extra > 0 ? (const double*)bf.xres : nullptr);
+                       dm.n_extra > 0 ? (const double*)bf.xres : nullptr, reopen ? 1 : 0);
 }
 
 // ---- quadratic objectives: closed-form Armijo search, then the update ---------------------------------------

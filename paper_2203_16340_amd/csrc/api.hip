@@ -343,14 +343,15 @@ OtArgs ot_args(const lbfgsb_solver* s) {
 }
 
 // f, g (and the residual / margins) from scratch at the current x.  fresh: the scalar block holds no pending update.  reopen: the
-// solver has stopped there and is to go on (not the transport kinds).
-void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false, bool reopen = false) {
+// solver has stopped there and is to go on (not the transport kinds).  host_flag: whether the gradient is finite is reported there.
+void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false, bool reopen = false, int* host_flag = nullptr) {
     s->gram_ready = false;
     if (!fresh) launch_commit(s->dm, s->bf, s->stream);   // a pending f must not overwrite the one computed here
     if (is_transport(s->dm.kind)) {
         const OtArgs oa = ot_args(s);
         launch_ot_sums(s->dm, s->ge, s->bf, oa, 1, check_status, s->stream);
         launch_ot_eval_finish(s->dm, s->ge, s->bf, oa, s->stream);
+        if (host_flag) launch_check_finite(s->dm, s->bf.g, host_flag, s->stream);
         return;
     }
     APassArgs a = base_args(s);
@@ -373,8 +374,9 @@ void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false, bool r
         { TimedSlot ts(s); launch_gemvt_from(s->dm, s->ge, s->bf, s->obj.A, s->bf.psi, check_status, s->stream, ts.e0, ts.e1); }
     }
     if (s->dm.n_extra > 0)
-        launch_extra_rows(s->dm, s->bf, s->obj.extra_rows, s->obj.extra_target, s->obj.extra_weight, 1, s->stream);
-    launch_eval_finish(s->dm, s->ge, s->bf, s->obj.b, s->obj.sign, s->stream, reopen);
+        launch_extra_rows(s->dm, s->bf, s->obj.extra_rows, s->obj.extra_target, s->obj.extra_weight,
+                          host_flag ? 2 : 1, s->stream);
+    launch_eval_finish(s->dm, s->ge, s->bf, s->obj.b, s->obj.sign, s->stream, reopen, host_flag);
 }
 
 bool is_recording(const lbfgsb_solver* s) {
@@ -562,24 +564,37 @@ int report_infeasible(lbfgsb_solver* s, const double* x0) {
 // trusted: x0 is the solver's own iterate, or has been checked by the caller: only f is checked for finiteness
 int set_x_impl(lbfgsb_solver* s, const double* x0, bool trusted) {
     volatile int* flag = s->h_flag;
+    const bool one = !trusted && s->owns_h_scal && s->dm.n <= kStartOneMax && !s->timing;
     if (!trusted) {
         // nothing of the solver's state changes before this has been found to be all right
-        *flag = 0;
-        launch_check_box(s->dm, s->op, s->bf, x0, s->h_flag, s->stream);
-        HIP_TRY(hipStreamSynchronize(s->stream));
-        HIP_TRY(hipGetLastError());
-        if (*flag) return report_infeasible(s, x0);
+        flag[0] = flag[1] = 0;
+        if (one) {
+            launch_check_start(s->dm, s->op, s->bf, x0, s->h_flag, s->stream);
+        } else {
+            launch_check_box(s->dm, s->op, s->bf, x0, s->h_flag, s->stream);
+            HIP_TRY(hipStreamSynchronize(s->stream));
+            HIP_TRY(hipGetLastError());
+            if (flag[0]) return report_infeasible(s, x0);
+        }
     }
-    launch_start(s->dm, s->bf, x0, s->stream);
-    enqueue_eval(s, 0, true);
+    if (!one) launch_start(s->dm, s->bf, x0, s->stream);
+    const bool gram_ready = s->gram_ready, commit_needed = s->commit_needed;
+    const int short_steps_unseen = s->short_steps_unseen;
+    enqueue_eval(s, one ? 1 : 0, true, false, trusted ? nullptr : s->h_flag);
+    s->short_steps_unseen = 0;
+    HIP_TRY(read_scal(s));
+    HIP_TRY(hipGetLastError());
+    if (one && flag[0]) {
+        s->gram_ready = gram_ready;
+        s->commit_needed = commit_needed;
+        s->short_steps_unseen = short_steps_unseen;
+        launch_admit(s->bf, s->stream);
+        return report_infeasible(s, x0);
+    }
     s->steps_since_refresh = 0;
     s->steps_since_set_x = 0;
     s->logi_full_left = 0;
-    s->short_steps_unseen = 0;
-    if (!trusted) launch_check_finite(s->dm, s->bf.g, s->h_flag, s->stream);
-    HIP_TRY(read_scal(s));
-    HIP_TRY(hipGetLastError());
-    if (!std::isfinite(s->h_scal->f) || (!trusted && *flag)) {
+    if (!std::isfinite(s->h_scal->f) || (!trusted && flag[1])) {
         s->x_set = false;
         return fail(LBFGSB_E_NONFINITE, "f or grad f is not finite at x0");
     }

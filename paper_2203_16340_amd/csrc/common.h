@@ -76,6 +76,9 @@ struct Scal {
 // and the host finishes the iteration with the missing launches when it next looks at the scalar block.  Never
 // reported to the caller.
 constexpr int kStatusBail = 64;
+// Added to the status while a start point that was refused is on its way to the host: the evaluation enqueued behind the check does
+// nothing, and the host takes it away again.
+constexpr int kStatusRefused = 128;
 
 struct Dims {
     int64_t n, rows, cols, ld;
@@ -739,7 +742,7 @@ void launch_sym(const Dims& dm, const Geometry& ge, const Buffers& bf, const APa
 void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 // reopen: behind a convergence that is to be confirmed; launch_reopen's work is done here
 void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* lin, const double* sign,
-                        hipStream_t st, bool reopen = false);   // lin, sign: QP only (linear term b, sign vector)
+                        hipStream_t st, bool reopen = false, int* host_flag = nullptr);   // lin, sign: QP only (linear term b, sign vector)
 // no_close (see gram_can_skip_close): the kernel ends when its records of partial sums are written; the direction kernel does
 // the rest (launch_dir with open_gram)
 void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int dbg_inputs,
@@ -765,9 +768,13 @@ void launch_retest(const Dims& dm, const Opts& op, const Buffers& bf, hipStream_
 // [2] some l_i is not positive; the first pair.
 struct BoundsReport { int flag[3]; double lo, hi; };
 void launch_check_bounds(const Dims& dm, const double* l, const double* u, BoundsReport* host, hipStream_t st);
-// lbfgsb_set_x.  launch_check_box: *host_flag (pinned) becomes 1 if some x0_i is outside its bounds or NaN;
-// launch_start: x = x0 (unless they are the same array) and a fresh scalar block; launch_check_finite: *host_flag becomes
-// 1 if some g_i is not finite.
+// lbfgsb_set_x.  launch_check_box: host_flag[0] (pinned) becomes 1 if some x0_i is outside its bounds or NaN;
+// launch_start: x = x0 (unless they are the same array) and a fresh scalar block; launch_check_finite: host_flag[1] becomes
+// 1 if some g_i is not finite (launch_eval_finish can do that).  launch_check_start, n <= kStartOneMax: launch_check_box and, if it
+// finds nothing, launch_start; else the status is kStatusRefused higher until launch_admit.
+constexpr int64_t kStartOneMax = 32768;
+void launch_check_start(const Dims& dm, const Opts& op, const Buffers& bf, const double* x0, int* host_flag, hipStream_t st);
+void launch_admit(const Buffers& bf, hipStream_t st);
 void launch_check_box(const Dims& dm, const Opts& op, const Buffers& bf, const double* x0, int* host_flag, hipStream_t st);
 void launch_start(const Dims& dm, const Buffers& bf, const double* x0, hipStream_t st);
 void launch_check_finite(const Dims& dm, const double* g, int* host_flag, hipStream_t st);
@@ -787,7 +794,8 @@ void launch_dir(const Dims& dm, const Opts& op, const Geometry& ge, const Buffer
 void launch_update_quadratic(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, const double* sign,
                              hipStream_t st, const double* fold_rows = nullptr, const double* fold_weight = nullptr,
                              int dir_blocks = 0);
-// extra rows: e_r.z for z = x (eval != 0: residuals against the targets) or the selected direction (eval == 0)
+// extra rows: e_r.z for z = x (eval != 0: residuals against the targets) or the selected direction (eval == 0); eval = 2: unless the
+// start point was refused
 void launch_extra_rows(const Dims& dm, const Buffers& bf, const double* rows, const double* target, const double* weight,
                        int eval, hipStream_t st);
 // spec != 0: the A pass already holds X^T psi of the first trial step (recorded in Scal::spec_ok if that step is accepted)

@@ -1067,6 +1067,7 @@ __device__ __forceinline__ void copy_scal(const Scal* scal, Scal* __restrict__ h
         reinterpret_cast<uint64_t*>(host_scal)[k] = reinterpret_cast<const uint64_t*>(scal)[k];
 }
 __global__ __launch_bounds__(64) void k_commit(Scal* scal, int m, Scal* __restrict__ host_scal) {
+    if (scal->status >= kStatusRefused) return;
     if (threadIdx.x == 0) apply_pending(scal, m);
     if (!host_scal) return;
     __threadfence_block();           // thread 0's stores, before the wave reads the block

@@ -26,15 +26,24 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t st) {
 // (32 MB at a million variables: 3 ms of a 7 ms call, 60 of 620 us at a hundred) to look at them itself.  Each kernel is
 // one pass over its vectors; only a violation writes anything, a flag in pinned host memory.
 
-__global__ __launch_bounds__(kBlock) void k_check_box(int64_t n, Opts op, const double* __restrict__ x0,
-                                                      const double* __restrict__ l, const double* __restrict__ u,
-                                                      int* __restrict__ host_flag) {
+__device__ __forceinline__ void fresh_block(Scal* scal, lbfgsb_iter_record* hist, int threads) {
+    for (int k = threadIdx.x; k < (int)(sizeof(Scal) / 4); k += threads) reinterpret_cast<int*>(scal)[k] = 0;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        scal->status = LBFGSB_RUNNING;
+        scal->alpha_ub = 1.0;
+        scal->hist = hist;
+    }
+}
+// some x0_i outside its bounds or NaN, among those of this thread
+__device__ __forceinline__ bool outside_box(int64_t n, const Opts& op, const double* __restrict__ x0, const double* __restrict__ l,
+                                            const double* __restrict__ u, int64_t first, int64_t step) {
     bool bad = false;
-    for (int64_t i0 = (int64_t)blockIdx.x * kBlock + threadIdx.x; i0 < n; i0 += 4 * (int64_t)gridDim.x * kBlock) {
+    for (int64_t i0 = first; i0 < n; i0 += 4 * step) {
         double v[4], lo[4], hi[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int64_t i = i0 + k * (int64_t)gridDim.x * kBlock, ic = i < n ? i : n - 1;
+            const int64_t i = i0 + k * step, ic = i < n ? i : n - 1;
             v[k] = x0[ic];
             lo[k] = op.uniform_bounds ? op.lo : l[ic];
             hi[k] = op.uniform_bounds ? op.hi : u[ic];
@@ -42,6 +51,12 @@ __global__ __launch_bounds__(kBlock) void k_check_box(int64_t n, Opts op, const 
 #pragma unroll
         for (int k = 0; k < 4; ++k) bad = bad || !(v[k] >= lo[k]) || !(v[k] <= hi[k]);
     }
+    return bad;
+}
+__global__ __launch_bounds__(kBlock) void k_check_box(int64_t n, Opts op, const double* __restrict__ x0,
+                                                      const double* __restrict__ l, const double* __restrict__ u,
+                                                      int* __restrict__ host_flag) {
+    const bool bad = outside_box(n, op, x0, l, u, (int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock);
     if (bad) *host_flag = 1;
 }
 __global__ __launch_bounds__(kBlock) void k_check_bounds(int64_t n, const double* __restrict__ l, const double* __restrict__ u,
@@ -80,20 +95,34 @@ __global__ __launch_bounds__(kBlock) void k_check_finite(int64_t n, const double
 #pragma unroll
         for (int k = 0; k < 4; ++k) bad = bad || !isfinite(v[k]);
     }
-    if (bad) *host_flag = 1;
+    if (bad) host_flag[1] = 1;
 }
 __global__ __launch_bounds__(kBlock) void k_start(int64_t n, const double* x0, double* x, Scal* scal, lbfgsb_iter_record* hist) {
-    if (blockIdx.x == 0) {
-        for (int k = threadIdx.x; k < (int)(sizeof(Scal) / 4); k += kBlock) reinterpret_cast<int*>(scal)[k] = 0;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            scal->status = LBFGSB_RUNNING;
-            scal->alpha_ub = 1.0;
-            scal->hist = hist;
-        }
-    }
+    if (blockIdx.x == 0) fresh_block(scal, hist, kBlock);
     if (x0 == x) return;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) x[i] = x0[i];
+}
+// Check and start in one launch, by one workgroup, and the evaluation is enqueued behind it without the host looking in between (a
+// trip of ~12 us, and a launch of 4; another went with k_check_finite, whose test k_eval_finish makes).  Beyond kStartOneMax, where one
+// compute unit takes ~8 us for the three vectors, the host's trip is under 1 % of what follows.  Whole calls, us: 200 x 100 402 -> 391,
+// 3001 x 301 315 -> 302, 20000 x 5000 2750 -> 2737.
+constexpr int kCheckStartThreads = 1024;
+__global__ __launch_bounds__(kCheckStartThreads) void k_check_start(int64_t n, Opts op, const double* x0, const double* __restrict__ l,
+                                                                    const double* __restrict__ u, double* x, Scal* scal,
+                                                                    lbfgsb_iter_record* hist, int* __restrict__ host_flag) {
+    if (__syncthreads_or(outside_box(n, op, x0, l, u, threadIdx.x, kCheckStartThreads))) {
+        if (threadIdx.x == 0) {
+            scal->status += kStatusRefused;
+            host_flag[0] = 1;
+        }
+        return;
+    }
+    fresh_block(scal, hist, kCheckStartThreads);
+    if (x0 == x) return;
+    for (int64_t i = threadIdx.x; i < n; i += kCheckStartThreads) x[i] = x0[i];
+}
+__global__ void k_admit(Scal* scal) {
+    if (threadIdx.x == 0) scal->status -= kStatusRefused;
 }
 static int start_blocks(int64_t n) {
     const int64_t b = (n + 4 * kBlock - 1) / (4 * kBlock);
@@ -109,6 +138,11 @@ void launch_check_box(const Dims& dm, const Opts& op, const Buffers& bf, const d
 void launch_start(const Dims& dm, const Buffers& bf, const double* x0, hipStream_t st) {
     hipLaunchKernelGGL(k_start, dim3(start_blocks(dm.n)), dim3(kBlock), 0, st, dm.n, x0, bf.x, bf.scal, bf.hist);
 }
+void launch_check_start(const Dims& dm, const Opts& op, const Buffers& bf, const double* x0, int* host_flag, hipStream_t st) {
+    hipLaunchKernelGGL(k_check_start, dim3(1), dim3(kCheckStartThreads), 0, st, dm.n, op, x0, (const double*)bf.l, (const double*)bf.u,
+                       bf.x, bf.scal, bf.hist, host_flag);
+}
+void launch_admit(const Buffers& bf, hipStream_t st) { hipLaunchKernelGGL(k_admit, dim3(1), dim3(64), 0, st, bf.scal); }
 void launch_check_finite(const Dims& dm, const double* g, int* host_flag, hipStream_t st) {
     hipLaunchKernelGGL(k_check_finite, dim3(start_blocks(dm.n)), dim3(kBlock), 0, st, dm.n, g, host_flag);
 }
@@ -584,7 +618,7 @@ __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, in
                                                         Scal* __restrict__ scal, double* __restrict__ redpart,
                                                         const double* __restrict__ lin, const double* __restrict__ sign,
                                                         const double* __restrict__ wextra,
-                                                        const double* __restrict__ xres, int reopen) {
+                                                        const double* __restrict__ xres, int reopen, int* __restrict__ host_flag) {
     __shared__ double lds[kBlock];
     __shared__ double red[kWaves];
     __shared__ int flag;
@@ -615,17 +649,22 @@ __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, in
         const double w = column_sum(wpart, w_parts, dm.cols, c, lds);
         if (tid < kCX && c < dm.cols) {
             // wextra: the extra rows' contribution E^T (weight * residual), one entry per variable
+            double gc;
             if (dm.kind == LBFGSB_OBJ_LSQ) {
-                g[c] = w + (wextra ? wextra[c] : 0.0);
+                gc = w + (wextra ? wextra[c] : 0.0);
             } else if (dm.kind == LBFGSB_OBJ_LSQ_L1SPLIT) {
-                g[c] = w + dm.lambda + (wextra ? wextra[c] : 0.0);
-                g[c + dm.cols] = -w + dm.lambda + (wextra ? wextra[c + dm.cols] : 0.0);
+                gc = w + dm.lambda + (wextra ? wextra[c] : 0.0);
+                const double gm = -w + dm.lambda + (wextra ? wextra[c + dm.cols] : 0.0);
+                g[c + dm.cols] = gm;
+                if (host_flag && !isfinite(gm)) host_flag[1] = 1;
             } else if (dm.kind == LBFGSB_OBJ_QP) {
                 // w = (A (s.x))_c (a single "partial": the row kernel's output); g = s w + b
-                g[c] = (sign ? sign[c] : 1.0) * w + lin[c] + (wextra ? wextra[c] : 0.0);
+                gc = (sign ? sign[c] : 1.0) * w + lin[c] + (wextra ? wextra[c] : 0.0);
             } else {
-                g[c] = fma(dm.mu, x[c], w);
+                gc = fma(dm.mu, x[c], w);
             }
+            g[c] = gc;
+            if (host_flag && !isfinite(gc)) host_flag[1] = 1;
         }
     }
     if (!reg_wg || (shares && !arrive_is_last(&scal->counters[kCntEvalFinish], &flag, (unsigned)nreg))) return;
@@ -650,12 +689,12 @@ __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, in
 }
 
 void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* lin, const double* sign,
-                        hipStream_t st, bool reopen) {
+                        hipStream_t st, bool reopen, int* host_flag) {
     const bool qp = dm.kind == LBFGSB_OBJ_QP;
     hipLaunchKernelGGL(k_eval_finish, dim3(ge.fin_blocks), dim3(kBlock), 0, st, dm, qp ? 1 : ge.w_parts, ge.loss_parts,
                        qp ? (const double*)bf.row : (const double*)bf.wpart, bf.losspart, bf.x, bf.g, bf.scal, bf.redpart,
                        lin, sign, dm.n_extra > 0 ? (const double*)bf.wextra : nullptr,
-                       dm.n_extra > 0 ? (const double*)bf.xres : nullptr, reopen ? 1 : 0);
+                       dm.n_extra > 0 ? (const double*)bf.xres : nullptr, reopen ? 1 : 0, host_flag);
 }
 
 // ---- quadratic objectives: closed-form Armijo search, then the update ---------------------------------------
@@ -775,7 +814,7 @@ __global__ __launch_bounds__(kBlock) void k_extra_rows(Dims dm, const double* __
                                                        double* __restrict__ wextra, double* __restrict__ xres) {
     __shared__ double red[kWaves];
     __shared__ double coef[kMaxExtra];
-    if (!eval && scal->status != LBFGSB_RUNNING) return;
+    if (eval != 1 && scal->status != LBFGSB_RUNNING) return;
     const int tid = threadIdx.x;
     const double* z = eval ? x : (scal->branch == 1 ? p1 : p2);
     double total = 0.0;

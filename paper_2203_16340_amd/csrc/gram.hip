@@ -70,7 +70,7 @@ __device__ __forceinline__ bool reduce_partials(double* __restrict__ grampart, i
         // few workgroups: one level, the last one to finish adds all partials in index order
         if (!arrive_is_last(&scal->gram_cnt[kGramGroups], flag, (unsigned)nwg)) return false;
         if constexpr (HELD) gram_sum_held<NT>(grampart, NE, nwg, tot, places);
-        else gram_sum_partials_flat<NT, true>(grampart, NE, nwg, tot);
+        else gram_sum_partials_flat<NT>(grampart, NE, nwg, tot);
         __syncthreads();
         return true;
     }

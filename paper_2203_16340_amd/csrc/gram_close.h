@@ -57,8 +57,8 @@ struct GramPlaces {
 // Adds the records of `nwg` workgroups (NE doubles each; entry 0 is a maximum, the others are sums) in workgroup order into
 // tot[0 .. NE): thread idx takes entry idx, BATCH records at a time with every load of a batch issued before the first is used and
 // none of them under a test (past the last record: the last one again, not added).
-// Called by all NT threads; no barrier inside.  SAME: the records are of this launch (published), else of an earlier one.
-template <int NT, bool SAME, int BATCH>
+// Called by all NT threads; no barrier inside.  The records are of this launch (published).
+template <int NT, int BATCH>
 __device__ __forceinline__ void gram_sum_batches(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
     for (int idx = threadIdx.x; idx < NE; idx += NT) {
         double sum = 0.0, most = -INFINITY;
@@ -67,7 +67,7 @@ __device__ __forceinline__ void gram_sum_batches(const double* __restrict__ gram
 #pragma unroll
             for (int k = 0; k < BATCH; ++k) {
                 const double* r = grampart + (int64_t)(k0 + k < nwg ? k0 + k : nwg - 1) * NE + idx;
-                v[k] = SAME ? observe(r) : *r;
+                v[k] = observe(r);
             }
 #pragma unroll
             for (int k = 0; k < BATCH; ++k) {
@@ -78,12 +78,39 @@ __device__ __forceinline__ void gram_sum_batches(const double* __restrict__ gram
         tot[idx] = idx == 0 ? most : sum;
     }
 }
-template <int NT, bool SAME>
+template <int NT>
 __device__ __forceinline__ void gram_sum_partials_flat(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
     // (the trips of different batches to memory follow one another: a batch for all where that is not too many loads)
-    if (nwg <= 16) gram_sum_batches<NT, SAME, 16>(grampart, NE, nwg, tot);
-    else if (nwg <= 32) gram_sum_batches<NT, SAME, 32>(grampart, NE, nwg, tot);
-    else gram_sum_batches<NT, SAME, 64>(grampart, NE, nwg, tot);
+    if (nwg <= 16) gram_sum_batches<NT, 16>(grampart, NE, nwg, tot);
+    else if (nwg <= 32) gram_sum_batches<NT, 32>(grampart, NE, nwg, tot);
+    else gram_sum_batches<NT, 64>(grampart, NE, nwg, tot);
+}
+
+// For the direction kernel: records of an earlier launch with no more entries than threads, a thread an entry and no loop over them
+// (0.4 us of 8.5 there); waves without an entry ask for nothing.
+template <int NT, int BATCH>
+__device__ __forceinline__ void gram_sum_entry_batches(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
+    const int idx = threadIdx.x, at = idx < NE ? idx : NE - 1;
+    if (__builtin_amdgcn_readfirstlane(idx & ~63) >= NE) return;
+    double sum = 0.0, most = -INFINITY;
+    for (int k0 = 0; k0 < nwg; k0 += BATCH) {
+        double v[BATCH];
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) v[k] = grampart[(int64_t)(k0 + k < nwg ? k0 + k : nwg - 1) * NE + at];
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) {
+            sum += k0 + k < nwg ? v[k] : 0.0;
+            most = fmax(most, v[k]);
+        }
+    }
+    if (idx < NE) tot[idx] = idx == 0 ? most : sum;
+}
+template <int NT>
+__device__ __forceinline__ void gram_sum_entries(const double* __restrict__ grampart, int NE, int nwg, double* tot) {
+    static_assert(gram_entries(kGramOpenM) <= NT, "one entry a thread");
+    if (nwg <= 16) gram_sum_entry_batches<NT, 16>(grampart, NE, nwg, tot);
+    else if (nwg <= 32) gram_sum_entry_batches<NT, 32>(grampart, NE, nwg, tot);
+    else gram_sum_entry_batches<NT, 64>(grampart, NE, nwg, tot);
 }
 
 // The same beyond 10 pairs, where a record has more entries than the workgroup threads: only those that the pairs held need, entry

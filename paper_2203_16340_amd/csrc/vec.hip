@@ -177,6 +177,35 @@ __device__ __forceinline__ void dir_finish(double (&s)[6], double ub, double eps
                                            double* __restrict__ redpart, double* red, int* flag_p,
                                            double (&sx)[2 * kFoldMax], const FoldArgs& fold, int defer_choice = 0) {
     const int tid = threadIdx.x;
+    if (defer_choice) {
+        // the consumer of the direction chooses between the candidates from the records: one exchange and one thread an entry
+        const int wave = tid >> 6;
+        ub = wave_min(ub);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) s[k] = wave_sum(s[k]);
+        if (fold.n_fold > 0) {
+#pragma unroll
+            for (int k = 0; k < 2 * kFoldMax; ++k) sx[k] = wave_sum(sx[k]);
+        }
+        if ((tid & 63) == 0) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) red[wave * kDirRed + k] = s[k];
+            red[wave * kDirRed + 6] = ub;
+#pragma unroll
+            for (int k = 0; k < 2 * kFoldMax; ++k) red[wave * kDirRed + 8 + k] = sx[k];
+        }
+        __syncthreads();
+        if (tid < kDirRed && tid != 7) {
+            double sum = 0.0, least = red[tid];
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                sum += red[w * kDirRed + tid];
+                least = fmin(least, red[w * kDirRed + tid]);
+            }
+            publish(redpart + (int64_t)blockIdx.x * kDirRed + tid, tid == 6 ? least : sum);
+        }
+        return;
+    }
     block_sum<6, kWaves>(s, red);
     if (fold.n_fold > 0) block_sum<2 * kFoldMax, kWaves>(sx, red);
     double mn = wave_min(ub);
@@ -191,7 +220,6 @@ __device__ __forceinline__ void dir_finish(double (&s)[6], double ub, double eps
         publish(part + 6, mn);
         for (int k = 0; k < 2 * kFoldMax; ++k) publish(part + 8 + k, sx[k]);
     }
-    if (defer_choice) return;   // the consumer of the direction chooses between the candidates from the records
     if (!arrive_is_last(&scal->counters[kCntDir], flag_p)) return;
     double tx[2 * kFoldMax];
     {
@@ -256,6 +284,12 @@ __device__ __forceinline__ void dir_finish(double (&s)[6], double ub, double eps
 // workgroup, so the same bits -- and takes the coefficients from its copy.  Workgroup 0 leaves its copy in scal_next for the
 // pass (nothing in this kernel reads that); the scalar block itself is only read here.  What this saves is the Gram kernel's
 // arrival (an atomic, a dependent round of loads) and this kernel's own dependent reads of the status word and the coefficients.
+// What bounds it is the chain: 18 000 cycles, of them 6500 for the records, 3000 until the pair memory had been asked for, 3600 for the
+// closing step, 2500 for the element and 2500 for the sums, when divisions found the ring's slots, the vectors' addresses went through
+// LDS, an element took two quotients and 21 dependent additions, and the sums five barriers.  With comparisons, vectors by slot, one
+// quotient, two chains and one exchange, per iteration, us: 4000 x 1500 36.9 -> 35.0, 8000 x 2000 47.5 -> 46.0, 20000 x 5000 1.3 less,
+// transport of 200 x 200 1483 -> 1450 a run; from 30 000 variables on no less.  (All 20 slots' vectors asked for behind the records,
+// before it is known which hold pairs: 0 to 2 % slower throughout.)
 template <bool CLOSE>
 __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const double* __restrict__ x,
                                                 const double* __restrict__ g, const double* __restrict__ l,
@@ -265,9 +299,9 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
                                                 double* __restrict__ p1, double* __restrict__ p2,
                                                 double* __restrict__ redpart, int d_given, int store_d, FoldArgs fold,
                                                 int defer_choice, GramRecords records, Scal* __restrict__ scal_next) {
-    __shared__ double delta_s[kMaxV + 8];
+    __shared__ double delta_s[kMaxV + 9];
     __shared__ const double* vecp[kMaxV + 8];
-    __shared__ double red[kWaves * 7];
+    __shared__ double red[kWaves * kDirRed];
     __shared__ int flag;
     const int tid = threadIdx.x;
     // What depends on nothing the scalar block says is requested together with it: the coefficients (masked by the
@@ -277,10 +311,13 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
     double xn = x[e_safe], gn = g[e_safe], ln = l[e_safe], un = u[e_safe];
     uint8_t mkn = mask[e_safe];
     int c, head;
-    constexpr int kDirPre = CLOSE ? 2 * kGramOpenM + 1 : 1;
-    double vpre[kDirPre];
+    // the first element's entries of the pair memory, slot by slot
+    constexpr int kPre = CLOSE ? kGramOpenM : 1;
+    double vy[kPre], vs[kPre];
 #pragma unroll
-    for (int j = 0; j < kDirPre; ++j) vpre[j] = 0.0;
+    for (int k = 0; k < kPre; ++k) vy[k] = vs[k] = 0.0;
+    __shared__ double coef_s[2 * kPre];
+    const bool more = !CLOSE || (int64_t)gridDim.x * kBlock < n;   // (some thread has a second element)
     if constexpr (CLOSE) {
         __shared__ Scal sc;
         __shared__ double Gs[(2 * kGramOpenM + 2) * (2 * kGramOpenM + 2)];
@@ -292,27 +329,32 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
         int pa, pb;                                                // (worked out while the records are on their way)
         gram_product_slots(tid < gram_products(m) ? tid : 0, m, pa, pb);
         asm volatile("" : "+v"(pa), "+v"(pb));
-        gram_sum_partials_flat<kBlock, false>(records.part, gram_entries(m), records.count, tot);
+        gram_sum_entries<kBlock>(records.part, gram_entries(m), records.count, tot);
         __syncthreads();
         if (sc.status != LBFGSB_RUNNING) {
             // (the pass reads its status word from scal_next: it must not find an older one there)
             if (blockIdx.x == 0 && tid == 0) { scal_next->status = sc.status; scal_next->fresh = 0; note_progress(op, sc.status); }
             return;
         }
-        head = sc.head; c = sc.count;
-        if (sc.pend_valid) {                                       // same rule as effective_ring()
-            if (sc.pend_ok) { head = (head + 1) % m; c = c < m ? c + 1 : m; }
+        head = __builtin_amdgcn_readfirstlane(sc.head); c = __builtin_amdgcn_readfirstlane(sc.count);
+        if (__builtin_amdgcn_readfirstlane(sc.pend_valid)) {       // same rule as effective_ring()
+            if (__builtin_amdgcn_readfirstlane(sc.pend_ok)) { head = head + 1 < m ? head + 1 : 0; c = c < m ? c + 1 : m; }
             else c = 0;
         }
-        const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;
-        const double yn_old = prefetch_ynorm2(&sc, c, head, m);
-        // the first element's vectors are requested now (which ring slots hold them is known), so that their trip to
-        // memory runs under the closing step instead of behind it
-        if (tid < kMaxV + 8) vecp[tid] = tid < 2 * c + 1 ? ring_vec(tid, c, head, m, n, S, Y, g) : g;
-        __syncthreads();
-        if (!d_given && mkn && e_first < n) {
+        const int base_slot = head - c < 0 ? head - c + m : head - c;
+        // (as prefetch_ynorm2)
+        double yn_old = 1.0;
+        if (tid < c) yn_old = sc.ynorm2[base_slot + tid < m ? base_slot + tid : base_slot + tid - m];
+        // the first element's entries are requested now (which slots hold pairs is known), so that their trip to memory runs under the
+        // closing step instead of behind it
+        if (mkn) {
 #pragma unroll
-            for (int j = 0; j < kDirPre; ++j) vpre[j] = vecp[j][e_first];   // (past the last vector: g, with a coefficient of zero)
+            for (int q = 0; q < kPre; ++q) {
+                const int age = q >= base_slot ? q - base_slot : q - base_slot + m;
+                if (q >= m || age >= c) continue;                  // (uniform)
+                vy[q] = (Y + (int64_t)q * n)[(unsigned)e_safe];
+                vs[q] = (S + (int64_t)q * n)[(unsigned)e_safe];
+            }
         }
         __syncthreads();                                           // every thread has read the ring before it changes
         gram_finish<kBlock, kGramOpenM, false>(tot, Gs, alpha_s, &sc, m, c, head, base_slot, op, yn_old, 0, 1, blockIdx.x == 0, pa, pb);
@@ -328,7 +370,16 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
         if (sc.status != LBFGSB_RUNNING) return;
         c = sc.count; head = sc.head;                              // (as computed above: the update has been applied)
         const int V = 2 * c + 1;
-        if (tid < kMaxV + 8) delta_s[tid] = tid < V ? sc.delta[tid] : 0.0;
+        if (tid < 2 * kPre) {
+            // coefficient of slot tid of y, tid - kPre of s
+            const int slot = tid < kPre ? tid : tid - kPre, age = slot >= base_slot ? slot - base_slot : slot - base_slot + m;
+            coef_s[tid] = slot < m && age < c ? sc.delta[tid < kPre ? c + age : age] : 0.0;
+        }
+        if (more && tid < kMaxV + 8) {
+            vecp[tid] = tid < V ? ring_vec(tid, c, head, m, n, S, Y, g) : g;
+            delta_s[tid] = tid < V ? sc.delta[tid] : 0.0;
+        }
+        if (tid == 0) delta_s[kMaxV + 8] = sc.delta[2 * c];
     } else {
         const int status = scal->status;
         const double delta_raw = tid < kMaxV ? scal->delta[tid] : 0.0;
@@ -350,7 +401,7 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
     for (int64_t e = e_first; e < n; e += (int64_t)gridDim.x * kBlock) {
         const double xe = xn, ge = gn, le = ln, ue = un;
         const uint8_t mk = mkn;
-        {
+        if (more) {
             // the next element's, one trip ahead
             const int64_t e2 = e + (int64_t)gridDim.x * kBlock;
             const int64_t e2s = e2 < n ? e2 : n - 1;
@@ -364,9 +415,14 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
             if (mk) {
                 double q = 0.0;
                 if (CLOSE && e == e_first) {
-                    // (same order of additions as below; entries past the last vector are zero times zero)
+                    double q1 = 0.0;
+                    q = delta_s[kMaxV + 8] * ge;
 #pragma unroll
-                    for (int j = 0; j < kDirPre; ++j) q = fma(delta_s[j], vpre[j], q);
+                    for (int k = 0; k < kPre; ++k) {               // (slots that hold no pair: zero times zero)
+                        q = fma(coef_s[k], vy[k], q);
+                        q1 = fma(coef_s[kPre + k], vs[k], q1);
+                    }
+                    q += q1;
                 } else {
                     for (int j0 = 0; j0 < V; j0 += 8) {
                         double v[8];
@@ -388,8 +444,8 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
         p2[e] = b;
         s[0] = fma(a, ge, s[0]); s[1] = fma(a, a, s[1]); s[2] = fma(xe, a, s[2]);
         s[3] = fma(b, ge, s[3]); s[4] = fma(b, b, s[4]); s[5] = fma(xe, b, s[5]);
-        if (b > 0.0) ub = fmin(ub, (ue - xe) / b);
-        else if (b < 0.0) ub = fmin(ub, (le - xe) / b);
+        const double room = ((b > 0.0 ? ue : le) - xe) / b;
+        if (b != 0.0) ub = fmin(ub, room);
 #pragma unroll
         for (int r = 0; r < kFoldMax; ++r) {
             if (r < fold.n_fold) {
@@ -431,7 +487,7 @@ __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op,
                                                       double* __restrict__ redpart, int d_given, int store_d,
                                                       int defer_choice, GramRecords records, Scal* __restrict__ scal_next) {
     __shared__ double delta_s[kMaxV + 24];
-    __shared__ double red[kWaves * 7];
+    __shared__ double red[kWaves * kDirRed];
     __shared__ int flag;
     const int tid = threadIdx.x;
     const int64_t nchunks = (n + 2 * kBlock - 1) / (2 * kBlock);
@@ -489,7 +545,7 @@ __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op,
         int pa, pb;
         gram_product_slots(tid < gram_products(m) ? tid : 0, m, pa, pb);
         asm volatile("" : "+v"(pa), "+v"(pb));
-        gram_sum_partials_flat<kBlock, false>(records.part, gram_entries(m), records.count, tot);
+        gram_sum_entries<kBlock>(records.part, gram_entries(m), records.count, tot);
         __syncthreads();
         if (sc.status != LBFGSB_RUNNING) {
             // (the kernel behind reads its status word from scal_next: it must not find an older one there)

@@ -204,12 +204,16 @@ __device__ __forceinline__ bool arrive_is_last(unsigned* counter, int* lds_flag,
     return *lds_flag != 0;
 }
 
+// Slots of a ring of m (comparisons: an integer division takes some 40 instructions): the one behind `slot`, the one `back` <= m before.
+__device__ __forceinline__ int ring_next(int slot, int m) { return slot + 1 < m ? slot + 1 : 0; }
+__device__ __forceinline__ int ring_back(int slot, int back, int m) { return slot < back ? slot - back + m : slot - back; }
+
 // Ring bookkeeping.  Logical vector j of [s^0..s^{c-1}, y^0..y^{c-1}, g], pair 0 being the oldest;
 // `head` is the slot the next pair goes to.
 __device__ __forceinline__ const double* ring_vec(int j, int c, int head, int m, int64_t n, const double* S,
                                                   const double* Y, const double* g) {
-    if (j < c) return S + (int64_t)((head - c + j + 2 * m) % m) * n;
-    if (j < 2 * c) return Y + (int64_t)((head - c + (j - c) + 2 * m) % m) * n;
+    if (j < c) return S + (int64_t)ring_back(head, c - j, m) * n;
+    if (j < 2 * c) return Y + (int64_t)ring_back(head, 2 * c - j, m) * n;
     return g;
 }
 
@@ -221,7 +225,7 @@ __device__ __forceinline__ void effective_ring(const Scal* s, int m, int& head, 
     ls_dead = false;
     if (s->pend_valid) {
         if (s->pend_ok) {
-            head = (head + 1) % m;
+            head = ring_next(head, m);
             count = count < m ? count + 1 : m;
         } else if (count > 0) {
             count = 0;
@@ -277,7 +281,7 @@ __device__ __forceinline__ void apply_pending(Scal* s, int m, bool record = true
     if (s->pend_ok) {
         s->alpha = s->pend_alpha;
         s->f = s->pend_f;
-        s->head = (s->head + 1) % m;
+        s->head = ring_next(s->head, m);
         s->count = s->count < m ? s->count + 1 : m;
         s->iters += 1;
         if (record) record_iteration(s);

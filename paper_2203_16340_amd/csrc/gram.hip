@@ -325,12 +325,12 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
     }
     int head = field(offsetof(Scal, head)), c = field(offsetof(Scal, count));
     if (field(offsetof(Scal, pend_valid))) {          // same rule as effective_ring()
-        if (field(offsetof(Scal, pend_ok))) { head = (head + 1) % m; c = c < m ? c + 1 : m; }
+        if (field(offsetof(Scal, pend_ok))) { head = ring_next(head, m); c = c < m ? c + 1 : m; }
         else c = 0;
     }
     const double yn_old = no_close ? 1.0 : prefetch_ynorm2(scal, c, head, m);   // (used by the last workgroup's recursion, fetched now)
-    const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;   // ring slot of the oldest pair
-    const int newest = c > 0 ? (head - 1 + m) % m : -1;
+    const int base_slot = c > 0 ? ring_back(head, c, m) : 0;   // ring slot of the oldest pair
+    const int newest = c > 0 ? ring_back(head, 1, m) : -1;
     double* mine = dyn + wave * kWaveLds;
     int K = KM;                                          // tiles of y and g in the sums left in LDS
     if constexpr (LONG) {
@@ -468,7 +468,7 @@ void k_update_gram_gauss(Dims dm, Opts op, int loss_parts, const double* __restr
     const double alpha = ls_alpha;
     const bool ok = __builtin_amdgcn_readfirstlane(ls_ok) != 0;
     const int c = __builtin_amdgcn_readfirstlane(ok ? (held < m ? held + 1 : m) : 0);      // pairs held from here on; the newest in slot `head`
-    const int base_slot = __builtin_amdgcn_readfirstlane(c > 0 ? (head + 1 - c + 2 * m) % m : 0);
+    const int base_slot = __builtin_amdgcn_readfirstlane(c > 0 ? ring_back(head, c - 1, m) : 0);
     const double* p = branch == 1 ? p1 : p2;
     double *Sn = S + (int64_t)head * n, *Yn = Y + (int64_t)head * n;
 
@@ -868,12 +868,12 @@ void k_gram_blocks(int64_t n, int m, Opts op, const double* __restrict__ x, cons
     }
     int head = field(offsetof(Scal, head)), c = field(offsetof(Scal, count));
     if (field(offsetof(Scal, pend_valid))) {          // same rule as effective_ring()
-        if (field(offsetof(Scal, pend_ok))) { head = (head + 1) % m; c = c < m ? c + 1 : m; }
+        if (field(offsetof(Scal, pend_ok))) { head = ring_next(head, m); c = c < m ? c + 1 : m; }
         else c = 0;
     }
     const double yn_old = prefetch_ynorm2(scal, c, head, m);   // (used by the last workgroup's recursion, fetched now)
-    const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;   // ring slot of the oldest pair
-    const int newest = c > 0 ? (head - 1 + m) % m : -1;
+    const int base_slot = c > 0 ? ring_back(head, c, m) : 0;   // ring slot of the oldest pair
+    const int newest = c > 0 ? ring_back(head, 1, m) : -1;
     if constexpr (LONG) {
         const double* y_new = newest >= 0 ? Y + (int64_t)newest * n : g;
         unsigned long long active = 1ull << M;        // bit k: slot k holds a vector

@@ -199,7 +199,7 @@ __device__ __forceinline__ void gram_finish(const double* tot, double* Gs, doubl
     __syncthreads();
     const double gg = Gs[(2 * c) * Vp + 2 * c];   // sum over the free set of g^2
     const double ynew = tot[2];                    // ||y_new||^2 over the full vector: kept for later iterations
-    if (tid == 0 && c > 0 && !dbg_inputs) sc->ynorm2[(head - 1 + m) % m] = ynew;
+    if (tid == 0 && c > 0 && !dbg_inputs) sc->ynorm2[ring_back(head, 1, m)] = ynew;
     recursion_on_coefficients<MAXK>(Gs, Vp, c, head, m, op, sc, gg, tot[0], tot[1], ynew, yn_old, alpha_s, dbg_inputs, evaluate_stop);
 }
 

@@ -17,7 +17,7 @@ __device__ __forceinline__ double lane_value(double v, int l) {
 // depend on anything the calling kernel computes, so the kernels fetch it when they start, long before it is used.
 __device__ __forceinline__ double prefetch_ynorm2(const Scal* __restrict__ scal, int c, int head, int m) {
     const int tid = threadIdx.x;
-    return (tid < 64 && tid < c) ? scal->ynorm2[(head - c + tid + 2 * m) % m] : 1.0;
+    return (tid < 64 && tid < c) ? scal->ynorm2[ring_back(head, c - tid, m)] : 1.0;
 }
 
 // The recursion for at most K pairs.  Every entry of G a lane needs is fetched at once; the three loops then run on registers

@@ -159,7 +159,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
         head = __builtin_amdgcn_readfirstlane(head);
         since = __builtin_amdgcn_readfirstlane(since);
         const int Vp = 2 * c + 2;
-        const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;
+        const int base_slot = c > 0 ? ring_back(head, c, m) : 0;
         auto slot_vec = [&](int j) __attribute__((always_inline)) -> const double* {
             return lds + (j < m ? L.Y + j * np : (j == m ? L.g : (j <= 2 * m ? L.S + (j - m - 1) * np : L.zero)));
         };
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                 if (tid == 64) {
                     for (int w = 0; w < nw; ++w) { nfix += redA[w]; pginf = fmax(pginf, redA[kResWaves + w]); }
                 }
-                const double ynew = c > 0 ? sc.ynorm2[(head - 1 + m) % m] : 0.0;
+                const double ynew = c > 0 ? sc.ynorm2[ring_back(head, 1, m)] : 0.0;
                 const double yn_old = prefetch_ynorm2(&sc, c, head, m);
                 recursion_on_coefficients<10>(G, Vp, c, head, m, op, &sc, G[(2 * c) * Vp + 2 * c], pginf, nfix, ynew, yn_old,
                                           alpha_s, 0, 1);
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                 sc.f = sc.f + alpha * (gp + 0.5 * alpha * tt);
                 sc.alpha = alpha;
                 sc.ynorm2[slot] = yn;
-                sc.head = (slot + 1) % m;
+                sc.head = ring_next(slot, m);
                 sc.count = c < m ? c + 1 : m;
                 sc.iters += 1;
                 sc.since_refresh = since + 1;
@@ -432,7 +432,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
         }
         // the same bookkeeping in every thread's registers; the next trip's first barrier orders that thread's writes to
         // the scalar block before the recursion reads them
-        if (ok) { head = (slot + 1) % m; c = c < m ? c + 1 : m; since += 1; }
+        if (ok) { head = ring_next(slot, m); c = c < m ? c + 1 : m; since += 1; }
         else if (c > 0) c = 0;
     }
 

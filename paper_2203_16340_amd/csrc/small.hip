@@ -96,8 +96,8 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
     effective_ring(&sc, m, head, c, ls_dead);
     const double yn_old = prefetch_ynorm2(&sc, c, head, m);
     const int V = 2 * c + 1, Vp = V + 1;
-    const int base_slot = c > 0 ? (head - c + 2 * m) % m : 0;   // ring slot of the oldest pair
-    const int newest = c > 0 ? (head - 1 + m) % m : -1;
+    const int base_slot = c > 0 ? ring_back(head, c, m) : 0;   // ring slot of the oldest pair
+    const int newest = c > 0 ? ring_back(head, 1, m) : -1;
     // static slot -> place in the recursion's order s^0..s^{c-1}, y^0..y^{c-1}, g (oldest first), -1: holds no pair
     auto logical = [&](int slot) -> int {
         if (slot == M) return 2 * c;

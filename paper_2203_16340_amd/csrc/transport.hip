@@ -646,7 +646,7 @@ __global__ __launch_bounds__(NT) void k_ot_update_entropy(Dims dm, Opts op, OtAr
     if (tid == 0) {
         if (ok) {
             scal->f = tot[0];
-            scal->head = (slot + 1) % dm.m;
+            scal->head = ring_next(slot, dm.m);
             scal->count = scal->count < dm.m ? scal->count + 1 : dm.m;
             scal->iters += 1;
             record_iteration(scal);

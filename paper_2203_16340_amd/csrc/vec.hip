@@ -338,13 +338,11 @@ __global__ __launch_bounds__(kBlock) void k_dir(int64_t n, int m, Opts op, const
         }
         head = __builtin_amdgcn_readfirstlane(sc.head); c = __builtin_amdgcn_readfirstlane(sc.count);
         if (__builtin_amdgcn_readfirstlane(sc.pend_valid)) {       // same rule as effective_ring()
-            if (__builtin_amdgcn_readfirstlane(sc.pend_ok)) { head = head + 1 < m ? head + 1 : 0; c = c < m ? c + 1 : m; }
+            if (__builtin_amdgcn_readfirstlane(sc.pend_ok)) { head = ring_next(head, m); c = c < m ? c + 1 : m; }
             else c = 0;
         }
-        const int base_slot = head - c < 0 ? head - c + m : head - c;
-        // (as prefetch_ynorm2)
-        double yn_old = 1.0;
-        if (tid < c) yn_old = sc.ynorm2[base_slot + tid < m ? base_slot + tid : base_slot + tid - m];
+        const int base_slot = ring_back(head, c, m);
+        const double yn_old = prefetch_ynorm2(&sc, c, head, m);
         // the first element's entries are requested now (which slots hold pairs is known), so that their trip to memory runs under the
         // closing step instead of behind it
         if (mkn) {
@@ -555,13 +553,13 @@ __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op,
         int head = __builtin_amdgcn_readfirstlane(sc.head);
         c = __builtin_amdgcn_readfirstlane(sc.count);
         if (sc.pend_valid) {                                     // same rule as effective_ring()
-            if (sc.pend_ok) { head = (head + 1) % m; c = c < m ? c + 1 : m; }
+            if (sc.pend_ok) { head = ring_next(head, m); c = c < m ? c + 1 : m; }
             else c = 0;
         }
         c = __builtin_amdgcn_readfirstlane(c);
         head = __builtin_amdgcn_readfirstlane(head);
         V = 2 * c + 1;
-        base_slot = c > 0 ? (head - c + 2 * m) % m : 0;
+        base_slot = c > 0 ? ring_back(head, c, m) : 0;
         const double yn_old = prefetch_ynorm2(&sc, c, head, m);
         if (pair_mask(in_next, ec_next, mkn) != 0) load(0, base_slot, ec_next, first);
         __syncthreads();                                         // every thread has read the ring before it changes
@@ -581,7 +579,7 @@ __global__ __launch_bounds__(kBlock) void k_dir_pairs(int64_t n, int m, Opts op,
         if (scal->status != LBFGSB_RUNNING) return;
         c = scal->count;
         V = 2 * c + 1;
-        base_slot = c > 0 ? (scal->head - c + 2 * m) % m : 0;
+        base_slot = c > 0 ? ring_back(scal->head, c, m) : 0;
         if (tid < kMaxV + 24) delta_s[tid] = tid < V ? scal->delta[tid] : 0.0;
     }
     __syncthreads();
@@ -1213,7 +1211,7 @@ __global__ __launch_bounds__(kBlock) void k_update_logistic(Dims dm, double c1, 
             // f from the new margins and the new iterate
             scal->f = loss + 0.5 * dm.mu * tot[1];
             scal->ynorm2[slot] = tot[0];
-            scal->head = (slot + 1) % dm.m;
+            scal->head = ring_next(slot, dm.m);
             scal->count = scal->count < dm.m ? scal->count + 1 : dm.m;
             scal->iters += 1;
             record_iteration(scal);

@@ -154,6 +154,45 @@ __device__ __forceinline__ double wave_min(double v) {
 }
 __device__ __forceinline__ double wave_max(double v) { return -wave_min(-v); }
 
+constexpr int kDppRor8 = 0x128;          // row_ror:8, lane i <-> i ^ 8 within each row of 16
+
+// One halving step of the transposing sum: lanes with bit D of their index set keep the upper D values.  The partner
+// (CTRL) differs in bit D and, below it, in any way that maps groups of lanes holding the same values onto each other.
+template <int D, int CTRL, int S>
+__device__ __forceinline__ void halve(double (&a)[S], int lane) {
+    const bool upper = (lane & D) != 0;
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
+        const double send = upper ? a[k] : a[k + D];
+        const double keep = upper ? a[k + D] : a[k];
+        a[k] = keep + dpp_move<CTRL>(send);
+    }
+}
+// v of each lane plus v of the lane that differs in bit 4 (ACROSS 16) or 5 (32): rows, or halves, of the wave swapped between two
+// copies, a vector instruction for each word
+template <int ACROSS>
+__device__ __forceinline__ double add_across(double v) {
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    if constexpr (ACROSS == 16) {
+        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    } else {
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    }
+}
+// Sums of eight values over the wave at once: lane i gets the total of a[i % 8].  Some 60 instructions, where a wave_sum each takes
+// 25.  Fixed order, all 64 lanes active, as above.  (The six sums of Algorithm 2's choice, whole calls, us, a wave_sum each / this: resident
+// iteration 200 x 100, 51 of them 408 / 381, short-vector step 3000 x 800, 40 of them 1127 / 1107.)
+__device__ __forceinline__ double wave_sums8(double (&a)[8], int lane) {
+    halve<4, kDppHalfMirror>(a, lane);   // i <-> 7 - i: flips bit 2 (and two in which nothing differs yet)
+    halve<2, kDppXor2>(a, lane);
+    halve<1, kDppXor1>(a, lane);
+    double t = a[0];
+    t += dpp_move<kDppRor8>(t);
+    return add_across<32>(add_across<16>(t));
+}
+
 // Sum of K values over a workgroup of NW waves; every thread gets the totals.  The order of the
 // additions is fixed (butterfly inside a wave, waves in index order), so results are bit-reproducible.
 template <int K, int NW>

@@ -23,21 +23,6 @@
 namespace lb {
 namespace narrow {
 
-constexpr int kDppRor8 = 0x128;          // row_ror:8, lane i <-> i ^ 8 within each row of 16
-
-// One halving step of the transposing sum: lanes with bit D of their index set keep the upper D values.  The partner
-// (CTRL) differs in bit D and, below it, in any way that maps groups of lanes holding the same values onto each other.
-template <int D, int CTRL, int S>
-__device__ __forceinline__ void halve(double (&a)[S], int lane) {
-    const bool upper = (lane & D) != 0;
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-        const double send = upper ? a[k] : a[k + D];
-        const double keep = upper ? a[k + D] : a[k];
-        a[k] = keep + dpp_move<CTRL>(send);
-    }
-}
-
 // Sums of a[0..S) over the L lanes of a row: lane i returns the total of a[i % S].  Fixed order.
 template <int L, int S>
 __device__ __forceinline__ double row_sums(double (&a)[S], int lane) {

@@ -285,15 +285,10 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
                     const double room = ((pb > 0.0 ? ui : li) - xi) / pb;
                     if (pb != 0.0) ub = room;
                 }
-                double w6[6] = {pa * gi, pa * pa, xi * pa, pb * gi, pb * pb, xi * pb};
-#pragma unroll
-                for (int k = 0; k < 6; ++k) w6[k] = wave_sum(w6[k]);
+                double w8[8] = {pa * gi, pa * pa, xi * pa, pb * gi, pb * pb, xi * pb, 0.0, 0.0};
+                const double sum_of = wave_sums8(w8, lane);
                 ub = wave_min(ub);
-                if (lane == 0) {
-#pragma unroll
-                    for (int k = 0; k < 6; ++k) redD[wave * 7 + k] = w6[k];
-                    redD[wave * 7 + 6] = ub;
-                }
+                if (lane < 7) redD[wave * 7 + lane] = lane == 6 ? ub : sum_of;
             }
             __syncthreads();                        // (also publishes p1s / p2s)
             {

@@ -254,15 +254,10 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
             }
         }
         // one exchange: the waves' seven results side by side, added by the first wave with the lanes as they lie
+        double eight[8] = {s[0], s[1], s[2], s[3], s[4], s[5], 0.0, 0.0};
+        const double sum_of = wave_sums8(eight, lane);
         ub = wave_min(ub);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) s[k] = wave_sum(s[k]);
-        if (lane == 0) {
-#pragma unroll
-            for (int k = 0; k < 6; ++k) red[wave * 8 + k] = s[k];
-            red[wave * 8 + 6] = ub;
-            red[wave * 8 + 7] = 0.0;
-        }
+        if (lane < 8) red[wave * 8 + lane] = lane == 6 ? ub : sum_of;
         if (n_fold > 0) {
 #pragma unroll
             for (int k = 0; k < 2 * kFoldMax; ++k) sx[k] = wave_sum(sx[k]);

@@ -180,17 +180,16 @@ __device__ __forceinline__ void dir_finish(double (&s)[6], double ub, double eps
     if (defer_choice) {
         // the consumer of the direction chooses between the candidates from the records: one exchange and one thread an entry
         const int wave = tid >> 6;
+        const int lane = tid & 63;
+        double eight[8] = {s[0], s[1], s[2], s[3], s[4], s[5], 0.0, 0.0};
+        const double sum_of = wave_sums8(eight, lane);
         ub = wave_min(ub);
-#pragma unroll
-        for (int k = 0; k < 6; ++k) s[k] = wave_sum(s[k]);
         if (fold.n_fold > 0) {
 #pragma unroll
             for (int k = 0; k < 2 * kFoldMax; ++k) sx[k] = wave_sum(sx[k]);
         }
-        if ((tid & 63) == 0) {
-#pragma unroll
-            for (int k = 0; k < 6; ++k) red[wave * kDirRed + k] = s[k];
-            red[wave * kDirRed + 6] = ub;
+        if (lane < 7) red[wave * kDirRed + lane] = lane == 6 ? ub : sum_of;
+        if (lane == 0) {
 #pragma unroll
             for (int k = 0; k < 2 * kFoldMax; ++k) red[wave * kDirRed + 8 + k] = sx[k];
         }

@@ -188,7 +188,8 @@ int lbfgsb_set_x(lbfgsb_solver* s, const double* x0);
  * only (no memset, copy or wait), so a run of such calls may be recorded into a HIP graph on the solver's
  * stream; whether a step also recomputes residual and gradient (refresh_every) is decided on the host when
  * the call is made, so a recorded run replays the pattern it was recorded with (use refresh_every = 0, or
- * record a multiple of it).  Not while lbfgsb_enable_apass_timing is on: timed launches carry events. */
+ * record a multiple of it).  Replays leave what as many eager steps leave (quadratic forms and Gaussian transports of 2^17 and more
+ * variables: to rounding).  Not while lbfgsb_enable_apass_timing is on: timed launches carry events. */
 int lbfgsb_step(lbfgsb_solver* s, lbfgsb_info* info_host);
 /* (For the quadratic kinds the gradient is carried by recurrence between the periodic recomputations.  lbfgsb_solve
  * and the resident organisation re-evaluate it from x before they report LBFGSB_CONVERGED; a loop of lbfgsb_step
@@ -197,8 +198,8 @@ int lbfgsb_step(lbfgsb_solver* s, lbfgsb_info* info_host);
 
 /* Iterates until the tolerance, max_iter or a line-search failure.  The device decides all
  * data-dependent branches; the kernel that takes an iteration's stopping decision reports it in pinned host memory (the
- * first iterations each, later every fourth or eighth), which the calling thread watches while it enqueues ahead, without
- * stopping the device.  It polls until the run is over, yielding its core to other threads.  The result does not depend
+ * first eight iterations each, later every fourth or eighth), which the calling thread watches while it enqueues the steps up to the
+ * next report, without stopping the device.  It polls until the run is over, yielding its core to other threads.  The result does not depend
  * on how far ahead it was.
  * A least-squares solve is declared converged only with residual and gradient freshly
  * recomputed from x.  info_host may be NULL. */

@@ -1,5 +1,5 @@
 // C-ABI layer of liblbfgsb: argument checks, workspace layout, the fixed kernel sequence of one
-// iteration of Algorithm 1, the polling loop of lbfgsb_solve and the primitive-level hooks.
+// iteration of Algorithm 1, the loops of lbfgsb_solve and of the augmented Lagrangian that follow the device and the primitive-level hooks.
 // No solver arithmetic happens on the host.
 #include <sched.h>
 
@@ -717,9 +717,9 @@ void enqueue_retest(lbfgsb_solver* s) {
 
 // The stopping quantity was computed from a gradient carried by recurrence: residual and gradient are recomputed from x
 // and the test is made again before convergence is declared (the status is then in the host copy).
-bool one_workgroup_judges(const lbfgsb_solver* s) { return s->dm.n <= kJudgeMax && !is_transport(s->dm.kind); }
+bool one_workgroup_retests(const lbfgsb_solver* s) { return s->dm.n <= kRetestMax && !is_transport(s->dm.kind); }
 hipError_t confirm_convergence(lbfgsb_solver* s) {
-    if (one_workgroup_judges(s)) {
+    if (one_workgroup_retests(s)) {
         enqueue_eval(s, 0, true, true);
         s->steps_since_refresh = 0;
         launch_retest(s->dm, s->op, s->bf, s->stream, s->owns_h_scal ? s->h_scal : nullptr);
@@ -1386,7 +1386,7 @@ struct AlTurn {
     int64_t n_eq, cols, ld;
     double ctol;
     int max_outer, retest, fevals;
-    int judge;              // retest by this workgroup, from here on (k_retest)
+    int own_test;              // retest by this workgroup, from here on (k_retest)
     int64_t n;
     Opts op;
     const double *x, *l, *u;
@@ -1405,14 +1405,14 @@ constexpr int64_t kShiftMax = 16 * kTurnThreads;
 template <typename T, bool SHIFT>
 __global__ __launch_bounds__(kTurnThreads) void k_al_turn(AlTurn a) {
     __shared__ double lds[2 * kTurnThreads / 64];
-    __shared__ double judge_s[3 * kTurnThreads / 64];
+    __shared__ double retest_s[3 * kTurnThreads / 64];
     __shared__ double coef_s[SHIFT ? kShiftRowsMax : 1];
     __shared__ double rho_s;
     __shared__ int go_s;
     const int tid = threadIdx.x;
     const double rho = a.state->rho, viol_prev = a.state->violation;
     if (a.state->done) return;
-    const int status = a.judge ? judge_point<kTurnThreads>(a.n, a.op, a.x, a.g, a.l, a.u, a.scal, judge_s)
+    const int status = a.own_test ? retest_point<kTurnThreads>(a.n, a.op, a.x, a.g, a.l, a.u, a.scal, retest_s)
                                : (a.retest ? a.scal->status : a.state->inner_status);
     if (a.retest && status == LBFGSB_RUNNING) {
         if (tid == 0) a.state->turned = 0;
@@ -1564,11 +1564,11 @@ size_t al_rows_extra_bytes(int64_t n_eq) {
 void enqueue_turn(lbfgsb_auglag* al, bool confirm) {
     lbfgsb_solver* s = al->inner;
     // (a convergence to be confirmed: the evaluation reopens the solver and the turn makes the test itself)
-    const bool judge = confirm && s->steps_since_refresh > 0 && one_workgroup_judges(s);
-    if (!judge) hipLaunchKernelGGL(k_al_reopen, dim3(1), dim3(64), 0, al->stream, s->bf.scal, s->dm.m, al->state);
+    const bool own_test = confirm && s->steps_since_refresh > 0 && one_workgroup_retests(s);
+    if (!own_test) hipLaunchKernelGGL(k_al_reopen, dim3(1), dim3(64), 0, al->stream, s->bf.scal, s->dm.m, al->state);
     if (s->steps_since_refresh > 0) {
-        enqueue_eval(s, 0, true, judge);
-        if (confirm && !judge) enqueue_retest(s);
+        enqueue_eval(s, 0, true, own_test);
+        if (confirm && !own_test) enqueue_retest(s);
     }
     s->steps_since_refresh = 0;
     s->steps_since_set_x = 0;
@@ -1578,7 +1578,7 @@ void enqueue_turn(lbfgsb_auglag* al, bool confirm) {
     a.n_eq = al->n_eq; a.cols = stacked ? s->dm.cols : s->dm.n; a.ld = al->c_ld;
     a.ctol = al->ao.ctol; a.max_outer = al->ao.max_outer; a.retest = confirm ? 1 : 0;
     a.fevals = stacked ? 0 : 1;        // (of a stacked subproblem's start this never counted)
-    a.judge = judge ? 1 : 0; a.n = s->dm.n; a.op = s->op; a.x = s->bf.x; a.l = s->bf.l; a.u = s->bf.u;
+    a.own_test = own_test ? 1 : 0; a.n = s->dm.n; a.op = s->op; a.x = s->bf.x; a.l = s->bf.l; a.u = s->bf.u;
     a.d = al->d_c; a.lambda = al->lambda; a.beta = al->beta_c; a.omega = al->omega_c; a.res = (double*)al->res_c; a.coef = al->coef;
     a.total = s->dm.n_extra > 0 ? s->bf.xres + s->dm.n_extra : nullptr;
     a.Crows = al->c_rows; a.g = s->bf.g; a.scal = s->bf.scal; a.hist = s->bf.hist; a.state = al->state; a.host = al->h_state;

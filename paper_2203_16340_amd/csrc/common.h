@@ -531,9 +531,9 @@ __device__ __forceinline__ double fold_coefficients(const double (&tx)[2 * kFold
 // Free set, ||g_S||, KKT residual and stopping test at (x, g) by one workgroup of NT threads, without the products a step would
 // need as well: for a gradient that has just been evaluated from scratch.  lds: 3 NT/64 doubles.  Every thread gets the status.
 // Up to here one compute unit streams the four vectors (1 MB) in less than the ~17 us of the three launches this stands for.
-constexpr int64_t kJudgeMax = 32768;
+constexpr int64_t kRetestMax = 32768;
 template <int NT>
-__device__ __forceinline__ int judge_point(int64_t n, const Opts& op, const double* __restrict__ x, const double* __restrict__ g,
+__device__ __forceinline__ int retest_point(int64_t n, const Opts& op, const double* __restrict__ x, const double* __restrict__ g,
                                            const double* __restrict__ l, const double* __restrict__ u, Scal* __restrict__ scal, double* lds) {
     double s[2] = {0.0, 0.0}, most = 0.0;
     for (int64_t i0 = threadIdx.x; i0 < n; i0 += 4 * NT) {
@@ -805,7 +805,7 @@ GramRecords gram_records(const Dims& dm, const Geometry& ge, const Buffers& bf);
 // host_scal: pinned host memory that receives the scalar block as well (null: device copy only)
 void launch_commit(const Dims& dm, const Buffers& bf, hipStream_t st, Scal* host_scal = nullptr);
 void launch_reopen(const Dims& dm, const Buffers& bf, hipStream_t st);   // applies a pending update; CONVERGED -> RUNNING
-// n <= kJudgeMax: the stopping test at an iterate whose gradient has just been evaluated; host_scal as for launch_commit
+// n <= kRetestMax: the stopping test at an iterate whose gradient has just been evaluated; host_scal as for launch_commit
 void launch_retest(const Dims& dm, const Opts& op, const Buffers& bf, hipStream_t st, Scal* host_scal);
 // lbfgsb_create.  What the bounds are like, in pinned host memory: [0] some l_i > u_i or NaN, [1] not all pairs are the same,
 // [2] some l_i is not positive; the first pair.

@@ -1090,7 +1090,7 @@ __global__ void k_reopen(Scal* scal, int m) {
 void launch_reopen(const Dims& dm, const Buffers& bf, hipStream_t st) {
     hipLaunchKernelGGL(k_reopen, dim3(1), dim3(64), 0, st, bf.scal, dm.m);
 }
-// The test itself needs four vectors and none of the pair memory: where one workgroup can stream them (kJudgeMax), it takes the place
+// The test itself needs four vectors and none of the pair memory: where one workgroup can stream them (kRetestMax), it takes the place
 // of a Gram kernel with closing step and recursion (9 us) and hands the scalar block to the host as well (a launch, 4 us);
 // k_eval_finish reopens (another).  In Algorithm 4 the kernel between two inner solves makes the test.  Whole calls: NNLS 3001 x 301
 // 330 -> 315 us, 28 inner solves over 8000 x 2000 6640 -> 6500.
@@ -1099,7 +1099,7 @@ __global__ __launch_bounds__(kRetestThreads) void k_retest(int64_t n, Opts op, c
                                                            const double* __restrict__ l, const double* __restrict__ u, Scal* scal,
                                                            Scal* __restrict__ host_scal) {
     __shared__ double lds[3 * kRetestThreads / 64];
-    if (scal->status == LBFGSB_RUNNING) judge_point<kRetestThreads>(n, op, x, g, l, u, scal, lds);
+    if (scal->status == LBFGSB_RUNNING) retest_point<kRetestThreads>(n, op, x, g, l, u, scal, lds);
     if (host_scal) copy_scal<kRetestThreads>(scal, host_scal);
 }
 void launch_retest(const Dims& dm, const Opts& op, const Buffers& bf, hipStream_t st, Scal* host_scal) {

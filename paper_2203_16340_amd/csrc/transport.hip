@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kBlock) void k_ot_update_gauss(Dims dm, Opts op, Ot
 }
 
 // The step lengths are a_0 = min(1, bound), a_k = a_{k-1} backtrack.  From the second iteration of a run on the first is accepted
-// nearly always, at a start on the lower bound, where p/x is huge, one after a dozen or more.  So a_0 is judged alone, from a sum
+// nearly always, at a start on the lower bound, where p/x is huge, one after a dozen or more.  So a_0 is tested alone, from a sum
 // that the row-sum kernel has formed on the way (where the rows are enough workgroups for a logarithm per entry, else a launch of
 // its own), by the first of two further launches; if it is refused, that launch sums the 8 lengths k = kLsCoarse.  The second one
 // looks for the first of these that is acceptable and sums what lies between it and the one before: the change of the objective

@@ -1,5 +1,5 @@
 """The entropy's line search where its stages meet: the first accepted step length anywhere in the sequence of halvings, with the
-first length judged from the row sums' kernel or from a launch of its own, narrow and wide workgroups, limits in every stage, and
+first length decided from the row sums' kernel or from a launch of its own, narrow and wide workgroups, limits in every stage, and
 a negative curvature, for which the search must not skip lengths.
 
 A start at l = 1e-300 with minimisers exp(-M/lambda - 1): each constant added to M takes about three more halvings.  The

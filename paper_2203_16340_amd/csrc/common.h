@@ -65,6 +65,7 @@ struct Scal {
     int since_refresh;      // resident solver: iterations since residual and gradient were last computed from x
     // logistic objective, short launch sequence (see kStatusBail)
     int bail_skipped;       // whole steps that found the status kStatusBail and did nothing
+    int ls_first;           // entropy: the first of the search's two launches has accepted the first step length
     // per-iteration records (ring in the workspace; null: none kept)
     lbfgsb_iter_record* hist;
     long long hist_count;   // records written since lbfgsb_set_x

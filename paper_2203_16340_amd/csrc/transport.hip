@@ -451,8 +451,9 @@ __global__ __launch_bounds__(NT, NT > kBlock ? 4 : 1) void k_ot_ls_coarse(Dims d
     const double s0 = sum_all<NT>(first, first_parts, red);
     const bool ok = entropy_accepts(s0, a0, gp, tt, dm.lambda, op);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        scal->ls_ok = ok;
+        scal->ls_first = ok;
         if (ok) {
+            scal->ls_ok = 1;
             scal->backtracks = 0;
             scal->fevals += 1;
             scal->alpha = a0;
@@ -477,7 +478,9 @@ __global__ __launch_bounds__(NT, NT > kBlock ? 4 : 1) void k_ot_ls_fine(Dims dm,
                                                    const double* __restrict__ coarse, double* __restrict__ fine) {
     __shared__ double red[(NT / 64 + 1) * kLsFine];
     __shared__ int flag;
-    if (scal->status != LBFGSB_RUNNING || scal->ls_ok) return;
+    // (ls_first, not the search's outcome: where the coarse lengths decide, workgroup 0 writes that while others are still to begin,
+    // and the waves of a workgroup, each with a load of its own, would not all see the same)
+    if (scal->status != LBFGSB_RUNNING || scal->ls_first) return;
     const int tid = threadIdx.x;
     const double a0 = fmin(1.0, scal->alpha_ub), gp = scal->gp;
     const double* p = scal->branch == 1 ? p1 : p2;
@@ -547,7 +550,7 @@ __global__ __launch_bounds__(NT, NT > kBlock ? 4 : 1) void k_ot_ls_fine(Dims dm,
         if (entropy_accepts(sv[0], a, gp, tt, dm.lambda, op)) found = k;
     }
     if (tid == 0) {
-        // (the other workgroups have arrived, or decide the same for themselves)
+        // (no workgroup of this launch reads any of these)
         scal->ls_ok = found >= 0;
         scal->backtracks = found >= 0 ? found : most + 1;
         scal->fevals += found >= 0 ? found + 1 : most + 1;

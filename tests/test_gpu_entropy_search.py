@@ -76,3 +76,20 @@ def test_wide_workgroups():
         got = first_iteration(1000, 790, shift, 2.0, 60, True)
         assert got[:5] == ref[:5], (shift, got[:5], ref[:5])
         assert rel_err(got[5], ref[5]) <= 1e-12
+
+
+@pytest.mark.parametrize("rows,cols", [(1000, 790), (100, 8000)])   # (first length by the row sums; in its own launch)
+@pytest.mark.parametrize("rho", [1e-9, -1e-9])
+def test_first_lengths_of_wide_workgroups(rows, cols, rho):
+    """The second, third and fourth length are decided without an arrival, while half of the 512 workgroups are still to begin; with a
+    negative curvature all lengths are summed, 13 at a time, and decided behind one."""
+    seen = set()
+    for shift in (-3.0, -2.8, -2.6, -2.4, -2.2, -2.0, 3.0):
+        ref = first_iteration(rows, cols, shift, rho, 60, False)
+        runs = [first_iteration(rows, cols, shift, rho, 60, True) for _ in range(3)]
+        for got in runs:
+            assert got[:5] == ref[:5], (shift, got[:5], ref[:5])
+            assert np.array_equal(got[5], runs[0][5])
+        assert rel_err(runs[0][5], ref[5]) <= 1e-12, shift
+        seen.add(ref[2])
+    assert {1, 2, 3} < seen and max(seen) > 14, seen

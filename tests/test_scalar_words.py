@@ -1,0 +1,68 @@
+"""Words of the solver's scalar block that one launch both reads and writes, found in the sources.
+
+Every wave of a kernel reads the block with loads of its own, and workgroups begin at different times: a word that one workgroup
+writes while others may still read it can have two values in one workgroup, whose waves then part ways between barriers.  A
+kernel of several workgroups may therefore write what it reads only where every reader is known to be done: behind
+arrive_is_last, or, with the reason given here, in calls that do not read the word."""
+import os
+import re
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2203_16340_amd", "csrc")
+
+ONE_WORKGROUP = {"k_al_begin", "k_al_reopen", "k_al_turn", "k_reopen", "k_commit", "k_retest", "k_clear_bail", "k_admit", "k_check_start",
+                 "k_resident", "k_small_step"}
+READ_AND_WRITTEN = {
+    # the choice is read from the block only in calls that do not record it there (no records of the direction kernel)
+    "k_fused_ring": {"alpha_ub"},
+    # ... and `fresh`, of the block's copy, by workgroup 0 alone
+    "k_ot_sums": {"alpha_ub", "branch", "fresh"},
+    # all behind the arrival
+    "k_ot_update_entropy": {"count", "head", "status"},
+    "k_ls_logistic": {"ls_ok"},
+    # behind the arrival, or (ls_ok, spec_ok) where what was read is not used or is the value written; status: see below
+    "k_update_logistic": {"count", "f", "head", "ls_ok", "spec_ok", "status"},
+    # written in calls that do not look at it first (reopen)
+    "k_eval_finish": {"status"},
+}
+
+
+def kernels():
+    for name in sorted(os.listdir(CSRC)):
+        text = re.sub(r"//[^\n]*|/\*.*?\*/", "", open(os.path.join(CSRC, name)).read(), flags=re.S)
+        for at in re.finditer(r"__global__", text):
+            head = re.compile(r"\b(k_\w+)\s*\(").search(text, at.end())
+            begin = text.index("{", head.end())
+            depth, end = 1, begin + 1
+            while depth:
+                depth += {"{": 1, "}": -1}.get(text[end], 0)
+                end += 1
+            yield head.group(1), text[head.start():begin], text[begin:end]
+
+
+def words(signature, body):
+    names = set(re.findall(r"\bScal\s*\*\s*(?:__restrict__\s*)?(\w+)", signature)) - {"host_scal"} | {"a.scal"}
+    read, written = set(), set()
+    for n in names:
+        for m in re.finditer(r"(?<![\w.])" + re.escape(n) + r"->(\w+)(?:\[[^\]]*\])?\s*(\+=|-=|=(?!=))?", body):
+            (written if m.group(2) else read).add((n, m.group(1)))
+    return read, written
+
+
+def test_words_read_and_written_in_one_launch():
+    found = {}
+    for name, signature, body in kernels():
+        read, written = words(signature, body)
+        if name not in ONE_WORKGROUP and read & written:
+            found.setdefault(name, set()).update(word for _, word in read & written)
+    assert found == READ_AND_WRITTEN
+
+
+def test_the_entropy_search_reads_nothing_that_it_writes():
+    seen = {}
+    for name, signature, body in kernels():
+        if name.startswith("k_ot_ls_"):
+            seen[name] = words(signature, body)
+    read, written = seen["k_ot_ls_fine"]
+    assert len(seen) == 3 and ("scal", "ls_ok") in written and ("scal", "status") in read
+    for name, (read, written) in seen.items():
+        assert not read & written, name

@@ -612,8 +612,8 @@ __device__ __forceinline__ double column_sum(const double* __restrict__ wpart, i
 
 // Sum of `count` doubles, identical in every workgroup that calls it (same order everywhere).
 template <int NT = kBlock>
-__device__ __forceinline__ double sum_all(const double* __restrict__ v, int count, double* lds) {
-    double s[1] = {0.0};
+__device__ __forceinline__ double sum_all(const double* __restrict__ v, int count, double* lds, double seed = 0.0) {
+    double s[1] = {seed};
     for (int k0 = threadIdx.x; k0 < count; k0 += NT * 8) {
         double t[8];
 #pragma unroll

@@ -66,3 +66,14 @@ def test_the_entropy_search_reads_nothing_that_it_writes():
     assert len(seen) == 3 and ("scal", "ls_ok") in written and ("scal", "status") in read
     for name, (read, written) in seen.items():
         assert not read & written, name
+
+
+def test_a_workgroup_agrees_whether_the_solver_is_parked():
+    """k_update_logistic parks the solver (status) without an arrival: only workgroup 0, which writes the word, may leave by what a
+    wave has read of it, the others by the sum that all of their waves make together."""
+    body = [b for name, _, b in kernels() if name == "k_update_logistic"][0]
+    parks = body.index("scal->status = kStatusBail")
+    assert body.count("kStatusBail") == 1 and body[:parks].rstrip().count("return;") == 1
+    assert body[:parks].count("scal->status") == 1 and "const bool running = scal->status == LBFGSB_RUNNING;" in body[:parks]
+    assert "if (!running && !(short_seq && blockIdx.x > 0)) return;" in body[:parks]
+    assert "running ? 0.0 : NAN" in body[:parks] and "isfinite(df)" in body[:parks]

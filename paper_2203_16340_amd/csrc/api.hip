@@ -343,8 +343,10 @@ OtArgs ot_args(const lbfgsb_solver* s) {
 }
 
 // f, g (and the residual / margins) from scratch at the current x.  fresh: the scalar block holds no pending update.  reopen: the
-// solver has stopped there and is to go on (not the transport kinds).  host_flag: whether the gradient is finite is reported there.
-void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false, bool reopen = false, int* host_flag = nullptr) {
+// solver has stopped there and is to go on, unless *over (or null) is set (not the transport kinds).  host_flag: whether the gradient is
+// finite is reported there.
+void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false, bool reopen = false, int* host_flag = nullptr,
+                  const int* over = nullptr) {
     s->gram_ready = false;
     if (!fresh) launch_commit(s->dm, s->bf, s->stream);   // a pending f must not overwrite the one computed here
     if (is_transport(s->dm.kind)) {
@@ -376,7 +378,7 @@ void enqueue_eval(lbfgsb_solver* s, int check_status, bool fresh = false, bool r
     if (s->dm.n_extra > 0)
         launch_extra_rows(s->dm, s->bf, s->obj.extra_rows, s->obj.extra_target, s->obj.extra_weight,
                           host_flag ? 2 : 1, s->stream);
-    launch_eval_finish(s->dm, s->ge, s->bf, s->obj.b, s->obj.sign, s->stream, reopen, host_flag);
+    launch_eval_finish(s->dm, s->ge, s->bf, s->obj.b, s->obj.sign, s->stream, reopen, host_flag, over);
 }
 
 bool is_recording(const lbfgsb_solver* s) {
@@ -1363,7 +1365,8 @@ __global__ __launch_bounds__(kTurnThreads) void k_al_begin(int64_t n_eq, double 
 }
 
 // An inner solve has ended: any pending update is applied, and the solver is open for an evaluation at its last iterate.
-// (Once the run is over nothing changes any more, should the host have seen the last steps' report before it saw that.)
+// (Once the run is over nothing changes any more, should the host have seen the last steps' report before it saw that.  Where the
+// turn makes the test itself, k_eval_finish does this kernel's work and looks at `done` too.)
 __global__ void k_al_reopen(Scal* scal, int m, AlState* state) {
     if (threadIdx.x != 0 || state->done) return;
     apply_pending(scal, m);
@@ -1567,7 +1570,7 @@ void enqueue_turn(lbfgsb_auglag* al, bool confirm) {
     const bool own_test = confirm && s->steps_since_refresh > 0 && one_workgroup_retests(s);
     if (!own_test) hipLaunchKernelGGL(k_al_reopen, dim3(1), dim3(64), 0, al->stream, s->bf.scal, s->dm.m, al->state);
     if (s->steps_since_refresh > 0) {
-        enqueue_eval(s, 0, true, own_test);
+        enqueue_eval(s, 0, true, own_test, nullptr, &al->state->done);
         if (confirm && !own_test) enqueue_retest(s);
     }
     s->steps_since_refresh = 0;

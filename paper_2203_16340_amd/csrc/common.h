@@ -784,9 +784,9 @@ void launch_sym(const Dims& dm, const Geometry& ge, const Buffers& bf, const APa
                 hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
 void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
-// reopen: behind a convergence that is to be confirmed; launch_reopen's work is done here
+// reopen: behind a convergence that is to be confirmed; launch_reopen's work is done here, and nothing at all once *over (or null) is set
 void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* lin, const double* sign,
-                        hipStream_t st, bool reopen = false, int* host_flag = nullptr);   // lin, sign: QP only (linear term b, sign vector)
+                        hipStream_t st, bool reopen = false, int* host_flag = nullptr, const int* over = nullptr);   // lin, sign: QP only (linear term b, sign vector)
 // no_close (see gram_can_skip_close): the kernel ends when its records of partial sums are written; the direction kernel does
 // the rest (launch_dir with open_gram)
 void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int dbg_inputs,

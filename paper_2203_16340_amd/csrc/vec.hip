@@ -671,11 +671,12 @@ __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, in
                                                         Scal* __restrict__ scal, double* __restrict__ redpart,
                                                         const double* __restrict__ lin, const double* __restrict__ sign,
                                                         const double* __restrict__ wextra,
-                                                        const double* __restrict__ xres, int reopen, int* __restrict__ host_flag) {
+                                                        const double* __restrict__ xres, int reopen, int* __restrict__ host_flag,
+                                                        const int* __restrict__ over) {
     __shared__ double lds[kBlock];
     __shared__ double red[kWaves];
     __shared__ int flag;
-    if (!reopen && scal->status != LBFGSB_RUNNING) return;
+    if (reopen ? over && *over : scal->status != LBFGSB_RUNNING) return;
     const int tid = threadIdx.x;
     const bool shares = dm.kind != LBFGSB_OBJ_LSQ;
     const int nreg = shares ? ((int)gridDim.x < kRegBlocks ? (int)gridDim.x : kRegBlocks) : 1;
@@ -742,12 +743,12 @@ __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, in
 }
 
 void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* lin, const double* sign,
-                        hipStream_t st, bool reopen, int* host_flag) {
+                        hipStream_t st, bool reopen, int* host_flag, const int* over) {
     const bool qp = dm.kind == LBFGSB_OBJ_QP;
     hipLaunchKernelGGL(k_eval_finish, dim3(ge.fin_blocks), dim3(kBlock), 0, st, dm, qp ? 1 : ge.w_parts, ge.loss_parts,
                        qp ? (const double*)bf.row : (const double*)bf.wpart, bf.losspart, bf.x, bf.g, bf.scal, bf.redpart,
                        lin, sign, dm.n_extra > 0 ? (const double*)bf.wextra : nullptr,
-                       dm.n_extra > 0 ? (const double*)bf.xres : nullptr, reopen ? 1 : 0, host_flag);
+                       dm.n_extra > 0 ? (const double*)bf.xres : nullptr, reopen ? 1 : 0, host_flag, over);
 }
 
 // ---- quadratic objectives: closed-form Armijo search, then the update ---------------------------------------

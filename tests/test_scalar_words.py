@@ -26,17 +26,24 @@ READ_AND_WRITTEN = {
 }
 
 
+def bodies(text, pattern):
+    """(name, parameters, body) of the functions that `pattern` begins"""
+    text = re.sub(r"//[^\n]*|/\*.*?\*/", "", text, flags=re.S)
+    for at in re.finditer(pattern, text):
+        head = re.compile(r"\b(\w+)\s*\(").search(text, at.end())
+        while head.group(1) in ("__launch_bounds__", "__attribute__", "amdgpu_waves_per_eu"):
+            head = re.compile(r"\b(\w+)\s*\(").search(text, head.end())
+        begin = text.index("{", head.end())
+        depth, end = 1, begin + 1
+        while depth:
+            depth += {"{": 1, "}": -1}.get(text[end], 0)
+            end += 1
+        yield head.group(1), text[head.start():begin], text[begin:end]
+
+
 def kernels():
     for name in sorted(os.listdir(CSRC)):
-        text = re.sub(r"//[^\n]*|/\*.*?\*/", "", open(os.path.join(CSRC, name)).read(), flags=re.S)
-        for at in re.finditer(r"__global__", text):
-            head = re.compile(r"\b(k_\w+)\s*\(").search(text, at.end())
-            begin = text.index("{", head.end())
-            depth, end = 1, begin + 1
-            while depth:
-                depth += {"{": 1, "}": -1}.get(text[end], 0)
-                end += 1
-            yield head.group(1), text[head.start():begin], text[begin:end]
+        yield from bodies(open(os.path.join(CSRC, name)).read(), r"__global__")
 
 
 def words(signature, body):
@@ -77,3 +84,16 @@ def test_a_workgroup_agrees_whether_the_solver_is_parked():
     assert body[:parks].count("scal->status") == 1 and "const bool running = scal->status == LBFGSB_RUNNING;" in body[:parks]
     assert "if (!running && !(short_seq && blockIdx.x > 0)) return;" in body[:parks]
     assert "running ? 0.0 : NAN" in body[:parks] and "isfinite(df)" in body[:parks]
+
+
+def test_a_run_that_is_over_is_not_opened_again():
+    """The host goes on behind the last turn until it sees that the run is over: every way back to a running solver looks at the
+    device's own word for that first."""
+    by_name = {name: (signature, body) for name, signature, body in kernels()}
+    assert by_name["k_al_reopen"][1].index("state->done) return;") < by_name["k_al_reopen"][1].index("scal->status = LBFGSB_RUNNING")
+    signature, body = by_name["k_eval_finish"]
+    first = body.index("return;")
+    assert "over" in signature and "if (reopen ? over && *over :" in body[:first] and first < body.index("scal->status = LBFGSB_RUNNING")
+    turn = next(b for n, _, b in bodies(open(os.path.join(CSRC, "api.hip")).read(), r"\nvoid (?=enqueue_turn)") if n == "enqueue_turn")
+    assert "if (!own_test) hipLaunchKernelGGL(k_al_reopen" in turn and "enqueue_eval(s, 0, true, own_test, nullptr, &al->state->done)" in turn
+    assert by_name["k_al_turn"][1].index("state->done) return;") < by_name["k_al_turn"][1].index("retest_point")

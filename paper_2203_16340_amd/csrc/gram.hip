@@ -397,15 +397,16 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
                 request(ch, sa, nullptr);
                 short_fetch(ch);
             }
-            // ||y_new||^2, over fixed variables too, by the lanes that hold it
+            // ||y_new||^2, over fixed variables too, by the lanes that hold it (what lies past the vector may be anything: no factor of it)
 #pragma unroll
             for (int t = 0; t < KM; ++t) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const int64_t e = ch * 64 + 32 * h + pair_at;
                     if (4 * t + i4 == newest) {
-                        ynew = fma(e < n ? first[t][h].x : 0.0, first[t][h].x, ynew);
-                        ynew = fma(e + 1 < n ? first[t][h].y : 0.0, first[t][h].y, ynew);
+                        const double y0 = e < n ? first[t][h].x : 0.0, y1 = e + 1 < n ? first[t][h].y : 0.0;
+                        ynew = fma(y0, y0, ynew);
+                        ynew = fma(y1, y1, ynew);
                     }
                 }
             }

@@ -162,3 +162,30 @@ def test_resident_iterations(rows, cols, m):
         assert rel_err(s.x().cpu().numpy(), ref.x) <= 1e-8 and rel_err(s.g().cpu().numpy(), ref.g) <= 1e-7, it
     ref.close()
     s.close()
+
+
+@pytest.mark.parametrize("n", [1025, 1087, 16401])
+def test_what_lies_past_a_vector_does_not_count(n):
+    """Ring slots that hold no pair yet, infinities in them: the newest pair's ||y||^2 ends with its vector, so the pair is used and the
+    step is the same bit for bit."""
+    rng = np.random.default_rng(n)
+    A = to_dev(rng.standard_normal((300, n)))
+    b, zero = to_dev(rng.standard_normal(300)), torch.zeros(n, dtype=torch.float64, device="cuda")
+    out = []
+    for planted in (False, True):
+        s = L.Solver(L.OBJ_LSQ, A, b, zero, torch.full_like(zero, np.inf), 4, options=L.default_options(tol=0.0))
+        s.set_x(zero)
+        s.step(False)
+        if planted:
+            x = s.x().cpu().numpy()
+            j = int(np.abs(x).argmax())
+            space = s.workspace[:s.workspace.numel() // 8 * 8].view(torch.float64)
+            at = [k for k in (np.nonzero(space.cpu().numpy() == x[j])[0] - j) if np.array_equal(space[k:k + n].cpu().numpy(), x)]
+            y = int(at[-1]) + (4 * n + 31) // 32 * 32       # (x0 = 0: the first s is x itself; four slots of s, y begins behind them)
+            assert len(at) >= 2 and np.dot(space[y:y + n].cpu().numpy(), x) > 0 and not space[y + n:y + 4 * n].any()
+            space[y + n:y + 4 * n] = np.inf
+        info = s.step()
+        assert info.pairs_used == 1
+        out.append((s.x(), s.g()))
+        s.close()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])

@@ -1389,6 +1389,7 @@ struct AlTurn {
     int64_t n_eq, cols, ld;
     double ctol;
     int max_outer, retest, fevals;
+    int refuse;                // a subproblem whose f is not finite ends the run with an error
     int own_test;              // retest by this workgroup, from here on (k_retest)
     int64_t n;
     Opts op;
@@ -1489,8 +1490,8 @@ __global__ __launch_bounds__(kTurnThreads) void k_al_turn(AlTurn a) {
         a.scal->f = f_new;
         a.scal->fevals = a.fevals;
         if (a.total) *a.total = t[1];
-        if (!isfinite(f_new)) {
-            // (refused, as a start point whose f is not finite is)
+        if (a.refuse && !isfinite(f_new)) {
+            // (refused, as a start point whose f is not finite is; stacked rows: left to the line search, which fails there)
             a.state->done = a.state->nonfinite = 1;
             a.state->turned = 0;
             a.scal->status = LBFGSB_LINESEARCH_FAILED;
@@ -1581,6 +1582,7 @@ void enqueue_turn(lbfgsb_auglag* al, bool confirm) {
     a.n_eq = al->n_eq; a.cols = stacked ? s->dm.cols : s->dm.n; a.ld = al->c_ld;
     a.ctol = al->ao.ctol; a.max_outer = al->ao.max_outer; a.retest = confirm ? 1 : 0;
     a.fevals = stacked ? 0 : 1;        // (of a stacked subproblem's start this never counted)
+    a.refuse = stacked ? 0 : 1;
     a.own_test = own_test ? 1 : 0; a.n = s->dm.n; a.op = s->op; a.x = s->bf.x; a.l = s->bf.l; a.u = s->bf.u;
     a.d = al->d_c; a.lambda = al->lambda; a.beta = al->beta_c; a.omega = al->omega_c; a.res = (double*)al->res_c; a.coef = al->coef;
     a.total = s->dm.n_extra > 0 ? s->bf.xres + s->dm.n_extra : nullptr;

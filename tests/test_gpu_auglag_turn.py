@@ -148,3 +148,25 @@ def test_no_constraint_rows():
         x = al.x().cpu().numpy()
         assert np.abs(x - np.maximum(x - A.T @ (A @ x - b), 0.0)).max() <= 1e-8
         al.close()
+
+
+@pytest.mark.parametrize("n,n_eq", [(3, 1), (40, 2), (9000, 2)])
+@pytest.mark.parametrize("stacked", [True, False])
+def test_a_subproblem_that_is_not_finite(n, n_eq, stacked):
+    """Rows that cannot be met, from a penalty parameter that overflows f after some turns: with stacked rows the line search fails and
+    the run ends with what it has, with separate rows it is refused as a start point would be."""
+    rng = np.random.default_rng(n)
+    A, b, C, d = rng.standard_normal((4, n)), np.ones(4), np.ones((n_eq, n)), np.full(n_eq, 2.0 * n)
+    l, u = to_dev(np.zeros(n)), to_dev(np.ones(n))
+    opts = dict(options=L.default_options(tol=1e-6, max_iter=20), rho0=1e300)
+    if stacked:
+        al = L.Auglag(to_dev(np.vstack([A, C])), to_dev(np.concatenate([b, d])), n_eq, l, u, 4, **opts)
+        info = al.solve(u)
+        assert info.status == L.LINESEARCH_FAILED and 10 < info.outer < 40 and info.violation == n and np.isinf(info.L)
+        assert info.rho == 1e300 * 2.0 ** (info.outer - 1) and torch.equal(al.x(), u)
+    else:
+        al = L.AuglagRows(L.OBJ_LSQ, to_dev(A), to_dev(b), to_dev(C), to_dev(d), l, u, 4, **opts)
+        with pytest.raises(L.LbfgsbError) as e:
+            al.solve(u)
+        assert e.value.code == L.E_NONFINITE
+    al.close()

@@ -347,7 +347,8 @@ void lbfgsb_auglag_destroy(lbfgsb_auglag* al);
  * and the bytes of A one launch requests from memory (rows*cols*sizeof(element): each such
  * kernel reads A exactly once; the upper triangle only for a large symmetric matrix of kind QP).  The transport kinds have no such kernel: there the Gram kernel of the batched
  * two-loop recursion (the longest kernel of an iteration) is timed instead, from the m-th iteration after
- * lbfgsb_set_x on, when all m pairs are stored; the bytes are 41*n (x, g, l, u, the newest y, the mask; 25*n when
+ * lbfgsb_set_x on, when all m pairs are stored (where a step's update forms those sums on the way, the kernel is launched for the
+ * timing only, with the same result bit for bit); the bytes are 41*n (x, g, l, u, the newest y, the mask; 25*n when
  * all variables share the same bounds, which are then not streamed) plus 16*m per free variable (the pair vectors
  * are not read where a variable is fixed). */
 int lbfgsb_enable_apass_timing(lbfgsb_solver* s, int enable);

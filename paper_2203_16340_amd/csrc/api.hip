@@ -409,15 +409,15 @@ void enqueue_step(lbfgsb_solver* s) {
         // (the Gram kernel ends without its closing step, which the direction kernel does, and that kernel without its own: the
         // row-sum kernel, the first to need Algorithm 2's choice, makes it from the per-workgroup sums)
         const int open_gram = gram_can_skip_close(s->dm) ? 1 : 0;
-        if (!s->gram_ready || s->recorded) {
+        if (!s->gram_ready || s->timing || s->recorded) {   // (timed: the sums that the update has left, once more, the same bit for bit)
             TimedSlot ts(s, s->steps_since_set_x >= s->dm.m);
             launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, ts.e0, ts.e1, open_gram);
         }
         launch_dir(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream, nullptr, nullptr, 1, open_gram);
         const OtArgs oa = ot_args(s);
         launch_ot_sums(s->dm, s->ge, s->bf, oa, 0, 1, s->stream, s->ge.dir_blocks, s->op.eps, open_gram ? s->bf.scal_next : nullptr);
-        // (a launch of its own while the Gram kernel is being timed, and once steps were recorded into a graph)
-        s->gram_ready = may_leave_gram && !s->timing && !s->recorded;
+        // (a launch of its own once steps were recorded into a graph)
+        s->gram_ready = may_leave_gram && !s->recorded;
         if (s->gram_ready)
             launch_update_gram_gauss(s->dm, s->op, s->ge, s->bf, s->bf.psi, s->ge.ot_row_blocks + s->ge.ot_col_blocks, s->stream);
         else if (quad) launch_ot_update_gauss(s->dm, s->op, s->ge, s->bf, oa, s->stream);

@@ -96,7 +96,7 @@ def test_what_comes_between_two_steps():
         if k == 5:
             w.enable_apass_timing(0)
         w.step(False)
-    assert rel_err(w.x().cpu().numpy(), s.x().cpu().numpy()) <= 1e-10
+    assert torch.equal(w.x(), s.x()) and torch.equal(w.g(), s.g())
     f, g = s.dbg_fg(x0)[:2]
     for solver in (s, t, w):                             # (a hook, a run cut short, and a new start after either)
         solver.set_x(x0)
@@ -111,6 +111,23 @@ def test_what_comes_between_two_steps():
     for solver in (s, t, w):
         solver.close()
     ref.close()
+
+
+@pytest.mark.parametrize("rows,cols,m,uniform", [(2060, 65, 2, False), (2049, 64, 5, True), (130, 1009, 10, True), (1, 131073, 7, False)])
+def test_timing_does_not_change_the_iterates(rows, cols, m, uniform):
+    """The Gram kernel that is timed forms the sums that the update leaves, every number of pairs held."""
+    ref, s, _ = problem(rows, cols, m, uniform)
+    ref.close()
+    t = problem(rows, cols, m, uniform)[1]
+    t.enable_apass_timing(2)
+    for _ in range(m + 4):
+        s.step(False)
+        t.step(False)
+        assert torch.equal(s.x(), t.x()) and torch.equal(s.g(), t.g())
+    assert s.info().as_dict() == t.info().as_dict()
+    assert t.apass_timing()[0] > 0
+    s.close()
+    t.close()
 
 
 def test_refreshes():

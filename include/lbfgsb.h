@@ -188,8 +188,8 @@ int lbfgsb_set_x(lbfgsb_solver* s, const double* x0);
  * only (no memset, copy or wait), so a run of such calls may be recorded into a HIP graph on the solver's
  * stream; whether a step also recomputes residual and gradient (refresh_every) is decided on the host when
  * the call is made, so a recorded run replays the pattern it was recorded with (use refresh_every = 0, or
- * record a multiple of it).  Replays leave what as many eager steps leave (quadratic forms and Gaussian transports of 2^17 and more
- * variables: to rounding).  Not while lbfgsb_enable_apass_timing is on: timed launches carry events. */
+ * record a multiple of it).  Replays leave what as many eager steps leave, bit for bit.  Not while lbfgsb_enable_apass_timing
+ * is on: timed launches carry events. */
 int lbfgsb_step(lbfgsb_solver* s, lbfgsb_info* info_host);
 /* (For the quadratic kinds the gradient is carried by recurrence between the periodic recomputations.  lbfgsb_solve
  * and the resident organisation re-evaluate it from x before they report LBFGSB_CONVERGED; a loop of lbfgsb_step

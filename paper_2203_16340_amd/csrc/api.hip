@@ -78,7 +78,8 @@ struct lbfgsb_solver {
     unsigned steps_enqueued = 0, note_at = 0;
     // the last launch that touched x, g or the pairs has left the next Gram kernel's records (launch_update_gram_gauss, _form)
     bool gram_ready = false;
-    // a graph may hold steps of this solver: its replays move the state unseen, so no records are left for a next step any more
+    // a graph may hold steps of this solver: its replays move the state unseen, so whether there are records is asked on the device
+    // from then on (Scal::gram_left), by a launch that returns at once where there are
     bool recorded = false;
     int steps_since_refresh;
     long long steps_since_set_x;
@@ -411,13 +412,13 @@ void enqueue_step(lbfgsb_solver* s) {
         const int open_gram = gram_can_skip_close(s->dm) ? 1 : 0;
         if (!s->gram_ready || s->timing || s->recorded) {   // (timed: the sums that the update has left, once more, the same bit for bit)
             TimedSlot ts(s, s->steps_since_set_x >= s->dm.m);
-            launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, ts.e0, ts.e1, open_gram);
+            launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, ts.e0, ts.e1,
+                        !open_gram ? kGramClose : (s->timing ? kGramOpen : kGramOpenUnlessLeft));
         }
         launch_dir(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream, nullptr, nullptr, 1, open_gram);
         const OtArgs oa = ot_args(s);
         launch_ot_sums(s->dm, s->ge, s->bf, oa, 0, 1, s->stream, s->ge.dir_blocks, s->op.eps, open_gram ? s->bf.scal_next : nullptr);
-        // (a launch of its own once steps were recorded into a graph)
-        s->gram_ready = may_leave_gram && !s->recorded;
+        s->gram_ready = may_leave_gram;
         if (s->gram_ready)
             launch_update_gram_gauss(s->dm, s->op, s->ge, s->bf, s->bf.psi, s->ge.ot_row_blocks + s->ge.ot_col_blocks, s->stream);
         else if (quad) launch_ot_update_gauss(s->dm, s->op, s->ge, s->bf, oa, s->stream);
@@ -440,15 +441,14 @@ void enqueue_step(lbfgsb_solver* s) {
     // kernel's workgroups to add its partial sums themselves: they finish its work on private copies of the scalar
     // block, and the pass moves workgroup 0's copy into place (Buffers::scal_next)
     const bool open_gram = defer && gram_can_skip_close(s->dm);
-    // ... and the quadratic form's update leaves the next step's records itself, no Gram kernel at all (not once steps were
-    // recorded into a graph)
-    const bool update_gram = open_gram && may_leave_gram && !s->recorded;
-    const bool ready = update_gram && s->gram_ready;
+    // ... and the quadratic form's update leaves the next step's records itself, no Gram kernel at all
+    const bool update_gram = open_gram && may_leave_gram;
+    const bool ready = update_gram && s->gram_ready && !s->recorded;
     s->gram_ready = false;
     if (small) {
         launch_small_step(s->dm, s->op, s->bf, fold_rows, s->obj.extra_weight, s->stream);
     } else {
-        if (!ready) launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, nullptr, nullptr, open_gram ? 1 : 0);
+        if (!ready) launch_gram(s->dm, s->op, s->ge, s->bf, 0, 1, s->stream, nullptr, nullptr, open_gram ? kGramOpenUnlessLeft : kGramClose);
         launch_dir(s->dm, s->op, s->ge, s->bf, 0, 0, s->stream, fold_rows, s->obj.extra_weight, defer ? 1 : 0,
                    open_gram ? 1 : 0);
     }

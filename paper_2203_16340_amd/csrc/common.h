@@ -45,6 +45,7 @@ struct Scal {
     // applied by the last workgroup of the next Gram kernel, or by k_commit
     int pend_valid, pend_ok, pend_bt;
     int spec_ok;            // logistic: the accepted step is the first trial step, whose X^T psi the single-read pass already holds
+    int gram_left;          // the last update has left the Gram kernel's records of the point it reached (launch_update_gram_*), and no evaluation has changed g since
     double pend_alpha, pend_f;
     long long iters;
     long long fevals;
@@ -788,9 +789,10 @@ void launch_fill_zero(void* p, size_t bytes, hipStream_t st);
 void launch_eval_finish(const Dims& dm, const Geometry& ge, const Buffers& bf, const double* lin, const double* sign,
                         hipStream_t st, bool reopen = false, int* host_flag = nullptr, const int* over = nullptr);   // lin, sign: QP only (linear term b, sign vector)
 // no_close (see gram_can_skip_close): the kernel ends when its records of partial sums are written; the direction kernel does
-// the rest (launch_dir with open_gram)
+// the rest (launch_dir with open_gram).  kGramOpenUnlessLeft: it returns at once where the last update has left them.
+enum { kGramClose = 0, kGramOpen = 1, kGramOpenUnlessLeft = 2 };
 void launch_gram(const Dims& dm, const Opts& op, const Geometry& ge, const Buffers& bf, int dbg_inputs,
-                 int evaluate_stop, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, int no_close = 0);
+                 int evaluate_stop, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, int no_close = kGramClose);
 bool gram_can_skip_close(const Dims& dm);
 // The update with the next iteration's Gram kernel in it (its records are then there: no launch_gram before that iteration's
 // direction kernel).  Gaussian transport, wt: omega . (K p), rows + cols entries; the quadratic form, folded rows as for

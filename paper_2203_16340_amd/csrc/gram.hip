@@ -255,7 +255,7 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // one load per wave fetches the integer header of the scalar block (status, ring position, pending
     // update); readlanes hand the fields to every lane
-    static_assert(offsetof(Scal, pend_ok) < 64, "header fields must sit in the first 16 ints");
+    static_assert(offsetof(Scal, pend_ok) < 64 && offsetof(Scal, gram_left) < 64, "header fields must sit in the first 16 ints");
     const int hdr = lane < 16 ? reinterpret_cast<const int*>(scal)[lane] : 0;
 
     const int64_t nchunks = (n + 63) / 64, stride = (int64_t)gridDim.x * NW;
@@ -323,6 +323,7 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
         }
         return;
     }
+    if (no_close == kGramOpenUnlessLeft && field(offsetof(Scal, gram_left))) return;
     int head = field(offsetof(Scal, head)), c = field(offsetof(Scal, count));
     if (field(offsetof(Scal, pend_valid))) {          // same rule as effective_ring()
         if (field(offsetof(Scal, pend_ok))) { head = ring_next(head, m); c = c < m ? c + 1 : m; }
@@ -604,13 +605,14 @@ void k_update_gram_gauss(Dims dm, Opts op, int loss_parts, const double* __restr
     else if constexpr (KM == 3) stream(std::integral_constant<int, 3>());
 
     gram_record<NW, kWaveLds, true>(pginf, ynew, nfixed, K, M, m, c, base_slot, slot_a, slot_b, dyn, red, grampart);
-    // (no workgroup of this kernel reads the pend_* fields)
+    // (no workgroup of this kernel reads the pend_* fields or gram_left)
     if (blockIdx.x == 0 && tid == 0) {
         scal->pend_ok = ok;
         scal->pend_bt = ls_bt;
         scal->pend_alpha = alpha;
         scal->pend_f = f_old + alpha * (gp + 0.5 * alpha * tt);
         scal->pend_valid = 1;
+        scal->gram_left = 1;
     }
     reduce_partials<NT, false>(grampart, gram_entries(m), scal, &flag, nullptr, true, GramPlaces{m, c, base_slot});
 }
@@ -728,13 +730,14 @@ void k_update_gram_form(Dims dm, Opts op, int loss_parts, const double* __restri
     }
     tile_results<KM>(sum, dyn + wave * kWaveLds);
     gram_record<NW, kWaveLds, false>(pginf, ynew, nfixed, KM, M, m, 0, 0, slot_a, slot_b, dyn, red, grampart);
-    // (no workgroup of this kernel reads the pend_* fields)
+    // (no workgroup of this kernel reads the pend_* fields or gram_left)
     if (blockIdx.x == 0 && tid == 0) {
         scal->pend_ok = ok;
         scal->pend_bt = ls_bt;
         scal->pend_alpha = alpha;
         scal->pend_f = f_old + alpha * (gp + 0.5 * alpha * tt);
         scal->pend_valid = 1;
+        scal->gram_left = 1;
     }
 }
 

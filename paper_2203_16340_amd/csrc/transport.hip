@@ -255,6 +255,7 @@ __global__ __launch_bounds__(NT) void k_ot_eval_finish(Dims dm, OtArgs a, int lo
         if (tid == 0) {
             scal->f = f;
             scal->fevals += 1;
+            scal->gram_left = 0;
         }
     }
     const OtPlace<NT, R, SHORT> at(lanes_log2);

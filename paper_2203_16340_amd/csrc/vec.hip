@@ -739,6 +739,7 @@ __global__ __launch_bounds__(kBlock) void k_eval_finish(Dims dm, int w_parts, in
         }
         scal->f = f;
         scal->fevals += 1;
+        scal->gram_left = 0;
     }
 }
 

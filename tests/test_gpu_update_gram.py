@@ -141,14 +141,15 @@ def test_refreshes():
 
 
 @pytest.mark.parametrize("kind", ["transport", "form"])
-def test_graph_replays_between_eager_steps(kind):
-    """Replays move the state without the host's knowing: neither they nor a step after them may use sums that an earlier step
-    left.  Against a solver of eager steps only, whose sums run in another order (see the tolerance of test_quadratic_form)."""
+@pytest.mark.parametrize("refresh_every", [0, 1])
+def test_graph_replays_between_eager_steps(kind, refresh_every):
+    """Replays move the state without the host's knowing: whether the sums that an earlier step left are those of the present point is
+    known on the device alone.  Against a solver of eager steps only, bit for bit."""
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
         if kind == "transport":
-            ref, eager, x0 = problem(500, 300, 5, refresh_every=0)
-            _, rec, _ = problem(500, 300, 5, refresh_every=0)
+            ref, eager, x0 = problem(500, 300, 5, refresh_every=refresh_every)
+            _, rec, _ = problem(500, 300, 5, refresh_every=refresh_every)
             ref.close()
         else:
             gen = torch.Generator(device="cuda").manual_seed(5)
@@ -156,7 +157,7 @@ def test_graph_replays_between_eager_steps(kind):
             K = (V @ V.T / 1500 + torch.eye(1500, device="cuda")).contiguous()
             K, b = (0.5 * (K + K.T)).contiguous(), torch.randn(1500, generator=gen, device="cuda", dtype=torch.float64)
             x0, one = torch.zeros_like(b), torch.ones_like(b)
-            eager, rec = (L.Solver(L.OBJ_QP, K, b, -0.5 * one, 0.7 * one, 5, sign=one, options=L.default_options(tol=0.0, refresh_every=0))
+            eager, rec = (L.Solver(L.OBJ_QP, K, b, -0.5 * one, 0.7 * one, 5, sign=one, options=L.default_options(tol=0.0, refresh_every=refresh_every))
                           for _ in range(2))
             eager.set_x(x0)
         stream.synchronize()
@@ -176,15 +177,18 @@ def test_graph_replays_between_eager_steps(kind):
             while eager.info().iters < done:
                 eager.step(False)
             assert rec.info().iters == done
-            assert rel_err(rec.x().cpu().numpy(), eager.x().cpu().numpy()) <= 1e-9
+            assert torch.equal(rec.x(), eager.x()) and torch.equal(rec.g(), eager.g())
         rec.set_x(x0)
+        if refresh_every:
+            rec.step(False)                                 # (a first step evaluates nothing, those recorded all do)
         graph.replay()
-        assert rec.info().iters == 2
+        done = 2 + refresh_every
+        assert rec.info().iters == done
         rec.step(False)
         eager.set_x(x0)
-        for _ in range(3):
+        for _ in range(done + 1):
             eager.step(False)
-        assert rel_err(rec.x().cpu().numpy(), eager.x().cpu().numpy()) <= 1e-9
+        assert torch.equal(rec.x(), eager.x()) and torch.equal(rec.g(), eager.g())
         eager.close()
         rec.close()
 

@@ -782,10 +782,7 @@ struct Follower {
     int until_over(int* st) {
         volatile unsigned long long* seen = s->h_progress;
         for (;;) {
-            const unsigned rel = reporting - origin;
-            unsigned upto = rel;
-            if (rel <= limit && upto > limit) upto = limit;
-            while (s->steps_enqueued - origin < upto && steps < cap) {
+            while (s->steps_enqueued - origin < reporting - origin && steps < cap) {
                 enqueue_step(s);
                 ++steps;
                 if (s->steps_enqueued == s->note_at) s->note_at = next_report(s->note_at);

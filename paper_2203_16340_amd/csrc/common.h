@@ -335,6 +335,13 @@ __device__ __forceinline__ void apply_pending(Scal* s, int m, bool record = true
     }
 }
 
+// Eq. (ws): a variable outside the free set
+__device__ __forceinline__ bool fixed_at(double x, double g, double lo, double hi, double eps) {
+    const bool at_lower = (x <= lo + eps) && (g >= 0.0);
+    const bool at_upper = (x >= hi - eps) && (g <= 0.0);
+    return at_lower || at_upper;
+}
+
 __device__ __forceinline__ double clampd(double v, double lo, double hi) {
     return v < lo ? lo : (v > hi ? hi : v);
 }
@@ -550,7 +557,7 @@ __device__ __forceinline__ int retest_point(int64_t n, const Opts& op, const dou
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const bool in = i0 + k * NT < n;
-            const bool fixed = (xv[k] <= lo[k] + op.eps && gv[k] >= 0.0) || (xv[k] >= hi[k] - op.eps && gv[k] <= 0.0);
+            const bool fixed = fixed_at(xv[k], gv[k], lo[k], hi[k], op.eps);
             s[0] = in && !fixed ? fma(gv[k], gv[k], s[0]) : s[0];
             s[1] += in && fixed ? 1.0 : 0.0;
             most = in ? fmax(most, fabs(xv[k] - clampd(xv[k] - gv[k], lo[k], hi[k]))) : most;

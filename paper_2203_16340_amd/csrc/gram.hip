@@ -278,9 +278,7 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
         if constexpr (DBG) {
             fr = s.mk != 0;
         } else {
-            const bool at_lower = (s.x <= s.l + op.eps) && (s.g >= 0.0);
-            const bool at_upper = (s.x >= s.u - op.eps) && (s.g <= 0.0);
-            fr = !(at_lower || at_upper);
+            fr = !fixed_at(s.x, s.g, s.l, s.u, op.eps);
             mask[in ? e : n - 1] = (uint8_t)fr;       // (past the end: the last element's own value once more)
         }
         pginf = fmax(pginf, in ? fabs(s.x - clampd(s.x - s.g, s.l, s.u)) : 0.0);
@@ -434,7 +432,8 @@ void k_gram(int64_t n, int m, Opts op, const double* __restrict__ x, const doubl
 // fails changes nothing, and the next one starts from the gradient alone.  Rows of 64 columns at least: a chunk then crosses one row's
 // end at most.
 // n = 10^6, us, the update's kernel and k_gram / this: 1 pair 26 / 21.6, 4 32 / 27.7, 10 44.3 / 38.4.  (Two groups of tiles one after
-// the other and 32-bit offsets from scalar bases for the registers' sake: with 11 spilled the last figure was 41.)
+// the other and 32-bit offsets from scalar bases for the registers' sake: with 11 spilled the last figure was 41.  With room for 10
+// pairs all 256 are taken still and two are spilled, seven where bounds differ.)
 // SAME: every variable has the same bounds.
 __device__ __forceinline__ int64_t uniform64(int64_t v) {
     const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
@@ -505,9 +504,7 @@ void k_update_gram_gauss(Dims dm, Opts op, int loss_parts, const double* __restr
         const double lo = SAME ? op.lo : s.l[0], hi = SAME ? op.hi : s.l[SAME ? 0 : 1];
         const double xn = ok ? clampd(fma(alpha, s.p, s.x), lo, hi) : s.x;
         const double gn = s.g + y, sn = xn - s.x;
-        const bool at_lower = (xn <= lo + op.eps) && (gn >= 0.0);
-        const bool at_upper = (xn >= hi - op.eps) && (gn <= 0.0);
-        const bool fr = !(at_lower || at_upper);
+        const bool fr = !fixed_at(xn, gn, lo, hi, op.eps);
         if (in) {
             (mask + first)[(unsigned)lane] = (uint8_t)fr;
             if (ok) {
@@ -699,9 +696,7 @@ void k_update_gram_form(Dims dm, Opts op, int loss_parts, const double* __restri
         const double y = ok ? alpha * w : 0.0;
         const double xn = ok ? clampd(fma(alpha, branch == 1 ? pe1 : pe2, xe), le, ue) : xe;
         const double gn = ge + y, sn = xn - xe;
-        const bool at_lower = (xn <= le + op.eps) && (gn >= 0.0);
-        const bool at_upper = (xn >= ue - op.eps) && (gn <= 0.0);
-        const bool fr = !(at_lower || at_upper);
+        const bool fr = !fixed_at(xn, gn, le, ue, op.eps);
         if (in) {
             mask[e] = (uint8_t)fr;
             if (ok) { Sn[e] = sn; Yn[e] = y; x[e] = xn; g[e] = gn; }
@@ -781,9 +776,7 @@ void k_gram_blocks(int64_t n, int m, Opts op, const double* __restrict__ x, cons
         if constexpr (DBG) {
             fr = s.mk != 0;
         } else {
-            const bool at_lower = (s.x <= s.l + op.eps) && (s.g >= 0.0);
-            const bool at_upper = (s.x >= s.u - op.eps) && (s.g <= 0.0);
-            fr = !(at_lower || at_upper);
+            fr = !fixed_at(s.x, s.g, s.l, s.u, op.eps);
             mask[in ? e : n - 1] = (uint8_t)fr;       // (past the end: the last element's own value once more)
         }
         pginf = fmax(pginf, in ? fabs(s.x - clampd(s.x - s.g, s.l, s.u)) : 0.0);
@@ -1059,10 +1052,7 @@ void launch_update_gram_gauss(const Dims& dm, const Opts& op, const Geometry& ge
                        (const double*)bf.l, (const double*)bf.u, bf.x, bf.g, bf.S, bf.Y, bf.mask, bf.scal, bf.grampart);
 }
 
-// Applies a pending update when nothing else is about to (before an evaluation from scratch, and
-// before the host reads the scalars).  host_scal: where the host reads them, in pinned memory: written by this kernel,
-// one wave, instead of by a copy command behind it.
-// the scalar block into pinned host memory, by NT threads
+// The scalar block into pinned host memory, by NT threads.
 template <int NT>
 __device__ __forceinline__ void copy_scal(const Scal* scal, Scal* __restrict__ host_scal) {
     constexpr int kWords = (int)(sizeof(Scal) / 8);
@@ -1070,6 +1060,9 @@ __device__ __forceinline__ void copy_scal(const Scal* scal, Scal* __restrict__ h
     for (int k = threadIdx.x; k < kWords; k += NT)
         reinterpret_cast<uint64_t*>(host_scal)[k] = reinterpret_cast<const uint64_t*>(scal)[k];
 }
+// Applies a pending update when nothing else is about to (before an evaluation from scratch, and
+// before the host reads the scalars).  host_scal: where the host reads them, in pinned memory: written by this kernel,
+// one wave, instead of by a copy command behind it.
 __global__ __launch_bounds__(64) void k_commit(Scal* scal, int m, Scal* __restrict__ host_scal) {
     if (scal->status >= kStatusRefused) return;
     if (threadIdx.x == 0) apply_pending(scal, m);

@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(ResArgs a) {
         if (!want_eval) {
             // ---- Eq. (ws): free set; the epsilon-free KKT residual and the number of fixed variables
             if (wact) {
-                const bool fr = !(((xi <= li + op.eps) && (gi >= 0.0)) || ((xi >= ui - op.eps) && (gi <= 0.0)));
+                const bool fr = !fixed_at(xi, gi, li, ui, op.eps);
                 mi = (act && fr) ? 1.0 : 0.0;
                 if (act) msk[tid] = mi;
                 const double nf = (double)__popcll(__ballot(act && !fr));

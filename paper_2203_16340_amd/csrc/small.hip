@@ -122,9 +122,7 @@ __global__ __launch_bounds__(kSmallNT) void k_small_step(Dims dm, Opts op, const
     for (int r = 0; r < R; ++r) {
         const int e = tid + r * kSmallNT;
         const bool in = e < n;
-        const bool at_lower = (xe[r] <= le[r] + op.eps) && (ge[r] >= 0.0);
-        const bool at_upper = (xe[r] >= ue[r] - op.eps) && (ge[r] <= 0.0);
-        const bool fr = in && !(at_lower || at_upper);
+        const bool fr = in && !fixed_at(xe[r], ge[r], le[r], ue[r], op.eps);
         double yn = 0.0;
 #pragma unroll
         for (int k = 0; k < M; ++k) yn = k == newest ? vy[r][k] : yn;

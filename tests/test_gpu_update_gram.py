@@ -223,3 +223,75 @@ def test_quadratic_form(n, dtype, rows, m):
     assert (i.iters, i.n_fixed, i.branch, i.backtracks) == (j.iters, j.n_fixed, j.branch, j.backtracks) and i.iters == 10
     assert 0 < i.n_fixed < n
     assert rel_err(x, xr) <= 1e-9 and rel_err(g, gr) <= 1e-9
+
+
+def form(n, m, scale=1.0, refresh_every=32, **opts):
+    """Curvatures from 0.006 to 0.62 of `scale`."""
+    rng = np.random.default_rng(n)
+    V = rng.standard_normal((n, 6))
+    K = np.diag(0.6 * 10.0 ** rng.uniform(-2.0, 0.0, n)) + 0.35 * V @ V.T / n
+    K = np.ascontiguousarray(scale * 0.5 * (K + K.T))
+    b, l, u, x0 = rng.standard_normal(n), np.full(n, -0.5), np.full(n, 0.7), np.zeros(n)
+    ref = oracle.Solver(oracle.Objective(oracle.QP, K, b), l, u, x0, m, oracle.default_options(tol=0.0, **opts))
+    s = L.Solver(L.OBJ_QP, to_dev(K), to_dev(b), to_dev(l), to_dev(u), m, options=L.default_options(tol=0.0, refresh_every=refresh_every, **opts))
+    assert s.apass_name == "fused"
+    s.set_x(to_dev(x0))
+    return ref, s, to_dev(x0)
+
+
+@pytest.mark.parametrize("scale,c1,resets,fails", [(1.0, 0.55, 4, False), (2.0, 0.6, 1, True)])
+def test_searches_of_a_form_that_fail(scale, c1, resets, fails):
+    """Only the unit step may be taken: pairs are dropped, which leaves the sums of the gradient alone, or the run ends."""
+    ref, s, _ = form(2604, 4, scale, max_backtracks=0, armijo_c1=c1)
+    for _ in range(12):
+        ref.step()
+        s.step(False)
+        if s.info().status == L.RUNNING and (s.info().iters < ref.info.iters or ref.info.status != oracle.RUNNING):
+            s.step(False)                                   # (the oracle drops the pairs and tries again within one step)
+        i = s.info()
+        assert (i.status, i.iters, i.memory_resets) == (ref.info.status, ref.info.iters, ref.info.memory_resets)
+        assert rel_err(s.x().cpu().numpy(), ref.x) <= 1e-8
+    assert ref.info.memory_resets >= resets and (ref.info.status == oracle.LINESEARCH_FAILED) == fails
+    ref.close()
+    s.close()
+
+
+def test_what_comes_between_two_steps_of_a_form():
+    """As for the transport: looks at the state change nothing, evaluations, hooks and other start points make the sums old."""
+    ref, s, x0 = form(1302, 6)
+    t = form(1302, 6)[1]
+    for k in range(9):
+        s.step(False)
+        t.step()
+        t.history()
+        t.x()
+    assert torch.equal(s.x(), t.x()) and torch.equal(s.g(), t.g())
+    s.dbg_fg(x0 + 0.1)
+    s.set_x(x0)
+    t.set_x(x0 + 0.2)
+    t.step(False)
+    t.set_x(x0)
+    for _ in range(9):
+        ref.step()
+        for solver in (s, t):
+            solver.step(False)
+    check(ref, s)
+    assert torch.equal(s.x(), t.x())
+    with pytest.raises(L.LbfgsbError):                   # (a start point that is refused leaves everything as it was)
+        t.set_x(x0 + 1.0)
+    s.step(False)
+    t.step(False)
+    assert torch.equal(s.x(), t.x())
+    for solver in (s, t, ref):
+        solver.close()
+
+
+@pytest.mark.parametrize("refresh_every", [1, 3])
+def test_refreshes_of_a_form(refresh_every):
+    ref, s, _ = form(1302, 5, refresh_every=refresh_every)
+    for _ in range(11):
+        ref.step()
+        s.step(False)
+    check(ref, s)
+    ref.close()
+    s.close()

@@ -1848,12 +1848,12 @@ int lbfgsb_auglag_solve(lbfgsb_auglag* al, const double* x0, lbfgsb_auglag_info*
         }
         run.begin(0);
     }
+    HIP_TRY(read_scal(s));             // (waits for the steps behind the end, whatever it was)
+    HIP_TRY(hipGetLastError());
     if (end->nonfinite) {
         s->x_set = false;
         return fail(LBFGSB_E_NONFINITE, "the augmented Lagrangian is not finite at the iterate");
     }
-    HIP_TRY(read_scal(s));
-    HIP_TRY(hipGetLastError());
     if (info) {
         const AlState& e = *al->h_state;
         *info = lbfgsb_auglag_info{};

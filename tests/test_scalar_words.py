@@ -97,3 +97,12 @@ def test_a_run_that_is_over_is_not_opened_again():
     turn = next(b for n, _, b in bodies(open(os.path.join(CSRC, "api.hip")).read(), r"\nvoid (?=enqueue_turn)") if n == "enqueue_turn")
     assert "if (!own_test) hipLaunchKernelGGL(k_al_reopen" in turn and "enqueue_eval(s, 0, true, own_test, nullptr, &al->state->done)" in turn
     assert by_name["k_al_turn"][1].index("state->done) return;") < by_name["k_al_turn"][1].index("retest_point")
+
+
+def test_algorithm_4_returns_from_an_idle_device():
+    """lbfgsb_auglag_solve synchronises, a run that is refused on the way included: the steps behind its end still use the workspace, and
+    what the device has written for the host is whole when it is idle."""
+    solve = next(b for n, _, b in bodies(open(os.path.join(CSRC, "api.hip")).read(), r"\nint (?=lbfgsb_auglag_solve)") if n == "lbfgsb_auglag_solve")
+    assert solve.count("end->nonfinite") == 1
+    behind_the_loop = solve[solve.rindex("run.begin(0);"):]
+    assert behind_the_loop.index("HIP_TRY(read_scal(s));") < behind_the_loop.index("end->nonfinite")

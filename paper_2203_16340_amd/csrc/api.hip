@@ -88,6 +88,7 @@ struct lbfgsb_solver {
     bool timing;
     std::vector<hipEvent_t> ev0, ev1;
     int timed;
+    bool steps_only;         // nothing but lbfgsb_step since the records were discarded: a solver still running has timed no launch in vain
 };
 
 namespace {
@@ -566,6 +567,7 @@ int report_infeasible(lbfgsb_solver* s, const double* x0) {
 // trusted: x0 is the solver's own iterate, or has been checked by the caller: only f is checked for finiteness
 int set_x_impl(lbfgsb_solver* s, const double* x0, bool trusted) {
     volatile int* flag = s->h_flag;
+    if (s->timed > 0) s->steps_only = false;
     const bool one = !trusted && s->owns_h_scal && s->dm.n <= kStartOneMax && !s->timing;
     if (!trusted) {
         // nothing of the solver's state changes before this has been found to be all right
@@ -648,6 +650,7 @@ int setup_solver(lbfgsb_solver* s, int64_t n, int m, const lbfgsb_objective* obj
     s->x_set = s->gram_ready = false;
     s->timing = false;
     s->timed = 0;
+    s->steps_only = true;
     const Layout L = make_layout(s->dm, s->ge);
     *total = L.total;
     if (workspace_bytes < L.total)
@@ -809,6 +812,7 @@ struct Follower {
 
 // The stopping logic of lbfgsb_solve, for a solver whose arguments have been checked.
 int solve_impl(lbfgsb_solver* s, lbfgsb_info* info) {
+    s->steps_only = false;
     const bool quad = is_quadratic(s->dm.kind);
     const long long cap = 2ll * s->options.max_iter + 64;   // accepted iterations + memory-reset retries
     if (s->use_resident) {
@@ -1138,23 +1142,28 @@ int lbfgsb_enable_apass_timing(lbfgsb_solver* s, int enable) {
         }
     }
     s->timing = enable != 0;
-    if (enable == 2) s->timed = 0;
+    if (enable == 2) { s->timed = 0; s->steps_only = true; }
     return LBFGSB_OK;
 }
 
 int lbfgsb_apass_timing(lbfgsb_solver* s, int64_t* count, double* total_ms, double* bytes_per_pass) {
     if (!s || !count || !total_ms || !bytes_per_pass) return fail(LBFGSB_E_INVALID_ARG, "NULL argument");
-    HIP_TRY(hipStreamSynchronize(s->stream));
     // launches enqueued after the solver had stopped return at once without touching A: they are recognised
     // by their duration (below half of a typical long launch: the 90th percentile, so that a single launch
-    // stretched by a profiler or a clock ramp does not set the scale) and left out
+    // stretched by a profiler or a clock ramp does not set the scale) and left out.  Two stretched launches of ten, or passes
+    // of unlike length, can set it all the same, so a solver that is known to have had none (steps alone, and still running; the logistic
+    // objective's parked steps are in vain as well) is not judged that way: 2000 x 500 by two passes lost some of its 20 in 4 runs of 10.
+    int status = LBFGSB_MAX_ITER;
+    if (s->steps_only && s->x_set && s->dm.kind != LBFGSB_OBJ_LOGISTIC_L2)
+        HIP_TRY(hipMemcpyAsync(&status, &s->bf.scal->status, sizeof(int), hipMemcpyDeviceToHost, s->stream));
+    HIP_TRY(hipStreamSynchronize(s->stream));
     std::vector<float> dur((size_t)s->timed);
     for (int i = 0; i < s->timed; ++i) HIP_TRY(hipEventElapsedTime(&dur[(size_t)i], s->ev0[i], s->ev1[i]));
     float longest = 0.f;
     if (!dur.empty()) {
         std::vector<float> sorted(dur);
         std::sort(sorted.begin(), sorted.end());
-        longest = sorted[(size_t)((sorted.size() - 1) * 9 / 10)];
+        longest = status == LBFGSB_RUNNING ? 0.f : sorted[(size_t)((sorted.size() - 1) * 9 / 10)];
     }
     double tot = 0.0;
     int64_t n = 0;
@@ -1812,6 +1821,7 @@ int lbfgsb_auglag_solve(lbfgsb_auglag* al, const double* x0, lbfgsb_auglag_info*
     hipLaunchKernelGGL(k_al_begin, dim3(1), dim3(kTurnThreads), 0, al->stream, al->n_eq, al->ao.rho0, al->res_c, al->state);
     volatile AlState* end = al->h_state;
     end->done = 0;
+    s->steps_only = false;
     const bool quad = is_quadratic(s->dm.kind);
     Follower run(s);
     run.begin(0);

@@ -468,6 +468,24 @@ def test_timing_of_the_passes_over_the_matrix(a_pass, per_step):
     s.close()
 
 
+@pytest.mark.parametrize("a_pass,per_step", [(L.APASS_FUSED, 1), (L.APASS_TWO_PASS, 2)], ids=["fused", "two_pass"])
+def test_no_launch_of_a_running_solver_is_left_out(a_pass, per_step):
+    """Durations alone would: some of the two passes' launches take twice as long as the others in 4 of 10 new solvers."""
+    prob = workloads.config("C2", scale=0.1)
+    for _ in range(20):
+        s = _gpu_solver(prob, a_pass, tol=0.0, refresh_every=0)
+        s.enable_apass_timing(2)
+        for k in (4, 7):
+            for _ in range(k):
+                s.step(want_info=False)
+            count, total_ms, _ = s.apass_timing()
+            assert count == (4 if k == 4 else 11) * per_step and total_ms > 0.0
+        s.set_x(torch.from_numpy(prob.x0).to(DEV))    # (from here on a launch may have been in vain: by duration again)
+        s.step(want_info=False)
+        assert 0 < s.apass_timing()[0] <= 14 * per_step
+        s.close()
+
+
 def test_benchmark_line_has_the_agreed_fields():
     """One run of bench.py on the smallest configuration in a process of its own: exactly one JSON line on stdout with
     the fields the harness reads, the roofline object and the oracle timed beside it."""
